@@ -155,65 +155,4 @@ __global__ __launch_bounds__(64) void encode_kernel(
     }
 }
 
-// PQ encoding of displacements, one THREAD per point with the whole codebook in LDS (M * 256 * DS
-// floats, DS = D / M): all lanes walk the 256 codewords of a block together, so every codeword
-// is one broadcast LDS read, the running minimum stays in the lane (no cross-lane reduction), and
-// the arithmetic per (point, codeword) is the same sequence of fused multiply-adds as in
-// encode_kernel: the codes are identical.  Also the per-point constant t = 2<mu, r> + ||r||^2
-// of Eq. (6) and its nearest table entry, lowest index on ties.  E and MU are [n][D] fp32 (MU == NULL: codes only, the assignment step of the codebook training).
-// A workgroup encodes several batches of blockDim.x points (grid-stride).
-template <int DS>
-__global__ __launch_bounds__(1024) void pq_encode_kernel(
-    const float *__restrict__ E, const float *__restrict__ MU, int64_t n, int M,
-    const float *__restrict__ codebook, const float *__restrict__ const_table,
-    uint8_t *__restrict__ out_codes, uint8_t *__restrict__ out_byte, float *__restrict__ out_t)
-{
-    extern __shared__ __attribute__((aligned(16))) float cb[];   // M * 256 * DS
-    __shared__ float tab[256];
-    const int D = M * DS;
-    for (int i = threadIdx.x; i < M * 256 * DS; i += blockDim.x) cb[i] = codebook[i];
-    if (threadIdx.x < 256) tab[threadIdx.x] = const_table ? const_table[threadIdx.x] : 0.f;
-    __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        float tval = 0.f;
-        for (int m = 0; m < M; ++m) {
-            float ev[DS];
-#pragma unroll
-            for (int t = 0; t < DS; ++t) ev[t] = E[i * D + m * DS + t];
-            float bd = INFINITY;
-            int bj = 0;
-            const float *cwm = cb + m * 256 * DS;
-#pragma unroll 4
-            for (int j = 0; j < 256; ++j) {
-                float dd = 0.f;
-#pragma unroll
-                for (int t = 0; t < DS; ++t) {
-                    const float u = ev[t] - cwm[j * DS + t];
-                    dd = fmaf(u, u, dd);
-                }
-                if (dd < bd) { bd = dd; bj = j; }   // ascending j: lowest index on ties
-            }
-            out_codes[i * M + m] = (uint8_t)bj;
-            const float *cw = cwm + bj * DS;
-            if (MU) {
-#pragma unroll
-                for (int t = 0; t < DS; ++t) {
-                    const float rv = cw[t];
-                    tval = fmaf(2.f * MU[i * D + m * DS + t], rv, fmaf(rv, rv, tval));
-                }
-            }
-        }
-        if (out_t) out_t[i] = tval;
-        if (const_table) {
-            float bd = INFINITY;
-            int bj = 0;
-            for (int j = 0; j < 256; ++j) {
-                const float dd = fabsf(tval - tab[j]);
-                if (dd < bd) { bd = dd; bj = j; }
-            }
-            out_byte[i] = (uint8_t)bj;
-        }
-    }
-}
-
 }  // namespace ivf

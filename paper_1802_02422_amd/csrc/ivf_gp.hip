@@ -21,6 +21,7 @@
 #include "encode.hpp"
 #include "latency.hpp"
 #include "layout.hpp"
+#include "pq.hpp"
 #include "query.hpp"
 #include "scan.hpp"
 #include "train.hpp"
@@ -930,6 +931,36 @@ int coarse_topk_tiled(const float *centroids, int64_t K, int D, const float *x, 
 
 }  // namespace
 
+namespace {
+
+bool pq_width(int ds) { return ds == 4 || ds == 6 || ds == 8 || ds == 12 || ds == 16; }
+
+// Codes of n displacements (and, with MU, constants), for the block widths pq_width() names.
+template <int DS>
+int launch_pq_encode_ds(const float *E, const float *MU, int64_t n, int M, const float *codebook, const float *const_table,
+                        uint8_t *out_codes, uint8_t *out_byte, float *out_t, hipStream_t st)
+{
+    const int Mg = pq_per_group(M, PqRow<DS>::bytes), groups = (M + Mg - 1) / Mg;
+    if (MU && groups > 1) return fail(IVF_EINVAL, "the constants need all quantisers in one workgroup");
+    const int lds = Mg * PqRow<DS>::bytes;
+    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&pq_encode_kernel<DS>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    int64_t grid = (n + WAVE - 1) / WAVE;   // one workgroup of 16 wavefronts fits a compute unit
+    if (grid > 256) grid = 256;
+    pq_encode_kernel<DS><<<dim3((unsigned)grid, (unsigned)groups), dim3(1024), lds, st>>>(E, MU, n, M, Mg, codebook, const_table, out_codes, out_byte, out_t);
+    LAUNCHCHK("pq_encode_kernel");
+    return IVF_OK;
+}
+
+int launch_pq_encode(int ds, const float *E, const float *MU, int64_t n, int M, const float *codebook, const float *const_table,
+                     uint8_t *out_codes, uint8_t *out_byte, float *out_t, hipStream_t st)
+{
+    auto fn = ds == 4 ? &launch_pq_encode_ds<4> : ds == 6 ? &launch_pq_encode_ds<6> : ds == 8 ? &launch_pq_encode_ds<8>
+            : ds == 12 ? &launch_pq_encode_ds<12> : &launch_pq_encode_ds<16>;
+    return fn(E, MU, n, M, codebook, const_table, out_codes, out_byte, out_t, st);
+}
+
+}  // namespace
+
 extern "C" void ivf_assign_stats(int64_t *out)
 {
     out[0] = g_assign_short.load();
@@ -982,12 +1013,11 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
         g_err = keep;
         if (rc) return rc;
     }
-    // PQ codes by the thread-per-point kernel when the codebook fits LDS and D / M is one of the
-    // compiled block widths; else by the wavefront-per-point kernel, which does everything.
+    // PQ codes on the matrix units when the codebook fits LDS and D / M is one of the compiled
+    // block widths; else by the wavefront-per-point kernel, which does everything.
     const int ds = t->D / t->M;
     const size_t cb_bytes = (size_t)256 * t->D * sizeof(float);
-    const bool fast = t->pq_codebook && cb_bytes <= 140 * 1024 &&
-                      (ds == 4 || ds == 6 || ds == 8 || ds == 12 || ds == 16);
+    const bool fast = t->pq_codebook && cb_bytes <= 140 * 1024 && pq_width(ds);
     if (t->rotation && t->pq_codebook && !fast)
         return fail(IVF_EINVAL, "a rotation in front of the PQ needs D/M in {4, 6, 8, 12, 16} and a codebook that fits LDS");
     if (!fast) {
@@ -1010,10 +1040,6 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
             transpose_square_kernel<<<dim3((unsigned)((D * D + 255) / 256)), dim3(256), 0, st>>>(t->rotation, D, static_cast<float *>(rt.p));
             LAUNCHCHK("transpose_square_kernel");
         }
-        const void *fn = ds == 4 ? (const void *)&pq_encode_kernel<4> : ds == 6 ? (const void *)&pq_encode_kernel<6>
-                       : ds == 8 ? (const void *)&pq_encode_kernel<8> : ds == 12 ? (const void *)&pq_encode_kernel<12>
-                                                                                 : (const void *)&pq_encode_kernel<16>;
-        HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cb_bytes));
         float *muc = static_cast<float *>(mu.p);
         for (int64_t i0 = 0; i0 < n; i0 += chunk) {
             const int64_t m = n - i0 < chunk ? n - i0 : chunk;
@@ -1032,21 +1058,11 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
                 LAUNCHCHK("rotate_rows_kernel");
                 pe = static_cast<float *>(erot.p);
             }
-            int64_t grid = (m + 1023) / 1024;
-            if (grid > 512) grid = 512;
             uint8_t *oc = out_codes + i0 * t->M;
             uint8_t *ob = out_const_byte ? out_const_byte + i0 : nullptr;
             float *ot = out_const_t ? out_const_t + i0 : nullptr;
-#define IVF_PQ_LAUNCH(DSV)                                                                               \
-    pq_encode_kernel<DSV><<<dim3((unsigned)grid), dim3(1024), cb_bytes, st>>>(pe, muc, m, t->M, t->pq_codebook, \
-                                                                               t->const_table, oc, ob, ot)
-            if (ds == 4) IVF_PQ_LAUNCH(4);
-            else if (ds == 6) IVF_PQ_LAUNCH(6);
-            else if (ds == 8) IVF_PQ_LAUNCH(8);
-            else if (ds == 12) IVF_PQ_LAUNCH(12);
-            else IVF_PQ_LAUNCH(16);
-#undef IVF_PQ_LAUNCH
-            LAUNCHCHK("pq_encode_kernel");
+            int r2 = launch_pq_encode(ds, pe, muc, m, t->M, t->pq_codebook, t->const_table, oc, ob, ot, st);
+            if (r2) return r2;
         }
         HIPCHK(hipStreamSynchronize(st));
         return IVF_OK;

@@ -1,0 +1,331 @@
+// Nearest codeword of every block of a displacement (Section 2: product quantiser), the per-point constant of
+// Eq. (6), and the sums of the codebook training.
+//
+// The nearest codeword is decided on the matrix units, with a proof per decision.  <x, c> - |c|^2 / 2 is formed for
+// all 256 codewords as fp16 products of operands split into a high and a low half (22 bits, accumulated in fp32); a
+// point whose best value leads the second best by more than twice the error bound has its answer, the others (about
+// one in a thousand) are decided by the whole wavefront with the chain of fused multiply-adds over the differences
+// that defines the result.  The codes are therefore those of that chain, the lowest index on ties.
+#pragma once
+#include "coarse.hpp"
+
+namespace ivf {
+
+// A codeword of DS components in LDS: CH pieces of 8 fp16 (high halves) and CH of 8 (low halves).  -|c|^2 / 2 takes
+// two more slots (high and low): those the last piece has left over, or a word of its own.
+template <int DS>
+struct PqRow {
+    static constexpr int CH = (DS + 7) / 8;
+    static constexpr int LAST = DS - 8 * (CH - 1);        // components in the last piece
+    static constexpr bool ROOM = LAST <= 6;
+    static constexpr int GROUP = DS == 4 ? 4 : DS <= 8 ? 2 : 1;   // quantisers whose components are loaded together
+    static constexpr int bytes = 256 * (32 * CH + (ROOM ? 0 : 4));   // of a quantiser in LDS
+};
+
+constexpr int PQ_LDS_MAX = 150 * 1024;
+
+// quantisers of one workgroup (their codewords stay in LDS): all of them, or a multiple of 4
+inline int pq_per_group(int M, int quantiser_bytes)
+{
+    const int g = PQ_LDS_MAX / quantiser_bytes;
+    return M <= g ? M : g & ~3;
+}
+
+// E and MU are [n][M * DS] fp32 (MU == NULL: codes only); grid (workgroups, groups of Mg quantisers; one group when MU
+// is given).  Also t = 2<mu, r> + ||r||^2 of Eq. (6), a chain over the components in order, and its nearest entry
+// of const_table, the lowest index on ties.
+//
+// A wavefront takes 64 points as two blocks of 32: v_mfma_f32_32x32x16_f16 with 32 codewords as the rows and 32 points
+// as the columns.  Lane half 0 feeds the high halves of its point's 8 components and half 1 the low halves, against
+// the codeword's high halves in both lane halves, then against its low halves: two products a piece of 8
+// components, and the points' operands are built once for all 256 codewords.  What is left on the vector units
+// is three instructions a value (value index into the low 4 bits, second largest, largest), which is what bounds the
+// kernel: 192 cycles a tile of 32 x 32 against 64 of the matrix units.  10^6 points x 96 components, 16 quantisers:
+// 0.58 ms (1.48 ms with a thread a point that walks all codewords in LDS, 15 instructions a codeword and quantiser).
+template <int DS>
+__global__ __launch_bounds__(1024) void pq_encode_kernel(
+    const float *__restrict__ E, const float *__restrict__ MU, int64_t n, int M, int Mg,
+    const float *__restrict__ codebook, const float *__restrict__ const_table,
+    uint8_t *__restrict__ out_codes, uint8_t *__restrict__ out_byte, float *__restrict__ out_t)
+{
+    typedef PqRow<DS> R;
+    constexpr int CH = R::CH, G = R::GROUP;
+    extern __shared__ __attribute__((aligned(16))) unsigned char pq_lds[];
+    __shared__ float tab[256];
+    __shared__ float cmax_s[64];                           // largest |c'|^2 of a quantiser (scaled), NaN: decide by the chain
+    __shared__ int kexp_s[64];                              // exponent of its largest component
+    __shared__ int tab_sorted;
+    gu32x4 *rows = reinterpret_cast<gu32x4 *>(pq_lds);      // [Mg][CH][high, low][256]
+    uint32_t *norms = reinterpret_cast<uint32_t *>(rows + (size_t)Mg * CH * 512);   // [Mg][256], only without ROOM
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    const int D = M * DS;
+    const int m0 = blockIdx.y * Mg, mn = M - m0 < Mg ? M - m0 : Mg;
+
+    if (tid == 0) tab_sorted = 1;
+    if (tid < 256) tab[tid] = const_table ? const_table[tid] : 0.f;
+    __syncthreads();
+    if (const_table && tid < 255 && !(tab[tid] <= tab[tid + 1])) tab_sorted = 0;
+    for (int m = wave; m < mn; m += 16) {                   // a wavefront packs a quantiser, four codewords a lane
+        const float *cb = codebook + (int64_t)(m0 + m) * 256 * DS;
+        float big = 0.f;
+        bool odd = false;                                   // an infinity or not a number among them
+        for (int j = lane; j < 256 * DS; j += WAVE) {
+            const float v = fabsf(cb[j]);
+            big = fmaxf(big, v);
+            odd = odd || !(v < INFINITY);
+        }
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) big = fmaxf(big, __shfl_xor(big, o, WAVE));
+        const int ec = __builtin_amdgcn_frexp_expf(big);    // components scaled to below 2^6
+        float cm = 0.f;
+#pragma unroll 1
+        for (int j = lane; j < 256; j += WAVE) {
+            float n2 = 0.f;
+            _Float16 hi[CH * 8], lo[CH * 8];
+#pragma unroll
+            for (int t = 0; t < CH * 8; ++t) {
+                const float v = t < DS ? __builtin_amdgcn_ldexpf(cb[j * DS + t], 6 - ec) : 0.f;
+                n2 = fmaf(v, v, n2);
+                hi[t] = (_Float16)v;
+                lo[t] = (_Float16)(v - (float)hi[t]);
+            }
+            cm = fmaxf(cm, n2);
+            const float nh = -0.5f * n2;                     // |c'|^2 / 2 <= 16 * 2^12 / 2: inside fp16's range
+            const _Float16 nhi = (_Float16)nh, nlo = (_Float16)(nh - (float)nhi);
+            if (R::ROOM) {
+                hi[CH * 8 - 2] = nhi;
+                hi[CH * 8 - 1] = nlo;
+            } else {
+                typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+                const halfx2 p = {nhi, nlo};
+                norms[m * 256 + j] = __builtin_bit_cast(uint32_t, p);
+            }
+#pragma unroll
+            for (int q = 0; q < CH; ++q) {
+                halfx8 a, b;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) { a[t] = hi[8 * q + t]; b[t] = lo[8 * q + t]; }
+                rows[((m * CH + q) * 2 + 0) * 256 + j] = __builtin_bit_cast(gu32x4, a);
+                rows[((m * CH + q) * 2 + 1) * 256 + j] = __builtin_bit_cast(gu32x4, b);
+            }
+        }
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) cm = fmaxf(cm, __shfl_xor(cm, o, WAVE));
+        if (__any(odd) || ec < -40 || ec > 55) cm = NAN;     // the chain's own under- and overflows decide there
+        if (lane == 0) {
+            cmax_s[m] = cm;
+            kexp_s[m] = ec;
+        }
+    }
+    __syncthreads();
+    const bool sorted = tab_sorted != 0;
+    const bool words = (M & 3) == 0 && (Mg & 3) == 0 && (reinterpret_cast<uintptr_t>(out_codes) & 3) == 0;
+
+    // a wavefront's batches of 64 points, dealt so that few points spread over the workgroups
+    for (int64_t b0 = ((int64_t)wave * gridDim.x + blockIdx.x) * WAVE; b0 < n; b0 += (int64_t)16 * gridDim.x * WAVE) {
+        const int64_t own = b0 + lane;                       // the point this lane writes
+        const int64_t i0 = b0 + l32 < n ? b0 + l32 : n - 1, i1 = b0 + 32 + l32 < n ? b0 + 32 + l32 : n - 1;
+        float tval = 0.f;
+        uint32_t word = 0;
+        for (int mg = 0; mg < mn; mg += G) {
+            float x[2][G * DS];                               // both blocks' points (the last group may reach back)
+            const int ml = mg + G <= mn ? mg : (mn - G > 0 ? mn - G : 0);
+#pragma unroll
+            for (int t = 0; t < G * DS; ++t) {
+                const int64_t at = (m0 + ml) * DS + t < D ? (m0 + ml) * DS + t : D - 1;
+                x[0][t] = E[i0 * D + at];
+                x[1][t] = E[i1 * D + at];
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int m = ml + g;
+                if (m < mg || m >= mn) continue;             // (uniform)
+                const float cm = cmax_s[m];
+                const int ec = kexp_s[m];
+                halfx8 B[2][CH], Bn[2];
+                float band[2];
+                bool chain[2];
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const float *xv = &x[b][g * DS];
+                    float big = 0.f;
+#pragma unroll
+                    for (int t = 0; t < DS; ++t) big = fmaxf(big, fabsf(xv[t]));
+                    // scaled like the codewords by powers of two: components below 2^6 where the ratio of the two
+                    // scales, 2^dk, is one that fp16 holds beside the norms
+                    const int e = __builtin_amdgcn_frexp_expf(big);
+                    int dk = ec - e;
+                    chain[b] = dk < -20 || e > 55;            // (the halves would overflow, or the chain does)
+                    dk = dk < -14 ? -14 : dk > 8 ? 8 : dk;
+                    const int sh = 6 - ec + dk;
+                    float x2 = 0.f;
+                    _Float16 w[CH * 8];
+#pragma unroll
+                    for (int t = 0; t < CH * 8; ++t) {
+                        w[t] = (_Float16)0.f;
+                        if (t < DS) {
+                            const float v = __builtin_amdgcn_ldexpf(xv[t], sh);
+                            x2 = fmaf(v, v, x2);
+                            const _Float16 hi = (_Float16)v;
+                            w[t] = h ? (_Float16)(v - (float)hi) : hi;
+                        }
+                    }
+                    const _Float16 r = (_Float16)__builtin_amdgcn_ldexpf(1.f, dk);
+                    if (R::ROOM) {
+                        if (h == 0) w[CH * 8 - 2] = w[CH * 8 - 1] = r;
+                    }
+#pragma unroll
+                    for (int q = 0; q < CH; ++q)
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) B[b][q][t] = w[8 * q + t];
+                    if (!R::ROOM) {   // last product: half 0 high halves against low ones, half 1 the norm
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) Bn[b][t] = h ? (t < 2 ? r : (_Float16)0.f) : w[8 * (CH - 1) + t];
+                    }
+                    // Bound, in units of the products: halves of 22 bits on either side 2^-22 (X + C), the norm 2^-21 C,
+                    // fp32 accumulation 2^-21 (X + C), the chain's own roundings 18 * 2^-24 (X + C), the 4 bits an index
+                    // replaces 2^-19 (X + C): together below 2^-17 (X + C), X = |x|^2, C = the largest |c|^2; a leads b
+                    // truly if it leads by twice that here
+                    band[b] = 0x1p-16f * (__builtin_amdgcn_ldexpf(x2, -dk) + __builtin_amdgcn_ldexpf(cm, dk));
+                }
+                float v1[2] = {-INFINITY, -INFINITY}, v2[2] = {-INFINITY, -INFINITY};
+                int at[2] = {0, 0};
+                const gu32x4 *mrow = rows + (size_t)m * CH * 512;
+#pragma unroll 1
+                for (int tile = 0; tile < 8; ++tile) {
+                    floatx16 acc[2];
+                    gu32x4 a[CH][2];
+#pragma unroll
+                    for (int q = 0; q < CH; ++q) {
+                        a[q][0] = mrow[(q * 2 + 0) * 256 + tile * 32 + l32];
+                        a[q][1] = mrow[(q * 2 + 1) * 256 + tile * 32 + l32];
+                    }
+                    if (!R::ROOM) {
+                        const uint32_t nw = norms[m * 256 + tile * 32 + l32];
+                        a[CH - 1][1] = h ? gu32x4{nw, 0u, 0u, 0u} : a[CH - 1][1];
+                    }
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+#pragma unroll
+                    for (int q = 0; q < CH; ++q)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p)
+#pragma unroll
+                            for (int b = 0; b < 2; ++b)
+                                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                                    __builtin_bit_cast(halfx8, a[q][p]), (!R::ROOM && q == CH - 1 && p == 1) ? Bn[b] : B[b][q], acc[b], 0, 0, 0);
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const float before = v1[b];
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const float s = __uint_as_float((__float_as_uint(acc[b][v]) & ~15u) | (uint32_t)v);
+                            v2[b] = __builtin_amdgcn_fmed3f(v1[b], v2[b], s);
+                            // the larger (an instruction of its own: fmaxf first quiets both operands, two more)
+                            asm("v_max_f32 %0, %1, %2" : "=v"(v1[b]) : "v"(v1[b]), "v"(s));
+                        }
+                        at[b] = v1[b] != before ? tile : at[b];
+                    }
+                }
+                // the halves of the lanes hold the even and odd groups of four codewords: lane p < 32 takes point p
+                // of block 0, lane 32 + p point p of block 1
+                auto swap = [](uint32_t a, uint32_t b, uint32_t &lo, uint32_t &hi) {
+                    const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+                    lo = s[0];
+                    hi = s[1];
+                };
+                uint32_t u1, w1, u2, w2, ut, wt;
+                swap(__float_as_uint(v1[0]), __float_as_uint(v1[1]), u1, w1);
+                swap(__float_as_uint(v2[0]), __float_as_uint(v2[1]), u2, w2);
+                swap((uint32_t)at[0], (uint32_t)at[1], ut, wt);
+                const float a1 = __uint_as_float(u1), b1 = __uint_as_float(w1);
+                const bool upper = b1 > a1;
+                const float best = upper ? b1 : a1;
+                const float next = fmaxf(fminf(a1, b1), fmaxf(__uint_as_float(u2), __uint_as_float(w2)));
+                const uint32_t v = (upper ? w1 : u1) & 15u;
+                int code = (int)((upper ? wt : ut) * 32u + 8u * (v >> 2) + (upper ? 4u : 0u) + (v & 3u));
+                const bool sure = best - next > (h ? band[1] : band[0]) && !(h ? chain[1] : chain[0]) && best < INFINITY;
+                uint64_t open = __ballot(!sure && own < n);
+                if (open) {
+                    float xo[DS];
+#pragma unroll
+                    for (int t = 0; t < DS; ++t) xo[t] = h ? x[1][g * DS + t] : x[0][g * DS + t];
+                    while (open) {
+                        const int s = __builtin_ctzll(open);
+                        open &= open - 1;
+                        float xs[DS];
+#pragma unroll
+                        for (int t = 0; t < DS; ++t) xs[t] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(xo[t]), s));
+                        float bd = INFINITY;
+                        int bj = 0x7fffffff;
+#pragma nounroll
+                        for (int j = lane; j < 256; j += WAVE) {
+                            const float *cw = codebook + ((int64_t)(m0 + m) * 256 + j) * DS;
+                            float dd = 0.f;
+#pragma unroll
+                            for (int t = 0; t < DS; ++t) {
+                                const float u = xs[t] - cw[t];
+                                dd = fmaf(u, u, dd);
+                            }
+                            if (dd < bd) { bd = dd; bj = j; }
+                        }
+                        wave_argmin(bd, bj);
+                        if (lane == s) code = bj == 0x7fffffff ? 0 : bj;
+                    }
+                }
+                if (words) {                                  // four codes at a time
+                    word |= (uint32_t)code << (8 * (m & 3));
+                    if ((m & 3) == 3) {
+                        if (own < n) *reinterpret_cast<uint32_t *>(out_codes + own * M + m0 + m - 3) = word;
+                        word = 0;
+                    }
+                } else if (own < n) {
+                    out_codes[own * M + m0 + m] = (uint8_t)code;
+                }
+                if (MU && own < n) {
+                    const float *cw = codebook + ((int64_t)(m0 + m) * 256 + code) * DS, *mu = MU + own * D + (m0 + m) * DS;
+#pragma unroll
+                    for (int t = 0; t < DS; ++t) {
+                        const float rv = cw[t];
+                        tval = fmaf(2.f * mu[t], rv, fmaf(rv, rv, tval));
+                    }
+                }
+            }
+        }
+        if (own >= n) continue;
+        if (out_t) out_t[own] = tval;
+        if (const_table) {
+            int bj = 0;
+            if (sorted && tval == tval) {
+                // differences grow to both sides of the value's place: the nearest is one of its two neighbours, and
+                // the lowest index among equals lies at or before the left one
+                int lo = 0, hi = 256;                          // first entry >= tval
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (tab[mid] < tval) lo = mid + 1;
+                    else hi = mid;
+                }
+                const float dl = lo > 0 ? fabsf(tval - tab[lo - 1]) : INFINITY, dr = lo < 256 ? fabsf(tval - tab[lo]) : INFINITY;
+                bj = lo < 256 ? lo : 255;
+                if (lo > 0 && dl <= dr) {
+                    bj = lo - 1;
+                    while (bj > 0 && fabsf(tval - tab[bj - 1]) <= dl) --bj;
+                }
+                if (!(fminf(dl, dr) < INFINITY)) bj = 0;
+            } else {
+                float bd = INFINITY;
+                for (int j = 0; j < 256; ++j) {
+                    const float dd = fabsf(tval - tab[j]);
+                    if (dd < bd) { bd = dd; bj = j; }
+                }
+            }
+            out_byte[own] = (uint8_t)bj;
+        }
+    }
+}
+
+}  // namespace ivf

@@ -221,7 +221,7 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
     if (n < 256 || n >= (1ll << 31)) return fail(IVF_EINVAL, "n=%lld: need at least 256 training rows", (long long)n);
     if (iters < 0) return fail(IVF_EINVAL, "iters must be >= 0");
     const int ds = D / M;
-    if (!(ds == 4 || ds == 6 || ds == 8 || ds == 12 || ds == 16))
+    if (!pq_width(ds))
         return fail(IVF_EINVAL, "D/M=%d: the codeword assignment kernel is built for block widths 4, 6, 8, 12 and 16", ds);
     const size_t cb_bytes = (size_t)256 * D * sizeof(float);
     if (cb_bytes > 140 * 1024) return fail(IVF_EINVAL, "codebook of %zu bytes does not fit LDS", cb_bytes);
@@ -239,24 +239,10 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
         if ((r2 = rb.init(n))) return r2;
         HIPCHK(hipMalloc(&codes.p, (size_t)n * M));
         HIPCHK(hipMalloc(&off.p, 257 * sizeof(uint32_t)));
-        const void *fn = ds == 4 ? (const void *)&pq_encode_kernel<4> : ds == 6 ? (const void *)&pq_encode_kernel<6>
-                       : ds == 8 ? (const void *)&pq_encode_kernel<8> : ds == 12 ? (const void *)&pq_encode_kernel<12>
-                                                                                 : (const void *)&pq_encode_kernel<16>;
-        HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cb_bytes));
-        int64_t grid = (n + 1023) / 1024;
-        if (grid > 512) grid = 512;
         uint8_t *cd = static_cast<uint8_t *>(codes.p);
         for (int it = 0; it < iters; ++it) {
             // nearest codeword of every block of every row, by (distance, index)
-#define IVF_PQ_ASSIGN(DSV) \
-    pq_encode_kernel<DSV><<<dim3((unsigned)grid), dim3(1024), cb_bytes, st>>>(E, nullptr, n, M, codebook, nullptr, cd, nullptr, nullptr)
-            if (ds == 4) IVF_PQ_ASSIGN(4);
-            else if (ds == 6) IVF_PQ_ASSIGN(6);
-            else if (ds == 8) IVF_PQ_ASSIGN(8);
-            else if (ds == 12) IVF_PQ_ASSIGN(12);
-            else IVF_PQ_ASSIGN(16);
-#undef IVF_PQ_ASSIGN
-            LAUNCHCHK("pq_encode_kernel");
+            if ((r2 = launch_pq_encode(ds, E, nullptr, n, M, codebook, nullptr, cd, nullptr, nullptr, st))) return r2;
             for (int m = 0; m < M; ++m) {   // every codeword becomes the mean of the rows assigned to it
                 byte_column_kernel<<<dim3(grid_for(n)), dim3(256), 0, st>>>(cd, n, M, m, rb.keys_a());
                 LAUNCHCHK("byte_column_kernel");

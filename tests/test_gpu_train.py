@@ -201,3 +201,42 @@ def test_whole_construction_from_the_oracles_start(small):
     rep = parity.check_search(ix2, Q[:100], spec.nprobe, spec.prune_frac, spec.k, out)
     print(rep, flush=True)
     rep.assert_ok()
+
+
+@pytest.mark.parametrize("M,ds,n", [(16, 6, 64 * 256 * 16 + 33), (16, 8, 1), (8, 16, 4097), (8, 12, 63), (16, 4, 65), (8, 6, 1000)])
+@pytest.mark.parametrize("kind", ["gauss", "grid", "scales"])
+def test_codes_are_the_nearest_codewords(M, ds, n, kind):
+    """Codes of displacements against fp64 distances.  "grid": small whole numbers, where every distance is exact, so
+    that the lowest index of the many exact ties has to come out; else a code may be off the nearest by what the fp32
+    chain of differences can round, 2 (ds + 2) u (|x|^2 + |c|^2)."""
+    print("case: codes", M, ds, n, kind, flush=True)
+    rng = np.random.default_rng(M * ds + n)
+    D = M * ds
+    x = rng.standard_normal((n, D)).astype(np.float32)
+    cb = rng.standard_normal((M, 256, ds)).astype(np.float32)
+    if kind == "grid":
+        x, cb = np.round(x), np.round(cb)
+    if kind == "scales":   # points far smaller and far larger than the codewords, zeros, one block at another scale
+        x *= np.exp2(rng.integers(-30, 25, (n, 1))).astype(np.float32)
+        x[::5] = 0
+        cb[1] *= 1e-20
+    z = lambda *s, dt=np.float32: dev(np.zeros(s, dt))
+    desc = ivf.IndexDesc(z(2, D), dev(np.array([[1], [0]], np.int32)), z(2), z(2, 1), dev(cb), const_table=dev(np.linspace(-1, 1, 256, dtype=np.float32)))
+    _, _, codes, byte, t = ivf.ivf_encode(desc, dev(x), region_in=z(n, dt=np.int32), want_t=True)
+    codes, byte, t = codes.cpu().numpy(), byte.cpu().numpy(), t.cpu().numpy()
+    take = np.unique(np.linspace(0, n - 1, min(n, 5000)).astype(np.int64))
+    xs = x[take].astype(np.float64).reshape(-1, M, ds)
+    c64 = cb.astype(np.float64)
+    rec = np.zeros((len(take), M, ds))
+    for m in range(M):
+        d = ((xs[:, m, None] - c64[m][None]) ** 2).sum(-1)
+        got = codes[take, m]
+        if kind == "grid":
+            assert (got == d.argmin(1)).all()
+        room = 2 * (ds + 2) * parity.U * ((xs[:, m] ** 2).sum(-1) + (c64[m] ** 2).sum(-1).max())
+        assert (d[np.arange(len(take)), got] <= d.min(1) + room).all()
+        rec[:, m] = c64[m][got]
+    ref = (rec ** 2).sum((1, 2))                                # mu = 0
+    assert np.abs(t[take] - ref).max() <= 2 * D * parity.U * ref.max()
+    tab = np.linspace(-1, 1, 256, dtype=np.float32)
+    assert (byte[take] == np.abs(t[take][:, None] - tab[None]).argmin(1)).all()
