@@ -110,6 +110,16 @@ int check_trained(const ivf_index_desc *d)
 }
 
 // ------------------------------------------------------------ stage 1 driver
+int launch_absmax(const float *X, int64_t count, uint32_t *gmax, hipStream_t st)
+{
+    HIPCHK(hipMemsetAsync(gmax, 0, sizeof(uint32_t), st));
+    int64_t grid = (count + 1023) / 1024;
+    if (grid > 1024) grid = 1024;
+    absmax_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(X, count, gmax);
+    LAUNCHCHK("absmax_kernel");
+    return IVF_OK;
+}
+
 // Packs the rows of X for the GEMM (hi/lo fp16 stages, see split_rows_kernel) and writes their
 // squared norms and inverse scales.  gmax != NULL: one scale for the whole matrix (gmax is a
 // device word used for the reduction, inv receives one float); else one scale per row.
@@ -118,12 +128,8 @@ int pack_rows(const float *X, int64_t n, int D, uint32_t *gmax, _Float16 *P, flo
 {
     if (n <= 0) return IVF_OK;
     if (gmax) {
-        HIPCHK(hipMemsetAsync(gmax, 0, sizeof(uint32_t), st));
-        const int64_t count = n * D;
-        int64_t grid = (count + 255) / 256;
-        if (grid > 16384) grid = 16384;
-        absmax_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(X, count, gmax);
-        LAUNCHCHK("absmax_kernel");
+        int rc = launch_absmax(X, n * D, gmax, st);
+        if (rc) return rc;
     }
     split_rows_kernel<<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st>>>(X, n, D, gmax, P, norm, inv);
     LAUNCHCHK("split_rows_kernel");
@@ -957,6 +963,32 @@ int launch_pq_encode(int ds, const float *E, const float *MU, int64_t n, int M, 
     auto fn = ds == 4 ? &launch_pq_encode_ds<4> : ds == 6 ? &launch_pq_encode_ds<6> : ds == 8 ? &launch_pq_encode_ds<8>
             : ds == 12 ? &launch_pq_encode_ds<12> : &launch_pq_encode_ds<16>;
     return fn(E, MU, n, M, codebook, const_table, out_codes, out_byte, out_t, st);
+}
+
+// The codebook update from the codes: slices of sums and counts (scratch of pq_sum_slices(n) of them), then the means.
+// state: the largest magnitude of E, the flag of pq_means_kernel, and [M][256] counts that start at 0.
+int64_t pq_sum_slices(int64_t n) { return n >= 2048 * PQ_SUM_MAX_G ? PQ_SUM_MAX_G : (n + 2047) / 2048; }
+
+template <int DS>
+int launch_pq_means_ds(const float *E, int64_t n, int M, const uint8_t *codes, uint32_t *state, double *psum, uint32_t *pcnt,
+                       float *codebook, hipStream_t st)
+{
+    const int64_t G = pq_sum_slices(n), per = (n + G - 1) / G;
+    const int groups = (M + PqSums<DS>::MG - 1) / PqSums<DS>::MG;
+    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&pq_sums_kernel<DS>), hipFuncAttributeMaxDynamicSharedMemorySize, PqSums<DS>::lds));
+    pq_sums_kernel<DS><<<dim3((unsigned)G, (unsigned)groups), dim3(512), PqSums<DS>::lds, st>>>(E, n, M, codes, state, per, psum, pcnt, state + 2);
+    LAUNCHCHK("pq_sums_kernel");
+    pq_means_kernel<DS><<<dim3((unsigned)(M * 256 * DS / 64)), dim3(256), 0, st>>>(psum, pcnt, M, (int)G, state, state + 2, state + 1, codebook);
+    LAUNCHCHK("pq_means_kernel");
+    return IVF_OK;
+}
+
+int launch_pq_means(int ds, const float *E, int64_t n, int M, const uint8_t *codes, uint32_t *state, double *psum, uint32_t *pcnt,
+                    float *codebook, hipStream_t st)
+{
+    auto fn = ds == 4 ? &launch_pq_means_ds<4> : ds == 6 ? &launch_pq_means_ds<6> : ds == 8 ? &launch_pq_means_ds<8>
+            : ds == 12 ? &launch_pq_means_ds<12> : &launch_pq_means_ds<16>;
+    return fn(E, n, M, codes, state, psum, pcnt, codebook, st);
 }
 
 }  // namespace

@@ -227,23 +227,24 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
     if (cb_bytes > 140 * 1024) return fail(IVF_EINVAL, "codebook of %zu bytes does not fit LDS", cb_bytes);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     RadixBufs rb;
-    DevTmp codes, off;
-    auto body = [&]() -> int {
+    DevTmp codes, off, state, psum, pcnt;
+    uint32_t seen[2];                            // largest magnitude, flag
+    // all rounds, the means from fixed-point sums (exact unless the flag is raised) or from fp64 segment sums
+    auto rounds = [&](bool fixed) -> int {
         int r2;
+        uint8_t *cd = static_cast<uint8_t *>(codes.p);
+        uint32_t *sw = static_cast<uint32_t *>(state.p);
         for (int m = 0; m < M; ++m) {   // codeword j of block m starts as block m of row init_idx[j]
             take_rows_kernel<<<dim3(grid_for(256 * ds)), dim3(256), 0, st>>>(E, D, m * ds, ds, init_idx, 256,
                                                                               codebook + (size_t)m * 256 * ds, ds, 0);
             LAUNCHCHK("take_rows_kernel");
         }
-        if (iters == 0) return IVF_OK;
-        if ((r2 = rb.init(n))) return r2;
-        HIPCHK(hipMalloc(&codes.p, (size_t)n * M));
-        HIPCHK(hipMalloc(&off.p, 257 * sizeof(uint32_t)));
-        uint8_t *cd = static_cast<uint8_t *>(codes.p);
         for (int it = 0; it < iters; ++it) {
             // nearest codeword of every block of every row, by (distance, index)
             if ((r2 = launch_pq_encode(ds, E, nullptr, n, M, codebook, nullptr, cd, nullptr, nullptr, st))) return r2;
-            for (int m = 0; m < M; ++m) {   // every codeword becomes the mean of the rows assigned to it
+            // every codeword becomes the mean of the rows assigned to it
+            if (fixed && (r2 = launch_pq_means(ds, E, n, M, cd, sw, static_cast<double *>(psum.p), static_cast<uint32_t *>(pcnt.p), codebook, st))) return r2;
+            for (int m = 0; !fixed && m < M; ++m) {
                 byte_column_kernel<<<dim3(grid_for(n)), dim3(256), 0, st>>>(cd, n, M, m, rb.keys_a());
                 LAUNCHCHK("byte_column_kernel");
                 uint32_t *ks, *vs;
@@ -255,8 +256,27 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
                 LAUNCHCHK("segment_sum_kernel");
             }
         }
+        if (iters) HIPCHK(hipMemcpyAsync(seen, state.p, sizeof(seen), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         return IVF_OK;
+    };
+    auto body = [&]() -> int {
+        if (iters == 0) return rounds(true);
+        int r2;
+        const size_t state_words = 2 + (size_t)M * 256, words = (size_t)pq_sum_slices(n) * M * 256;
+        HIPCHK(hipMalloc(&codes.p, (size_t)n * M));
+        HIPCHK(hipMalloc(&state.p, state_words * sizeof(uint32_t)));
+        HIPCHK(hipMalloc(&psum.p, words * ds * sizeof(double)));
+        HIPCHK(hipMalloc(&pcnt.p, words * sizeof(uint32_t)));
+        fill_u64_kernel<<<dim3(grid_for(state_words / 2)), dim3(256), 0, st>>>(static_cast<unsigned long long *>(state.p), state_words / 2, 0ull);
+        LAUNCHCHK("fill_u64_kernel");
+        if ((r2 = launch_absmax(E, n * D, static_cast<uint32_t *>(state.p), st))) return r2;
+        if ((r2 = rounds(true))) return r2;
+        // (infinities and values that are not numbers have to find their way into the means: by the segment sums too)
+        if (seen[0] < 0x7F800000u && !seen[1]) return IVF_OK;
+        if ((r2 = rb.init(n))) return r2;
+        HIPCHK(hipMalloc(&off.p, 257 * sizeof(uint32_t)));
+        return rounds(false);
     };
     int rc = body();
     std::string keep = g_err;

@@ -240,3 +240,29 @@ def test_codes_are_the_nearest_codewords(M, ds, n, kind):
     assert np.abs(t[take] - ref).max() <= 2 * D * parity.U * ref.max()
     tab = np.linspace(-1, 1, 256, dtype=np.float32)
     assert (byte[take] == np.abs(t[take][:, None] - tab[None]).argmin(1)).all()
+
+
+@pytest.mark.parametrize("M,ds,n,small", [(8, 6, 256, 0), (16, 6, 8192 + 2049, 0), (3, 8, 20_000, 0), (8, 16, 5000, 0), (5, 12, 3000, 0),
+                                          (16, 4, 70_000, 20), (8, 6, 5000, 45), (8, 8, 5000, 100)])
+def test_codeword_means_of_one_round(M, ds, n, small):
+    """One round from well separated rows: every mean is the fp64 mean rounded once, also where half of the components are
+    2^-small of the others (below the exact range of the fixed-point sums the segment sums take over)."""
+    print("case: codeword means", M, ds, n, small, flush=True)
+    rng = np.random.default_rng(n + small)
+    D = M * ds
+    code = np.stack([np.concatenate([rng.permutation(256), rng.integers(0, 256, n - 256)]) for _ in range(M)], 1)
+    code[:256] = np.arange(256)[:, None]
+    centre = rng.permutation(2048)[:256].astype(np.float64)
+    E = np.zeros((n, M, ds))
+    E[:, :, 0] = centre[code]                              # apart by 1 at least
+    E += rng.uniform(-0.1, 0.1, E.shape)
+    E[:, :, 1::2] *= 2.0 ** -small
+    E = E.astype(np.float32).reshape(n, D)
+    got = ivf.ivf_pq_train(dev(E), M, 1, dev(np.arange(256, dtype=np.int64))).cpu().numpy()
+    for m in range(M):
+        x = E.reshape(n, M, ds)[:, m].astype(np.float64)
+        s, a, c = np.zeros((256, ds)), np.zeros((256, ds)), np.bincount(code[:, m], minlength=256)[:, None]
+        np.add.at(s, code[:, m], x)
+        np.add.at(a, code[:, m], np.abs(x))
+        # one rounding to fp32; n additions in fp64 on either side; what the flag lets pass, 2^-29 of the mean
+        assert (np.abs(got[m] - s / c) <= (2.0 ** -24 + 2.0 ** -28) * np.abs(s / c) + 2 * n * 2.0 ** -53 * a / c).all()
