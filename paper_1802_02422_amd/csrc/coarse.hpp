@@ -21,22 +21,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef uint32_t gu32x4 __attribute__((ext_vector_type(4)));
 
-// ||row||^2 of an [n][D] fp32 matrix, one wavefront per row.
-__global__ __launch_bounds__(256) void row_norm_kernel(const float *__restrict__ X, int64_t n,
-                                                       int D, float *__restrict__ out)
-{
-    int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    int lane = threadIdx.x & 63;
-    if (row >= n) return;
-    float s = 0.f;
-    for (int i = lane; i < D; i += WAVE) {
-        float v = X[row * D + i];
-        s = fmaf(v, v, s);
-    }
-    s = wave_sum(s);
-    if (lane == 0) out[row] = s;
-}
-
 // Largest magnitude of count floats, as the bit pattern of a non-negative float (those order like unsigned integers;
 // one that is not a number counts as larger than infinity); out must start at 0.  One atomic a workgroup: with
 // one a wavefront and 2^16 of them the reduction of a 25 MB table took 0.75 ms, all of it spent at that one address.
@@ -805,146 +789,225 @@ __global__ __launch_bounds__(256) void argmin_unpack_kernel(const unsigned long 
 }
 
 // ---- Nearest centroid through a certified shortlist ----
-// The hi halves alone give <q,c> to about 2^-10 of |q||c| at a third of the MFMA work.  With
-//   approx(q,c) = |q|^2 + |c|^2 - 2 <hi(q), hi(c)>  (fp32 accumulation),
-//   eps(q,c)    = 2^-9 (|q|^2 + |c|^2) + abs_term,
-// the exact squared distance d lies in [approx - eps, approx + eps]: an element of hi(x) differs from x
-// by at most 2^-11 |x_i| (fp16 rounding; below the normal range by at most 2^-39 of the largest
-// magnitude under the row's or table's scale, which abs_term covers), so the inner product is off by at
-// most (2^-10 + 2^-22) sum |q_i c_i| <= (2^-11 + 2^-23)(|q|^2 + |c|^2), the distance by twice that,
-// and the factor 2^-9 leaves as much again for the fp32 roundings of the accumulation and the epilogue.
-// U[q], the smallest approx + eps seen so far, never drops below the true minimum distance of q, so
-// every centroid that attains that minimum has approx - eps <= U[q] whenever it is looked at: the
-// kernel appends each (q, c) with approx - eps <= U[q] to a candidate list, and rerank_kernel decides
-// among the candidates with exact arithmetic.  Stale reads of U only lengthen the list.
+// The nearest centroid of q is the one with the largest G = <q,c> - |c|^2 / 2.  The hi halves alone, one product
+// per 16 dimensions instead of three, give it as g = <hq, hc> - |c|^2 / 2 with hq, hc the operands rounded to fp16
+// (one power-of-two scale for all rows, one for the table).  With dq = q - hq and dc = c - hc, whose lengths are
+// computed when the rows are packed,
+//   <q,c> - <hq,hc> = <dq, c> + <hq, dc>,  so  |g - G| <= |dq| |c| + (|q| + |dq|) |dc| + roundings,
+// the roundings of the accumulation and of the norms being below k (|q| |c| + |c|^2), k = (Dp + 32) 2^-24.  A tile of 128
+// centroids has the largest |c| and |dc| in it: e(q, tile) = |dq| cm + (|q| + |dq|) dcm + k |q| cm.  The |c|^2 part of
+// the bound goes into the product's start value: acc starts at -|c|^2 / 2 + k |c|^2, so that acc + e is an upper end
+// of G and acc - 2 k |c|^2 - e a lower end.  L[q], the largest lower end seen so far, never exceeds the true maximum:
+// every centroid that attains it has acc + e >= L[q] when it is looked at.  The kernel looks at the 16 centroids of a lane
+// together: if their largest acc + e reaches L[q] it appends (q, those of the 16 that do, that upper end) to a list.  When all
+// tiles have been seen, shortlist_pairs_kernel drops the entries whose upper end lies below L[q] by then (nearly all:
+// entries made before the bound was tight), looks at the centroids of the others one by one with the lengths of their
+// own instead of the tile's largest (rows of a table may lie many powers of two apart), which tightens L further, and
+// lists the pairs that are left; rerank_kernel decides among those with exact arithmetic.  Stale reads of L only lengthen
+// the lists.
 
-// Row r of the hi-only table from row r of the hi/lo table (split_rows_kernel; Dp dimensions, a multiple
-// of 32): per 32 dimensions the 16-byte chunks [k 0-7 | k 16-23 | k 8-15 | k 24-31], so that lane half h
-// of gemm_tile<true> finds its dimensions of the two 16-wide products in chunks 2h and 2h+1.
-__global__ __launch_bounds__(256) void pack_hi_kernel(const _Float16 *__restrict__ P, int64_t n_rows, int Dp,
-                                                      _Float16 *__restrict__ H)
+// Rows of X ([n][D] fp32) as fp16 in the layout of gemm_tile<true>: per 32 dimensions the 16-byte chunks [k 0-7 | k
+// 16-23 | k 8-15 | k 24-31], so that lane half h finds its dimensions of the two 16-wide products in chunks 2h and
+// 2h+1; zero beyond D and in the rows n .. n_pad-1.  Scaled by 2^(14 - floor(log2 m)), m the largest magnitude *gmax.
+// len[r] = (|row|, |row - packed row|) in scaled units, both rounded up (n_pad of them).  16 lanes per row, a chunk of 8 dimensions a
+// lane: whole 16-byte stores, 32-byte reads.
+__host__ __device__ inline int hi_scale(uint32_t gmax_bits)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // one 16-byte chunk of the output each
-    const int chunks = Dp / 8;
-    if (i >= n_rows * chunks) return;
-    const int64_t r = i / chunks;
-    const int ch = (int)(i % chunks), t = ch >> 2, slot = ch & 3;
-    const int k8 = (slot & 1) * 2 + (slot >> 1);               // which 8 dimensions of the 32: slots 0,1,2,3 -> 0,2,1,3
-    const int dim = 32 * t + 8 * k8;                            // first dimension of the chunk
-    // in the hi/lo table dimension d sits at stage d / 16: [hi k0..7 | lo k0..7 | hi k8..15 | lo k8..15]
-    const _Float16 *src = P + r * (int64_t)Dp * 2 + (dim >> 4) * 32 + ((dim >> 3) & 1) * 16;
-    *reinterpret_cast<gu32x4 *>(H + r * (int64_t)Dp + ch * 8) = *reinterpret_cast<const gu32x4 *>(src);
+    const int e = (int)(gmax_bits >> 23) - 127;             // (a subnormal or zero maximum: the clamp)
+    return gmax_bits >= 0x7F800000u ? 0 : 14 - (e < -62 ? -62 : e > 62 ? 62 : e);
 }
 
-constexpr float SHORTLIST_KAPPA = 0x1p-9f;
+__global__ __launch_bounds__(256) void pack_hi_rows_kernel(const float *__restrict__ X, int64_t n, int64_t n_pad, int D, int Dp,
+                                                           const uint32_t *__restrict__ gmax, _Float16 *__restrict__ H,
+                                                           float2 *__restrict__ len)
+{
+    const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int lane = threadIdx.x & 15;
+    if (row >= n_pad) return;
+    const int sh = hi_scale(*gmax);
+    float s2 = 0.f, d2 = 0.f;
+    for (int ch = lane; ch < Dp / 8; ch += 16) {
+        const int dim = 32 * (ch >> 2) + 8 * ((ch & 1) * 2 + ((ch & 3) >> 1));   // chunks 0,1,2,3 hold k 0, 16, 8, 24
+        halfx8 w;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (row < n && dim + 4 * u < D) v = *reinterpret_cast<const float4 *>(X + row * D + dim + 4 * u);   // (D is a multiple of 4)
+            const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float f = __builtin_amdgcn_ldexpf(e[t], sh);
+                const _Float16 hi = (_Float16)f;
+                const float d = f - (float)hi;
+                w[4 * u + t] = hi;
+                s2 = fmaf(f, f, s2);
+                d2 = fmaf(d, d, d2);
+            }
+        }
+        *reinterpret_cast<halfx8 *>(H + row * (int64_t)Dp + ch * 8) = w;
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+        s2 += __shfl_xor(s2, o, WAVE);
+        d2 += __shfl_xor(d2, o, WAVE);
+    }
+    if (lane == 0) len[row] = make_float2(sqrtf(s2) * (1.f + 0x1p-10f), sqrtf(d2) * (1.f + 0x1p-10f));
+}
+
+// Start values and bounds of the centroids for rows of scale *xmax: start[c] = (-1/2 + k) |c|^2 in units of the product,
+// -inf for c in [K, tiles * 128); tile[t] = (largest |c|, largest |dc|, smallest start value) of tile t, the lengths in
+// the table's units.
+__global__ __launch_bounds__(128) void shortlist_tiles_kernel(const float2 *__restrict__ clen, int64_t K, int Dp, const uint32_t *__restrict__ cmax,
+                                                              const uint32_t *__restrict__ xmax, float *__restrict__ start,
+                                                              float4 *__restrict__ tile)
+{
+    __shared__ float4 part[2];
+    const int64_t c = (int64_t)blockIdx.x * 128 + threadIdx.x;
+    float2 l = make_float2(0.f, 0.f);
+    float v = -INFINITY, low = INFINITY;
+    if (c < K) {
+        l = clen[c];
+        // (the length was rounded up by 2^-10: not into the start value, which has to be |c|^2 to k)
+        const float len0 = l.x * (1.f / (1.f + 0x1p-10f));
+        v = low = (-0.5f + (float)(Dp + 32) * 0x1p-24f) * __builtin_amdgcn_ldexpf(len0 * len0, hi_scale(*xmax) - hi_scale(*cmax));
+    }
+    start[c] = v;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        l.x = fmaxf(l.x, __shfl_xor(l.x, o, WAVE));
+        l.y = fmaxf(l.y, __shfl_xor(l.y, o, WAVE));
+        low = fminf(low, __shfl_xor(low, o, WAVE));
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float4(l.x, l.y, low, 0.f);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        tile[blockIdx.x] = make_float4(fmaxf(part[0].x, part[1].x), fmaxf(part[0].y, part[1].y), fminf(part[0].z, part[1].z), 0.f);
+}
+
 constexpr int SHORTLIST_SEGS = 64;
 
-// gmax_bits: the centroid table's largest magnitude (bit pattern), D: the dimension; abs_term =
-// 2^-30 (|q|^2 + D gmax^2) covers what lies below fp16's normal range under the table-wide scale.
-// U must be pre-filled with all ones, the segment counters with 0; pairs beyond a segment's capacity are
-// dropped (the caller compares the counters with seg_cap and falls back to the exact kernel).
-__global__ __launch_bounds__(256) void coarse_shortlist_kernel(
-    const _Float16 *__restrict__ Qh, const float *__restrict__ qn, const float *__restrict__ qsi, int64_t nq,
-    const _Float16 *__restrict__ Ch, const float *__restrict__ cn, const float *__restrict__ csi, int64_t K,
-    int Dph, int D, uint32_t *__restrict__ U, int2 *__restrict__ cand_all, unsigned long long *__restrict__ cand_count_all,
-    unsigned long long seg_cap, int tiles_q)
+// One entry of the list: query, first of the lane's 16 centroids, which of them (bit v: centroid c + 8 (v / 4) + v % 4),
+// the largest upper end.  A pair has a whole centroid.  The segments have a counter each (128 bytes apart), so that the
+// appends of different workgroups do not all queue at one address.  Entries beyond a segment's capacity are dropped (the
+// caller compares the counters with the capacity and falls back to the exact kernel).
+struct ShortEntry { int q, c; uint32_t which; float up; };
+struct ShortPair { int q, c; float up; };
+
+struct ShortlistArgs {
+    const _Float16 *Qh;          // packed rows
+    const float2 *qlen;          // their lengths
+    int64_t nq, K;
+    const _Float16 *Ch;          // packed centroids
+    const float *start;          // start values, whole tiles
+    const float4 *tile;          // per tile bounds
+    const float2 *clen;          // lengths of the centroids, whole tiles
+    int Dp;
+    uint32_t *L;                 // [nq] float_key of the largest lower end seen (starts at 0: below every key)
+    ShortEntry *list;
+    ShortPair *pairs;
+    unsigned long long *count, *pair_count;
+    unsigned long long seg_cap, pair_cap;
+    int tiles_q, tiles_c;
+};
+
+// (c: |c|, d: |dc|)
+__device__ __forceinline__ float shortlist_eps(float2 ql, float c, float d, int Dp)
 {
-    // the list is kept in SHORTLIST_SEGS segments with a counter each (128 bytes apart), so that the appends
-    // of different workgroups do not all queue at one address
-    int2 *cand = cand_all + (blockIdx.x % SHORTLIST_SEGS) * seg_cap;
-    unsigned long long *cand_count = cand_count_all + (blockIdx.x % SHORTLIST_SEGS) * 16;
-    const unsigned long long cand_cap = seg_cap;
+    return fmaf(ql.y, c, fmaf(ql.x + ql.y, d, (float)(Dp + 32) * 0x1p-24f * ql.x * c));
+}
+
+// The larger of a lane's value and that of the other lane half (the same query, the other 16 centroids).
+__device__ __forceinline__ float max_of_halves(float v)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+
+// Bit v: acc[v] reaches thr.
+__device__ __forceinline__ uint32_t reaching(const floatx16 &acc, float thr)
+{
+    uint32_t w = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) w |= (acc[v] >= thr ? 1u : 0u) << v;
+    return w;
+}
+
+// Lower end of G of the value top of a tile whose smallest start value is low (acc - 2 k |c|^2 - eps, and a start
+// value is (-1/2 + k) |c|^2).
+__device__ __forceinline__ float shortlist_lower(float top, float low, float eps, int Dp)
+{
+    const float k = (float)(Dp + 32) * 0x1p-24f, back = 2.f * k / (0.5f - k);
+    return fmaf(back, low, top) - eps;
+}
+
+// Any packed dimension: the tile loop of gemm_tile, one tile of 128 x 128 a workgroup.
+__global__ __launch_bounds__(256) void coarse_shortlist_kernel(ShortlistArgs a)
+{
+    ShortEntry *list = a.list + (blockIdx.x % SHORTLIST_SEGS) * a.seg_cap;
+    unsigned long long *count = a.count + (blockIdx.x % SHORTLIST_SEGS) * 16;
     __shared__ __attribute__((aligned(16))) float ops0[DBUF];
     __shared__ __attribute__((aligned(16))) float ops1[DBUF];
     __shared__ __attribute__((aligned(16))) float cns[GT];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int64_t q0, c0;
-    if (!tile_of_block(blockIdx.x, tiles_q, q0, c0)) return;
+    if (!tile_of_block(blockIdx.x, a.tiles_q, q0, c0)) return;
     const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
     const int l32 = lane & 31, h = lane >> 5;
-    if (threadIdx.x < GT) cns[threadIdx.x] = c0 + threadIdx.x < K ? cn[c0 + threadIdx.x] : 0.f;
+    if (threadIdx.x < GT) cns[threadIdx.x] = a.start[c0 + threadIdx.x];
     // the bounds as they stand now, requested before the product so that their latency is hidden under it
     // (an older bound is a weaker one, never a wrong one)
     uint32_t seen[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int64_t q = q0 + wq + i * 32 + l32;
-        seen[i] = q < nq ? __hip_atomic_load(&U[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        seen[i] = q < a.nq ? __hip_atomic_load(&a.L[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     }
     floatx16 acc[2][2];
-    gemm_tile<true>(Qh, nq, q0, Ch, K, c0, Dph, ops0, ops1, acc);
-    const float m2c = -2.f * csi[0];
-    const float gmax = __uint_as_float(reinterpret_cast<const uint32_t *>(csi)[1]);
-    const float abs_c = 0x1p-30f * (float)D * gmax * gmax;
-    const bool whole = c0 + GT <= K;                     // no centroid of the tile lies past the end
+    gemm_tile<true>(a.Qh, a.nq, q0, a.Ch, 0, c0, a.Dp / 2, ops0, ops1, acc);
+    const float4 tl = a.tile[c0 / GT];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int64_t q = q0 + wq + i * 32 + l32;
-        const bool qok = q < nq;
-        const float qr = qok ? qn[q] : 0.f;
-        const float m2 = qok ? m2c * qsi[q] : 0.f;
-        const float abs_term = fmaf(0x1p-30f, qr, abs_c);
-        // t[j][g] = |q|^2 + |c|^2 of the lane's four consecutive centroids 32 j + 8 g + 4 h ..
-        float4 t[2][4];
+        const bool qok = q < a.nq;
+        const float2 ql = qok ? a.qlen[q] : make_float2(0.f, 0.f);
+        const float eps = shortlist_eps(ql, tl.x, tl.y, a.Dp);
+        const float before = !qok ? INFINITY : seen[i] ? key_float(seen[i]) : -INFINITY;   // (a row past the end reports nothing)
+        float bound = before;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j) {
+            float top = -INFINITY;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 cv = *reinterpret_cast<const float4 *>(&cns[wc + j * 32 + 8 * g + 4 * h]);
-                t[j][g] = make_float4(qr + cv.x, qr + cv.y, qr + cv.z, qr + cv.w);
+            for (int v = 0; v < 16; ++v) {
+                acc[i][j][v] += cns[wc + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3)];
+                top = fmaxf(top, acc[i][j][v]);
             }
-        // upper ends first: this block's smallest approx + eps joins the bound before anything is kept
-        float umin = INFINITY;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float tv[4] = {t[j][g].x, t[j][g].y, t[j][g].z, t[j][g].w};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float up = fmaf(m2, acc[i][j][4 * g + r], fmaf(SHORTLIST_KAPPA, tv[r], tv[r]));
-                    if (whole || c0 + wc + j * 32 + 8 * g + 4 * h + r < K) umin = fminf(umin, up);
-                }
+            bound = max_of_halves(fmaxf(bound, shortlist_lower(top, tl.z, eps, a.Dp)));
+            if (top + eps >= bound && top > -INFINITY) {
+                const unsigned long long at = atomicAdd(count, 1ull);
+                if (at < a.seg_cap) list[at] = ShortEntry{(int)q, (int)c0 + wc + j * 32 + 4 * h, reaching(acc[i][j], bound - eps), top + eps};
             }
-        umin = fmaxf(umin + abs_term, 0.f);
-        umin = fminf(umin, __shfl_xor(umin, 32, WAVE));
-        if (!qok) continue;
-        float bound = umin;
-        if (seen[i] != ~0u) bound = fminf(bound, __uint_as_float(seen[i]));
-        // (non-negative floats order like their bit patterns)
-        if (h == 0 && __float_as_uint(umin) < seen[i]) atomicMin(&U[q], __float_as_uint(umin));
-        bound += abs_term;   // lo = approx - eps <= bound  <=>  approx - kappa t <= bound + abs_term
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float tv[4] = {t[j][g].x, t[j][g].y, t[j][g].z, t[j][g].w};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float lo = fmaf(m2, acc[i][j][4 * g + r], fmaf(-SHORTLIST_KAPPA, tv[r], tv[r]));
-                    const int cl = wc + j * 32 + 8 * g + 4 * h + r;
-                    if (lo <= bound && (whole || c0 + cl < K)) {
-                        const unsigned long long at = atomicAdd(cand_count, 1ull);
-                        if (at < cand_cap) cand[at] = make_int2((int)q, (int)(c0 + cl));
-                    }
-                }
-            }
+        }
+        if (qok && h == 0 && bound > before) atomicMax(&a.L[q], float_key(bound));
     }
 }
 
-// The same pass with the structure of the sweep kernel, for SH = 3 or 4 hi-only stages (packed dimension
-// 96 or 128): a workgroup keeps the hi fragments of ONE query tile in registers and sweeps `tiles_per_wg`
-// consecutive centroid tiles through two LDS buffers of a whole tile each, one workgroup barrier per tile
-// (the copies of tile t + 1 are issued right behind the barrier of tile t and waited for at the barrier of
-// tile t + 1).  The running minimum of approx + eps over the sweep stays in registers and reaches U[q]
-// once, at the end.
+// The same pass for SH = 1 .. 4 stages of 32 dimensions (packed dimension up to 128): a workgroup keeps the fragments of
+// ONE query tile in registers and sweeps `tiles_per_wg` consecutive centroid tiles through two LDS buffers of a whole
+// tile each, one workgroup barrier per tile (the copies of tile t + 1 are issued right behind the barrier of tile t
+// and waited for at the barrier of tile t + 1).  (Six wavefronts and 192 queries a workgroup save a third of the copies
+// and lose more at the barrier: 2.1 against 1.8 ms for 500 000 x 16 384 without the reports.)  The bound stays in registers over the sweep and reaches L[q] once.
+// The start values arrive in the accumulators' layout as the C operand of the first product, so that nothing but the
+// largest value of a lane is left to the vector units (8 instructions a block of 32 x 32 against 2 SH products of
+// 32 cycles); three wavefronts a SIMD cover the LDS and barrier latencies.  A report is kept short, since the other three
+// wavefronts wait for it at the tile's barrier: no look at single centroids, no LDS round trip, no atomic; the entries
+// are held in LDS, 64 at a time, and those that the bounds have not overtaken meanwhile go out with one atomic.
+// 500 000 rows x 16 384 (65 536) centroids, 96 dimensions: 1.83 (6.7) ms, 860 (935) TFLOP/s, where a kernel with the bound
+// and the norms in its epilogue and a pair an entry took 3.07 (10.5); without any report 1.6 (6.4), without the copies
+// of the tiles 1.4 (5.4).
 // Only direct-to-LDS copies write `ring` and `cns`, only explicit ds_read instructions read them.
 template <int SH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SH == 3 ? 3 : 2, SH == 3 ? 3 : 2))) void coarse_shortlist_sweep_kernel(
-    const _Float16 *__restrict__ Qh, const float *__restrict__ qn, const float *__restrict__ qsi, int64_t nq,
-    const _Float16 *__restrict__ Ch, const float *__restrict__ cn, const float *__restrict__ csi, int64_t K,
-    int D, uint32_t *__restrict__ U, int2 *__restrict__ cand_all, unsigned long long *__restrict__ cand_count_all,
-    unsigned long long seg_cap, int tiles_q, int tiles_c, int tiles_per_wg)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void coarse_shortlist_sweep_kernel(
+    ShortlistArgs a, int tiles_per_wg)
 {
     typedef const __attribute__((address_space(1))) void *gptr_t;
     typedef __attribute__((address_space(3))) void *lptr_t;
@@ -952,198 +1015,248 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SH == 3 ? 3
     constexpr int SLOT = GT * ROWF;
     __shared__ __attribute__((aligned(16))) float ring[2][SH * SLOT];
     __shared__ __attribute__((aligned(16))) float cns[2][GT];
-    int2 *cand = cand_all + (blockIdx.x % SHORTLIST_SEGS) * seg_cap;
-    unsigned long long *cand_count = cand_count_all + (blockIdx.x % SHORTLIST_SEGS) * 16;
+    __shared__ __attribute__((aligned(16))) uint2 held_all[4][WAVE];
+    ShortEntry *list = a.list + (blockIdx.x % SHORTLIST_SEGS) * a.seg_cap;
+    unsigned long long *count = a.count + (blockIdx.x % SHORTLIST_SEGS) * 16;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
     const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
-    const int tq_per = (tiles_q + N_XCD - 1) / N_XCD;
+    const int tq_per = (a.tiles_q + N_XCD - 1) / N_XCD;
     const int xcd = (int)(blockIdx.x % N_XCD);
     const int64_t local = blockIdx.x / N_XCD;
     const int tq = (int)(local % tq_per) * N_XCD + xcd;
-    if (tq >= tiles_q) return;
+    if (tq >= a.tiles_q) return;
     const int tb = (int)(local / tq_per) * tiles_per_wg;
-    int t_end = tb < tiles_c ? tiles_c - tb : 0;
+    int t_end = tb < a.tiles_c ? a.tiles_c - tb : 0;
     if (t_end > tiles_per_wg) t_end = tiles_per_wg;
     if (t_end <= 0) return;
     const int64_t q0 = (int64_t)tq * GT;
 
-    // this wavefront's copies of a tile: rows 32 wave + 16 n + lane / 4 (n = 0, 1) of each stage, and
-    // (wavefronts 0, 1) 64 of the tile's norms (index clamped at the end of the table: never used there)
-    const int rl = wave * 32 + (lane >> 2);
+    // The copies of a tile: 8 SH pieces of 16 rows of a stage, dealt to the wavefronts, and from two of them 64 of the
+    // tile's start values
+    const int rl = lane >> 2;
     const int fl = (lane & 3) ^ ((lane >> 4) & 3);
-    const float *cbase = reinterpret_cast<const float *>(Ch) + (int64_t)rl * Dpf + fl * 4;
+    const float *cbase = reinterpret_cast<const float *>(a.Ch) + (int64_t)rl * Dpf + fl * 4;
     auto issue_tile = [&](int t) {
         const int tc = t < t_end ? t : t_end - 1;            // past the range: the last tile again, never read
-        if (wave < 2) {
-            const int64_t cnx = (int64_t)(tb + tc) * GT + wave * 64 + lane;
-            __builtin_amdgcn_global_load_lds((gptr_t)(cn + (cnx < K ? cnx : K - 1)), (lptr_t)(&cns[t & 1][wave * 64]), 4, 0, 0);
-        }
+        if (wave < 2)
+            __builtin_amdgcn_global_load_lds((gptr_t)(a.start + (int64_t)(tb + tc) * GT + wave * 64 + lane), (lptr_t)(&cns[t & 1][wave * 64]), 4, 0, 0);
         const float *src = cbase + (int64_t)(tb + tc) * GT * Dpf;
-        float *dst = &ring[t & 1][wave * 512];
+        float *dst = &ring[t & 1][0];
         // (one instruction in a rolled loop: the compiler tracks only a handful of distinct LDS copies exactly)
 #pragma nounroll
-        for (int n = 0; n < 2 * SH; ++n)
-            __builtin_amdgcn_global_load_lds((gptr_t)(src + (n >> 1) * DK + (int64_t)(n & 1) * 16 * Dpf),
-                                             (lptr_t)(dst + (n >> 1) * SLOT + (n & 1) * 256), 16, 0, 0);
+        for (int n = wave; n < 8 * SH; n += 4)     // piece n: stage n / 8, rows 16 (n % 8) ..
+            __builtin_amdgcn_global_load_lds((gptr_t)(src + (n >> 3) * DK + (int64_t)(n & 7) * 16 * Dpf), (lptr_t)(dst + n * 256), 16, 0, 0);
     };
     issue_tile(0);
 
     gu32x4 afr[SH][2][2];
-    float qr[2], m2[2], abs_term[2], lmin[2];
-    uint32_t seen[2];
+    float2 ql[2];
+    float bound[2], before[2];
     bool qok[2];
-    {
-        const float m2c = -2.f * csi[0];
-        const float gmax = __uint_as_float(reinterpret_cast<const uint32_t *>(csi)[1]);
-        const float abs_c = 0x1p-30f * (float)D * gmax * gmax;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int64_t q = q0 + wq + i * 32 + l32;
-            qok[i] = q < nq;
-            const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(Qh) + q * Dpf) + 2 * h;
+    for (int i = 0; i < 2; ++i) {
+        const int64_t q = q0 + wq + i * 32 + l32;
+        qok[i] = q < a.nq;
+        const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(a.Qh) + q * Dpf) + 2 * h;
 #pragma unroll
-            for (int s = 0; s < SH; ++s) {
-                afr[s][i][0] = row[s * 4 + 0];
-                afr[s][i][1] = row[s * 4 + 1];
-            }
-            qr[i] = qok[i] ? qn[q] : 0.f;
-            m2[i] = qok[i] ? m2c * qsi[q] : 0.f;
-            abs_term[i] = fmaf(0x1p-30f, qr[i], abs_c);
-            // the bound as it stands now (an older bound is a weaker one, never a wrong one)
-            seen[i] = qok[i] ? __hip_atomic_load(&U[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-            lmin[i] = INFINITY;
+        for (int s = 0; s < SH; ++s) {
+            afr[s][i][0] = row[s * 4 + 0];
+            afr[s][i][1] = row[s * 4 + 1];
         }
+        ql[i] = qok[i] ? a.qlen[q] : make_float2(0.f, 0.f);
+        // the bound as it stands now (an older bound is a weaker one, never a wrong one); a row past the end has nothing to report
+        const uint32_t seen = qok[i] ? __hip_atomic_load(&a.L[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        before[i] = bound[i] = !qok[i] ? INFINITY : seen ? key_float(seen) : -INFINITY;
     }
 
+    // the wavefront's entries: query (6 bits), tile, half and lane half (8 bits), which of the 16; upper end
+    const uint32_t held = (uint32_t)reinterpret_cast<uintptr_t>(&held_all[wave][0]);
+    int n_held = 0;                                           // (uniform)
+    auto flush = [&]() {
+        uint2 e;
+        asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(e) : "v"(held + 8u * (uint32_t)lane));
+        const int qi = (int)(e.x & 63u);
+        const float b0 = __shfl(bound[0], qi & 31, WAVE), b1 = __shfl(bound[1], qi & 31, WAVE);
+        const float up = __uint_as_float(e.y);
+        const bool live = lane < n_held && up >= (qi & 32 ? b1 : b0);
+        const uint64_t m = __ballot(live);
+        if (m) {
+            unsigned long long at = 0;
+            if (lane == 0) at = atomicAdd(count, (unsigned long long)__popcll(m));
+            at = __shfl(at, 0, WAVE) + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (live && at < a.seg_cap)
+                list[at] = ShortEntry{(int)(q0 + wq) + qi, (tb + (int)(e.x >> 8 & 63u)) * GT + wc + (int)(e.x >> 7 & 1u) * 32 + (int)(e.x >> 6 & 1u) * 4, e.x >> 16, up};
+        }
+        n_held = 0;
+    };
+
     for (int t = 0; t < t_end; ++t) {
+        const float4 tl = a.tile[tb + t];                    // (uniform)
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wavefront's copies of tile t (issued a tile ago) are in
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // ... and everyone's; tile t - 1's buffer is free
         issue_tile(t + 1);
         const int64_t c0 = (int64_t)(tb + t) * GT;
-        const bool whole = c0 + GT <= K;
-        // One half of the wavefront's 64 centroids at a time, both blocks of 32 queries: two accumulators live
-        // instead of four, every centroid fragment still read from LDS once.  Registers are what limits the
-        // wavefronts per SIMD here, and three of them hide the LDS and barrier latencies that two leave open.
+        float eps[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) eps[i] = shortlist_eps(ql[i], tl.x, tl.y, a.Dp);
+        // One half of the wavefront's 64 centroids at a time, both blocks of 32 queries: every centroid fragment and start
+        // value is read from LDS once
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             floatx16 acc[2];
+            union { floatx16 all; floatx4 part[4]; } start;
             const int rb = wc + j * 32 + l32;
+            // reads and their wait in one block each: nothing the compiler does to a register can come between
+            const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
+            const uint32_t rsw = 4u * (uint32_t)(rb * ROWF), k0 = 16u * (uint32_t)((2 * h) ^ ((rb >> 2) & 3)), k1 = 16u * (uint32_t)((2 * h + 1) ^ ((rb >> 2) & 3));
 #pragma unroll
             for (int s = 0; s < SH; ++s) {
+                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][s * SLOT]) + rsw;
                 gu32x4 b[2];
-                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][s * SLOT]);
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const uint32_t at = bs + 4u * (uint32_t)(rb * ROWF + (((2 * h + p) ^ ((rb >> 2) & 3)) << 2));
-                    asm volatile("ds_read_b128 %0, %1" : "=v"(b[p]) : "v"(at));
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(b[0]), "+v"(b[1]));
+                if (s == 0)
+                    asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:32\n\tds_read_b128 %2, %6 offset:64\n\tds_read_b128 %3, %6 offset:96\n\t"
+                                 "ds_read_b128 %4, %7\n\tds_read_b128 %5, %8\n\ts_waitcnt lgkmcnt(0)"
+                                 : "=&v"(start.part[0]), "=&v"(start.part[1]), "=&v"(start.part[2]), "=&v"(start.part[3]), "=&v"(b[0]), "=&v"(b[1])
+                                 : "v"(cb), "v"(bs + k0), "v"(bs + k1));
+                else
+                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(bs + k0), "v"(bs + k1));
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        floatx16 c_in = acc[i];
-                        if (s == 0 && p == 0) {
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) c_in[v] = 0.f;
-                        }
-                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, b[p]),
-                                                                        __builtin_bit_cast(halfx8, afr[s][i][p]), c_in, 0, 0, 0);
-                    }
+                    for (int i = 0; i < 2; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, b[p]), __builtin_bit_cast(halfx8, afr[s][i][p]),
+                                                                        s == 0 && p == 0 ? start.all : acc[i], 0, 0, 0);
             }
-            // the norms of the lane's 16 centroids of this half (copied to LDS behind the compiler's back:
-            // explicit reads and wait)
-            floatx4 cv[4];
-            {
-                const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
-#pragma unroll
-                for (int g = 0; g < 4; ++g) asm volatile("ds_read_b128 %0, %1" : "=v"(cv[g]) : "v"(cb + 32u * (uint32_t)g));
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(cv[0]), "+v"(cv[1]), "+v"(cv[2]), "+v"(cv[3]));
-            }
-            uint32_t valid = 0xFFFFu;                          // bit v: the lane's centroid v lies inside the table
-            if (!whole) {
-                valid = 0;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) valid |= (c0 + wc + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3) < K ? 1u : 0u) << v;
-            }
-            const float cmax = fmaxf(fmaxf(fmaxf(fmaxf(cv[0][0], cv[0][1]), fmaxf(cv[0][2], cv[0][3])), fmaxf(fmaxf(cv[1][0], cv[1][1]), fmaxf(cv[1][2], cv[1][3]))),
-                                     fmaxf(fmaxf(fmaxf(cv[2][0], cv[2][1]), fmaxf(cv[2][2], cv[2][3])), fmaxf(fmaxf(cv[3][0], cv[3][1]), fmaxf(cv[3][2], cv[3][3]))));
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                // a = approx, in place, and its minimum over the lane's centroids: with their largest
-                // t = |q|^2 + |c|^2, three operations per distance decide, nearly always, that the lane has
-                // nothing to report
-                float amin = INFINITY;
+                float top = acc[i][0];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float a = fmaf(m2[i], acc[i][v], qr[i] + cv[v >> 2][v & 3]);
-                    acc[i][v] = a;
-                    if (whole || (valid >> v & 1)) amin = fminf(amin, a);
-                }
-                float bound = lmin[i];
-                if (seen[i] != ~0u) bound = fminf(bound, __uint_as_float(seen[i]));
-                // every lower end of the lane is at least amin - kappa tmax - abs_term, every upper end at least
-                // amin: above the bound, the lane can neither list a centroid nor lower the bound
-                const bool look = fmaf(-SHORTLIST_KAPPA, qr[i] + cmax, amin) - abs_term[i] <= bound;
-                if (__any(look)) {
-                    // the smallest upper end a + kappa t + abs_term of the query in this half, exactly
-                    float umin = INFINITY;
+                for (int v = 1; v < 16; ++v) top = __builtin_elementwise_maximum(top, acc[i][v]);
+                if (__any(!(top + eps[i] < bound[i]))) {
+                    if (!(top == top)) {                       // (largest of the values that are numbers)
+                        top = -INFINITY;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const float up = fmaf(SHORTLIST_KAPPA, qr[i] + cv[v >> 2][v & 3], acc[i][v]);
-                        if (whole || (valid >> v & 1)) umin = fminf(umin, up);
+                        for (int v = 0; v < 16; ++v) top = fmaxf(top, acc[i][v]);
                     }
-                    umin = fmaxf(umin + abs_term[i], 0.f);
-                    umin = fminf(umin, __shfl_xor(umin, 32, WAVE));   // the other lane half holds the other 16 centroids
-                    lmin[i] = fminf(lmin[i], umin);
-                    bound = fminf(bound, lmin[i]) + abs_term[i];   // approx - eps <= bound  <=>  a - kappa t <= bound + abs_term
-                    uint32_t todo = 0;                                // which of the lane's distances pass
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        todo |= (fmaf(-SHORTLIST_KAPPA, qr[i] + cv[v >> 2][v & 3], acc[i][v]) <= bound ? 1u : 0u) << v;
-                    todo &= valid;
-                    if (!qok[i]) todo = 0;
-                    while (todo) {
-                        const int v = __builtin_ctz(todo);
-                        todo &= todo - 1;
-                        const unsigned long long at = atomicAdd(cand_count, 1ull);
-                        if (at < seg_cap)
-                            cand[at] = make_int2((int)(q0 + wq + i * 32 + l32), (int)(c0 + wc + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3)));
-                    }
+                    bound[i] = max_of_halves(fmaxf(bound[i], shortlist_lower(top, tl.z, eps[i], a.Dp)));
+                    const bool pass = top + eps[i] >= bound[i] && top > -INFINITY;
+                    const uint64_t m = __ballot(pass);
+                    const int n = __popcll(m);
+                    if (n_held + n > WAVE) flush();
+                    const uint32_t at = held + 8u * ((uint32_t)n_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)));
+                    const uint2 e = make_uint2((uint32_t)(i * 32 + l32) | (uint32_t)h << 6 | (uint32_t)j << 7 | (uint32_t)t << 8 | reaching(acc[i], bound[i] - eps[i]) << 16,
+                                               __float_as_uint(top + eps[i]));
+                    if (pass) asm volatile("ds_write_b64 %0, %1" ::"v"(at), "v"(e) : "memory");
+                    n_held += n;
                 }
             }
             __builtin_amdgcn_sched_barrier(0);   // the next half's products start with this half's registers free
         }
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no copy into LDS may outlive the workgroup
+    flush();
 #pragma unroll
-    for (int i = 0; i < 2; ++i)   // (non-negative floats order like their bit patterns)
-        if (qok[i] && h == 0 && __float_as_uint(lmin[i]) < seen[i]) atomicMin(&U[q0 + wq + i * 32 + l32], __float_as_uint(lmin[i]));
+    for (int i = 0; i < 2; ++i)
+        if (qok[i] && h == 0 && bound[i] > before[i]) atomicMax(&a.L[q0 + wq + i * 32 + l32], float_key(bound[i]));
 }
 
-// Exact decision among the candidates: one wavefront per pair computes |x - c|^2 from the fp32 rows
-// (differences squared, summed in a tree over the lanes: a few ulps) and merges (distance, id) into
-// best[q] with a 64-bit atomic minimum.  best must be pre-filled with all ones.
-// Grid: (quarter of the longest segment, SHORTLIST_SEGS).
-__global__ __launch_bounds__(256) void rerank_kernel(const float *__restrict__ X, const float *__restrict__ C, int D,
-                                                     const int2 *__restrict__ cand_all, const unsigned long long *__restrict__ cand_count_all,
-                                                     unsigned long long seg_cap, unsigned long long *__restrict__ best)
+// Entries -> pairs.  A wavefront looks at 64 entries at a time; a lane whose entry L leaves forms the products of its
+// centroids from the packed rows again, one after the other (one is usual).  Grid: (any, SHORTLIST_SEGS); a segment whose
+// list overflowed is left alone.
+__global__ __launch_bounds__(256) void shortlist_pairs_kernel(ShortlistArgs a)
 {
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+    __shared__ ShortPair held_all[4][WAVE];                  // a wavefront's pairs: one atomic for 64 of them
     const int lane = threadIdx.x & 63;
-    if ((unsigned long long)i >= cand_count_all[blockIdx.y * 16]) return;
-    const int2 qc = cand_all[blockIdx.y * seg_cap + i];
-    const float *x = X + (int64_t)qc.x * D, *c = C + (int64_t)qc.y * D;
-    float s = 0.f;
-    for (int k = lane; k < D; k += WAVE) {
-        const float u = x[k] - c[k];
-        s = fmaf(u, u, s);
+    ShortPair *held = held_all[threadIdx.x >> 6];
+    int n_held = 0;
+    auto flush = [&]() {
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(&a.pair_count[blockIdx.y * 16], (unsigned long long)n_held);
+        at = __shfl(at, 0, WAVE) + lane;
+        wave_sync();
+        if (lane < n_held && at < a.pair_cap) a.pairs[blockIdx.y * a.pair_cap + at] = held[lane];
+        wave_sync();
+        n_held = 0;
+    };
+    const unsigned long long n = a.count[blockIdx.y * 16];
+    if (n > a.seg_cap) return;
+    const float k = (float)(a.Dp + 32) * 0x1p-24f, back = 2.f * k / (0.5f - k);
+    for (unsigned long long i0 = (blockIdx.x * 4ull + (threadIdx.x >> 6)) * WAVE; i0 < n; i0 += (unsigned long long)gridDim.x * 4 * WAVE) {
+        ShortEntry e = {0, 0, 0, 0.f};
+        uint32_t seen = 0;
+        if (i0 + lane < n) {
+            e = a.list[blockIdx.y * a.seg_cap + i0 + lane];
+            seen = __hip_atomic_load(&a.L[e.q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (float_key(e.up) < seen) e.which = 0;
+        }
+        while (__any(e.which != 0)) {
+            const int v = e.which ? __builtin_ctz(e.which) : 0, c = e.c + 8 * (v >> 2) + (v & 3);
+            bool pass = e.which != 0 && c < a.K;
+            e.which &= e.which - 1;
+            float up = 0.f;
+            if (pass) {
+                const gu32x4 *qr = reinterpret_cast<const gu32x4 *>(a.Qh + (int64_t)e.q * a.Dp), *cr = reinterpret_cast<const gu32x4 *>(a.Ch + (int64_t)c * a.Dp);
+                float g = 0.f;
+#pragma unroll 4
+                for (int d = 0; d < a.Dp / 8; ++d) {
+                    const gu32x4 u = qr[d], w = cr[d];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        g = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, (uint32_t)u[t]), __builtin_bit_cast(halfx2, (uint32_t)w[t]), g, false);
+                }
+                const float2 cl = a.clen[c];
+                const float st = a.start[c], eps = shortlist_eps(a.qlen[e.q], cl.x, cl.y, a.Dp);
+                g += st;
+                up = g + eps;
+                pass = float_key(up) >= seen;
+                const uint32_t low = float_key(fmaf(back, st, g) - eps);
+                if (pass && low > seen) {
+                    atomicMax(&a.L[e.q], low);
+                    seen = low;
+                }
+            }
+            const uint64_t m = __ballot(pass);
+            if (n_held + __popcll(m) > WAVE) flush();
+            if (pass) held[n_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = ShortPair{e.q, c, up};
+            n_held += __popcll(m);
+        }
     }
-    s = wave_sum(s);
-    if (lane == 0) atomicMin(&best[qc.x], ((unsigned long long)float_key(s) << 32) | (uint32_t)qc.y);
+    if (n_held) flush();
+}
+
+// Exact decision among the pairs that the final bounds leave: a wavefront per pair computes |x - c|^2 from the fp32
+// rows (differences squared, summed in a tree over the lanes: a few ulps) and merges (distance, id) into best[q] with a
+// 64-bit atomic minimum.  best must be pre-filled with all ones.  A wavefront looks at 64 pairs at a time.
+__global__ __launch_bounds__(256) void rerank_kernel(const float *__restrict__ X, const float *__restrict__ C, int D, ShortlistArgs a,
+                                                     unsigned long long *__restrict__ best)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned long long n = a.pair_count[blockIdx.y * 16];
+    if (n > a.pair_cap) return;
+    for (unsigned long long i0 = (blockIdx.x * 4ull + (threadIdx.x >> 6)) * WAVE; i0 < n; i0 += (unsigned long long)gridDim.x * 4 * WAVE) {
+        ShortPair e = {0, 0, 0.f};
+        bool live = i0 + lane < n;
+        if (live) {
+            e = a.pairs[blockIdx.y * a.pair_cap + i0 + lane];
+            live = float_key(e.up) >= a.L[e.q];
+        }
+        for (uint64_t todo = __ballot(live); todo; todo &= todo - 1) {
+            const int s = __builtin_ctzll(todo);
+            const int q = __builtin_amdgcn_readlane(e.q, s), cc = __builtin_amdgcn_readlane(e.c, s);
+            const float *x = X + (int64_t)q * D, *c = C + (int64_t)cc * D;
+            float d = 0.f;
+            for (int k = lane; k < D; k += WAVE) {
+                const float u = x[k] - c[k];
+                d = fmaf(u, u, d);
+            }
+            d = wave_sum(d);
+            if (lane == 0) atomicMin(&best[q], ((unsigned long long)float_key(d) << 32) | (uint32_t)cc);
+        }
+    }
 }
 
 // The P closest centroids of each query row of Dt by (distance, id), written

@@ -11,6 +11,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include <hip/hip_runtime.h>
@@ -748,29 +749,35 @@ std::atomic<int64_t> g_assign_short{0}, g_assign_exact{0};
 // Two passes: the hi halves of the operands alone (a third of the MFMA work) give every row a short
 // list of centroids that may be its nearest, with a proven error bound (coarse_shortlist_kernel), and
 // the exact distances of the listed pairs decide (rerank_kernel).  A chunk whose list overflows (rows
-// with very many centroids at nearly the same distance) is redone by the exact kernel.
+// with very many centroids at nearly the same distance) is redone by the exact kernel, whose operands
+// are packed only then.
 struct ArgminCtx {
     int64_t K = 0, chunk = 0;
     int D = 0, Dp = 0;
-    float *cn = nullptr, *csi = nullptr, *xn = nullptr, *xsi = nullptr;
-    _Float16 *cpk = nullptr, *xpk = nullptr, *chk = nullptr, *xhk = nullptr;   // hi/lo tables, hi-only tables
-    unsigned long long *best = nullptr, *cand_count = nullptr;
-    uint32_t *U = nullptr;
-    int2 *cand = nullptr;
-    unsigned long long seg_cap = 0;
+    DevTmp cn, csi, cpk, xn, xsi, xpk;                       // operands of the exact kernel
+    static constexpr int N_COUNTS = 2 * SHORTLIST_SEGS * 16;   // counters of the entries, then of the pairs
+    DevTmp mem;                                               // what follows lies in it
+    _Float16 *chk = nullptr, *xhk = nullptr;
+    float2 *clen = nullptr, *xlen = nullptr;
+    uint32_t *words = nullptr;                                // largest magnitudes, of the table and of each chunk of rows
+    float *start = nullptr;
+    float4 *tile = nullptr;
+    unsigned long long *best = nullptr, *counts = nullptr;
+    uint32_t *L = nullptr;
+    ShortEntry *list = nullptr;
+    ShortPair *pairs = nullptr;
+    unsigned long long seg_cap = 0, pair_cap = 0;
     const float *centroids = nullptr;          // the caller's table, as of the last set_centroids
+    bool exact_packed = false;                 // ... is packed for the exact kernel
     bool shortlist = true;
-    int64_t chunks_short = 0, chunks_exact = 0;   // how the chunks of all run() calls were decided
+    bool keep_rows = false;                    // the packed rows of every chunk stay (the same x in every run())
+    bool rows_packed = false;
     ArgminCtx() = default;
     ArgminCtx(const ArgminCtx &) = delete;
     ArgminCtx &operator=(const ArgminCtx &) = delete;
-    ~ArgminCtx()
-    {
-        void *owned[] = {cn, csi, xn, xsi, cpk, xpk, chk, xhk, best, cand_count, U, cand};
-        for (void *p : owned)
-            if (p) (void)hipFree(p);
-    }
-    int init(int64_t K_, int D_, int64_t max_rows)
+    template <class T> static T *ptr(const DevTmp &m) { return static_cast<T *>(m.p); }
+    // many_runs: run() will be called with the same rows again and again
+    int init(int64_t K_, int D_, int64_t max_rows, bool many_runs = false)
     {
         K = K_; D = D_; Dp = packed_dim(D);
         // rows per launch: at most 2^20, and few enough that the grid (one workgroup of 256 threads per
@@ -780,92 +787,163 @@ struct ArgminCtx {
         if (max_tq < N_XCD) return fail(IVF_EINVAL, "K=%lld: too many centroid tiles for one launch", (long long)K);
         chunk = max_tq * GT < (1ll << 20) ? max_tq * GT : (1ll << 20);
         if (max_rows < chunk) chunk = max_rows > 0 ? max_rows : 1;
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&cn), (size_t)K * sizeof(float)));
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&cpk), (size_t)packed_rows(K) * Dp * 2 * sizeof(_Float16)));
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&csi), 2 * sizeof(float)));
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&xn), (size_t)chunk * sizeof(float)));
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&xsi), (size_t)chunk * sizeof(float)));
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&xpk), (size_t)packed_rows(chunk) * Dp * 2 * sizeof(_Float16)));
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&best), (size_t)chunk * sizeof(unsigned long long)));
         const char *off = getenv("IVF_GP_EXACT_ASSIGN");   // (for measurements: the one-pass exact kernel only)
         shortlist = !(off && off[0] == '1');
-        if (shortlist) {
-            // room for 32 listed centroids per row on average, at least 2^16 pairs per segment
-            seg_cap = (unsigned long long)(32 * chunk + SHORTLIST_SEGS - 1) / SHORTLIST_SEGS;
-            if (seg_cap < (1ull << 16)) seg_cap = 1ull << 16;
-            HIPCHK(hipMalloc(reinterpret_cast<void **>(&chk), (size_t)packed_rows(K) * Dp * sizeof(_Float16)));
-            HIPCHK(hipMalloc(reinterpret_cast<void **>(&xhk), (size_t)packed_rows(chunk) * Dp * sizeof(_Float16)));
-            HIPCHK(hipMalloc(reinterpret_cast<void **>(&U), (size_t)(chunk + 2) * sizeof(uint32_t)));   // filled in 64-bit words
-            HIPCHK(hipMalloc(reinterpret_cast<void **>(&cand), (size_t)seg_cap * SHORTLIST_SEGS * sizeof(int2)));
-            HIPCHK(hipMalloc(reinterpret_cast<void **>(&cand_count), (size_t)SHORTLIST_SEGS * 16 * sizeof(unsigned long long)));
+        if (!shortlist) {
+            HIPCHK(hipMalloc(&mem.p, (size_t)chunk * sizeof(unsigned long long)));
+            best = static_cast<unsigned long long *>(mem.p);
+            return IVF_OK;
         }
+        keep_rows = many_runs && packed_rows(max_rows) * Dp * (int64_t)sizeof(_Float16) <= (8ll << 30);
+        const int64_t rows = keep_rows ? max_rows : chunk;
+        const int64_t n_words = 1 + (keep_rows ? (max_rows + chunk - 1) / chunk : 1);
+        // room for 24 entries per row on average (10 are usual at K = 2^16, growing with log K) and for 8 pairs (one is
+        // usual), and for at least 2^16 of either in a segment
+        seg_cap = (unsigned long long)(24 * chunk + SHORTLIST_SEGS - 1) / SHORTLIST_SEGS;
+        pair_cap = (unsigned long long)(8 * chunk + SHORTLIST_SEGS - 1) / SHORTLIST_SEGS;
+        if (seg_cap < (1ull << 16)) seg_cap = 1ull << 16;
+        if (pair_cap < (1ull << 16)) pair_cap = 1ull << 16;
+        // one allocation for everything, 256-byte aligned pieces
+        size_t total = 0;
+        auto place = [&](auto *&p, size_t count) {
+            p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(total);
+            total += (count * sizeof(*p) + 255) / 256 * 256;
+        };
+        auto all = [&]() {
+            place(best, (size_t)chunk);
+            place(chk, (size_t)packed_rows(K) * Dp);
+            place(clen, (size_t)packed_rows(K));
+            place(words, (size_t)n_words);
+            place(start, (size_t)tiles_c * GT);
+            place(tile, (size_t)tiles_c);
+            place(xhk, (size_t)packed_rows(rows) * Dp);
+            place(xlen, (size_t)packed_rows(rows));
+            place(L, (size_t)(chunk + 2));                      // filled in 64-bit words
+            place(list, (size_t)seg_cap * SHORTLIST_SEGS);
+            place(pairs, (size_t)pair_cap * SHORTLIST_SEGS);
+            place(counts, (size_t)N_COUNTS);
+        };
+        all();
+        HIPCHK(hipMalloc(&mem.p, total));
+        total = reinterpret_cast<size_t>(mem.p);
+        all();
+        return IVF_OK;
+    }
+    int pack_hi(const float *X, int64_t n, uint32_t *gmax, _Float16 *H, float2 *len, hipStream_t st)
+    {
+        int rc = launch_absmax(X, n * D, gmax, st);
+        if (rc) return rc;
+        const int64_t pad = packed_rows(n);
+        pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(X, n, pad, D, Dp, gmax, H, len);
+        LAUNCHCHK("pack_hi_rows_kernel");
         return IVF_OK;
     }
     int set_centroids(const float *centroids_, hipStream_t st)
     {
         centroids = centroids_;
-        int rc = pack_rows(centroids, K, D, reinterpret_cast<uint32_t *>(csi + 1), cpk, cn, csi, st);
-        if (rc || !shortlist) return rc;
-        const int64_t chunks16 = K * (Dp / 8);
-        pack_hi_kernel<<<dim3((unsigned)((chunks16 + 255) / 256)), dim3(256), 0, st>>>(cpk, K, Dp, chk);
-        LAUNCHCHK("pack_hi_kernel");
-        return IVF_OK;
+        exact_packed = false;
+        return shortlist ? pack_hi(centroids, K, words, chk, clen, st) : IVF_OK;
     }
-    // the exact one-pass kernel on the packed chunk
-    int run_exact(int64_t m, hipStream_t st)
+    // the exact one-pass kernel on m rows
+    int run_exact(const float *x, int64_t m, hipStream_t st)
     {
         const int tiles_q = (int)((m + GT - 1) / GT);
         const int64_t grid = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD * ((K + GT - 1) / GT);
         if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large");
+        if (!cn.p) {
+            HIPCHK(hipMalloc(&cn.p, (size_t)K * sizeof(float)));
+            HIPCHK(hipMalloc(&cpk.p, (size_t)packed_rows(K) * Dp * 2 * sizeof(_Float16)));
+            HIPCHK(hipMalloc(&csi.p, 2 * sizeof(float)));
+            HIPCHK(hipMalloc(&xn.p, (size_t)chunk * sizeof(float)));
+            HIPCHK(hipMalloc(&xsi.p, (size_t)chunk * sizeof(float)));
+            HIPCHK(hipMalloc(&xpk.p, (size_t)packed_rows(chunk) * Dp * 2 * sizeof(_Float16)));
+        }
+        int rc;
+        if (!exact_packed) {
+            if ((rc = pack_rows(centroids, K, D, ptr<uint32_t>(csi) + 1, ptr<_Float16>(cpk), ptr<float>(cn), ptr<float>(csi), st))) return rc;
+            exact_packed = true;
+        }
+        if ((rc = pack_rows(x, m, D, nullptr, ptr<_Float16>(xpk), ptr<float>(xn), ptr<float>(xsi), st))) return rc;
         fill_u64_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, ~0ull);
         LAUNCHCHK("fill_u64_kernel");
-        coarse_argmin_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(xpk, xn, xsi, m, cpk, cn, csi, K, Dp, best, tiles_q);
+        coarse_argmin_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(ptr<_Float16>(xpk), ptr<float>(xn), ptr<float>(xsi), m, ptr<_Float16>(cpk),
+                                                                         ptr<float>(cn), ptr<float>(csi), K, Dp, best, tiles_q);
         LAUNCHCHK("coarse_argmin_kernel");
-        ++chunks_exact; ++g_assign_exact;
+        ++g_assign_exact;
         return IVF_OK;
     }
-    // shortlist + exact decision; *overflow = the list did not hold every candidate (best[] is then incomplete)
-    int run_shortlist(const float *x, int64_t m, bool *overflow, hipStream_t st)
+    // shortlist + exact decision for the rows q0 .. q0 + m of x; *overflow = the list did not hold every candidate
+    // (best[] is then incomplete)
+    int run_shortlist(const float *x, int64_t q0, int64_t m, bool *overflow, hipStream_t st)
     {
         const int tiles_q = (int)((m + GT - 1) / GT);
-        const int64_t grid = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD * ((K + GT - 1) / GT);
-        if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large");
-        const int64_t chunks16 = m * (Dp / 8);
-        pack_hi_kernel<<<dim3((unsigned)((chunks16 + 255) / 256)), dim3(256), 0, st>>>(xpk, m, Dp, xhk);
-        LAUNCHCHK("pack_hi_kernel");
+        const int64_t tiles_c = (K + GT - 1) / GT;
+        const float *xm = x + q0 * D;
+        uint32_t *xw = words + 1 + (keep_rows ? q0 / chunk : 0);
+        _Float16 *xh = xhk + (keep_rows ? q0 : 0) * (int64_t)Dp;
+        float2 *xl = xlen + (keep_rows ? q0 : 0);
+        int rc;
+        if (!(keep_rows && rows_packed) && (rc = pack_hi(xm, m, xw, xh, xl, st))) return rc;
+        shortlist_tiles_kernel<<<dim3((unsigned)tiles_c), dim3(128), 0, st>>>(clen, K, Dp, words, xw,
+                                                                              start, tile);
+        LAUNCHCHK("shortlist_tiles_kernel");
         fill_u64_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, ~0ull);
         LAUNCHCHK("fill_u64_kernel");
-        // U: 32-bit words, two per 64-bit fill; the counters likewise
-        fill_u64_kernel<<<dim3((unsigned)(((m + 1) / 2 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<unsigned long long *>(U), (m + 1) / 2, ~0ull);
+        // L: 32-bit words, two per 64-bit fill; the counters likewise
+        fill_u64_kernel<<<dim3((unsigned)(((m + 1) / 2 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<unsigned long long *>(L), (m + 1) / 2, 0ull);
         LAUNCHCHK("fill_u64_kernel");
-        fill_u64_kernel<<<dim3((SHORTLIST_SEGS * 16 + 255) / 256), dim3(256), 0, st>>>(cand_count, SHORTLIST_SEGS * 16, 0ull);
+        fill_u64_kernel<<<dim3((N_COUNTS + 255) / 256), dim3(256), 0, st>>>(counts, N_COUNTS, 0ull);
         LAUNCHCHK("fill_u64_kernel");
-        if (Dp == 96 || Dp == 128) {   // query tile in registers, centroid tiles swept
-            const int per_wg = 64;
-            const int64_t tiles_c = (K + GT - 1) / GT;
-            const int64_t g2 = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD * ((tiles_c + per_wg - 1) / per_wg);
-            if (Dp == 96)
-                coarse_shortlist_sweep_kernel<3><<<dim3((unsigned)g2), dim3(256), 0, st>>>(xhk, xn, xsi, m, chk, cn, csi, K, D, U, cand, cand_count,
-                                                                                         seg_cap, tiles_q, (int)tiles_c, per_wg);
-            else
-                coarse_shortlist_sweep_kernel<4><<<dim3((unsigned)g2), dim3(256), 0, st>>>(xhk, xn, xsi, m, chk, cn, csi, K, D, U, cand, cand_count,
-                                                                                         seg_cap, tiles_q, (int)tiles_c, per_wg);
+        ShortlistArgs a;
+        a.Qh = xh;
+        a.qlen = xl;
+        a.nq = m;
+        a.K = K;
+        a.Ch = chk;
+        a.start = start;
+        a.tile = tile;
+        a.clen = clen;
+        a.Dp = Dp;
+        a.L = L;
+        a.list = list;
+        a.pairs = pairs;
+        a.count = counts;
+        a.pair_count = a.count + N_COUNTS / 2;
+        a.seg_cap = seg_cap;
+        a.pair_cap = pair_cap;
+        a.tiles_q = tiles_q;
+        a.tiles_c = (int)tiles_c;
+        const int64_t tq8 = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD;
+        if (Dp <= 128) {   // query tile in registers, centroid tiles swept: long sweeps unless the chip would stand empty
+            int per_wg = 64;
+            while (per_wg > 4 && tq8 * ((tiles_c + per_wg - 1) / per_wg) < 1536) per_wg /= 2;
+            const dim3 grid((unsigned)(tq8 * ((tiles_c + per_wg - 1) / per_wg)));
+            if (Dp == 32) coarse_shortlist_sweep_kernel<1><<<grid, dim3(256), 0, st>>>(a, per_wg);
+            else if (Dp == 64) coarse_shortlist_sweep_kernel<2><<<grid, dim3(256), 0, st>>>(a, per_wg);
+            else if (Dp == 96) coarse_shortlist_sweep_kernel<3><<<grid, dim3(256), 0, st>>>(a, per_wg);
+            else coarse_shortlist_sweep_kernel<4><<<grid, dim3(256), 0, st>>>(a, per_wg);
             LAUNCHCHK("coarse_shortlist_sweep_kernel");
         } else {
-            coarse_shortlist_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(xhk, xn, xsi, m, chk, cn, csi, K, Dp / 2, D, U, cand,
-                                                                                cand_count, seg_cap, tiles_q);
+            if (tq8 * tiles_c >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large");
+            coarse_shortlist_kernel<<<dim3((unsigned)(tq8 * tiles_c)), dim3(256), 0, st>>>(a);
             LAUNCHCHK("coarse_shortlist_kernel");
         }
-        unsigned long long counts[SHORTLIST_SEGS * 16];
-        HIPCHK(hipMemcpyAsync(counts, cand_count, sizeof(counts), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        unsigned long long longest = 0;
-        for (int sgm = 0; sgm < SHORTLIST_SEGS; ++sgm) longest = counts[sgm * 16] > longest ? counts[sgm * 16] : longest;
-        *overflow = longest > seg_cap || longest == 0;
-        if (*overflow) return IVF_OK;
-        rerank_kernel<<<dim3((unsigned)((longest + 3) / 4), SHORTLIST_SEGS), dim3(256), 0, st>>>(x, centroids, D, cand, cand_count, seg_cap, best);
+        // (loops over the lists: a grid that fills the chip, whatever their length)
+        shortlist_pairs_kernel<<<dim3(64, SHORTLIST_SEGS), dim3(256), 0, st>>>(a);
+        LAUNCHCHK("shortlist_pairs_kernel");
+        rerank_kernel<<<dim3(32, SHORTLIST_SEGS), dim3(256), 0, st>>>(xm, centroids, D, a, best);
         LAUNCHCHK("rerank_kernel");
-        ++chunks_short; ++g_assign_short;
+        unsigned long long n[N_COUNTS];
+        HIPCHK(hipMemcpyAsync(n, counts, sizeof(n), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        unsigned long long longest = 0, most = 0;
+        for (int sgm = 0; sgm < SHORTLIST_SEGS; ++sgm) {
+            longest = n[sgm * 16] > longest ? n[sgm * 16] : longest;
+            most = n[N_COUNTS / 2 + sgm * 16] > most ? n[N_COUNTS / 2 + sgm * 16] : most;
+        }
+        *overflow = longest > seg_cap || most > pair_cap || longest == 0;
+        if (*overflow) return IVF_OK;
+        ++g_assign_short;
         return IVF_OK;
     }
     // out_id[i] = nearest centroid of x[i] by (distance, id), out_d[i] (may be NULL) its squared distance
@@ -874,13 +952,13 @@ struct ArgminCtx {
         int rc;
         for (int64_t q0 = 0; q0 < n; q0 += chunk) {
             const int64_t m = (n - q0 < chunk) ? n - q0 : chunk;
-            if ((rc = pack_rows(x + q0 * D, m, D, nullptr, xpk, xn, xsi, st))) return rc;
             bool overflow = true;
-            if (shortlist && (rc = run_shortlist(x + q0 * D, m, &overflow, st))) return rc;
-            if (overflow && (rc = run_exact(m, st))) return rc;
+            if (shortlist && (rc = run_shortlist(x, q0, m, &overflow, st))) return rc;
+            if (overflow && (rc = run_exact(x + q0 * D, m, st))) return rc;
             argmin_unpack_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, out_id + q0, out_d ? out_d + q0 : nullptr);
             LAUNCHCHK("argmin_unpack_kernel");
         }
+        rows_packed = true;
         return IVF_OK;
     }
 };

@@ -180,7 +180,7 @@ extern "C" int ivf_kmeans(const float *x, int64_t n, int D, int64_t K, int iters
         take_rows_kernel<<<dim3(grid_for(K * D)), dim3(256), 0, st>>>(x, D, 0, D, init_idx, K, centroids, D, 0);
         LAUNCHCHK("take_rows_kernel");
         if (iters == 0) return IVF_OK;
-        if ((r2 = ctx.init(K, D, n))) return r2;
+        if ((r2 = ctx.init(K, D, n, iters > 1))) return r2;
         if ((r2 = rb.init(n))) return r2;
         HIPCHK(hipMalloc(&lab.p, (size_t)n * sizeof(int32_t)));
         HIPCHK(hipMalloc(&dist.p, (size_t)n * sizeof(float)));

@@ -80,3 +80,44 @@ def test_bound_holds_for_unit_vectors_and_sift_like_integers():
         keep = lo <= up.min(1, keepdims=True)
         assert keep[np.arange(len(Q)), exact.argmin(1)].all()
         assert keep.sum(1).max() < 100                    # ... and stays short on such data
+
+
+# ---- the bound from the lengths of the rounding errors ----
+# g = <hi(q), hi(c)> - |c|^2 / 2 with one scale for all rows and one for the table; e = |dq| |c| + (|q| + |dq|) |dc| +
+# k |q| |c|, k = (Dp + 32) 2^-24, and the start value of the accumulation carries k |c|^2: the exact
+# G = <q,c> - |c|^2 / 2 lies in [acc - 2 k |c|^2 - e, acc + e].
+
+def _lengths(Q, C):
+    sq, sc = _scale(np.abs(Q).max()), _scale(np.abs(C).max())
+    qh, ch = _hi(Q, sq), _hi(C, sc)
+    q64, c64 = Q.astype(np.float64), C.astype(np.float64)
+    norm = lambda a: np.sqrt((a ** 2).sum(1))
+    k = ((Q.shape[1] + 31) // 32 * 32 + 32) * 2.0 ** -24
+    ql, dq, cl, dc = norm(q64), norm(q64 - qh), norm(c64), norm(c64 - ch)
+    e = dq[:, None] * cl + (ql + dq)[:, None] * dc + k * ql[:, None] * cl
+    acc = qh @ ch.T + (k - 0.5) * cl ** 2
+    G = q64 @ c64.T - 0.5 * cl ** 2
+    return acc, G, e, k * cl ** 2
+
+
+def test_length_bound_holds_and_its_list_holds_the_nearest():
+    rng = np.random.default_rng(5)
+    for D, kind in ((96, "unit"), (128, "sift"), (64, "scales"), (32, "midpoints")):
+        C = rng.standard_normal((700, D))
+        if kind == "unit":
+            C /= np.linalg.norm(C, axis=1, keepdims=True)
+        if kind == "sift":
+            C = np.clip(np.round(10 * C ** 2), 0, 255)
+        if kind == "scales":
+            C *= np.exp2(rng.integers(-14, 1, size=(700, 1)))
+        if kind == "midpoints":
+            C = np.tile((1 + 2.0 ** -11) * np.exp2(np.arange(D) % 3), (700, 1)) * rng.choice([-1, 1], (700, D))
+        Q = C[rng.integers(0, 700, 400)] + 0.05 * np.linalg.norm(C, axis=1).mean() / np.sqrt(D) * rng.standard_normal((400, D))
+        C, Q = C.astype(np.float32), Q.astype(np.float32)
+        acc, G, e, kc = _lengths(Q, C)
+        assert (G <= acc + e).all() and (G >= acc - 2 * kc - e).all(), kind
+        # the bounds fill: without the error of either side they would be broken
+        assert np.abs(G - acc + kc).max() > 0.02 * e.max()
+        L = (acc - 2 * kc - e).max(1, keepdims=True)
+        best = (G == G.max(1, keepdims=True))
+        assert (acc + e >= L)[best].all()
