@@ -103,7 +103,8 @@ typedef struct ivf_index_desc {
  */
 int ivf_load_index(const ivf_index_desc *desc, void *hip_stream, ivf_index **out);
 
-/* Release the handle and all device memory it owns (waits for the device). */
+/* Release the handle and all device memory it owns (waits for the device), and the scratch that the library
+ * keeps between index-time calls (at most 1 GiB a GPU). */
 void ivf_free_index(ivf_index *index);
 
 /*
@@ -207,8 +208,8 @@ int64_t ivf_num_kept(int nprobe, int L, float prune_frac);
  * centroids [K][D] for each of the nq vectors x [nq][D], by (distance, id),
  * written in ascending centroid id: out_id [nq][P], out_d [nq][P] squared
  * distances.  Used for query assignment, for assigning points to regions
- * (P = 1) and for the neighbour table NN_L (Eq. (2)).  Allocates and frees its
- * own scratch (waits for the stream).
+ * (P = 1) and for the neighbour table NN_L (Eq. (2)).  Has scratch of its
+ * own (waits for the stream).
  * P = 1 (also inside ivf_encode and ivf_kmeans) runs in two passes: a
  * reduced-precision product (the fp16 leading halves of the operands, a third
  * of the matrix work) with a proven error bound lists for every row the
@@ -265,7 +266,8 @@ int ivf_rotate(const float *x, int64_t n, int D, const float *rotation, float *o
 /*
  * ---- Index construction on the device (Section 3.2 "The model" and "Learning
  * the scaling factor"; Section 2 for the PQ codebooks).  Each routine waits
- * for the stream before it returns, allocates and frees its own scratch, and
+ * for the stream before it returns, has scratch of its own (blocks of up to 1 GiB
+ * together are kept per GPU for later calls, see ivf_free_index), and
  * is deterministic: no floating-point atomics, every sum is taken in an order
  * fixed by the data layout, so the same inputs give the same bits.
  */

@@ -20,15 +20,15 @@ struct RadixBufs {
         nblocks = (n + RS_TILE - 1) / RS_TILE;
         if (nblocks < 1) nblocks = 1;
         const size_t nb = (size_t)(n > 0 ? n : 1) * sizeof(uint32_t);
-        HIPCHK(hipMalloc(&ka.p, nb));
-        HIPCHK(hipMalloc(&kb.p, nb));
-        HIPCHK(hipMalloc(&va.p, nb));
-        HIPCHK(hipMalloc(&vb.p, nb));
-        HIPCHK(hipMalloc(&hist.p, (size_t)256 * nblocks * sizeof(uint32_t)));
-        HIPCHK(hipMalloc(&base.p, (size_t)256 * nblocks * sizeof(uint32_t)));
+        HIPCHK(ka.alloc(nb));
+        HIPCHK(kb.alloc(nb));
+        HIPCHK(va.alloc(nb));
+        HIPCHK(vb.alloc(nb));
+        HIPCHK(hist.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
+        HIPCHK(base.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
         HIPCHK(rocprim::exclusive_scan(nullptr, scan_bytes, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p),
                                        0u, (size_t)256 * nblocks, rocprim::plus<uint32_t>(), nullptr));
-        HIPCHK(hipMalloc(&scan.p, scan_bytes ? scan_bytes : 16));
+        HIPCHK(scan.alloc(scan_bytes ? scan_bytes : 16));
         return IVF_OK;
     }
     uint32_t *keys_a() { return static_cast<uint32_t *>(ka.p); }
@@ -141,7 +141,7 @@ extern "C" int ivf_cluster_means(const float *x, int64_t n, int D, const int32_t
     auto body = [&]() -> int {
         int r2;
         if ((r2 = rb.init(n))) return r2;
-        HIPCHK(hipMalloc(&off.p, (size_t)(K + 1) * sizeof(uint32_t)));
+        HIPCHK(off.alloc((size_t)(K + 1) * sizeof(uint32_t)));
         HIPCHK(hipMemcpyAsync(rb.keys_a(), assign, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
         uint32_t *ks, *vs;
         if ((r2 = rb.sort(n, bits_for(K), false, &ks, &vs, st))) return r2;
@@ -174,7 +174,7 @@ extern "C" int ivf_kmeans(const float *x, int64_t n, int D, int64_t K, int iters
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     ArgminCtx ctx;
     RadixBufs rb;
-    DevTmp lab, dist;
+    DevTmp lab, dist, off;
     auto body = [&]() -> int {
         int r2;
         take_rows_kernel<<<dim3(grid_for(K * D)), dim3(256), 0, st>>>(x, D, 0, D, init_idx, K, centroids, D, 0);
@@ -182,10 +182,9 @@ extern "C" int ivf_kmeans(const float *x, int64_t n, int D, int64_t K, int iters
         if (iters == 0) return IVF_OK;
         if ((r2 = ctx.init(K, D, n, iters > 1))) return r2;
         if ((r2 = rb.init(n))) return r2;
-        HIPCHK(hipMalloc(&lab.p, (size_t)n * sizeof(int32_t)));
-        HIPCHK(hipMalloc(&dist.p, (size_t)n * sizeof(float)));
-        DevTmp off;
-        HIPCHK(hipMalloc(&off.p, (size_t)(K + 1) * sizeof(uint32_t)));
+        HIPCHK(lab.alloc((size_t)n * sizeof(int32_t)));
+        HIPCHK(dist.alloc((size_t)n * sizeof(float)));
+        HIPCHK(off.alloc((size_t)(K + 1) * sizeof(uint32_t)));
         const int bits = bits_for(K);
         for (int it = 0; it < iters; ++it) {
             if ((r2 = ctx.set_centroids(centroids, st))) return r2;
@@ -264,10 +263,10 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
         if (iters == 0) return rounds(true);
         int r2;
         const size_t state_words = 2 + (size_t)M * 256, words = (size_t)pq_sum_slices(n) * M * 256;
-        HIPCHK(hipMalloc(&codes.p, (size_t)n * M));
-        HIPCHK(hipMalloc(&state.p, state_words * sizeof(uint32_t)));
-        HIPCHK(hipMalloc(&psum.p, words * ds * sizeof(double)));
-        HIPCHK(hipMalloc(&pcnt.p, words * sizeof(uint32_t)));
+        HIPCHK(codes.alloc((size_t)n * M));
+        HIPCHK(state.alloc(state_words * sizeof(uint32_t)));
+        HIPCHK(psum.alloc(words * ds * sizeof(double)));
+        HIPCHK(pcnt.alloc(words * sizeof(uint32_t)));
         fill_u64_kernel<<<dim3(grid_for(state_words / 2)), dim3(256), 0, st>>>(static_cast<unsigned long long *>(state.p), state_words / 2, 0ull);
         LAUNCHCHK("fill_u64_kernel");
         if ((r2 = launch_absmax(E, n * D, static_cast<uint32_t *>(state.p), st))) return r2;
@@ -275,7 +274,7 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
         // (infinities and values that are not numbers have to find their way into the means: by the segment sums too)
         if (seen[0] < 0x7F800000u && !seen[1]) return IVF_OK;
         if ((r2 = rb.init(n))) return r2;
-        HIPCHK(hipMalloc(&off.p, 257 * sizeof(uint32_t)));
+        HIPCHK(off.alloc(257 * sizeof(uint32_t)));
         return rounds(false);
     };
     int rc = body();
@@ -296,9 +295,9 @@ extern "C" int ivf_lloyd_1d(const float *t, int64_t n, int iters, float *table, 
     auto body = [&]() -> int {
         int r2;
         if ((r2 = rb.init(n))) return r2;
-        HIPCHK(hipMalloc(&sorted.p, (size_t)n * sizeof(float)));
-        HIPCHK(hipMalloc(&off.p, 257 * sizeof(uint32_t)));
-        HIPCHK(hipMalloc(&sum.p, 256 * sizeof(double)));
+        HIPCHK(sorted.alloc((size_t)n * sizeof(float)));
+        HIPCHK(off.alloc(257 * sizeof(uint32_t)));
+        HIPCHK(sum.alloc(256 * sizeof(double)));
         float *s = static_cast<float *>(sorted.p);
         float_keys_kernel<<<dim3(grid_for(n)), dim3(256), 0, st>>>(t, n, rb.keys_a());
         LAUNCHCHK("float_keys_kernel");
@@ -344,10 +343,10 @@ extern "C" int ivf_learn_alpha(const float *centroids, int64_t K, int D, const i
     auto body = [&]() -> int {
         int r2;
         if ((r2 = rb.init(n))) return r2;
-        HIPCHK(hipMalloc(&stat.p, (size_t)(n > 0 ? n : 1) * 2 * sizeof(double)));
-        HIPCHK(hipMalloc(&off.p, (size_t)(K + 1) * sizeof(uint32_t)));
-        HIPCHK(hipMalloc(&nd.p, (size_t)K * 2 * sizeof(double)));
-        HIPCHK(hipMalloc(&tot.p, 2 * sizeof(double)));
+        HIPCHK(stat.alloc((size_t)(n > 0 ? n : 1) * 2 * sizeof(double)));
+        HIPCHK(off.alloc((size_t)(K + 1) * sizeof(uint32_t)));
+        HIPCHK(nd.alloc((size_t)K * 2 * sizeof(double)));
+        HIPCHK(tot.alloc(2 * sizeof(double)));
         HIPCHK(hipMemsetAsync(stat.p, 0, (size_t)(n > 0 ? n : 1) * 2 * sizeof(double), st));
         HIPCHK(hipMemsetAsync(off.p, 0, (size_t)(K + 1) * sizeof(uint32_t), st));
         if (n > 0) {
@@ -390,8 +389,8 @@ extern "C" int ivf_neighbours(const float *centroids, int64_t K, int D, int L, i
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const int P = L + 1;
     DevTmp tid, td;
-    HIPCHK(hipMalloc(&tid.p, (size_t)K * P * sizeof(int32_t)));
-    HIPCHK(hipMalloc(&td.p, (size_t)K * P * sizeof(float)));
+    HIPCHK(tid.alloc((size_t)K * P * sizeof(int32_t)));
+    HIPCHK(td.alloc((size_t)K * P * sizeof(float)));
     rc = coarse_topk_tiled(centroids, K, D, centroids, K, P, static_cast<int32_t *>(tid.p), static_cast<float *>(td.p), st);
     if (!rc) {
         neighbour_rows_kernel<<<dim3((unsigned)K), dim3(64), (size_t)P * sizeof(unsigned long long), st>>>(
