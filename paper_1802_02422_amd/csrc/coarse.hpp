@@ -240,6 +240,19 @@ __device__ __forceinline__ bool tile_of_block(int64_t b, int tiles_q, int64_t &q
     return tq < tiles_q;
 }
 
+// The distance GEMMs deal the other way round: XCD x = b % 8 owns the centroid groups (of whatever many tiles) x, x + 8,
+// ... and takes each of them through all query tiles, which are few: a group comes from memory once for the whole chip,
+// and all XCDs have work however few the query tiles are.
+__device__ __forceinline__ void group_of_block(int64_t b, int tiles_q, int64_t &tq, int64_t &group)
+{
+    const int64_t local = b / N_XCD;
+    tq = local % tiles_q;
+    group = local / tiles_q * N_XCD + b % N_XCD;
+}
+
+// workgroups of a launch that deals this way
+inline int64_t group_grid(int64_t tiles_q, int64_t groups) { return (groups + N_XCD - 1) / N_XCD * N_XCD * tiles_q; }
+
 constexpr int SLD = 64 + 4;   // row stride (floats) of a wavefront's 32x64 output staging area in LDS
 
 // Epilogue of one 32-query x 64-centroid block held by a wavefront as two accumulators
@@ -349,7 +362,7 @@ __host__ __device__ inline int64_t dt_stride(int64_t K) { return K; }
 // Dt[q][j] = max(0, qn[q] + cn[j] - 2 <Q[q], C[j]>), and bm[q][b] = the minimum
 // of Dt[q][64b .. 64b+63] (each wavefront's 64-centroid quadrant gives one block
 // minimum per query).  qsi[q] and csi[0] are the inverse operand scales.  The
-// grid has 8 * ceil(tiles_q / 8) * tiles_c workgroups.
+// grid has group_grid(tiles_q, tiles_c) workgroups.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void coarse_gemm_kernel(
     const _Float16 *__restrict__ Qp, const float *__restrict__ qn, const float *__restrict__ qsi, int64_t nq,
     const _Float16 *__restrict__ Cp, const float *__restrict__ cn, const float *__restrict__ csi, int64_t K,
@@ -362,7 +375,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     __shared__ __attribute__((aligned(16))) float cns[GT];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int64_t q0, c0;
-    if (!tile_of_block(blockIdx.x, tiles_q, q0, c0)) return;
+    group_of_block(blockIdx.x, tiles_q, q0, c0);
+    q0 *= GT;
+    c0 *= GT;
+    if (c0 >= K) return;
     const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
     const int l32 = lane & 31, h = lane >> 5;
     if (threadIdx.x < GT) cns[threadIdx.x] = c0 + threadIdx.x < K ? cn[c0 + threadIdx.x] : 0.f;
@@ -452,19 +468,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int l32 = lane & 31, h = lane >> 5;
     const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
 
-    // workgroup -> (query tile, range of centroid tiles): XCD x = b % 8 owns query tiles x, x+8, ...;
-    // step t of the workgroup is centroid tile tb + t
-    const int tq_per = (tiles_q + N_XCD - 1) / N_XCD;
-    const int xcd = (int)(blockIdx.x % N_XCD);
-    const int64_t local = blockIdx.x / N_XCD;
-    const int tq = (int)(local % tq_per) * N_XCD + xcd;
-    if (tq >= tiles_q) return;
-    const int tb = (int)(local / tq_per) * tiles_per_wg;    // a multiple of SWEEP_BMC (the host's tiles_per_wg is)
+    // workgroup -> (query tile, range of centroid tiles); step t of the workgroup is centroid tile tb + t
+    int64_t tq, group;
+    group_of_block(blockIdx.x, tiles_q, tq, group);
+    const int tb = (int)(group * tiles_per_wg);             // a multiple of SWEEP_BMC (the host's tiles_per_wg is)
     const int t_begin = 0;
     int t_end = tb < tiles_c ? tiles_c - tb : 0;            // steps inside the matrix
     if (t_end > tiles_per_wg) t_end = tiles_per_wg;
     if (t_begin >= t_end) return;
-    const int64_t q0 = (int64_t)tq * GT;
+    const int64_t q0 = tq * GT;
 
     // this wave's two copies per stage: rows 32 wave + 16 n + lane / 4 of the centroid tile
     const int rl = wave * 32 + (lane >> 2);
@@ -1434,6 +1446,182 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 {
     extern __shared__ __attribute__((aligned(16))) int ps_dyn[];
     probe_select_lds_body(Dt, ldt, bm, K, nb, P, probe_id, probe_d, blockIdx.x, ps_dyn);
+}
+
+// ---- The selection by one wavefront per query, for small tables ----
+// The workgroup selection above spends its time in barriers when there are few keys for its 1024 threads (10 000 queries x
+// 65 536 centroids, P = 64: 0.44 ms, 0.11 here).  With the keys of a query in the registers of one wavefront the nsel-th
+// smallest is found by a binary search over the key's bits, a comparison and a population count a register and bit.
+
+// pivot and need such that the nsel smallest keys are those below pivot and `need` of those equal to it (the first ones in
+// order).  Keys of 0xFFFFFFFF are no keys; nsel is at most the number of keys.
+template <int R>
+__device__ __forceinline__ void wave_select(const uint32_t (&k)[R], uint32_t nsel, uint32_t &pivot, uint32_t &need)
+{
+    uint32_t lo = 0xFFFFFFFFu, hi = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        lo = k[r] < lo ? k[r] : lo;
+        hi = k[r] != 0xFFFFFFFFu && k[r] > hi ? k[r] : hi;
+    }
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        const uint32_t a = __shfl_xor(lo, o, WAVE), b = __shfl_xor(hi, o, WAVE);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+    const int top = lo < hi ? 31 - __builtin_clz(lo ^ hi) : -1;   // highest bit in which keys differ
+    uint32_t t = top >= 0 ? hi & ~((2u << top) - 1u) : lo;
+    uint32_t below = 0;                                        // keys < t
+    for (int bit = top; bit >= 0; --bit) {
+        const uint32_t trial = t | 1u << bit;
+        uint32_t c = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(k[r] < trial));
+        if (c <= nsel) {
+            t = trial;
+            below = c;
+            if (c == nsel) break;
+        }
+    }
+    pivot = t;
+    need = nsel - below;
+}
+
+// Calls emit(position among the selected, r, key) for the selected keys in the order r * 64 + lane.
+template <int R, class EmitFn>
+__device__ __forceinline__ void wave_emit(const uint32_t (&k)[R], uint32_t pivot, uint32_t need, EmitFn emit)
+{
+    uint32_t out = 0, eq_seen = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint64_t eqm = __ballot(k[r] == pivot && need > 0);
+        const uint32_t eq_rank = eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u));
+        const bool sel = k[r] < pivot || (k[r] == pivot && eq_rank < need);
+        const uint64_t m = __ballot(sel);
+        if (sel) emit(out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)), r, k[r]);
+        out += (uint32_t)__popcll(m);
+        eq_seen += (uint32_t)__popcll(eqm);
+    }
+}
+
+constexpr int PW_K_DIRECT = 2048;   // up to here the whole row of distances goes into registers
+constexpr int PW_NB_MAX = 1024;     // up to here the block minima do (and P <= nb, P <= PW_P_MAX)
+constexpr int PW_P_MAX = 64;
+constexpr int PW_CAP = 512;         // survivors held in LDS; more (duplicated centroids) are searched in memory
+
+// Four queries a workgroup.  Same three steps and the same result as probe_select_kernel.
+template <bool DIRECT>
+__global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__restrict__ Dt, int64_t ldt, const float *__restrict__ bm,
+                                                                int64_t K, int nb, int P, int64_t nq, int32_t *__restrict__ probe_id,
+                                                                float *__restrict__ probe_d)
+{
+    constexpr int R = DIRECT ? PW_K_DIRECT / WAVE : PW_NB_MAX / WAVE;
+    __shared__ int blist_all[DIRECT ? 1 : 4][DIRECT ? 1 : 2 * PW_P_MAX];
+    __shared__ uint32_t sk_all[DIRECT ? 1 : 4][DIRECT ? 1 : PW_CAP];
+    __shared__ int si_all[DIRECT ? 1 : 4][DIRECT ? 1 : PW_CAP];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t q = (int64_t)blockIdx.x * 4 + wave;
+    if (q >= nq) return;                                       // (whole wavefronts; no barrier follows)
+    const float *row = Dt + q * ldt;
+    int32_t *oid = probe_id + q * P;
+    float *od = probe_d + q * P;
+    uint32_t k[R], pivot, need;
+    const int n = DIRECT ? (int)K : nb;
+    const float *src = DIRECT ? row : bm + q * nb;
+#pragma unroll
+    for (int r = 0; r < R; ++r) k[r] = r * WAVE + lane < n ? float_key(src[r * WAVE + lane]) : 0xFFFFFFFFu;
+    wave_select<R>(k, (uint32_t)P, pivot, need);
+    if (DIRECT) {
+        wave_emit<R>(k, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
+            oid[pos] = r * WAVE + lane;
+            od[pos] = key_float(key);
+        });
+        return;
+    }
+    // blocks that may hold one of the P closest: minimum below pivot, or (first P of them) equal to it; with need == 0
+    // the P-th smallest minimum itself lies below pivot, and so do the P closest distances
+    int *blist = blist_all[wave];
+    uint32_t *sk = sk_all[wave];
+    int *si = si_all[wave];
+    uint32_t nflag = 0;
+    wave_emit<R>(k, pivot, need > 0 ? (uint32_t)P : 0u, [&](uint32_t pos, int r, uint32_t) { blist[pos] = r * WAVE + lane; });
+#pragma unroll
+    for (int r = 0; r < R; ++r) nflag += (uint32_t)__popcll(__ballot(k[r] < pivot));
+    if (need > 0) {
+        uint32_t eq = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) eq += (uint32_t)__popcll(__ballot(k[r] == pivot));
+        nflag += eq < (uint32_t)P ? eq : (uint32_t)P;
+    }
+    wave_sync();
+    const uint32_t lim = need > 0 ? pivot : pivot - 1u;        // the P closest have keys of at most lim
+    uint32_t total = 0;
+    for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
+        uint32_t kv[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int64_t c = f0 + j < nflag ? (int64_t)blist[f0 + j] * BMW + lane : K;
+            kv[j] = c < K ? float_key(row[c]) : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const bool sel = kv[j] <= lim && kv[j] != 0xFFFFFFFFu;
+            const uint64_t m = __ballot(sel);
+            const uint32_t o = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (sel && o < (uint32_t)PW_CAP) {
+                sk[o] = kv[j];
+                si[o] = blist[f0 + j] * BMW + lane;
+            }
+            total += (uint32_t)__popcll(m);
+        }
+    }
+    wave_sync();
+    if (total <= (uint32_t)PW_CAP) {
+        uint32_t s[PW_CAP / WAVE];
+#pragma unroll
+        for (int r = 0; r < PW_CAP / WAVE; ++r) s[r] = r * WAVE + lane < (int)total ? sk[r * WAVE + lane] : 0xFFFFFFFFu;
+        wave_select<PW_CAP / WAVE>(s, (uint32_t)P, pivot, need);
+        wave_emit<PW_CAP / WAVE>(s, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
+            oid[pos] = si[r * WAVE + lane];
+            od[pos] = key_float(key);
+        });
+        return;
+    }
+    // very many distances at or below the threshold: the same search, reading them again for every bit
+    auto key_at = [&](uint32_t f) {
+        const int64_t c = (int64_t)blist[f] * BMW + lane;
+        return c < K ? float_key(row[c]) : 0xFFFFFFFFu;
+    };
+    uint32_t t = 0, below = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t trial = t | 1u << bit;
+        uint32_t c = 0;
+        for (uint32_t f = 0; f < nflag; ++f) c += (uint32_t)__popcll(__ballot(key_at(f) < trial));
+        if (c <= (uint32_t)P) {
+            t = trial;
+            below = c;
+            if (c == (uint32_t)P) break;
+        }
+    }
+    const uint32_t rest = (uint32_t)P - below;
+    uint32_t out = 0, eq_seen = 0;
+    for (uint32_t f = 0; f < nflag; ++f) {
+        const uint32_t key = key_at(f);
+        const uint64_t eqm = __ballot(key == t);
+        const uint32_t eq_rank = eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u));
+        const bool sel = key < t || (key == t && eq_rank < rest);
+        const uint64_t m = __ballot(sel);
+        if (sel) {
+            const uint32_t o = out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            oid[o] = blist[f] * BMW + lane;
+            od[o] = key_float(key);
+        }
+        out += (uint32_t)__popcll(m);
+        eq_seen += (uint32_t)__popcll(eqm);
+    }
 }
 
 }  // namespace ivf

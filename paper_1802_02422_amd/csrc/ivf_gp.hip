@@ -222,6 +222,10 @@ int pack_rows(const float *X, int64_t n, int D, uint32_t *gmax, _Float16 *P, flo
     return IVF_OK;
 }
 
+// Tiles from which the swept GEMM is taken: below, one tile a workgroup spreads them over more of the chip (100 queries x
+// 1024 centroids: 40 us as one workgroup's sweep, 16 as eight).
+constexpr int64_t SWEEP_MIN_TILES = 2048;
+
 int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t nq, const _Float16 *Cp,
                   const float *cn, const float *csi, int64_t K, int Dp, float *Dt, float *bm, hipStream_t st)
 {
@@ -237,19 +241,18 @@ int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t
         LAUNCHCHK("coarse_gemm_skinny_kernel");
         return IVF_OK;
     }
-    int tiles_q = (int)((nq + GT - 1) / GT);
-    int64_t tiles_c = (K + GT - 1) / GT;
-    int64_t grid = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD * tiles_c;
-    if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
+    const int tiles_q = (int)((nq + GT - 1) / GT);
+    const int64_t tiles_c = (K + GT - 1) / GT;
     const int stages = Dp / DK;
-    if ((stages == 6 || stages == 8) && K % GT == 0) {
+    if ((stages == 6 || stages == 8) && K % GT == 0 && (int64_t)tiles_q * tiles_c >= SWEEP_MIN_TILES) {
         // Query tile held in registers, centroid tiles swept.  The kernel works on whole tiles: the
         // rows of a partial last query tile are computed too, into the padding every per-query
-        // buffer of the coarse stage carries up to a multiple of the tile height.
-        const int per_wg = 64;
-        static_assert(per_wg % SWEEP_BMC == 0, "a workgroup's first tile starts a 64-byte piece of the block minima");
-        const int64_t groups = (tiles_c + per_wg - 1) / per_wg;
-        const int64_t g2 = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD * groups;
+        // buffer of the coarse stage carries up to a multiple of the tile height.  Two workgroups fit a
+        // compute unit: shorter sweeps where 64 tiles each would leave some without work.
+        int per_wg = 64;
+        static_assert(64 % SWEEP_BMC == 0, "a workgroup's first tile starts a 64-byte piece of the block minima");
+        while (per_wg > SWEEP_BMC && tiles_q * ((tiles_c + per_wg - 1) / per_wg) < 1024) per_wg /= 2;
+        const int64_t g2 = group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg);
         if (g2 >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
         if (stages == 6)
             coarse_gemm_sweep_kernel<6><<<dim3((unsigned)g2), dim3(256), 0, st>>>(xp, xn, xsi, (int64_t)tiles_q * GT, Cp, cn, csi, K, Dt, ldt, bm, nb, tiles_q, (int)tiles_c, per_wg);
@@ -258,9 +261,20 @@ int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t
         LAUNCHCHK("coarse_gemm_sweep_kernel");
         return IVF_OK;
     }
+    const int64_t grid = group_grid(tiles_q, tiles_c);
+    if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
     coarse_gemm_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(xp, xn, xsi, nq, Cp, cn, csi, K, Dp, Dt, ldt, bm, nb, tiles_q);
     LAUNCHCHK("coarse_gemm_kernel");
     return IVF_OK;
+}
+
+// whether probe_select_wave_kernel takes the selection of P of K: one wavefront reads the P flagged blocks, 16 at a
+// time, which takes it longer than a workgroup's barriers where P is large (2000 queries x 65 536, P = 256: 0.16 ms)
+bool wave_select_fits(int64_t K, int P)
+{
+    if (K <= PW_K_DIRECT) return true;
+    const int64_t nb = (K + BMW - 1) / BMW;
+    return nb <= PW_NB_MAX && P <= nb && P <= PW_P_MAX;
 }
 
 int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K, int P, int32_t *pid,
@@ -268,6 +282,13 @@ int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K,
 {
     const int nb = (int)((K + BMW - 1) / BMW);
     const size_t lds = (size_t)2 * P * sizeof(int);
+    if (wave_select_fits(K, P)) {            // a wavefront per query, keys in registers
+        const dim3 grid((unsigned)((nq + 3) / 4));
+        if (K <= PW_K_DIRECT) probe_select_wave_kernel<true><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
+        else probe_select_wave_kernel<false><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
+        LAUNCHCHK("probe_select_wave_kernel");
+        return IVF_OK;
+    }
     if (P <= PS_P_MAX && nb <= PS_NB_MAX) {   // keys in LDS
         const size_t lds2 = ((size_t)2 * P + 3 + (nb > 2 * PS_CAP ? nb : 2 * PS_CAP)) * sizeof(int);
         if (lds2 > 48 * 1024)
@@ -310,7 +331,7 @@ struct SearchPlan {
 int64_t dt_rows(int64_t n, int64_t K, int Dp)
 {
     const int stages = Dp / DK;
-    const bool sweep = n > 2 * SKQ && (stages == 6 || stages == 8) && K % GT == 0;
+    const bool sweep = n > 2 * SKQ && (stages == 6 || stages == 8) && K % GT == 0;   // (with enough tiles)
     return sweep ? (n + GT - 1) / GT * GT : n;
 }
 
@@ -319,13 +340,15 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, int k, int64_t til
     SearchPlan pl;
     pl.tile = tile;
     pl.S = S;
-    // workgroups per query in the scan: fill the chip when the batch is small, but with at most 8 per
+    // Workgroups per query in the scan: fill the chip when the batch is small, but with at most 8 per
     // query: every workgroup hands 4 k candidates to the final k-select, whose time grows with them
     // faster than the scan's shrinks (one query on the 100M-point workload, scan + k-select in us:
-    // 17 + 9 with 2 workgroups, 12 + 9 with 4, 10.5 + 10 with 8, 10 + 12 / 14 / 20 with 16 / 32 / 64)
+    // 17 + 9 with 2 workgroups, 12 + 9 with 4, 10.5 + 10 with 8, 10 + 12 / 14 / 20 with 16 / 32 / 64), and no
+    // more than there are batches of descriptors for their four wavefronts: a further workgroup only loads the
+    // table again (333 queries, S = 288: scan + k-select 47 us with 7, 28 with 2).
     int nsplit = (int)((2048 + tile - 1) / tile);
     if (nsplit > 8) nsplit = 8;
-    if (nsplit > (S + 15) / 16) nsplit = (S + 15) / 16;
+    if (nsplit > (S + SCAN_WAVES * WAVE - 1) / (SCAN_WAVES * WAVE)) nsplit = (S + SCAN_WAVES * WAVE - 1) / (SCAN_WAVES * WAVE);
     while (nsplit > 1 && (int64_t)nsplit * SCAN_WAVES * k > 8192) --nsplit;
     if (nsplit < 1) nsplit = 1;
     pl.nsplit = nsplit;
@@ -534,19 +557,42 @@ int check_search_args(const ivf_index *ix, const float *queries, int64_t nq, int
 }
 
 // Dynamic LDS sizes of the stage kernels; raises the kernels' limits where they exceed the default window.
-struct LdsPlan { size_t scan, merge, sp, ssp; };   // ssp: the fused selection + scoring launch of small batches
+struct LdsPlan { size_t scan, merge, sp, ssp; };   // ssp: the fused selection + scoring launch
+
+// How the scoring of a search runs.  SCORE_STREAM_*: the whole row of distances through LDS, where it is at most as many
+// bytes as half the 128-byte lines that P L gathers touch (10 000 queries, K = 65 536: P L = 4096 0.95 -> 0.81 ms; 2000 queries
+// with P L = 16 384, selection included, 0.99 -> 0.78); SCORE_FUSED: selection and scoring in one launch of 1024 threads a query (large tables, where
+// the selection needs a workgroup of its own too); SCORE_GATHER: the rest.
+enum ScoreMode { SCORE_GATHER, SCORE_FUSED, SCORE_STREAM_512, SCORE_STREAM_1024 };
+constexpr int STREAM_512 = 8192, STREAM_1024 = 16384;   // distances in LDS at a time (512 / 1024 threads)
+
+ScoreMode score_mode(int64_t K, int P, int L)
+{
+    const int64_t PL = (int64_t)P * L, nb = (K + BMW - 1) / BMW;
+    if (K <= 16 * PL && PL <= 16384) return PL <= 4096 ? SCORE_STREAM_512 : SCORE_STREAM_1024;
+    if (P <= PS_P_MAX && nb <= PS_NB_MAX && PL > 4096) return SCORE_FUSED;
+    return SCORE_GATHER;
+}
 
 int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l)
 {
     const int64_t PL = (int64_t)P * ix->L;
+    const ScoreMode mode = score_mode(ix->K, P, ix->L);
     l.scan = (size_t)SCAN_WAVES * pool_capacity(k) * sizeof(uint64_t);   // dynamic part: the pools
     l.merge = ((size_t)pl.merge_n + pl.merge_pow2) * sizeof(uint64_t);
     l.sp = (size_t)(PL + 3 * P) * sizeof(uint32_t);
     if (l.sp < (size_t)ix->D * sizeof(float)) l.sp = (size_t)ix->D * sizeof(float);   // the table workgroups hold a query
     if (l.sp > 154 * 1024)   // one workgroup holds a query's scores in the 160 KB of LDS, beside 5 KB of static data
         return fail(IVF_EINVAL, "nprobe*L + 3*nprobe = %lld words exceed the LDS of one workgroup", (long long)(PL + 3 * P));
+    if (mode == SCORE_STREAM_512 || mode == SCORE_STREAM_1024) {
+        const int64_t part = mode == SCORE_STREAM_512 ? STREAM_512 : STREAM_1024;
+        const size_t need = (size_t)((PL > part + 4 ? PL : part + 4) + 3 * P) * sizeof(uint32_t);
+        if (l.sp < need) l.sp = need;
+    }
     if (l.sp > 48 * 1024) {
-        const void *fn = PL > 16384 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 8>)
+        const void *fn = mode == SCORE_STREAM_512 ? reinterpret_cast<const void *>(&score_prune_kernel<512, 2, STREAM_512>)
+                         : mode == SCORE_STREAM_1024 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 4, STREAM_1024>)
+                         : PL > 16384 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 8>)
                          : PL > 4096 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 4>)
                                      : reinterpret_cast<const void *>(&score_prune_kernel<256, 4>);
         HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.sp));
@@ -555,7 +601,7 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
         const int64_t nb = (ix->K + BMW - 1) / BMW;
         const size_t sel = ((size_t)2 * P + 3 + (nb > 2 * PS_CAP ? nb : 2 * PS_CAP)) * sizeof(int);
         l.ssp = sel > l.sp ? sel : l.sp;
-        if (P <= PS_P_MAX && nb <= PS_NB_MAX && PL > 4096 && l.ssp > 48 * 1024) {
+        if (mode == SCORE_FUSED && l.ssp > 48 * 1024) {
             const void *fn = PL > 16384 ? reinterpret_cast<const void *>(&select_score_prune_kernel<8>)
                                         : reinterpret_cast<const void *>(&select_score_prune_kernel<4>);
             HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.ssp));
@@ -604,9 +650,8 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         // scoring launch (one workgroup per query does both): one kernel boundary less, and the selection
         // of one query (LDS and ALU work) runs while the other workgroup of the CU waits for its gathers.
         const int nb = (int)((K + BMW - 1) / BMW);
-        // (nprobe * L <= 4096 keeps the two launches: its scoring kernel runs 256 threads a workgroup, and
-        // measured as one launch of 1024 it is slower: 1.33 against 0.44 + 0.85 ms on the 10^7-point workloads)
-        const bool fused = P <= PS_P_MAX && nb <= PS_NB_MAX && PL > 4096;
+        const ScoreMode mode = score_mode(K, P, L);
+        const bool fused = mode == SCORE_FUSED;
         if (!fused && (rc = launch_probe_select(ws.dt, ws.bm, n, K, P, pid, pd, st))) return rc;
         if ((rc = mark(2))) return rc;
 
@@ -620,8 +665,8 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
             Qt = ws.qrot;
         }
         // stages 2-3 (one workgroup per query) and stage 4 (one more workgroup per query) in one launch
-#define IVF_SP_LAUNCH(BLK, MV)                                                                                     \
-    score_prune_kernel<BLK, MV><<<dim3((unsigned)(2 * n)), dim3(BLK), lds.sp, st>>>(                                \
+#define IVF_SP_LAUNCH(BLK, ...)                                                                                    \
+    score_prune_kernel<BLK, __VA_ARGS__><<<dim3((unsigned)(2 * n)), dim3(BLK), lds.sp, st>>>(                                \
         ws.dt, dt_stride(K), K, pid, pd, P, L, ix->nbr, ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, n, Qt, \
         D, M, ix->codebook, ws.lut)
 #define IVF_SSP_LAUNCH(MV)                                                                                          \
@@ -630,6 +675,8 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         n, Qt, D, M, ix->codebook, ws.lut)
         if (fused && PL > 16384) IVF_SSP_LAUNCH(8);
         else if (fused) IVF_SSP_LAUNCH(4);
+        else if (mode == SCORE_STREAM_512) IVF_SP_LAUNCH(512, 2, STREAM_512);
+        else if (mode == SCORE_STREAM_1024) IVF_SP_LAUNCH(1024, 4, STREAM_1024);
         else if (PL > 16384) IVF_SP_LAUNCH(1024, 8);
         else if (PL > 4096) IVF_SP_LAUNCH(1024, 4);
         else IVF_SP_LAUNCH(256, 4);

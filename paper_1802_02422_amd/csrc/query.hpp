@@ -50,8 +50,12 @@ __device__ __forceinline__ void lut_body(const float *__restrict__ Qrow, int D, 
 // table (lut_body, from Qt = the queries, rotated if the index has a rotation) while the first nq
 // gather and select; the two halves share nothing, and the table work hides under the gathers.
 // Dynamic LDS must also hold D floats.
+// STREAM > 0: the query's whole row of the tile is read, STREAM distances at a time, into LDS (over the place of the keys,
+// which come after it), and the neighbours' distances are picked there: a gather costs a 128-byte line of the row for
+// each 4 bytes, so that with 16 P L >= K the row is the smaller number of bytes, and whole lines in order.  Dynamic LDS:
+// max(P*L, STREAM + 4) + 3 P words.
 // (the body of a scoring workgroup, for query q of the batch: also the second half of select_score_prune_kernel)
-template <int BLOCK, int MAXV>
+template <int BLOCK, int MAXV, int STREAM = 0>
 __device__ __forceinline__ void score_prune_body(
     const float *__restrict__ Dt, int64_t ldt, int64_t K, const int32_t *__restrict__ probe_id,
     const float *__restrict__ probe_d, int P, int L, const int32_t *__restrict__ nbr,
@@ -64,9 +68,10 @@ __device__ __forceinline__ void score_prune_body(
     __shared__ unsigned long long codes_total;
     const int PL = P * L;
     uint32_t *keys = dyn;
-    int32_t *pid = reinterpret_cast<int32_t *>(dyn + PL);
-    float *pd = reinterpret_cast<float *>(dyn + PL + P);
-    float *pa = reinterpret_cast<float *>(dyn + PL + 2 * P);
+    const int front = STREAM && PL < STREAM + 4 ? STREAM + 4 : PL;
+    int32_t *pid = reinterpret_cast<int32_t *>(dyn + front);
+    float *pd = reinterpret_cast<float *>(dyn + front + P);
+    float *pa = reinterpret_cast<float *>(dyn + front + 2 * P);
     const float *row = Dt + q * ldt;
     for (int p = threadIdx.x; p < P; p += BLOCK) {
         const int32_t r = probe_id[q * P + p];
@@ -76,13 +81,62 @@ __device__ __forceinline__ void score_prune_body(
     }
     if (threadIdx.x == 0) codes_total = 0;
     __syncthreads();
+    if constexpr (STREAM > 0) {
+        constexpr int U = 4 * MAXV;                      // items of a thread: threadIdx.x + u * BLOCK
+        uint32_t word[U];                                 // neighbour id, then the distance (found: bit u)
+        uint32_t found = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * BLOCK;
+            word[u] = 0xFFFFFFFFu;
+            if (i < PL) {
+                const int p = i / L;
+                word[u] = (uint32_t)nbr[(int64_t)pid[p] * L + (i - p * L)];
+            }
+        }
+        float *part = reinterpret_cast<float *>(keys);
+        const int skew = (int)((reinterpret_cast<uintptr_t>(row) >> 2) & 3);
+        for (int64_t c0 = 0; c0 < K; c0 += STREAM) {
+            const int n = K - c0 < STREAM ? (int)(K - c0) : STREAM;
+            if (c0) __syncthreads();                      // the previous part has been picked from
+            // 16-byte loads from the boundary at or before the part, `skew` floats of the row before (or of the part before)
+            // with it; what is left at the end one by one
+            const int whole = (n + skew) / 4;
+            const float4 *src = reinterpret_cast<const float4 *>(row + c0 - skew);
+            // (a register array that has all loads on their way before the first store took 0.45 ms more)
+#pragma unroll
+            for (int v = 0; v <= STREAM / 4 / BLOCK; ++v)
+                if ((int)threadIdx.x + v * BLOCK < whole) reinterpret_cast<float4 *>(part)[threadIdx.x + v * BLOCK] = src[threadIdx.x + v * BLOCK];
+            if ((int)threadIdx.x < n + skew - 4 * whole) part[4 * whole + threadIdx.x] = row[c0 - skew + 4 * whole + threadIdx.x];
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t at = word[u] - (uint32_t)c0;
+                if (!(found >> u & 1u) && at < (uint32_t)n) {
+                    word[u] = __float_as_uint(part[at + skew]);
+                    found |= 1u << u;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * BLOCK;
+            if (i < PL) {
+                const int p = i / L;
+                const float a = pa[p];
+                keys[i] = float_key(fmaf(a, __uint_as_float(word[u]), fmaf(1.f - a, pd[p], cst[(int64_t)pid[p] * L + (i - p * L)])));
+            }
+        }
+    } else {
 #pragma unroll 4
-    for (int i = threadIdx.x; i < PL; i += BLOCK) {
-        const int p = i / L, l = i - p * L;
-        const int64_t r = pid[p];
-        const float a = pa[p];
-        const float ds = row[nbr[r * L + l]];
-        keys[i] = float_key(fmaf(a, ds, fmaf(1.f - a, pd[p], cst[r * L + l])));
+        for (int i = threadIdx.x; i < PL; i += BLOCK) {
+            const int p = i / L, l = i - p * L;
+            const int64_t r = pid[p];
+            const float a = pa[p];
+            const float ds = row[nbr[r * L + l]];
+            keys[i] = float_key(fmaf(a, ds, fmaf(1.f - a, pd[p], cst[r * L + l])));
+        }
     }
     __syncthreads();
     auto key = [keys](int64_t i) { return keys[i]; };
@@ -126,8 +180,8 @@ __device__ __forceinline__ void score_prune_body(
     if (threadIdx.x == 0 && n_scanned) n_scanned[q] = (int64_t)codes_total;
 }
 
-template <int BLOCK, int MAXV>
-__global__ __launch_bounds__(BLOCK) void score_prune_kernel(
+template <int BLOCK, int MAXV, int STREAM = 0>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STREAM ? 8 : 1, 8))) void score_prune_kernel(
     const float *__restrict__ Dt, int64_t ldt, int64_t K, const int32_t *__restrict__ probe_id,
     const float *__restrict__ probe_d, int P, int L, const int32_t *__restrict__ nbr,
     const float *__restrict__ cst, const float *__restrict__ alpha, int S,
@@ -142,7 +196,7 @@ __global__ __launch_bounds__(BLOCK) void score_prune_kernel(
         lut_body<BLOCK>(Qt + ql * D, D, M, codebook, lut + ql * (int64_t)M * 256, reinterpret_cast<float *>(dyn));
         return;
     }
-    score_prune_body<BLOCK, MAXV>(Dt, ldt, K, probe_id, probe_d, P, L, nbr, cst, alpha, S, sub_info, desc, kept_sub, n_scanned,
+    score_prune_body<BLOCK, MAXV, STREAM>(Dt, ldt, K, probe_id, probe_d, P, L, nbr, cst, alpha, S, sub_info, desc, kept_sub, n_scanned,
                                   blockIdx.x, dyn);
 }
 

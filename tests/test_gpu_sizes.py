@@ -219,3 +219,68 @@ def test_degenerate_scaling_factors(tiny, mode):
     assert (codes[same] == enc.codes[:n][same]).mean() >= 0.999
     if mode == "zero":
         assert (sub == 0).all()
+
+
+@pytest.mark.parametrize("nq,K,D", [(129, 128 * 1025, 96), (65, 128 * 2049, 100), (1100, 128 * 228, 128), (700, 128 * 340, 96), (70, 4224, 96), (200, 1000, 64)])
+def test_distance_gemm_over_few_query_tiles(nq, K, D):
+    """Few query tiles: the swept kernel in sweeps of 8 to 64 tiles whose last group is partial, and one tile a workgroup
+    below its threshold.  The three nearest centroids against fp64: ids where fp32 can tell, distances within the bound
+    that stage 1 is held to, 16 u (|q|^2 + max |c|^2)."""
+    print("case: few query tiles", nq, K, D, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(nq)
+    C = torch.randn(K, D, generator=g, device="cuda")
+    Q = torch.randn(nq, D, generator=g, device="cuda")
+    ids, d = ivf.ivf_coarse_topk(C, Q, 3)
+    c64, q64 = C.double(), Q.double()
+    cn, qn = (c64 * c64).sum(1), (q64 * q64).sum(1)
+    tol = 16 * 2.0 ** -24 * (qn + cn.max())
+    for a in range(0, nq, 64):
+        full = (cn[None] - 2 * q64[a:a + 64] @ c64.t() + qn[a:a + 64, None])
+        ref, at = full.topk(4, dim=1, largest=False)
+        got = torch.gather(full, 1, ids[a:a + 64].long())
+        t = tol[a:a + 64, None]
+        assert ((d[a:a + 64].double() - got).abs() <= t).all()
+        assert (got.sort(1)[0] <= ref[:, :3] + 2 * t).all()
+        clear = ref[:, 3] - ref[:, 2] > 2 * t[:, 0]
+        assert (ids[a:a + 64][clear].long() == at[clear, :3].sort(1)[0]).all()
+
+
+@pytest.mark.parametrize("nq,K,P", [(1, 1, 1), (5, 63, 63), (7, 64, 16), (300, 1024, 16), (3, 2048, 256), (66, 2000, 1500), (130, 2049, 33),
+                                    (70, 65536, 64), (5, 65473, 1), (9, 20000, 256), (33, 30000, 64)])
+@pytest.mark.parametrize("kind", ["plain", "ties"])
+def test_selection_of_the_nearest_by_distance_and_id(nq, K, P, kind):
+    """Whole-number vectors, so that every distance is exact: the P nearest by (distance, id), whatever the kernel, also
+    where thousands of centroids tie with the P-th (more than a wavefront's survivors, all of them equal)."""
+    print("case: selection", nq, K, P, kind, flush=True)
+    rng = np.random.default_rng(nq + K + P)
+    C = rng.integers(-9, 10, (K, 32)).astype(np.float32)
+    if kind == "ties":
+        C[rng.random(K) < 0.7] = C[0]
+    Q = rng.integers(-9, 10, (nq, 32)).astype(np.float32)
+    Q[0] = C[0]
+    if P == 1 and K > 1:                                             # (P = 1 is the assignment: another kernel)
+        P = 2
+    ids, d = ivf.ivf_coarse_topk(torch.from_numpy(C).cuda(), torch.from_numpy(Q).cuda(), P)
+    ids, d = ids.cpu().numpy(), d.cpu().numpy()
+    full = ((Q[:, None, :].astype(np.int64) - C[None].astype(np.int64)) ** 2).sum(-1) if nq * K < 3e6 else None
+    for q in range(nq):
+        row = full[q] if full is not None else ((Q[q].astype(np.int64) - C.astype(np.int64)) ** 2).sum(-1)
+        ref = np.sort(np.lexsort((np.arange(K), row))[:P])
+        assert (ids[q] == ref).all(), q
+        assert (d[q] == row[ref]).all()
+
+
+@pytest.mark.parametrize("K,L,nprobe,nq", [(512, 31, 20, 40), (8192, 16, 40, 33), (9001, 40, 70, 9), (12000, 64, 64, 17), (16385, 64, 100, 5), (3000, 63, 250, 70)])
+def test_scoring_from_whole_rows(K, L, nprobe, nq):
+    """Scoring that reads the whole row of distances through LDS: one and several parts, partial and unaligned last ones,
+    both workgroup sizes."""
+    print("case: scoring from rows", K, L, nprobe, nq, flush=True)
+    rng = np.random.default_rng(K + L)
+    D, M, N = 32, 8, 20000
+    X = rng.standard_normal((N, D)).astype(np.float32)
+    Xt = rng.standard_normal((max(K, 4000), D)).astype(np.float32)
+    ix = orc.build_index(Xt, X, K, L, M, np.arange(K), np.arange(256), kmeans_iters=0, pq_iters=1)
+    h = ivf.ivf_load_index(parity.to_device(ix))
+    Q = rng.standard_normal((nq, D)).astype(np.float32)
+    out = parity.run_gpu_search(h, Q, nprobe, 0.3, 20)
+    parity.check_search(ix, Q, nprobe, 0.3, 20, out).assert_ok()
