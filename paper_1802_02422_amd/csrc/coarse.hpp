@@ -790,13 +790,13 @@ __global__ __launch_bounds__(256) void coarse_argmin_kernel(
 }
 
 __global__ __launch_bounds__(256) void argmin_unpack_kernel(const unsigned long long *__restrict__ best,
-                                                            int64_t n, int32_t *__restrict__ out_id,
+                                                            int64_t n, int32_t missing, int32_t *__restrict__ out_id,
                                                             float *__restrict__ out_d)
-{
+{   // missing: the id of a row without any distance that is a number
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     unsigned long long k = best[i];
-    out_id[i] = (int32_t)(uint32_t)k;
+    out_id[i] = k == ~0ull ? missing : (int32_t)(uint32_t)k;
     if (out_d) out_d[i] = key_float((uint32_t)(k >> 32));
 }
 

@@ -878,6 +878,17 @@ namespace {
 
 std::atomic<int64_t> g_assign_short{0}, g_assign_exact{0};
 
+// Rows as fp16 with their lengths, for packed_rows(n) rows (see pack_hi_rows_kernel).
+int launch_pack_hi(const float *X, int64_t n, int D, uint32_t *gmax, _Float16 *H, float2 *len, hipStream_t st)
+{
+    int rc = launch_absmax(X, n * D, gmax, st);
+    if (rc) return rc;
+    const int64_t pad = packed_rows(n);
+    pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(X, n, pad, D, packed_dim(D), gmax, H, len);
+    LAUNCHCHK("pack_hi_rows_kernel");
+    return IVF_OK;
+}
+
 // Nearest-centroid assignment (P = 1) with buffers that live across calls: the packed centroid
 // table and the per-chunk query scratch.  No distance tile: the minimum is fused into the GEMM.
 //
@@ -964,20 +975,11 @@ struct ArgminCtx {
         all();
         return IVF_OK;
     }
-    int pack_hi(const float *X, int64_t n, uint32_t *gmax, _Float16 *H, float2 *len, hipStream_t st)
-    {
-        int rc = launch_absmax(X, n * D, gmax, st);
-        if (rc) return rc;
-        const int64_t pad = packed_rows(n);
-        pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(X, n, pad, D, Dp, gmax, H, len);
-        LAUNCHCHK("pack_hi_rows_kernel");
-        return IVF_OK;
-    }
     int set_centroids(const float *centroids_, hipStream_t st)
     {
         centroids = centroids_;
         exact_packed = false;
-        return shortlist ? pack_hi(centroids, K, words, chk, clen, st) : IVF_OK;
+        return shortlist ? launch_pack_hi(centroids, K, D, words, chk, clen, st) : IVF_OK;
     }
     // the exact one-pass kernel on m rows
     int run_exact(const float *x, int64_t m, hipStream_t st)
@@ -1018,7 +1020,7 @@ struct ArgminCtx {
         _Float16 *xh = xhk + (keep_rows ? q0 : 0) * (int64_t)Dp;
         float2 *xl = xlen + (keep_rows ? q0 : 0);
         int rc;
-        if (!(keep_rows && rows_packed) && (rc = pack_hi(xm, m, xw, xh, xl, st))) return rc;
+        if (!(keep_rows && rows_packed) && (rc = launch_pack_hi(xm, m, D, xw, xh, xl, st))) return rc;
         shortlist_tiles_kernel<<<dim3((unsigned)tiles_c), dim3(128), 0, st>>>(clen, K, Dp, words, xw,
                                                                               start, tile);
         LAUNCHCHK("shortlist_tiles_kernel");
@@ -1082,7 +1084,7 @@ struct ArgminCtx {
         return IVF_OK;
     }
     // out_id[i] = nearest centroid of x[i] by (distance, id), out_d[i] (may be NULL) its squared distance
-    int run(const float *x, int64_t n, int32_t *out_id, float *out_d, hipStream_t st)
+    int run(const float *x, int64_t n, int32_t *out_id, float *out_d, hipStream_t st, int32_t missing = -1)
     {
         int rc;
         for (int64_t q0 = 0; q0 < n; q0 += chunk) {
@@ -1090,7 +1092,7 @@ struct ArgminCtx {
             bool overflow = true;
             if (shortlist && (rc = run_shortlist(x, q0, m, &overflow, st))) return rc;
             if (overflow && (rc = run_exact(x + q0 * D, m, st))) return rc;
-            argmin_unpack_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, out_id + q0, out_d ? out_d + q0 : nullptr);
+            argmin_unpack_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, missing, out_id + q0, out_d ? out_d + q0 : nullptr);
             LAUNCHCHK("argmin_unpack_kernel");
         }
         rows_packed = true;
@@ -1231,6 +1233,97 @@ extern "C" int ivf_coarse_topk(const float *centroids, int64_t K, int D, const f
     return rc;
 }
 
+namespace {
+
+inline unsigned grid_for(int64_t n, int block = 256) { return (unsigned)((n + block - 1) / block); }
+
+// Stable sort of n (key, value) pairs by the low `bits` bits of the key, ascending: one
+// least-significant-digit pass per 8 bits.  vals_in == NULL: the values are the positions 0..n-1.
+// The sorted pairs end up in *keys_sorted / *vals_sorted, which point into the caller's two pairs
+// of buffers (a: first, b: second; keys_in may be the a buffer).  hist: 256 * nblocks words,
+// scan_tmp: temporary of rocprim's scan (scan_bytes).
+struct RadixBufs {
+    DevTmp ka, kb, va, vb, hist, base, scan;
+    size_t scan_bytes = 0;
+    int64_t nblocks = 0, cap = 0;
+    int init(int64_t n)
+    {
+        cap = n;
+        nblocks = (n + RS_TILE - 1) / RS_TILE;
+        if (nblocks < 1) nblocks = 1;
+        const size_t nb = (size_t)(n > 0 ? n : 1) * sizeof(uint32_t);
+        HIPCHK(ka.alloc(nb));
+        HIPCHK(kb.alloc(nb));
+        HIPCHK(va.alloc(nb));
+        HIPCHK(vb.alloc(nb));
+        HIPCHK(hist.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
+        HIPCHK(base.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
+        HIPCHK(rocprim::exclusive_scan(nullptr, scan_bytes, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p),
+                                       0u, (size_t)256 * nblocks, rocprim::plus<uint32_t>(), nullptr));
+        HIPCHK(scan.alloc(scan_bytes ? scan_bytes : 16));
+        return IVF_OK;
+    }
+    uint32_t *keys_a() { return static_cast<uint32_t *>(ka.p); }
+    // Sorts the n keys held in the a buffer (values: positions, or the a value buffer when
+    // have_vals).  Returns the buffers that hold the result.
+    int sort(int64_t n, int bits, bool have_vals, uint32_t **keys_sorted, uint32_t **vals_sorted, hipStream_t st)
+    {
+        if (n > cap) return fail(IVF_EINVAL, "radix sort buffers too small");
+        uint32_t *kin = static_cast<uint32_t *>(ka.p), *kout = static_cast<uint32_t *>(kb.p);
+        uint32_t *vin = static_cast<uint32_t *>(va.p), *vout = static_cast<uint32_t *>(vb.p);
+        const int64_t nbk = (n + RS_TILE - 1) / RS_TILE > 0 ? (n + RS_TILE - 1) / RS_TILE : 1;
+        bool first = !have_vals;
+        if (bits < 1) bits = 1;
+        for (int shift = 0; shift < bits; shift += 8) {
+            radix_hist_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(kin, n, shift, static_cast<uint32_t *>(hist.p), nbk);
+            LAUNCHCHK("radix_hist_kernel");
+            size_t sb = scan_bytes;
+            HIPCHK(rocprim::exclusive_scan(scan.p, sb, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p), 0u,
+                                           (size_t)256 * nbk, rocprim::plus<uint32_t>(), st));
+            radix_scatter_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(
+                kin, first ? nullptr : vin, n, shift, static_cast<uint32_t *>(base.p), nbk, kout, vout);
+            LAUNCHCHK("radix_scatter_kernel");
+            first = false;
+            std::swap(kin, kout);
+            std::swap(vin, vout);
+        }
+        *keys_sorted = kin;
+        *vals_sorted = vin;
+        return IVF_OK;
+    }
+};
+
+int bits_for(int64_t nbuckets)
+{
+    int b = 1;
+    while (b < 32 && (1ll << b) < nbuckets) ++b;
+    return b;
+}
+
+}  // namespace
+
+namespace {
+
+// The centroid table as fp16 rows, their lengths and the word with its largest magnitude (rows NULL: not packed).
+struct SubregionTable {
+    const _Float16 *rows = nullptr;
+    const float2 *len = nullptr;
+    const uint32_t *cmax = nullptr;
+};
+
+int launch_subregions(const ivf_index_desc *t, const float *x, int64_t n, const int32_t *region, const int32_t *perm,
+                      const SubregionTable &table, int32_t *out_sub, float *out_res, float *out_mu, hipStream_t st)
+{
+    const int nch = packed_dim(t->D) / 8;
+    auto kernel = nch == 4 ? &subregion_kernel<4> : nch == 8 ? &subregion_kernel<8> : nch == 12 ? &subregion_kernel<12> : &subregion_kernel<16>;
+    kernel<<<dim3((unsigned)((n + 4 * SUB_RUN - 1) / (4 * SUB_RUN))), dim3(256), 0, st>>>(
+        x, n, t->D, t->L, region, perm, t->centroids, table.rows, table.len, table.cmax, t->nbr, t->alpha, t->cs_dist2, out_sub, out_res, out_mu);
+    LAUNCHCHK("subregion_kernel");
+    return IVF_OK;
+}
+
+}  // namespace
+
 extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, const int32_t *region_in,
                           int32_t *out_region, int32_t *out_sub, uint8_t *out_codes,
                           uint8_t *out_const_byte, float *out_const_t, float *out_residual,
@@ -1246,14 +1339,22 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     if (n < 0 || n >= (1ll << 31)) return fail(IVF_EINVAL, "n out of range");
     if (n == 0) return IVF_OK;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    ArgminCtx ctx;                               // the assignment's, with the packed centroid table
+    DevTmp hi_mem;
+    SubregionTable table;
     if (region_in) {
         if (region_in != out_region)
             HIPCHK(hipMemcpyAsync(out_region, region_in, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     } else {
-        DevTmp d1;
-        HIPCHK(d1.alloc((size_t)n * sizeof(float)));
-        rc = ivf_coarse_topk(t->centroids, t->K, t->D, x, n, 1, out_region, static_cast<float *>(d1.p), hip_stream);
-        if (rc) return rc;
+        rc = ctx.init(t->K, t->D, n);
+        if (!rc) rc = ctx.set_centroids(t->centroids, st);
+        if (!rc) rc = ctx.run(x, n, out_region, nullptr, st, 0);   // (rows that are not numbers: a region that can be read)
+        if (rc) {
+            std::string keep = g_err;
+            (void)hipStreamSynchronize(st);   // the temporaries are released on return
+            g_err = keep;
+            return rc;
+        }
     }
     // PQ codes on the matrix units when the codebook fits LDS and D / M is one of the compiled
     // block widths; else by the wavefront-per-point kernel, which does everything.
@@ -1262,6 +1363,34 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     const bool fast = t->pq_codebook && cb_bytes <= 140 * 1024 && pq_width(ds);
     if (t->rotation && t->pq_codebook && !fast)
         return fail(IVF_EINVAL, "a rotation in front of the PQ needs D/M in {4, 6, 8, 12, 16} and a codebook that fits LDS");
+    // Subregions by fp16 rows with a bound where the rows fit registers; reading the table to pack it costs as much as
+    // the fp32 rows of K / 6 points with 64 neighbours do more than the fp16 ones.
+    const bool packed_rows_fit = packed_dim(t->D) <= 128 && t->L <= 64;
+    auto prepare_table = [&]() -> int {
+        if (!packed_rows_fit) return IVF_OK;
+        if (!region_in && ctx.shortlist) {
+            table = SubregionTable{ctx.chk, ctx.clen, ctx.words};
+        } else if (n * t->L >= 10 * t->K) {
+            const size_t rows = (size_t)packed_rows(t->K), row_bytes = (size_t)packed_dim(t->D) * sizeof(_Float16);
+            HIPCHK(hi_mem.alloc(rows * (row_bytes + sizeof(float2)) + sizeof(uint32_t)));
+            _Float16 *h = static_cast<_Float16 *>(hi_mem.p);
+            float2 *len = reinterpret_cast<float2 *>(reinterpret_cast<char *>(h) + rows * row_bytes);
+            uint32_t *word = reinterpret_cast<uint32_t *>(len + rows);
+            table = SubregionTable{h, len, word};
+            return launch_pack_hi(t->centroids, t->K, t->D, word, h, len, st);
+        }
+        return IVF_OK;
+    };
+    if (!fast && !t->pq_codebook) {
+        rc = prepare_table();
+        if (!rc && table.rows) rc = launch_subregions(t, x, n, out_region, nullptr, table, out_sub, out_residual, nullptr, st);
+        if (rc || table.rows) {
+            std::string keep = g_err;
+            const hipError_t e = hipStreamSynchronize(st);
+            g_err = keep;
+            return rc ? rc : e == hipSuccess ? IVF_OK : fail(IVF_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+        }
+    }
     if (!fast) {
         encode_kernel<<<dim3((unsigned)n), dim3(64), (size_t)4 * t->D * sizeof(float), st>>>(
             x, n, t->D, t->M, t->L, out_region, t->centroids, t->nbr, t->alpha, t->cs_dist2, t->pq_codebook,
@@ -1273,7 +1402,13 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     const int64_t chunk = n < (1ll << 20) ? n : (1ll << 20);
     const int D = t->D;
     DevTmp e, mu, erot, rt;
+    RadixBufs rb;
     auto body = [&]() -> int {
+        int r3 = prepare_table();
+        if (r3) return r3;
+        // regions found here come in the order of the points: sorted, the points of a region share its rows
+        const bool order = table.rows && !region_in && n >= 4 * t->K;
+        if (order && (r3 = rb.init(chunk))) return r3;
         if (!out_residual) HIPCHK(e.alloc((size_t)chunk * D * sizeof(float)));
         HIPCHK(mu.alloc((size_t)chunk * D * sizeof(float)));
         if (t->rotation) {   // the PQ sees R (x - mu), the per-point constant is taken with R mu
@@ -1286,10 +1421,21 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
         for (int64_t i0 = 0; i0 < n; i0 += chunk) {
             const int64_t m = n - i0 < chunk ? n - i0 : chunk;
             float *ec = out_residual ? out_residual + i0 * D : static_cast<float *>(e.p);
-            encode_kernel<<<dim3((unsigned)m), dim3(64), (size_t)4 * D * sizeof(float), st>>>(
-                x + i0 * D, m, D, t->M, t->L, out_region + i0, t->centroids, t->nbr, t->alpha, t->cs_dist2,
-                nullptr, nullptr, out_sub + i0, nullptr, nullptr, nullptr, ec, muc);
-            LAUNCHCHK("encode_kernel");
+            if (table.rows) {
+                const int32_t *perm = nullptr;
+                if (order) {
+                    HIPCHK(hipMemcpyAsync(rb.keys_a(), out_region + i0, (size_t)m * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+                    uint32_t *ks, *vs;
+                    if ((r3 = rb.sort(m, bits_for(t->K), false, &ks, &vs, st))) return r3;
+                    perm = reinterpret_cast<const int32_t *>(vs);
+                }
+                if ((r3 = launch_subregions(t, x + i0 * D, m, out_region + i0, perm, table, out_sub + i0, ec, muc, st))) return r3;
+            } else {
+                encode_kernel<<<dim3((unsigned)m), dim3(64), (size_t)4 * D * sizeof(float), st>>>(
+                    x + i0 * D, m, D, t->M, t->L, out_region + i0, t->centroids, t->nbr, t->alpha, t->cs_dist2,
+                    nullptr, nullptr, out_sub + i0, nullptr, nullptr, nullptr, ec, muc);
+                LAUNCHCHK("encode_kernel");
+            }
             const float *pe = ec;
             if (t->rotation) {
                 const unsigned rg = (unsigned)((m + ROT_ROWS - 1) / ROT_ROWS);

@@ -1,75 +1,6 @@
 // Host side of the index-time training entry points (included by ivf_gp.hip, after its helpers).
 #pragma once
 
-namespace {
-
-inline unsigned grid_for(int64_t n, int block = 256) { return (unsigned)((n + block - 1) / block); }
-
-// Stable sort of n (key, value) pairs by the low `bits` bits of the key, ascending: one
-// least-significant-digit pass per 8 bits.  vals_in == NULL: the values are the positions 0..n-1.
-// The sorted pairs end up in *keys_sorted / *vals_sorted, which point into the caller's two pairs
-// of buffers (a: first, b: second; keys_in may be the a buffer).  hist: 256 * nblocks words,
-// scan_tmp: temporary of rocprim's scan (scan_bytes).
-struct RadixBufs {
-    DevTmp ka, kb, va, vb, hist, base, scan;
-    size_t scan_bytes = 0;
-    int64_t nblocks = 0, cap = 0;
-    int init(int64_t n)
-    {
-        cap = n;
-        nblocks = (n + RS_TILE - 1) / RS_TILE;
-        if (nblocks < 1) nblocks = 1;
-        const size_t nb = (size_t)(n > 0 ? n : 1) * sizeof(uint32_t);
-        HIPCHK(ka.alloc(nb));
-        HIPCHK(kb.alloc(nb));
-        HIPCHK(va.alloc(nb));
-        HIPCHK(vb.alloc(nb));
-        HIPCHK(hist.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
-        HIPCHK(base.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
-        HIPCHK(rocprim::exclusive_scan(nullptr, scan_bytes, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p),
-                                       0u, (size_t)256 * nblocks, rocprim::plus<uint32_t>(), nullptr));
-        HIPCHK(scan.alloc(scan_bytes ? scan_bytes : 16));
-        return IVF_OK;
-    }
-    uint32_t *keys_a() { return static_cast<uint32_t *>(ka.p); }
-    // Sorts the n keys held in the a buffer (values: positions, or the a value buffer when
-    // have_vals).  Returns the buffers that hold the result.
-    int sort(int64_t n, int bits, bool have_vals, uint32_t **keys_sorted, uint32_t **vals_sorted, hipStream_t st)
-    {
-        if (n > cap) return fail(IVF_EINVAL, "radix sort buffers too small");
-        uint32_t *kin = static_cast<uint32_t *>(ka.p), *kout = static_cast<uint32_t *>(kb.p);
-        uint32_t *vin = static_cast<uint32_t *>(va.p), *vout = static_cast<uint32_t *>(vb.p);
-        const int64_t nbk = (n + RS_TILE - 1) / RS_TILE > 0 ? (n + RS_TILE - 1) / RS_TILE : 1;
-        bool first = !have_vals;
-        if (bits < 1) bits = 1;
-        for (int shift = 0; shift < bits; shift += 8) {
-            radix_hist_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(kin, n, shift, static_cast<uint32_t *>(hist.p), nbk);
-            LAUNCHCHK("radix_hist_kernel");
-            size_t sb = scan_bytes;
-            HIPCHK(rocprim::exclusive_scan(scan.p, sb, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p), 0u,
-                                           (size_t)256 * nbk, rocprim::plus<uint32_t>(), st));
-            radix_scatter_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(
-                kin, first ? nullptr : vin, n, shift, static_cast<uint32_t *>(base.p), nbk, kout, vout);
-            LAUNCHCHK("radix_scatter_kernel");
-            first = false;
-            std::swap(kin, kout);
-            std::swap(vin, vout);
-        }
-        *keys_sorted = kin;
-        *vals_sorted = vin;
-        return IVF_OK;
-    }
-};
-
-int bits_for(int64_t nbuckets)
-{
-    int b = 1;
-    while (b < 32 && (1ll << b) < nbuckets) ++b;
-    return b;
-}
-
-}  // namespace
-
 extern "C" int ivf_group(const int32_t *bucket, int64_t n, int64_t nbuckets, int32_t *perm, uint32_t *offsets,
                          void *hip_stream)
 {

@@ -67,6 +67,37 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// Sum and smallest value over the wave in 6 DPP steps each (see wave_inclusive_scan), no LDS: for values that
+// only enter a bound, where the order of the additions does not matter.
+__device__ __forceinline__ float wave_total(float v)
+{
+    v += __uint_as_float(dpp_or_zero<0x111, 0xf>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x112, 0xf>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x114, 0xf>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x118, 0xf>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x142, 0xa>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x143, 0xc>(__float_as_uint(v)));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), WAVE - 1));
+}
+
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_or_self(float v)
+{
+    const int u = (int)__float_as_uint(v);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(u, u, CTRL, ROW_MASK, 0xf, false));
+}
+
+__device__ __forceinline__ float wave_smallest(float v)
+{
+    v = fminf(v, dpp_or_self<0x111, 0xf>(v));
+    v = fminf(v, dpp_or_self<0x112, 0xf>(v));
+    v = fminf(v, dpp_or_self<0x114, 0xf>(v));
+    v = fminf(v, dpp_or_self<0x118, 0xf>(v));
+    v = fminf(v, dpp_or_self<0x142, 0xa>(v));
+    v = fminf(v, dpp_or_self<0x143, 0xc>(v));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), WAVE - 1));
+}
+
 // argmin over the wave of (value, index) pairs, lowest index on equal values;
 // every lane receives the winner.
 __device__ __forceinline__ void wave_argmin(float &v, int &idx)

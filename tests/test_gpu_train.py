@@ -266,3 +266,50 @@ def test_codeword_means_of_one_round(M, ds, n, small):
         np.add.at(a, code[:, m], np.abs(x))
         # one rounding to fp32; n additions in fp64 on either side; what the flag lets pass, 2^-29 of the mean
         assert (np.abs(got[m] - s / c) <= (2.0 ** -24 + 2.0 ** -28) * np.abs(s / c) + 2 * n * 2.0 ** -53 * a / c).all()
+
+
+@pytest.mark.parametrize("D,L,n,order", [(32, 64, 1000, "sorted"), (64, 5, 1601, "mixed"), (96, 63, 1000, "sorted"), (104, 64, 999, "mixed"),
+                                         (128, 17, 65, "sorted"), (96, 1, 4000, "mixed"), (96, 64, 3, "mixed")])
+@pytest.mark.parametrize("kind", ["plain", "tight", "flat"])
+def test_subregions_and_displacements(D, L, n, order, kind):
+    """Subregion of every point against fp64 scores of Eq. (7): the lowest within what fp32 can tell, the lowest index among
+    exact ties.  "tight": neighbours that differ by little more than fp16 resolves, where the fp32 scores have to decide;
+    "flat": half of the scaling factors are 0, every score of such a region ties.  With codebooks (codes and constants
+    follow) and without (displacements only)."""
+    print("case: subregions", D, L, n, order, kind, flush=True)
+    rng = np.random.default_rng(D + L + n)
+    K, M = max(L + 1, 70), 8 if D % 16 else 16
+    M = M if D // M in (4, 6, 8, 12, 16) else 8
+    C = rng.standard_normal((K, D))
+    if kind == "tight":
+        C = C[:1] + 2.0 ** -9 * C
+    C = C.astype(np.float32)
+    reg = rng.integers(0, K, n).astype(np.int32)
+    if order == "sorted":
+        reg.sort()
+    x = (C[reg] + 0.3 * (2.0 ** -9 if kind == "tight" else 1) * rng.standard_normal((n, D))).astype(np.float32)
+    nbr = np.stack([rng.permutation(np.delete(np.arange(K), r))[:L] for r in range(K)]).astype(np.int32)
+    cs = ((C[:, None].astype(np.float64) - C[nbr]) ** 2).sum(-1).astype(np.float32)
+    alpha = rng.uniform(0, 1, K).astype(np.float32)
+    if kind == "flat":
+        alpha[::2] = 0
+    cb = (0.3 * rng.standard_normal((M, 256, D // M))).astype(np.float32)
+    d = ivf.IndexDesc(dev(C), dev(nbr), dev(alpha), dev(cs), dev(cb) if D % M == 0 and D // M in (4, 6, 8, 12, 16) else None, M=M)
+    _, sub, codes, _, t, res = ivf.ivf_encode(d, dev(x), region_in=dev(reg), want_t=True, want_residual=True)
+    d.pq_codebook = None
+    _, sub2, _, _, _, res2 = ivf.ivf_encode(d, dev(x), region_in=dev(reg), want_residual=True)
+    sub, res = sub.cpu().numpy(), res.cpu().numpy()
+    assert (sub == sub2.cpu().numpy()).all() and (res == res2.cpu().numpy()).all()
+    x64, c64, a = x.astype(np.float64), C.astype(np.float64), alpha[reg].astype(np.float64)[:, None]
+    dxc = ((x64 - c64[reg]) ** 2).sum(-1)[:, None]
+    dxs = ((x64[:, None] - c64[nbr[reg]]) ** 2).sum(-1)
+    sc = a * dxs + (1 - a) * dxc - a * (1 - a) * cs[reg]
+    u = 2.0 ** -24
+    room = 2 * (a * (D / 16 + 12) * u * dxs.max(1, keepdims=True) + 8 * u * (dxc + a * dxs.max(1, keepdims=True) + cs[reg].max(1, keepdims=True)))
+    got = sc[np.arange(n), sub]
+    assert (got <= sc.min(1) + room[:, 0]).all()
+    flat = a[:, 0] == 0
+    assert (sub[flat] == 0).all()
+    s = c64[nbr[reg, sub]]
+    mu = c64[reg] + a * (s - c64[reg])
+    assert np.abs(res - (x64 - mu)).max() <= 8 * u * (np.abs(x64).max() + np.abs(c64).max())
