@@ -313,3 +313,23 @@ def test_subregions_and_displacements(D, L, n, order, kind):
     s = c64[nbr[reg, sub]]
     mu = c64[reg] + a * (s - c64[reg])
     assert np.abs(res - (x64 - mu)).max() <= 8 * u * (np.abs(x64).max() + np.abs(c64).max())
+
+
+@pytest.mark.parametrize("n,D,K", [(1, 1, 1), (2560, 64, 10), (2561, 64, 10), (5000, 65, 700), (999, 130, 1500), (300, 1024, 40), (4097, 96, 3)])
+def test_cluster_means_of_short_and_long_clusters(n, D, K):
+    """Both kernels and the line between them (256 rows a cluster on average), clusters of none, one and many rows, columns
+    past a wavefront's 64: the fp64 mean rounded once."""
+    print("case: cluster means", n, D, K, flush=True)
+    rng = np.random.default_rng(n + D)
+    x = (rng.standard_normal((n, D)) * 10 + 3).astype(np.float32)
+    lab = (rng.random(n) ** 3 * K).astype(np.int32)
+    c0 = rng.standard_normal((K, D)).astype(np.float32)
+    got = ivf.ivf_cluster_means(dev(x), dev(lab), dev(c0)).cpu().numpy()
+    s, a = np.zeros((K, D)), np.zeros((K, D))
+    np.add.at(s, lab, x.astype(np.float64))
+    np.add.at(a, lab, np.abs(x).astype(np.float64))
+    cnt = np.bincount(lab, minlength=K)[:, None]
+    ref = s / np.maximum(cnt, 1)
+    assert (got[cnt[:, 0] == 0] == c0[cnt[:, 0] == 0]).all()
+    full = cnt[:, 0] > 0
+    assert (np.abs(got - ref)[full] <= (2.0 ** -24 * np.abs(ref) + 2 * n * 2.0 ** -53 * a / np.maximum(cnt, 1))[full]).all()
