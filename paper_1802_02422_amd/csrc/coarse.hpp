@@ -1480,9 +1480,12 @@ __device__ __forceinline__ void wave_select(const uint32_t (&k)[R], uint32_t nse
     uint32_t below = 0;                                        // keys < t
     for (int bit = top; bit >= 0; --bit) {
         const uint32_t trial = t | 1u << bit;
-        uint32_t c = 0;
+        // counted per lane and added over the lanes: a population count per register goes through the scalar unit, whose
+        // waits a lone wavefront has nothing to cover with (333 queries x 2000: 29 us, 26 so)
+        uint32_t mine = 0;
 #pragma unroll
-        for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(k[r] < trial));
+        for (int r = 0; r < R; ++r) mine += k[r] < trial ? 1u : 0u;
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(mine), WAVE - 1);
         if (c <= nsel) {
             t = trial;
             below = c;
@@ -1515,13 +1518,18 @@ constexpr int PW_NB_MAX = 1024;     // up to here the block minima do (and P <= 
 constexpr int PW_P_MAX = 64;
 constexpr int PW_CAP = 512;         // survivors held in LDS; more (duplicated centroids) are searched in memory
 
-// Four queries a workgroup.  Same three steps and the same result as probe_select_kernel.
-template <bool DIRECT>
+// Four queries a workgroup.  Same three steps and the same result as probe_select_kernel.  KMAX > 0: the whole row, of
+// at most KMAX distances, goes into registers (and LDS, from where a short loop writes the selected ones out).  A small
+// batch waits for one wavefront's chain of steps, which grows with the registers it holds: 100 queries x 1024 19 us with
+// KMAX = 2048, 13 with 1024.
+template <int KMAX>
 __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__restrict__ Dt, int64_t ldt, const float *__restrict__ bm,
                                                                 int64_t K, int nb, int P, int64_t nq, int32_t *__restrict__ probe_id,
                                                                 float *__restrict__ probe_d)
 {
-    constexpr int R = DIRECT ? PW_K_DIRECT / WAVE : PW_NB_MAX / WAVE;
+    constexpr bool DIRECT = KMAX > 0;
+    constexpr int R = DIRECT ? KMAX / WAVE : PW_NB_MAX / WAVE;
+    __shared__ uint32_t row_all[DIRECT ? 4 : 1][DIRECT ? KMAX : 1];
     __shared__ int blist_all[DIRECT ? 1 : 4][DIRECT ? 1 : 2 * PW_P_MAX];
     __shared__ uint32_t sk_all[DIRECT ? 1 : 4][DIRECT ? 1 : PW_CAP];
     __shared__ int si_all[DIRECT ? 1 : 4][DIRECT ? 1 : PW_CAP];
@@ -1536,14 +1544,31 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
     const float *src = DIRECT ? row : bm + q * nb;
 #pragma unroll
     for (int r = 0; r < R; ++r) k[r] = r * WAVE + lane < n ? float_key(src[r * WAVE + lane]) : 0xFFFFFFFFu;
-    wave_select<R>(k, (uint32_t)P, pivot, need);
     if (DIRECT) {
-        wave_emit<R>(k, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
-            oid[pos] = r * WAVE + lane;
-            od[pos] = key_float(key);
-        });
+        uint32_t *held = row_all[DIRECT ? wave : 0];
+#pragma unroll
+        for (int r = 0; r < R; ++r) held[DIRECT ? r * WAVE + lane : 0] = k[r];
+        wave_select<R>(k, (uint32_t)P, pivot, need);
+        wave_sync();
+        uint32_t out = 0, eq_seen = 0;
+#pragma nounroll
+        for (int c0 = 0; c0 < n; c0 += WAVE) {
+            const uint32_t key = held[DIRECT ? c0 + lane : 0];
+            const uint64_t eqm = __ballot(key == pivot && need > 0);
+            const uint32_t eq_rank = eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u));
+            const bool sel = key < pivot || (key == pivot && eq_rank < need);
+            const uint64_t m = __ballot(sel);
+            if (sel) {
+                const uint32_t o = out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                oid[o] = c0 + lane;
+                od[o] = key_float(key);
+            }
+            out += (uint32_t)__popcll(m);
+            eq_seen += (uint32_t)__popcll(eqm);
+        }
         return;
     }
+    wave_select<R>(k, (uint32_t)P, pivot, need);
     // blocks that may hold one of the P closest: minimum below pivot, or (first P of them) equal to it; with need == 0
     // the P-th smallest minimum itself lies below pivot, and so do the P closest distances
     int *blist = blist_all[wave];

@@ -284,8 +284,9 @@ int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K,
     const size_t lds = (size_t)2 * P * sizeof(int);
     if (wave_select_fits(K, P)) {            // a wavefront per query, keys in registers
         const dim3 grid((unsigned)((nq + 3) / 4));
-        if (K <= PW_K_DIRECT) probe_select_wave_kernel<true><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
-        else probe_select_wave_kernel<false><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
+        if (K <= PW_K_DIRECT / 2) probe_select_wave_kernel<PW_K_DIRECT / 2><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
+        else if (K <= PW_K_DIRECT) probe_select_wave_kernel<PW_K_DIRECT><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
+        else probe_select_wave_kernel<0><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
         LAUNCHCHK("probe_select_wave_kernel");
         return IVF_OK;
     }
