@@ -161,7 +161,7 @@ __global__ __launch_bounds__(64) void encode_kernel(
 // the region stays the same: points in the order of their regions share the read.  Four lanes hold a row, 64 bytes of it
 // each load (a row a lane: 64 rows for 16 bytes each, 0.54 against 0.50 ms for 500 000 points on 65 536 regions);
 // neighbour 16 p + g is looked after by lane 4 g + p.  The score of Eq. (7) is then known to within
-//   err_l = 2 a e_l + roundings,  e_l = |dx| |s_l| + (|x| + |dx|) |ds_l| + k |x| |s_l|
+//   err_l = 2 |a| e_l + roundings,  e_l = |dx| |s_l| + (|x| + |dx|) |ds_l| + k |x| |s_l|
 // (see the nearest-centroid shortlist), and only neighbours whose lower end does not exceed the smallest upper end, 1.1
 // of 64 on unit vectors, are decided by the fp32 differences, with encode_kernel's arithmetic: the same subregion.
 // 2 * 10^6 points in region order (two a region), K = 2^20, L = 64, D = 96: 3.8 ms against 7.3, and 5.7 TB/s of the
@@ -277,9 +277,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH <= 12 ?
         const float2 ql = make_float2(sqrtf(x2) * (1.f + 0x1p-10f), sqrtf(d2) * (1.f + 0x1p-10f));
         const float css = __builtin_amdgcn_ldexpf(cs, 2 * sh);
         const float h = fmaf(a, fmaf(-2.f, dot, s2), -a * (1.f - a) * css);
-        // roundings: of the fp32 sum of differences, (D/16 + 12) 2^-24 of at most 2 (x2 + s2), and of the three-term
-        // score, 2^-20 of its terms
-        const float err = fmaf(2.f * a, shortlist_eps(ql, sl.x, sl.y, Dp), fmaf(a * (float)(D / 16 + 12) * 0x1p-23f, x2 + s2, 0x1p-20f * (x2 + c2 + css + s2)));
+        // roundings: of the fp32 sum of differences, (D/16 + 12) 2^-24 of at most 2 (x2 + s2), and of the three-term score,
+        // 2^-20 of the size of its terms (the scaling factor may be any number: none of them has to be small)
+        const float aa = fabsf(a), ac = fabsf(1.f - a);
+        const float size = fmaf(aa, x2 + s2, fmaf(ac, x2 + c2, aa * ac * fabsf(css)));
+        const float err = fmaf(2.f * aa, shortlist_eps(ql, sl.x, sl.y, Dp), fmaf(aa * (float)(D / 16 + 12) * 0x1p-23f, x2 + s2, 0x1p-20f * size));
         float up = my_l < L ? h + err : INFINITY;
         up = wave_smallest(up);
         uint64_t todo = __ballot(my_l < L && !(h - err > up));

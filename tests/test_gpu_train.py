@@ -333,3 +333,37 @@ def test_cluster_means_of_short_and_long_clusters(n, D, K):
     assert (got[cnt[:, 0] == 0] == c0[cnt[:, 0] == 0]).all()
     full = cnt[:, 0] > 0
     assert (np.abs(got - ref)[full] <= (2.0 ** -24 * np.abs(ref) + 2 * n * 2.0 ** -53 * a / np.maximum(cnt, 1))[full]).all()
+
+
+@pytest.mark.parametrize("a", [-0.5, -0.01, 1.5, 4.0, 1e4, -1e4])
+@pytest.mark.parametrize("D,L,n", [(96, 64, 1000), (128, 7, 333)])
+def test_subregions_with_scaling_factors_outside_0_1(D, L, n, a):
+    """The scaling factor of a region may be any number: subregions against fp64 scores of Eq. (7), within what the fp32
+    score rounds, its terms being |a| |x - s|^2, |1 - a| |x - c|^2 and |a (1 - a)| |c - s|^2."""
+    print("case: subregions, scaling factor", D, L, n, a, flush=True)
+    rng = np.random.default_rng(D + L)
+    K = 80
+    C = rng.standard_normal((K, D))
+    C = (C / np.linalg.norm(C, axis=1, keepdims=True)).astype(np.float32)
+    reg = rng.integers(0, K, n).astype(np.int32)
+    x = (C[reg] + 0.05 * rng.standard_normal((n, D))).astype(np.float32)
+    nbr = np.stack([rng.permutation(np.delete(np.arange(K), r))[:L] for r in range(K)]).astype(np.int32)
+    cs = ((C[:, None].astype(np.float64) - C[nbr]) ** 2).sum(-1).astype(np.float32)
+    alpha = np.full(K, a, np.float32)
+    alpha[::7] = 0.1
+    d = ivf.IndexDesc(dev(C), dev(nbr), dev(alpha), dev(cs), None, M=8)
+    _, sub, _, _, _, res = ivf.ivf_encode(d, dev(x), region_in=dev(reg), want_residual=True)
+    sub, res = sub.cpu().numpy(), res.cpu().numpy()
+    x64, c64, al = x.astype(np.float64), C.astype(np.float64), alpha[reg].astype(np.float64)[:, None]
+    dxc = ((x64 - c64[reg]) ** 2).sum(-1)[:, None]
+    dxs = ((x64[:, None] - c64[nbr[reg]]) ** 2).sum(-1)
+    sc = al * dxs + (1 - al) * dxc - al * (1 - al) * cs[reg]
+    u = 2.0 ** -24
+    terms = np.abs(al) * dxs.max(1, keepdims=True) + np.abs(1 - al) * dxc + np.abs(al * (1 - al)) * cs[reg].max(1, keepdims=True)
+    room = 2 * (np.abs(al) * (D / 16 + 12) * u * dxs.max(1, keepdims=True) + 8 * u * terms)
+    assert (sc[np.arange(n), sub] <= sc.min(1) + room[:, 0]).all()
+    clear = np.sort(sc, 1)[:, 1] - sc.min(1) > 2 * room[:, 0]
+    assert (sub[clear] == sc.argmin(1)[clear]).all()
+    s = c64[nbr[reg, sub]]
+    mu = c64[reg] + al * (s - c64[reg])
+    assert (np.abs(res - (x64 - mu)) <= 8 * u * (np.abs(x64) + np.abs(mu) + (1 + np.abs(al)) * (np.abs(s) + np.abs(c64[reg])))).all()
