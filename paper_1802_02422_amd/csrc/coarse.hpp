@@ -21,9 +21,11 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef uint32_t gu32x4 __attribute__((ext_vector_type(4)));
 
-// Largest magnitude of count floats, as the bit pattern of a non-negative float (those order like unsigned integers;
-// one that is not a number counts as larger than infinity); out must start at 0.  One atomic a workgroup: with
+// Largest magnitude of count floats, as the bit pattern of a non-negative float (those order like unsigned integers);
+// out must start at 0.  FINITE: infinities and values that are not numbers are left out, so that the scale taken from it
+// is the others' own; else they count, one that is not a number as larger than infinity.  One atomic a workgroup: with
 // one a wavefront and 2^16 of them the reduction of a 25 MB table took 0.75 ms, all of it spent at that one address.
+template <bool FINITE>
 __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ X, int64_t count,
                                                      uint32_t *__restrict__ out)
 {
@@ -32,7 +34,7 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ X
 #pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
         const uint32_t v = __float_as_uint(X[i]) & 0x7FFFFFFFu;
-        m = v > m ? v : m;
+        m = v > m && (!FINITE || v < 0x7F800000u) ? v : m;
     }
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) {
@@ -821,12 +823,14 @@ __global__ __launch_bounds__(256) void argmin_unpack_kernel(const unsigned long 
 // Rows of X ([n][D] fp32) as fp16 in the layout of gemm_tile<true>: per 32 dimensions the 16-byte chunks [k 0-7 | k
 // 16-23 | k 8-15 | k 24-31], so that lane half h finds its dimensions of the two 16-wide products in chunks 2h and
 // 2h+1; zero beyond D and in the rows n .. n_pad-1.  Scaled by 2^(14 - floor(log2 m)), m the largest magnitude *gmax.
-// len[r] = (|row|, |row - packed row|) in scaled units, both rounded up (n_pad of them).  16 lanes per row, a chunk of 8 dimensions a
-// lane: whole 16-byte stores, 32-byte reads.
+// len[r] = (|row|, |row - packed row|) in scaled units (n_pad of them), both rounded up and at least 2^-50: what a square
+// loses below fp32's range (a row 2^-89 the size of the largest) cannot make a length too short.  A row whose length is
+// not a number or beyond fp32 is packed as zeros, its lengths infinite: it has no nearest centroid, and as a centroid it
+// is nobody's.  16 lanes per row, a chunk of 8 dimensions a lane: whole 16-byte stores, 32-byte reads.
 __host__ __device__ inline int hi_scale(uint32_t gmax_bits)
 {
     const int e = (int)(gmax_bits >> 23) - 127;             // (a subnormal or zero maximum: the clamp)
-    return gmax_bits >= 0x7F800000u ? 0 : 14 - (e < -62 ? -62 : e > 62 ? 62 : e);
+    return 14 - (e < -62 ? -62 : e > 62 ? 62 : e);
 }
 
 __global__ __launch_bounds__(256) void pack_hi_rows_kernel(const float *__restrict__ X, int64_t n, int64_t n_pad, int D, int Dp,
@@ -863,12 +867,16 @@ __global__ __launch_bounds__(256) void pack_hi_rows_kernel(const float *__restri
         s2 += __shfl_xor(s2, o, WAVE);
         d2 += __shfl_xor(d2, o, WAVE);
     }
-    if (lane == 0) len[row] = make_float2(sqrtf(s2) * (1.f + 0x1p-10f), sqrtf(d2) * (1.f + 0x1p-10f));
+    const bool fits = s2 < INFINITY && d2 < INFINITY;
+    if (!fits)
+        for (int ch = lane; ch < Dp / 8; ch += 16) *reinterpret_cast<gu32x4 *>(H + row * (int64_t)Dp + ch * 8) = gu32x4{0u, 0u, 0u, 0u};
+    if (lane == 0)
+        len[row] = fits ? make_float2(sqrtf(s2 + 0x1p-100f) * (1.f + 0x1p-10f), sqrtf(d2 + 0x1p-100f) * (1.f + 0x1p-10f)) : make_float2(INFINITY, INFINITY);
 }
 
 // Start values and bounds of the centroids for rows of scale *xmax: start[c] = (-1/2 + k) |c|^2 in units of the product,
-// -inf for c in [K, tiles * 128); tile[t] = (largest |c|, largest |dc|, smallest start value) of tile t, the lengths in
-// the table's units.
+// -inf for c in [K, tiles * 128) and for centroids without a length; tile[t] = (largest |c|, largest |dc|, smallest start
+// value) of tile t, the lengths in the table's units.
 __global__ __launch_bounds__(128) void shortlist_tiles_kernel(const float2 *__restrict__ clen, int64_t K, int Dp, const uint32_t *__restrict__ cmax,
                                                               const uint32_t *__restrict__ xmax, float *__restrict__ start,
                                                               float4 *__restrict__ tile)
@@ -877,8 +885,10 @@ __global__ __launch_bounds__(128) void shortlist_tiles_kernel(const float2 *__re
     const int64_t c = (int64_t)blockIdx.x * 128 + threadIdx.x;
     float2 l = make_float2(0.f, 0.f);
     float v = -INFINITY, low = INFINITY;
-    if (c < K) {
-        l = clen[c];
+    if (c < K) l = clen[c];
+    if (!(l.x < INFINITY)) {
+        l = make_float2(0.f, 0.f);
+    } else if (c < K) {
         // (the length was rounded up by 2^-10: not into the start value, which has to be |c|^2 to k)
         const float len0 = l.x * (1.f / (1.f + 0x1p-10f));
         v = low = (-0.5f + (float)(Dp + 32) * 0x1p-24f) * __builtin_amdgcn_ldexpf(len0 * len0, hi_scale(*xmax) - hi_scale(*cmax));
@@ -980,10 +990,11 @@ __global__ __launch_bounds__(256) void coarse_shortlist_kernel(ShortlistArgs a)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int64_t q = q0 + wq + i * 32 + l32;
-        const bool qok = q < a.nq;
-        const float2 ql = qok ? a.qlen[q] : make_float2(0.f, 0.f);
+        float2 ql = q < a.nq ? a.qlen[q] : make_float2(INFINITY, INFINITY);
+        const bool qok = ql.x < INFINITY;
+        if (!qok) ql = make_float2(0.f, 0.f);
         const float eps = shortlist_eps(ql, tl.x, tl.y, a.Dp);
-        const float before = !qok ? INFINITY : seen[i] ? key_float(seen[i]) : -INFINITY;   // (a row past the end reports nothing)
+        const float before = !qok ? INFINITY : seen[i] ? key_float(seen[i]) : -INFINITY;   // (a row past the end, or without a length, reports nothing)
         float bound = before;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -1071,15 +1082,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int64_t q = q0 + wq + i * 32 + l32;
-        qok[i] = q < a.nq;
         const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(a.Qh) + q * Dpf) + 2 * h;
 #pragma unroll
         for (int s = 0; s < SH; ++s) {
             afr[s][i][0] = row[s * 4 + 0];
             afr[s][i][1] = row[s * 4 + 1];
         }
-        ql[i] = qok[i] ? a.qlen[q] : make_float2(0.f, 0.f);
-        // the bound as it stands now (an older bound is a weaker one, never a wrong one); a row past the end has nothing to report
+        ql[i] = q < a.nq ? a.qlen[q] : make_float2(INFINITY, INFINITY);
+        qok[i] = ql[i].x < INFINITY;
+        if (!qok[i]) ql[i] = make_float2(0.f, 0.f);
+        // the bound as it stands now (an older bound is a weaker one, never a wrong one); a row past the end, or without a length,
+        // has nothing to report
         const uint32_t seen = qok[i] ? __hip_atomic_load(&a.L[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
         before[i] = bound[i] = !qok[i] ? INFINITY : seen ? key_float(seen) : -INFINITY;
     }

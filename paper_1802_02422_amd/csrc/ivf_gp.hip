@@ -196,12 +196,13 @@ int check_trained(const ivf_index_desc *d)
 }
 
 // ------------------------------------------------------------ stage 1 driver
+template <bool FINITE>
 int launch_absmax(const float *X, int64_t count, uint32_t *gmax, hipStream_t st)
 {
     HIPCHK(hipMemsetAsync(gmax, 0, sizeof(uint32_t), st));
     int64_t grid = (count + 1023) / 1024;
     if (grid > 1024) grid = 1024;
-    absmax_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(X, count, gmax);
+    absmax_kernel<FINITE><<<dim3((unsigned)grid), dim3(256), 0, st>>>(X, count, gmax);
     LAUNCHCHK("absmax_kernel");
     return IVF_OK;
 }
@@ -214,7 +215,7 @@ int pack_rows(const float *X, int64_t n, int D, uint32_t *gmax, _Float16 *P, flo
 {
     if (n <= 0) return IVF_OK;
     if (gmax) {
-        int rc = launch_absmax(X, n * D, gmax, st);
+        int rc = launch_absmax<true>(X, n * D, gmax, st);
         if (rc) return rc;
     }
     split_rows_kernel<<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st>>>(X, n, D, gmax, P, norm, inv);
@@ -882,7 +883,7 @@ std::atomic<int64_t> g_assign_short{0}, g_assign_exact{0};
 // Rows as fp16 with their lengths, for packed_rows(n) rows (see pack_hi_rows_kernel).
 int launch_pack_hi(const float *X, int64_t n, int D, uint32_t *gmax, _Float16 *H, float2 *len, hipStream_t st)
 {
-    int rc = launch_absmax(X, n * D, gmax, st);
+    int rc = launch_absmax<true>(X, n * D, gmax, st);
     if (rc) return rc;
     const int64_t pad = packed_rows(n);
     pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(X, n, pad, D, packed_dim(D), gmax, H, len);

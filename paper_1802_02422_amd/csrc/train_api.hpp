@@ -214,7 +214,7 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
         HIPCHK(pcnt.alloc(words * sizeof(uint32_t)));
         fill_u64_kernel<<<dim3(grid_for(state_words / 2)), dim3(256), 0, st>>>(static_cast<unsigned long long *>(state.p), state_words / 2, 0ull);
         LAUNCHCHK("fill_u64_kernel");
-        if ((r2 = launch_absmax(E, n * D, static_cast<uint32_t *>(state.p), st))) return r2;
+        if ((r2 = launch_absmax<false>(E, n * D, static_cast<uint32_t *>(state.p), st))) return r2;
         if ((r2 = rounds(true))) return r2;
         // (infinities and values that are not numbers have to find their way into the means: by the segment sums too)
         if (seen[0] < 0x7F800000u && !seen[1]) return IVF_OK;

@@ -113,3 +113,81 @@ def test_shortlist_and_one_pass_kernel_agree(small):
     unclear = _check(C, P, a_id, a_d)
     _check(C, P, b_id, b_d)
     assert (a_id != b_id).sum() <= unclear
+
+
+def _mixed_chunk(D, K, nq):
+    """Rows and centroids of sizes 1 and 10^6, where fp16 without a scale would overflow."""
+    rng = np.random.default_rng(D + K + nq)
+    C = rng.standard_normal((K, D)) * np.where(rng.random((K, 1)) < 0.5, 1.0, 1e6)
+    own = rng.integers(0, K, nq)
+    Q = C[own] + 0.3 * rng.standard_normal((nq, D)) * np.linalg.norm(C[own], axis=1, keepdims=True) / np.sqrt(D)
+    return C.astype(np.float32), Q.astype(np.float32)
+
+
+@pytest.mark.parametrize("D,K,nq", [(96, 1000, 700), (136, 300, 257), (24, 70, 1000)])
+@pytest.mark.parametrize("bad", ["nan", "inf", "both"])
+def test_rows_that_are_not_finite_harm_only_themselves(D, K, nq, bad):
+    """Rows with an infinity or not a number in them have no nearest centroid; all the others of their chunk do."""
+    print("case: shortlist, rows not finite", D, K, nq, bad, flush=True)
+    C, Q = _mixed_chunk(D, K, nq)
+    lost = np.zeros(nq, bool)
+    if bad != "inf":
+        Q[5, D - 1], Q[nq - 1] = np.nan, np.nan
+        lost[[5, nq - 1]] = True
+    if bad != "nan":
+        Q[130, 3], Q[131, 0] = np.inf, -np.inf
+        lost[[130, 131]] = True
+    before = ivf.ivf_assign_stats()
+    gid, gd = _assign(C, Q)
+    after = ivf.ivf_assign_stats()
+    assert after[0] == before[0] + 1 and after[1] == before[1]
+    assert (gid[lost] == -1).all()
+    _check(C, Q[~lost], gid[~lost], gd[~lost])
+
+
+@pytest.mark.parametrize("D,K,nq", [(96, 1000, 700), (132, 300, 257)])
+def test_centroids_that_are_not_finite_are_nobodys_nearest(D, K, nq):
+    print("case: shortlist, centroids not finite", D, K, nq, flush=True)
+    C, Q = _mixed_chunk(D, K, nq)
+    bad = np.array([3, 130, K - 1])
+    Q = Q[:nq]
+    C[3], C[130, 1], C[K - 1, D - 1] = np.nan, np.inf, -np.inf
+    gid, gd = _assign(C, Q)
+    assert not np.isin(gid, bad).any() and (gid >= 0).all()
+    good = np.setdiff1d(np.arange(K), bad)
+    place = np.full(K, -1)
+    place[good] = np.arange(len(good))
+    _check(C[good], Q, place[gid], gd)
+
+
+def test_centroid_that_is_not_a_number_leaves_the_tables_scale_alone():
+    """The distances of the other centroids keep their accuracy (in the distance tile, P > 1)."""
+    print("case: distance tile, centroid not a number", flush=True)
+    rng = np.random.default_rng(3)
+    C = (1e6 * rng.standard_normal((300, 96))).astype(np.float32)
+    Q = (C[rng.integers(0, 299, 50)] + 1e5 * rng.standard_normal((50, 96))).astype(np.float32)
+    C[299] = np.nan
+    ids, d = (v.cpu().numpy() for v in ivf.ivf_coarse_topk(torch.from_numpy(C).cuda(), torch.from_numpy(Q).cuda(), 4))
+    full = _exact(C[:299], Q)
+    tol = 16 * U * ((Q.astype(np.float64) ** 2).sum(1) + (C[:299].astype(np.float64) ** 2).sum(1).max())
+    for q in range(50):
+        m = ids[q] != 299
+        assert (np.abs(d[q][m] - full[q][ids[q][m]]) <= tol[q]).all()
+        assert (full[q][ids[q][m]] <= np.sort(full[q])[3] + 2 * tol[q]).all()
+
+
+@pytest.mark.parametrize("D", [96, 132])
+def test_one_huge_row_does_not_hide_the_others(D):
+    """A row 2^92 times the size of the others of its chunk: what is left of those under the chunk's scale is nothing, and
+    the bound has to know."""
+    print("case: shortlist, one huge row", D, flush=True)
+    rng = np.random.default_rng(9)
+    K, nq = 500, 300
+    C = (2.0 ** -30 * rng.standard_normal((K, D))).astype(np.float32)
+    Q = (C[rng.integers(0, K, nq)] + 2.0 ** -33 * rng.standard_normal((nq, D))).astype(np.float32)
+    Q[77] = 0
+    Q[77, 5] = 2.0 ** 62
+    gid, gd = _assign(C, Q)
+    assert gid[77] >= 0
+    keep = np.arange(nq) != 77
+    _check(C, Q[keep], gid[keep], gd[keep])
