@@ -103,6 +103,7 @@ __global__ __launch_bounds__(64) void encode_kernel(
         }
     }
     wave_argmin(best, best_l);
+    if (best_l == 0x7fffffff) best_l = 0;              // (no score is a number)
     if (lane == 0) out_sub[i] = best_l;
 
     // Eq. (4): displacement from the chosen subcentroid
@@ -133,6 +134,7 @@ __global__ __launch_bounds__(64) void encode_kernel(
             if (dd < bd) { bd = dd; bj = j; }
         }
         wave_argmin(bd, bj);
+        if (bj == 0x7fffffff) bj = 0;
         if (lane == 0) out_codes[i * M + m] = (uint8_t)bj;
         const float *cw = codebook + ((int64_t)m * 256 + bj) * ds;
         for (int t = lane; t < ds; t += WAVE) {

@@ -191,3 +191,28 @@ def test_one_huge_row_does_not_hide_the_others(D):
     assert gid[77] >= 0
     keep = np.arange(nq) != 77
     _check(C, Q[keep], gid[keep], gd[keep])
+
+
+@pytest.mark.parametrize("D,M,codes", [(96, 8, True), (96, 8, False), (136, 8, False), (40, 8, True)])
+def test_encoder_takes_rows_that_are_not_finite(D, M, codes):
+    """They go to region 0, subregion 0 and, where the displacement is not a number, word 0; the other rows to their own.
+    Both subregion kernels and both code kernels (D = 136; D / M = 5)."""
+    print("case: encoder, rows not finite", D, M, codes, flush=True)
+    K, nq = 300, 257
+    C, Q = _mixed_chunk(D, K, nq)
+    lost = np.array([5, 130, 256])
+    Q[5], Q[130, 3], Q[256, D - 1] = np.nan, np.inf, np.nan
+    rest = np.setdiff1d(np.arange(nq), lost)
+    nbr = np.stack([(np.arange(K) + 1) % K, (np.arange(K) + 2) % K], 1).astype(np.int32)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cb = np.random.default_rng(1).standard_normal((M, 256, D // M)).astype(np.float32)
+    d = ivf.IndexDesc(up(C), up(nbr), up(np.zeros(K, np.float32)), up(np.zeros((K, 2), np.float32)), up(cb) if codes else None,
+                      M=M, const_table=up(np.linspace(-1, 1, 256, dtype=np.float32)) if codes else None)
+    region, sub, code, byte, _ = ivf.ivf_encode(d, up(Q))
+    region, sub = region.cpu().numpy(), sub.cpu().numpy()
+    gid, gd = _assign(C, Q)
+    assert (region[lost] == 0).all() and (region[rest] == gid[rest]).all() and (sub == 0).all()
+    if codes:
+        assert (code.cpu().numpy()[5] == 0).all()
+        alone = ivf.ivf_encode(d, up(Q[rest]))
+        assert (alone[2].cpu().numpy() == code.cpu().numpy()[rest]).all() and (alone[3].cpu().numpy() == byte.cpu().numpy()[rest]).all()
