@@ -1183,19 +1183,21 @@ int launch_pq_encode(int ds, const float *E, const float *MU, int64_t n, int M, 
 }
 
 // The codebook update from the codes: slices of sums and counts (scratch of pq_sum_slices(n) of them), then the means.
-// state: the largest magnitude of E, the flag of pq_means_kernel, and [M][256] counts that start at 0.
+// state: the largest magnitude of E and the flag of pq_means_kernel (32 bits each), [M][256] counts and [M][256][DS] rests
+// (64 bits each), which start at 0.
 int64_t pq_sum_slices(int64_t n) { return n >= 2048 * PQ_SUM_MAX_G ? PQ_SUM_MAX_G : (n + 2047) / 2048; }
 
 template <int DS>
 int launch_pq_means_ds(const float *E, int64_t n, int M, const uint8_t *codes, uint32_t *state, double *psum, uint32_t *pcnt,
                        float *codebook, hipStream_t st)
 {
+    unsigned long long *small = reinterpret_cast<unsigned long long *>(state + 2), *rest = small + (size_t)M * 256;
     const int64_t G = pq_sum_slices(n), per = (n + G - 1) / G;
     const int groups = (M + PqSums<DS>::MG - 1) / PqSums<DS>::MG;
     HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&pq_sums_kernel<DS>), hipFuncAttributeMaxDynamicSharedMemorySize, PqSums<DS>::lds));
-    pq_sums_kernel<DS><<<dim3((unsigned)G, (unsigned)groups), dim3(512), PqSums<DS>::lds, st>>>(E, n, M, codes, state, per, psum, pcnt, state + 2);
+    pq_sums_kernel<DS><<<dim3((unsigned)G, (unsigned)groups), dim3(512), PqSums<DS>::lds, st>>>(E, n, M, codes, state, per, psum, pcnt, rest, small);
     LAUNCHCHK("pq_sums_kernel");
-    pq_means_kernel<DS><<<dim3((unsigned)(M * 256 * DS / 64)), dim3(256), 0, st>>>(psum, pcnt, M, (int)G, state, state + 2, state + 1, codebook);
+    pq_means_kernel<DS><<<dim3((unsigned)(M * 256 * DS / 64)), dim3(256), 0, st>>>(psum, pcnt, M, (int)G, state, rest, small, state + 1, codebook);
     LAUNCHCHK("pq_means_kernel");
     return IVF_OK;
 }

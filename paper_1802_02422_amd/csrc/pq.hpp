@@ -331,9 +331,11 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
 // ------------------------------------------------------------------ codeword sums of the training
 // Sums of the rows of each codeword in fixed point, so that the order of the additions does not matter: every value
 // is taken to a multiple of q = 2^-49 of the largest magnitude of E and added as a 64-bit whole number in LDS.  Values
-// of at least 2^-26 of that magnitude are exact; smaller ones are off by q / 2 at most, and their number per codeword
-// is kept: a mean that this could move by 2^-29 of itself raises a flag, and the training is done again with
-// fp64 segment sums (data whose rows lie many powers of two apart).
+// of at least 2^-26 of that magnitude are whole multiples; what is left of a smaller one (a few in 10^8 of normally
+// distributed values are so small) is added in memory, as a multiple of 2^-31 q.  Values below 2^-57 of the largest
+// magnitude may lose 2^-32 q each there, and are counted: where that could reach 2^-53 of a sum, the last place of an
+// fp64 sum, a flag is raised and the training is done again with fp64 segment sums (data whose rows lie many
+// powers of two apart).
 // This takes the place of a sort by code, a segment sum with one workgroup a codeword and five more launches per
 // quantiser: 10^6 x 96, 16 quantisers, one round: 1.55 -> 0.17 ms.  Bound by the LDS additions and by reading E.
 template <int DS>
@@ -345,13 +347,13 @@ constexpr int PQ_SUM_PART = 8192;                           // points between tw
 constexpr int PQ_SUM_MAX_G = 256;
 
 // Workgroup (g, group of quantisers): points [g * per, (g + 1) * per).  psum [G][M][256][DS] fp64 and pcnt [G][M][256]
-// receive its sums and counts (each slice is written by one workgroup, part by part in order); small [M][256] counts the
-// values below the exact range.
+// receive its sums and counts (each slice is written by one workgroup, part by part in order); rest [M][256][DS] receives
+// the multiples of 2^-31 q, small [M][256] counts the values below their exact range.
 template <int DS>
 __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ E, int64_t n, int M,
                                                       const uint8_t *__restrict__ codes, const uint32_t *__restrict__ gmax,
                                                       int64_t per, double *__restrict__ psum, uint32_t *__restrict__ pcnt,
-                                                      uint32_t *__restrict__ small)
+                                                      unsigned long long *__restrict__ rest, unsigned long long *__restrict__ small)
 {
     constexpr int MG = PqSums<DS>::MG, W = MG * DS / 2;      // pairs of components a point has in this group
     extern __shared__ __attribute__((aligned(16))) unsigned char pq_lds[];
@@ -366,8 +368,9 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
     const int ex = __builtin_amdgcn_frexp_expf(__uint_as_float(*gmax));
     const double scale = __builtin_amdgcn_ldexp(1.0, 49 - ex), back = __builtin_amdgcn_ldexp(1.0, ex - 49);
     const double magic = 6755399441055744.0;                 // 1.5 * 2^52
-    // first magnitude whose last bit is q or more (as a bit pattern; 1: all of them)
+    // first magnitude whose last bit is q, or 2^-31 q, or more (as a bit pattern; 1: all of them)
     const uint32_t whole_from = ex - 26 > -126 ? (uint32_t)(ex - 26 + 127) << 23 : 1u;
+    const uint32_t rest_from = ex - 57 > -126 ? (uint32_t)(ex - 57 + 127) << 23 : 1u;
     const unsigned long long mbits = __builtin_bit_cast(unsigned long long, magic);
     const int64_t lo = g * per, hi = lo + per < n ? lo + per : n;
     for (int64_t p0 = lo; p0 < hi || p0 == lo; p0 += PQ_SUM_PART) {
@@ -391,8 +394,15 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
                 atomicAdd(to + 1, __builtin_bit_cast(unsigned long long, b));
                 if (t == 0) atomicAdd(&cnt[m * 256 + code], 1u);
                 const uint32_t ua = (__float_as_uint(va) & 0x7FFFFFFFu) - 1u, ub = (__float_as_uint(vb) & 0x7FFFFFFFu) - 1u;
-                const uint32_t lost = (ua < whole_from - 1u ? 1u : 0u) + (ub < whole_from - 1u ? 1u : 0u);
-                if (lost) atomicAdd(&cut[m * 256 + code], lost);
+                if (ua < whole_from - 1u || ub < whole_from - 1u) {
+                    // (magic - a is a whole number, and what the fma leaves of the value at most 1/2: both exact)
+                    unsigned long long *over = rest + (((int64_t)m0 + m) * 256 + code) * DS + t;
+                    const double ra = fma((double)va, scale, magic - a) * 0x1p31, rb = fma((double)vb, scale, magic - b) * 0x1p31;
+                    if (ua < whole_from - 1u) atomicAdd(over, (unsigned long long)(long long)rint(ra));
+                    if (ub < whole_from - 1u) atomicAdd(over + 1, (unsigned long long)(long long)rint(rb));
+                    const uint32_t lost = (ua < rest_from - 1u ? 1u : 0u) + (ub < rest_from - 1u ? 1u : 0u);
+                    if (lost) atomicAdd(&cut[m * 256 + code], lost);
+                }
             }
         }
         __syncthreads();
@@ -405,20 +415,20 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
         uint32_t *pc = pcnt + (g * M + m0) * 256;
         for (int i = tid; i < mn * 256; i += 512) {
             pc[i] = p0 == lo ? cnt[i] : pc[i] + cnt[i];
-            if (cut[i]) atomicAdd(&small[m0 * 256 + i], cut[i]);
+            if (cut[i]) atomicAdd(&small[m0 * 256 + i], (unsigned long long)cut[i]);
         }
         __syncthreads();
     }
 }
 
-// codebook[m][j][t] = sum over the G slices / count, rounded to fp32; a codeword without points keeps its value.
-// A workgroup takes 64 components; four threads a component add a quarter of the slices each, in order.  *inexact is
-// set where values below the exact range (counted over all rounds) could show in the mean.
+// codebook[m][j][t] = sum over the G slices and rest / count, rounded to fp32; a codeword without points keeps its value.
+// A workgroup takes 64 components; four threads a component add a quarter of the slices each, in order.  rest is left at
+// 0 for the next round.  *inexact is set where values that were not added exactly (counted over all rounds) could show.
 template <int DS>
 __global__ __launch_bounds__(256) void pq_means_kernel(const double *__restrict__ psum, const uint32_t *__restrict__ pcnt,
                                                        int M, int G, const uint32_t *__restrict__ gmax,
-                                                       const uint32_t *__restrict__ small, uint32_t *__restrict__ inexact,
-                                                       float *__restrict__ codebook)
+                                                       unsigned long long *__restrict__ rest, const unsigned long long *__restrict__ small,
+                                                       uint32_t *__restrict__ inexact, float *__restrict__ codebook)
 {
     __shared__ double part[4][64];
     __shared__ uint32_t part_n[4][64];
@@ -439,9 +449,11 @@ __global__ __launch_bounds__(256) void pq_means_kernel(const double *__restrict_
     s = ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
     k = part_n[0][c] + part_n[1][c] + part_n[2][c] + part_n[3][c];
     if (!k) return;
+    const int ex = __builtin_amdgcn_frexp_expf(__uint_as_float(*gmax));
+    s += (double)(long long)rest[i] * __builtin_amdgcn_ldexp(1.0, ex - 80);
+    rest[i] = 0;
     codebook[i] = (float)(s / (double)k);
-    const double off = (double)small[i / DS] * __builtin_amdgcn_ldexp(1.0, __builtin_amdgcn_frexp_expf(__uint_as_float(*gmax)) - 50);
-    if (off > 0x1p-29 * fabs(s)) *inexact = 1u;
+    if ((double)small[i / DS] * __builtin_amdgcn_ldexp(1.0, ex - 81) > 0x1p-53 * fabs(s)) *inexact = 1u;
 }
 
 }  // namespace ivf

@@ -207,7 +207,7 @@ extern "C" int ivf_pq_train(const float *E, int64_t n, int D, int M, int iters, 
     auto body = [&]() -> int {
         if (iters == 0) return rounds(true);
         int r2;
-        const size_t state_words = 2 + (size_t)M * 256, words = (size_t)pq_sum_slices(n) * M * 256;
+        const size_t state_words = 2 + 2 * (size_t)M * 256 * (1 + ds), words = (size_t)pq_sum_slices(n) * M * 256;
         HIPCHK(codes.alloc((size_t)n * M));
         HIPCHK(state.alloc(state_words * sizeof(uint32_t)));
         HIPCHK(psum.alloc(words * ds * sizeof(double)));

@@ -367,3 +367,38 @@ def test_subregions_with_scaling_factors_outside_0_1(D, L, n, a):
     s = c64[nbr[reg, sub]]
     mu = c64[reg] + al * (s - c64[reg])
     assert (np.abs(res - (x64 - mu)) <= 8 * u * (np.abs(x64) + np.abs(mu) + (1 + np.abs(al)) * (np.abs(s) + np.abs(c64[reg])))).all()
+
+
+@pytest.mark.parametrize("M,ds,n", [(8, 4, 256 * 3), (16, 8, 70_001)])
+def test_codeword_means_keep_every_bit_of_an_fp64_sum(M, ds, n):
+    """Two rows a codeword, a component of them a + b with b a little above half a unit in the last place of a and nearly all
+    of its bits far below 2^-49 of the matrix's largest magnitude: the mean is the exact one rounded once, which goes up."""
+    print("case: codeword means, last bits", M, ds, n, flush=True)
+    rng = np.random.default_rng(n)
+    E = np.zeros((n, M, ds))
+    code = rng.permutation(np.arange(n) % 255)
+    first, second = np.full(255, -1), np.full(255, -1)
+    for i, j in enumerate(code):                            # (the rows beyond two a codeword are left out)
+        if first[j] < 0: first[j] = i
+        elif second[j] < 0: second[j] = i
+    E[:, :, 0] = (code[:, None] + 1) / 256.0
+    k = rng.integers(0, 1 << 21, (255, M)) * 2              # an even last place: a tie would go down
+    E[:, :, 2:] = 2.0 ** -10
+    E[first, :, 1] = 2.0 ** -19 * (1 + k * 2.0 ** -23)
+    E[second, :, 1] = 2.0 ** -43 * (1 + rng.integers(1, 1 << 9, k.shape) * 2.0 ** -20)
+    keep = (np.arange(n) == first[code]) | (np.arange(n) == second[code])
+    E = E[keep]                                             # two rows of each codeword ...
+    E = np.concatenate([E, np.full((2, M, ds), 1.0)])       # ... and the largest magnitude, 1, a codeword of its own
+    order = rng.permutation(len(E))
+    E, code = E[order], np.concatenate([code[keep], [255, 255]])[order]
+    start = np.array([np.flatnonzero(code == j)[0] for j in range(256)])
+    E32 = E.astype(np.float32)
+    assert (E32.astype(np.float64) == E).all()
+    reps = max(1, n // len(E))
+    E32, code = np.tile(E32.reshape(len(E), M * ds), (reps, 1)), np.tile(code, reps)
+    got = ivf.ivf_pq_train(dev(E32), M, 1, dev(start.astype(np.int64))).cpu().numpy()
+    s = np.zeros((256, M, ds))
+    np.add.at(s, code, E32.reshape(-1, M, ds).astype(np.float64))      # exact: multiples of 2^-63, sums below 2^-10 but for component 0
+    ref = (s / np.bincount(code, minlength=256)[:, None, None]).astype(np.float32)
+    assert (got[:, :, 1] == ref.transpose(1, 0, 2)[:, :, 1]).all()
+    assert np.abs(got - ref.transpose(1, 0, 2)).max() <= 2.0 ** -24
