@@ -1529,7 +1529,7 @@ __device__ __forceinline__ void wave_emit(const uint32_t (&k)[R], uint32_t pivot
 constexpr int PW_K_DIRECT = 2048;   // up to here the whole row of distances goes into registers
 constexpr int PW_NB_MAX = 1024;     // up to here the block minima do (and P <= nb, P <= PW_P_MAX)
 constexpr int PW_P_MAX = 64;
-constexpr int PW_CAP = 512;         // survivors held in LDS; more (duplicated centroids) are searched in memory
+constexpr int PW_CAP = 512;         // survivors held in LDS; where there are more, the bound is taken from these and lowered
 
 // Four queries a workgroup.  Same three steps and the same result as probe_select_kernel.  KMAX > 0: the whole row, of
 // at most KMAX distances, goes into registers (and LDS, from where a short loop writes the selected ones out).  A small
@@ -1598,70 +1598,68 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
         nflag += eq < (uint32_t)P ? eq : (uint32_t)P;
     }
     wave_sync();
-    const uint32_t lim = need > 0 ? pivot : pivot - 1u;        // the P closest have keys of at most lim
-    uint32_t total = 0;
-    for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
-        uint32_t kv[16];
+    uint32_t lim = need > 0 ? pivot : pivot - 1u;              // the P closest have keys of at most lim
+    auto fetch = [&](uint32_t f0, uint32_t (&kv)[16]) {        // the lane's column of 16 flagged blocks
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int64_t c = f0 + j < nflag ? (int64_t)blist[f0 + j] * BMW + lane : K;
             kv[j] = c < K ? float_key(row[c]) : 0xFFFFFFFFu;
         }
+    };
+    for (int round = 0;; ++round) {
+        uint32_t total = 0, eq_seen = 0;
+        for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
+            uint32_t kv[16];
+            fetch(f0, kv);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const bool sel = kv[j] <= lim && kv[j] != 0xFFFFFFFFu;
-            const uint64_t m = __ballot(sel);
-            const uint32_t o = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (sel && o < (uint32_t)PW_CAP) {
-                sk[o] = kv[j];
-                si[o] = blist[f0 + j] * BMW + lane;
+            for (int j = 0; j < 16; ++j) {
+                bool sel = kv[j] <= lim && kv[j] != 0xFFFFFFFFu;
+                if (round) {                                   // of those equal to lim only the first P can be among the P closest
+                    const uint64_t eqm = __ballot(sel && kv[j] == lim);
+                    if (kv[j] == lim) sel = sel && eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u)) < (uint32_t)P;
+                    eq_seen += (uint32_t)__popcll(eqm);
+                }
+                const uint64_t m = __ballot(sel);
+                const uint32_t o = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (sel && o < (uint32_t)PW_CAP) {
+                    sk[o] = kv[j];
+                    si[o] = blist[f0 + j] * BMW + lane;
+                }
+                total += (uint32_t)__popcll(m);
             }
-            total += (uint32_t)__popcll(m);
         }
-    }
-    wave_sync();
-    if (total <= (uint32_t)PW_CAP) {
+        wave_sync();
         uint32_t s[PW_CAP / WAVE];
 #pragma unroll
         for (int r = 0; r < PW_CAP / WAVE; ++r) s[r] = r * WAVE + lane < (int)total ? sk[r * WAVE + lane] : 0xFFFFFFFFu;
         wave_select<PW_CAP / WAVE>(s, (uint32_t)P, pivot, need);
-        wave_emit<PW_CAP / WAVE>(s, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
-            oid[pos] = si[r * WAVE + lane];
-            od[pos] = key_float(key);
-        });
-        return;
-    }
-    // very many distances at or below the threshold: the same search, reading them again for every bit
-    auto key_at = [&](uint32_t f) {
-        const int64_t c = (int64_t)blist[f] * BMW + lane;
-        return c < K ? float_key(row[c]) : 0xFFFFFFFFu;
-    };
-    uint32_t t = 0, below = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t trial = t | 1u << bit;
-        uint32_t c = 0;
-        for (uint32_t f = 0; f < nflag; ++f) c += (uint32_t)__popcll(__ballot(key_at(f) < trial));
-        if (c <= (uint32_t)P) {
-            t = trial;
-            below = c;
-            if (c == (uint32_t)P) break;
+        if (total <= (uint32_t)PW_CAP) {
+            wave_emit<PW_CAP / WAVE>(s, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
+                oid[pos] = si[r * WAVE + lane];
+                od[pos] = key_float(key);
+            });
+            return;
         }
-    }
-    const uint32_t rest = (uint32_t)P - below;
-    uint32_t out = 0, eq_seen = 0;
-    for (uint32_t f = 0; f < nflag; ++f) {
-        const uint32_t key = key_at(f);
-        const uint64_t eqm = __ballot(key == t);
-        const uint32_t eq_rank = eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u));
-        const bool sel = key < t || (key == t && eq_rank < rest);
-        const uint64_t m = __ballot(sel);
-        if (sel) {
-            const uint32_t o = out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            oid[o] = blist[f] * BMW + lane;
-            od[o] = key_float(key);
+        // More than fit.  The P closest of any PW_CAP distances bound the P closest of all: first of the 512 smallest, one of
+        // each lane's column of every eighth block, which are near ones wherever those lie (of the ones kept, the first in
+        // order, centroids whose numbers follow their places took six rounds, 0.2 ms); should that not be enough, of those
+        // kept.  At most P of these equal lim then, the others lie below it, and at least PW_CAP - P distances fall above
+        // the new bound every time.
+        if (round == 0) {
+            uint32_t low[PW_CAP / WAVE];
+#pragma unroll
+            for (int r = 0; r < PW_CAP / WAVE; ++r) low[r] = 0xFFFFFFFFu;
+            for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
+                uint32_t kv[16];
+                fetch(f0, kv);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) low[j % (PW_CAP / WAVE)] = kv[j] < low[j % (PW_CAP / WAVE)] ? kv[j] : low[j % (PW_CAP / WAVE)];
+            }
+            wave_select<PW_CAP / WAVE>(low, (uint32_t)P, pivot, need);
         }
-        out += (uint32_t)__popcll(m);
-        eq_seen += (uint32_t)__popcll(eqm);
+        const uint32_t lower = need > 0 ? pivot : pivot - 1u;
+        lim = lower < lim ? lower : lim;
+        wave_sync();                                           // the kept ones have been read
     }
 }
 

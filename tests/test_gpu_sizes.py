@@ -284,3 +284,26 @@ def test_scoring_from_whole_rows(K, L, nprobe, nq):
     Q = rng.standard_normal((nq, D)).astype(np.float32)
     out = parity.run_gpu_search(h, Q, nprobe, 0.3, 20)
     parity.check_search(ix, Q, nprobe, 0.3, 20, out).assert_ok()
+
+
+@pytest.mark.parametrize("nq,K,P", [(1100, 4096, 64), (1100, 4161, 64), (640, 20000, 40), (1030, 65536, 64), (5, 4096, 16), (600, 4096, 60)])
+@pytest.mark.parametrize("kind", ["line", "pairs"])
+def test_selection_where_near_centroids_have_near_ids(nq, K, P, kind):
+    """Numbers that follow the places: a block of 64 centroids is near or far as a whole, so that thousands of distances lie
+    at or below the P-th smallest block minimum ("pairs": and most of them tie with another).  Whole numbers: exact."""
+    print("case: selection, sorted centroids", nq, K, P, kind, flush=True)
+    rng = np.random.default_rng(nq + K + P)
+    C = rng.integers(-2, 3, (K, 32)).astype(np.float32)
+    C[:, 0] = np.arange(K) // (2048 if kind == "pairs" else 64)
+    if kind == "pairs":
+        C[1::2] = C[0:-1:2][:len(C[1::2])]
+    Q = np.concatenate([C[rng.integers(0, K, nq, dtype=np.int64)][:, :1], rng.integers(-2, 3, (nq, 31))], 1).astype(np.float32)
+    ids, d = ivf.ivf_coarse_topk(torch.from_numpy(C).cuda(), torch.from_numpy(Q).cuda(), P)
+    ids, d = ids.cpu().numpy(), d.cpu().numpy()
+    c64 = C.astype(np.float64)
+    for a in range(0, nq, 128):
+        q64 = Q[a:a + 128].astype(np.float64)
+        full = ((q64 ** 2).sum(1)[:, None] + (c64 ** 2).sum(1)[None] - 2 * q64 @ c64.T).astype(np.int64) * K + np.arange(K)
+        ref = np.sort(np.partition(full, P - 1, axis=1)[:, :P] % K, axis=1)
+        assert (ids[a:a + 128] == ref).all()
+        assert (d[a:a + 128] == np.take_along_axis(full, ref, 1) // K).all()
