@@ -269,13 +269,17 @@ int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t
     return IVF_OK;
 }
 
-// whether probe_select_wave_kernel takes the selection of P of K: one wavefront reads the P flagged blocks, 16 at a
-// time, which takes it longer than a workgroup's barriers where P is large (2000 queries x 65 536, P = 256: 0.16 ms)
-bool wave_select_fits(int64_t K, int P)
+// Whether probe_select_wave_kernel takes the selection of P of K for nq queries.  Up to PW_K_DIRECT distances always (1000:
+// 17 us for 300 queries, 38 for 10 000; a workgroup a query 26 and 405).  Above, a wavefront has P flagged blocks to read,
+// 16 at a time, and takes 20 us (P = 16), 33 (40) or 50 (64) however few the queries are, where the 512 workgroups
+// that run at a time take 24: 500 queries 29, 1000 51, 2000 94, P = 64 with a wavefront each 51, 52, 54.  Where more
+// distances survive than a wavefront holds it takes twice that: from 24 P queries on it is the faster one, and
+// about equal then.
+bool wave_select_fits(int64_t K, int P, int64_t nq)
 {
     if (K <= PW_K_DIRECT) return true;
     const int64_t nb = (K + BMW - 1) / BMW;
-    return nb <= PW_NB_MAX && P <= nb && P <= PW_P_MAX;
+    return nb <= PW_NB_MAX && P <= nb && P <= PW_P_MAX && nq >= 24 * P;
 }
 
 int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K, int P, int32_t *pid,
@@ -283,7 +287,7 @@ int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K,
 {
     const int nb = (int)((K + BMW - 1) / BMW);
     const size_t lds = (size_t)2 * P * sizeof(int);
-    if (wave_select_fits(K, P)) {            // a wavefront per query, keys in registers
+    if (wave_select_fits(K, P, nq)) {            // a wavefront per query, keys in registers
         const dim3 grid((unsigned)((nq + 3) / 4));
         if (K <= PW_K_DIRECT / 2) probe_select_wave_kernel<PW_K_DIRECT / 2><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);
         else if (K <= PW_K_DIRECT) probe_select_wave_kernel<PW_K_DIRECT><<<grid, dim3(256), 0, st>>>(Dt, dt_stride(K), bm, K, nb, P, nq, pid, pd);

@@ -286,8 +286,9 @@ def test_scoring_from_whole_rows(K, L, nprobe, nq):
     parity.check_search(ix, Q, nprobe, 0.3, 20, out).assert_ok()
 
 
-@pytest.mark.parametrize("nq,K,P", [(1100, 4096, 64), (1100, 4161, 64), (640, 20000, 40), (1030, 65536, 64), (5, 4096, 16), (600, 4096, 60)])
-@pytest.mark.parametrize("kind", ["line", "pairs"])
+@pytest.mark.parametrize("nq,K,P", [(1536, 4096, 64), (1541, 4161, 64), (1535, 4096, 64), (960, 20000, 40), (1537, 65536, 64), (5, 4096, 16),
+                                    (384, 2049, 16), (49, 8192, 2)])
+@pytest.mark.parametrize("kind", ["line", "pairs", "ties"])
 def test_selection_where_near_centroids_have_near_ids(nq, K, P, kind):
     """Numbers that follow the places: a block of 64 centroids is near or far as a whole, so that thousands of distances lie
     at or below the P-th smallest block minimum ("pairs": and most of them tie with another).  Whole numbers: exact."""
@@ -297,6 +298,8 @@ def test_selection_where_near_centroids_have_near_ids(nq, K, P, kind):
     C[:, 0] = np.arange(K) // (2048 if kind == "pairs" else 64)
     if kind == "pairs":
         C[1::2] = C[0:-1:2][:len(C[1::2])]
+    if kind == "ties":
+        C[rng.random(K) < 0.7] = C[K // 2]
     Q = np.concatenate([C[rng.integers(0, K, nq, dtype=np.int64)][:, :1], rng.integers(-2, 3, (nq, 31))], 1).astype(np.float32)
     ids, d = ivf.ivf_coarse_topk(torch.from_numpy(C).cuda(), torch.from_numpy(Q).cuda(), P)
     ids, d = ids.cpu().numpy(), d.cpu().numpy()
