@@ -565,17 +565,26 @@ int check_search_args(const ivf_index *ix, const float *queries, int64_t nq, int
 // Dynamic LDS sizes of the stage kernels; raises the kernels' limits where they exceed the default window.
 struct LdsPlan { size_t scan, merge, sp, ssp; };   // ssp: the fused selection + scoring launch
 
-// How the scoring of a search runs.  SCORE_STREAM_*: the whole row of distances through LDS, where it is at most as many
-// bytes as half the 128-byte lines that P L gathers touch (10 000 queries, K = 65 536: P L = 4096 0.95 -> 0.81 ms; 2000 queries
-// with P L = 16 384, selection included, 0.99 -> 0.78); SCORE_FUSED: selection and scoring in one launch of 1024 threads a query (large tables, where
-// the selection needs a workgroup of its own too); SCORE_GATHER: the rest.
+// How the scoring of a search runs.  SCORE_STREAM_*: the whole row of distances through LDS, STREAM_512 / STREAM_1024 at a
+// time; SCORE_FUSED: selection and scoring in one launch of 1024 threads a query (where the selection needs a workgroup
+// of its own too); SCORE_GATHER: the rest.
 enum ScoreMode { SCORE_GATHER, SCORE_FUSED, SCORE_STREAM_512, SCORE_STREAM_1024 };
 constexpr int STREAM_512 = 8192, STREAM_1024 = 16384;   // distances in LDS at a time (512 / 1024 threads)
 
-ScoreMode score_mode(int64_t K, int P, int L)
+// Rows are read where they are at most as many bytes as half the 128-byte lines that P L gathers touch, K <= 16 P L, with these
+// exceptions (selection + scoring in us, rows against the rest):
+//  - a batch that leaves compute units idle waits for one workgroup's parts, a longer chain than the gathers where the row is
+//    long: K = 65 536, P L = 4096, 1 to 128 queries 67 - 92 against 64 - 87, 500 equal, 2000 220 against 251; K = 131 072,
+//    P L = 12 800, 64 queries 84 against 81, 256 93 against 106; K = 262 144, P L = 16 384, 64 queries 116 against 95, 256 equal,
+//    500 185 against 220; K = 32 768, P L = 4096, any number of queries: rows.
+//  - a short row stays in the caches under its gathers, which 256 threads do with more queries at a time: 10 000 queries,
+//    P L = 2048 and K = 1024 326 against 293, 4096 688 against 662, 8192 431 against 455; P L = 1024, K = 8192 396 against 369;
+//    P L = 4096, K = 4096 772 against 790.  Up to 500 queries rows are equal or 2 us better there.
+ScoreMode score_mode(int64_t K, int P, int L, int64_t nq)
 {
     const int64_t PL = (int64_t)P * L, nb = (K + BMW - 1) / BMW;
-    if (K <= 16 * PL && PL <= 16384) return PL <= 4096 ? SCORE_STREAM_512 : SCORE_STREAM_1024;
+    if (PL <= 4096 && K <= 16 * PL && (nq <= 512 ? K <= 12 * PL : K * PL >= (1ll << 24))) return SCORE_STREAM_512;
+    if (PL > 4096 && PL <= 16384 && K <= 16 * PL && (K <= 8 * PL || nq >= 256)) return SCORE_STREAM_1024;
     if (P <= PS_P_MAX && nb <= PS_NB_MAX && PL > 4096) return SCORE_FUSED;
     return SCORE_GATHER;
 }
@@ -583,7 +592,7 @@ ScoreMode score_mode(int64_t K, int P, int L)
 int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l)
 {
     const int64_t PL = (int64_t)P * ix->L;
-    const ScoreMode mode = score_mode(ix->K, P, ix->L);
+    const ScoreMode mode = score_mode(ix->K, P, ix->L, pl.tile);
     l.scan = (size_t)SCAN_WAVES * pool_capacity(k) * sizeof(uint64_t);   // dynamic part: the pools
     l.merge = ((size_t)pl.merge_n + pl.merge_pow2) * sizeof(uint64_t);
     l.sp = (size_t)(PL + 3 * P) * sizeof(uint32_t);
@@ -656,7 +665,7 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         // scoring launch (one workgroup per query does both): one kernel boundary less, and the selection
         // of one query (LDS and ALU work) runs while the other workgroup of the CU waits for its gathers.
         const int nb = (int)((K + BMW - 1) / BMW);
-        const ScoreMode mode = score_mode(K, P, L);
+        const ScoreMode mode = score_mode(K, P, L, pl.tile);
         const bool fused = mode == SCORE_FUSED;
         if (!fused && (rc = launch_probe_select(ws.dt, ws.bm, n, K, P, pid, pd, st))) return rc;
         if ((rc = mark(2))) return rc;

@@ -52,7 +52,8 @@ __device__ __forceinline__ void lut_body(const float *__restrict__ Qrow, int D, 
 // Dynamic LDS must also hold D floats.
 // STREAM > 0: the query's whole row of the tile is read, STREAM distances at a time, into LDS (over the place of the keys,
 // which come after it), and the neighbours' distances are picked there: a gather costs a 128-byte line of the row for
-// each 4 bytes, so that with 16 P L >= K the row is the smaller number of bytes, and whole lines in order.  Dynamic LDS:
+// each 4 bytes, so that with 16 P L >= K the row is the smaller number of bytes, and whole lines in order (where that
+// pays: score_mode).  Dynamic LDS:
 // max(P*L, STREAM + 4) + 3 P words.
 // (the body of a scoring workgroup, for query q of the batch: also the second half of select_score_prune_kernel)
 template <int BLOCK, int MAXV, int STREAM = 0>

@@ -310,3 +310,34 @@ def test_selection_where_near_centroids_have_near_ids(nq, K, P, kind):
         ref = np.sort(np.partition(full, P - 1, axis=1)[:, :P] % K, axis=1)
         assert (ids[a:a + 128] == ref).all()
         assert (d[a:a + 128] == np.take_along_axis(full, ref, 1) // K).all()
+
+
+def _random_index(K, L, D, M, N, seed):
+    """An index of random parts (neighbours included): what the query path does with it does not depend on how it was made."""
+    rng = np.random.default_rng(seed)
+    C = rng.standard_normal((K, D)).astype(np.float32)
+    nbr = ((np.arange(K)[:, None] + 1 + rng.integers(0, K - 1, (K, L))) % K).astype(np.int32)
+    cs = np.concatenate([((C[a:a + 4096, None] - C[nbr[a:a + 4096]]) ** 2).sum(-1) for a in range(0, K, 4096)]).astype(np.float32)
+    sizes = rng.multinomial(N, np.full(K * L, 1.0 / (K * L)))
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+    return orc.Index(D, M, L, K, N, C, nbr, rng.uniform(0.05, 0.2, K).astype(np.float32), cs,
+                     (0.3 * rng.standard_normal((M, 256, D // M))).astype(np.float32), np.sort(rng.standard_normal(256)).astype(np.float32),
+                     off, rng.integers(0, 256, (N, M)).astype(np.uint8), rng.integers(0, 256, N).astype(np.uint8),
+                     rng.permutation(N).astype(np.int32))
+
+
+@pytest.mark.parametrize("K,L,nprobe,few,many", [(1024, 24, 40, 512, 513), (16384, 16, 64, 512, 513), (49160, 64, 65, 255, 256), (70000, 64, 65, 3, 300),
+                                                 (20001, 8, 100, 5, 600), (3000, 30, 300, 2, 520), (40001, 16, 300, 9, 257)])
+def test_scoring_does_not_depend_on_the_batch(K, L, nprobe, few, many):
+    """Both sides of the rules by which rows, gathers or the launch with the selection in it do the scoring (and a
+    workgroup or a wavefront the selection): the same bits for a query in a small and in a large batch, and what the oracle says."""
+    print("case: scoring by batch", K, L, nprobe, few, many, flush=True)
+    ix = _random_index(K, L, 32, 8, 200_000, K + L)
+    h = ivf.ivf_load_index(parity.to_device(ix))
+    Q = np.random.default_rng(K).standard_normal((many, 32)).astype(np.float32)
+    big = parity.run_gpu_search(h, Q, nprobe, 0.3, 20)
+    small = parity.run_gpu_search(h, Q[:few], nprobe, 0.3, 20)
+    for n in big:
+        assert np.array_equal(big[n][:few], small[n]), n
+    take = np.linspace(0, many - 1, 12).astype(np.int64)
+    parity.check_search(ix, Q[take], nprobe, 0.3, 20, {n: v[take] for n, v in big.items()}).assert_ok()
