@@ -579,11 +579,12 @@ constexpr int STREAM_512 = 8192, STREAM_1024 = 16384;   // distances in LDS at a
 //    500 185 against 220; K = 32 768, P L = 4096, any number of queries: rows.
 //  - a short row stays in the caches under its gathers, which 256 threads do with more queries at a time: 10 000 queries,
 //    P L = 2048 and K = 1024 326 against 293, 4096 688 against 662, 8192 431 against 455; P L = 1024, K = 8192 396 against 369;
-//    P L = 4096, K = 4096 772 against 790.  Up to 500 queries rows are equal or 2 us better there.
+//    K = 4096, P L = 3072 745 against 726, 4096 772 against 790 (M = 16; with M = 8, K = 3324, P L = 3840, 2202 queries a search
+//    takes 268 against 274).  Up to 500 queries rows are equal or 2 us better there.
 ScoreMode score_mode(int64_t K, int P, int L, int64_t nq)
 {
     const int64_t PL = (int64_t)P * L, nb = (K + BMW - 1) / BMW;
-    if (PL <= 4096 && K <= 16 * PL && (nq <= 512 ? K <= 12 * PL : K * PL >= (1ll << 24))) return SCORE_STREAM_512;
+    if (PL <= 4096 && K <= 16 * PL && (nq <= 512 ? K <= 12 * PL : K * PL >= (3ll << 22))) return SCORE_STREAM_512;
     if (PL > 4096 && PL <= 16384 && K <= 16 * PL && (K <= 8 * PL || nq >= 256)) return SCORE_STREAM_1024;
     if (P <= PS_P_MAX && nb <= PS_NB_MAX && PL > 4096) return SCORE_FUSED;
     return SCORE_GATHER;
