@@ -341,7 +341,8 @@ int64_t dt_rows(int64_t n, int64_t K, int Dp)
     return sweep ? (n + GT - 1) / GT * GT : n;
 }
 
-SearchPlan plan_search(int64_t K, int D, int M, int P, int S, int k, int64_t tile, bool rotated)
+// per: points of a subregion on average
+SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated)
 {
     SearchPlan pl;
     pl.tile = tile;
@@ -349,12 +350,17 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, int k, int64_t til
     // Workgroups per query in the scan: fill the chip when the batch is small, but with at most 8 per
     // query: every workgroup hands 4 k candidates to the final k-select, whose time grows with them
     // faster than the scan's shrinks (one query on the 100M-point workload, scan + k-select in us:
-    // 17 + 9 with 2 workgroups, 12 + 9 with 4, 10.5 + 10 with 8, 10 + 12 / 14 / 20 with 16 / 32 / 64), and no
-    // more than there are batches of descriptors for their four wavefronts: a further workgroup only loads the
-    // table again (333 queries, S = 288: scan + k-select 47 us with 7, 28 with 2).
+    // 17 + 9 with 2 workgroups, 12 + 9 with 4, 10.5 + 10 with 8, 10 + 12 / 14 / 20 with 16 / 32 / 64).
+    // A wavefront takes up to 64 descriptors at a time, so that more than S / 256 workgroups divide what one wavefront would
+    // do, each of them loading the table again.  That pays while the chip has wavefronts to spare, and the longer the
+    // longer the lists are (scan + k-select in us with one for 16 descriptors against one for 256; 64 descriptors of 30
+    // points, 64 queries 27 against 34, 333 40 against 36; of 120 points, 333 63 against 85, 1000 114 against 93; 256 of 30
+    // points, 64 queries 33 against 37, 200 52 against 41; of 120, 64 61 against 81, 200 98 against 88; of 6, 200 35 against 24).
     int nsplit = (int)((2048 + tile - 1) / tile);
     if (nsplit > 8) nsplit = 8;
-    if (nsplit > (S + SCAN_WAVES * WAVE - 1) / (SCAN_WAVES * WAVE)) nsplit = (S + SCAN_WAVES * WAVE - 1) / (SCAN_WAVES * WAVE);
+    const bool spare = (double)tile * (S < WAVE ? WAVE : S) < 16384.0 + 200.0 * (per < 190.0 ? per : 190.0);
+    const int descs = spare ? 16 : SCAN_WAVES * WAVE;
+    if (nsplit > (S + descs - 1) / descs) nsplit = (S + descs - 1) / descs;
     while (nsplit > 1 && (int64_t)nsplit * SCAN_WAVES * k > 8192) --nsplit;
     if (nsplit < 1) nsplit = 1;
     pl.nsplit = nsplit;
@@ -530,6 +536,8 @@ extern "C" int ivf_load_index(const ivf_index_desc *d, void *hip_stream, ivf_ind
 }
 
 namespace {
+
+double mean_length(const ivf_index *ix) { return (double)ix->N / ((double)ix->K * ix->L); }
 
 struct SearchArgs {
     const float *queries;
@@ -772,7 +780,7 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
     else if (tile >= 256) tile -= tile % 256;   // whole blocks of the padded row count
     else if (tile >= GT) tile -= tile % GT;
 
-    const SearchPlan pl = plan_search(K, ix->D, ix->M, nprobe, S, k, tile, ix->rot_t != nullptr);
+    const SearchPlan pl = plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr);
     Buf *bufs[WS_COUNT] = {&ix->dt, &ix->bm, &ix->qn, &ix->qsi, &ix->qpk, &ix->probe_id, &ix->probe_d,
                            &ix->desc, &ix->lut, &ix->partial, &ix->qrot};
     for (int i = 0; i < WS_COUNT; ++i)
@@ -824,7 +832,7 @@ extern "C" int ivf_search_noalloc(ivf_index *ix, const float *queries, int64_t n
     if (rc || nq == 0) return rc;
     const int S = (int)ivf_num_kept(nprobe, ix->L, prune_frac);
     // the whole batch in one pass: the scratch is carved out of the static array, 256-byte aligned pieces
-    const SearchPlan pl = plan_search(ix->K, ix->D, ix->M, nprobe, S, k, nq, ix->rot_t != nullptr);
+    const SearchPlan pl = plan_search(ix->K, ix->D, ix->M, nprobe, S, mean_length(ix), k, nq, ix->rot_t != nullptr);
     size_t off[WS_COUNT], total = 0;
     for (int i = 0; i < WS_COUNT; ++i) {
         off[i] = total;

@@ -327,7 +327,7 @@ def _random_index(K, L, D, M, N, seed):
 
 
 @pytest.mark.parametrize("K,L,nprobe,few,many", [(1024, 24, 40, 512, 513), (16384, 16, 64, 512, 513), (49160, 64, 65, 255, 256), (70000, 64, 65, 3, 300),
-                                                 (20001, 8, 100, 5, 600), (3000, 30, 300, 2, 520), (40001, 16, 300, 9, 257)])
+                                                 (20001, 8, 100, 5, 600), (1024, 8, 16, 5, 700), (3000, 30, 300, 2, 520), (40001, 16, 300, 9, 257)])
 def test_scoring_does_not_depend_on_the_batch(K, L, nprobe, few, many):
     """Both sides of the rules by which rows, gathers or the launch with the selection in it do the scoring (and a
     workgroup or a wavefront the selection): the same bits for a query in a small and in a large batch, and what the oracle says."""
