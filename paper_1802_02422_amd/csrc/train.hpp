@@ -208,11 +208,16 @@ __global__ __launch_bounds__(256) void segment_sum_kernel(const T *__restrict__ 
     }
 }
 
-// Means of many short segments of whole rows of X ([.][D] fp32): one wavefront per segment and 64 columns, lane = column,
-// the rows one after the other in fp64, eight on their way at a time: a chain in member order, a function of the member
-// list alone.  segment_sum_kernel has 256 threads and a tree with 8 barriers for every 8 columns, most of them idle when
-// a segment has 30 rows (500 000 rows in 16 384 clusters, 96 columns: 0.63 against 0.16 ms); it stays where segments are
-// long.  An empty segment's mean is left alone.
+// Means of segments of whole rows of X ([.][D] fp32), lane = column, in fp64, eight rows on their way at a time: one
+// wavefront per segment and 64 columns where the segment has up to SHORT_SEGMENT rows, the rows one after the other; a
+// workgroup of 16 wavefronts where it has more, wavefront w taking rows 8 w .. 8 w + 7 of every 128.  Either way the sum is a
+// function of the member list alone.  An empty segment's mean is left alone.
+// segment_sum_kernel has 256 threads and a tree with 8 barriers for every 8 columns, most of them idle when a segment
+// has 30 rows (500 000 rows in 16 384 clusters, 96 columns: 0.77 ms a call, 0.20 so).  The bound is what a wavefront's chain
+// may take beside the rest: 64 steps of about a microsecond.  With 1 % (10, 60) of those rows in one cluster a call takes
+// 0.40 (2.1, 12) ms, with one wavefront for them 1.7 (15, 93), with segment_sum_kernel 0.77 (3.8, 22).
+constexpr uint32_t SHORT_SEGMENT = 512;
+
 __global__ __launch_bounds__(256) void short_segment_mean_kernel(const float *__restrict__ X, int D, const uint32_t *__restrict__ perm,
                                                                  const uint32_t *__restrict__ off, int64_t n_seg, float *__restrict__ mean)
 {
@@ -220,7 +225,7 @@ __global__ __launch_bounds__(256) void short_segment_mean_kernel(const float *__
     const int c = blockIdx.y * WAVE + (threadIdx.x & 63);
     if (g >= n_seg) return;
     const uint32_t b = off[g], e = off[g + 1];
-    if (e <= b) return;
+    if (e <= b || e - b > SHORT_SEGMENT) return;
     double sum = 0.0;
     for (uint32_t j0 = b; j0 < e; j0 += 8) {
         float v[8];
@@ -231,6 +236,41 @@ __global__ __launch_bounds__(256) void short_segment_mean_kernel(const float *__
             if (j0 + u < e) sum += (double)v[u];
     }
     if (c < D) mean[g * D + c] = (float)(sum / (double)(e - b));
+}
+
+// grid: (any, columns / 64); a workgroup looks through a share of the segments for the long ones, 64 at a time
+__global__ __launch_bounds__(1024) void long_segment_mean_kernel(const float *__restrict__ X, int D, const uint32_t *__restrict__ perm,
+                                                                 const uint32_t *__restrict__ off, int64_t n_seg, float *__restrict__ mean)
+{
+    __shared__ double part[16][WAVE];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int c = blockIdx.y * WAVE + lane;
+    const int64_t share = (n_seg + gridDim.x - 1) / gridDim.x, first = blockIdx.x * share, last = first + share < n_seg ? first + share : n_seg;
+    for (int64_t g0 = first; g0 < last; g0 += WAVE) {
+        const bool mine = g0 + lane < last;
+        const uint32_t bs = mine ? off[g0 + lane] : 0, es = mine ? off[g0 + lane + 1] : 0;
+        // (the same in all wavefronts)
+        for (uint64_t todo = __ballot(es > bs && es - bs > SHORT_SEGMENT); todo; todo &= todo - 1) {
+            const int s = __builtin_ctzll(todo);
+            const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)bs, s), e = (uint32_t)__builtin_amdgcn_readlane((int)es, s);
+            double sum = 0.0;
+            for (int64_t j0 = (int64_t)b + 8 * wave; j0 < e; j0 += 128) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = j0 + u < e && c < D ? X[(int64_t)perm[j0 + u] * D + c] : 0.f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (j0 + u < e) sum += (double)v[u];
+            }
+            part[wave][lane] = sum;
+            __syncthreads();
+            if (wave == 0 && c < D) {
+                for (int w = 1; w < 16; ++w) sum += part[w][lane];
+                mean[(g0 + s) * D + c] = (float)(sum / (double)(e - b));
+            }
+            __syncthreads();
+        }
+    }
 }
 
 // out[0] = sum of v[0..n) in fp64 by one workgroup, fixed order (thread t adds t, t + 1024, ...; tree).

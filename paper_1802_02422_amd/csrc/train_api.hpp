@@ -61,17 +61,14 @@ extern "C" int ivf_bucket_ids(const int32_t *region, const int32_t *sub, int64_t
 
 namespace {
 
-// centroids[j] = mean of the rows perm[off[j]] .. of x; one wavefront a cluster where clusters are short on average,
-// a workgroup where they are long
-int launch_cluster_means(const float *x, int64_t n, int D, const uint32_t *perm, const uint32_t *off, int64_t K, float *centroids, hipStream_t st)
+// centroids[j] = mean of the rows perm[off[j]] .. of x
+int launch_cluster_means(const float *x, int D, const uint32_t *perm, const uint32_t *off, int64_t K, float *centroids, hipStream_t st)
 {
-    if (n <= 256 * K) {
-        short_segment_mean_kernel<<<dim3(grid_for(K, 4), (unsigned)((D + WAVE - 1) / WAVE)), dim3(256), 0, st>>>(x, D, perm, off, K, centroids);
-        LAUNCHCHK("short_segment_mean_kernel");
-        return IVF_OK;
-    }
-    segment_sum_kernel<float, 1><<<dim3((unsigned)K), dim3(256), 0, st>>>(x, D, 0, D, perm, off, nullptr, centroids, D, 0);
-    LAUNCHCHK("segment_sum_kernel");
+    const unsigned columns = (unsigned)((D + WAVE - 1) / WAVE);
+    long_segment_mean_kernel<<<dim3((unsigned)(K < 256 ? K : 256), columns), dim3(1024), 0, st>>>(x, D, perm, off, K, centroids);
+    LAUNCHCHK("long_segment_mean_kernel");
+    short_segment_mean_kernel<<<dim3(grid_for(K, 4), columns), dim3(256), 0, st>>>(x, D, perm, off, K, centroids);
+    LAUNCHCHK("short_segment_mean_kernel");
     return IVF_OK;
 }
 
@@ -96,7 +93,7 @@ extern "C" int ivf_cluster_means(const float *x, int64_t n, int D, const int32_t
         if ((r2 = rb.sort(n, bits_for(K), false, &ks, &vs, st))) return r2;
         bucket_offsets_kernel<<<dim3(grid_for(n + 1)), dim3(256), 0, st>>>(ks, n, K, static_cast<uint32_t *>(off.p));
         LAUNCHCHK("bucket_offsets_kernel");
-        if ((r2 = launch_cluster_means(x, n, D, vs, static_cast<uint32_t *>(off.p), K, centroids, st))) return r2;
+        if ((r2 = launch_cluster_means(x, D, vs, static_cast<uint32_t *>(off.p), K, centroids, st))) return r2;
         HIPCHK(hipStreamSynchronize(st));
         return IVF_OK;
     };
@@ -145,7 +142,7 @@ extern "C" int ivf_kmeans(const float *x, int64_t n, int D, int64_t K, int iters
             if ((r2 = rb.sort(n, bits, false, &ks, &vs, st))) return r2;
             bucket_offsets_kernel<<<dim3(grid_for(n + 1)), dim3(256), 0, st>>>(ks, n, K, static_cast<uint32_t *>(off.p));
             LAUNCHCHK("bucket_offsets_kernel");
-            if ((r2 = launch_cluster_means(x, n, D, vs, static_cast<uint32_t *>(off.p), K, centroids, st))) return r2;
+            if ((r2 = launch_cluster_means(x, D, vs, static_cast<uint32_t *>(off.p), K, centroids, st))) return r2;
         }
         HIPCHK(hipStreamSynchronize(st));
         return IVF_OK;

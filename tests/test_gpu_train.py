@@ -402,3 +402,26 @@ def test_codeword_means_keep_every_bit_of_an_fp64_sum(M, ds, n):
     ref = (s / np.bincount(code, minlength=256)[:, None, None]).astype(np.float32)
     assert (got[:, :, 1] == ref.transpose(1, 0, 2)[:, :, 1]).all()
     assert np.abs(got - ref.transpose(1, 0, 2)).max() <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,D,K,crowd", [(9000, 96, 300, [512, 513, 640, 641]), (40_000, 130, 5000, [20_000]), (3000, 64, 3, [2487, 513]),
+                                         (5000, 20, 2, [5000])])
+def test_cluster_means_where_a_cluster_is_crowded(n, D, K, crowd):
+    """Clusters on both sides of the length from which a workgroup takes them, beside short and empty ones: the fp64 mean
+    rounded once, n additions in fp64 on either side."""
+    print("case: crowded clusters", n, D, K, crowd, flush=True)
+    rng = np.random.default_rng(n + D)
+    x = (rng.standard_normal((n, D)) * 10 + 3).astype(np.float32)
+    lab = np.concatenate([np.full(c, i) for i, c in enumerate(crowd)] + [rng.integers(len(crowd), K, n - sum(crowd)) if n > sum(crowd) else np.empty(0, int)])
+    lab = rng.permutation(lab).astype(np.int32)
+    c0 = rng.standard_normal((K, D)).astype(np.float32)
+    got = ivf.ivf_cluster_means(dev(x), dev(lab), dev(c0)).cpu().numpy()
+    s, a = np.zeros((K, D)), np.zeros((K, D))
+    np.add.at(s, lab, x.astype(np.float64))
+    np.add.at(a, lab, np.abs(x).astype(np.float64))
+    cnt = np.bincount(lab, minlength=K)[:, None]
+    assert (got[cnt[:, 0] == 0] == c0[cnt[:, 0] == 0]).all()
+    full = cnt[:, 0] > 0
+    ref = s / np.maximum(cnt, 1)
+    assert (np.abs(got - ref)[full] <= (2.0 ** -24 * np.abs(ref) + 2 * n * 2.0 ** -53 * a / np.maximum(cnt, 1))[full]).all()
+    assert (got == ivf.ivf_cluster_means(dev(x), dev(lab), dev(c0)).cpu().numpy()).all()
