@@ -425,3 +425,25 @@ def test_cluster_means_where_a_cluster_is_crowded(n, D, K, crowd):
     ref = s / np.maximum(cnt, 1)
     assert (np.abs(got - ref)[full] <= (2.0 ** -24 * np.abs(ref) + 2 * n * 2.0 ** -53 * a / np.maximum(cnt, 1))[full]).all()
     assert (got == ivf.ivf_cluster_means(dev(x), dev(lab), dev(c0)).cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("M,ds,n", [(16, 6, 5000), (16, 8, 333), (8, 16, 1000), (8, 12, 64), (16, 4, 5000)])
+@pytest.mark.parametrize("kinds", [1, 3, 40, 200])
+def test_codes_where_codewords_are_equal(M, ds, n, kinds):
+    """Codebooks of few distinct codewords (one block of each quantiser with -0 for 0, one with a codeword of its own behind its
+    copies): the first of the nearest ones."""
+    print("case: equal codewords", M, ds, n, kinds, flush=True)
+    rng = np.random.default_rng(M * ds + n + kinds)
+    D = M * ds
+    base = rng.integers(-20, 21, (M, kinds, ds)).astype(np.float32)
+    cb = np.stack([base[m][rng.integers(0, kinds, 256)] for m in range(M)])
+    cb[:, 255] = 50.0 + np.arange(M)[:, None]
+    cb[:, 100:120] = np.where(cb[:, 100:120] == 0, -0.0, cb[:, 100:120])
+    x = rng.integers(-25, 60, (n, D)).astype(np.float32)
+    x[::3] = cb[:, rng.integers(0, 256, len(x[::3]))].transpose(1, 0, 2).reshape(-1, D)
+    z = lambda *s, dt=np.float32: dev(np.zeros(s, dt))
+    desc = ivf.IndexDesc(z(2, D), dev(np.array([[1], [0]], np.int32)), z(2), z(2, 1), dev(cb), const_table=dev(np.linspace(-1, 1, 256, dtype=np.float32)))
+    codes = ivf.ivf_encode(desc, dev(x), region_in=z(n, dt=np.int32))[2].cpu().numpy()
+    for m in range(M):                                      # whole numbers: exact
+        d = ((x.reshape(n, M, ds)[:, m, None].astype(np.int64) - cb[m][None].astype(np.int64)) ** 2).sum(-1)
+        assert (codes[:, m] == d.argmin(1)).all()
