@@ -22,6 +22,7 @@
 #include "encode.hpp"
 #include "latency.hpp"
 #include "layout.hpp"
+#include "pool.hpp"
 #include "pq.hpp"
 #include "query.hpp"
 #include "scan.hpp"
@@ -63,79 +64,6 @@ struct Buf {
     size_t bytes = 0;
 };
 
-// Device memory kept for the next call.  The index-time entry points need scratch of a call's size for a call's time and
-// wait for their stream before they return; hipMalloc and hipFree cost them more than their kernels on small inputs (encoding
-// 26 000 points: 1.5 to 2.8 ms, 0.3 ms of it kernels).  Blocks come back only when no work that uses them is pending, so
-// any thread and stream may take them next.  At most POOL_BYTES a device are kept (anything else is freed);
-// ivf_free_index and an allocation that fails give all of it back.
-constexpr size_t POOL_BYTES = 1ull << 30;
-
-struct DevPool {
-    struct Block { void *p; size_t bytes; int dev; };
-    std::mutex mu;
-    std::vector<Block> idle;
-    void trim(int dev)
-    {
-        std::vector<Block> out;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            for (size_t i = 0; i < idle.size();)
-                if (idle[i].dev == dev) { out.push_back(idle[i]); idle[i] = idle.back(); idle.pop_back(); }
-                else ++i;
-        }
-        for (const Block &b : out) (void)hipFree(b.p);
-    }
-    // the smallest idle block that is not much larger than asked for, else a new one
-    hipError_t take(void **p, size_t *got, int *dev, size_t bytes)
-    {
-        hipError_t e = hipGetDevice(dev);
-        if (e != hipSuccess) return e;
-        bytes = bytes < 4096 ? 4096 : bytes;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            size_t best = idle.size();
-            for (size_t i = 0; i < idle.size(); ++i)
-                if (idle[i].dev == *dev && idle[i].bytes >= bytes && idle[i].bytes <= 2 * bytes && (best == idle.size() || idle[i].bytes < idle[best].bytes)) best = i;
-            if (best < idle.size()) {
-                *p = idle[best].p;
-                *got = idle[best].bytes;
-                idle[best] = idle.back();
-                idle.pop_back();
-                return hipSuccess;
-            }
-        }
-        e = hipMalloc(p, bytes);
-        if (e == hipErrorOutOfMemory) {
-            (void)hipGetLastError();
-            trim(*dev);
-            e = hipMalloc(p, bytes);
-        }
-        *got = bytes;
-        return e;
-    }
-    void give(void *p, size_t bytes, int dev)
-    {
-        std::vector<void *> out;                             // what no longer fits, oldest first
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            size_t held = bytes;
-            if (bytes <= POOL_BYTES) idle.push_back(Block{p, bytes, dev});
-            else out.push_back(p);
-            for (size_t i = 0; i + 1 < idle.size(); ++i)
-                if (idle[i].dev == dev) held += idle[i].bytes;
-            for (size_t i = 0; held > POOL_BYTES && i + 1 < idle.size();)
-                if (idle[i].dev == dev) {
-                    out.push_back(idle[i].p);
-                    held -= idle[i].bytes;
-                    idle.erase(idle.begin() + (long)i);
-                } else {
-                    ++i;
-                }
-        }
-        for (void *q : out) (void)hipFree(q);
-    }
-};
-
 DevPool g_pool;
 
 // Scratch from the pool, given back when the scope ends, error returns included: the owner has waited for the stream by then.
@@ -166,7 +94,7 @@ int ensure(Buf &b, size_t bytes)
         b.p = nullptr;
         b.bytes = 0;
     }
-    HIPCHK(hipMalloc(&b.p, bytes));
+    HIPCHK(g_pool.fresh(&b.p, bytes));
     b.bytes = bytes;
     return IVF_OK;
 }
@@ -446,7 +374,7 @@ namespace {
 template <class T>
 int dev_copy(T *&dst, const T *src, size_t count, hipStream_t st)
 {
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&dst), count * sizeof(T) ? count * sizeof(T) : 16));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&dst), count * sizeof(T) ? count * sizeof(T) : 16));
     if (count) HIPCHK(hipMemcpyAsync(dst, src, count * sizeof(T), hipMemcpyDeviceToDevice, st));
     return IVF_OK;
 }
@@ -465,16 +393,16 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
     if ((rc = dev_copy(ix->ids, d->ids, (size_t)N, st))) return rc;
 
     if (d->rotation) {
-        HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->rot_t), (size_t)D * D * sizeof(float)));
+        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->rot_t), (size_t)D * D * sizeof(float)));
         transpose_square_kernel<<<dim3((unsigned)((D * D + 255) / 256)), dim3(256), 0, st>>>(d->rotation, D, ix->rot_t);
         LAUNCHCHK("transpose_square_kernel");
     }
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->cnorm), (size_t)K * sizeof(float)));
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->cpk), (size_t)packed_rows(K) * packed_dim(D) * 2 * sizeof(_Float16)));
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->csi), 2 * sizeof(float)));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->cnorm), (size_t)K * sizeof(float)));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->cpk), (size_t)packed_rows(K) * packed_dim(D) * 2 * sizeof(_Float16)));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->csi), 2 * sizeof(float)));
     if ((rc = pack_rows(ix->centroids, K, D, reinterpret_cast<uint32_t *>(ix->csi + 1), ix->cpk, ix->cnorm, ix->csi, st)))
         return rc;
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->cst), (size_t)nsub * sizeof(float)));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->cst), (size_t)nsub * sizeof(float)));
     cst_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->alpha, d->cs_dist2, L, nsub, ix->cst);
     LAUNCHCHK("cst_kernel");
 
@@ -500,11 +428,11 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
     HIPCHK(hipMemcpyAsync(&last_sz, sz + nsub - 1, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     const uint64_t total_blk = (uint64_t)last_off + last_sz;
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->blocks), (size_t)(total_blk ? total_blk : 1) * BLK_ALIGN));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->blocks), (size_t)(total_blk ? total_blk : 1) * BLK_ALIGN));
     repack_kernel<<<dim3((unsigned)((nsub * 16 + 255) / 256)), dim3(256), 0, st>>>(
         d->sub_offsets, blk_off, nsub, M, d->codes, d->const_byte, ix->blocks);
     LAUNCHCHK("repack_kernel");
-    HIPCHK(hipMalloc(reinterpret_cast<void **>(&ix->sub_info), (size_t)nsub * sizeof(uint4)));
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->sub_info), (size_t)nsub * sizeof(uint4)));
     sub_info_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(d->sub_offsets, blk_off, nsub, ix->sub_info);
     LAUNCHCHK("sub_info_kernel");
     HIPCHK(hipStreamSynchronize(st));   // the temporaries are released on return

@@ -1,0 +1,45 @@
+// The pool of device blocks on a device of the host (stub/hip/hip_runtime.h): prints "ok" or the first thing that is wrong.
+#include "../../paper_1802_02422_amd/csrc/pool.hpp"
+
+#include <cstdio>
+
+using namespace ivf;
+
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+
+// a block through the pool and back
+static int once(DevPool &pool, size_t bytes)
+{
+    void *p = nullptr;
+    size_t got = 0;
+    int dev = -1;
+    if (pool.take(&p, &got, &dev, bytes) != hipSuccess) return 1;
+    pool.give(p, got, dev);
+    return 0;
+}
+
+// an allocation that has no room beside the idle blocks gets theirs, one that has none at all fails and leaves NULL
+static int idle_blocks_make_room()
+{
+    DevPool pool;
+    FakeDevice &d = fake();
+    d.room = 1 << 20;
+    CHECK(!once(pool, 600000));
+    CHECK(d.used == 600000);
+    void *p = nullptr;
+    CHECK(pool.fresh(&p, 900000) == hipSuccess && p && d.used == 900000);
+    void *q = &d;
+    CHECK(pool.fresh(&q, 900000) == hipErrorOutOfMemory && !q);
+    hipFree(p);
+    CHECK(!once(pool, 600000) && pool.fresh(&p, 500000) == hipSuccess && d.used == 500000);
+    hipFree(p);
+    CHECK(d.used == 0);
+    return 0;
+}
+
+int main()
+{
+    if (idle_blocks_make_room()) return 1;
+    std::puts("ok");
+    return 0;
+}

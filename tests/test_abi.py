@@ -130,3 +130,12 @@ def test_ctypes_signatures_follow_the_header():
         assert got == kinds, (name, got, kinds)
         if ret == "int64_t":
             assert fn.restype is C.c_int64, name
+
+
+def test_pool_of_device_blocks(tmp_path):
+    """csrc/pool.hpp against a device of the host."""
+    import subprocess
+    exe = str(tmp_path / "pool_check")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-pthread", "-I", os.path.join(ROOT, "tests", "abi", "stub"),
+                           "-o", exe, os.path.join(ROOT, "tests", "abi", "pool_check.cpp")])
+    assert subprocess.run([exe], capture_output=True, text=True, timeout=60).stdout == "ok\n"
