@@ -65,12 +65,15 @@ struct DevPool {
     }
     void give(void *p, size_t bytes, int dev)
     {
+        if (bytes > POOL_BYTES) {
+            (void)hipFree(p);
+            return;
+        }
         std::vector<void *> out;                             // what no longer fits, oldest first
         {
             std::lock_guard<std::mutex> lock(mu);
             size_t held = bytes;
-            if (bytes <= POOL_BYTES) idle.push_back(Block{p, bytes, dev});
-            else out.push_back(p);
+            idle.push_back(Block{p, bytes, dev});
             for (size_t i = 0; i + 1 < idle.size(); ++i)
                 if (idle[i].dev == dev) held += idle[i].bytes;
             for (size_t i = 0; held > POOL_BYTES && i + 1 < idle.size();)

@@ -37,9 +37,27 @@ static int idle_blocks_make_room()
     return 0;
 }
 
+// a block larger than the pool may hold is freed, and the ones that are held stay
+static int large_blocks_leave_the_others()
+{
+    DevPool pool;
+    FakeDevice &d = fake();
+    d.room = (size_t)8 << 30;
+    CHECK(!once(pool, 1000000) && !once(pool, 5000000));
+    const int frees = d.frees;
+    CHECK(!once(pool, POOL_BYTES + 1) && d.frees == frees + 1 && d.used == 6000000);
+    const int mallocs = d.mallocs;
+    CHECK(!once(pool, 1000000) && !once(pool, 5000000) && d.mallocs == mallocs);
+    // more than fits: the oldest go
+    CHECK(!once(pool, POOL_BYTES - 5500000) && d.used == POOL_BYTES - 500000);
+    pool.trim(0);
+    CHECK(d.used == 0);
+    return 0;
+}
+
 int main()
 {
-    if (idle_blocks_make_room()) return 1;
+    if (idle_blocks_make_room() || large_blocks_leave_the_others()) return 1;
     std::puts("ok");
     return 0;
 }
