@@ -1,7 +1,6 @@
 // Device memory of the host side: blocks kept between calls.
 #pragma once
 #include <mutex>
-#include <vector>
 
 #include <hip/hip_runtime.h>
 
@@ -16,18 +15,26 @@ constexpr size_t POOL_BYTES = 1ull << 30;
 
 struct DevPool {
     struct Block { void *p; size_t bytes; int dev; };
+    static constexpr int MAX_IDLE = 64;                      // (a call has a dozen)
     std::mutex mu;
-    std::vector<Block> idle;
+    Block idle[MAX_IDLE];                                     // oldest first; no containers: nothing here throws
+    int n = 0;
+    Block remove(int i)
+    {
+        const Block b = idle[i];
+        for (--n; i < n; ++i) idle[i] = idle[i + 1];
+        return b;
+    }
     void trim(int dev)
     {
-        std::vector<Block> out;
+        Block out[MAX_IDLE];
+        int m = 0;
         {
             std::lock_guard<std::mutex> lock(mu);
-            for (size_t i = 0; i < idle.size();)
-                if (idle[i].dev == dev) { out.push_back(idle[i]); idle[i] = idle.back(); idle.pop_back(); }
-                else ++i;
+            for (int i = n - 1; i >= 0; --i)
+                if (idle[i].dev == dev) out[m++] = remove(i);
         }
-        for (const Block &b : out) (void)hipFree(b.p);
+        for (int i = 0; i < m; ++i) (void)hipFree(out[i].p);
     }
     // a new allocation, here or for good; where there is no room for it the idle blocks of the device are given up first
     hipError_t fresh(void **p, size_t bytes)
@@ -49,14 +56,13 @@ struct DevPool {
         bytes = bytes < 4096 ? 4096 : bytes;
         {
             std::lock_guard<std::mutex> lock(mu);
-            size_t best = idle.size();
-            for (size_t i = 0; i < idle.size(); ++i)
-                if (idle[i].dev == *dev && idle[i].bytes >= bytes && idle[i].bytes <= 2 * bytes && (best == idle.size() || idle[i].bytes < idle[best].bytes)) best = i;
-            if (best < idle.size()) {
-                *p = idle[best].p;
-                *got = idle[best].bytes;
-                idle[best] = idle.back();
-                idle.pop_back();
+            int best = -1;
+            for (int i = 0; i < n; ++i)
+                if (idle[i].dev == *dev && idle[i].bytes >= bytes && idle[i].bytes <= 2 * bytes && (best < 0 || idle[i].bytes < idle[best].bytes)) best = i;
+            if (best >= 0) {
+                const Block b = remove(best);
+                *p = b.p;
+                *got = b.bytes;
                 return hipSuccess;
             }
         }
@@ -69,23 +75,24 @@ struct DevPool {
             (void)hipFree(p);
             return;
         }
-        std::vector<void *> out;                             // what no longer fits, oldest first
+        Block out[MAX_IDLE];                                  // what no longer fits, oldest first
+        int m = 0;
         {
             std::lock_guard<std::mutex> lock(mu);
+            if (n == MAX_IDLE) out[m++] = remove(0);
             size_t held = bytes;
-            idle.push_back(Block{p, bytes, dev});
-            for (size_t i = 0; i + 1 < idle.size(); ++i)
+            for (int i = 0; i < n; ++i)
                 if (idle[i].dev == dev) held += idle[i].bytes;
-            for (size_t i = 0; held > POOL_BYTES && i + 1 < idle.size();)
+            for (int i = 0; held > POOL_BYTES && i < n;)
                 if (idle[i].dev == dev) {
-                    out.push_back(idle[i].p);
                     held -= idle[i].bytes;
-                    idle.erase(idle.begin() + (long)i);
+                    out[m++] = remove(i);
                 } else {
                     ++i;
                 }
+            idle[n++] = Block{p, bytes, dev};
         }
-        for (void *q : out) (void)hipFree(q);
+        for (int i = 0; i < m; ++i) (void)hipFree(out[i].p);
     }
 };
 

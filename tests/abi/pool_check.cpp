@@ -2,6 +2,19 @@
 #include "../../paper_1802_02422_amd/csrc/pool.hpp"
 
 #include <cstdio>
+#include <new>
+
+static bool no_new = false;
+void *operator new(size_t n)
+{
+    if (no_new) {
+        std::puts("operator new");
+        std::exit(1);
+    }
+    return std::malloc(n);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 using namespace ivf;
 
@@ -55,9 +68,34 @@ static int large_blocks_leave_the_others()
     return 0;
 }
 
+// no memory of the host is asked for (a container that grows throws where there is none, out of a destructor), however many
+// blocks come back; devices do not share them
+static int many_blocks_and_devices()
+{
+    DevPool pool;
+    FakeDevice &d = fake();
+    void *p[200];
+    size_t got[200];
+    int dev[200];
+    for (int i = 0; i < 200; ++i) CHECK(pool.take(&p[i], &got[i], &dev[i], 4096) == hipSuccess);
+    no_new = true;
+    for (int i = 0; i < 200; ++i) pool.give(p[i], got[i], dev[i]);
+    no_new = false;
+    CHECK(d.live.size() > 0 && d.live.size() < 200);
+    const int mallocs = d.mallocs;
+    d.current = 1;
+    CHECK(!once(pool, 4096) && d.mallocs == mallocs + 1);
+    pool.trim(0);
+    CHECK(d.live.size() == 1);
+    pool.trim(1);
+    CHECK(d.used == 0);
+    d.current = 0;
+    return 0;
+}
+
 int main()
 {
-    if (idle_blocks_make_room() || large_blocks_leave_the_others()) return 1;
+    if (idle_blocks_make_room() || large_blocks_leave_the_others() || many_blocks_and_devices()) return 1;
     std::puts("ok");
     return 0;
 }
