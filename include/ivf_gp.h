@@ -104,7 +104,7 @@ typedef struct ivf_index_desc {
 int ivf_load_index(const ivf_index_desc *desc, void *hip_stream, ivf_index **out);
 
 /* Release the handle and all device memory it owns (waits for the device), and the scratch that the library
- * keeps between index-time calls (at most 1 GiB a GPU). */
+ * keeps on its GPU between index-time calls (at most 1 GiB). */
 void ivf_free_index(ivf_index *index);
 
 /*

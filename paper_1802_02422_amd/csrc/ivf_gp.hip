@@ -316,6 +316,7 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k,
 }  // namespace
 
 struct ivf_index {
+    int dev = 0;                 // the GPU it lies on
     int D = 0, M = 0, L = 0;
     int64_t K = 0, N = 0;
     float *centroids = nullptr, *cnorm = nullptr, *alpha = nullptr, *cst = nullptr;
@@ -357,8 +358,7 @@ extern "C" void ivf_free_index(ivf_index *ix)
         if (p) (void)hipFree(p);
     for (auto &v : ix->ev)
         for (hipEvent_t e : v) (void)hipEventDestroy(e);
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) g_pool.trim(dev);
+    g_pool.trim(ix->dev);
     delete ix;
 }
 
@@ -384,6 +384,7 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
     const int64_t K = d->K, N = d->N, nsub = K * d->L;
     const int D = d->D, M = d->M, L = d->L;
     ix->D = D; ix->M = M; ix->L = L; ix->K = K; ix->N = N;
+    HIPCHK(hipGetDevice(&ix->dev));
     int rc;
     if ((rc = dev_copy(ix->centroids, d->centroids, (size_t)K * D, st))) return rc;
     if ((rc = dev_copy(ix->nbr, d->nbr, (size_t)nsub, st))) return rc;
