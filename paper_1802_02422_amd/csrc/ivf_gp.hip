@@ -893,22 +893,22 @@ struct ArgminCtx {
             best = static_cast<unsigned long long *>(mem.p);
             return IVF_OK;
         }
-        keep_rows = many_runs && packed_rows(max_rows) * Dp * (int64_t)sizeof(_Float16) <= (8ll << 30);
-        const int64_t rows = keep_rows ? max_rows : chunk;
-        const int64_t n_words = 1 + (keep_rows ? (max_rows + chunk - 1) / chunk : 1);
         // room for 24 entries per row on average (10 are usual at K = 2^16, growing with log K) and for 8 pairs (one is
         // usual), and for at least 2^16 of either in a segment
         seg_cap = (unsigned long long)(24 * chunk + SHORTLIST_SEGS - 1) / SHORTLIST_SEGS;
         pair_cap = (unsigned long long)(8 * chunk + SHORTLIST_SEGS - 1) / SHORTLIST_SEGS;
         if (seg_cap < (1ull << 16)) seg_cap = 1ull << 16;
         if (pair_cap < (1ull << 16)) pair_cap = 1ull << 16;
+        keep_rows = many_runs && packed_rows(max_rows) * Dp * (int64_t)sizeof(_Float16) <= (8ll << 30);
         // one allocation for everything, 256-byte aligned pieces
         size_t total = 0;
         auto place = [&](auto *&p, size_t count) {
             p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(total);
             total += (count * sizeof(*p) + 255) / 256 * 256;
         };
-        auto all = [&]() {
+        auto all = [&](size_t base) {
+            const int64_t rows = keep_rows ? max_rows : chunk, n_words = 1 + (keep_rows ? (max_rows + chunk - 1) / chunk : 1);
+            total = base;
             place(best, (size_t)chunk);
             place(chk, (size_t)packed_rows(K) * Dp);
             place(clen, (size_t)packed_rows(K));
@@ -921,11 +921,15 @@ struct ArgminCtx {
             place(list, (size_t)seg_cap * SHORTLIST_SEGS);
             place(pairs, (size_t)pair_cap * SHORTLIST_SEGS);
             place(counts, (size_t)N_COUNTS);
+            return total;
         };
-        all();
-        HIPCHK(mem.alloc(total));
-        total = reinterpret_cast<size_t>(mem.p);
-        all();
+        hipError_t e = mem.alloc(all(0));
+        if (e == hipErrorOutOfMemory && keep_rows) {            // packed a chunk at a time then, again in every run
+            keep_rows = false;
+            e = mem.alloc(all(0));
+        }
+        HIPCHK(e);
+        all(reinterpret_cast<size_t>(mem.p));
         return IVF_OK;
     }
     int set_centroids(const float *centroids_, hipStream_t st)

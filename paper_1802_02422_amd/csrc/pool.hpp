@@ -46,7 +46,8 @@ struct DevPool {
         int dev = 0;
         if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
         trim(dev);
-        return hipMalloc(p, bytes);
+        if ((e = hipMalloc(p, bytes)) != hipSuccess) (void)hipGetLastError();   // (reported here, not by the next launch)
+        return e;
     }
     // the smallest idle block that is not much larger than asked for, else a new one
     hipError_t take(void **p, size_t *got, int *dev, size_t bytes)
