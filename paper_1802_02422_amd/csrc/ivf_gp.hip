@@ -1300,6 +1300,7 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     ArgminCtx ctx;                               // the assignment's, with the packed centroid table
     DevTmp hi_mem;
+    StreamWait before_they_go(st);               // (every return below: the pool takes their blocks back when nothing uses them)
     SubregionTable table;
     if (region_in) {
         if (region_in != out_region)
