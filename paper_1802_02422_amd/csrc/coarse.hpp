@@ -12,6 +12,8 @@
 // rounding error of a distance is that of an fp32 dot product with 18 instead
 // of 96 accumulation steps.
 #pragma once
+#include <type_traits>
+
 #include "select.hpp"
 
 namespace ivf {
@@ -1606,7 +1608,9 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
             kv[j] = c < K ? float_key(row[c]) : 0xFFFFFFFFu;
         }
     };
-    for (int round = 0;; ++round) {
+    // the survivors, in order, up to PW_CAP of them; AGAIN: of those equal to lim only the first P, which alone can be among
+    // the P closest
+    auto collect = [&](auto again) {
         uint32_t total = 0, eq_seen = 0;
         for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
             uint32_t kv[16];
@@ -1614,7 +1618,7 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 bool sel = kv[j] <= lim && kv[j] != 0xFFFFFFFFu;
-                if (round) {                                   // of those equal to lim only the first P can be among the P closest
+                if constexpr (decltype(again)::value) {
                     const uint64_t eqm = __ballot(sel && kv[j] == lim);
                     if (kv[j] == lim) sel = sel && eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u)) < (uint32_t)P;
                     eq_seen += (uint32_t)__popcll(eqm);
@@ -1629,38 +1633,43 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
             }
         }
         wave_sync();
-        uint32_t s[PW_CAP / WAVE];
+        return total;
+    };
+    uint32_t s[PW_CAP / WAVE];
+    auto select_kept = [&](uint32_t total) {
 #pragma unroll
         for (int r = 0; r < PW_CAP / WAVE; ++r) s[r] = r * WAVE + lane < (int)total ? sk[r * WAVE + lane] : 0xFFFFFFFFu;
         wave_select<PW_CAP / WAVE>(s, (uint32_t)P, pivot, need);
-        if (total <= (uint32_t)PW_CAP) {
-            wave_emit<PW_CAP / WAVE>(s, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
-                oid[pos] = si[r * WAVE + lane];
-                od[pos] = key_float(key);
-            });
-            return;
-        }
-        // More than fit.  The P closest of any PW_CAP distances bound the P closest of all: first of the 512 smallest, one of
-        // each lane's column of every eighth block, which are near ones wherever those lie (of the ones kept, the first in
-        // order, centroids whose numbers follow their places took six rounds, 0.2 ms); should that not be enough, of those
-        // kept.  At most P of these equal lim then, the others lie below it, and at least PW_CAP - P distances fall above
-        // the new bound every time.
-        if (round == 0) {
-            uint32_t low[PW_CAP / WAVE];
+    };
+    uint32_t total = collect(std::false_type());
+    if (total > (uint32_t)PW_CAP) {
+        // The P closest of any PW_CAP distances bound the P closest of all: first of the 512 smallest, one of each lane's column
+        // of every eighth block, which are near ones wherever those lie (of the first survivors in order, centroids whose
+        // numbers follow their places took six rounds, 0.2 ms); should that not be enough, of those kept.  At most P of
+        // these equal lim then, the others lie below it, and at least PW_CAP - P distances fall above the new bound every time.
 #pragma unroll
-            for (int r = 0; r < PW_CAP / WAVE; ++r) low[r] = 0xFFFFFFFFu;
-            for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
-                uint32_t kv[16];
-                fetch(f0, kv);
+        for (int r = 0; r < PW_CAP / WAVE; ++r) s[r] = 0xFFFFFFFFu;
+        for (uint32_t f0 = 0; f0 < nflag; f0 += 16) {
+            uint32_t kv[16];
+            fetch(f0, kv);
 #pragma unroll
-                for (int j = 0; j < 16; ++j) low[j % (PW_CAP / WAVE)] = kv[j] < low[j % (PW_CAP / WAVE)] ? kv[j] : low[j % (PW_CAP / WAVE)];
-            }
-            wave_select<PW_CAP / WAVE>(low, (uint32_t)P, pivot, need);
+            for (int j = 0; j < 16; ++j) s[j % (PW_CAP / WAVE)] = kv[j] < s[j % (PW_CAP / WAVE)] ? kv[j] : s[j % (PW_CAP / WAVE)];
         }
-        const uint32_t lower = need > 0 ? pivot : pivot - 1u;
-        lim = lower < lim ? lower : lim;
-        wave_sync();                                           // the kept ones have been read
+        wave_select<PW_CAP / WAVE>(s, (uint32_t)P, pivot, need);
+        while (true) {
+            const uint32_t lower = need > 0 ? pivot : pivot - 1u;
+            lim = lower < lim ? lower : lim;
+            wave_sync();                                       // the kept ones have been read
+            total = collect(std::true_type());
+            if (total <= (uint32_t)PW_CAP) break;
+            select_kept(total);
+        }
     }
+    select_kept(total);
+    wave_emit<PW_CAP / WAVE>(s, pivot, need, [&](uint32_t pos, int r, uint32_t key) {
+        oid[pos] = si[r * WAVE + lane];
+        od[pos] = key_float(key);
+    });
 }
 
 }  // namespace ivf

@@ -201,13 +201,13 @@ int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t
 // 17 us for 300 queries, 38 for 10 000; a workgroup a query 26 and 405).  Above, a wavefront has P flagged blocks to read,
 // 16 at a time, and takes 20 us (P = 16), 33 (40) or 50 (64) however few the queries are, where the 512 workgroups
 // that run at a time take 24: 500 queries 29, 1000 51, 2000 94, P = 64 with a wavefront each 51, 52, 54.  Where more
-// distances survive than a wavefront holds it takes twice that: from 24 P queries on it is the faster one, and
-// about equal then.
+// distances survive than a wavefront holds (centroids whose numbers follow their places) it takes twice that.  From 16 P
+// queries on it is the faster one, or equal, and then at most 1.4 times as slow up to 24 P.
 bool wave_select_fits(int64_t K, int P, int64_t nq)
 {
     if (K <= PW_K_DIRECT) return true;
     const int64_t nb = (K + BMW - 1) / BMW;
-    return nb <= PW_NB_MAX && P <= nb && P <= PW_P_MAX && nq >= 24 * P;
+    return nb <= PW_NB_MAX && P <= nb && P <= PW_P_MAX && nq >= 16 * P;
 }
 
 int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K, int P, int32_t *pid,

@@ -286,7 +286,7 @@ def test_scoring_from_whole_rows(K, L, nprobe, nq):
     parity.check_search(ix, Q, nprobe, 0.3, 20, out).assert_ok()
 
 
-@pytest.mark.parametrize("nq,K,P", [(1536, 4096, 64), (1541, 4161, 64), (1535, 4096, 64), (960, 20000, 40), (1537, 65536, 64), (5, 4096, 16),
+@pytest.mark.parametrize("nq,K,P", [(1024, 4096, 64), (1031, 4161, 64), (1023, 4096, 64), (960, 20000, 40), (1025, 65536, 64), (5, 4096, 16),
                                     (384, 2049, 16), (49, 8192, 2)])
 @pytest.mark.parametrize("kind", ["line", "pairs", "ties"])
 def test_selection_where_near_centroids_have_near_ids(nq, K, P, kind):
