@@ -155,6 +155,32 @@ int pack_rows(const float *X, int64_t n, int D, uint32_t *gmax, _Float16 *P, flo
 // 1024 centroids: 40 us as one workgroup's sweep, 16 as eight).
 constexpr int64_t SWEEP_MIN_TILES = 2048;
 
+// Centroid tiles that a workgroup of the swept GEMM takes: as many as leave 1024 workgroups, but no more than 64 and no
+// fewer than 8, unless the last round is the better filled with another number.  Two workgroups fit a compute unit, 64 an
+// XCD; the XCD with most work goes through its sweeps, each with a tile's time for loading its query tile, in rounds, and half
+// a sweep more where they drift apart.  By sweep length 64, 32, 16, 8 (us; in brackets the one taken, a * for 1024 workgroups):
+// 10 000 queries x 65 536 844, 748*, [695], 666; x 131 072 1412*, 1300, [1232], 1271; x 100 096 1150*, 1062, [974], 981;
+// 7000 x 65 536 510, 496, [459]*, 469; 4000 259, 231, [248]*, 252; 100 000 x 2432 (19 tiles) 315, 315, 371*, [271]; x 1152
+// (9 tiles: all but 8 take it whole) [181], 181, 181, 217*.
+int sweep_length(int64_t tiles_q, int64_t tiles_c)
+{
+    auto estimate = [&](int p) {
+        const int64_t groups = (tiles_c + p - 1) / p, rounds = (group_grid(tiles_q, groups) / N_XCD + 63) / 64;
+        return (double)rounds * ((double)tiles_c / (double)groups + 1.0) + 0.5 * (double)(p < tiles_c ? p : tiles_c);
+    };
+    int best = 64;
+    while (best > SWEEP_BMC && tiles_q * ((tiles_c + best - 1) / best) < 1024) best /= 2;
+    double least = 0.95 * estimate(best);
+    for (int p = 64; p >= SWEEP_BMC; p /= 2) {
+        const double e = estimate(p);
+        if (e < least) {
+            best = p;
+            least = e;
+        }
+    }
+    return best;
+}
+
 int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t nq, const _Float16 *Cp,
                   const float *cn, const float *csi, int64_t K, int Dp, float *Dt, float *bm, hipStream_t st)
 {
@@ -176,11 +202,9 @@ int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t
     if ((stages == 6 || stages == 8) && K % GT == 0 && (int64_t)tiles_q * tiles_c >= SWEEP_MIN_TILES) {
         // Query tile held in registers, centroid tiles swept.  The kernel works on whole tiles: the
         // rows of a partial last query tile are computed too, into the padding every per-query
-        // buffer of the coarse stage carries up to a multiple of the tile height.  Two workgroups fit a
-        // compute unit: shorter sweeps where 64 tiles each would leave some without work.
-        int per_wg = 64;
+        // buffer of the coarse stage carries up to a multiple of the tile height.
+        const int per_wg = sweep_length(tiles_q, tiles_c);
         static_assert(64 % SWEEP_BMC == 0, "a workgroup's first tile starts a 64-byte piece of the block minima");
-        while (per_wg > SWEEP_BMC && tiles_q * ((tiles_c + per_wg - 1) / per_wg) < 1024) per_wg /= 2;
         const int64_t g2 = group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg);
         if (g2 >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
         if (stages == 6)
