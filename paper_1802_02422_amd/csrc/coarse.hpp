@@ -138,7 +138,7 @@ __device__ __forceinline__ floatx16 mfma3(const gu32x4 (&bfrag)[2], const gu32x4
 // consecutive centroids, which the epilogues store as 128-bit words and reduce
 // without leaving the lane.  buf0 and buf1 each hold (128 + 128) rows x 64 bytes.
 //
-// HI = true: the operands are the hi-only tables of pack_hi_kernel (a row stage of 64 bytes holds 32
+// HI = true: the operands are the hi-only tables of pack_hi_rows_kernel (a row stage of 64 bytes holds 32
 // dimensions: for lane half h the chunks 2h and 2h+1 are its 8 dimensions of the stage's first and
 // second 16), Dp is that table's row length in 4-byte units, and a stage is two products hi*hi: a
 // third of the MFMA work and half the bytes for an approximation of <q,c> whose error the caller bounds.

@@ -45,8 +45,8 @@ def _check(C, Q, gid, gd):
 @pytest.mark.parametrize("D,K,nq", [(96, 4096, 3000), (128, 1000, 700), (20, 300, 1), (100, 2500, 129), (64, 64, 50),
                                     (96, 1000, 300), (96, 50, 40), (96, 20000, 500), (128, 128, 128)])
 def test_shortlist_assignment_is_the_exact_nearest(D, K, nq):
-    """Widths that take the swept kernel (96, 128, 100 -> 128) and the tile kernel (20, 64); whole and partial
-    last centroid tiles, fewer centroids than a tile, more tiles than one workgroup sweeps, one row."""
+    """Widths of 1 to 4 stages of the swept kernel (20 -> 32, 64, 96, 100 -> 128; wider rows take the tile kernel, below); whole
+    and partial last centroid tiles, fewer centroids than a tile, more tiles than one workgroup sweeps, one row."""
     print("case: shortlist", D, K, nq, flush=True)
     rng = np.random.default_rng(7 * D + K + nq)
     # clustered points around the centroids, rows of very different magnitude, a point that is a centroid
@@ -216,3 +216,25 @@ def test_encoder_takes_rows_that_are_not_finite(D, M, codes):
         assert (code.cpu().numpy()[5] == 0).all()
         alone = ivf.ivf_encode(d, up(Q[rest]))
         assert (alone[2].cpu().numpy() == code.cpu().numpy()[rest]).all() and (alone[3].cpu().numpy() == byte.cpu().numpy()[rest]).all()
+
+
+@pytest.mark.parametrize("D,K,nq", [(132, 700, 300), (160, 128, 129), (256, 2000, 500), (1024, 300, 130)])
+def test_wide_rows_take_the_tile_kernel(D, K, nq):
+    """More than 128 dimensions: one tile of rows and centroids a workgroup, partial ones of either, rows of different size;
+    decided by the shortlist, and by the one-pass kernel where every centroid is the same."""
+    print("case: shortlist, wide rows", D, K, nq, flush=True)
+    rng = np.random.default_rng(D + K)
+    C = rng.standard_normal((K, D)) * np.exp2(rng.integers(-6, 1, size=(K, 1)))
+    own = rng.integers(0, K, size=nq)
+    Q = C[own] + 0.3 * rng.standard_normal((nq, D)) * np.linalg.norm(C[own], axis=1, keepdims=True) / np.sqrt(D)
+    C, Q = C.astype(np.float32), Q.astype(np.float32)
+    before = ivf.ivf_assign_stats()
+    gid, gd = _assign(C, Q)
+    after = ivf.ivf_assign_stats()
+    assert after[0] == before[0] + 1 and after[1] == before[1]
+    _check(C, Q, gid, gd)
+    big = np.tile(Q, (20000 // nq + 1, 1))
+    gid, gd = _assign(np.tile(C[:1], (2048, 1)), big)
+    last = ivf.ivf_assign_stats()
+    assert last[1] == after[1] + 1 and last[0] == after[0]
+    assert (gid == 0).all()
