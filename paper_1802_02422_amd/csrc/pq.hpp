@@ -98,8 +98,8 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
         for (int k = 0; k < 4; ++k) {
             hash[k] = 0;
 #pragma unroll
-            for (int t = 0; t < DS; ++t) hash[k] = (hash[k] ^ __float_as_uint(cw[k][t] + 0.f)) * 0x9E3779B1u;   // (-0 is 0)
-            hash[k] >>= 24;
+            for (int t = 0; t < DS; ++t) hash[k] = (hash[k] << 7 | hash[k] >> 25) ^ __float_as_uint(cw[k][t] + 0.f);   // (-0 is 0)
+            hash[k] = hash[k] * 0x9E3779B1u >> 24;
             atomicMin(&first[hash[k]], (uint32_t)(lane + k * WAVE));
         }
         wave_sync();
