@@ -308,14 +308,15 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k,
     // longer the lists are (scan + k-select in us with one for 16 descriptors against one for 256; 64 descriptors of 30
     // points, 64 queries 27 against 34, 333 40 against 36; of 120 points, 333 63 against 85, 1000 114 against 93; 256 of 30
     // points, 64 queries 33 against 37, 200 52 against 41; of 120, 64 61 against 81, 200 98 against 88; of 6, 200 35 against
-    // 24), and where there are points for them (288 descriptors of 6, k = 100, one query 32 against 28; 520 of 3, a search 63
-    // against 58).
+    // 24), and where there are points for them, more where four wavefronts share them anyway and the k-select has more to do
+    // (288 descriptors of 6, k = 100, one query 32 against 28; 520 of 3, k = 89, a search 63 against 58; 530 of 23, k = 94, five
+    // queries 158 against 151).
     int nsplit = (int)((2048 + tile - 1) / tile);
     if (nsplit > 8) nsplit = 8;
     const int whole = (S + SCAN_WAVES * WAVE - 1) / (SCAN_WAVES * WAVE);
     int most = whole;
     if ((double)tile * (S < WAVE ? WAVE : S) < 16384.0 + 200.0 * (per < 190.0 ? per : 190.0)) {
-        const double by_points = (double)S * per / 640.0;
+        const double by_points = (double)S * per / (640.0 * (whole > 1 ? 1.0 + k / 32.0 : 1.0));
         most = (S + 15) / 16;
         if (by_points < (double)most) most = by_points > (double)whole ? (int)by_points : whole;
     }
