@@ -214,7 +214,7 @@ int launch_coarse(const _Float16 *xp, const float *xn, const float *xsi, int64_t
         LAUNCHCHK("coarse_gemm_sweep_kernel");
         return IVF_OK;
     }
-    const int64_t grid = group_grid(tiles_q, tiles_c);
+    const int64_t grid = tile_grid(tiles_q, tiles_c);
     if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
     coarse_gemm_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(xp, xn, xsi, nq, Cp, cn, csi, K, Dp, Dt, ldt, bm, nb, tiles_q);
     LAUNCHCHK("coarse_gemm_kernel");

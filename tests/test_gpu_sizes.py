@@ -343,7 +343,9 @@ def test_scoring_does_not_depend_on_the_batch(K, L, nprobe, few, many):
     parity.check_search(ix, Q[take], nprobe, 0.3, 20, {n: v[take] for n, v in big.items()}).assert_ok()
 
 
-@pytest.mark.parametrize("nq,K,D", [(4100, 100, 64), (1300, 1100, 96), (33_000, 9 * 128, 96), (66_000, 19 * 128, 128), (1000, 73 * 128, 96)])
+@pytest.mark.parametrize("nq,K,D", [(4100, 100, 64), (1300, 1100, 96), (33_000, 9 * 128, 96), (66_000, 19 * 128, 128), (1000, 73 * 128, 96),
+                                     (2900, 1100, 96), (2950, 130, 200), (3400, 2001, 32)])
 def test_distance_gemm_over_few_groups(nq, K, D):
-    """The same where the groups of centroids that are dealt to the XCDs are fewer than 8, or no multiple of 8."""
+    """The same where the groups of centroids that are dealt to the XCDs are fewer than 8, or no multiple of 8, and on both
+    sides of the 24 query tiles from which these are dealt."""
     test_distance_gemm_over_few_query_tiles(nq, K, D)
