@@ -186,7 +186,8 @@ def measure(args, workload, nq=0, with_oracle=True, with_cpu_baseline=True, cali
     gemm_ms = stage_ms["coarse_gemm"] / max(passes, 1)
     gemm_bytes = spec.nq * args.steps / max(passes, 1) * (spec.K + nb + spec.D) * 4 + spec.K * spec.D * 4   # per launch
     gemm_kernel = ("coarse_gemm_skinny_kernel" if spec.nq <= 64 else
-                   "coarse_gemm_sweep_kernel" if spec.K % 128 == 0 and -(-spec.D // 32) * 2 in (6, 8) else "coarse_gemm_kernel")
+                   "coarse_gemm_sweep_kernel" if spec.K % 128 == 0 and -(-spec.D // 32) * 2 in (6, 8)
+                   and -(-spec.nq // 128) * (spec.K // 128) >= 2048 else "coarse_gemm_kernel")
     gemm_achieved = gemm_bytes / (gemm_ms * 1e-3) / 1e9 if gemm_ms > 0 else 0.0
 
     copy_gbs = None
