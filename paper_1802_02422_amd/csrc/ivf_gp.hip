@@ -293,8 +293,9 @@ int64_t dt_rows(int64_t n, int64_t K, int Dp)
     return sweep ? (n + GT - 1) / GT * GT : n;
 }
 
-// per: points of a subregion on average
-SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated)
+// per: points of a subregion on average; shared: whether several workgroups may divide what one wavefront would do (scratch for
+// more partial lists; the results are the same)
+SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated, bool shared = true)
 {
     SearchPlan pl;
     pl.tile = tile;
@@ -315,7 +316,7 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k,
     if (nsplit > 8) nsplit = 8;
     const int whole = (S + SCAN_WAVES * WAVE - 1) / (SCAN_WAVES * WAVE);
     int most = whole;
-    if ((double)tile * (S < WAVE ? WAVE : S) < 16384.0 + 200.0 * (per < 190.0 ? per : 190.0)) {
+    if (shared && (double)tile * (S < WAVE ? WAVE : S) < 16384.0 + 200.0 * (per < 190.0 ? per : 190.0)) {
         const double by_points = (double)S * per / (640.0 * (whole > 1 ? 1.0 + k / 32.0 : 1.0));
         most = (S + 15) / 16;
         if (by_points < (double)most) most = by_points > (double)whole ? (int)by_points : whole;
@@ -793,11 +794,16 @@ extern "C" int ivf_search_noalloc(ivf_index *ix, const float *queries, int64_t n
     if (rc || nq == 0) return rc;
     const int S = (int)ivf_num_kept(nprobe, ix->L, prune_frac);
     // the whole batch in one pass: the scratch is carved out of the static array, 256-byte aligned pieces
-    const SearchPlan pl = plan_search(ix->K, ix->D, ix->M, nprobe, S, mean_length(ix), k, nq, ix->rot_t != nullptr);
+    SearchPlan pl;
     size_t off[WS_COUNT], total = 0;
-    for (int i = 0; i < WS_COUNT; ++i) {
-        off[i] = total;
-        total += (pl.bytes[i] + 255) / 256 * 256;
+    for (bool shared : {true, false}) {
+        pl = plan_search(ix->K, ix->D, ix->M, nprobe, S, mean_length(ix), k, nq, ix->rot_t != nullptr, shared);
+        total = 0;
+        for (int i = 0; i < WS_COUNT; ++i) {
+            off[i] = total;
+            total += (pl.bytes[i] + 255) / 256 * 256;
+        }
+        if (total <= (size_t)IVF_NOALLOC_SCRATCH_BYTES) break;
     }
     if (total > (size_t)IVF_NOALLOC_SCRATCH_BYTES)
         return fail(IVF_EINVAL, "ivf_search_noalloc: this batch needs %zu bytes of scratch, the static array holds %zu "

@@ -349,3 +349,20 @@ def test_distance_gemm_over_few_groups(nq, K, D):
     """The same where the groups of centroids that are dealt to the XCDs are fewer than 8, or no multiple of 8, and on both
     sides of the 24 query tiles from which these are dealt."""
     test_distance_gemm_over_few_query_tiles(nq, K, D)
+
+
+def test_noalloc_takes_a_batch_that_fits_with_fewer_workgroups_a_query():
+    """298 queries x 52 001 centroids fill the 64 MiB array: 66.7 MB with one scan workgroup a query, 67.7 with two (the array
+    holds 67.1), which the lists of 20 points would have otherwise.  The results do not depend on it."""
+    print("case: noalloc at its limit", flush=True)
+    ix = _random_index(52_001, 4, 32, 8, 4_300_000, 3)
+    h = ivf.ivf_load_index(parity.to_device(ix))
+    Q = torch.from_numpy(np.random.default_rng(4).standard_normal((301, 32)).astype(np.float32)).cuda()
+    ids = torch.full((301, 100), -7, dtype=torch.int32, device="cuda")
+    d = torch.full((301, 100), -7.0, dtype=torch.float32, device="cuda")
+    ivf.ivf_search_noalloc(h, Q[:298], 16, 1.0, 100, ids[:298], d[:298])
+    ref_ids, ref_d = ivf.ivf_search(h, Q[:298], 16, 1.0, 100)
+    assert torch.equal(ids[:298], ref_ids) and torch.equal(d[:298], ref_d)
+    with pytest.raises(ivf.IvfError):
+        ivf.ivf_search_noalloc(h, Q, 16, 1.0, 100, ids, d)
+    ivf.ivf_free_index(h)
