@@ -26,6 +26,7 @@
 #include "pq.hpp"
 #include "query.hpp"
 #include "scan.hpp"
+#include "sparse.hpp"
 #include "train.hpp"
 
 using namespace ivf;
@@ -274,11 +275,57 @@ struct SearchWs {
     float *lut = nullptr;
     uint64_t *partial = nullptr;
     float *qrot = nullptr;       // rotated queries (indexes with a rotation in front of the PQ)
+    unsigned char *sparse = nullptr;
 };
 
 enum { WS_DT, WS_BM, WS_QN, WS_QSI, WS_QPK, WS_PID, WS_PD, WS_DESC, WS_LUT, WS_PARTIAL, WS_QROT, WS_COUNT };
 
+// Scratch of a pass of the search without the distance matrix: pieces of one buffer.
+enum { SP_QH, SP_QLEN, SP_BEST, SP_FLAG, SP_LIST, SP_RANK, SP_THR, SP_COUNT, SP_OFFSET, SP_HARD, SP_HROWS, SP_HN, SP_HSI, SP_PAIRS, SP_ITEMS,
+       SP_BIG, SP_PIECES };   // SP_BIG: the distances of the flagged blocks, then the scores
+struct SparsePlan {
+    int cap = 0, shift = 0;
+    int64_t block_items = 0, region_items = 0, count_words = 0;
+    size_t off[SP_PIECES], total = 0;
+};
+
+// Whether an index gets the tables for it.
+bool sparse_table(int64_t K, int D) { return K >= SPARSE_MIN_K && (K + BMW - 1) / BMW <= PS_NB_MAX && packed_dim(D) <= 128; }
+
+SparsePlan plan_sparse(int64_t K, int D, int P, int L, int64_t n)
+{
+    SparsePlan sp;
+    const int Dp = packed_dim(D);
+    const int64_t nb = (K + BMW - 1) / BMW, pad = packed_rows(n);
+    while ((1 << sp.shift) < 2 * P || sp.shift < 2) ++sp.shift;
+    sp.cap = 1 << sp.shift;
+    const int64_t bp = n * (sp.cap < nb ? sp.cap : nb), rp = n * P;
+    sp.block_items = bp / PAIR_Q + (bp < nb ? bp : nb);
+    sp.region_items = rp / PAIR_Q + (rp < K ? rp : K);
+    sp.count_words = (nb + K + 8 + 1) / 2;                     // 64-bit words: counts of blocks and regions, totals
+    size_t bytes[SP_PIECES];
+    bytes[SP_QH] = (size_t)pad * Dp * sizeof(_Float16);
+    bytes[SP_QLEN] = (size_t)pad * sizeof(float2);
+    bytes[SP_BEST] = (size_t)pad * 2 * minima_half(K) * sizeof(float);
+    bytes[SP_FLAG] = bytes[SP_THR] = bytes[SP_HARD] = (size_t)n * 4;
+    bytes[SP_LIST] = bytes[SP_RANK] = (size_t)n * sp.cap * 4;
+    bytes[SP_COUNT] = (size_t)sp.count_words * 8;
+    bytes[SP_OFFSET] = (size_t)(K > nb ? K : nb) * 4;
+    bytes[SP_HROWS] = (size_t)pad * Dp * 2 * sizeof(_Float16);
+    bytes[SP_HN] = bytes[SP_HSI] = (size_t)pad * sizeof(float);
+    bytes[SP_PAIRS] = (size_t)n * sp.cap * 4;
+    bytes[SP_ITEMS] = (size_t)(sp.block_items > sp.region_items ? sp.block_items : sp.region_items) * sizeof(uint4);
+    const size_t cand = (size_t)n * sp.cap * BMW * 4, keys = (size_t)n * P * L * 4;
+    bytes[SP_BIG] = cand > keys ? cand : keys;
+    for (int i = 0; i < SP_PIECES; ++i) {
+        sp.off[i] = sp.total;
+        sp.total += (bytes[i] + 255) / 256 * 256;
+    }
+    return sp;
+}
+
 struct SearchPlan {
+    bool sparse = false;         // without the distance matrix
     int64_t tile = 0;            // queries per pass
     int S = 0, nsplit = 1, n_lists = 0, merge_n = 0, merge_pow2 = 0;
     size_t bytes[WS_COUNT] = {};
@@ -295,9 +342,10 @@ int64_t dt_rows(int64_t n, int64_t K, int Dp)
 
 // per: points of a subregion on average; shared: whether several workgroups may divide what one wavefront would do (scratch for
 // more partial lists; the results are the same)
-SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated, bool shared = true)
+SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated, bool shared = true, bool sparse = false)
 {
     SearchPlan pl;
+    pl.sparse = sparse;
     pl.tile = tile;
     pl.S = S;
     // Workgroups per query in the scan: fill the chip when the batch is small, but with at most 8 per
@@ -332,8 +380,8 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k,
     const size_t rows = (size_t)dt_rows(tile, K, Dp);
     const size_t tile_pad = (size_t)packed_rows(tile);   // the GEMM tiles copy whole tiles of packed rows
     const int64_t nb = (K + BMW - 1) / BMW;
-    pl.bytes[WS_DT] = rows * dt_stride(K) * sizeof(float);
-    pl.bytes[WS_BM] = rows * nb * sizeof(float);
+    pl.bytes[WS_DT] = sparse ? 0 : rows * dt_stride(K) * sizeof(float);
+    pl.bytes[WS_BM] = sparse ? 0 : rows * nb * sizeof(float);
     pl.bytes[WS_QN] = tile_pad * sizeof(float);
     pl.bytes[WS_QSI] = tile_pad * sizeof(float);
     pl.bytes[WS_QPK] = tile_pad * Dp * 2 * sizeof(_Float16);
@@ -354,6 +402,12 @@ struct ivf_index {
     int64_t K = 0, N = 0;
     float *centroids = nullptr, *cnorm = nullptr, *alpha = nullptr, *cst = nullptr;
     _Float16 *cpk = nullptr;     // centroids packed for the GEMM
+    // for the search without the distance matrix (NULL: not built): fp16 rows and their lengths, start values and bounds of the
+    // tiles, squared norms of the neighbours
+    _Float16 *chi = nullptr;
+    float2 *clen = nullptr;
+    float *mstart = nullptr, *nbr_norm = nullptr;
+    float4 *mtile = nullptr;
     float *csi = nullptr;        // csi[0] inverse scale of the packed centroids; csi[1] reduction word
     float *codebook = nullptr, *const_table = nullptr;
     float *rot_t = nullptr;      // transposed rotation in front of the PQ, or NULL
@@ -361,7 +415,7 @@ struct ivf_index {
     uint4 *sub_info = nullptr;   // per subregion: block offset, first position, length
     uint8_t *blocks = nullptr;
     int64_t scratch_limit = 8ll << 30;
-    Buf dt, bm, qn, qpk, qsi, probe_id, probe_d, desc, lut, partial, qrot;
+    Buf dt, bm, qn, qpk, qsi, probe_id, probe_d, desc, lut, partial, qrot, sparse;
     // optional per-stage timing with HIP events on the caller's stream
     bool profile = false;
     std::vector<hipEvent_t> ev[IVF_N_STAGES + 1];   // ev[s][i], ev[s+1][i] bracket stage s of pass i
@@ -386,7 +440,8 @@ extern "C" void ivf_free_index(ivf_index *ix)
     void *owned[] = {ix->centroids, ix->cnorm, ix->alpha, ix->cst, ix->codebook, ix->const_table,
                      ix->nbr, ix->ids, ix->sub_info, ix->blocks, ix->dt.p, ix->bm.p, ix->qn.p,
                      ix->cpk, ix->csi, ix->qpk.p, ix->qsi.p,
-                     ix->probe_id.p, ix->probe_d.p, ix->desc.p, ix->lut.p, ix->partial.p, ix->qrot.p, ix->rot_t};
+                     ix->probe_id.p, ix->probe_d.p, ix->desc.p, ix->lut.p, ix->partial.p, ix->qrot.p, ix->rot_t,
+                     ix->sparse.p, ix->chi, ix->clen, ix->mstart, ix->nbr_norm, ix->mtile};
     for (void *p : owned)
         if (p) (void)hipFree(p);
     for (auto &v : ix->ev)
@@ -436,6 +491,22 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
     HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->csi), 2 * sizeof(float)));
     if ((rc = pack_rows(ix->centroids, K, D, reinterpret_cast<uint32_t *>(ix->csi + 1), ix->cpk, ix->cnorm, ix->csi, st)))
         return rc;
+    if (sparse_table(K, D)) {
+        const int Dp = packed_dim(D);
+        const int64_t tiles = (K + GT - 1) / GT, pad = packed_rows(K);
+        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->chi), (size_t)pad * Dp * sizeof(_Float16)));
+        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->clen), (size_t)pad * sizeof(float2)));
+        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->mstart), (size_t)tiles * GT * sizeof(float)));
+        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->mtile), (size_t)tiles * sizeof(float4)));
+        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->nbr_norm), (size_t)nsub * sizeof(float)));
+        pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(ix->centroids, K, pad, D, Dp,
+                                                                                     reinterpret_cast<uint32_t *>(ix->csi + 1), ix->chi, ix->clen);
+        LAUNCHCHK("pack_hi_rows_kernel");
+        minima_tiles_kernel<<<dim3((unsigned)tiles), dim3(128), 0, st>>>(ix->clen, K, Dp, ix->mstart, ix->mtile);
+        LAUNCHCHK("minima_tiles_kernel");
+        neighbour_norm_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->nbr, nsub, ix->cnorm, ix->nbr_norm);
+        LAUNCHCHK("neighbour_norm_kernel");
+    }
     HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->cst), (size_t)nsub * sizeof(float)));
     cst_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->alpha, d->cs_dist2, L, nsub, ix->cst);
     LAUNCHCHK("cst_kernel");
@@ -536,9 +607,9 @@ int check_search_args(const ivf_index *ix, const float *queries, int64_t nq, int
 struct LdsPlan { size_t scan, merge, sp, ssp; };   // ssp: the fused selection + scoring launch
 
 // How the scoring of a search runs.  SCORE_STREAM_*: the whole row of distances through LDS, STREAM_512 / STREAM_1024 at a
-// time; SCORE_FUSED: selection and scoring in one launch of 1024 threads a query (where the selection needs a workgroup
+// time; SCORE_GIVEN_*: the scores are there (search without the distance matrix); SCORE_FUSED: selection and scoring in one launch of 1024 threads a query (where the selection needs a workgroup
 // of its own too); SCORE_GATHER: the rest.
-enum ScoreMode { SCORE_GATHER, SCORE_FUSED, SCORE_STREAM_512, SCORE_STREAM_1024 };
+enum ScoreMode { SCORE_GATHER, SCORE_FUSED, SCORE_STREAM_512, SCORE_STREAM_1024, SCORE_GIVEN_512, SCORE_GIVEN_1024 };
 constexpr int STREAM_512 = 8192, STREAM_1024 = 16384;   // distances in LDS at a time (512 / 1024 threads)
 
 // Rows are read where they are at most as many bytes as half the 128-byte lines that P L gathers touch, K <= 16 P L, with these
@@ -551,9 +622,10 @@ constexpr int STREAM_512 = 8192, STREAM_1024 = 16384;   // distances in LDS at a
 //    P L = 2048 and K = 1024 326 against 293, 4096 688 against 662, 8192 431 against 455; P L = 1024, K = 8192 396 against 369;
 //    K = 4096, P L = 3072 745 against 726, 4096 772 against 790 (M = 16; with M = 8, K = 3324, P L = 3840, 2202 queries a search
 //    takes 268 against 274).  Up to 500 queries rows are equal or 2 us better there.
-ScoreMode score_mode(int64_t K, int P, int L, int64_t nq)
+ScoreMode score_mode(int64_t K, int P, int L, const SearchPlan &pl)
 {
-    const int64_t PL = (int64_t)P * L, nb = (K + BMW - 1) / BMW;
+    const int64_t PL = (int64_t)P * L, nb = (K + BMW - 1) / BMW, nq = pl.tile;
+    if (pl.sparse) return PL <= 4096 ? SCORE_GIVEN_512 : SCORE_GIVEN_1024;
     if (PL <= 4096 && K <= 16 * PL && (nq <= 512 ? K <= 12 * PL : K * PL >= (3ll << 22))) return SCORE_STREAM_512;
     if (PL > 4096 && PL <= 16384 && K <= 16 * PL && (K <= 8 * PL || nq >= 256)) return SCORE_STREAM_1024;
     if (P <= PS_P_MAX && nb <= PS_NB_MAX && PL > 4096) return SCORE_FUSED;
@@ -563,7 +635,7 @@ ScoreMode score_mode(int64_t K, int P, int L, int64_t nq)
 int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l)
 {
     const int64_t PL = (int64_t)P * ix->L;
-    const ScoreMode mode = score_mode(ix->K, P, ix->L, pl.tile);
+    const ScoreMode mode = score_mode(ix->K, P, ix->L, pl);
     l.scan = (size_t)SCAN_WAVES * pool_capacity(k) * sizeof(uint64_t);   // dynamic part: the pools
     l.merge = ((size_t)pl.merge_n + pl.merge_pow2) * sizeof(uint64_t);
     l.sp = (size_t)(PL + 3 * P) * sizeof(uint32_t);
@@ -576,7 +648,8 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
         if (l.sp < need) l.sp = need;
     }
     if (l.sp > 48 * 1024) {
-        const void *fn = mode == SCORE_STREAM_512 ? reinterpret_cast<const void *>(&score_prune_kernel<512, 2, STREAM_512>)
+        const void *fn = mode == SCORE_GIVEN_1024 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 4, -1>)
+                         : mode == SCORE_STREAM_512 ? reinterpret_cast<const void *>(&score_prune_kernel<512, 2, STREAM_512>)
                          : mode == SCORE_STREAM_1024 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 4, STREAM_1024>)
                          : PL > 16384 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 8>)
                          : PL > 4096 ? reinterpret_cast<const void *>(&score_prune_kernel<1024, 4>)
@@ -601,6 +674,121 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
                                      : reinterpret_cast<const void *>(&scan_kernel<8>);
         HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.scan));
     }
+    return IVF_OK;
+}
+
+// Stages 1 and 2 without the distance matrix: probes to pid and pd, the keys of the scores to ws.sparse (SP_BIG).
+template <class Mark>
+int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchWs &ws, int32_t *pid, float *pd, Mark mark, hipStream_t st)
+{
+    const int64_t K = ix->K;
+    const int D = ix->D, L = ix->L, Dp = packed_dim(D), nb = (int)((K + BMW - 1) / BMW);
+    const SparsePlan sp = plan_sparse(K, D, P, L, n);
+    auto piece = [&](auto *&p, int i) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(ws.sparse + sp.off[i]); };
+    int rc;
+    _Float16 *qh;
+    float2 *qlen;
+    piece(qh, SP_QH);
+    piece(qlen, SP_QLEN);
+    SparseArgs a;
+    piece(a.best, SP_BEST);
+    piece(a.n_flag, SP_FLAG);
+    piece(a.blist, SP_LIST);
+    piece(a.rank, SP_RANK);
+    piece(a.thr, SP_THR);
+    piece(a.count, SP_COUNT);
+    piece(a.offset, SP_OFFSET);
+    piece(a.hard, SP_HARD);
+    piece(a.hard_rows, SP_HROWS);
+    piece(a.hard_n, SP_HN);
+    piece(a.hard_si, SP_HSI);
+    piece(a.pairs, SP_PAIRS);
+    piece(a.items, SP_ITEMS);
+    piece(a.cand, SP_BIG);
+    piece(a.keys, SP_BIG);
+    a.total = a.count + nb + K;
+    a.K = K;
+    a.half_ld = minima_half(K);
+    a.nb = nb;
+    a.P = P;
+    a.L = L;
+    a.cap = sp.cap;
+    a.shift = sp.shift;
+    a.Dp = Dp;
+    a.tile = ix->mtile;
+    a.qlen = qlen;
+    a.qn = ws.qn;
+    a.qsi = ws.qsi;
+    a.cmax = reinterpret_cast<const uint32_t *>(ix->csi + 1);
+    a.Qp = ws.qpk;
+    a.Cp = ix->cpk;
+    a.cnorm = ix->cnorm;
+    a.csi = ix->csi;
+    a.probe_id = pid;
+    a.probe_d = pd;
+    a.nbr = ix->nbr;
+    a.nbr_norm = ix->nbr_norm;
+    a.cst = ix->cst;
+    a.alpha = ix->alpha;
+
+    const int64_t pad = packed_rows(n);
+    const unsigned rows_grid = (unsigned)(pad / 4), zero_grid = (unsigned)((sp.count_words + 2047) / 2048);
+    sparse_queries_kernel<<<dim3(rows_grid + zero_grid), dim3(256), 0, st>>>(Q, n, pad, D, Dp, a.cmax, qh, qlen, rows_grid,
+                                                                            reinterpret_cast<unsigned long long *>(a.count), sp.count_words);
+    LAUNCHCHK("sparse_queries_kernel");
+    const int tiles_q = (int)((n + GT - 1) / GT), tiles_c = (int)((K + GT - 1) / GT);
+    int per_wg = 64;
+    while (per_wg > 4 && group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg) < 1536) per_wg /= 2;
+    const int64_t grid = group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg);
+    if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
+    auto sweep = [&](auto kernel) {
+        kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(qh, ix->chi, ix->mstart, a.best, a.half_ld, tiles_q, tiles_c, per_wg);
+    };
+    if (Dp == 32) sweep(&coarse_minima_kernel<1>);
+    else if (Dp == 64) sweep(&coarse_minima_kernel<2>);
+    else if (Dp == 96) sweep(&coarse_minima_kernel<3>);
+    else sweep(&coarse_minima_kernel<4>);
+    LAUNCHCHK("coarse_minima_kernel");
+    const size_t flag_lds = (size_t)2 * a.half_ld * sizeof(uint32_t);
+    auto flag = [&](auto kernel, int grid_n, int block, size_t lds) -> int {
+        if (lds > 48 * 1024)
+            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        kernel<<<dim3((unsigned)grid_n), dim3(block), lds, st>>>(a);
+        LAUNCHCHK("flag_blocks_kernel");
+        return IVF_OK;
+    };
+    const bool wide = nb > 4096;                                // (16 blocks a thread at most)
+    if ((rc = wide ? flag(&flag_blocks_kernel<1024>, (int)n, 1024, flag_lds) : flag(&flag_blocks_kernel<256>, (int)n, 256, flag_lds))) return rc;
+    hard_rows_kernel<<<dim3(256), dim3(256), 0, st>>>(a);
+    LAUNCHCHK("hard_rows_kernel");
+    hard_minima_kernel<<<dim3(1024), dim3(256), 0, st>>>(a);
+    LAUNCHCHK("hard_minima_kernel");
+    if ((rc = wide ? flag(&hard_flag_kernel<1024>, 512, 1024, flag_lds) : flag(&hard_flag_kernel<256>, 1024, 256, flag_lds))) return rc;
+    auto grouped = [&](uint32_t *count, int64_t buckets, uint32_t *total, const int32_t *bucket, int width, const uint32_t *n_flag) -> int {
+        bucket_items_kernel<<<dim3((unsigned)((buckets + 1023) / 1024)), dim3(1024), 0, st>>>(count, buckets, total, a.offset, a.items);
+        LAUNCHCHK("bucket_items_kernel");
+        place_pairs_kernel<<<dim3((unsigned)((n * width + 255) / 256)), dim3(256), 0, st>>>(bucket, a.rank, n, width, sp.cap, sp.shift, n_flag, a.offset, a.pairs);
+        LAUNCHCHK("place_pairs_kernel");
+        return IVF_OK;
+    };
+    if ((rc = grouped(a.count, nb, a.total + 1, a.blist, sp.cap, a.n_flag))) return rc;
+#define IVF_PAIRS(REGION, N, TOTAL)                                                                                             \
+    do {                                                                                                                       \
+        const dim3 g_((unsigned)(N));                                                                                            \
+        if (Dp == 32) pair_distance_kernel<2, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                       \
+        else if (Dp == 64) pair_distance_kernel<4, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                  \
+        else if (Dp == 96) pair_distance_kernel<6, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                  \
+        else pair_distance_kernel<8, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                                \
+        LAUNCHCHK("pair_distance_kernel");                                                                                     \
+    } while (0)
+    IVF_PAIRS(false, sp.block_items, a.total + 2);
+    if ((rc = mark(1))) return rc;
+    probe_pick_kernel<256><<<dim3((unsigned)n), dim3(256), (size_t)(sp.cap + 2 * PICK_CAP) * sizeof(uint32_t), st>>>(a);
+    LAUNCHCHK("probe_pick_kernel");
+    if ((rc = mark(2))) return rc;
+    if ((rc = grouped(a.count + nb, K, a.total + 3, pid, P, nullptr))) return rc;
+    IVF_PAIRS(true, sp.region_items, a.total + 4);
+#undef IVF_PAIRS
     return IVF_OK;
 }
 
@@ -630,16 +818,18 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         };
         if ((rc = mark(0))) return rc;
         if ((rc = pack_rows(Q, n, D, nullptr, ws.qpk, ws.qn, ws.qsi, st))) return rc;
-        if ((rc = launch_coarse(ws.qpk, ws.qn, ws.qsi, n, ix->cpk, ix->cnorm, ix->csi, K, Dp, ws.dt, ws.bm, st))) return rc;
-        if ((rc = mark(1))) return rc;
+        if (pl.sparse) {
+            if ((rc = launch_sparse(ix, Q, n, P, ws, pid, pd, mark, st))) return rc;
+        } else if ((rc = launch_coarse(ws.qpk, ws.qn, ws.qsi, n, ix->cpk, ix->cnorm, ix->csi, K, Dp, ws.dt, ws.bm, st))) return rc;
+        if (!pl.sparse && (rc = mark(1))) return rc;
         // Where both are workgroups of 1024 threads with their keys in LDS, the selection runs inside the
         // scoring launch (one workgroup per query does both): one kernel boundary less, and the selection
         // of one query (LDS and ALU work) runs while the other workgroup of the CU waits for its gathers.
         const int nb = (int)((K + BMW - 1) / BMW);
-        const ScoreMode mode = score_mode(K, P, L, pl.tile);
+        const ScoreMode mode = score_mode(K, P, L, pl);
         const bool fused = mode == SCORE_FUSED;
-        if (!fused && (rc = launch_probe_select(ws.dt, ws.bm, n, K, P, pid, pd, st))) return rc;
-        if ((rc = mark(2))) return rc;
+        if (!fused && !pl.sparse && (rc = launch_probe_select(ws.dt, ws.bm, n, K, P, pid, pd, st))) return rc;
+        if (!pl.sparse && (rc = mark(2))) return rc;
 
         int64_t *ks = a.kept_sub_out ? a.kept_sub_out + q0 * S : nullptr;
         int64_t *ns = a.n_scanned_out ? a.n_scanned_out + q0 : nullptr;
@@ -659,7 +849,15 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
     select_score_prune_kernel<MV><<<dim3((unsigned)(2 * n)), dim3(1024), lds.ssp, st>>>(                             \
         ws.dt, dt_stride(K), ws.bm, K, nb, pid, pd, P, L, ix->nbr, ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, \
         n, Qt, D, M, ix->codebook, ws.lut)
-        if (fused && PL > 16384) IVF_SSP_LAUNCH(8);
+        if (pl.sparse) {
+            const uint32_t *given = reinterpret_cast<const uint32_t *>(ws.sparse + plan_sparse(K, D, P, L, n).off[SP_BIG]);
+            auto prune = [&](auto kernel, int block) {
+                kernel<<<dim3((unsigned)(2 * n)), dim3(block), lds.sp, st>>>(reinterpret_cast<const float *>(given), PL, K, pid, pd, P, L, ix->nbr,
+                    ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, n, Qt, D, M, ix->codebook, ws.lut);
+            };
+            if (mode == SCORE_GIVEN_512) prune(&score_prune_kernel<512, 2, -1>, 512);
+            else prune(&score_prune_kernel<1024, 4, -1>, 1024);
+        } else if (fused && PL > 16384) IVF_SSP_LAUNCH(8);
         else if (fused) IVF_SSP_LAUNCH(4);
         else if (mode == SCORE_STREAM_512) IVF_SP_LAUNCH(512, 2, STREAM_512);
         else if (mode == SCORE_STREAM_1024) IVF_SP_LAUNCH(1024, 4, STREAM_1024);
@@ -723,6 +921,30 @@ int scratch_of_current_device(unsigned char **out)
     return IVF_OK;
 }
 
+// Whether a pass of nq queries goes without the distance matrix (sparse.hpp).  What it saves grows with nq K, what it costs with
+// nq P and the launches.  A search in us, with / without, L = 64, D = 96: K = 2^20, P = 256, 512 queries 939 / 961, 1024 1821 / 1608,
+// 10 000 15 507 / 9418; P = 16, 128 queries 317 / 190, 10 000 11 251 / 4277; K = 262 144, P = 256, 2048 queries 1479 / 1577, 4096
+// 2857 / 2325; P = 64, 512 330 / 294, 4096 1968 / 1291; K = 65 536, P = 64, 2048 482 / 501, 4096 830 / 748; P = 256 10 000
+// 3106 / 3327; P = 16, 1024 177 / 192, 2048 344 / 298; K = 32 768, P = 16, 1024 137 / 182, 4096 454 / 424; P = 64, 4096 607 / 645;
+// D = 128, where the sweep has two wavefronts a SIMD, K = 65 536, P = 64, 4096 857 / 907, 10 000 1858 / 1546.
+bool sparse_pays(int64_t K, int D, int P, int64_t nq)
+{
+#ifdef IVF_PROBE_SPARSE
+    return IVF_PROBE_SPARSE;
+#endif
+    const int64_t pairs = (int64_t)P << (packed_dim(D) <= 96 ? 22 : 23);
+    return K >= 1024 * (int64_t)P && nq * K >= (pairs > (1ll << 27) ? pairs : 1ll << 27);
+}
+
+// Queries of a pass without the distance matrix; 0: with it.
+int64_t sparse_tile(const ivf_index *ix, int P, int64_t nq)
+{
+    if (!ix->chi || P > PS_P_MAX || (int64_t)P * ix->L > 16384) return 0;
+    int64_t n = nq < (1 << 20) ? nq : (1 << 20);
+    while (sparse_pays(ix->K, ix->D, P, n) && (int64_t)plan_sparse(ix->K, ix->D, P, ix->L, n).total > ix->scratch_limit) n = (n / 2 + 127) & ~127ll;
+    return sparse_pays(ix->K, ix->D, P, n) ? n : 0;
+}
+
 // The query path on the handle's own growable scratch (allocates when a call needs more than any before).
 int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, float prune_frac, int k,
                  int32_t *out_ids, float *out_dists, int32_t *probe_id_out, float *probe_d_out,
@@ -742,12 +964,17 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
     else if (tile >= 256) tile -= tile % 256;   // whole blocks of the padded row count
     else if (tile >= GT) tile -= tile % GT;
 
-    const SearchPlan pl = plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr);
+    const int64_t sparse_n = sparse_tile(ix, nprobe, nq);
+    const bool sparse = sparse_n > 0;
+    if (sparse) tile = sparse_n;
+    const SearchPlan pl = plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr, true, sparse);
     Buf *bufs[WS_COUNT] = {&ix->dt, &ix->bm, &ix->qn, &ix->qsi, &ix->qpk, &ix->probe_id, &ix->probe_d,
                            &ix->desc, &ix->lut, &ix->partial, &ix->qrot};
     for (int i = 0; i < WS_COUNT; ++i)
         if ((rc = ensure(*bufs[i], pl.bytes[i]))) return rc;
+    if (sparse && (rc = ensure(ix->sparse, plan_sparse(K, ix->D, nprobe, ix->L, tile).total))) return rc;
     SearchWs ws;
+    ws.sparse = static_cast<unsigned char *>(ix->sparse.p);
     ws.dt = static_cast<float *>(ix->dt.p);
     ws.bm = static_cast<float *>(ix->bm.p);
     ws.qn = static_cast<float *>(ix->qn.p);

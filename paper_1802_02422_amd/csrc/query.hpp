@@ -55,6 +55,7 @@ __device__ __forceinline__ void lut_body(const float *__restrict__ Qrow, int D, 
 // each 4 bytes, so that with 16 P L >= K the row is the smaller number of bytes, and whole lines in order (where that
 // pays: score_mode).  Dynamic LDS:
 // max(P*L, STREAM + 4) + 3 P words.
+// STREAM < 0: the keys of the scores are given (pair_distance_kernel), ldt = P*L of them a query in the place of Dt.
 // (the body of a scoring workgroup, for query q of the batch: also the second half of select_score_prune_kernel)
 template <int BLOCK, int MAXV, int STREAM = 0>
 __device__ __forceinline__ void score_prune_body(
@@ -69,7 +70,7 @@ __device__ __forceinline__ void score_prune_body(
     __shared__ unsigned long long codes_total;
     const int PL = P * L;
     uint32_t *keys = dyn;
-    const int front = STREAM && PL < STREAM + 4 ? STREAM + 4 : PL;
+    const int front = STREAM > 0 && PL < STREAM + 4 ? STREAM + 4 : PL;
     int32_t *pid = reinterpret_cast<int32_t *>(dyn + front);
     float *pd = reinterpret_cast<float *>(dyn + front + P);
     float *pa = reinterpret_cast<float *>(dyn + front + 2 * P);
@@ -82,7 +83,19 @@ __device__ __forceinline__ void score_prune_body(
     }
     if (threadIdx.x == 0) codes_total = 0;
     __syncthreads();
-    if constexpr (STREAM > 0) {
+    if constexpr (STREAM < 0) {
+        const uint32_t *given = reinterpret_cast<const uint32_t *>(row);
+        if ((PL & 3) == 0) {                             // (rows of PL words from a 16-byte boundary on)
+#pragma unroll
+            for (int v = 0; v < MAXV; ++v) {
+                const int i = threadIdx.x + v * BLOCK;
+                if (4 * i < PL) reinterpret_cast<uint4 *>(keys)[i] = reinterpret_cast<const uint4 *>(given)[i];
+            }
+        } else {
+#pragma unroll 4
+            for (int i = threadIdx.x; i < PL; i += BLOCK) keys[i] = given[i];
+        }
+    } else if constexpr (STREAM > 0) {
         constexpr int U = 4 * MAXV;                      // items of a thread: threadIdx.x + u * BLOCK
         uint32_t word[U];                                 // neighbour id, then the distance (found: bit u)
         uint32_t found = 0;

@@ -1,0 +1,634 @@
+// Stages 1 to 2 of the query path for large batches without the distance matrix.  Of the nq x K distances a search needs
+// some hundred blocks of 64 per query (the nprobe closest regions lie in them) and the L neighbours of its nprobe
+// regions: 2 % of them at K = 2^20.  Writing all of them, and reading 4 bytes from a 128-byte line each, took 14.3 of the
+// 16.3 ms of 10 000 queries there.  Here:
+//   1. coarse_minima_kernel: <q, c> - |c|^2 / 2 with operands rounded to fp16, a third of the matrix work, and only the largest
+//      value of every 64 centroids is written.  It is known within a bound (coarse_shortlist_sweep_kernel has the same).
+//   2. flag_blocks_kernel: the blocks of 64 that can hold one of the P closest, a few more than P.
+//   3. pair_distance_kernel<false>: the exact distances of the flagged blocks, grouped by block, so that the rows of a block are
+//      read once for the up to 32 queries a wavefront takes.
+//   4. probe_pick_kernel: the P closest regions among them.
+//   5. pair_distance_kernel<true>: the scores of Eq. (7), grouped by region: the neighbours' rows are read once for the
+//      queries that probe the region.
+// The distances are formed by the same products in the same order as in coarse_gemm_kernel, so a query's results do
+// not depend on which way its batch goes.  A query whose bound is too wide to leave at most 2 P blocks (vectors far from the
+// origin compared with their spread, rows that are not finite) gets exact block minima first (hard_* kernels, which end at
+// once when there is none).
+#pragma once
+#include "coarse.hpp"
+#include "query.hpp"
+
+namespace ivf {
+
+// The queries' fp16 rows have the centroid table's scale, four times smaller: room for components eight times the table's
+// largest; a query with a larger one is a hard one.
+constexpr int SPARSE_HEADROOM = 2;
+constexpr int64_t SPARSE_MIN_K = 8192;
+
+// |x| and |dx| of a row (see pack_hi_rows_kernel) with infinite lengths where a centroid of the tile is not finite: such a
+// block is always looked at.  start[c] = (-1/2 + k) |c|^2 in units of the product, -inf past K; tile[t] = (largest |c|,
+// largest |dc|, smallest start value, 0).
+__global__ __launch_bounds__(128) void minima_tiles_kernel(const float2 *__restrict__ clen, int64_t K, int Dp, float *__restrict__ start,
+                                                           float4 *__restrict__ tile)
+{
+    __shared__ float4 part[2];
+    const int64_t c = (int64_t)blockIdx.x * 128 + threadIdx.x;
+    float2 l = make_float2(0.f, 0.f);
+    float v = -INFINITY, low = 0.f;
+    if (c < K) {
+        l = clen[c];
+        if (l.x < INFINITY) {
+            const float len0 = l.x * (1.f / (1.f + 0x1p-10f));     // (the length was rounded up by 2^-10)
+            v = low = (-0.5f + (float)(Dp + 32) * 0x1p-24f) * __builtin_amdgcn_ldexpf(len0 * len0, -SPARSE_HEADROOM);
+        }
+    }
+    start[c] = v;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        l.x = fmaxf(l.x, __shfl_xor(l.x, o, WAVE));
+        l.y = fmaxf(l.y, __shfl_xor(l.y, o, WAVE));
+        low = fminf(low, __shfl_xor(low, o, WAVE));
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float4(l.x, l.y, low, 0.f);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        tile[blockIdx.x] = make_float4(fmaxf(part[0].x, part[1].x), fmaxf(part[0].y, part[1].y), fminf(part[0].z, part[1].z), 0.f);
+}
+
+// nbr_norm[r][l] = |s_l|^2: read as one piece where the neighbours' own norms would be a line each
+__global__ __launch_bounds__(256) void neighbour_norm_kernel(const int32_t *__restrict__ nbr, int64_t total, const float *__restrict__ cnorm,
+                                                             float *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < total) out[i] = cnorm[nbr[i]];
+}
+
+// The queries as fp16 rows in pack_hi_rows_kernel's layout, at the table's scale; a wavefront a row.  Rows past n (up to n_pad)
+// are zeros.  Workgroups from rows_grid on clear `words` 64-bit words of counters.
+__global__ __launch_bounds__(256) void sparse_queries_kernel(const float *__restrict__ X, int64_t n, int64_t n_pad, int D, int Dp,
+                                                             const uint32_t *__restrict__ cmax, _Float16 *__restrict__ H, float2 *__restrict__ len,
+                                                             unsigned rows_grid, unsigned long long *__restrict__ zero, int64_t words)
+{
+    if (blockIdx.x >= rows_grid) {
+        for (int64_t i = (int64_t)(blockIdx.x - rows_grid) * 256 + threadIdx.x; i < words; i += (int64_t)(gridDim.x - rows_grid) * 256) zero[i] = 0;
+        return;
+    }
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= n_pad) return;
+    const int sh = hi_scale(*cmax) - SPARSE_HEADROOM;
+    float s2 = 0.f, d2 = 0.f;
+    _Float16 hi[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = lane + u * WAVE;
+        const float f = row < n && i < D ? __builtin_amdgcn_ldexpf(X[row * D + i], sh) : 0.f;
+        hi[u] = (_Float16)f;
+        const float d = f - (float)hi[u];
+        s2 = fmaf(f, f, s2);
+        d2 = fmaf(d, d, d2);
+    }
+    s2 = wave_sum(s2);
+    d2 = wave_sum(d2);
+    const bool fits = s2 < INFINITY && d2 < INFINITY;              // (a component that fp16 cannot hold leaves an infinite rest)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = lane + u * WAVE, k8 = (i >> 3) & 3;
+        if (i < Dp) H[row * Dp + (i & ~31) + 8 * ((k8 & 1) * 2 + (k8 >> 1)) + (i & 7)] = fits ? hi[u] : (_Float16)0.f;
+    }
+    if (lane == 0)
+        len[row] = fits ? make_float2(sqrtf(s2 + 0x1p-100f) * (1.f + 0x1p-10f), sqrtf(d2 + 0x1p-100f) * (1.f + 0x1p-10f)) : make_float2(INFINITY, INFINITY);
+}
+
+// Row q of the block maxima: the even blocks of 64 (first halves of the tiles), then the odd ones, each padded to a
+// multiple of four.
+__host__ __device__ inline int64_t minima_half(int64_t K) { return ((K + GT - 1) / GT + 3) / 4 * 4; }
+
+// best[q][half][t] = the largest of <q, c> - (1/2 - k) |c|^2 over the 64 centroids of the half of tile t, for a sweep of
+// `tiles_per_wg` (a multiple of four) centroid tiles by a workgroup that keeps the fragments of ONE query tile in registers:
+// coarse_shortlist_sweep_kernel's loop without its bounds and reports.  A lane ends up with the maxima of one query, four tiles
+// in a row, and stores them as 16 bytes.  10 000 x 2^20, 96 dimensions: 2.2 ms (0.92
+// PFLOP/s), x 65 536 0.14; the distance GEMM takes 9.8 and 0.70.
+template <int SH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void coarse_minima_kernel(
+    const _Float16 *__restrict__ Qh, const _Float16 *__restrict__ Ch, const float *__restrict__ start, float *__restrict__ best, int64_t half_ld,
+    int tiles_q, int tiles_c, int tiles_per_wg)
+{
+    typedef const __attribute__((address_space(1))) void *gptr_t;
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    constexpr int Dpf = SH * DK;                           // floats per row of the hi-only tables
+    constexpr int SLOT = GT * ROWF;
+    __shared__ __attribute__((aligned(16))) float ring[2][SH * SLOT];
+    __shared__ __attribute__((aligned(16))) float cns[2][GT];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
+    int64_t tq, group;
+    if (!group_of_block(blockIdx.x, tiles_q, (tiles_c + tiles_per_wg - 1) / tiles_per_wg, tq, group)) return;
+    const int tb = (int)(group * tiles_per_wg);
+    int t_end = tb < tiles_c ? tiles_c - tb : 0;
+    if (t_end > tiles_per_wg) t_end = tiles_per_wg;
+    if (t_end <= 0) return;
+    const int64_t q0 = tq * GT;
+
+    const int rl = lane >> 2;
+    const int fl = (lane & 3) ^ ((lane >> 4) & 3);
+    const float *cbase = reinterpret_cast<const float *>(Ch) + (int64_t)rl * Dpf + fl * 4;
+    auto issue_tile = [&](int t) {
+        const int tc = t < t_end ? t : t_end - 1;            // past the range: the last tile again, never read
+        if (wave < 2)
+            __builtin_amdgcn_global_load_lds((gptr_t)(start + (int64_t)(tb + tc) * GT + wave * 64 + lane), (lptr_t)(&cns[t & 1][wave * 64]), 4, 0, 0);
+        const float *src = cbase + (int64_t)(tb + tc) * GT * Dpf;
+        float *dst = &ring[t & 1][0];
+#pragma nounroll
+        for (int n = wave; n < 8 * SH; n += 4)     // piece n: stage n / 8, rows 16 (n % 8) ..
+            __builtin_amdgcn_global_load_lds((gptr_t)(src + (n >> 3) * DK + (int64_t)(n & 7) * 16 * Dpf), (lptr_t)(dst + n * 256), 16, 0, 0);
+    };
+    issue_tile(0);
+    gu32x4 afr[SH][2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(Qh) + (q0 + wq + i * 32 + l32) * Dpf) + 2 * h;
+#pragma unroll
+        for (int s = 0; s < SH; ++s) {
+            afr[s][i][0] = row[s * 4 + 0];
+            afr[s][i][1] = row[s * 4 + 1];
+        }
+    }
+    float *out = best + (q0 + wq + lane) * (2 * half_ld) + (wave & 1) * half_ld + tb;
+    floatx4 four = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int t = 0; t < t_end; ++t) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wavefront's copies of tile t (issued a tile ago) are in
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // ... and everyone's; tile t - 1's buffer is free
+        issue_tile(t + 1);
+        float top[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            floatx16 acc[2];
+            union { floatx16 all; floatx4 part[4]; } init;
+            const int rb = wc + j * 32 + l32;
+            const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
+            const uint32_t rsw = 4u * (uint32_t)(rb * ROWF), k0 = 16u * (uint32_t)((2 * h) ^ ((rb >> 2) & 3)), k1 = 16u * (uint32_t)((2 * h + 1) ^ ((rb >> 2) & 3));
+#pragma unroll
+            for (int s = 0; s < SH; ++s) {
+                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][s * SLOT]) + rsw;
+                gu32x4 b[2];
+                if (s == 0)
+                    asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:32\n\tds_read_b128 %2, %6 offset:64\n\tds_read_b128 %3, %6 offset:96\n\t"
+                                 "ds_read_b128 %4, %7\n\tds_read_b128 %5, %8\n\ts_waitcnt lgkmcnt(0)"
+                                 : "=&v"(init.part[0]), "=&v"(init.part[1]), "=&v"(init.part[2]), "=&v"(init.part[3]), "=&v"(b[0]), "=&v"(b[1])
+                                 : "v"(cb), "v"(bs + k0), "v"(bs + k1));
+                else
+                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(bs + k0), "v"(bs + k1));
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, b[p]), __builtin_bit_cast(halfx8, afr[s][i][p]),
+                                                                        s == 0 && p == 0 ? init.all : acc[i], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                float m = acc[i][0];
+#pragma unroll
+                for (int v = 1; v < 16; ++v) m = __builtin_elementwise_maximum(m, acc[i][v]);
+                top[i] = j == 0 ? m : __builtin_elementwise_maximum(top[i], m);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the next half's products start with this half's registers free
+        }
+        // lane half 0 gets query block 0's maximum over both halves' centroids, lane half 1 block 1's
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(top[0]), __float_as_uint(top[1]), false, false);
+        four = floatx4{four[1], four[2], four[3], __builtin_elementwise_maximum(__uint_as_float(s[0]), __uint_as_float(s[1]))};
+        if ((t & 3) == 3) *reinterpret_cast<floatx4 *>(out + t - 3) = four;
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no copy into LDS may outlive the workgroup
+    if (t_end & 3) {
+        for (int t = t_end; t & 3; ++t) four = floatx4{four[1], four[2], four[3], -INFINITY};
+        *reinterpret_cast<floatx4 *>(out + (t_end & ~3)) = four;
+    }
+}
+
+// What the kernels after the sweep share.
+struct SparseArgs {
+    int64_t K, half_ld;
+    int nb, P, L, cap, shift, Dp;              // cap >= 2 P: blocks a query may list; a pair is query << shift | slot
+    const float4 *tile;
+    const float2 *qlen;
+    const float *qn, *qsi;                     // |q|^2, inverse scales
+    const uint32_t *cmax;
+    const _Float16 *Qp, *Cp;                   // hi/lo rows
+    const float *cnorm, *csi;
+    float *best;                               // [rows][2 half_ld] block maxima (of hard queries: smallest distances)
+    uint32_t *n_flag;                          // [nq]
+    int32_t *blist;                            // [nq][cap] flagged blocks, ascending
+    uint32_t *rank;                            // [nq][cap] place of a pair among those of its bucket
+    float *thr;                                // [nq] no distance of the P closest is larger
+    uint32_t *count;                           // [nb] blocks, then [K] regions: pairs of a bucket
+    uint32_t *offset;                          // [max(nb, K)] first pair of a bucket
+    uint32_t *total;                           // [0]: hard queries; [1], [2]: pairs, work items of the blocks; [3], [4]: of the regions
+    uint32_t *hard;                            // [nq] the hard queries
+    _Float16 *hard_rows;
+    float *hard_n, *hard_si;
+    uint32_t *pairs;
+    uint4 *items;                              // bucket, first pair, pairs
+    float *cand;                               // [nq][cap][64] distances of the flagged blocks
+    uint32_t *keys;                            // [nq][P L] scores
+    int32_t *probe_id;
+    float *probe_d;
+    const int32_t *nbr;
+    const float *nbr_norm, *cst, *alpha;
+};
+
+// Lists the blocks of query q that can hold one of its P closest centroids.  EXACT: best holds smallest distances (the
+// rule of probe_select_kernel).  Else a block is known by low, the lower end of its best value, and is listed if its upper end reaches
+// the P-th largest lower end; low and the upper end are widened by the rounding of the exact distances too, by whose
+// computed values everything that follows decides.  Dynamic LDS: 2 half_ld words.
+template <int BLOCK, bool EXACT>
+__device__ __forceinline__ void flag_blocks_body(const SparseArgs &a, int64_t q, uint32_t *keys, SelectShared &sh)
+{
+    const int tid = threadIdx.x;
+    const float *row = a.best + q * 2 * a.half_ld;
+    const float k = (float)(a.Dp + 32) * 0x1p-24f, back = 2.f * k / (0.5f - k);
+    const float2 ql = EXACT ? make_float2(0.f, 0.f) : a.qlen[q];
+    // half a distance's rounding error, 64 u (|q|^2 + |c|^2), in units of the product (four times the measured bound of the
+    // parity checks), and the low halves below fp16's range
+    const float up2 = 1.f * (1 << SPARSE_HEADROOM), down2 = 1.f / (1 << SPARSE_HEADROOM);
+    auto eps_of = [&](float4 tl) {
+        return shortlist_eps(ql, tl.x, tl.y, a.Dp) + 0x1p-18f * fmaf(up2 * ql.x, ql.x, down2 * tl.x * tl.x) + 0x1p-20f * ql.x;
+    };
+    for (int64_t i = tid; i < a.half_ld / 4; i += BLOCK) {
+        const float4 e = reinterpret_cast<const float4 *>(row)[i], o = reinterpret_cast<const float4 *>(row + a.half_ld)[i];
+        const float ev[4] = {e.x, e.y, e.z, e.w}, ov[4] = {o.x, o.y, o.z, o.w};
+        uint32_t w[8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t t = 4 * i + u;
+            float x = ev[u], y = ov[u];
+            if (!EXACT) {
+                const float4 tl = 2 * t < a.nb ? a.tile[t] : make_float4(0.f, 0.f, 0.f, 0.f);
+                const float eps = eps_of(tl);
+                x = eps < INFINITY ? eps - fmaf(back, tl.z, x) : INFINITY;   // the negative of the lower end
+                y = eps < INFINITY ? eps - fmaf(back, tl.z, y) : INFINITY;
+            }
+            w[2 * u] = 2 * t < a.nb ? float_key(x) : 0xFFFFFFFFu;
+            w[2 * u + 1] = 2 * t + 1 < a.nb ? float_key(y) : 0xFFFFFFFFu;
+        }
+        reinterpret_cast<uint4 *>(keys)[2 * i] = make_uint4(w[0], w[1], w[2], w[3]);
+        reinterpret_cast<uint4 *>(keys)[2 * i + 1] = make_uint4(w[4], w[5], w[6], w[7]);
+    }
+    __syncthreads();
+    const uint32_t nsel = a.P < a.nb ? (uint32_t)a.P : (uint32_t)a.nb;
+    uint32_t pivot, need;
+    block_radix_select<BLOCK>([keys](int64_t b) { return keys[b]; }, a.nb, nsel, sh, pivot, need);
+    int32_t *list = a.blist + q * a.cap;
+    uint32_t *rank = a.rank + q * a.cap;
+    auto put = [&](uint32_t pos, int b) {
+        list[pos] = b;
+        rank[pos] = atomicAdd(&a.count[b], 1u);
+    };
+    uint32_t total;
+    if (EXACT) {
+        total = block_emit_selected_runs<BLOCK, 4>(keys, a.nb, pivot, (uint32_t)a.P, sh, [&](uint32_t pos, int64_t b, uint32_t) { put(pos, (int)b); });
+        if (tid == 0) {
+            a.n_flag[q] = total;
+            a.thr[q] = a.nb < a.P ? INFINITY : key_float(pivot);
+        }
+        return;
+    }
+    const float limit = a.nb < a.P ? INFINITY : key_float(pivot);            // the negative of the P-th largest lower end
+    const int ipt = ((a.nb + BLOCK - 1) / BLOCK + 3) & ~3, i0 = tid * ipt;     // at most 16 blocks a thread
+    uint32_t flags = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (4 * v < ipt && i0 + 4 * v < a.nb) {
+            const uint4 w = *reinterpret_cast<const uint4 *>(&keys[i0 + 4 * v]);
+            const uint32_t kv[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int b = i0 + 4 * v + u;
+                if (b >= a.nb) break;
+                const float4 tl = a.tile[b >> 1];
+                const float neg = key_float(kv[u]);
+                // upper end = lower end + 2 eps - back z;  the rounding of these few operations is far inside the margins above
+                if (!(neg - (2.f * eps_of(tl) - back * tl.z) > limit) || !(neg < INFINITY)) flags |= 1u << (4 * v + u);
+            }
+        }
+    const uint32_t exc = block_exclusive_scan<BLOCK>((uint32_t)__popc(flags), sh.scan, total);
+    if (total > (uint32_t)a.cap || !(ql.x < INFINITY)) {                       // uniform
+        if (tid == 0) {
+            a.n_flag[q] = 0;
+            a.hard[atomicAdd(&a.total[0], 1u)] = (uint32_t)q;
+        }
+        return;
+    }
+    uint32_t at = exc;
+    while (flags) {
+        put(at++, i0 + __builtin_ctz(flags));
+        flags &= flags - 1;
+    }
+    if (tid == 0) {
+        a.n_flag[q] = total;
+        const int shc = hi_scale(*a.cmax);
+        // d = |q|^2 - 2 G, and the lower end is one of G in the units of the product
+        const float two_g = __builtin_amdgcn_ldexpf(limit, 1 + SPARSE_HEADROOM - 2 * shc), n = a.qn[q];
+        const float d = n + two_g + 0x1p-21f * (n + fabsf(two_g));
+        a.thr[q] = limit < INFINITY ? fmaxf(d, 0.f) : INFINITY;
+    }
+}
+
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void flag_blocks_kernel(SparseArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    __shared__ SelectShared sh;
+    flag_blocks_body<BLOCK, false>(a, blockIdx.x, dyn, sh);
+}
+
+// ---- hard queries: block minima of their exact distances.  Loops over what there is, nearly always nothing ----
+__global__ __launch_bounds__(256) void hard_rows_kernel(SparseArgs a)
+{
+    const uint32_t n = a.total[0];
+    const int chunks = a.Dp / 4;                                            // 16-byte pieces of a row
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (int64_t)n * chunks; i += (int64_t)gridDim.x * 256) {
+        const int64_t r = i / chunks, c = i - r * chunks, q = a.hard[r];
+        reinterpret_cast<gu32x4 *>(a.hard_rows)[i] = reinterpret_cast<const gu32x4 *>(a.Qp)[q * chunks + c];
+        if (c == 0) {
+            a.hard_n[r] = a.qn[q];
+            a.hard_si[r] = a.qsi[q];
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void hard_minima_kernel(SparseArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float ops0[DBUF];
+    __shared__ __attribute__((aligned(16))) float ops1[DBUF];
+    __shared__ __attribute__((aligned(16))) float cns[GT];
+    const int64_t n = a.total[0], tiles_h = (n + GT - 1) / GT, tiles_c = (a.K + GT - 1) / GT;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64, l32 = lane & 31, h = lane >> 5;
+    for (int64_t item = blockIdx.x; item < tiles_h * tiles_c; item += gridDim.x) {
+        const int64_t q0 = item % tiles_h * GT, t = item / tiles_h, c0 = t * GT;
+        __syncthreads();                                                   // everyone has read the norms of the last tile
+        if (threadIdx.x < GT) cns[threadIdx.x] = c0 + threadIdx.x < a.K ? a.cnorm[c0 + threadIdx.x] : 0.f;
+        floatx16 acc[2][2];
+        gemm_tile(a.hard_rows, n, q0, a.Cp, a.K, c0, a.Dp, ops0, ops1, acc);
+        const float m2c = -2.f * a.csi[0];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int64_t r = q0 + wq + i * 32 + l32;
+            const float qr = r < n ? a.hard_n[r] : 0.f, m2 = r < n ? m2c * a.hard_si[r] : 0.f;
+            float m = INFINITY;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int cl = wc + j * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+                    if (c0 + cl < a.K) m = fminf(m, fmaxf(fmaf(m2, acc[i][j][v], qr + cns[cl]), 0.f));
+                }
+            m = fminf(m, __shfl_xor(m, 32, WAVE));
+            if (h == 0 && r < n) a.best[a.hard[r] * 2 * a.half_ld + (wave & 1) * a.half_ld + t] = m;
+        }
+    }
+}
+
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void hard_flag_kernel(SparseArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    __shared__ SelectShared sh;
+    const uint32_t n = a.total[0];
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        __syncthreads();
+        flag_blocks_body<BLOCK, true>(a, a.hard[i], dyn, sh);
+    }
+}
+
+// ---- pairs in the order of their buckets (blocks or regions) ----
+constexpr int PAIR_Q = 32;   // queries of a work item
+
+// First pair of every bucket and the work items.  The order of the buckets among each other does not matter: a workgroup
+// adds up its 1024 and takes room for them with one atomic.
+__global__ __launch_bounds__(1024) void bucket_items_kernel(const uint32_t *__restrict__ count, int64_t n, uint32_t *__restrict__ total,
+                                                            uint32_t *__restrict__ offset, uint4 *__restrict__ items)
+{
+    __shared__ uint32_t scan[16], base[2];
+    const int64_t b = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    const uint32_t c = b < n ? count[b] : 0u, m = (c + PAIR_Q - 1) / PAIR_Q;
+    uint32_t pairs, work;
+    const uint32_t at = block_exclusive_scan<1024>(c, scan, pairs), it = block_exclusive_scan<1024>(m, scan, work);
+    if (threadIdx.x == 0) {
+        base[0] = pairs ? atomicAdd(&total[0], pairs) : 0u;
+        base[1] = work ? atomicAdd(&total[1], work) : 0u;
+    }
+    __syncthreads();
+    if (b >= n) return;
+    offset[b] = base[0] + at;
+    for (uint32_t u = 0; u < m; ++u) {
+        const uint32_t left = c - u * PAIR_Q;
+        items[base[1] + it + u] = make_uint4((uint32_t)b, base[0] + at + u * PAIR_Q, left < PAIR_Q ? left : PAIR_Q, 0u);
+    }
+}
+
+// slot s of query q (n_flag[q] of them, or P where there is none) to its place
+__global__ __launch_bounds__(256) void place_pairs_kernel(const int32_t *__restrict__ bucket, const uint32_t *__restrict__ rank, int64_t nq, int width,
+                                                          int rank_ld, int shift, const uint32_t *__restrict__ n_flag,
+                                                          const uint32_t *__restrict__ offset, uint32_t *__restrict__ pairs)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= nq * width) return;
+    const int64_t q = i / width;
+    const int s = (int)(i - q * width);
+    if (n_flag && (uint32_t)s >= n_flag[q]) return;
+    pairs[offset[bucket[i]] + rank[q * rank_ld + s]] = (uint32_t)q << shift | (uint32_t)s;
+}
+
+// A work item a wavefront: the exact distances of up to 32 queries to 64 rows of the table at a time, copied to LDS directly
+// (a whole item's rows are on their way at once; six such workgroups a compute unit).  REGION: the rows are the neighbours of
+// region `bucket` and the result is the score of Eq. (7) as an ordered key; else they are the 64 centroids of a block.
+// Products and their order are those of gemm_tile.
+template <int STAGES, bool REGION>
+__global__ __launch_bounds__(64) void pair_distance_kernel(SparseArgs a, const uint32_t *__restrict__ n_items)
+{
+    typedef const __attribute__((address_space(1))) void *gptr_t;
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    constexpr int Dp = STAGES * DK;                                        // floats per row
+    constexpr int OLD = BMW + 4;                                           // row stride of the results in LDS
+    constexpr int ROWS = STAGES * BMW * ROWF > PAIR_Q * OLD ? STAGES * BMW * ROWF : PAIR_Q * OLD;
+    __shared__ __attribute__((aligned(16))) float rows[ROWS];
+    __shared__ __attribute__((aligned(16))) float cn[BMW];
+    __shared__ __attribute__((aligned(16))) float cs[REGION ? BMW : 4];
+    if (blockIdx.x >= *n_items) return;
+    const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5;
+    const uint4 item = a.items[blockIdx.x];
+    const int n = (int)item.z, mask = (1 << a.shift) - 1;
+    const int64_t bucket = item.x;
+    const uint32_t pair = a.pairs[item.y + (l32 < n ? l32 : 0)];           // (columns past n: the first query again)
+    const int64_t q = pair >> a.shift;
+    const int width = REGION ? a.L : BMW;
+    for (int l0 = 0; l0 < width; l0 += BMW) {
+        const int nl = width - l0 < BMW ? width - l0 : BMW;
+        int32_t my;
+        if (REGION) my = a.nbr[bucket * a.L + l0 + (lane < nl ? lane : 0)];
+        else my = (int32_t)(bucket * BMW) + lane;                          // (the packed table has whole tiles of rows)
+        const float *src[4];
+        const int f = (lane & 3) ^ ((lane >> 4) & 3);                      // chunk this slot holds
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            src[g] = reinterpret_cast<const float *>(a.Cp) + (int64_t)__shfl(my, 16 * g + (lane >> 2), WAVE) * Dp + f * 4;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (16 * g < nl) {
+#pragma unroll
+                for (int s = 0; s < STAGES; ++s)
+                    __builtin_amdgcn_global_load_lds((gptr_t)(src[g] + s * DK), (lptr_t)(rows + s * (BMW * ROWF) + g * 256), 16, 0, 0);
+            }
+        gu32x4 qf[STAGES][2];
+        const gu32x4 *qrow = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(a.Qp) + q * Dp) + 2 * h;
+#pragma unroll
+        for (int s = 0; s < STAGES; ++s) {
+            qf[s][0] = qrow[s * 4 + 0];
+            qf[s][1] = qrow[s * 4 + 1];
+        }
+        const float qr = a.qn[q], m2 = -2.f * a.csi[0] * a.qsi[q];
+        float al = 0.f;
+        if (REGION) {
+            al = a.alpha[bucket];
+            cn[lane] = lane < nl ? a.nbr_norm[bucket * a.L + l0 + lane] : 0.f;
+            cs[REGION ? lane : 0] = lane < nl ? a.cst[bucket * a.L + l0 + lane] : 0.f;
+        } else {
+            cn[lane] = bucket * BMW + lane < a.K ? a.cnorm[bucket * BMW + lane] : 0.f;
+        }
+        const float pd = REGION ? a.probe_d[q * a.P + (pair & (uint32_t)mask)] : 0.f;
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        wave_sync();
+        floatx16 acc[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        const bool both = nl > 32;                                         // (uniform)
+#pragma unroll
+        for (int s = 0; s < STAGES; ++s) {
+            gu32x4 b[2][2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int r = j * 32 + l32;
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+                    b[j][p] = *reinterpret_cast<const gu32x4 *>(&rows[s * (BMW * ROWF) + r * ROWF + (((2 * h + p) ^ ((r >> 2) & 3)) << 2)]);
+            }
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                acc[0] = mfma3(b[0], qf[s], acc[0], e);
+                if (both) acc[1] = mfma3(b[1], qf[s], acc[1], e);
+            }
+        }
+        wave_sync();                                                       // the rows have been read: their place takes the results
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int cl = j * 32 + 8 * g + 4 * h;
+                const float4 cv = *reinterpret_cast<const float4 *>(&cn[cl]);
+                const float ce[4] = {cv.x, cv.y, cv.z, cv.w};
+                float4 sv = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (REGION) sv = *reinterpret_cast<const float4 *>(&cs[REGION ? cl : 0]);
+                const float se[4] = {sv.x, sv.y, sv.z, sv.w};
+                float r[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float d = fmaxf(fmaf(m2, acc[j][4 * g + u], qr + ce[u]), 0.f);
+                    r[u] = REGION ? __uint_as_float(float_key(fmaf(al, d, fmaf(1.f - al, pd, se[u])))) : d;
+                }
+                *reinterpret_cast<float4 *>(&rows[l32 * OLD + cl]) = make_float4(r[0], r[1], r[2], r[3]);
+            }
+        wave_sync();
+        for (int i = 0; i < n; ++i) {
+            const uint32_t pr = (uint32_t)__builtin_amdgcn_readlane((int)pair, i);
+            const int64_t qi = pr >> a.shift, s = pr & (uint32_t)mask;
+            const float v = rows[i * OLD + lane];
+            if (REGION) {
+                if (lane < nl) a.keys[(qi * a.P + s) * a.L + l0 + lane] = __float_as_uint(v);
+            } else {
+                a.cand[(qi * a.cap + s) * BMW + lane] = v;
+            }
+        }
+        wave_sync();
+    }
+}
+
+// The P closest of the distances of a query's flagged blocks by (distance, id), ascending in id: the second half of
+// probe_select_lds_body.  Dynamic LDS: cap + 2 PICK_CAP words.
+constexpr int PICK_CAP = 2048;
+
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void probe_pick_kernel(SparseArgs a)
+{
+    __shared__ SelectShared sh;
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    int32_t *blist = reinterpret_cast<int32_t *>(dyn);
+    uint32_t *sk = dyn + a.cap;
+    int32_t *si = reinterpret_cast<int32_t *>(dyn + a.cap + PICK_CAP);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, P = a.P;
+    const int64_t q = blockIdx.x;
+    const int n = (int)a.n_flag[q];
+    const float *cand = a.cand + q * a.cap * BMW;
+    for (int i = tid; i < n; i += BLOCK) blist[i] = a.blist[q * a.cap + i];
+    const uint32_t tf = float_key(a.thr[q]);
+    __syncthreads();
+    auto put = [&](uint32_t pos, int32_t id, uint32_t key) {
+        a.probe_id[q * P + pos] = id;
+        a.probe_d[q * P + pos] = key_float(key);
+        a.rank[q * a.cap + pos] = atomicAdd(&a.count[a.nb + id], 1u);
+    };
+    constexpr int CB = 16;
+    uint32_t total = 0;
+    bool overflow = false;
+    for (int b0 = 0; b0 < n; b0 += CB * (BLOCK / WAVE)) {                  // uniform
+        uint32_t kv[CB];
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const int bi = b0 + wave * CB + j;
+            uint32_t k = 0xFFFFFFFFu;
+            if (bi < n && (int64_t)blist[bi] * BMW + lane < a.K) k = float_key(cand[bi * BMW + lane]);
+            kv[j] = k;
+        }
+        uint32_t wcnt = 0;
+#pragma unroll
+        for (int j = 0; j < CB; ++j) wcnt += (uint32_t)__popcll(__ballot(kv[j] <= tf && kv[j] != 0xFFFFFFFFu));
+        uint32_t round_total;
+        const uint32_t exc = block_exclusive_scan<BLOCK>(lane == 0 ? wcnt : 0u, sh.scan, round_total);
+        if (total + round_total > (uint32_t)PICK_CAP) { overflow = true; break; }   // uniform
+        uint32_t at = total + (uint32_t)__builtin_amdgcn_readfirstlane((int)exc);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const bool sel = kv[j] <= tf && kv[j] != 0xFFFFFFFFu;
+            const uint64_t m = __ballot(sel);
+            if (sel) {
+                const uint32_t o = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                sk[o] = kv[j];
+                si[o] = blist[b0 + wave * CB + j] * BMW + lane;
+            }
+            at += (uint32_t)__popcll(m);
+        }
+        total += round_total;
+    }
+    uint32_t pivot, need;
+    if (overflow || total < (uint32_t)P) {                                  // uniform; the second cannot happen
+        const int64_t nc = (int64_t)n * BMW;
+        __syncthreads();
+        auto key = [&](int64_t v) { return (int64_t)blist[v >> 6] * BMW + (v & 63) < a.K ? float_key(cand[v]) : 0xFFFFFFFFu; };
+        block_radix_select<BLOCK>(key, nc, (uint32_t)P, sh, pivot, need);
+        block_emit_selected<BLOCK>(key, nc, (uint32_t)P, pivot, need, sh,
+                                   [&](uint32_t pos, int64_t v, uint32_t k) { put(pos, blist[v >> 6] * BMW + (int)(v & 63), k); });
+        return;
+    }
+    __syncthreads();
+    block_radix_select<BLOCK>([sk](int64_t i) { return sk[i]; }, (int64_t)total, (uint32_t)P, sh, pivot, need);
+    static_assert(PICK_CAP <= 16 * BLOCK, "items per thread of the ordered emit");
+    block_emit_selected_runs<BLOCK, (PICK_CAP + 4 * BLOCK - 1) / (4 * BLOCK)>(sk, (int)total, pivot, need, sh, [&](uint32_t pos, int64_t i, uint32_t k) { put(pos, si[i], k); });
+}
+
+}  // namespace ivf

@@ -1,0 +1,57 @@
+"""Large batches go without the distance matrix: the same bits as the same queries in batches that go with it."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def make(K, D, L, M, seed, spread, offset):
+    import torch
+    import paper_1802_02422_amd as ivf
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    cent = torch.randn(K, D, generator=g, device="cuda") * spread + offset
+    nbr = torch.randint(0, K, (K, L), generator=g, device="cuda", dtype=torch.int32)
+    cs = torch.stack([((cent - cent[nbr[:, l].long()]) ** 2).sum(1) for l in range(L)], 1).contiguous()
+    alpha = torch.rand(K, generator=g, device="cuda") * 0.3
+    cb = torch.randn(M, 256, D // M, generator=g, device="cuda") * 0.1 * spread
+    n = 2 * K * L
+    off = torch.sort(torch.randint(0, n + 1, (K * L + 1,), generator=g, device="cuda"))[0].int()
+    off[0], off[-1] = 0, n
+    desc = ivf.IndexDesc(cent, nbr, alpha, cs, cb, const_table=torch.sort(torch.randn(256, generator=g, device="cuda"))[0].contiguous(),
+                         sub_offsets=off, codes=torch.randint(0, 256, (n, M), generator=g, device="cuda", dtype=torch.uint8),
+                         const_byte=torch.randint(0, 256, (n,), generator=g, device="cuda", dtype=torch.uint8),
+                         ids=torch.randperm(n, generator=g, device="cuda").int())
+    return ivf.ivf_load_index(desc), cent, g
+
+
+# partial last tiles and blocks, every packed width, L below, at and above a group of 64 neighbours and of odd length; "hard": bounds
+# too wide for every query; "some": queries too large for the table's scale, without a finite length, zero, and equal to centroids
+@pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
+    (16_400, 96, 64, 16, 16, 9000, "plain"), (16_385, 32, 7, 8, 13, 8500, "plain"), (20_033, 64, 65, 16, 16, 7001, "plain"),
+    (17_000, 128, 33, 16, 8, 9000, "plain"), (70_001, 48, 64, 8, 60, 4200, "plain"), (16_400, 96, 32, 16, 16, 8300, "hard"),
+    (16_640, 96, 16, 16, 16, 8300, "some"), (16_400, 96, 16, 16, 16, 8300, "equal")])
+def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
+    import torch
+    import paper_1802_02422_amd as ivf
+    h, cent, g = make(K, D, L, M, K + D, 0.01 if kind == "hard" else 1.0, 50.0 if kind == "hard" else 0.0)
+    q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")]
+    q = (q + 0.5 * (cent.std() if kind == "hard" else 1.0) * torch.randn(nq, D, generator=g, device="cuda")).contiguous()
+    if kind == "some":
+        q[::7] *= 1e5
+        q[3::11] = 0.0
+        q[5::13] = cent[:q[5::13].shape[0]]
+        q[1, 0], q[2, 3], q[400, 5] = float("nan"), float("inf"), -float("inf")
+    if kind == "equal":                                       # every query the same: one block and one region have all pairs
+        q[:] = q[0]
+    ivf.ivf_set_scratch_limit(h, 16 << 30)
+    whole = ivf.ivf_search_stages(h, q, P, 0.3, 20)
+    parts = [ivf.ivf_search_stages(h, q[a:a + 500].contiguous(), P, 0.3, 20) for a in range(0, nq, 500)]
+    for name in whole:
+        got, ref = whole[name].cpu().numpy(), torch.cat([p[name] for p in parts]).cpu().numpy()
+        assert np.array_equal(got.view(np.uint8), ref.view(np.uint8)), name
+    # a scratch limit that cuts the batch in passes
+    ivf.ivf_set_scratch_limit(h, 1 << 30)
+    again = ivf.ivf_search_stages(h, q, P, 0.3, 20)
+    for name in whole:
+        assert torch.equal(again[name].view(torch.uint8), whole[name].view(torch.uint8)), name
+    ivf.ivf_free_index(h)
