@@ -1364,55 +1364,44 @@ __global__ __launch_bounds__(BLOCK) void probe_select_kernel(const float *__rest
                                });
 }
 
-// The same selection with the keys held in LDS, for nb <= PS_NB_MAX block minima and
+// The same selection with the keys held in registers, for nb <= PS_NB_MAX block minima and
 // P <= PS_P_MAX: the block minima are read once (not once per radix pass), and of the flagged
 // blocks' elements only those at or below the block threshold t are kept (t is the P-th
 // smallest block minimum, so the P closest centroids are among them; with randomly numbered
 // centroids little more than P survive), compacted in ascending centroid id, and selected
 // from LDS.  A query with more than PS_CAP survivors (duplicated centroids) takes the
-// global-memory path of probe_select_kernel.  Dynamic LDS: 2P + 3 + max(nb, 2 PS_CAP) words.
+// global-memory path of probe_select_kernel.  Dynamic LDS: ps_lds_bytes(P).
 constexpr int PS_NB_MAX = 16384, PS_P_MAX = 256, PS_CAP = 4096;
+inline size_t ps_lds_bytes(int P) { return ((size_t)2 * P + 3 + 2 * PS_CAP) * sizeof(int); }
 
 // (the body, for query q of the batch: also the first half of select_score_prune_kernel)
 __device__ __forceinline__ void probe_select_lds_body(const float *__restrict__ Dt, int64_t ldt,
                                                       const float *__restrict__ bm, int64_t K, int nb, int P,
                                                       int32_t *__restrict__ probe_id, float *__restrict__ probe_d,
-                                                      int64_t q, int *ps_dyn)
+                                                      int64_t q, int *ps_dyn, SelectRegs<1024> &sh)
 {
     constexpr int BLOCK = 1024;
-    __shared__ SelectShared sh;
+    SelectShared &sh_mem = *reinterpret_cast<SelectShared *>(&sh);  // (only where more survive than fit)
+    static_assert(sizeof(SelectShared) <= sizeof(sh), "the same place");
     __shared__ uint32_t nflag_s;
     int *blist = ps_dyn;                                           // 2P flagged blocks
-    uint32_t *keys = reinterpret_cast<uint32_t *>(ps_dyn + ((2 * P + 3) & ~3));   // (16-byte aligned) nb block-minimum keys, then the survivors
+    uint32_t *keys = reinterpret_cast<uint32_t *>(ps_dyn + ((2 * P + 3) & ~3));   // (16-byte aligned) the survivors
     const int tid = threadIdx.x;
     const float *row = Dt + q * ldt;
-    const float *bmr = bm + q * nb;
-    if ((nb & 3) == 0) {   // rows of bm are then 16-byte aligned: four loads in flight per thread, 128 bits each
-        const float4 *src = reinterpret_cast<const float4 *>(bmr);
-        for (int i0 = tid; i0 < nb / 4; i0 += 4 * BLOCK) {
-            float4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + u * BLOCK < nb / 4) v[u] = src[i0 + u * BLOCK];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + u * BLOCK < nb / 4)
-                    *reinterpret_cast<uint4 *>(&keys[4 * (i0 + u * BLOCK)]) =
-                        make_uint4(float_key(v[u].x), float_key(v[u].y), float_key(v[u].z), float_key(v[u].w));
-        }
-    } else {
-        for (int i = tid; i < nb; i += BLOCK) keys[i] = float_key(bmr[i]);
+    const uint32_t *bmr = reinterpret_cast<const uint32_t *>(bm + q * nb);
+    static_assert(PS_NB_MAX <= 16 * BLOCK && PS_CAP <= 4 * BLOCK, "items of a thread");
+    uint32_t t, needb, nflag;
+    {
+        uint32_t kv[16];
+        auto as_key = [](uint32_t w) { return float_key(__uint_as_float(w)); };
+        if ((nb & 3) == 0) load_run<BLOCK>(bmr, nb, kv, as_key);
+        else load_run<BLOCK, false>(bmr, nb, kv, as_key);
+        block_select_runs<BLOCK>(kv, run_length<BLOCK>(nb), P < nb ? (uint32_t)P : (uint32_t)nb, sh, t, needb);
+        nflag = block_emit_runs<BLOCK>(kv, run_length<BLOCK>(nb), t, (uint32_t)P, sh.scan,
+                                       [&](uint32_t pos, int b, uint32_t) { blist[pos] = b; });
     }
-    __syncthreads();
-    auto keyb = [keys](int64_t b) { return keys[b]; };
-    const uint32_t nselb = P < nb ? (uint32_t)P : (uint32_t)nb;
-    uint32_t t, needb;
-    block_radix_select<BLOCK>(keyb, nb, nselb, sh, t, needb);
-    static_assert(PS_NB_MAX <= 16 * BLOCK && PS_CAP <= 4 * BLOCK, "items per thread of the two ordered emits below");
-    uint32_t nflag = block_emit_selected_runs<BLOCK, 4>(keys, nb, t, (uint32_t)P, sh,
-                                                     [&](uint32_t pos, int64_t b, uint32_t) { blist[pos] = (int)b; });
     if (tid == 0) nflag_s = nflag;
-    __syncthreads();                                               // blist complete, the block keys are dead
+    __syncthreads();                                               // blist complete
     nflag = nflag_s;
     const uint32_t tf = nb >= P ? t : 0xFFFFFFFFu;                 // fewer blocks than P: no filter
     // Candidates: the 64 distances of every flagged block, a block per wavefront and step (one
@@ -1429,13 +1418,11 @@ __device__ __forceinline__ void probe_select_lds_body(const float *__restrict__ 
         uint32_t kv[CB];
 #pragma unroll
         for (int j = 0; j < CB; ++j) {
+            // (every lane loads, or each load would be waited for inside its branch)
             const int bi = b0 + wave * CB + j;
-            uint32_t k = 0xFFFFFFFFu;
-            if (bi < (int)nflag) {
-                const int64_t c = (int64_t)blist[bi] * BMW + lane;
-                if (c < K) k = float_key(row[c]);
-            }
-            kv[j] = k;
+            const int64_t c = (int64_t)blist[bi < (int)nflag ? bi : 0] * BMW + lane;
+            const uint32_t key = float_key(row[c < K ? c : K - 1]);
+            kv[j] = bi < (int)nflag && c < K ? key : 0xFFFFFFFFu;
         }
         uint32_t wcnt = 0;
 #pragma unroll
@@ -1465,8 +1452,8 @@ __device__ __forceinline__ void probe_select_lds_body(const float *__restrict__ 
             return c < K ? float_key(row[c]) : 0xFFFFFFFFu;
         };
         uint32_t pivot, need;
-        block_radix_select<BLOCK>(key, (int64_t)n_c, (uint32_t)P, sh, pivot, need);
-        block_emit_selected<BLOCK>(key, (int64_t)n_c, (uint32_t)P, pivot, need, sh,
+        block_radix_select<BLOCK>(key, (int64_t)n_c, (uint32_t)P, sh_mem, pivot, need);
+        block_emit_selected<BLOCK>(key, (int64_t)n_c, (uint32_t)P, pivot, need, sh_mem,
                                    [&](uint32_t pos, int64_t v, uint32_t k) {
                                        probe_id[q * P + pos] = blist[v >> 6] * BMW + (int)(v & 63);
                                        probe_d[q * P + pos] = key_float(k);
@@ -1474,14 +1461,13 @@ __device__ __forceinline__ void probe_select_lds_body(const float *__restrict__ 
         return;
     }
     __syncthreads();
-    auto skey = [sk](int64_t i) { return sk[i]; };
-    uint32_t pivot, need;
-    block_radix_select<BLOCK>(skey, (int64_t)total, (uint32_t)P, sh, pivot, need);
-    block_emit_selected_runs<BLOCK, 1>(sk, (int)total, pivot, need, sh,
-                                    [&](uint32_t pos, int64_t i, uint32_t k) {
-                                        probe_id[q * P + pos] = si[i];
-                                        probe_d[q * P + pos] = key_float(k);
-                                    });
+    uint32_t kv[4], pivot, need;
+    load_run<BLOCK>(sk, (int)total, kv, [](uint32_t w) { return w; });
+    block_select_runs<BLOCK>(kv, 4, (uint32_t)P, sh, pivot, need);
+    block_emit_runs<BLOCK>(kv, run_length<BLOCK>((int)total), pivot, need, sh.scan, [&](uint32_t pos, int i, uint32_t k) {
+        probe_id[q * P + pos] = si[i];
+        probe_d[q * P + pos] = key_float(k);
+    });
 }
 
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void probe_select_lds_kernel(const float *__restrict__ Dt, int64_t ldt,
@@ -1491,7 +1477,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                                                                 float *__restrict__ probe_d)
 {
     extern __shared__ __attribute__((aligned(16))) int ps_dyn[];
-    probe_select_lds_body(Dt, ldt, bm, K, nb, P, probe_id, probe_d, blockIdx.x, ps_dyn);
+    __shared__ SelectRegs<1024> sh;
+    probe_select_lds_body(Dt, ldt, bm, K, nb, P, probe_id, probe_d, blockIdx.x, ps_dyn, sh);
 }
 
 // ---- The selection by one wavefront per query, for small tables ----
@@ -1524,7 +1511,7 @@ __device__ __forceinline__ void wave_select(const uint32_t (&k)[R], uint32_t nse
     for (int bit = top; bit >= 0; --bit) {
         const uint32_t trial = t | 1u << bit;
         // counted per lane and added over the lanes: a population count per register goes through the scalar unit, whose
-        // waits a lone wavefront has nothing to cover with (333 queries x 2000: 29 us, 26 so)
+        // waits a lone wavefront has nothing to cover with (333 queries x 2000: 29 us, 26 so, 15 with all loads ahead of their use)
         uint32_t mine = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) mine += k[r] < trial ? 1u : 0u;
@@ -1564,7 +1551,7 @@ constexpr int PW_CAP = 512;         // survivors held in LDS; where there are mo
 // Four queries a workgroup.  Same three steps and the same result as probe_select_kernel.  KMAX > 0: the whole row, of
 // at most KMAX distances, goes into registers (and LDS, from where a short loop writes the selected ones out).  A small
 // batch waits for one wavefront's chain of steps, which grows with the registers it holds: 100 queries x 1024 19 us with
-// KMAX = 2048, 13 with 1024.
+// KMAX = 2048, 13 with 1024 (9 with all loads ahead of their use).
 template <int KMAX>
 __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__restrict__ Dt, int64_t ldt, const float *__restrict__ bm,
                                                                 int64_t K, int nb, int P, int64_t nq, int32_t *__restrict__ probe_id,
@@ -1586,7 +1573,11 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
     const int n = DIRECT ? (int)K : nb;
     const float *src = DIRECT ? row : bm + q * nb;
 #pragma unroll
-    for (int r = 0; r < R; ++r) k[r] = r * WAVE + lane < n ? float_key(src[r * WAVE + lane]) : 0xFFFFFFFFu;
+    for (int r = 0; r < R; ++r) {
+        const int i = r * WAVE + lane;
+        const uint32_t key = float_key(src[i < n ? i : n - 1]);   // (every lane loads: all are on their way together)
+        k[r] = i < n ? key : 0xFFFFFFFFu;
+    }
     if (DIRECT) {
         uint32_t *held = row_all[DIRECT ? wave : 0];
 #pragma unroll
@@ -1632,8 +1623,9 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
     auto fetch = [&](uint32_t f0, uint32_t (&kv)[16]) {        // the lane's column of 16 flagged blocks
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int64_t c = f0 + j < nflag ? (int64_t)blist[f0 + j] * BMW + lane : K;
-            kv[j] = c < K ? float_key(row[c]) : 0xFFFFFFFFu;
+            const int64_t c = (int64_t)blist[f0 + j < nflag ? f0 + j : 0] * BMW + lane;
+            const uint32_t key = float_key(row[c < K ? c : K - 1]);   // (every lane loads: all 16 are on their way together)
+            kv[j] = f0 + j < nflag && c < K ? key : 0xFFFFFFFFu;
         }
     };
     // the survivors, in order, up to PW_CAP of them; AGAIN: of those equal to lim only the first P, which alone can be among

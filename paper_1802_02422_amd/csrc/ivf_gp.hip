@@ -249,7 +249,7 @@ int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K,
         return IVF_OK;
     }
     if (P <= PS_P_MAX && nb <= PS_NB_MAX) {   // keys in LDS
-        const size_t lds2 = ((size_t)2 * P + 3 + (nb > 2 * PS_CAP ? nb : 2 * PS_CAP)) * sizeof(int);
+        const size_t lds2 = ps_lds_bytes(P);
         if (lds2 > 48 * 1024)
             HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&probe_select_lds_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2));
@@ -282,7 +282,7 @@ enum { WS_DT, WS_BM, WS_QN, WS_QSI, WS_QPK, WS_PID, WS_PD, WS_DESC, WS_LUT, WS_P
 
 // Scratch of a pass of the search without the distance matrix: pieces of one buffer.
 enum { SP_QH, SP_QLEN, SP_BEST, SP_FLAG, SP_LIST, SP_RANK, SP_THR, SP_COUNT, SP_OFFSET, SP_HARD, SP_HROWS, SP_HN, SP_HSI, SP_PAIRS, SP_ITEMS,
-       SP_BIG, SP_PIECES };   // SP_BIG: the distances of the flagged blocks, then the scores
+       SP_HEAD, SP_BIG, SP_PIECES };   // SP_BIG: the distances of the flagged blocks, then the scores
 struct SparsePlan {
     int cap = 0, shift = 0;
     int64_t block_items = 0, region_items = 0, count_words = 0;
@@ -302,7 +302,7 @@ SparsePlan plan_sparse(int64_t K, int D, int P, int L, int64_t n)
     const int64_t bp = n * (sp.cap < nb ? sp.cap : nb), rp = n * P;
     sp.block_items = bp / PAIR_Q + (bp < nb ? bp : nb);
     sp.region_items = rp / PAIR_Q + (rp < K ? rp : K);
-    sp.count_words = (nb + K + 8 + 1) / 2;                     // 64-bit words: counts of blocks and regions, totals
+    sp.count_words = (N_XCD * (nb + K) + 8) / 2;               // 64-bit words: counts of blocks and regions, totals
     size_t bytes[SP_PIECES];
     bytes[SP_QH] = (size_t)pad * Dp * sizeof(_Float16);
     bytes[SP_QLEN] = (size_t)pad * sizeof(float2);
@@ -310,11 +310,12 @@ SparsePlan plan_sparse(int64_t K, int D, int P, int L, int64_t n)
     bytes[SP_FLAG] = bytes[SP_THR] = bytes[SP_HARD] = (size_t)n * 4;
     bytes[SP_LIST] = bytes[SP_RANK] = (size_t)n * sp.cap * 4;
     bytes[SP_COUNT] = (size_t)sp.count_words * 8;
-    bytes[SP_OFFSET] = (size_t)(K > nb ? K : nb) * 4;
+    bytes[SP_OFFSET] = (size_t)N_XCD * K * 4;
     bytes[SP_HROWS] = (size_t)pad * Dp * 2 * sizeof(_Float16);
     bytes[SP_HN] = bytes[SP_HSI] = (size_t)pad * sizeof(float);
     bytes[SP_PAIRS] = (size_t)n * sp.cap * 4;
     bytes[SP_ITEMS] = (size_t)(sp.block_items > sp.region_items ? sp.block_items : sp.region_items) * sizeof(uint4);
+    bytes[SP_HEAD] = (size_t)n * sp.cap * sizeof(uint4);
     const size_t cand = (size_t)n * sp.cap * BMW * 4, keys = (size_t)n * P * L * 4;
     bytes[SP_BIG] = cand > keys ? cand : keys;
     for (int i = 0; i < SP_PIECES; ++i) {
@@ -403,7 +404,7 @@ struct ivf_index {
     float *centroids = nullptr, *cnorm = nullptr, *alpha = nullptr, *cst = nullptr;
     _Float16 *cpk = nullptr;     // centroids packed for the GEMM
     // for the search without the distance matrix (NULL: not built): fp16 rows and their lengths, start values and bounds of the
-    // tiles, squared norms of the neighbours
+    // tiles, squared norms of the neighbours, in one allocation
     _Float16 *chi = nullptr;
     float2 *clen = nullptr;
     float *mstart = nullptr, *nbr_norm = nullptr;
@@ -441,7 +442,7 @@ extern "C" void ivf_free_index(ivf_index *ix)
                      ix->nbr, ix->ids, ix->sub_info, ix->blocks, ix->dt.p, ix->bm.p, ix->qn.p,
                      ix->cpk, ix->csi, ix->qpk.p, ix->qsi.p,
                      ix->probe_id.p, ix->probe_d.p, ix->desc.p, ix->lut.p, ix->partial.p, ix->qrot.p, ix->rot_t,
-                     ix->sparse.p, ix->chi, ix->clen, ix->mstart, ix->nbr_norm, ix->mtile};
+                     ix->sparse.p, ix->chi};
     for (void *p : owned)
         if (p) (void)hipFree(p);
     for (auto &v : ix->ev)
@@ -494,11 +495,27 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
     if (sparse_table(K, D)) {
         const int Dp = packed_dim(D);
         const int64_t tiles = (K + GT - 1) / GT, pad = packed_rows(K);
-        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->chi), (size_t)pad * Dp * sizeof(_Float16)));
-        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->clen), (size_t)pad * sizeof(float2)));
-        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->mstart), (size_t)tiles * GT * sizeof(float)));
-        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->mtile), (size_t)tiles * sizeof(float4)));
-        HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->nbr_norm), (size_t)nsub * sizeof(float)));
+        size_t total = 0;
+        auto place = [&](auto *&p, size_t count) {               // pieces of one allocation, which starts with chi
+            p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(reinterpret_cast<unsigned char *>(ix->chi) + total);
+            total += (count * sizeof(*p) + 255) / 256 * 256;
+        };
+        auto all = [&]() {
+            total = ((size_t)pad * Dp * sizeof(_Float16) + 255) / 256 * 256;
+            place(ix->clen, (size_t)pad);
+            place(ix->mstart, (size_t)tiles * GT);
+            place(ix->mtile, (size_t)tiles);
+            place(ix->nbr_norm, (size_t)nsub);
+            return total;
+        };
+        const hipError_t e = g_pool.fresh(reinterpret_cast<void **>(&ix->chi), all());
+        if (e != hipSuccess && e != hipErrorOutOfMemory) HIPCHK(e);
+        if (e != hipSuccess) ix->chi = nullptr;                  // (no room: searches go with the distance matrix)
+        else (void)all();
+    }
+    if (ix->chi) {
+        const int Dp = packed_dim(D);
+        const int64_t tiles = (K + GT - 1) / GT, pad = packed_rows(K);
         pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(ix->centroids, K, pad, D, Dp,
                                                                                      reinterpret_cast<uint32_t *>(ix->csi + 1), ix->chi, ix->clen);
         LAUNCHCHK("pack_hi_rows_kernel");
@@ -637,8 +654,8 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
     const int64_t PL = (int64_t)P * ix->L;
     const ScoreMode mode = score_mode(ix->K, P, ix->L, pl);
     l.scan = (size_t)SCAN_WAVES * pool_capacity(k) * sizeof(uint64_t);   // dynamic part: the pools
-    l.merge = ((size_t)pl.merge_n + pl.merge_pow2) * sizeof(uint64_t);
-    l.sp = (size_t)(PL + 3 * P) * sizeof(uint32_t);
+    l.merge = (size_t)pl.merge_pow2 * sizeof(uint64_t);
+    l.sp = (size_t)((pl.sparse ? 2 * (int64_t)pl.S : PL) + 3 * P) * sizeof(uint32_t);
     if (l.sp < (size_t)ix->D * sizeof(float)) l.sp = (size_t)ix->D * sizeof(float);   // the table workgroups hold a query
     if (l.sp > 154 * 1024)   // one workgroup holds a query's scores in the 160 KB of LDS, beside 5 KB of static data
         return fail(IVF_EINVAL, "nprobe*L + 3*nprobe = %lld words exceed the LDS of one workgroup", (long long)(PL + 3 * P));
@@ -657,8 +674,7 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
         HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.sp));
     }
     {   // the fused launch needs what either half needs (see launch_probe_select for the selection's share)
-        const int64_t nb = (ix->K + BMW - 1) / BMW;
-        const size_t sel = ((size_t)2 * P + 3 + (nb > 2 * PS_CAP ? nb : 2 * PS_CAP)) * sizeof(int);
+        const size_t sel = ps_lds_bytes(P);
         l.ssp = sel > l.sp ? sel : l.sp;
         if (mode == SCORE_FUSED && l.ssp > 48 * 1024) {
             const void *fn = PL > 16384 ? reinterpret_cast<const void *>(&select_score_prune_kernel<8>)
@@ -667,7 +683,7 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
         }
     }
     if (l.merge > 40 * 1024)
-        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&merge_kernel<256>),
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&merge_kernel<256, 32>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.merge));
     if (l.scan > 32 * 1024) {   // dynamic + static LDS above the default 64 KB window
         const void *fn = ix->M == 16 ? reinterpret_cast<const void *>(&scan_kernel<16>)
@@ -704,9 +720,11 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     piece(a.hard_si, SP_HSI);
     piece(a.pairs, SP_PAIRS);
     piece(a.items, SP_ITEMS);
+    piece(a.head, SP_HEAD);
     piece(a.cand, SP_BIG);
     piece(a.keys, SP_BIG);
-    a.total = a.count + nb + K;
+    a.region_count = a.count + N_XCD * nb;
+    a.total = a.region_count + N_XCD * K;
     a.K = K;
     a.half_ld = minima_half(K);
     a.nb = nb;
@@ -749,25 +767,26 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     else if (Dp == 96) sweep(&coarse_minima_kernel<3>);
     else sweep(&coarse_minima_kernel<4>);
     LAUNCHCHK("coarse_minima_kernel");
-    const size_t flag_lds = (size_t)2 * a.half_ld * sizeof(uint32_t);
-    auto flag = [&](auto kernel, int grid_n, int block, size_t lds) -> int {
-        if (lds > 48 * 1024)
-            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        kernel<<<dim3((unsigned)grid_n), dim3(block), lds, st>>>(a);
-        LAUNCHCHK("flag_blocks_kernel");
-        return IVF_OK;
-    };
     const bool wide = nb > 4096;                                // (16 blocks a thread at most)
-    if ((rc = wide ? flag(&flag_blocks_kernel<1024>, (int)n, 1024, flag_lds) : flag(&flag_blocks_kernel<256>, (int)n, 256, flag_lds))) return rc;
+    // pieces: at least 8 P of them (sparse_pays: the table has at least 8 P tiles), or 2048
+    const dim3 gq((unsigned)n);
+    static_assert(PS_NB_MAX <= 2 * 4 * 4 * 512, "four pieces of four tiles a thread, 512 threads");
+    if (tiles_c <= 512) flag_blocks_kernel<256, 1, 2><<<gq, dim3(256), 0, st>>>(a);
+    else if (tiles_c <= 2048) flag_blocks_kernel<256, 1, 8><<<gq, dim3(256), 0, st>>>(a);
+    else if (tiles_c <= 4096) flag_blocks_kernel<512, 2, 4><<<gq, dim3(512), 0, st>>>(a);
+    else flag_blocks_kernel<512, 4, 4><<<gq, dim3(512), 0, st>>>(a);
+    LAUNCHCHK("flag_blocks_kernel");
     hard_rows_kernel<<<dim3(256), dim3(256), 0, st>>>(a);
     LAUNCHCHK("hard_rows_kernel");
     hard_minima_kernel<<<dim3(1024), dim3(256), 0, st>>>(a);
     LAUNCHCHK("hard_minima_kernel");
-    if ((rc = wide ? flag(&hard_flag_kernel<1024>, 512, 1024, flag_lds) : flag(&hard_flag_kernel<256>, 1024, 256, flag_lds))) return rc;
+    if (wide) hard_flag_kernel<1024><<<dim3(512), dim3(1024), 0, st>>>(a);
+    else hard_flag_kernel<256><<<dim3(1024), dim3(256), 0, st>>>(a);
+    LAUNCHCHK("hard_flag_kernel");
     auto grouped = [&](uint32_t *count, int64_t buckets, uint32_t *total, const int32_t *bucket, int width, const uint32_t *n_flag) -> int {
         bucket_items_kernel<<<dim3((unsigned)((buckets + 1023) / 1024)), dim3(1024), 0, st>>>(count, buckets, total, a.offset, a.items);
         LAUNCHCHK("bucket_items_kernel");
-        place_pairs_kernel<<<dim3((unsigned)((n * width + 255) / 256)), dim3(256), 0, st>>>(bucket, a.rank, n, width, sp.cap, sp.shift, n_flag, a.offset, a.pairs);
+        place_pairs_kernel<<<dim3((unsigned)((n * width + 255) / 256)), dim3(256), 0, st>>>(bucket, a.rank, n, width, buckets, sp.cap, sp.shift, n_flag, a.offset, a.pairs);
         LAUNCHCHK("place_pairs_kernel");
         return IVF_OK;
     };
@@ -783,10 +802,11 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     } while (0)
     IVF_PAIRS(false, sp.block_items, a.total + 2);
     if ((rc = mark(1))) return rc;
-    probe_pick_kernel<256><<<dim3((unsigned)n), dim3(256), (size_t)(sp.cap + 2 * PICK_CAP) * sizeof(uint32_t), st>>>(a);
+    static_assert(2 * PICK_BLOCK >= 2 * PS_P_MAX, "two of a query's blocks a thread");
+    probe_pick_kernel<<<dim3((unsigned)n), dim3(PICK_BLOCK), 2 * PICK_CAP * sizeof(uint32_t), st>>>(a);
     LAUNCHCHK("probe_pick_kernel");
     if ((rc = mark(2))) return rc;
-    if ((rc = grouped(a.count + nb, K, a.total + 3, pid, P, nullptr))) return rc;
+    if ((rc = grouped(a.region_count, K, a.total + 3, pid, P, nullptr))) return rc;
     IVF_PAIRS(true, sp.region_items, a.total + 4);
 #undef IVF_PAIRS
     return IVF_OK;
@@ -840,20 +860,21 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
             LAUNCHCHK("rotate_rows_kernel");
             Qt = ws.qrot;
         }
-        // stages 2-3 (one workgroup per query) and stage 4 (one more workgroup per query) in one launch
+        // stages 2-3 (one workgroup per query) and stage 4 (one more for every lut_per queries) in one launch
 #define IVF_SP_LAUNCH(BLK, ...)                                                                                    \
-    score_prune_kernel<BLK, __VA_ARGS__><<<dim3((unsigned)(2 * n)), dim3(BLK), lds.sp, st>>>(                                \
+    score_prune_kernel<BLK, __VA_ARGS__><<<dim3(lut_grid(n, lut_per)), dim3(BLK), lds.sp, st>>>(                                \
         ws.dt, dt_stride(K), K, pid, pd, P, L, ix->nbr, ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, n, Qt, \
-        D, M, ix->codebook, ws.lut)
+        D, M, ix->codebook, ws.lut, lut_per)
 #define IVF_SSP_LAUNCH(MV)                                                                                          \
-    select_score_prune_kernel<MV><<<dim3((unsigned)(2 * n)), dim3(1024), lds.ssp, st>>>(                             \
+    select_score_prune_kernel<MV><<<dim3(lut_grid(n, lut_per)), dim3(1024), lds.ssp, st>>>(                             \
         ws.dt, dt_stride(K), ws.bm, K, nb, pid, pd, P, L, ix->nbr, ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, \
-        n, Qt, D, M, ix->codebook, ws.lut)
+        n, Qt, D, M, ix->codebook, ws.lut, lut_per)
+        const int lut_per = lut_queries(n, D, lds.sp);
         if (pl.sparse) {
             const uint32_t *given = reinterpret_cast<const uint32_t *>(ws.sparse + plan_sparse(K, D, P, L, n).off[SP_BIG]);
             auto prune = [&](auto kernel, int block) {
-                kernel<<<dim3((unsigned)(2 * n)), dim3(block), lds.sp, st>>>(reinterpret_cast<const float *>(given), PL, K, pid, pd, P, L, ix->nbr,
-                    ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, n, Qt, D, M, ix->codebook, ws.lut);
+                kernel<<<dim3(lut_grid(n, lut_per)), dim3(block), lds.sp, st>>>(reinterpret_cast<const float *>(given), PL, K, pid, pd, P, L, ix->nbr,
+                    ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, n, Qt, D, M, ix->codebook, ws.lut, lut_per);
             };
             if (mode == SCORE_GIVEN_512) prune(&score_prune_kernel<512, 2, -1>, 512);
             else prune(&score_prune_kernel<1024, 4, -1>, 1024);
@@ -885,8 +906,12 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         LAUNCHCHK("scan_kernel");
         if ((rc = mark(5))) return rc;
 
-        merge_kernel<256><<<dim3((unsigned)n), dim3(256), lds.merge, st>>>(
-            ws.partial, ix->ids, pl.merge_n, pl.merge_pow2, k, a.out_ids + q0 * k, a.out_dists + q0 * k);
+        auto merge = [&](auto kernel) {
+            kernel<<<dim3((unsigned)n), dim3(256), lds.merge, st>>>(ws.partial, ix->ids, pl.merge_n, k, a.out_ids + q0 * k, a.out_dists + q0 * k);
+        };
+        if (pl.merge_n <= 4 * 256) merge(&merge_kernel<256, 4>);
+        else if (pl.merge_n <= 16 * 256) merge(&merge_kernel<256, 16>);
+        else merge(&merge_kernel<256, 32>);
         LAUNCHCHK("merge_kernel");
         if ((rc = mark(6))) return rc;
         if (timed) ix->launches++;
@@ -964,7 +989,11 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
     else if (tile >= 256) tile -= tile % 256;   // whole blocks of the padded row count
     else if (tile >= GT) tile -= tile % GT;
 
-    const int64_t sparse_n = sparse_tile(ix, nprobe, nq);
+    int64_t sparse_n = sparse_tile(ix, nprobe, nq);
+    if (sparse_n > 0 && (rc = ensure(ix->sparse, plan_sparse(K, ix->D, nprobe, ix->L, sparse_n).total))) {
+        if (rc != IVF_ENOMEM) return rc;
+        sparse_n = 0;                                            // (no room: with the distance matrix, in as many passes as its limit asks for)
+    }
     const bool sparse = sparse_n > 0;
     if (sparse) tile = sparse_n;
     const SearchPlan pl = plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr, true, sparse);
@@ -972,7 +1001,6 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
                            &ix->desc, &ix->lut, &ix->partial, &ix->qrot};
     for (int i = 0; i < WS_COUNT; ++i)
         if ((rc = ensure(*bufs[i], pl.bytes[i]))) return rc;
-    if (sparse && (rc = ensure(ix->sparse, plan_sparse(K, ix->D, nprobe, ix->L, tile).total))) return rc;
     SearchWs ws;
     ws.sparse = static_cast<unsigned char *>(ix->sparse.p);
     ws.dt = static_cast<float *>(ix->dt.p);

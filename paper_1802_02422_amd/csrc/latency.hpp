@@ -12,8 +12,8 @@
 
 namespace ivf {
 
-// Workgroups 0 .. nq-1: select, then score and prune, query q = blockIdx.x; nq .. 2nq-1: the lookup
-// tables.  Dynamic LDS: the larger of what the two halves need (they use it one after the other).
+// Workgroups 0 .. nq-1: select, then score and prune, query q = blockIdx.x; then the lookup
+// tables, lut_per queries a workgroup.  Dynamic LDS: the larger of what the two halves need (they use it one after the other).
 // Registers are capped so that two workgroups fit a compute unit (MAXV = 4: 64 VGPRs).
 template <int MAXV>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MAXV == 4 ? 8 : 4, MAXV == 4 ? 8 : 5))) void select_score_prune_kernel(
@@ -22,18 +22,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MAXV == 4 
     const float *__restrict__ cst, const float *__restrict__ alpha, int S, const uint4 *__restrict__ sub_info,
     SubDesc *__restrict__ desc, int64_t *__restrict__ kept_sub, int64_t *__restrict__ n_scanned,
     int64_t nq, const float *__restrict__ Qt, int D, int M, const float *__restrict__ codebook,
-    float *__restrict__ lut)
+    float *__restrict__ lut, int lut_per)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     if ((int64_t)blockIdx.x >= nq) {   // (uniform) a table workgroup
-        const int64_t ql = (int64_t)blockIdx.x - nq;
-        lut_body<1024>(Qt + ql * D, D, M, codebook, lut + ql * (int64_t)M * 256, reinterpret_cast<float *>(dyn));
+        const int64_t ql = ((int64_t)blockIdx.x - nq) * lut_per;
+        lut_body<1024>(Qt + ql * D, nq - ql < lut_per ? (int)(nq - ql) : lut_per, D, M, codebook, lut + ql * (int64_t)M * 256, reinterpret_cast<float *>(dyn));
         return;
     }
-    probe_select_lds_body(Dt, ldt, bm, K, nb, P, probe_id, probe_d, blockIdx.x, reinterpret_cast<int *>(dyn));
+    __shared__ SelectRegs<SCORE_BINS> sh;
+    probe_select_lds_body(Dt, ldt, bm, K, nb, P, probe_id, probe_d, blockIdx.x, reinterpret_cast<int *>(dyn), sh);
     __syncthreads();   // the probes are written (and the selection is done with the LDS the scoring reuses)
     score_prune_body<1024, MAXV>(Dt, ldt, K, probe_id, probe_d, P, L, nbr, cst, alpha, S, sub_info, desc, kept_sub, n_scanned,
-                                 blockIdx.x, dyn);
+                                 blockIdx.x, dyn, sh);
 }
 
 }  // namespace ivf

@@ -6,6 +6,9 @@
 
 namespace ivf {
 
+constexpr int SCORE_BINS = 1024;
+template <int BLOCK, int STREAM> constexpr int score_bins() { return STREAM < 0 ? 4 * BLOCK : SCORE_BINS; }
+
 // One kept subregion of one query, as the scan consumes it.
 struct SubDesc {
     uint32_t blk;    // start of the subregion's record block, in BLK_ALIGN-byte units
@@ -14,24 +17,55 @@ struct SubDesc {
     float base;      // distance from the query to the subcentroid
 };
 
-// T[q][m][j] = -2 <q_m, r^m_j> (Eq. (6)) for one query by one workgroup of BLOCK threads: the query
-// in LDS (qs, D floats), every thread one (sub-quantiser, codeword) pair at a time, each entry one
-// chain of fused multiply-adds over the block's dimensions.
+// T[q][m][j] = -2 <q_m, r^m_j> (Eq. (6)) for nl <= LUT_Q queries in a row by one workgroup of BLOCK threads: the queries in LDS
+// (qs, [D][LUT_Q] floats; [D] for one), every thread one (sub-quantiser, codeword) pair at a time, each entry one chain of fused
+// multiply-adds over the block's dimensions.  Bound by the reads of the codewords, so that where there are queries enough a
+// workgroup takes LUT_Q of them.
+constexpr int LUT_Q = 8;
+
 template <int BLOCK>
-__device__ __forceinline__ void lut_body(const float *__restrict__ Qrow, int D, int M,
-                                         const float *__restrict__ codebook, float *__restrict__ Tq, float *qs)
+__device__ __forceinline__ void lut_body(const float *__restrict__ Q, int nl, int D, int M, const float *__restrict__ codebook,
+                                         float *__restrict__ T, float *qs)
 {
     const int ds = D / M;
-    for (int i = threadIdx.x; i < D; i += BLOCK) qs[i] = Qrow[i];
+    if (nl == 1) {
+        for (int i = threadIdx.x; i < D; i += BLOCK) qs[i] = Q[i];
+        __syncthreads();
+        for (int e = threadIdx.x; e < M * 256; e += BLOCK) {
+            const float *cw = codebook + (int64_t)e * ds, *qm = qs + (e >> 8) * ds;
+            float s = 0.f;
+            for (int i = 0; i < ds; ++i) s = fmaf(qm[i], cw[i], s);
+            T[e] = -2.f * s;
+        }
+        return;
+    }
+    for (int i = threadIdx.x; i < nl * D; i += BLOCK) qs[(i % D) * LUT_Q + i / D] = Q[i];
     __syncthreads();
     for (int e = threadIdx.x; e < M * 256; e += BLOCK) {
-        const int m = e >> 8;
-        const float *cw = codebook + (int64_t)e * ds;
-        float s = 0.f;
-        for (int i = 0; i < ds; ++i) s = fmaf(qs[m * ds + i], cw[i], s);
-        Tq[e] = -2.f * s;
+        const float *cw = codebook + (int64_t)e * ds, *qm = qs + (e >> 8) * ds * LUT_Q;
+        float s[LUT_Q];
+#pragma unroll
+        for (int j = 0; j < LUT_Q; ++j) s[j] = 0.f;
+        for (int i = 0; i < ds; ++i) {
+            const float c = cw[i];
+#pragma unroll
+            for (int j = 0; j < LUT_Q; j += 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(&qm[i * LUT_Q + j]);   // (past nl: whatever is there, not stored)
+                s[j] = fmaf(v.x, c, s[j]);
+                s[j + 1] = fmaf(v.y, c, s[j + 1]);
+                s[j + 2] = fmaf(v.z, c, s[j + 2]);
+                s[j + 3] = fmaf(v.w, c, s[j + 3]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < LUT_Q; ++j)
+            if (j < nl) T[(int64_t)j * M * 256 + e] = -2.f * s[j];
     }
 }
+
+// Queries of a table workgroup: LUT_Q where that leaves a workgroup for every compute unit and their rows fit the launch's LDS.
+inline int lut_queries(int64_t n, int D, size_t lds) { return n >= 256 * LUT_Q && (size_t)LUT_Q * D * sizeof(float) <= lds ? LUT_Q : 1; }
+inline unsigned lut_grid(int64_t n, int per) { return (unsigned)(n + (n + per - 1) / per); }   // scoring workgroups, then table ones
 
 // Stages 2 and 3 fused, one workgroup per query.
 // Stage 2 (Eq. (7)): score[p][l] = (1-a) D[q][r] + a D[q][nbr[r][l]] + cst[r][l], r = probe_id[q][p],
@@ -46,8 +80,8 @@ __device__ __forceinline__ void lut_body(const float *__restrict__ Qrow, int D, 
 // reads of the subregion table of four positions in flight per thread (filled item by item as
 // they were selected, every read of that table was waited for before the next was issued).
 // Dynamic LDS: P*L keys + P probe ids + P probe distances + P alphas.  P*L <= 4 * MAXV * BLOCK.
-// Stage 4 rides along: the grid has 2 nq workgroups, and workgroup nq + q builds query q's lookup
-// table (lut_body, from Qt = the queries, rotated if the index has a rotation) while the first nq
+// Stage 4 rides along: behind the nq workgroups there is one for every lut_per queries' lookup
+// tables (lut_body, from Qt = the queries, rotated if the index has a rotation) while the first nq
 // gather and select; the two halves share nothing, and the table work hides under the gathers.
 // Dynamic LDS must also hold D floats.
 // STREAM > 0: the query's whole row of the tile is read, STREAM distances at a time, into LDS (over the place of the keys,
@@ -55,7 +89,8 @@ __device__ __forceinline__ void lut_body(const float *__restrict__ Qrow, int D, 
 // each 4 bytes, so that with 16 P L >= K the row is the smaller number of bytes, and whole lines in order (where that
 // pays: score_mode).  Dynamic LDS:
 // max(P*L, STREAM + 4) + 3 P words.
-// STREAM < 0: the keys of the scores are given (pair_distance_kernel), ldt = P*L of them a query in the place of Dt.
+// STREAM < 0: the keys of the scores are given (pair_distance_kernel), ldt = P*L of them a query in the place of Dt, and go to
+// registers; dynamic LDS: 2 S + 3 P words.
 // (the body of a scoring workgroup, for query q of the batch: also the second half of select_score_prune_kernel)
 template <int BLOCK, int MAXV, int STREAM = 0>
 __device__ __forceinline__ void score_prune_body(
@@ -64,13 +99,12 @@ __device__ __forceinline__ void score_prune_body(
     const float *__restrict__ cst, const float *__restrict__ alpha, int S,
     const uint4 *__restrict__ sub_info,
     SubDesc *__restrict__ desc, int64_t *__restrict__ kept_sub, int64_t *__restrict__ n_scanned,
-    int64_t q, uint32_t *dyn)
+    int64_t q, uint32_t *dyn, SelectRegs<score_bins<BLOCK, STREAM>()> &sh)
 {
-    __shared__ SelectShared sh;
     __shared__ unsigned long long codes_total;
     const int PL = P * L;
     uint32_t *keys = dyn;
-    const int front = STREAM > 0 && PL < STREAM + 4 ? STREAM + 4 : PL;
+    const int front = STREAM < 0 ? 2 * S : STREAM > 0 && PL < STREAM + 4 ? STREAM + 4 : PL;
     int32_t *pid = reinterpret_cast<int32_t *>(dyn + front);
     float *pd = reinterpret_cast<float *>(dyn + front + P);
     float *pa = reinterpret_cast<float *>(dyn + front + 2 * P);
@@ -83,19 +117,7 @@ __device__ __forceinline__ void score_prune_body(
     }
     if (threadIdx.x == 0) codes_total = 0;
     __syncthreads();
-    if constexpr (STREAM < 0) {
-        const uint32_t *given = reinterpret_cast<const uint32_t *>(row);
-        if ((PL & 3) == 0) {                             // (rows of PL words from a 16-byte boundary on)
-#pragma unroll
-            for (int v = 0; v < MAXV; ++v) {
-                const int i = threadIdx.x + v * BLOCK;
-                if (4 * i < PL) reinterpret_cast<uint4 *>(keys)[i] = reinterpret_cast<const uint4 *>(given)[i];
-            }
-        } else {
-#pragma unroll 4
-            for (int i = threadIdx.x; i < PL; i += BLOCK) keys[i] = given[i];
-        }
-    } else if constexpr (STREAM > 0) {
+    if constexpr (STREAM > 0) {
         constexpr int U = 4 * MAXV;                      // items of a thread: threadIdx.x + u * BLOCK
         uint32_t word[U];                                 // neighbour id, then the distance (found: bit u)
         uint32_t found = 0;
@@ -142,7 +164,7 @@ __device__ __forceinline__ void score_prune_body(
                 keys[i] = float_key(fmaf(a, __uint_as_float(word[u]), fmaf(1.f - a, pd[p], cst[(int64_t)pid[p] * L + (i - p * L)])));
             }
         }
-    } else {
+    } else if constexpr (STREAM == 0) {
 #pragma unroll 4
         for (int i = threadIdx.x; i < PL; i += BLOCK) {
             const int p = i / L, l = i - p * L;
@@ -152,17 +174,22 @@ __device__ __forceinline__ void score_prune_body(
             keys[i] = float_key(fmaf(a, ds, fmaf(1.f - a, pd[p], cst[r * L + l])));
         }
     }
-    __syncthreads();
-    auto key = [keys](int64_t i) { return keys[i]; };
-    uint32_t pivot, need;
-    block_radix_select<BLOCK>(key, PL, (uint32_t)S, sh, pivot, need);
+    if (STREAM >= 0) __syncthreads();
+    uint32_t kv[4 * MAXV], pivot, need;
+    const int ipt = run_length<BLOCK>(PL);
+    auto same = [](uint32_t w) { return w; };
+    if (STREAM >= 0) load_run<BLOCK>(keys, PL, kv, same);
+    else if ((PL & 3) == 0) load_run<BLOCK>(reinterpret_cast<const uint32_t *>(row), PL, kv, same);
+    else load_run<BLOCK, false>(reinterpret_cast<const uint32_t *>(row), PL, kv, same);
+    block_select_runs<BLOCK>(kv, ipt, (uint32_t)S, sh, pivot, need);   // (every key is in registers behind its first barrier)
     float *base_of = &desc[q * S].base;                  // stride of one descriptor: 4 floats
-    block_emit_selected_runs<BLOCK, MAXV>(keys, PL, pivot, need, sh,
-                                          [&](uint32_t pos, int64_t i, uint32_t k) {
-                                              keys[pos] = (uint32_t)i;
-                                              base_of[4 * pos] = key_float(k);
-                                          });
+    block_emit_runs<BLOCK>(kv, ipt, pivot, need, sh.scan, [&](uint32_t pos, int i, uint32_t k) {
+        keys[pos] = (uint32_t)i;
+        if (STREAM < 0) keys[S + pos] = __float_as_uint(key_float(k));
+        else base_of[4 * pos] = key_float(k);
+    });
     __syncthreads();
+    const float per_l = 1.f / (float)L;                  // (i + 1/2) / L is at least 1/(2 L) from a whole number, and i below 2^15
     unsigned long long mine = 0;
     for (int p0 = 0; p0 < S; p0 += 4 * BLOCK) {
         uint4 info[4];
@@ -171,8 +198,8 @@ __device__ __forceinline__ void score_prune_body(
         for (int u = 0; u < 4; ++u) {
             const int pos = p0 + u * BLOCK + (int)threadIdx.x;
             if (pos < S) {
-                const int i = (int)keys[pos];
-                sub[u] = (int64_t)pid[i / L] * L + (i % L);
+                const int i = (int)keys[pos], p = (int)(((float)i + 0.5f) * per_l);
+                sub[u] = (int64_t)pid[p] * L + (i - p * L);
                 info[u] = sub_info[sub[u]];                // one 16-byte read per kept subregion
             }
         }
@@ -180,10 +207,14 @@ __device__ __forceinline__ void score_prune_body(
         for (int u = 0; u < 4; ++u) {
             const int pos = p0 + u * BLOCK + (int)threadIdx.x;
             if (pos < S) {
-                uint32_t *d = &desc[q * S + pos].blk;      // blk, pos0, len: the first 12 bytes
-                d[0] = info[u].x;
-                d[1] = info[u].y;
-                d[2] = info[u].z;
+                if (STREAM < 0) {
+                    *reinterpret_cast<uint4 *>(&desc[q * S + pos]) = make_uint4(info[u].x, info[u].y, info[u].z, keys[S + pos]);
+                } else {
+                    uint32_t *d = &desc[q * S + pos].blk;  // blk, pos0, len: the first 12 bytes
+                    d[0] = info[u].x;
+                    d[1] = info[u].y;
+                    d[2] = info[u].z;
+                }
                 if (kept_sub) kept_sub[q * S + pos] = sub[u];
                 mine += info[u].z;
             }
@@ -202,16 +233,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STREAM ? 
     const uint4 *__restrict__ sub_info,
     SubDesc *__restrict__ desc, int64_t *__restrict__ kept_sub, int64_t *__restrict__ n_scanned,
     int64_t nq, const float *__restrict__ Qt, int D, int M, const float *__restrict__ codebook,
-    float *__restrict__ lut)
+    float *__restrict__ lut, int lut_per)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     if ((int64_t)blockIdx.x >= nq) {   // (uniform) a table workgroup
-        const int64_t ql = (int64_t)blockIdx.x - nq;
-        lut_body<BLOCK>(Qt + ql * D, D, M, codebook, lut + ql * (int64_t)M * 256, reinterpret_cast<float *>(dyn));
+        const int64_t ql = ((int64_t)blockIdx.x - nq) * lut_per;
+        lut_body<BLOCK>(Qt + ql * D, nq - ql < lut_per ? (int)(nq - ql) : lut_per, D, M, codebook, lut + ql * (int64_t)M * 256, reinterpret_cast<float *>(dyn));
         return;
     }
+    __shared__ SelectRegs<score_bins<BLOCK, STREAM>()> sh;
     score_prune_body<BLOCK, MAXV, STREAM>(Dt, ldt, K, probe_id, probe_d, P, L, nbr, cst, alpha, S, sub_info, desc, kept_sub, n_scanned,
-                                  blockIdx.x, dyn);
+                                          blockIdx.x, dyn, sh);
 }
 
 // Rotation in front of the product quantiser (Section 4: OPQ-compressed displacements, one global

@@ -23,7 +23,7 @@ namespace ivf {
 // The queries' fp16 rows have the centroid table's scale, four times smaller: room for components eight times the table's
 // largest; a query with a larger one is a hard one.
 constexpr int SPARSE_HEADROOM = 2;
-constexpr int64_t SPARSE_MIN_K = 8192;
+constexpr int64_t SPARSE_MIN_K = 16384;   // (sparse_pays: below, no batch of less than 8192 queries takes it)
 
 // |x| and |dx| of a row (see pack_hi_rows_kernel) with infinite lengths where a centroid of the tile is not finite: such a
 // block is always looked at.  start[c] = (-1/2 + k) |c|^2 in units of the product, -inf past K; tile[t] = (largest |c|,
@@ -224,15 +224,16 @@ struct SparseArgs {
     int32_t *blist;                            // [nq][cap] flagged blocks, ascending
     uint32_t *rank;                            // [nq][cap] place of a pair among those of its bucket
     float *thr;                                // [nq] no distance of the P closest is larger
-    uint32_t *count;                           // [nb] blocks, then [K] regions: pairs of a bucket
-    uint32_t *offset;                          // [max(nb, K)] first pair of a bucket
+    uint32_t *count, *region_count;            // [N_XCD][nb], [N_XCD][K] pairs of a bucket, by query % N_XCD
+    uint32_t *offset;                          // the same for the first pair of each
     uint32_t *total;                           // [0]: hard queries; [1], [2]: pairs, work items of the blocks; [3], [4]: of the regions
     uint32_t *hard;                            // [nq] the hard queries
     _Float16 *hard_rows;
     float *hard_n, *hard_si;
     uint32_t *pairs;
     uint4 *items;                              // bucket, first pair, pairs
-    float *cand;                               // [nq][cap][64] distances of the flagged blocks
+    uint4 *head;                               // [nq][cap] of a flagged block: distances up to thr, the first one's key and centroid
+    uint32_t *cand;                            // [nq][cap][64] the keys of all 64, where it is more than one
     uint32_t *keys;                            // [nq][P L] scores
     int32_t *probe_id;
     float *probe_d;
@@ -240,81 +241,145 @@ struct SparseArgs {
     const float *nbr_norm, *cst, *alpha;
 };
 
-// Lists the blocks of query q that can hold one of its P closest centroids.  EXACT: best holds smallest distances (the
-// rule of probe_select_kernel).  Else a block is known by low, the lower end of its best value, and is listed if its upper end reaches
-// the P-th largest lower end; low and the upper end are widened by the rounding of the exact distances too, by whose
-// computed values everything that follows decides.  Dynamic LDS: 2 half_ld words.
-template <int BLOCK, bool EXACT>
-__device__ __forceinline__ void flag_blocks_body(const SparseArgs &a, int64_t q, uint32_t *keys, SelectShared &sh)
+// Lists the blocks of 64 that can hold one of a query's P closest centroids: a block's smallest distance lies between two ends,
+// and the block is listed if its lower end does not exceed an upper bound of the P-th smallest upper end.  The ends are widened by the
+// rounding of the exact distances too, by whose computed values everything that follows decides.  They are taken as distances in
+// units of the product, |q|^2 - 2 G: not negative, so that their bits order like them (and not -G, whose sign changes from block to
+// block: bins of equal width would be wasted on the exponents around zero).
+// A thread takes NP pieces of TP tiles (2 TP blocks) of every 256 in a row, all in registers.  The bound is the P-th smallest of
+// the pieces' smallest upper ends: where near blocks lie anywhere it lists 7 % more than need be, for an eighth of the keys to select
+// from.  Where it lists too many (near blocks side by side) a histogram of all blocks gives a closer one; what is over cap then
+// is a hard query.  Few threads a query: the selection's steps cost every wavefront the same instructions, few keys or many
+// (10 000 queries x 16 384 blocks: 340 us, 425 with 1024 threads, 750 with 256 and more blocks than registers).
+template <int BLOCK, int TP, int NP>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4, 8))) void flag_blocks_kernel(SparseArgs a)
 {
-    const int tid = threadIdx.x;
+    constexpr int NB = 2 * TP, NW = BLOCK / WAVE;
+    __shared__ SelectRegs<1024> sh;
+    __shared__ uint32_t base[NW * NP];
+    static_assert(NP * NW <= WAVE, "a lane for a piece and wavefront");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t q = blockIdx.x;
     const float *row = a.best + q * 2 * a.half_ld;
+    const int tiles = (a.nb + 1) / 2, pieces = (tiles + TP - 1) / TP;
     const float k = (float)(a.Dp + 32) * 0x1p-24f, back = 2.f * k / (0.5f - k);
-    const float2 ql = EXACT ? make_float2(0.f, 0.f) : a.qlen[q];
+    const float2 ql = a.qlen[q];
     // half a distance's rounding error, 64 u (|q|^2 + |c|^2), in units of the product (four times the measured bound of the
     // parity checks), and the low halves below fp16's range
-    const float up2 = 1.f * (1 << SPARSE_HEADROOM), down2 = 1.f / (1 << SPARSE_HEADROOM);
-    auto eps_of = [&](float4 tl) {
-        return shortlist_eps(ql, tl.x, tl.y, a.Dp) + 0x1p-18f * fmaf(up2 * ql.x, ql.x, down2 * tl.x * tl.x) + 0x1p-20f * ql.x;
-    };
-    for (int64_t i = tid; i < a.half_ld / 4; i += BLOCK) {
-        const float4 e = reinterpret_cast<const float4 *>(row)[i], o = reinterpret_cast<const float4 *>(row + a.half_ld)[i];
-        const float ev[4] = {e.x, e.y, e.z, e.w}, ov[4] = {o.x, o.y, o.z, o.w};
-        uint32_t w[8];
+    const float up2 = 1.f * (1 << SPARSE_HEADROOM), down2 = 1.f / (1 << SPARSE_HEADROOM), q2 = up2 * ql.x * ql.x;
+    const float eps_q = fmaf(0x1p-18f, q2, 0x1p-20f * ql.x), eps_c = fmaf(k, ql.x, ql.y), eps_d = ql.x + ql.y;
+    uint32_t far[NP][NB];                                        // upper ends
+    float gap[NP];                                               // ... to the lower ones, the largest of a piece
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t t = 4 * i + u;
-            float x = ev[u], y = ov[u];
-            if (!EXACT) {
-                const float4 tl = 2 * t < a.nb ? a.tile[t] : make_float4(0.f, 0.f, 0.f, 0.f);
-                const float eps = eps_of(tl);
-                x = eps < INFINITY ? eps - fmaf(back, tl.z, x) : INFINITY;   // the negative of the lower end
-                y = eps < INFINITY ? eps - fmaf(back, tl.z, y) : INFINITY;
-            }
-            w[2 * u] = 2 * t < a.nb ? float_key(x) : 0xFFFFFFFFu;
-            w[2 * u + 1] = 2 * t + 1 < a.nb ? float_key(y) : 0xFFFFFFFFu;
-        }
-        reinterpret_cast<uint4 *>(keys)[2 * i] = make_uint4(w[0], w[1], w[2], w[3]);
-        reinterpret_cast<uint4 *>(keys)[2 * i + 1] = make_uint4(w[4], w[5], w[6], w[7]);
-    }
-    __syncthreads();
-    const uint32_t nsel = a.P < a.nb ? (uint32_t)a.P : (uint32_t)a.nb;
-    uint32_t pivot, need;
-    block_radix_select<BLOCK>([keys](int64_t b) { return keys[b]; }, a.nb, nsel, sh, pivot, need);
-    int32_t *list = a.blist + q * a.cap;
-    uint32_t *rank = a.rank + q * a.cap;
-    auto put = [&](uint32_t pos, int b) {
-        list[pos] = b;
-        rank[pos] = atomicAdd(&a.count[b], 1u);
-    };
-    uint32_t total;
-    if (EXACT) {
-        total = block_emit_selected_runs<BLOCK, 4>(keys, a.nb, pivot, (uint32_t)a.P, sh, [&](uint32_t pos, int64_t b, uint32_t) { put(pos, (int)b); });
-        if (tid == 0) {
-            a.n_flag[q] = total;
-            a.thr[q] = a.nb < a.P ? INFINITY : key_float(pivot);
-        }
-        return;
-    }
-    const float limit = a.nb < a.P ? INFINITY : key_float(pivot);            // the negative of the P-th largest lower end
-    const int ipt = ((a.nb + BLOCK - 1) / BLOCK + 3) & ~3, i0 = tid * ipt;     // at most 16 blocks a thread
-    uint32_t flags = 0;
+    for (int u = 0; u < NP; ++u) {
+        const int pc = tid + u * BLOCK, t0 = pc < pieces ? pc * TP : (pieces - 1) * TP;   // (every thread loads)
+        float x[2][TP];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-        if (4 * v < ipt && i0 + 4 * v < a.nb) {
-            const uint4 w = *reinterpret_cast<const uint4 *>(&keys[i0 + 4 * v]);
-            const uint32_t kv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int b = i0 + 4 * v + u;
-                if (b >= a.nb) break;
-                const float4 tl = a.tile[b >> 1];
-                const float neg = key_float(kv[u]);
-                // upper end = lower end + 2 eps - back z;  the rounding of these few operations is far inside the margins above
-                if (!(neg - (2.f * eps_of(tl) - back * tl.z) > limit) || !(neg < INFINITY)) flags |= 1u << (4 * v + u);
+        for (int o = 0; o < 2; ++o) {
+            const float *src = row + o * a.half_ld + t0;
+            if constexpr (TP == 4) {
+                const float4 w = *reinterpret_cast<const float4 *>(src);
+                x[o][0] = w.x; x[o][1] = w.y; x[o][2] = w.z; x[o][3] = w.w;
+            } else if constexpr (TP == 2) {
+                const float2 w = *reinterpret_cast<const float2 *>(src);
+                x[o][0] = w.x; x[o][1] = w.y;
+            } else {
+                x[o][0] = src[0];
             }
         }
-    const uint32_t exc = block_exclusive_scan<BLOCK>((uint32_t)__popc(flags), sh.scan, total);
+        gap[u] = 0.f;
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            const float4 tl = a.tile[t0 + i < tiles ? t0 + i : tiles - 1];
+            const float eps = fmaf(eps_c, tl.x, fmaf(eps_d, tl.y, fmaf(0x1p-18f * down2 * tl.x, tl.x, eps_q))), low = back * tl.z;
+            const bool known = eps < INFINITY;
+            gap[u] = fmaxf(gap[u], known ? 2.f * (2.f * eps - low) : INFINITY);
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                const float d = known ? fmaxf(fmaf(-2.f, x[o][i], fmaf(2.f, eps - low, q2)), 0.f) : INFINITY;
+                far[u][2 * i + o] = pc < pieces && 2 * (t0 + i) + o < a.nb ? __float_as_uint(d) : NO_KEY;
+            }
+        }
+    }
+    uint32_t least[NP], pivot, need;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        least[u] = far[u][0];
+#pragma unroll
+        for (int i = 1; i < NB; ++i) least[u] = far[u][i] < least[u] ? far[u][i] : least[u];
+    }
+    // (fewer pieces than P: everything is listed that is not over cap)
+    float limit = INFINITY;
+    if (a.P <= pieces) {
+        block_select_runs<BLOCK>(least, NP, (uint32_t)a.P, sh, pivot, need);
+        limit = __uint_as_float(pivot);
+    }
+    uint32_t flags[NP], total;
+    auto flag = [&]() {                                           // which blocks, and the places of this thread's first in every piece
+        uint32_t word[3] = {0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            flags[u] = 0;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const float f = __uint_as_float(far[u][i]);      // (a block without an end: listed; a NaN is no block)
+                if (f - gap[u] <= limit || f == INFINITY) flags[u] |= 1u << i;
+            }
+            word[u / 3] |= (uint32_t)__popc(flags[u]) << (10 * (u % 3));
+        }
+        uint32_t inc[3];
+#pragma unroll
+        for (int w = 0; w < 3; ++w) inc[w] = wave_inclusive_scan(word[w]);   // (at most 64 * 8 of a piece: 10 bits)
+        if (lane == WAVE - 1) {
+#pragma unroll
+            for (int u = 0; u < NP; ++u) base[u * NW + wave] = inc[u / 3] >> (10 * (u % 3)) & 1023u;
+        }
+        __syncthreads();
+        const uint32_t in = lane < NW * NP ? base[lane] : 0u, all = wave_inclusive_scan(in);
+        total = (uint32_t)__builtin_amdgcn_readlane((int)all, WAVE - 1);
+        uint32_t at[NP];
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int from = u * NW + wave;                       // pieces are in order of u, then of the threads
+            at[u] = (uint32_t)__builtin_amdgcn_readlane((int)(all - in), from) + ((inc[u / 3] - word[u / 3]) >> (10 * (u % 3)) & 1023u);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NP; ++u) least[u] = at[u];
+    };
+    flag();
+    if (total > (uint32_t)a.cap && limit < INFINITY && limit > 0.f) {          // uniform
+        // bins of equal width up to the bound; its new value is the end of the bin that the P-th smallest falls into
+        const float per = 1024.f / limit;
+        for (int i = tid; i < 1024; i += BLOCK) sh.hist[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const float f = __uint_as_float(far[u][i]);
+                const int bin = (int)fminf(f * per, 1023.f);
+                if (f <= limit) atomicAdd(&sh.hist[bin], 1u);
+            }
+        __syncthreads();
+        constexpr int PER = 1024 / BLOCK;
+        uint32_t c[PER], s = 0, all;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) { c[j] = sh.hist[PER * tid + j]; s += c[j]; }
+        uint32_t cum = block_exclusive_scan<BLOCK>(s, sh.scan, all);
+        if (cum < (uint32_t)a.P && cum + s >= (uint32_t)a.P) {
+            int bin = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                if (cum < (uint32_t)a.P) bin = PER * tid + j;
+                cum += c[j];
+            }
+            sh.pick[0] = (uint32_t)bin;
+        }
+        __syncthreads();
+        limit = fminf(limit, (float)(sh.pick[0] + 1u) / per * (1.f + 0x1p-20f));
+        flag();
+    }
     if (total > (uint32_t)a.cap || !(ql.x < INFINITY)) {                       // uniform
         if (tid == 0) {
             a.n_flag[q] = 0;
@@ -322,27 +387,25 @@ __device__ __forceinline__ void flag_blocks_body(const SparseArgs &a, int64_t q,
         }
         return;
     }
-    uint32_t at = exc;
-    while (flags) {
-        put(at++, i0 + __builtin_ctz(flags));
-        flags &= flags - 1;
+    int32_t *list = a.blist + q * a.cap;
+    uint32_t *rank = a.rank + q * a.cap, *count = a.count + (q % N_XCD) * a.nb;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        uint32_t at = least[u];
+        while (flags[u]) {
+            const int b = 2 * TP * (tid + u * BLOCK) + __builtin_ctz(flags[u]);
+            list[at] = b;
+            rank[at++] = atomicAdd(&count[b], 1u);
+            flags[u] &= flags[u] - 1;
+        }
     }
     if (tid == 0) {
         a.n_flag[q] = total;
         const int shc = hi_scale(*a.cmax);
-        // d = |q|^2 - 2 G, and the lower end is one of G in the units of the product
-        const float two_g = __builtin_amdgcn_ldexpf(limit, 1 + SPARSE_HEADROOM - 2 * shc), n = a.qn[q];
+        const float two_g = __builtin_amdgcn_ldexpf(limit - q2, SPARSE_HEADROOM - 2 * shc), n = a.qn[q];
         const float d = n + two_g + 0x1p-21f * (n + fabsf(two_g));
         a.thr[q] = limit < INFINITY ? fmaxf(d, 0.f) : INFINITY;
     }
-}
-
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void flag_blocks_kernel(SparseArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
-    __shared__ SelectShared sh;
-    flag_blocks_body<BLOCK, false>(a, blockIdx.x, dyn, sh);
 }
 
 // ---- hard queries: block minima of their exact distances.  Loops over what there is, nearly always nothing ----
@@ -393,29 +456,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
+// flag_blocks_kernel for what hard_minima_kernel wrote: by the rule of probe_select_kernel, at most 2 P - 1 blocks
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void hard_flag_kernel(SparseArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
-    __shared__ SelectShared sh;
+    __shared__ SelectRegs<1024> sh;
+    constexpr int N = 16;
     const uint32_t n = a.total[0];
-    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int ipt = run_length<BLOCK>(a.nb), i0 = threadIdx.x * ipt;
+    for (uint32_t at = blockIdx.x; at < n; at += gridDim.x) {
         __syncthreads();
-        flag_blocks_body<BLOCK, true>(a, a.hard[i], dyn, sh);
+        const int64_t q = a.hard[at];
+        const float *row = a.best + q * 2 * a.half_ld;
+        uint32_t kv[N], pivot, need;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int b = j < ipt && i0 + j < a.nb ? i0 + j : 0;
+            const uint32_t key = float_key(row[(b & 1) * a.half_ld + (b >> 1)]);
+            kv[j] = j < ipt && i0 + j < a.nb ? key : NO_KEY;
+        }
+        block_select_runs<BLOCK>(kv, ipt, a.P < a.nb ? (uint32_t)a.P : (uint32_t)a.nb, sh, pivot, need);
+        int32_t *list = a.blist + q * a.cap;
+        uint32_t *rank = a.rank + q * a.cap, *count = a.count + (q % N_XCD) * a.nb;
+        const uint32_t total = block_emit_runs<BLOCK>(kv, ipt, pivot, (uint32_t)a.P, sh.scan, [&](uint32_t pos, int b, uint32_t) {
+            list[pos] = b;
+            rank[pos] = atomicAdd(&count[b], 1u);
+        });
+        if (threadIdx.x == 0) {
+            a.n_flag[q] = total;
+            a.thr[q] = a.nb < a.P ? INFINITY : key_float(pivot);
+        }
     }
 }
 
 // ---- pairs in the order of their buckets (blocks or regions) ----
 constexpr int PAIR_Q = 32;   // queries of a work item
 
-// First pair of every bucket and the work items.  The order of the buckets among each other does not matter: a workgroup
-// adds up its 1024 and takes room for them with one atomic.
+// A bucket's pairs are counted as N_XCD parts: workgroup q counts in part q % N_XCD, so that the counters that an XCD adds to stay
+// in its L2 (one part for all: 10 000 queries, 1024 blocks, 66 listed: 154 us for flag_blocks_kernel, 62 so).
+// First pair of every part of every bucket and the work items.  The order of the buckets among each other does not matter: a
+// workgroup adds up its 1024 and takes room for them with one atomic.
 __global__ __launch_bounds__(1024) void bucket_items_kernel(const uint32_t *__restrict__ count, int64_t n, uint32_t *__restrict__ total,
                                                             uint32_t *__restrict__ offset, uint4 *__restrict__ items)
 {
     __shared__ uint32_t scan[16], base[2];
     const int64_t b = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-    const uint32_t c = b < n ? count[b] : 0u, m = (c + PAIR_Q - 1) / PAIR_Q;
+    uint32_t part[N_XCD], c = 0;
+#pragma unroll
+    for (int x = 0; x < N_XCD; ++x) {
+        part[x] = b < n ? count[x * n + b] : 0u;
+        c += part[x];
+    }
+    const uint32_t m = (c + PAIR_Q - 1) / PAIR_Q;
     uint32_t pairs, work;
     const uint32_t at = block_exclusive_scan<1024>(c, scan, pairs), it = block_exclusive_scan<1024>(m, scan, work);
     if (threadIdx.x == 0) {
@@ -424,7 +516,12 @@ __global__ __launch_bounds__(1024) void bucket_items_kernel(const uint32_t *__re
     }
     __syncthreads();
     if (b >= n) return;
-    offset[b] = base[0] + at;
+    uint32_t first = base[0] + at;
+#pragma unroll
+    for (int x = 0; x < N_XCD; ++x) {
+        offset[x * n + b] = first;
+        first += part[x];
+    }
     for (uint32_t u = 0; u < m; ++u) {
         const uint32_t left = c - u * PAIR_Q;
         items[base[1] + it + u] = make_uint4((uint32_t)b, base[0] + at + u * PAIR_Q, left < PAIR_Q ? left : PAIR_Q, 0u);
@@ -433,7 +530,7 @@ __global__ __launch_bounds__(1024) void bucket_items_kernel(const uint32_t *__re
 
 // slot s of query q (n_flag[q] of them, or P where there is none) to its place
 __global__ __launch_bounds__(256) void place_pairs_kernel(const int32_t *__restrict__ bucket, const uint32_t *__restrict__ rank, int64_t nq, int width,
-                                                          int rank_ld, int shift, const uint32_t *__restrict__ n_flag,
+                                                          int64_t buckets, int rank_ld, int shift, const uint32_t *__restrict__ n_flag,
                                                           const uint32_t *__restrict__ offset, uint32_t *__restrict__ pairs)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -441,7 +538,7 @@ __global__ __launch_bounds__(256) void place_pairs_kernel(const int32_t *__restr
     const int64_t q = i / width;
     const int s = (int)(i - q * width);
     if (n_flag && (uint32_t)s >= n_flag[q]) return;
-    pairs[offset[bucket[i]] + rank[q * rank_ld + s]] = (uint32_t)q << shift | (uint32_t)s;
+    pairs[offset[(q % N_XCD) * buckets + bucket[i]] + rank[q * rank_ld + s]] = (uint32_t)q << shift | (uint32_t)s;
 }
 
 // A work item a wavefront: the exact distances of up to 32 queries to 64 rows of the table at a time, copied to LDS directly
@@ -500,6 +597,7 @@ __global__ __launch_bounds__(64) void pair_distance_kernel(SparseArgs a, const u
         } else {
             cn[lane] = bucket * BMW + lane < a.K ? a.cnorm[bucket * BMW + lane] : 0.f;
         }
+        const uint32_t tf = REGION ? 0u : float_key(a.thr[q]);
         const float pd = REGION ? a.probe_d[q * a.P + (pair & (uint32_t)mask)] : 0.f;
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         wave_sync();
@@ -540,95 +638,121 @@ __global__ __launch_bounds__(64) void pair_distance_kernel(SparseArgs a, const u
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const float d = fmaxf(fmaf(m2, acc[j][4 * g + u], qr + ce[u]), 0.f);
-                    r[u] = REGION ? __uint_as_float(float_key(fmaf(al, d, fmaf(1.f - al, pd, se[u])))) : d;
+                    if (REGION) r[u] = __uint_as_float(float_key(fmaf(al, d, fmaf(1.f - al, pd, se[u]))));
+                    else r[u] = __uint_as_float(bucket * BMW + cl + u < a.K ? float_key(d) : NO_KEY);
                 }
                 *reinterpret_cast<float4 *>(&rows[l32 * OLD + cl]) = make_float4(r[0], r[1], r[2], r[3]);
             }
         wave_sync();
+        uint4 head = make_uint4(0u, 0u, 0u, 0u);                           // of query `lane`
         for (int i = 0; i < n; ++i) {
             const uint32_t pr = (uint32_t)__builtin_amdgcn_readlane((int)pair, i);
             const int64_t qi = pr >> a.shift, s = pr & (uint32_t)mask;
-            const float v = rows[i * OLD + lane];
+            const uint32_t key = __float_as_uint(rows[i * OLD + lane]);
             if (REGION) {
-                if (lane < nl) a.keys[(qi * a.P + s) * a.L + l0 + lane] = __float_as_uint(v);
+                if (lane < nl) a.keys[(qi * a.P + s) * a.L + l0 + lane] = key;
             } else {
-                a.cand[(qi * a.cap + s) * BMW + lane] = v;
+                const uint64_t m = __ballot(key <= (uint32_t)__builtin_amdgcn_readlane((int)tf, i));
+                const int first = m ? __builtin_ctzll(m) : 0;
+                if (lane == i) {
+                    head.x = (uint32_t)__popcll(m);
+                    head.z = (uint32_t)(bucket * BMW + first);
+                }
+                const uint32_t kf = (uint32_t)__builtin_amdgcn_readlane((int)key, first);
+                head.y = lane == i ? kf : head.y;
+                if (m & (m - 1)) a.cand[(qi * a.cap + s) * BMW + lane] = key;   // (uniform; one is usual)
             }
         }
+        if (!REGION && lane < n) a.head[q * a.cap + (pair & (uint32_t)mask)] = head;
         wave_sync();
     }
 }
 
-// The P closest of the distances of a query's flagged blocks by (distance, id), ascending in id: the second half of
-// probe_select_lds_body.  Dynamic LDS: cap + 2 PICK_CAP words.
-constexpr int PICK_CAP = 2048;
+// The P closest of the distances of a query's flagged blocks by (distance, id), ascending in id.  A thread takes two blocks,
+// nearly all of which have one distance that matters; the others' rows are read by a wavefront each.  (All rows read and filtered
+// here, 16 a wavefront at a time: 440 us for 10 000 queries and P = 256, 130 so.)  Dynamic LDS: 2 PICK_CAP words.
+constexpr int PICK_CAP = 2048, PICK_BLOCK = 256;
 
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void probe_pick_kernel(SparseArgs a)
+__global__ __launch_bounds__(PICK_BLOCK) void probe_pick_kernel(SparseArgs a)
 {
-    __shared__ SelectShared sh;
+    constexpr int BLOCK = PICK_BLOCK;
+    __shared__ SelectRegs<1024> sh;
+    __shared__ uint2 more[2 * BLOCK];                                       // blocks with several: slot, first place
+    __shared__ uint32_t n_more;
+    SelectShared &sh_mem = *reinterpret_cast<SelectShared *>(&sh);          // (only where more survive than fit)
+    static_assert(sizeof(SelectShared) <= sizeof(sh), "the same place");
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
-    int32_t *blist = reinterpret_cast<int32_t *>(dyn);
-    uint32_t *sk = dyn + a.cap;
-    int32_t *si = reinterpret_cast<int32_t *>(dyn + a.cap + PICK_CAP);
+    uint32_t *sk = dyn;
+    int32_t *si = reinterpret_cast<int32_t *>(dyn + PICK_CAP);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, P = a.P;
     const int64_t q = blockIdx.x;
     const int n = (int)a.n_flag[q];
-    const float *cand = a.cand + q * a.cap * BMW;
-    for (int i = tid; i < n; i += BLOCK) blist[i] = a.blist[q * a.cap + i];
+    const uint4 *head = a.head + q * a.cap;
+    const uint32_t *cand = a.cand + q * a.cap * BMW;
     const uint32_t tf = float_key(a.thr[q]);
-    __syncthreads();
     auto put = [&](uint32_t pos, int32_t id, uint32_t key) {
         a.probe_id[q * P + pos] = id;
         a.probe_d[q * P + pos] = key_float(key);
-        a.rank[q * a.cap + pos] = atomicAdd(&a.count[a.nb + id], 1u);
+        a.rank[q * a.cap + pos] = atomicAdd(&a.region_count[(q % N_XCD) * a.K + id], 1u);
     };
-    constexpr int CB = 16;
-    uint32_t total = 0;
-    bool overflow = false;
-    for (int b0 = 0; b0 < n; b0 += CB * (BLOCK / WAVE)) {                  // uniform
-        uint32_t kv[CB];
+    uint4 h[2];
 #pragma unroll
-        for (int j = 0; j < CB; ++j) {
-            const int bi = b0 + wave * CB + j;
-            uint32_t k = 0xFFFFFFFFu;
-            if (bi < n && (int64_t)blist[bi] * BMW + lane < a.K) k = float_key(cand[bi * BMW + lane]);
-            kv[j] = k;
-        }
-        uint32_t wcnt = 0;
+    for (int u = 0; u < 2; ++u) h[u] = head[2 * tid + u < n ? 2 * tid + u : 0];
+    if (tid == 0) n_more = 0;
 #pragma unroll
-        for (int j = 0; j < CB; ++j) wcnt += (uint32_t)__popcll(__ballot(kv[j] <= tf && kv[j] != 0xFFFFFFFFu));
-        uint32_t round_total;
-        const uint32_t exc = block_exclusive_scan<BLOCK>(lane == 0 ? wcnt : 0u, sh.scan, round_total);
-        if (total + round_total > (uint32_t)PICK_CAP) { overflow = true; break; }   // uniform
-        uint32_t at = total + (uint32_t)__builtin_amdgcn_readfirstlane((int)exc);
-#pragma unroll
-        for (int j = 0; j < CB; ++j) {
-            const bool sel = kv[j] <= tf && kv[j] != 0xFFFFFFFFu;
-            const uint64_t m = __ballot(sel);
-            if (sel) {
-                const uint32_t o = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                sk[o] = kv[j];
-                si[o] = blist[b0 + wave * CB + j] * BMW + lane;
-            }
-            at += (uint32_t)__popcll(m);
-        }
-        total += round_total;
-    }
+    for (int u = 0; u < 2; ++u) h[u].x = 2 * tid + u < n ? h[u].x : 0u;
+    uint32_t total;
+    uint32_t at = block_exclusive_scan<BLOCK>(h[0].x + h[1].x, sh.scan, total);
     uint32_t pivot, need;
-    if (overflow || total < (uint32_t)P) {                                  // uniform; the second cannot happen
+    if (total > (uint32_t)PICK_CAP || total < (uint32_t)P) {                // uniform; the second cannot happen
         const int64_t nc = (int64_t)n * BMW;
         __syncthreads();
-        auto key = [&](int64_t v) { return (int64_t)blist[v >> 6] * BMW + (v & 63) < a.K ? float_key(cand[v]) : 0xFFFFFFFFu; };
-        block_radix_select<BLOCK>(key, nc, (uint32_t)P, sh, pivot, need);
-        block_emit_selected<BLOCK>(key, nc, (uint32_t)P, pivot, need, sh,
-                                   [&](uint32_t pos, int64_t v, uint32_t k) { put(pos, blist[v >> 6] * BMW + (int)(v & 63), k); });
+        auto key = [&](int64_t v) {
+            const uint4 w = head[v >> 6];
+            return w.x == 0 ? NO_KEY : w.x > 1 ? cand[v] : (w.z & 63u) == (uint32_t)(v & 63) ? w.y : NO_KEY;
+        };
+        block_radix_select<BLOCK>(key, nc, (uint32_t)P, sh_mem, pivot, need);
+        block_emit_selected<BLOCK>(key, nc, (uint32_t)P, pivot, need, sh_mem,
+                                   [&](uint32_t pos, int64_t v, uint32_t k) { put(pos, a.blist[q * a.cap + (v >> 6)] * BMW + (int)(v & 63), k); });
         return;
     }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        if (h[u].x == 1) {
+            sk[at] = h[u].y;
+            si[at] = (int32_t)h[u].z;
+        } else if (h[u].x > 1) {
+            more[atomicAdd(&n_more, 1u)] = make_uint2((uint32_t)(2 * tid + u), at);
+        }
+        at += h[u].x;
+    }
     __syncthreads();
-    block_radix_select<BLOCK>([sk](int64_t i) { return sk[i]; }, (int64_t)total, (uint32_t)P, sh, pivot, need);
-    static_assert(PICK_CAP <= 16 * BLOCK, "items per thread of the ordered emit");
-    block_emit_selected_runs<BLOCK, (PICK_CAP + 4 * BLOCK - 1) / (4 * BLOCK)>(sk, (int)total, pivot, need, sh, [&](uint32_t pos, int64_t i, uint32_t k) { put(pos, si[i], k); });
+    const int nm = (int)n_more;
+    for (int m0 = wave * 4; m0 < nm; m0 += BLOCK / WAVE * 4) {              // four rows on their way at a time
+        uint2 w[4];
+        uint32_t key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            w[u] = more[m0 + u < nm ? m0 + u : m0];
+            key[u] = cand[(int64_t)w[u].x * BMW + lane];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint64_t m = m0 + u < nm ? __ballot(key[u] <= tf) : 0ull;
+            if (m >> lane & 1u) {
+                const uint32_t o = w[u].y + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                sk[o] = key[u];
+                si[o] = a.blist[q * a.cap + w[u].x] * BMW + lane;
+            }
+        }
+    }
+    __syncthreads();
+    static_assert(PICK_CAP <= 8 * BLOCK, "items of a thread");
+    uint32_t kv[8];
+    const int ipt = run_length<BLOCK>((int)total);
+    load_run<BLOCK>(sk, (int)total, kv, [](uint32_t w) { return w; });
+    block_select_runs<BLOCK>(kv, ipt, (uint32_t)P, sh, pivot, need);
+    block_emit_runs<BLOCK>(kv, ipt, pivot, need, sh.scan, [&](uint32_t pos, int i, uint32_t k) { put(pos, si[i], k); });
 }
 
 }  // namespace ivf

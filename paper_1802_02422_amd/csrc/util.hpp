@@ -98,6 +98,26 @@ __device__ __forceinline__ float wave_smallest(float v)
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), WAVE - 1));
 }
 
+// Smallest and largest word over the wave, for every lane.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_word_or_self(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+
+template <bool LARGEST>
+__device__ __forceinline__ uint32_t wave_extreme(uint32_t v)
+{
+    auto of = [](uint32_t a, uint32_t b) { return (LARGEST ? a > b : a < b) ? a : b; };
+    v = of(v, dpp_word_or_self<0x111, 0xf>(v));
+    v = of(v, dpp_word_or_self<0x112, 0xf>(v));
+    v = of(v, dpp_word_or_self<0x114, 0xf>(v));
+    v = of(v, dpp_word_or_self<0x118, 0xf>(v));
+    v = of(v, dpp_word_or_self<0x142, 0xa>(v));
+    v = of(v, dpp_word_or_self<0x143, 0xc>(v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
+}
+
 // argmin over the wave of (value, index) pairs, lowest index on equal values;
 // every lane receives the winner.
 __device__ __forceinline__ void wave_argmin(float &v, int &idx)
