@@ -22,6 +22,7 @@
 #include "encode.hpp"
 #include "latency.hpp"
 #include "layout.hpp"
+#include "order.hpp"
 #include "pool.hpp"
 #include "pq.hpp"
 #include "query.hpp"
@@ -404,11 +405,12 @@ struct ivf_index {
     float *centroids = nullptr, *cnorm = nullptr, *alpha = nullptr, *cst = nullptr;
     _Float16 *cpk = nullptr;     // centroids packed for the GEMM
     // for the search without the distance matrix (NULL: not built): fp16 rows and their lengths, start values and bounds of the
-    // tiles, squared norms of the neighbours, in one allocation
+    // tiles, squared norms of the neighbours, the order of the regions, in one allocation
     _Float16 *chi = nullptr;
     float2 *clen = nullptr;
     float *mstart = nullptr, *nbr_norm = nullptr;
     float4 *mtile = nullptr;
+    uint32_t *order = nullptr, *order_inv = nullptr;   // regions with common neighbours side by side (order.hpp)
     float *csi = nullptr;        // csi[0] inverse scale of the packed centroids; csi[1] reduction word
     float *codebook = nullptr, *const_table = nullptr;
     float *rot_t = nullptr;      // transposed rotation in front of the PQ, or NULL
@@ -460,6 +462,91 @@ extern "C" int ivf_set_scratch_limit(ivf_index *ix, int64_t bytes)
 
 namespace {
 
+inline unsigned grid_for(int64_t n, int block = 256) { return (unsigned)((n + block - 1) / block); }
+
+// Stable sort of n (key, value) pairs by the low `bits` bits of the key, ascending: one
+// least-significant-digit pass per 8 bits.  vals_in == NULL: the values are the positions 0..n-1.
+// The sorted pairs end up in *keys_sorted / *vals_sorted, which point into the caller's two pairs
+// of buffers (a: first, b: second; keys_in may be the a buffer).  hist: 256 * nblocks words,
+// scan_tmp: temporary of rocprim's scan (scan_bytes).
+struct RadixBufs {
+    DevTmp ka, kb, va, vb, hist, base, scan;
+    size_t scan_bytes = 0;
+    int64_t nblocks = 0, cap = 0;
+    int init(int64_t n)
+    {
+        cap = n;
+        nblocks = (n + RS_TILE - 1) / RS_TILE;
+        if (nblocks < 1) nblocks = 1;
+        const size_t nb = (size_t)(n > 0 ? n : 1) * sizeof(uint32_t);
+        HIPCHK(ka.alloc(nb));
+        HIPCHK(kb.alloc(nb));
+        HIPCHK(va.alloc(nb));
+        HIPCHK(vb.alloc(nb));
+        HIPCHK(hist.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
+        HIPCHK(base.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
+        HIPCHK(rocprim::exclusive_scan(nullptr, scan_bytes, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p),
+                                       0u, (size_t)256 * nblocks, rocprim::plus<uint32_t>(), nullptr));
+        HIPCHK(scan.alloc(scan_bytes ? scan_bytes : 16));
+        return IVF_OK;
+    }
+    uint32_t *keys_a() { return static_cast<uint32_t *>(ka.p); }
+    // Sorts the n keys held in the a buffer (values: positions, or the a value buffer when
+    // have_vals).  Returns the buffers that hold the result.
+    int sort(int64_t n, int bits, bool have_vals, uint32_t **keys_sorted, uint32_t **vals_sorted, hipStream_t st)
+    {
+        if (n > cap) return fail(IVF_EINVAL, "radix sort buffers too small");
+        uint32_t *kin = static_cast<uint32_t *>(ka.p), *kout = static_cast<uint32_t *>(kb.p);
+        uint32_t *vin = static_cast<uint32_t *>(va.p), *vout = static_cast<uint32_t *>(vb.p);
+        const int64_t nbk = (n + RS_TILE - 1) / RS_TILE > 0 ? (n + RS_TILE - 1) / RS_TILE : 1;
+        bool first = !have_vals;
+        if (bits < 1) bits = 1;
+        for (int shift = 0; shift < bits; shift += 8) {
+            radix_hist_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(kin, n, shift, static_cast<uint32_t *>(hist.p), nbk);
+            LAUNCHCHK("radix_hist_kernel");
+            size_t sb = scan_bytes;
+            HIPCHK(rocprim::exclusive_scan(scan.p, sb, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p), 0u,
+                                           (size_t)256 * nbk, rocprim::plus<uint32_t>(), st));
+            radix_scatter_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(
+                kin, first ? nullptr : vin, n, shift, static_cast<uint32_t *>(base.p), nbk, kout, vout);
+            LAUNCHCHK("radix_scatter_kernel");
+            first = false;
+            std::swap(kin, kout);
+            std::swap(vin, vout);
+        }
+        *keys_sorted = kin;
+        *vals_sorted = vin;
+        return IVF_OK;
+    }
+};
+
+int bits_for(int64_t nbuckets)
+{
+    int b = 1;
+    while (b < 32 && (1ll << b) < nbuckets) ++b;
+    return b;
+}
+
+// order[p] = the region at place p of an order that puts regions with common neighbours together (order.hpp), inv its
+// inverse (NULL: not wanted); order ends up in rb's buffers, which have room for K pairs.
+int launch_region_order(const int32_t *nbr, int64_t K, int L, RadixBufs &rb, uint32_t *first, const uint32_t **order, uint32_t *inv, hipStream_t st)
+{
+    const dim3 grid((unsigned)((K * 16 + 255) / 256));
+    shingle_kernel<true><<<grid, dim3(256), 0, st>>>(nbr, K, L, nullptr, first);
+    LAUNCHCHK("shingle_kernel");
+    shingle_kernel<false><<<grid, dim3(256), 0, st>>>(nbr, K, L, first, rb.keys_a());
+    LAUNCHCHK("shingle_kernel");
+    uint32_t *keys, *vals;
+    int rc;
+    if ((rc = rb.sort(K, SHINGLE_BITS, false, &keys, &vals, st))) return rc;
+    *order = vals;
+    if (inv) {
+        inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(vals, K, inv);
+        LAUNCHCHK("inverse_kernel");
+    }
+    return IVF_OK;
+}
+
 template <class T>
 int dev_copy(T *&dst, const T *src, size_t count, hipStream_t st)
 {
@@ -506,6 +593,8 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
             place(ix->mstart, (size_t)tiles * GT);
             place(ix->mtile, (size_t)tiles);
             place(ix->nbr_norm, (size_t)nsub);
+            place(ix->order, (size_t)K);
+            place(ix->order_inv, (size_t)K);
             return total;
         };
         const hipError_t e = g_pool.fresh(reinterpret_cast<void **>(&ix->chi), all());
@@ -523,6 +612,14 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
         LAUNCHCHK("minima_tiles_kernel");
         neighbour_norm_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->nbr, nsub, ix->cnorm, ix->nbr_norm);
         LAUNCHCHK("neighbour_norm_kernel");
+        RadixBufs rb;
+        StreamWait before_they_go(st);
+        if ((rc = rb.init(K))) return rc;
+        const uint32_t *order;
+        if ((rc = launch_region_order(ix->nbr, K, L, rb, ix->order_inv, &order, nullptr, st))) return rc;
+        HIPCHK(hipMemcpyAsync(ix->order, order, (size_t)K * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+        inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(ix->order, K, ix->order_inv);
+        LAUNCHCHK("inverse_kernel");
     }
     HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->cst), (size_t)nsub * sizeof(float)));
     cst_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->alpha, d->cs_dist2, L, nsub, ix->cst);
@@ -748,6 +845,7 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     a.nbr_norm = ix->nbr_norm;
     a.cst = ix->cst;
     a.alpha = ix->alpha;
+    a.order_inv = ix->order_inv;
 
     const int64_t pad = packed_rows(n);
     const unsigned rows_grid = (unsigned)(pad / 4), zero_grid = (unsigned)((sp.count_words + 2047) / 2048);
@@ -783,32 +881,35 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     if (wide) hard_flag_kernel<1024><<<dim3(512), dim3(1024), 0, st>>>(a);
     else hard_flag_kernel<256><<<dim3(1024), dim3(256), 0, st>>>(a);
     LAUNCHCHK("hard_flag_kernel");
-    auto grouped = [&](uint32_t *count, int64_t buckets, uint32_t *total, const int32_t *bucket, int width, const uint32_t *n_flag) -> int {
-        bucket_items_kernel<<<dim3((unsigned)((buckets + 1023) / 1024)), dim3(1024), 0, st>>>(count, buckets, total, a.offset, a.items);
+    auto grouped = [&](uint32_t *count, int64_t buckets, uint32_t *total, const int32_t *bucket, int width, const uint32_t *n_flag,
+                       const uint32_t *order, const uint32_t *inv) -> int {
+        bucket_items_kernel<<<dim3((unsigned)((buckets + 1023) / 1024)), dim3(1024), 0, st>>>(count, buckets, total, a.offset, order, a.items);
         LAUNCHCHK("bucket_items_kernel");
-        place_pairs_kernel<<<dim3((unsigned)((n * width + 255) / 256)), dim3(256), 0, st>>>(bucket, a.rank, n, width, buckets, sp.cap, sp.shift, n_flag, a.offset, a.pairs);
+        place_pairs_kernel<<<dim3((unsigned)((n * width + 255) / 256)), dim3(256), 0, st>>>(bucket, a.rank, n, width, buckets, sp.cap, sp.shift, n_flag, inv, a.offset, a.pairs);
         LAUNCHCHK("place_pairs_kernel");
         return IVF_OK;
     };
-    if ((rc = grouped(a.count, nb, a.total + 1, a.blist, sp.cap, a.n_flag))) return rc;
-#define IVF_PAIRS(REGION, N, TOTAL)                                                                                             \
-    do {                                                                                                                       \
-        const dim3 g_((unsigned)(N));                                                                                            \
-        if (Dp == 32) pair_distance_kernel<2, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                       \
-        else if (Dp == 64) pair_distance_kernel<4, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                  \
-        else if (Dp == 96) pair_distance_kernel<6, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                  \
-        else pair_distance_kernel<8, REGION><<<g_, dim3(64), 0, st>>>(a, TOTAL);                                                \
-        LAUNCHCHK("pair_distance_kernel");                                                                                     \
-    } while (0)
-    IVF_PAIRS(false, sp.block_items, a.total + 2);
+    if ((rc = grouped(a.count, nb, a.total + 1, a.blist, sp.cap, a.n_flag, nullptr, nullptr))) return rc;
+    const int chunks = (L + BMW - 1) / BMW;
+    auto pairs = [&](auto region, int64_t items, const uint32_t *total) -> int {
+        constexpr bool REGION = decltype(region)::value;
+        const int c = REGION ? chunks : 1;
+        auto kernel = [&](auto whole) {
+            constexpr bool W = decltype(whole)::value;
+            return Dp == 32 ? &pair_distance_kernel<2, REGION, W> : Dp == 64 ? &pair_distance_kernel<4, REGION, W> : Dp == 96 ? &pair_distance_kernel<6, REGION, W> : &pair_distance_kernel<8, REGION, W>;
+        };
+        (!REGION || L % BMW == 0 ? kernel(std::true_type()) : kernel(std::bool_constant<!REGION>()))<<<dim3(pair_grid(items, c)), dim3(64), 0, st>>>(a, total, c);
+        LAUNCHCHK("pair_distance_kernel");
+        return IVF_OK;
+    };
+    if ((rc = pairs(std::false_type(), sp.block_items, a.total + 2))) return rc;
     if ((rc = mark(1))) return rc;
     static_assert(2 * PICK_BLOCK >= 2 * PS_P_MAX, "two of a query's blocks a thread");
     probe_pick_kernel<<<dim3((unsigned)n), dim3(PICK_BLOCK), 2 * PICK_CAP * sizeof(uint32_t), st>>>(a);
     LAUNCHCHK("probe_pick_kernel");
     if ((rc = mark(2))) return rc;
-    if ((rc = grouped(a.region_count, K, a.total + 3, pid, P, nullptr))) return rc;
-    IVF_PAIRS(true, sp.region_items, a.total + 4);
-#undef IVF_PAIRS
+    if ((rc = grouped(a.region_count, K, a.total + 3, pid, P, nullptr, ix->order, ix->order_inv))) return rc;
+    if ((rc = pairs(std::true_type(), sp.region_items, a.total + 4))) return rc;
     return IVF_OK;
 }
 
@@ -954,9 +1055,6 @@ int scratch_of_current_device(unsigned char **out)
 // D = 128, where the sweep has two wavefronts a SIMD, K = 65 536, P = 64, 4096 857 / 907, 10 000 1858 / 1546.
 bool sparse_pays(int64_t K, int D, int P, int64_t nq)
 {
-#ifdef IVF_PROBE_SPARSE
-    return IVF_PROBE_SPARSE;
-#endif
     const int64_t pairs = (int64_t)P << (packed_dim(D) <= 96 ? 22 : 23);
     return K >= 1024 * (int64_t)P && nq * K >= (pairs > (1ll << 27) ? pairs : 1ll << 27);
 }
@@ -1484,75 +1582,6 @@ extern "C" int ivf_coarse_topk(const float *centroids, int64_t K, int D, const f
     g_err = keep;
     return rc;
 }
-
-namespace {
-
-inline unsigned grid_for(int64_t n, int block = 256) { return (unsigned)((n + block - 1) / block); }
-
-// Stable sort of n (key, value) pairs by the low `bits` bits of the key, ascending: one
-// least-significant-digit pass per 8 bits.  vals_in == NULL: the values are the positions 0..n-1.
-// The sorted pairs end up in *keys_sorted / *vals_sorted, which point into the caller's two pairs
-// of buffers (a: first, b: second; keys_in may be the a buffer).  hist: 256 * nblocks words,
-// scan_tmp: temporary of rocprim's scan (scan_bytes).
-struct RadixBufs {
-    DevTmp ka, kb, va, vb, hist, base, scan;
-    size_t scan_bytes = 0;
-    int64_t nblocks = 0, cap = 0;
-    int init(int64_t n)
-    {
-        cap = n;
-        nblocks = (n + RS_TILE - 1) / RS_TILE;
-        if (nblocks < 1) nblocks = 1;
-        const size_t nb = (size_t)(n > 0 ? n : 1) * sizeof(uint32_t);
-        HIPCHK(ka.alloc(nb));
-        HIPCHK(kb.alloc(nb));
-        HIPCHK(va.alloc(nb));
-        HIPCHK(vb.alloc(nb));
-        HIPCHK(hist.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
-        HIPCHK(base.alloc((size_t)256 * nblocks * sizeof(uint32_t)));
-        HIPCHK(rocprim::exclusive_scan(nullptr, scan_bytes, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p),
-                                       0u, (size_t)256 * nblocks, rocprim::plus<uint32_t>(), nullptr));
-        HIPCHK(scan.alloc(scan_bytes ? scan_bytes : 16));
-        return IVF_OK;
-    }
-    uint32_t *keys_a() { return static_cast<uint32_t *>(ka.p); }
-    // Sorts the n keys held in the a buffer (values: positions, or the a value buffer when
-    // have_vals).  Returns the buffers that hold the result.
-    int sort(int64_t n, int bits, bool have_vals, uint32_t **keys_sorted, uint32_t **vals_sorted, hipStream_t st)
-    {
-        if (n > cap) return fail(IVF_EINVAL, "radix sort buffers too small");
-        uint32_t *kin = static_cast<uint32_t *>(ka.p), *kout = static_cast<uint32_t *>(kb.p);
-        uint32_t *vin = static_cast<uint32_t *>(va.p), *vout = static_cast<uint32_t *>(vb.p);
-        const int64_t nbk = (n + RS_TILE - 1) / RS_TILE > 0 ? (n + RS_TILE - 1) / RS_TILE : 1;
-        bool first = !have_vals;
-        if (bits < 1) bits = 1;
-        for (int shift = 0; shift < bits; shift += 8) {
-            radix_hist_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(kin, n, shift, static_cast<uint32_t *>(hist.p), nbk);
-            LAUNCHCHK("radix_hist_kernel");
-            size_t sb = scan_bytes;
-            HIPCHK(rocprim::exclusive_scan(scan.p, sb, static_cast<uint32_t *>(hist.p), static_cast<uint32_t *>(base.p), 0u,
-                                           (size_t)256 * nbk, rocprim::plus<uint32_t>(), st));
-            radix_scatter_kernel<<<dim3((unsigned)nbk), dim3(RS_BLOCK), 0, st>>>(
-                kin, first ? nullptr : vin, n, shift, static_cast<uint32_t *>(base.p), nbk, kout, vout);
-            LAUNCHCHK("radix_scatter_kernel");
-            first = false;
-            std::swap(kin, kout);
-            std::swap(vin, vout);
-        }
-        *keys_sorted = kin;
-        *vals_sorted = vin;
-        return IVF_OK;
-    }
-};
-
-int bits_for(int64_t nbuckets)
-{
-    int b = 1;
-    while (b < 32 && (1ll << b) < nbuckets) ++b;
-    return b;
-}
-
-}  // namespace
 
 namespace {
 

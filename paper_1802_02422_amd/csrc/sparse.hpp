@@ -239,6 +239,7 @@ struct SparseArgs {
     float *probe_d;
     const int32_t *nbr;
     const float *nbr_norm, *cst, *alpha;
+    const uint32_t *order_inv;                 // [K] a region's bucket: its place in the order of order.hpp
 };
 
 // Lists the blocks of 64 that can hold one of a query's P closest centroids: a block's smallest distance lies between two ends,
@@ -497,7 +498,7 @@ constexpr int PAIR_Q = 32;   // queries of a work item
 // First pair of every part of every bucket and the work items.  The order of the buckets among each other does not matter: a
 // workgroup adds up its 1024 and takes room for them with one atomic.
 __global__ __launch_bounds__(1024) void bucket_items_kernel(const uint32_t *__restrict__ count, int64_t n, uint32_t *__restrict__ total,
-                                                            uint32_t *__restrict__ offset, uint4 *__restrict__ items)
+                                                            uint32_t *__restrict__ offset, const uint32_t *__restrict__ order, uint4 *__restrict__ items)
 {
     __shared__ uint32_t scan[16], base[2];
     const int64_t b = (int64_t)blockIdx.x * 1024 + threadIdx.x;
@@ -522,149 +523,219 @@ __global__ __launch_bounds__(1024) void bucket_items_kernel(const uint32_t *__re
         offset[x * n + b] = first;
         first += part[x];
     }
+    const uint32_t name = order && c ? order[b] : (uint32_t)b;
     for (uint32_t u = 0; u < m; ++u) {
         const uint32_t left = c - u * PAIR_Q;
-        items[base[1] + it + u] = make_uint4((uint32_t)b, base[0] + at + u * PAIR_Q, left < PAIR_Q ? left : PAIR_Q, 0u);
+        items[base[1] + it + u] = make_uint4(name, base[0] + at + u * PAIR_Q, left < PAIR_Q ? left : PAIR_Q, 0u);
     }
 }
 
 // slot s of query q (n_flag[q] of them, or P where there is none) to its place
 __global__ __launch_bounds__(256) void place_pairs_kernel(const int32_t *__restrict__ bucket, const uint32_t *__restrict__ rank, int64_t nq, int width,
                                                           int64_t buckets, int rank_ld, int shift, const uint32_t *__restrict__ n_flag,
-                                                          const uint32_t *__restrict__ offset, uint32_t *__restrict__ pairs)
+                                                          const uint32_t *__restrict__ inv, const uint32_t *__restrict__ offset, uint32_t *__restrict__ pairs)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= nq * width) return;
     const int64_t q = i / width;
     const int s = (int)(i - q * width);
     if (n_flag && (uint32_t)s >= n_flag[q]) return;
-    pairs[offset[(q % N_XCD) * buckets + bucket[i]] + rank[q * rank_ld + s]] = (uint32_t)q << shift | (uint32_t)s;
+    const int64_t b = inv ? (int64_t)inv[bucket[i]] : (int64_t)bucket[i];
+    pairs[offset[(q % N_XCD) * buckets + b] + rank[q * rank_ld + s]] = (uint32_t)q << shift | (uint32_t)s;
 }
 
-// A work item a wavefront: the exact distances of up to 32 queries to 64 rows of the table at a time, copied to LDS directly
-// (a whole item's rows are on their way at once; six such workgroups a compute unit).  REGION: the rows are the neighbours of
+// The exact distances of up to 32 queries (a work item) to 64 rows of the table, a step.  REGION: the rows are neighbours of
 // region `bucket` and the result is the score of Eq. (7) as an ordered key; else they are the 64 centroids of a block.
-// Products and their order are those of gemm_tile.
-template <int STAGES, bool REGION>
-__global__ __launch_bounds__(64) void pair_distance_kernel(SparseArgs a, const uint32_t *__restrict__ n_items)
+// Products and their order are those of gemm_tile.  A wavefront takes PAIR_RUN steps in a row; rows are copied to LDS
+// directly, six such workgroups a compute unit.  While a step's results are written the rows of the next are on their way, and
+// before them the next one's pairs and neighbours, and before those the item after that: each depends on the one before, and
+// one step a workgroup waited 2 of its 4.7 us for them.  The results pass through LDS as they come, PAIR_OUT queries at a
+// time, and a lane a row makes distances of them for the queries there are (three of 32 for the regions of 10 000 queries on
+// 2^20).
+constexpr int PAIR_RUN = 8, PAIR_OUT = 8;
+
+inline unsigned pair_grid(int64_t items, int chunks)
+{
+    const int64_t share = (items + N_XCD - 1) / N_XCD * chunks;
+    return (unsigned)((share + PAIR_RUN - 1) / PAIR_RUN * N_XCD);
+}
+
+// WHOLE: every step has 64 rows (L a multiple of 64).
+template <int STAGES, bool REGION, bool WHOLE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_distance_kernel(SparseArgs a, const uint32_t *__restrict__ n_items, int chunks)
 {
     typedef const __attribute__((address_space(1))) void *gptr_t;
     typedef __attribute__((address_space(3))) void *lptr_t;
+    static_assert(STAGES % 2 == 0, "two stages at a time");
     constexpr int Dp = STAGES * DK;                                        // floats per row
     constexpr int OLD = BMW + 4;                                           // row stride of the results in LDS
-    constexpr int ROWS = STAGES * BMW * ROWF > PAIR_Q * OLD ? STAGES * BMW * ROWF : PAIR_Q * OLD;
-    __shared__ __attribute__((aligned(16))) float rows[ROWS];
-    __shared__ __attribute__((aligned(16))) float cn[BMW];
-    __shared__ __attribute__((aligned(16))) float cs[REGION ? BMW : 4];
-    if (blockIdx.x >= *n_items) return;
-    const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5;
-    const uint4 item = a.items[blockIdx.x];
-    const int n = (int)item.z, mask = (1 << a.shift) - 1;
-    const int64_t bucket = item.x;
-    const uint32_t pair = a.pairs[item.y + (l32 < n ? l32 : 0)];           // (columns past n: the first query again)
-    const int64_t q = pair >> a.shift;
+    __shared__ __attribute__((aligned(16))) float rows[STAGES * BMW * ROWF];
+    __shared__ __attribute__((aligned(16))) float out[PAIR_OUT * OLD];
+    // workgroup b runs on XCD b % N_XCD: an XCD takes items in a row, whose rows (those of a block; the neighbours that regions
+    // side by side have in common) it then finds in its L2
+    const uint32_t items = *n_items, share = (items + N_XCD - 1) / N_XCD;
+    const uint32_t i_end = (blockIdx.x % N_XCD + 1) * share < items ? (blockIdx.x % N_XCD + 1) * share : items;
+    const uint32_t begin = blockIdx.x % N_XCD * share * chunks + blockIdx.x / N_XCD * PAIR_RUN;
+    uint32_t end = i_end * chunks;
+    if (begin >= end) return;                                              // (also where blockIdx.x % N_XCD * share > items)
+    if (end - begin > (uint32_t)PAIR_RUN) end = begin + PAIR_RUN;
+    const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5, mask = (1 << a.shift) - 1;
     const int width = REGION ? a.L : BMW;
-    for (int l0 = 0; l0 < width; l0 += BMW) {
-        const int nl = width - l0 < BMW ? width - l0 : BMW;
-        int32_t my;
-        if (REGION) my = a.nbr[bucket * a.L + l0 + (lane < nl ? lane : 0)];
-        else my = (int32_t)(bucket * BMW) + lane;                          // (the packed table has whole tiles of rows)
-        const float *src[4];
-        const int f = (lane & 3) ^ ((lane >> 4) & 3);                      // chunk this slot holds
+    const float m2c = -2.f * a.csi[0];
+    struct Ids { uint32_t bucket; int n, l0, nl; uint32_t pair; int32_t row; };   // a step: all but pair and row uniform
+    struct Ops { float cn, cs, al, qr, si, pd; };                          // of row `lane`, of the region, of query l32
+    // (an index that the compiler does not know to be uniform: it would read the item into scalar registers, and wait for it, where it is
+    // asked for, and not where it is used)
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));
+    auto item_of = [&](uint32_t t) { return a.items[(t < end ? t : end - 1) / (uint32_t)chunks + zero]; };
+    auto ids_of = [&](uint32_t t, uint4 item) {
+        Ids s;
+        s.bucket = (uint32_t)__builtin_amdgcn_readfirstlane((int)item.x);
+        s.n = __builtin_amdgcn_readfirstlane((int)item.z);
+        s.l0 = (int)((t < end ? t : end - 1) % (uint32_t)chunks) * BMW;
+        s.nl = WHOLE || width - s.l0 > BMW ? BMW : width - s.l0;
+        s.pair = a.pairs[(uint32_t)__builtin_amdgcn_readfirstlane((int)item.y) + (l32 < s.n ? l32 : 0)];   // (columns past n: the first query again)
+        s.row = REGION ? a.nbr[(int64_t)s.bucket * a.L + s.l0 + (lane < s.nl ? lane : 0)] : (int32_t)(s.bucket * BMW) + lane;   // (the packed table has whole tiles of rows)
+        return s;
+    };
+    gu32x4 qf[STAGES][2];
+    const int f = (lane & 7) ^ (lane >> 3);                                // chunk of two stages that this lane copies
+    const float *src[8];                                                   // its rows of the step whose rows are copied, their query's row
+    const gu32x4 *qrow;
+    auto aim = [&](const Ids &s) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            src[g] = reinterpret_cast<const float *>(a.Cp) + (int64_t)__shfl(my, 16 * g + (lane >> 2), WAVE) * Dp + f * 4;
+        for (int g = 0; g < 8; ++g)
+            src[g] = reinterpret_cast<const float *>(a.Cp) + (int64_t)__shfl(s.row, 8 * g + (lane >> 3), WAVE) * Dp + f * 4;
+        qrow = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(a.Qp) + (int64_t)(s.pair >> a.shift) * Dp) + 2 * h;
+    };
+    // two stages, whole 128-byte lines of 8 rows a load: with a stage at a time (16 rows, half a line of each) the loads of the other
+    // halves waited for the lines, 2.41 ms for 10 000 queries on 2^20, P = 256, and 2.02 so
+    auto copy_stages = [&](const Ids &s, int c) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            if (16 * g < nl) {
-#pragma unroll
-                for (int s = 0; s < STAGES; ++s)
-                    __builtin_amdgcn_global_load_lds((gptr_t)(src[g] + s * DK), (lptr_t)(rows + s * (BMW * ROWF) + g * 256), 16, 0, 0);
-            }
-        gu32x4 qf[STAGES][2];
-        const gu32x4 *qrow = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(a.Qp) + q * Dp) + 2 * h;
-#pragma unroll
-        for (int s = 0; s < STAGES; ++s) {
-            qf[s][0] = qrow[s * 4 + 0];
-            qf[s][1] = qrow[s * 4 + 1];
+        for (int g = 0; g < 8; ++g)
+            if (WHOLE || 8 * g < s.nl) __builtin_amdgcn_global_load_lds((gptr_t)(src[g] + c * DK), (lptr_t)(rows + c * (BMW * ROWF) + g * 256), 16, 0, 0);
+    };
+    auto query_stage = [&](const Ids &s, int c) {
+        if (l32 < s.n) {                                                   // (columns past n: whatever is there, not stored)
+            qf[c][0] = qrow[c * 4 + 0];
+            qf[c][1] = qrow[c * 4 + 1];
         }
-        const float qr = a.qn[q], m2 = -2.f * a.csi[0] * a.qsi[q];
-        float al = 0.f;
+    };
+    auto operands = [&](const Ids &s) {
+        Ops o;
+        const int64_t q = s.pair >> a.shift;
+        o.qr = a.qn[q];
+        o.si = a.qsi[q];                                                   // (no arithmetic on them here: it would wait)
         if (REGION) {
-            al = a.alpha[bucket];
-            cn[lane] = lane < nl ? a.nbr_norm[bucket * a.L + l0 + lane] : 0.f;
-            cs[REGION ? lane : 0] = lane < nl ? a.cst[bucket * a.L + l0 + lane] : 0.f;
+            const int64_t at = (int64_t)s.bucket * a.L + s.l0 + (lane < s.nl ? lane : 0);
+            o.cn = a.nbr_norm[at];
+            o.cs = a.cst[at];
+            o.al = a.alpha[s.bucket + zero];
+            o.pd = a.probe_d[q * a.P + (s.pair & (uint32_t)mask)];
         } else {
-            cn[lane] = bucket * BMW + lane < a.K ? a.cnorm[bucket * BMW + lane] : 0.f;
+            const int64_t c = (int64_t)s.bucket * BMW + lane;
+            o.cn = a.cnorm[c < a.K ? c : a.K - 1];
+            o.cs = o.al = 0.f;
+            o.pd = a.thr[q];
         }
-        const uint32_t tf = REGION ? 0u : float_key(a.thr[q]);
-        const float pd = REGION ? a.probe_d[q * a.P + (pair & (uint32_t)mask)] : 0.f;
+        return o;
+    };
+    uint32_t t = begin;
+    Ids now = ids_of(t, item_of(t));
+    aim(now);
+#pragma unroll
+    for (int c = 0; c < STAGES; ++c) {
+        if (!(c & 1)) copy_stages(now, c);
+        qf[c][0] = qf[c][1] = gu32x4{0, 0, 0, 0};
+        query_stage(now, c);
+    }
+    Ops ops = operands(now);
+    Ids next = ids_of(t + 1, item_of(t + 1));
+    uint4 item = item_of(t + 2);
+    while (true) {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         wave_sync();
-        floatx16 acc[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-        const bool both = nl > 32;                                         // (uniform)
-#pragma unroll
-        for (int s = 0; s < STAGES; ++s) {
-            gu32x4 b[2][2];
+        const bool more = t + 1 < end;                                     // (uniform)
+        gu32x4 b[2][2][2];                                                 // of two stages
+        auto read_stage = [&](int c) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int r = j * 32 + l32;
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
-                    b[j][p] = *reinterpret_cast<const gu32x4 *>(&rows[s * (BMW * ROWF) + r * ROWF + (((2 * h + p) ^ ((r >> 2) & 3)) << 2)]);
+                    b[c & 1][j][p] = *reinterpret_cast<const gu32x4 *>(&rows[(c >> 1) * (2 * BMW * ROWF) + r * (2 * ROWF) + (((4 * (c & 1) + 2 * h + p) ^ (r & 7)) << 2)]);
             }
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                acc[0] = mfma3(b[0], qf[s], acc[0], e);
-                if (both) acc[1] = mfma3(b[1], qf[s], acc[1], e);
-            }
-        }
-        wave_sync();                                                       // the rows have been read: their place takes the results
+        };
+        read_stage(0);
+        floatx16 acc[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int cl = j * 32 + 8 * g + 4 * h;
-                const float4 cv = *reinterpret_cast<const float4 *>(&cn[cl]);
-                const float ce[4] = {cv.x, cv.y, cv.z, cv.w};
-                float4 sv = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (REGION) sv = *reinterpret_cast<const float4 *>(&cs[REGION ? cl : 0]);
-                const float se[4] = {sv.x, sv.y, sv.z, sv.w};
-                float r[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float d = fmaxf(fmaf(m2, acc[j][4 * g + u], qr + ce[u]), 0.f);
-                    if (REGION) r[u] = __uint_as_float(float_key(fmaf(al, d, fmaf(1.f - al, pd, se[u]))));
-                    else r[u] = __uint_as_float(bucket * BMW + cl + u < a.K ? float_key(d) : NO_KEY);
-                }
-                *reinterpret_cast<float4 *>(&rows[l32 * OLD + cl]) = make_float4(r[0], r[1], r[2], r[3]);
-            }
-        wave_sync();
-        uint4 head = make_uint4(0u, 0u, 0u, 0u);                           // of query `lane`
-        for (int i = 0; i < n; ++i) {
-            const uint32_t pr = (uint32_t)__builtin_amdgcn_readlane((int)pair, i);
-            const int64_t qi = pr >> a.shift, s = pr & (uint32_t)mask;
-            const uint32_t key = __float_as_uint(rows[i * OLD + lane]);
-            if (REGION) {
-                if (lane < nl) a.keys[(qi * a.P + s) * a.L + l0 + lane] = key;
-            } else {
-                const uint64_t m = __ballot(key <= (uint32_t)__builtin_amdgcn_readlane((int)tf, i));
-                const int first = m ? __builtin_ctzll(m) : 0;
-                if (lane == i) {
-                    head.x = (uint32_t)__popcll(m);
-                    head.z = (uint32_t)(bucket * BMW + first);
-                }
-                const uint32_t kf = (uint32_t)__builtin_amdgcn_readlane((int)key, first);
-                head.y = lane == i ? kf : head.y;
-                if (m & (m - 1)) a.cand[(qi * a.cap + s) * BMW + lane] = key;   // (uniform; one is usual)
-            }
+            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        const bool both = WHOLE || now.nl > 32;                                     // (uniform)
+        const Ids is = now;
+        const Ops o = ops;
+        if (more) {
+            aim(next);
+            ops = operands(next);
         }
-        if (!REGION && lane < n) a.head[q * a.cap + (pair & (uint32_t)mask)] = head;
-        wave_sync();
+#pragma unroll
+        for (int c = 0; c < STAGES; ++c) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // two stages' rows have been read: the next step's may come
+            if (more && (c & 1)) copy_stages(next, c - 1);
+            if (c + 1 < STAGES) read_stage(c + 1);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                acc[0] = mfma3(b[c & 1][0], qf[c], acc[0], e);
+                if (both) acc[1] = mfma3(b[c & 1][1], qf[c], acc[1], e);
+            }
+            if (more) query_stage(next, c);
+        }
+        if (more) {
+            now = next;
+            next = ids_of(t + 2, item);
+            item = item_of(t + 3);
+        }
+        uint4 head = make_uint4(0u, 0u, 0u, 0u);                           // of query `lane`
+        for (int i0 = 0; i0 < is.n; i0 += PAIR_OUT) {
+            if ((l32 & ~(PAIR_OUT - 1)) == i0) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<float4 *>(&out[(l32 & (PAIR_OUT - 1)) * OLD + j * 32 + 8 * g + 4 * h]) =
+                            make_float4(acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]);
+            }
+            wave_sync();
+            float v[PAIR_OUT];
+#pragma unroll
+            for (int u = 0; u < PAIR_OUT; ++u) v[u] = out[u * OLD + lane];
+#pragma unroll
+            for (int u = 0; u < PAIR_OUT; ++u) {
+                const int i = i0 + u;
+                if (i >= is.n) break;                                      // (uniform)
+                auto of = [&](float v) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), i)); };
+                const uint32_t pr = (uint32_t)__builtin_amdgcn_readlane((int)is.pair, i);
+                const int64_t qi = pr >> a.shift, s = pr & (uint32_t)mask;
+                const float d = fmaxf(fmaf(m2c * of(o.si), v[u], of(o.qr) + o.cn), 0.f), pd = of(o.pd);
+                if (REGION) {
+                    const uint32_t key = float_key(fmaf(o.al, d, fmaf(1.f - o.al, pd, o.cs)));
+                    if (lane < is.nl) a.keys[(qi * a.P + s) * a.L + is.l0 + lane] = key;
+                } else {
+                    const uint32_t key = (int64_t)is.bucket * BMW + lane < a.K ? float_key(d) : NO_KEY;
+                    const uint64_t m = __ballot(key <= float_key(pd));
+                    const int first = m ? __builtin_ctzll(m) : 0;
+                    const uint32_t kf = (uint32_t)__builtin_amdgcn_readlane((int)key, first);
+                    if (lane == i) head = make_uint4((uint32_t)__popcll(m), kf, is.bucket * BMW + (uint32_t)first, 0u);
+                    if (m & (m - 1)) a.cand[(qi * a.cap + s) * BMW + lane] = key;   // (uniform; one is usual)
+                }
+            }
+            wave_sync();                                                   // (read: the next queries' results may come)
+        }
+        if (!REGION && lane < is.n) a.head[(int64_t)(is.pair >> a.shift) * a.cap + (is.pair & (uint32_t)mask)] = head;
+        if (!more) break;
+        ++t;
     }
 }
 
@@ -693,7 +764,7 @@ __global__ __launch_bounds__(PICK_BLOCK) void probe_pick_kernel(SparseArgs a)
     auto put = [&](uint32_t pos, int32_t id, uint32_t key) {
         a.probe_id[q * P + pos] = id;
         a.probe_d[q * P + pos] = key_float(key);
-        a.rank[q * a.cap + pos] = atomicAdd(&a.region_count[(q % N_XCD) * a.K + id], 1u);
+        a.rank[q * a.cap + pos] = atomicAdd(&a.region_count[(q % N_XCD) * a.K + a.order_inv[id]], 1u);
     };
     uint4 h[2];
 #pragma unroll

@@ -27,7 +27,7 @@ def make(K, D, L, M, seed, spread, offset):
 # partial last tiles and blocks, every packed width, L below, at and above a group of 64 neighbours and of odd length; "hard": bounds
 # too wide for every query; "some": queries too large for the table's scale, without a finite length, zero, and equal to centroids
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
-    (16_400, 96, 64, 16, 16, 9000, "plain"), (16_385, 32, 7, 8, 13, 8500, "plain"), (20_033, 64, 65, 16, 16, 7001, "plain"),
+    (16_400, 96, 64, 16, 16, 9000, "plain"), (16_385, 32, 7, 8, 13, 8500, "plain"), (20_033, 64, 65, 16, 16, 7001, "plain"), (16_500, 32, 128, 8, 12, 8200, "plain"),
     (17_000, 128, 33, 16, 8, 9000, "plain"), (70_001, 48, 64, 8, 60, 4200, "plain"), (16_400, 96, 32, 16, 16, 8300, "hard"),
     (16_640, 96, 16, 16, 16, 8300, "some"), (16_400, 96, 16, 16, 16, 8300, "equal")])
 def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
