@@ -64,14 +64,10 @@ __host__ __device__ inline int64_t packed_rows(int64_t n) { return (n + 255) / 2
 // m is the row's largest magnitude, or the whole matrix's when gmax (the result
 // of absmax_kernel) is given.  Also writes ||row||^2 and 1/s (per row, or
 // inv_scale[0] for a matrix-wide scale).  One wavefront per row.
-__global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict__ X, int64_t n, int D,
-                                                         const uint32_t *__restrict__ gmax,
-                                                         _Float16 *__restrict__ P, float *__restrict__ norm,
-                                                         float *__restrict__ inv_scale)
+__device__ __forceinline__ void split_row(const float *__restrict__ X, int64_t row, int D, const uint32_t *__restrict__ gmax,
+                                          _Float16 *__restrict__ P, float *__restrict__ norm, float *__restrict__ inv_scale)
 {
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (row >= n) return;
     const int Dp = packed_dim(D);
     float s2 = 0.f, m = 0.f;
     for (int i = lane; i < D; i += WAVE) {
@@ -103,6 +99,15 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict
         if (!gmax) inv_scale[row] = ldexpf(1.f, e - 14);
         else if (row == 0) inv_scale[0] = ldexpf(1.f, e - 14);
     }
+}
+
+__global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict__ X, int64_t n, int D,
+                                                         const uint32_t *__restrict__ gmax,
+                                                         _Float16 *__restrict__ P, float *__restrict__ norm,
+                                                         float *__restrict__ inv_scale)
+{
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row < n) split_row(X, row, D, gmax, P, norm, inv_scale);
 }
 
 constexpr int GT = 128;        // tile: GT queries x GT centroids per workgroup

@@ -285,10 +285,17 @@ enum { WS_DT, WS_BM, WS_QN, WS_QSI, WS_QPK, WS_PID, WS_PD, WS_DESC, WS_LUT, WS_P
 enum { SP_QH, SP_QLEN, SP_BEST, SP_FLAG, SP_LIST, SP_RANK, SP_THR, SP_COUNT, SP_OFFSET, SP_HARD, SP_HROWS, SP_HN, SP_HSI, SP_PAIRS, SP_ITEMS,
        SP_HEAD, SP_BIG, SP_PIECES };   // SP_BIG: the distances of the flagged blocks, then the scores
 struct SparsePlan {
+    bool direct = false;         // a pair is a work item
     int cap = 0, shift = 0;
     int64_t block_items = 0, region_items = 0, count_words = 0;
     size_t off[SP_PIECES], total = 0;
 };
+
+// Queries up to which a pair is a work item of its own, instead of being grouped with the other queries' pairs of its block or region:
+// grouping takes four launches and counters for all regions.  A search in us grouped / so (the matrix where that is the faster), L = 64,
+// D = 96: K = 2^20, P = 16, 128 queries 188 / 132, 256 231 / 176, 512 317 / 269, 1024 496 / 468; P = 64, 256 323 / 279, 512 454 / 460;
+// P = 128, 256 445 / 409, 512 579 / 715; K = 262 144, P = 16, 256 140 / 115, 512 165 / 170.
+constexpr int64_t SPARSE_DIRECT = 256;
 
 // Whether an index gets the tables for it.
 bool sparse_table(int64_t K, int D) { return K >= SPARSE_MIN_K && (K + BMW - 1) / BMW <= PS_NB_MAX && packed_dim(D) <= 128; }
@@ -301,9 +308,10 @@ SparsePlan plan_sparse(int64_t K, int D, int P, int L, int64_t n)
     while ((1 << sp.shift) < 2 * P || sp.shift < 2) ++sp.shift;
     sp.cap = 1 << sp.shift;
     const int64_t bp = n * (sp.cap < nb ? sp.cap : nb), rp = n * P;
-    sp.block_items = bp / PAIR_Q + (bp < nb ? bp : nb);
-    sp.region_items = rp / PAIR_Q + (rp < K ? rp : K);
-    sp.count_words = (N_XCD * (nb + K) + 8) / 2;               // 64-bit words: counts of blocks and regions, totals
+    sp.direct = n <= SPARSE_DIRECT;
+    sp.block_items = sp.direct ? bp : bp / PAIR_Q + (bp < nb ? bp : nb);
+    sp.region_items = sp.direct ? rp : rp / PAIR_Q + (rp < K ? rp : K);
+    sp.count_words = ((sp.direct ? 0 : N_XCD * (nb + K)) + 8) / 2;   // 64-bit words: counts of blocks and regions, totals
     size_t bytes[SP_PIECES];
     bytes[SP_QH] = (size_t)pad * Dp * sizeof(_Float16);
     bytes[SP_QLEN] = (size_t)pad * sizeof(float2);
@@ -311,7 +319,7 @@ SparsePlan plan_sparse(int64_t K, int D, int P, int L, int64_t n)
     bytes[SP_FLAG] = bytes[SP_THR] = bytes[SP_HARD] = (size_t)n * 4;
     bytes[SP_LIST] = bytes[SP_RANK] = (size_t)n * sp.cap * 4;
     bytes[SP_COUNT] = (size_t)sp.count_words * 8;
-    bytes[SP_OFFSET] = (size_t)N_XCD * K * 4;
+    bytes[SP_OFFSET] = sp.direct ? 0 : (size_t)N_XCD * K * 4;
     bytes[SP_HROWS] = (size_t)pad * Dp * 2 * sizeof(_Float16);
     bytes[SP_HN] = bytes[SP_HSI] = (size_t)pad * sizeof(float);
     bytes[SP_PAIRS] = (size_t)n * sp.cap * 4;
@@ -324,6 +332,13 @@ SparsePlan plan_sparse(int64_t K, int D, int P, int L, int64_t n)
         sp.total += (bytes[i] + 255) / 256 * 256;
     }
     return sp;
+}
+
+// ... of a batch taken n at a time: the last pass may be a small one, of the other kind
+size_t sparse_bytes(int64_t K, int D, int P, int L, int64_t n)
+{
+    const size_t whole = plan_sparse(K, D, P, L, n).total, last = n > SPARSE_DIRECT ? plan_sparse(K, D, P, L, SPARSE_DIRECT).total : 0;
+    return whole > last ? whole : last;
 }
 
 struct SearchPlan {
@@ -527,23 +542,14 @@ int bits_for(int64_t nbuckets)
     return b;
 }
 
-// order[p] = the region at place p of an order that puts regions with common neighbours together (order.hpp), inv its
-// inverse (NULL: not wanted); order ends up in rb's buffers, which have room for K pairs.
-int launch_region_order(const int32_t *nbr, int64_t K, int L, RadixBufs &rb, uint32_t *first, const uint32_t **order, uint32_t *inv, hipStream_t st)
+// keys[r]: by which regions are sorted into the order of order.hpp; first: K words of scratch
+int launch_region_keys(const int32_t *nbr, int64_t K, int L, uint32_t *first, uint32_t *keys, hipStream_t st)
 {
     const dim3 grid((unsigned)((K * 16 + 255) / 256));
-    shingle_kernel<true><<<grid, dim3(256), 0, st>>>(nbr, K, L, nullptr, first);
+    shingle_kernel<true><<<grid, dim3(256), 0, st>>>(nbr, K, L, L, nullptr, first);
     LAUNCHCHK("shingle_kernel");
-    shingle_kernel<false><<<grid, dim3(256), 0, st>>>(nbr, K, L, first, rb.keys_a());
+    shingle_kernel<false><<<grid, dim3(256), 0, st>>>(nbr, K, L, L < 16 ? L : 16, first, keys);
     LAUNCHCHK("shingle_kernel");
-    uint32_t *keys, *vals;
-    int rc;
-    if ((rc = rb.sort(K, SHINGLE_BITS, false, &keys, &vals, st))) return rc;
-    *order = vals;
-    if (inv) {
-        inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(vals, K, inv);
-        LAUNCHCHK("inverse_kernel");
-    }
     return IVF_OK;
 }
 
@@ -615,8 +621,9 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
         RadixBufs rb;
         StreamWait before_they_go(st);
         if ((rc = rb.init(K))) return rc;
-        const uint32_t *order;
-        if ((rc = launch_region_order(ix->nbr, K, L, rb, ix->order_inv, &order, nullptr, st))) return rc;
+        uint32_t *keys, *order;
+        if ((rc = launch_region_keys(ix->nbr, K, L, ix->order_inv, rb.keys_a(), st))) return rc;
+        if ((rc = rb.sort(K, SHINGLE_BITS, false, &keys, &order, st))) return rc;
         HIPCHK(hipMemcpyAsync(ix->order, order, (size_t)K * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
         inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(ix->order, K, ix->order_inv);
         LAUNCHCHK("inverse_kernel");
@@ -820,8 +827,9 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     piece(a.head, SP_HEAD);
     piece(a.cand, SP_BIG);
     piece(a.keys, SP_BIG);
-    a.region_count = a.count + N_XCD * nb;
-    a.total = a.region_count + N_XCD * K;
+    a.direct = sp.direct;
+    a.region_count = sp.direct ? nullptr : a.count + N_XCD * nb;
+    a.total = sp.direct ? a.count : a.region_count + N_XCD * K;
     a.K = K;
     a.half_ld = minima_half(K);
     a.nb = nb;
@@ -849,7 +857,7 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
 
     const int64_t pad = packed_rows(n);
     const unsigned rows_grid = (unsigned)(pad / 4), zero_grid = (unsigned)((sp.count_words + 2047) / 2048);
-    sparse_queries_kernel<<<dim3(rows_grid + zero_grid), dim3(256), 0, st>>>(Q, n, pad, D, Dp, a.cmax, qh, qlen, rows_grid,
+    sparse_queries_kernel<<<dim3(rows_grid + zero_grid), dim3(256), 0, st>>>(Q, n, pad, D, Dp, a.cmax, ws.qpk, ws.qn, ws.qsi, qh, qlen, rows_grid,
                                                                             reinterpret_cast<unsigned long long *>(a.count), sp.count_words);
     LAUNCHCHK("sparse_queries_kernel");
     const int tiles_q = (int)((n + GT - 1) / GT), tiles_c = (int)((K + GT - 1) / GT);
@@ -874,8 +882,6 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     else if (tiles_c <= 4096) flag_blocks_kernel<512, 2, 4><<<gq, dim3(512), 0, st>>>(a);
     else flag_blocks_kernel<512, 4, 4><<<gq, dim3(512), 0, st>>>(a);
     LAUNCHCHK("flag_blocks_kernel");
-    hard_rows_kernel<<<dim3(256), dim3(256), 0, st>>>(a);
-    LAUNCHCHK("hard_rows_kernel");
     hard_minima_kernel<<<dim3(1024), dim3(256), 0, st>>>(a);
     LAUNCHCHK("hard_minima_kernel");
     if (wide) hard_flag_kernel<1024><<<dim3(512), dim3(1024), 0, st>>>(a);
@@ -889,16 +895,18 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
         LAUNCHCHK("place_pairs_kernel");
         return IVF_OK;
     };
-    if ((rc = grouped(a.count, nb, a.total + 1, a.blist, sp.cap, a.n_flag, nullptr, nullptr))) return rc;
+    if (!sp.direct && (rc = grouped(a.count, nb, a.total + 1, a.blist, sp.cap, a.n_flag, nullptr, nullptr))) return rc;
     const int chunks = (L + BMW - 1) / BMW;
     auto pairs = [&](auto region, int64_t items, const uint32_t *total) -> int {
         constexpr bool REGION = decltype(region)::value;
         const int c = REGION ? chunks : 1;
+        const int64_t each = items * c / 3072;                   // (1536 workgroups run at a time)
+        const int run = each < 1 ? 1 : each < PAIR_RUN ? (int)each : PAIR_RUN;
         auto kernel = [&](auto whole) {
             constexpr bool W = decltype(whole)::value;
             return Dp == 32 ? &pair_distance_kernel<2, REGION, W> : Dp == 64 ? &pair_distance_kernel<4, REGION, W> : Dp == 96 ? &pair_distance_kernel<6, REGION, W> : &pair_distance_kernel<8, REGION, W>;
         };
-        (!REGION || L % BMW == 0 ? kernel(std::true_type()) : kernel(std::bool_constant<!REGION>()))<<<dim3(pair_grid(items, c)), dim3(64), 0, st>>>(a, total, c);
+        (!REGION || L % BMW == 0 ? kernel(std::true_type()) : kernel(std::bool_constant<!REGION>()))<<<dim3(pair_grid(items, c, run)), dim3(64), 0, st>>>(a, total, c, run);
         LAUNCHCHK("pair_distance_kernel");
         return IVF_OK;
     };
@@ -908,7 +916,7 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     probe_pick_kernel<<<dim3((unsigned)n), dim3(PICK_BLOCK), 2 * PICK_CAP * sizeof(uint32_t), st>>>(a);
     LAUNCHCHK("probe_pick_kernel");
     if ((rc = mark(2))) return rc;
-    if ((rc = grouped(a.region_count, K, a.total + 3, pid, P, nullptr, ix->order, ix->order_inv))) return rc;
+    if (!sp.direct && (rc = grouped(a.region_count, K, a.total + 3, pid, P, nullptr, ix->order, ix->order_inv))) return rc;
     if ((rc = pairs(std::true_type(), sp.region_items, a.total + 4))) return rc;
     return IVF_OK;
 }
@@ -938,9 +946,10 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
             return IVF_OK;
         };
         if ((rc = mark(0))) return rc;
-        if ((rc = pack_rows(Q, n, D, nullptr, ws.qpk, ws.qn, ws.qsi, st))) return rc;
         if (pl.sparse) {
             if ((rc = launch_sparse(ix, Q, n, P, ws, pid, pd, mark, st))) return rc;
+        } else if ((rc = pack_rows(Q, n, D, nullptr, ws.qpk, ws.qn, ws.qsi, st))) {
+            return rc;
         } else if ((rc = launch_coarse(ws.qpk, ws.qn, ws.qsi, n, ix->cpk, ix->cnorm, ix->csi, K, Dp, ws.dt, ws.bm, st))) return rc;
         if (!pl.sparse && (rc = mark(1))) return rc;
         // Where both are workgroups of 1024 threads with their keys in LDS, the selection runs inside the
@@ -1053,10 +1062,20 @@ int scratch_of_current_device(unsigned char **out)
 // 2857 / 2325; P = 64, 512 330 / 294, 4096 1968 / 1291; K = 65 536, P = 64, 2048 482 / 501, 4096 830 / 748; P = 256 10 000
 // 3106 / 3327; P = 16, 1024 177 / 192, 2048 344 / 298; K = 32 768, P = 16, 1024 137 / 182, 4096 454 / 424; P = 64, 4096 607 / 645;
 // D = 128, where the sweep has two wavefronts a SIMD, K = 65 536, P = 64, 4096 857 / 907, 10 000 1858 / 1546.
+// Up to SPARSE_DIRECT queries, in us: half the table's bytes instead of all of them, the matrix (0.9 10^-6 a distance written and read)
+// and one workgroup's selection are saved, the launches of seven small kernels and 24 KB for every pair are spent.  With /
+// without: K = 2^20, P = 16, 1 query 134 / 93, 64 199 / 111, 128 308 / 130, 256 387 / 176; P = 128, 1 151 / 102, 64 224 / 193, 256 445 / 410;
+// P = 250, 1 170 / 110, 32 213 / 198, 64 252 / 260, 256 498 / 655; K = 262 144, P = 16, 1 70 / 69, 64 88 / 79, 256 140 / 114; P = 64, 1 81 / 73,
+// 64 104 / 104, 128 119 / 139; P = 250, 1 98 / 83, 32 123 / 146; K = 65 536, P = 16, 1 50 / 55, 64 63 / 68, 256 69 / 96; P = 64, 1 63 / 60, 32 76 / 78.
 bool sparse_pays(int64_t K, int D, int P, int64_t nq)
 {
+    if (K < 1024 * (int64_t)P) return false;
+    if (nq <= SPARSE_DIRECT) {
+        const double wide = packed_dim(D) / 96.0;
+        return (0.9 * (double)nq + 50.0 * wide) * 1e-6 * (double)K + 0.05 * P > 12.0 + 0.0078 * wide * (double)nq * P;
+    }
     const int64_t pairs = (int64_t)P << (packed_dim(D) <= 96 ? 22 : 23);
-    return K >= 1024 * (int64_t)P && nq * K >= (pairs > (1ll << 27) ? pairs : 1ll << 27);
+    return nq * K >= (pairs > (1ll << 27) ? pairs : 1ll << 27);
 }
 
 // Queries of a pass without the distance matrix; 0: with it.
@@ -1064,7 +1083,10 @@ int64_t sparse_tile(const ivf_index *ix, int P, int64_t nq)
 {
     if (!ix->chi || P > PS_P_MAX || (int64_t)P * ix->L > 16384) return 0;
     int64_t n = nq < (1 << 20) ? nq : (1 << 20);
-    while (sparse_pays(ix->K, ix->D, P, n) && (int64_t)plan_sparse(ix->K, ix->D, P, ix->L, n).total > ix->scratch_limit) n = (n / 2 + 127) & ~127ll;
+    while (sparse_pays(ix->K, ix->D, P, n) && (int64_t)sparse_bytes(ix->K, ix->D, P, ix->L, n) > ix->scratch_limit) {
+        if (n <= 128) return 0;
+        n = (n / 2 + 127) & ~127ll;
+    }
     return sparse_pays(ix->K, ix->D, P, n) ? n : 0;
 }
 
@@ -1088,7 +1110,7 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
     else if (tile >= GT) tile -= tile % GT;
 
     int64_t sparse_n = sparse_tile(ix, nprobe, nq);
-    if (sparse_n > 0 && (rc = ensure(ix->sparse, plan_sparse(K, ix->D, nprobe, ix->L, sparse_n).total))) {
+    if (sparse_n > 0 && (rc = ensure(ix->sparse, sparse_bytes(K, ix->D, nprobe, ix->L, sparse_n)))) {
         if (rc != IVF_ENOMEM) return rc;
         sparse_n = 0;                                            // (no room: with the distance matrix, in as many passes as its limit asks for)
     }

@@ -63,10 +63,11 @@ __global__ __launch_bounds__(256) void neighbour_norm_kernel(const int32_t *__re
     if (i < total) out[i] = cnorm[nbr[i]];
 }
 
-// The queries as fp16 rows in pack_hi_rows_kernel's layout, at the table's scale; a wavefront a row.  Rows past n (up to n_pad)
+// The queries as hi/lo rows (split_rows_kernel) and as fp16 rows in pack_hi_rows_kernel's layout, at the table's scale; a wavefront a row.  Rows past n (up to n_pad)
 // are zeros.  Workgroups from rows_grid on clear `words` 64-bit words of counters.
 __global__ __launch_bounds__(256) void sparse_queries_kernel(const float *__restrict__ X, int64_t n, int64_t n_pad, int D, int Dp,
-                                                             const uint32_t *__restrict__ cmax, _Float16 *__restrict__ H, float2 *__restrict__ len,
+                                                             const uint32_t *__restrict__ cmax, _Float16 *__restrict__ P, float *__restrict__ norm,
+                                                             float *__restrict__ inv_scale, _Float16 *__restrict__ H, float2 *__restrict__ len,
                                                              unsigned rows_grid, unsigned long long *__restrict__ zero, int64_t words)
 {
     if (blockIdx.x >= rows_grid) {
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(256) void sparse_queries_kernel(const float *__rest
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= n_pad) return;
+    if (row < n) split_row(X, row, D, nullptr, P, norm, inv_scale);
     const int sh = hi_scale(*cmax) - SPARSE_HEADROOM;
     float s2 = 0.f, d2 = 0.f;
     _Float16 hi[2];
@@ -213,6 +215,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 struct SparseArgs {
     int64_t K, half_ld;
     int nb, P, L, cap, shift, Dp;              // cap >= 2 P: blocks a query may list; a pair is query << shift | slot
+    bool direct;                               // small batches: a pair is a work item, listed by the workgroup that finds it
     const float4 *tile;
     const float2 *qlen;
     const float *qn, *qsi;                     // |q|^2, inverse scales
@@ -240,6 +243,31 @@ struct SparseArgs {
     const int32_t *nbr;
     const float *nbr_norm, *cst, *alpha;
     const uint32_t *order_inv;                 // [K] a region's bucket: its place in the order of order.hpp
+};
+
+// Takes a query's flagged blocks: counted by block, to be grouped (bucket_items_kernel), or as the work items themselves, of one pair
+// each, in room for `total` of them.  Built by the whole workgroup (a barrier); word: a word of LDS.
+struct PairList {
+    const SparseArgs &a;
+    int64_t q;
+    uint32_t first = 0;
+    __device__ __forceinline__ PairList(const SparseArgs &args, int64_t query, uint32_t total, uint32_t *word) : a(args), q(query)
+    {
+        if (!a.direct) return;
+        if (threadIdx.x == 0) *word = atomicAdd(&a.total[2], total);
+        __syncthreads();
+        first = *word;
+    }
+    __device__ __forceinline__ void operator()(uint32_t at, int b) const
+    {
+        a.blist[q * a.cap + at] = b;
+        if (a.direct) {
+            a.pairs[first + at] = (uint32_t)q << a.shift | at;
+            a.items[first + at] = make_uint4((uint32_t)b, first + at, 1u, 0u);
+        } else {
+            a.rank[q * a.cap + at] = atomicAdd(&a.count[(q % N_XCD) * a.nb + b], 1u);
+        }
+    }
 };
 
 // Lists the blocks of 64 that can hold one of a query's P closest centroids: a block's smallest distance lies between two ends,
@@ -383,20 +411,25 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4, 8))) v
     }
     if (total > (uint32_t)a.cap || !(ql.x < INFINITY)) {                       // uniform
         if (tid == 0) {
+            const uint32_t r = atomicAdd(&a.total[0], 1u);
             a.n_flag[q] = 0;
-            a.hard[atomicAdd(&a.total[0], 1u)] = (uint32_t)q;
+            a.hard[r] = (uint32_t)q;
+            a.hard_n[r] = a.qn[q];
+            a.hard_si[r] = a.qsi[q];
+            sh.pick[0] = r;
         }
+        __syncthreads();
+        const int64_t r = sh.pick[0], chunks = a.Dp / 4;                     // 16-byte pieces of a row
+        for (int c = tid; c < chunks; c += BLOCK) reinterpret_cast<gu32x4 *>(a.hard_rows)[r * chunks + c] = reinterpret_cast<const gu32x4 *>(a.Qp)[q * chunks + c];
         return;
     }
-    int32_t *list = a.blist + q * a.cap;
-    uint32_t *rank = a.rank + q * a.cap, *count = a.count + (q % N_XCD) * a.nb;
+    const PairList put(a, q, total, &sh.pick[0]);
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
         uint32_t at = least[u];
         while (flags[u]) {
             const int b = 2 * TP * (tid + u * BLOCK) + __builtin_ctz(flags[u]);
-            list[at] = b;
-            rank[at++] = atomicAdd(&count[b], 1u);
+            put(at++, b);
             flags[u] &= flags[u] - 1;
         }
     }
@@ -410,20 +443,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4, 8))) v
 }
 
 // ---- hard queries: block minima of their exact distances.  Loops over what there is, nearly always nothing ----
-__global__ __launch_bounds__(256) void hard_rows_kernel(SparseArgs a)
-{
-    const uint32_t n = a.total[0];
-    const int chunks = a.Dp / 4;                                            // 16-byte pieces of a row
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (int64_t)n * chunks; i += (int64_t)gridDim.x * 256) {
-        const int64_t r = i / chunks, c = i - r * chunks, q = a.hard[r];
-        reinterpret_cast<gu32x4 *>(a.hard_rows)[i] = reinterpret_cast<const gu32x4 *>(a.Qp)[q * chunks + c];
-        if (c == 0) {
-            a.hard_n[r] = a.qn[q];
-            a.hard_si[r] = a.qsi[q];
-        }
-    }
-}
-
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void hard_minima_kernel(SparseArgs a)
 {
     __shared__ __attribute__((aligned(16))) float ops0[DBUF];
@@ -477,12 +496,10 @@ __global__ __launch_bounds__(BLOCK) void hard_flag_kernel(SparseArgs a)
             kv[j] = j < ipt && i0 + j < a.nb ? key : NO_KEY;
         }
         block_select_runs<BLOCK>(kv, ipt, a.P < a.nb ? (uint32_t)a.P : (uint32_t)a.nb, sh, pivot, need);
-        int32_t *list = a.blist + q * a.cap;
-        uint32_t *rank = a.rank + q * a.cap, *count = a.count + (q % N_XCD) * a.nb;
-        const uint32_t total = block_emit_runs<BLOCK>(kv, ipt, pivot, (uint32_t)a.P, sh.scan, [&](uint32_t pos, int b, uint32_t) {
-            list[pos] = b;
-            rank[pos] = atomicAdd(&count[b], 1u);
-        });
+        // (at most P below the pivot and P more, or all blocks: counted first)
+        const uint32_t total = block_emit_runs<BLOCK>(kv, ipt, pivot, (uint32_t)a.P, sh.scan, [](uint32_t, int, uint32_t) {});
+        const PairList put(a, q, total, &sh.pick[0]);
+        block_emit_runs<BLOCK>(kv, ipt, pivot, (uint32_t)a.P, sh.scan, [&](uint32_t pos, int b, uint32_t) { put(pos, b); });
         if (threadIdx.x == 0) {
             a.n_flag[q] = total;
             a.thr[q] = a.nb < a.P ? INFINITY : key_float(pivot);
@@ -546,23 +563,23 @@ __global__ __launch_bounds__(256) void place_pairs_kernel(const int32_t *__restr
 
 // The exact distances of up to 32 queries (a work item) to 64 rows of the table, a step.  REGION: the rows are neighbours of
 // region `bucket` and the result is the score of Eq. (7) as an ordered key; else they are the 64 centroids of a block.
-// Products and their order are those of gemm_tile.  A wavefront takes PAIR_RUN steps in a row; rows are copied to LDS
-// directly, six such workgroups a compute unit.  While a step's results are written the rows of the next are on their way, and
+// Products and their order are those of gemm_tile.  A wavefront takes `run` = PAIR_RUN steps in a row; rows are copied to LDS
+// directly, six such workgroups a compute unit (fewer steps where there are not enough for all).  While a step's results are written the rows of the next are on their way, and
 // before them the next one's pairs and neighbours, and before those the item after that: each depends on the one before, and
 // one step a workgroup waited 2 of its 4.7 us for them.  The results pass through LDS as they come, PAIR_OUT queries at a
 // time, and a lane a row makes distances of them for the queries there are (three of 32 for the regions of 10 000 queries on
 // 2^20).
 constexpr int PAIR_RUN = 8, PAIR_OUT = 8;
 
-inline unsigned pair_grid(int64_t items, int chunks)
+inline unsigned pair_grid(int64_t items, int chunks, int run)
 {
     const int64_t share = (items + N_XCD - 1) / N_XCD * chunks;
-    return (unsigned)((share + PAIR_RUN - 1) / PAIR_RUN * N_XCD);
+    return (unsigned)((share + run - 1) / run * N_XCD);
 }
 
 // WHOLE: every step has 64 rows (L a multiple of 64).
 template <int STAGES, bool REGION, bool WHOLE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_distance_kernel(SparseArgs a, const uint32_t *__restrict__ n_items, int chunks)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_distance_kernel(SparseArgs a, const uint32_t *__restrict__ n_items, int chunks, int run)
 {
     typedef const __attribute__((address_space(1))) void *gptr_t;
     typedef __attribute__((address_space(3))) void *lptr_t;
@@ -575,10 +592,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // side by side have in common) it then finds in its L2
     const uint32_t items = *n_items, share = (items + N_XCD - 1) / N_XCD;
     const uint32_t i_end = (blockIdx.x % N_XCD + 1) * share < items ? (blockIdx.x % N_XCD + 1) * share : items;
-    const uint32_t begin = blockIdx.x % N_XCD * share * chunks + blockIdx.x / N_XCD * PAIR_RUN;
+    const uint32_t begin = blockIdx.x % N_XCD * share * chunks + blockIdx.x / N_XCD * run;
     uint32_t end = i_end * chunks;
     if (begin >= end) return;                                              // (also where blockIdx.x % N_XCD * share > items)
-    if (end - begin > (uint32_t)PAIR_RUN) end = begin + PAIR_RUN;
+    if (end - begin > (uint32_t)run) end = begin + run;
     const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5, mask = (1 << a.shift) - 1;
     const int width = REGION ? a.L : BMW;
     const float m2c = -2.f * a.csi[0];
@@ -764,8 +781,14 @@ __global__ __launch_bounds__(PICK_BLOCK) void probe_pick_kernel(SparseArgs a)
     auto put = [&](uint32_t pos, int32_t id, uint32_t key) {
         a.probe_id[q * P + pos] = id;
         a.probe_d[q * P + pos] = key_float(key);
-        a.rank[q * a.cap + pos] = atomicAdd(&a.region_count[(q % N_XCD) * a.K + a.order_inv[id]], 1u);
+        if (a.direct) {
+            a.pairs[q * P + pos] = (uint32_t)q << a.shift | pos;
+            a.items[q * P + pos] = make_uint4((uint32_t)id, (uint32_t)(q * P + pos), 1u, 0u);
+        } else {
+            a.rank[q * a.cap + pos] = atomicAdd(&a.region_count[(q % N_XCD) * a.K + a.order_inv[id]], 1u);
+        }
     };
+    if (a.direct && tid == 0) atomicAdd(&a.total[4], (uint32_t)P);
     uint4 h[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) h[u] = head[2 * tid + u < n ? 2 * tid + u : 0];

@@ -55,3 +55,25 @@ def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     for name in whole:
         assert torch.equal(again[name].view(torch.uint8), whole[name].view(torch.uint8)), name
     ivf.ivf_free_index(h)
+
+
+# batches whose pairs are not grouped: one query, odd numbers, the largest; bounds too wide for every query or for some
+@pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
+    (300_000, 32, 8, 8, 16, 100, "plain"), (262_144, 96, 64, 16, 64, 1, "plain"), (270_001, 64, 33, 16, 20, 33, "plain"),
+    (262_144, 128, 65, 8, 16, 129, "plain"), (262_144, 96, 16, 16, 16, 70, "hard"), (262_144, 96, 16, 16, 16, 256, "some")])
+def test_small_batches_same_bits(K, D, L, M, P, nq, kind):
+    import torch
+    import paper_1802_02422_amd as ivf
+    h, cent, g = make(K, D, L, M, K + D, 0.01 if kind == "hard" else 1.0, 50.0 if kind == "hard" else 0.0)
+    q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")]
+    q = (q + 0.5 * (cent.std() if kind == "hard" else 1.0) * torch.randn(nq, D, generator=g, device="cuda")).contiguous()
+    if kind == "some":
+        q[::7] *= 1e5
+        q[3::11] = 0.0
+        q[1, 0], q[2, 3] = float("nan"), float("inf")
+    got = ivf.ivf_search_stages(h, q, P, 0.3, 20)
+    ivf.ivf_set_scratch_limit(h, 4 << 20)                     # less than such a pass takes: the distance matrix, a few queries at a time
+    ref = ivf.ivf_search_stages(h, q, P, 0.3, 20)
+    for name in ref:
+        assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), name
+    ivf.ivf_free_index(h)
