@@ -1000,8 +1000,14 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         LAUNCHCHK("score_prune_kernel");
         if (a.budget > 0) {
             const uint32_t R = a.budget > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)a.budget;
-            budget_cut_kernel<256><<<dim3((unsigned)n), dim3(256), 0, st>>>(
-                ws.desc, S, R, a.visited_out ? a.visited_out + q0 * S : nullptr, ns);
+            auto cut = [&](auto kernel) {
+                kernel<<<dim3((unsigned)n), dim3(BUDGET_BLOCK), 0, st>>>(ws.desc, S, R, a.visited_out ? a.visited_out + q0 * S : nullptr, ns);
+            };
+            static_assert(IVF_MAX_SCORES <= 32 * BUDGET_BLOCK, "items of a thread");
+            if (S <= 4 * BUDGET_BLOCK) cut(&budget_cut_kernel<4>);
+            else if (S <= 8 * BUDGET_BLOCK) cut(&budget_cut_kernel<8>);
+            else if (S <= 16 * BUDGET_BLOCK) cut(&budget_cut_kernel<16>);
+            else cut(&budget_cut_kernel<32>);
             LAUNCHCHK("budget_cut_kernel");
         }
         if ((rc = mark(3))) return rc;

@@ -92,3 +92,26 @@ def test_largest_score_count_per_query():
     with pytest.raises(ivf.IvfError):
         ivf.ivf_search(handle, torch.from_numpy(Q).cuda(), 257, 0.2, 10)
     ivf.ivf_free_index(handle)
+
+
+def test_numbers_of_kept_subregions():
+    """One, and around what the cut holds in registers (4, 8, 16 and 32 times 1024), scores that tie exactly among them (alpha = 0)."""
+    mix = sd.make_mixture("deep", 300, 32, name="wide")
+    X = sd.draw_points(mix, 40000, 0, "wide-base")[0].numpy()
+    Xt = sd.draw_points(mix, 8000, 0, "wide-train")[0].numpy()
+    Q = sd.draw_queries(mix, 3, "wide-query").numpy()
+    ix = orc.build_index(Xt, X, 400, 128, 8, sd.draw_indices(8000, 400, "wide-k").numpy(),
+                         sd.draw_indices(8000, 256, "wide-pq").numpy(), kmeans_iters=3, pq_iters=3)
+    alpha = np.zeros(400, np.float32)
+    enc = orc.encode(X, ix.centroids, ix.nbr, alpha, ix.pq_codebook, ix.const_table)
+    perm, off = orc.group(enc.region, enc.sub, 128, 400)
+    tied = orc.Index(32, 8, 128, 400, 40000, ix.centroids, ix.nbr, alpha, ix.cs_dist2, ix.pq_codebook, ix.const_table,
+                     off, np.ascontiguousarray(enc.codes[perm]), np.ascontiguousarray(enc.const_byte[perm]),
+                     np.arange(40000, dtype=np.int32)[perm].copy())
+    for index in (ix, tied):
+        handle = ivf.ivf_load_index(parity.to_device(index))
+        for nprobe, tau in ((1, 0.001), (32, 1.0), (33, 1.0), (65, 1.0), (129, 1.0), (250, 0.95)):
+            print("case: nprobe %d of 128 subregions, tau %g" % (nprobe, tau), flush=True)
+            for R in (1, 900):
+                run_budget(handle, index, Q, nprobe, tau, R, 10, max_near_frac=1.0)
+        ivf.ivf_free_index(handle)
