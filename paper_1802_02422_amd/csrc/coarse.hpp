@@ -1049,6 +1049,25 @@ __global__ __launch_bounds__(256) void coarse_shortlist_kernel(ShortlistArgs a)
     }
 }
 
+// A tile of GT fp16 rows of SH 64-byte stages in LDS: the rows as they lie in memory, so that each load of 1 KB takes whole
+// 128-byte lines (16 rows' 64 bytes of a stage a load: the loads of the other halves of the lines waited for them: 500 000 rows x 65 536 6.2 - 6.4 ms,
+// 6.0 so; 10 000 x 2^20 block maxima 2.28 and 2.05), with
+// the 16-byte chunks of row r at their number ^ tile_twist(r): 16 rows' reads of a chunk then go to all banks.
+template <int SH>
+__device__ __forceinline__ uint32_t tile_twist(int r) { return SH == 4 ? r & 15 : SH == 2 ? (r >> 1) & 7 : (r >> 2) & 3; }
+
+// ... of the row that lane `lane` copies a chunk of in piece n = wave, wave + 4, ..: the same for all of them but for three stages
+template <int SH>
+struct TileTwists {
+    uint32_t word = 0;
+    __device__ __forceinline__ TileTwists(int wave, int lane)
+    {
+#pragma unroll
+        for (int k = 0; k < (SH == 3 ? 2 * SH : 1); ++k) word |= tile_twist<SH>((64 * (wave + 4 * k) + lane) / (4 * SH)) << (2 * k);
+    }
+    __device__ __forceinline__ uint32_t of(int n) const { return SH == 3 ? word >> (2 * (n >> 2)) & 3u : word; }
+};
+
 // The same pass for SH = 1 .. 4 stages of 32 dimensions (packed dimension up to 128): a workgroup keeps the fragments of
 // ONE query tile in registers and sweeps `tiles_per_wg` consecutive centroid tiles through two LDS buffers of a whole
 // tile each, one workgroup barrier per tile (the copies of tile t + 1 are issued right behind the barrier of tile t
@@ -1092,11 +1111,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     if (t_end <= 0) return;
     const int64_t q0 = (int64_t)tq * GT;
 
-    // The copies of a tile: 8 SH pieces of 16 rows of a stage, dealt to the wavefronts, and from two of them 64 of the
-    // tile's start values
-    const int rl = lane >> 2;
-    const int fl = (lane & 3) ^ ((lane >> 4) & 3);
-    const float *cbase = reinterpret_cast<const float *>(a.Ch) + (int64_t)rl * Dpf + fl * 4;
+    // The copies of a tile: 8 SH pieces, dealt to the wavefronts (tile_twist), and from two of them 64 of the tile's start values
+    const TileTwists<SH> twists(wave, lane);
+    const float *cbase = reinterpret_cast<const float *>(a.Ch);
     auto issue_tile = [&](int t) {
         const int tc = t < t_end ? t : t_end - 1;            // past the range: the last tile again, never read
         if (wave < 2)
@@ -1105,8 +1122,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         float *dst = &ring[t & 1][0];
         // (one instruction in a rolled loop: the compiler tracks only a handful of distinct LDS copies exactly)
 #pragma nounroll
-        for (int n = wave; n < 8 * SH; n += 4)     // piece n: stage n / 8, rows 16 (n % 8) ..
-            __builtin_amdgcn_global_load_lds((gptr_t)(src + (n >> 3) * DK + (int64_t)(n & 7) * 16 * Dpf), (lptr_t)(dst + n * 256), 16, 0, 0);
+        for (int n = wave; n < 8 * SH; n += 4)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src + n * 256 + 4 * (lane ^ (int)twists.of(n))), (lptr_t)(dst + n * 256), 16, 0, 0);
     };
     issue_tile(0);
 
@@ -1171,18 +1188,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             const int rb = wc + j * 32 + l32;
             // reads and their wait in one block each: nothing the compiler does to a register can come between
             const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
-            const uint32_t rsw = 4u * (uint32_t)(rb * ROWF), k0 = 16u * (uint32_t)((2 * h) ^ ((rb >> 2) & 3)), k1 = 16u * (uint32_t)((2 * h + 1) ^ ((rb >> 2) & 3));
+            const uint32_t rsw = 4u * (uint32_t)(rb * Dpf), k0 = 16u * ((uint32_t)(2 * h) ^ tile_twist<SH>(rb)), k1 = 16u * ((uint32_t)(2 * h + 1) ^ tile_twist<SH>(rb));
 #pragma unroll
             for (int s = 0; s < SH; ++s) {
-                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][s * SLOT]) + rsw;
+                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][0]) + rsw;
+                const uint32_t b0 = bs + (SH & 1 ? k0 + 64u * s : k0 ^ 64u * s), b1 = bs + (SH & 1 ? k1 + 64u * s : k1 ^ 64u * s);
                 gu32x4 b[2];
                 if (s == 0)
                     asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:32\n\tds_read_b128 %2, %6 offset:64\n\tds_read_b128 %3, %6 offset:96\n\t"
                                  "ds_read_b128 %4, %7\n\tds_read_b128 %5, %8\n\ts_waitcnt lgkmcnt(0)"
                                  : "=&v"(start.part[0]), "=&v"(start.part[1]), "=&v"(start.part[2]), "=&v"(start.part[3]), "=&v"(b[0]), "=&v"(b[1])
-                                 : "v"(cb), "v"(bs + k0), "v"(bs + k1));
+                                 : "v"(cb), "v"(b0), "v"(b1));
                 else
-                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(bs + k0), "v"(bs + k1));
+                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(b0), "v"(b1));
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
 #pragma unroll

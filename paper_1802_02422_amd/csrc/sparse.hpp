@@ -109,7 +109,7 @@ __host__ __device__ inline int64_t minima_half(int64_t K) { return ((K + GT - 1)
 // best[q][half][t] = the largest of <q, c> - (1/2 - k) |c|^2 over the 64 centroids of the half of tile t, for a sweep of
 // `tiles_per_wg` (a multiple of four) centroid tiles by a workgroup that keeps the fragments of ONE query tile in registers:
 // coarse_shortlist_sweep_kernel's loop without its bounds and reports.  A lane ends up with the maxima of one query, four tiles
-// in a row, and stores them as 16 bytes.  10 000 x 2^20, 96 dimensions: 2.2 ms (0.92
+// in a row, and stores them as 16 bytes.  10 000 x 2^20, 96 dimensions: 2.05 ms (0.98
 // PFLOP/s), x 65 536 0.14; the distance GEMM takes 9.8 and 0.70.
 template <int SH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void coarse_minima_kernel(
@@ -134,9 +134,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     if (t_end <= 0) return;
     const int64_t q0 = tq * GT;
 
-    const int rl = lane >> 2;
-    const int fl = (lane & 3) ^ ((lane >> 4) & 3);
-    const float *cbase = reinterpret_cast<const float *>(Ch) + (int64_t)rl * Dpf + fl * 4;
+    const TileTwists<SH> twists(wave, lane);
+    const float *cbase = reinterpret_cast<const float *>(Ch);
     auto issue_tile = [&](int t) {
         const int tc = t < t_end ? t : t_end - 1;            // past the range: the last tile again, never read
         if (wave < 2)
@@ -144,8 +143,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         const float *src = cbase + (int64_t)(tb + tc) * GT * Dpf;
         float *dst = &ring[t & 1][0];
 #pragma nounroll
-        for (int n = wave; n < 8 * SH; n += 4)     // piece n: stage n / 8, rows 16 (n % 8) ..
-            __builtin_amdgcn_global_load_lds((gptr_t)(src + (n >> 3) * DK + (int64_t)(n & 7) * 16 * Dpf), (lptr_t)(dst + n * 256), 16, 0, 0);
+        for (int n = wave; n < 8 * SH; n += 4)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src + n * 256 + 4 * (lane ^ (int)twists.of(n))), (lptr_t)(dst + n * 256), 16, 0, 0);
     };
     issue_tile(0);
     gu32x4 afr[SH][2][2];
@@ -171,18 +170,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             union { floatx16 all; floatx4 part[4]; } init;
             const int rb = wc + j * 32 + l32;
             const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
-            const uint32_t rsw = 4u * (uint32_t)(rb * ROWF), k0 = 16u * (uint32_t)((2 * h) ^ ((rb >> 2) & 3)), k1 = 16u * (uint32_t)((2 * h + 1) ^ ((rb >> 2) & 3));
+            const uint32_t rsw = 4u * (uint32_t)(rb * Dpf), k0 = 16u * ((uint32_t)(2 * h) ^ tile_twist<SH>(rb)), k1 = 16u * ((uint32_t)(2 * h + 1) ^ tile_twist<SH>(rb));
 #pragma unroll
             for (int s = 0; s < SH; ++s) {
-                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][s * SLOT]) + rsw;
+                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][0]) + rsw;
+                const uint32_t b0 = bs + (SH & 1 ? k0 + 64u * s : k0 ^ 64u * s), b1 = bs + (SH & 1 ? k1 + 64u * s : k1 ^ 64u * s);
                 gu32x4 b[2];
                 if (s == 0)
                     asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:32\n\tds_read_b128 %2, %6 offset:64\n\tds_read_b128 %3, %6 offset:96\n\t"
                                  "ds_read_b128 %4, %7\n\tds_read_b128 %5, %8\n\ts_waitcnt lgkmcnt(0)"
                                  : "=&v"(init.part[0]), "=&v"(init.part[1]), "=&v"(init.part[2]), "=&v"(init.part[3]), "=&v"(b[0]), "=&v"(b[1])
-                                 : "v"(cb), "v"(bs + k0), "v"(bs + k1));
+                                 : "v"(cb), "v"(b0), "v"(b1));
                 else
-                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(bs + k0), "v"(bs + k1));
+                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(b0), "v"(b1));
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
 #pragma unroll
