@@ -77,3 +77,19 @@ def test_small_batches_same_bits(K, D, L, M, P, nq, kind):
     for name in ref:
         assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), name
     ivf.ivf_free_index(h)
+
+
+def test_last_pass_of_a_large_batch_is_a_small_one():
+    """Scratch limits that cut 2100 queries into passes, the last of which may be small enough for pairs that are not grouped."""
+    import torch
+    import paper_1802_02422_amd as ivf
+    h, cent, g = make(262_144, 32, 8, 8, 5, 1.0, 0.0)
+    q = (cent[torch.randint(0, 262_144, (2100,), generator=g, device="cuda")] + 0.5 * torch.randn(2100, 32, generator=g, device="cuda")).contiguous()
+    ivf.ivf_set_scratch_limit(h, 16 << 30)
+    ref = ivf.ivf_search_stages(h, q, 16, 0.3, 20)
+    for mb in (45, 60, 20):
+        ivf.ivf_set_scratch_limit(h, mb << 20)
+        got = ivf.ivf_search_stages(h, q, 16, 0.3, 20)
+        for name in ref:
+            assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), (mb, name)
+    ivf.ivf_free_index(h)
