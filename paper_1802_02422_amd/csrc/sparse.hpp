@@ -1,4 +1,5 @@
-// Stages 1 to 2 of the query path for large batches without the distance matrix.  Of the nq x K distances a search needs
+// Stages 1 to 2 of the query path without the distance matrix, for large batches and for small ones on large tables
+// (sparse_pays).  Of the nq x K distances a search needs
 // some hundred blocks of 64 per query (the nprobe closest regions lie in them) and the L neighbours of its nprobe
 // regions: 2 % of them at K = 2^20.  Writing all of them, and reading 4 bytes from a 128-byte line each, took 14.3 of the
 // 16.3 ms of 10 000 queries there.  Here:
@@ -9,7 +10,8 @@
 //      read once for the up to 32 queries a wavefront takes.
 //   4. probe_pick_kernel: the P closest regions among them.
 //   5. pair_distance_kernel<true>: the scores of Eq. (7), grouped by region: the neighbours' rows are read once for the
-//      queries that probe the region.
+//      queries that probe the region, regions with common neighbours side by side (order.hpp).
+// Up to SPARSE_DIRECT queries the pairs of 3. and 5. are not grouped.
 // The distances are formed by the same products in the same order as in coarse_gemm_kernel, so a query's results do
 // not depend on which way its batch goes.  A query whose bound is too wide to leave at most 2 P blocks (vectors far from the
 // origin compared with their spread, rows that are not finite) gets exact block minima first (hard_* kernels, which end at
