@@ -200,6 +200,13 @@ int ivf_search_budget(ivf_index *index, const float *queries, int64_t nq, int np
                       int64_t max_candidates, int k, int32_t *out_ids, float *out_dists,
                       int64_t *kept_sub, uint8_t *visited, int64_t *n_scanned, void *hip_stream);
 
+/*
+ * Passes over batches of queries that this process has launched so far (out: two values, host memory): out[0] without
+ * the matrix of distances from the queries to the centroids, out[1] with it.  The results are the same bits either way; which way a
+ * batch goes depends on the sizes alone.  Host call.
+ */
+void ivf_search_stats(int64_t *out);
+
 /* S of stage 3 for the given parameters (host call, no device work). */
 int64_t ivf_num_kept(int nprobe, int L, float prune_frac);
 

@@ -17,6 +17,7 @@ from .binding import (  # noqa: F401
     ivf_search_stages,
     ivf_search_noalloc,
     ivf_search_budget,
+    ivf_search_stats,
     ivf_num_kept,
     ivf_coarse_topk,
     ivf_assign_stats,

@@ -58,6 +58,8 @@ def load_library():
     lib.ivf_coarse_topk.argtypes = [vp, i64, i32, vp, i64, i32, vp, vp, vp]
     lib.ivf_assign_stats.argtypes = [C.POINTER(C.c_int64)]
     lib.ivf_assign_stats.restype = None
+    lib.ivf_search_stats.argtypes = [C.POINTER(C.c_int64)]
+    lib.ivf_search_stats.restype = None
     lib.ivf_encode.argtypes = [C.POINTER(_Desc), vp, i64, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.ivf_rotate.argtypes = [vp, i64, i32, vp, vp, vp]
     lib.ivf_kmeans.argtypes = [vp, i64, i32, i64, i32, vp, vp, vp, vp]
@@ -250,6 +252,13 @@ def ivf_search_budget(index: IndexHandle, queries: torch.Tensor, nprobe: int, pr
         index.ptr, _ptr(queries), nq, nprobe, prune_frac, max_candidates, k, _ptr(out["ids"]), _ptr(out["dists"]),
         _ptr(out["kept_sub"]), _ptr(out["visited"]), _ptr(out["n_scanned"]), _stream()))
     return out
+
+
+def ivf_search_stats():
+    """(passes over batches of queries without the distance matrix, passes with it) so far in this process."""
+    out = (C.c_int64 * 2)()
+    load_library().ivf_search_stats(out)
+    return int(out[0]), int(out[1])
 
 
 def ivf_assign_stats():

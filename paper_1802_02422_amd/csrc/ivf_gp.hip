@@ -921,6 +921,8 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     return IVF_OK;
 }
 
+std::atomic<int64_t> g_passes_sparse{0}, g_passes_matrix{0};
+
 // The launch sequence of the query path over the batch, `pl.tile` queries per pass, on scratch the
 // caller provides.  Allocates nothing (stage timing, which creates events, is the allocating
 // entry points' option: `timed`).
@@ -946,6 +948,7 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
             return IVF_OK;
         };
         if ((rc = mark(0))) return rc;
+        (pl.sparse ? g_passes_sparse : g_passes_matrix)++;
         if (pl.sparse) {
             if ((rc = launch_sparse(ix, Q, n, P, ws, pid, pd, mark, st))) return rc;
         } else if ((rc = pack_rows(Q, n, D, nullptr, ws.qpk, ws.qn, ws.qsi, st))) {
@@ -1063,24 +1066,31 @@ int scratch_of_current_device(unsigned char **out)
 }
 
 // Whether a pass of nq queries goes without the distance matrix (sparse.hpp).  What it saves grows with nq K, what it costs with
-// nq P and the launches.  A search in us, with / without, L = 64, D = 96: K = 2^20, P = 256, 512 queries 939 / 961, 1024 1821 / 1608,
-// 10 000 15 507 / 9418; P = 16, 128 queries 317 / 190, 10 000 11 251 / 4277; K = 262 144, P = 256, 2048 queries 1479 / 1577, 4096
-// 2857 / 2325; P = 64, 512 330 / 294, 4096 1968 / 1291; K = 65 536, P = 64, 2048 482 / 501, 4096 830 / 748; P = 256 10 000
-// 3106 / 3327; P = 16, 1024 177 / 192, 2048 344 / 298; K = 32 768, P = 16, 1024 137 / 182, 4096 454 / 424; P = 64, 4096 607 / 645;
-// D = 128, where the sweep has two wavefronts a SIMD, K = 65 536, P = 64, 4096 857 / 907, 10 000 1858 / 1546.
+// nq P, with the 64 neighbours at a time of every region and with the launches.  A search in us, with / without, L = 64, D = 96: K = 2^20, P = 256,
+// 2048 queries 3390 / 2040, 10 000 14 490 / 6500; P = 16, 10 000 11 260 / 3530; K = 262 144, P = 256, 512 409 / 437, 1024 738 / 669, 10 000 6290 / 3000;
+// P = 64, 512 318 / 247, 4096 1890 / 855; K = 65 536, P = 64, 512 153 / 169, 1024 241 / 228, 4096 726 / 502; P = 16, 512 96 / 109, 1024 158 / 148,
+// 2048 295 / 232; K = 32 768, P = 16, 1024 137 / 182, 4096 454 / 424; D = 128, where the sweep has two wavefronts a SIMD, K = 65 536, P = 16, 2048 331 / 265,
+// P = 64, 10 000 1703 / 1095 (neighbours that regions of a group of 1024 have in common; neighbours anywhere in the table cost the way
+// without the matrix up to a fifth more).
+// With more than 64 neighbours the difference grows: a group of 2 L regions / neighbours anywhere, without over with: K = 65 536, P = 16,
+// L = 128 2048 queries .72 / .91; L = 256 2048 .90 / 1.20, 4096 .81 / 1.09, 10 000 .68 / .87; L = 512 4096 1.13 / 1.57, 10 000 .91 / 1.21; L = 1024 2048
+// 1.68 / 2.43, 10 000 1.16 / 1.57; K = 262 144, P = 64, L = 128 2048 .67 / .99, L = 256 2048 .85 / 1.41, 4096 .73 / 1.17, 10 000 .57 / .84; P = 128,
+// L = 128 2048 .79 / 1.22, 4096 .63 / .93; P = 16, L = 512 2048 .71 / 1.10, 4096 .67 / 1.03.  The line lies where neighbours anywhere lose nothing.
 // Up to SPARSE_DIRECT queries, in us: half the table's bytes instead of all of them, the matrix (0.9 10^-6 a distance written and read)
-// and one workgroup's selection are saved, the launches of seven small kernels and 24 KB for every pair are spent.  With /
-// without: K = 2^20, P = 16, 1 query 134 / 93, 64 199 / 111, 128 308 / 130, 256 387 / 176; P = 128, 1 151 / 102, 64 224 / 193, 256 445 / 410;
-// P = 250, 1 170 / 110, 32 213 / 198, 64 252 / 260, 256 498 / 655; K = 262 144, P = 16, 1 70 / 69, 64 88 / 79, 256 140 / 114; P = 64, 1 81 / 73,
-// 64 104 / 104, 128 119 / 139; P = 250, 1 98 / 83, 32 123 / 146; K = 65 536, P = 16, 1 50 / 55, 64 63 / 68, 256 69 / 96; P = 64, 1 63 / 60, 32 76 / 78.
-bool sparse_pays(int64_t K, int D, int P, int64_t nq)
+// and one workgroup's selection (less of it for few probes) are saved, the launches of seven small kernels and 24 KB for every 64 rows of a pair are spent.  With /
+// without: K = 2^20, P = 16, 1 query 134 / 93, 64 199 / 111, 128 308 / 130, 256 387 / 176; P = 128, 1 151 / 102, 64 224 / 193, 256 445 / 410 (L = 128 472 / 544);
+// P = 250, 1 170 / 110, 32 213 / 198, 64 252 / 260, 256 498 / 655; K = 262 144, P = 2, 1 58 / 60, 64 70 / 64, 256 120 / 78; P = 16, 1 70 / 69, 64 88 / 79, 256 140 / 114
+// (L = 256 176 / 159, L = 512 208 / 226); P = 64, 1 81 / 73, 64 104 / 104, 128 119 / 139; P = 250, 1 98 / 83, 32 123 / 146; K = 65 536, P = 2,
+// 256 55 / 64; P = 16, 1 50 / 55, 64 63 / 68, 256 69 / 96; P = 64, 1 63 / 60, 32 76 / 78.
+bool sparse_pays(int64_t K, int D, int P, int L, int64_t nq)
 {
     if (K < 1024 * (int64_t)P) return false;
+    const int64_t chunks = (L + BMW - 1) / BMW;
     if (nq <= SPARSE_DIRECT) {
-        const double wide = packed_dim(D) / 96.0;
-        return (0.9 * (double)nq + 50.0 * wide) * 1e-6 * (double)K + 0.05 * P > 12.0 + 0.0078 * wide * (double)nq * P;
+        const double wide = packed_dim(D) / 96.0, fixed = 17.0 - 5.0 / 16.0 * (P < 16 ? P : 16);
+        return (0.9 * (double)nq + 50.0 * wide) * 1e-6 * (double)K + 0.05 * P > fixed + (0.0055 + 0.0023 * (double)chunks) * wide * (double)nq * P;
     }
-    const int64_t pairs = (int64_t)P << (packed_dim(D) <= 96 ? 22 : 23);
+    const int64_t pairs = (int64_t)P * (chunks > 2 ? chunks * chunks / 2 : chunks) << (packed_dim(D) <= 96 ? 22 : 23);
     return nq * K >= (pairs > (1ll << 27) ? pairs : 1ll << 27);
 }
 
@@ -1089,11 +1099,11 @@ int64_t sparse_tile(const ivf_index *ix, int P, int64_t nq)
 {
     if (!ix->chi || P > PS_P_MAX || (int64_t)P * ix->L > 16384) return 0;
     int64_t n = nq < (1 << 20) ? nq : (1 << 20);
-    while (sparse_pays(ix->K, ix->D, P, n) && (int64_t)sparse_bytes(ix->K, ix->D, P, ix->L, n) > ix->scratch_limit) {
+    while (sparse_pays(ix->K, ix->D, P, ix->L, n) && (int64_t)sparse_bytes(ix->K, ix->D, P, ix->L, n) > ix->scratch_limit) {
         if (n <= 128) return 0;
         n = (n / 2 + 127) & ~127ll;
     }
-    return sparse_pays(ix->K, ix->D, P, n) ? n : 0;
+    return sparse_pays(ix->K, ix->D, P, ix->L, n) ? n : 0;
 }
 
 // The query path on the handle's own growable scratch (allocates when a call needs more than any before).
@@ -1156,6 +1166,12 @@ extern "C" int ivf_search_stages(ivf_index *ix, const float *queries, int64_t nq
 {
     return search_alloc(ix, queries, nq, nprobe, prune_frac, k, out_ids, out_dists, probe_id_out, probe_d_out,
                         kept_sub_out, n_scanned_out, 0, nullptr, hip_stream);
+}
+
+extern "C" void ivf_search_stats(int64_t *out)
+{
+    out[0] = g_passes_sparse;
+    out[1] = g_passes_matrix;
 }
 
 extern "C" int ivf_search_budget(ivf_index *ix, const float *queries, int64_t nq, int nprobe, float prune_frac,

@@ -93,3 +93,16 @@ def test_last_pass_of_a_large_batch_is_a_small_one():
         for name in ref:
             assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), (mb, name)
     ivf.ivf_free_index(h)
+
+
+# more than 64 neighbours a region: each further 64 are rows of their own to read, for every pair
+@pytest.mark.parametrize("L,nq,ways", [(64, 2048, (1, 0)), (128, 2048, (1, 0)), (256, 2048, (0, 1)), (256, 8192, (1, 0))])
+def test_way_by_the_number_of_neighbours(L, nq, ways):
+    import torch
+    import paper_1802_02422_amd as ivf
+    h, cent, g = make(65_536, 32, L, 8, 3, 1.0, 0.0)
+    q = cent[torch.randint(0, 65_536, (nq,), generator=g, device="cuda")].contiguous()
+    before = ivf.ivf_search_stats()
+    ivf.ivf_search(h, q, 16, 0.1, 10)
+    assert tuple(a - b for a, b in zip(ivf.ivf_search_stats(), before)) == ways
+    ivf.ivf_free_index(h)
