@@ -112,7 +112,11 @@ void ivf_free_index(ivf_index *index);
  * query-by-centroid distance tile of stage 1 (default 8 GiB).  Larger batches
  * are processed in several tiles of queries.  The tile is allocated in whole
  * blocks of 256 query rows, so it can exceed the bound by up to 255 rows of
- * 4*K bytes.  Host call.
+ * 4*K bytes.  What a pass needs beside it (descriptors, lookup tables and
+ * partial lists of its queries) is not counted.  Batches that go without the
+ * distance tile have their scratch in its place, under the same bound; a pass
+ * of more queries than a tile under that bound would have keeps to it with
+ * all its scratch.  Host call.
  */
 int ivf_set_scratch_limit(ivf_index *index, int64_t bytes);
 

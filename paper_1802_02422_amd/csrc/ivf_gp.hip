@@ -276,7 +276,7 @@ struct SearchWs {
     float *lut = nullptr;
     uint64_t *partial = nullptr;
     float *qrot = nullptr;       // rotated queries (indexes with a rotation in front of the PQ)
-    unsigned char *sparse = nullptr;
+    unsigned char *sparse() const { return reinterpret_cast<unsigned char *>(dt); }   // a pass has either
 };
 
 enum { WS_DT, WS_BM, WS_QN, WS_QSI, WS_QPK, WS_PID, WS_PD, WS_DESC, WS_LUT, WS_PARTIAL, WS_QROT, WS_COUNT };
@@ -358,11 +358,12 @@ int64_t dt_rows(int64_t n, int64_t K, int Dp)
 }
 
 // per: points of a subregion on average; shared: whether several workgroups may divide what one wavefront would do (scratch for
-// more partial lists; the results are the same)
-SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated, bool shared = true, bool sparse = false)
+// more partial lists; the results are the same); sparse: sparse_bytes() of such a pass where it goes without the distance matrix, in whose
+// place that scratch is
+SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k, int64_t tile, bool rotated, bool shared = true, size_t sparse = 0)
 {
     SearchPlan pl;
-    pl.sparse = sparse;
+    pl.sparse = sparse > 0;
     pl.tile = tile;
     pl.S = S;
     // Workgroups per query in the scan: fill the chip when the batch is small, but with at most 8 per
@@ -397,7 +398,7 @@ SearchPlan plan_search(int64_t K, int D, int M, int P, int S, double per, int k,
     const size_t rows = (size_t)dt_rows(tile, K, Dp);
     const size_t tile_pad = (size_t)packed_rows(tile);   // the GEMM tiles copy whole tiles of packed rows
     const int64_t nb = (K + BMW - 1) / BMW;
-    pl.bytes[WS_DT] = sparse ? 0 : rows * dt_stride(K) * sizeof(float);
+    pl.bytes[WS_DT] = sparse ? sparse : rows * dt_stride(K) * sizeof(float);
     pl.bytes[WS_BM] = sparse ? 0 : rows * nb * sizeof(float);
     pl.bytes[WS_QN] = tile_pad * sizeof(float);
     pl.bytes[WS_QSI] = tile_pad * sizeof(float);
@@ -433,7 +434,7 @@ struct ivf_index {
     uint4 *sub_info = nullptr;   // per subregion: block offset, first position, length
     uint8_t *blocks = nullptr;
     int64_t scratch_limit = 8ll << 30;
-    Buf dt, bm, qn, qpk, qsi, probe_id, probe_d, desc, lut, partial, qrot, sparse;
+    Buf dt, bm, qn, qpk, qsi, probe_id, probe_d, desc, lut, partial, qrot;
     // optional per-stage timing with HIP events on the caller's stream
     bool profile = false;
     std::vector<hipEvent_t> ev[IVF_N_STAGES + 1];   // ev[s][i], ev[s+1][i] bracket stage s of pass i
@@ -459,7 +460,7 @@ extern "C" void ivf_free_index(ivf_index *ix)
                      ix->nbr, ix->ids, ix->sub_info, ix->blocks, ix->dt.p, ix->bm.p, ix->qn.p,
                      ix->cpk, ix->csi, ix->qpk.p, ix->qsi.p,
                      ix->probe_id.p, ix->probe_d.p, ix->desc.p, ix->lut.p, ix->partial.p, ix->qrot.p, ix->rot_t,
-                     ix->sparse.p, ix->chi};
+                     ix->chi};
     for (void *p : owned)
         if (p) (void)hipFree(p);
     for (auto &v : ix->ev)
@@ -797,14 +798,14 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
     return IVF_OK;
 }
 
-// Stages 1 and 2 without the distance matrix: probes to pid and pd, the keys of the scores to ws.sparse (SP_BIG).
+// Stages 1 and 2 without the distance matrix: probes to pid and pd, the keys of the scores to ws.sparse() (SP_BIG).
 template <class Mark>
 int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchWs &ws, int32_t *pid, float *pd, Mark mark, hipStream_t st)
 {
     const int64_t K = ix->K;
     const int D = ix->D, L = ix->L, Dp = packed_dim(D), nb = (int)((K + BMW - 1) / BMW);
     const SparsePlan sp = plan_sparse(K, D, P, L, n);
-    auto piece = [&](auto *&p, int i) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(ws.sparse + sp.off[i]); };
+    auto piece = [&](auto *&p, int i) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(ws.sparse() + sp.off[i]); };
     int rc;
     _Float16 *qh;
     float2 *qlen;
@@ -984,7 +985,7 @@ int run_search(ivf_index *ix, const SearchArgs &a, const SearchPlan &pl, const L
         n, Qt, D, M, ix->codebook, ws.lut, lut_per)
         const int lut_per = lut_queries(n, D, lds.sp);
         if (pl.sparse) {
-            const uint32_t *given = reinterpret_cast<const uint32_t *>(ws.sparse + plan_sparse(K, D, P, L, n).off[SP_BIG]);
+            const uint32_t *given = reinterpret_cast<const uint32_t *>(ws.sparse() + plan_sparse(K, D, P, L, n).off[SP_BIG]);
             auto prune = [&](auto kernel, int block) {
                 kernel<<<dim3(lut_grid(n, lut_per)), dim3(block), lds.sp, st>>>(reinterpret_cast<const float *>(given), PL, K, pid, pd, P, L, ix->nbr,
                     ix->cst, ix->alpha, S, ix->sub_info, ws.desc, ks, ns, n, Qt, D, M, ix->codebook, ws.lut, lut_per);
@@ -1094,12 +1095,25 @@ bool sparse_pays(int64_t K, int D, int P, int L, int64_t nq)
     return nq * K >= (pairs > (1ll << 27) ? pairs : 1ll << 27);
 }
 
-// Queries of a pass without the distance matrix; 0: with it.
-int64_t sparse_tile(const ivf_index *ix, int P, int64_t nq)
+// Plan of a pass of n queries without the distance matrix
+SearchPlan plan_without_matrix(const ivf_index *ix, int P, int S, int k, int64_t n)
+{
+    return plan_search(ix->K, ix->D, ix->M, P, S, mean_length(ix), k, n, ix->rot_t != nullptr, true, sparse_bytes(ix->K, ix->D, P, ix->L, n));
+}
+
+// Queries of a pass without the distance matrix; 0: with it, `tile` of them.  Its own scratch keeps to the limit that the matrix would
+// keep to, and a pass of more queries than that keeps to it with everything that grows with them (descriptors, tables, lists).
+int64_t sparse_tile(const ivf_index *ix, int P, int S, int k, int64_t nq, int64_t tile)
 {
     if (!ix->chi || P > PS_P_MAX || (int64_t)P * ix->L > 16384) return 0;
+    auto fits = [&](int64_t n) {
+        const SearchPlan pl = plan_without_matrix(ix, P, S, k, n);
+        size_t total = 0;
+        for (size_t b : pl.bytes) total += b;
+        return (n <= tile ? pl.bytes[WS_DT] : total) <= (size_t)ix->scratch_limit;
+    };
     int64_t n = nq < (1 << 20) ? nq : (1 << 20);
-    while (sparse_pays(ix->K, ix->D, P, ix->L, n) && (int64_t)sparse_bytes(ix->K, ix->D, P, ix->L, n) > ix->scratch_limit) {
+    while (sparse_pays(ix->K, ix->D, P, ix->L, n) && !fits(n)) {
         if (n <= 128) return 0;
         n = (n / 2 + 127) & ~127ll;
     }
@@ -1125,20 +1139,14 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
     else if (tile >= 256) tile -= tile % 256;   // whole blocks of the padded row count
     else if (tile >= GT) tile -= tile % GT;
 
-    int64_t sparse_n = sparse_tile(ix, nprobe, nq);
-    if (sparse_n > 0 && (rc = ensure(ix->sparse, sparse_bytes(K, ix->D, nprobe, ix->L, sparse_n)))) {
-        if (rc != IVF_ENOMEM) return rc;
-        sparse_n = 0;                                            // (no room: with the distance matrix, in as many passes as its limit asks for)
-    }
-    const bool sparse = sparse_n > 0;
-    if (sparse) tile = sparse_n;
-    const SearchPlan pl = plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr, true, sparse);
+    const int64_t sparse_n = sparse_tile(ix, nprobe, S, k, nq, tile);
+    const SearchPlan pl = sparse_n > 0 ? plan_without_matrix(ix, nprobe, S, k, sparse_n)
+                                       : plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr);
     Buf *bufs[WS_COUNT] = {&ix->dt, &ix->bm, &ix->qn, &ix->qsi, &ix->qpk, &ix->probe_id, &ix->probe_d,
                            &ix->desc, &ix->lut, &ix->partial, &ix->qrot};
     for (int i = 0; i < WS_COUNT; ++i)
         if ((rc = ensure(*bufs[i], pl.bytes[i]))) return rc;
     SearchWs ws;
-    ws.sparse = static_cast<unsigned char *>(ix->sparse.p);
     ws.dt = static_cast<float *>(ix->dt.p);
     ws.bm = static_cast<float *>(ix->bm.p);
     ws.qn = static_cast<float *>(ix->qn.p);

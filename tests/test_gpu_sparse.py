@@ -106,3 +106,31 @@ def test_way_by_the_number_of_neighbours(L, nq, ways):
     ivf.ivf_search(h, q, 16, 0.1, 10)
     assert tuple(a - b for a, b in zip(ivf.ivf_search_stats(), before)) == ways
     ivf.ivf_free_index(h)
+
+
+def test_scratch_keeps_to_the_limit():
+    """Passes without the distance matrix are of more queries than passes with it: descriptors, tables and lists of all of
+    them count.  A handle that has seen both kinds holds one buffer for both."""
+    import torch
+    import paper_1802_02422_amd as ivf
+    K, nq, limit = 65_536, 40_000, 1 << 30
+    h, cent, g = make(K, 32, 32, 16, 9, 1.0, 0.0)
+    q = (cent[torch.randint(0, K, (nq,), generator=g, device="cuda")] + 0.5 * torch.randn(nq, 32, generator=g, device="cuda")).contiguous()
+    ids, dists = (torch.empty(nq, 1000, dtype=t, device="cuda") for t in (torch.int32, torch.float32))
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    before = ivf.ivf_search_stats()
+    ivf.ivf_set_scratch_limit(h, limit)
+    ivf.ivf_search(h, q, 16, 1.0, 1000, ids, dists)
+    without, matrix = (a - b for a, b in zip(ivf.ivf_search_stats(), before))
+    assert without >= 2 and matrix == 0
+    ivf.ivf_search(h, q[:1024], 16, 1.0, 1000, ids[:1024], dists[:1024])
+    assert ivf.ivf_search_stats()[1] == before[1] + 1
+    torch.cuda.synchronize()
+    held = free - torch.cuda.mem_get_info()[0]
+    assert held <= limit, held
+    again = torch.empty_like(ids), torch.empty_like(dists)
+    ivf.ivf_set_scratch_limit(h, 16 << 30)
+    ivf.ivf_search(h, q, 16, 1.0, 1000, *again)
+    assert torch.equal(ids, again[0]) and torch.equal(dists, again[1])
+    ivf.ivf_free_index(h)
