@@ -149,7 +149,11 @@ int ivf_set_scratch_limit(ivf_index *index, int64_t bytes);
  * frees and re-allocates; a call that fits what is there allocates nothing,
  * clears nothing with memset nodes and can be captured into a HIP graph (a
  * graph captured earlier holds the old addresses and is void once a later
- * call has grown the scratch).
+ * call has grown the scratch).  Where the GPU has no memory for a pass without
+ * the distance tile, the call and those after it take smaller passes or the
+ * tile (until ivf_set_scratch_limit is called again); where it has none for
+ * the tile, the handle gives up its tables for the other way (up to 0.5 KB a
+ * region) for good if that makes room for it.
  */
 int ivf_search(ivf_index *index, const float *queries, int64_t nq, int nprobe, float prune_frac,
                int k, int32_t *out_ids, float *out_dists, void *hip_stream);

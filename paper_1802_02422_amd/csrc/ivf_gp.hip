@@ -346,6 +346,12 @@ struct SearchPlan {
     int64_t tile = 0;            // queries per pass
     int S = 0, nsplit = 1, n_lists = 0, merge_n = 0, merge_pow2 = 0;
     size_t bytes[WS_COUNT] = {};
+    size_t total() const
+    {
+        size_t sum = 0;
+        for (size_t b : bytes) sum += b;
+        return sum;
+    }
 };
 
 // Rows of the distance tile (and of the block minima) a pass over n queries may write: the sweep
@@ -433,7 +439,9 @@ struct ivf_index {
     int32_t *nbr = nullptr, *ids = nullptr;
     uint4 *sub_info = nullptr;   // per subregion: block offset, first position, length
     uint8_t *blocks = nullptr;
+    size_t chi_bytes = 0;        // of that allocation
     int64_t scratch_limit = 8ll << 30;
+    size_t no_room = SIZE_MAX;   // scratch of the smallest pass without the distance matrix that there was no memory for
     Buf dt, bm, qn, qpk, qsi, probe_id, probe_d, desc, lut, partial, qrot;
     // optional per-stage timing with HIP events on the caller's stream
     bool profile = false;
@@ -473,6 +481,7 @@ extern "C" int ivf_set_scratch_limit(ivf_index *ix, int64_t bytes)
 {
     if (!ix || bytes < 4096) return fail(IVF_EINVAL, "scratch limit must be at least 4096 bytes");
     ix->scratch_limit = bytes;
+    ix->no_room = SIZE_MAX;
     return IVF_OK;
 }
 
@@ -604,7 +613,8 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
             place(ix->order_inv, (size_t)K);
             return total;
         };
-        const hipError_t e = g_pool.fresh(reinterpret_cast<void **>(&ix->chi), all());
+        ix->chi_bytes = all();
+        const hipError_t e = g_pool.fresh(reinterpret_cast<void **>(&ix->chi), ix->chi_bytes);
         if (e != hipSuccess && e != hipErrorOutOfMemory) HIPCHK(e);
         if (e != hipSuccess) ix->chi = nullptr;                  // (no room: searches go with the distance matrix)
         else (void)all();
@@ -1108,9 +1118,7 @@ int64_t sparse_tile(const ivf_index *ix, int P, int S, int k, int64_t nq, int64_
     if (!ix->chi || P > PS_P_MAX || (int64_t)P * ix->L > 16384) return 0;
     auto fits = [&](int64_t n) {
         const SearchPlan pl = plan_without_matrix(ix, P, S, k, n);
-        size_t total = 0;
-        for (size_t b : pl.bytes) total += b;
-        return (n <= tile ? pl.bytes[WS_DT] : total) <= (size_t)ix->scratch_limit;
+        return (n <= tile ? pl.bytes[WS_DT] : pl.total()) <= (size_t)ix->scratch_limit && pl.total() < ix->no_room;
     };
     int64_t n = nq < (1 << 20) ? nq : (1 << 20);
     while (sparse_pays(ix->K, ix->D, P, ix->L, n) && !fits(n)) {
@@ -1118,6 +1126,13 @@ int64_t sparse_tile(const ivf_index *ix, int P, int S, int k, int64_t nq, int64_
         n = (n / 2 + 127) & ~127ll;
     }
     return sparse_pays(ix->K, ix->D, P, ix->L, n) ? n : 0;
+}
+
+// Whether `bytes` of scratch find room once the tables of the search without the distance matrix have gone
+bool room_without_tables(const ivf_index *ix, size_t bytes)
+{
+    size_t left = 0, all = 0;
+    return ix->chi && hipMemGetInfo(&left, &all) == hipSuccess && left + ix->chi_bytes >= bytes;
 }
 
 // The query path on the handle's own growable scratch (allocates when a call needs more than any before).
@@ -1139,13 +1154,31 @@ int search_alloc(ivf_index *ix, const float *queries, int64_t nq, int nprobe, fl
     else if (tile >= 256) tile -= tile % 256;   // whole blocks of the padded row count
     else if (tile >= GT) tile -= tile % GT;
 
-    const int64_t sparse_n = sparse_tile(ix, nprobe, S, k, nq, tile);
-    const SearchPlan pl = sparse_n > 0 ? plan_without_matrix(ix, nprobe, S, k, sparse_n)
-                                       : plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr);
+    // Where memory is short, smaller passes without the matrix, then with it, then with it and without the tables of the other way
+    SearchPlan pl;
     Buf *bufs[WS_COUNT] = {&ix->dt, &ix->bm, &ix->qn, &ix->qsi, &ix->qpk, &ix->probe_id, &ix->probe_d,
                            &ix->desc, &ix->lut, &ix->partial, &ix->qrot};
-    for (int i = 0; i < WS_COUNT; ++i)
-        if ((rc = ensure(*bufs[i], pl.bytes[i]))) return rc;
+    while (true) {
+        const int64_t n = sparse_tile(ix, nprobe, S, k, nq, tile);
+        pl = n > 0 ? plan_without_matrix(ix, nprobe, S, k, n) : plan_search(K, ix->D, ix->M, nprobe, S, mean_length(ix), k, tile, ix->rot_t != nullptr);
+        for (int i = 0; i < WS_COUNT && !rc; ++i) rc = ensure(*bufs[i], pl.bytes[i]);
+        if (rc != IVF_ENOMEM) break;
+        HIPCHK(hipDeviceSynchronize());
+        for (Buf *b : bufs) {
+            if (b->p) HIPCHK(hipFree(b->p));
+            *b = Buf();
+        }
+        if (n > 0) {
+            ix->no_room = pl.total();
+        } else if (room_without_tables(ix, pl.total())) {
+            HIPCHK(hipFree(ix->chi));
+            ix->chi = nullptr;
+        } else {
+            break;
+        }
+        rc = IVF_OK;
+    }
+    if (rc) return rc;
     SearchWs ws;
     ws.dt = static_cast<float *>(ix->dt.p);
     ws.bm = static_cast<float *>(ix->bm.p);

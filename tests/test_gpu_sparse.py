@@ -134,3 +134,77 @@ def test_scratch_keeps_to_the_limit():
     ivf.ivf_search(h, q, 16, 1.0, 1000, *again)
     assert torch.equal(ids, again[0]) and torch.equal(dists, again[1])
     ivf.ivf_free_index(h)
+
+
+def fill_memory(leave):
+    """Takes all of the GPU's memory but `leave` bytes."""
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    while torch.cuda.mem_get_info()[0] > leave + (8 << 20):
+        held.append(torch.empty(min(8 << 30, torch.cuda.mem_get_info()[0] - leave), dtype=torch.uint8, device="cuda"))
+    return held
+
+
+def test_no_memory_for_a_whole_batch():
+    """Less memory than the batch's pass asks for, and the limit allows: it goes in smaller ones, and so do the next."""
+    import torch
+    import paper_1802_02422_amd as ivf
+    K, nq = 65_536, 40_000
+    h, cent, g = make(K, 32, 32, 16, 9, 1.0, 0.0)
+    q = (cent[torch.randint(0, K, (nq,), generator=g, device="cuda")] + 0.5 * torch.randn(nq, 32, generator=g, device="cuda")).contiguous()
+    ids, dists = (torch.empty(nq, 1000, dtype=t, device="cuda") for t in (torch.int32, torch.float32))
+    again = torch.empty_like(ids), torch.empty_like(dists)
+    ivf.ivf_set_scratch_limit(h, 1 << 30)
+    ivf.ivf_search(h, q, 16, 1.0, 1000, ids, dists)
+    ivf.ivf_free_index(h)
+    h, cent, g = make(K, 32, 32, 16, 9, 1.0, 0.0)
+    ivf.ivf_set_scratch_limit(h, 16 << 30)
+    held = fill_memory(2 << 30)                               # (a pass of all of them takes 2.9 GB)
+    try:
+        passes = []
+        for _ in range(2):
+            before = ivf.ivf_search_stats()
+            ivf.ivf_search(h, q, 16, 1.0, 1000, *again)
+            torch.cuda.synchronize()
+            passes.append(tuple(a - b for a, b in zip(ivf.ivf_search_stats(), before)) + torch.cuda.mem_get_info())
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert passes[0][0] >= 2 and passes[0][1] == 0 and passes[0] == passes[1]
+    assert torch.equal(ids, again[0]) and torch.equal(dists, again[1])
+    ivf.ivf_free_index(h)
+
+
+def test_no_memory_beside_the_tables():
+    """A batch that goes with the matrix, and has no room for it beside the tables of the other way."""
+    import torch
+    import paper_1802_02422_amd as ivf
+    K = 1 << 20
+    h, cent, g = make(K, 96, 64, 8, 9, 1.0, 0.0)
+    q = cent[torch.randint(0, K, (256,), generator=g, device="cuda")].contiguous()
+    few = q[:16].contiguous()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ref = ivf.ivf_search(h, q, 300, 0.2, 10)
+    before = ivf.ivf_search_stats()
+    small = ivf.ivf_search(h, few, 16, 0.2, 10)
+    assert ivf.ivf_search_stats()[0] == before[0] + 1
+    torch.cuda.synchronize()
+    need = free - torch.cuda.mem_get_info()[0]
+    ivf.ivf_free_index(h)
+    h = make(K, 96, 64, 8, 9, 1.0, 0.0)[0]
+    ivf.ivf_free_index(make(1000, 32, 8, 8, 1, 1.0, 0.0)[0])    # (gives back what the library keeps for index-time calls)
+    held = fill_memory(need - (200 << 20))
+    try:
+        got = ivf.ivf_search(h, q, 300, 0.2, 10)
+        before = ivf.ivf_search_stats()
+        less = ivf.ivf_search(h, few, 16, 0.2, 10)
+        assert ivf.ivf_search_stats()[1] == before[1] + 1
+        torch.cuda.synchronize()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert all(torch.equal(a, b) for a, b in zip(got + less, ref + small))
+    ivf.ivf_free_index(h)
