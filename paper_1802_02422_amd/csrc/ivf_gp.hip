@@ -571,6 +571,50 @@ int dev_copy(T *&dst, const T *src, size_t count, hipStream_t st)
     return IVF_OK;
 }
 
+// The tables of the search without the distance matrix, from the index's copies of centroids and neighbours
+int load_sparse_tables(ivf_index *ix, hipStream_t st)
+{
+    const int64_t K = ix->K, nsub = K * ix->L, tiles = (K + GT - 1) / GT, pad = packed_rows(K);
+    const int D = ix->D, L = ix->L, Dp = packed_dim(D);
+    int rc;
+    size_t total = 0;
+    auto place = [&](auto *&p, size_t count) {                   // pieces of one allocation, which starts with chi
+        p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(reinterpret_cast<unsigned char *>(ix->chi) + total);
+        total += (count * sizeof(*p) + 255) / 256 * 256;
+    };
+    auto all = [&]() {
+        total = ((size_t)pad * Dp * sizeof(_Float16) + 255) / 256 * 256;
+        place(ix->clen, (size_t)pad);
+        place(ix->mstart, (size_t)tiles * GT);
+        place(ix->mtile, (size_t)tiles);
+        place(ix->nbr_norm, (size_t)nsub);
+        place(ix->order, (size_t)K);
+        place(ix->order_inv, (size_t)K);
+        return total;
+    };
+    ix->chi_bytes = all();
+    HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->chi), ix->chi_bytes));
+    (void)all();
+    pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(ix->centroids, K, pad, D, Dp,
+                                                                                 reinterpret_cast<uint32_t *>(ix->csi + 1), ix->chi, ix->clen);
+    LAUNCHCHK("pack_hi_rows_kernel");
+    minima_tiles_kernel<<<dim3((unsigned)tiles), dim3(128), 0, st>>>(ix->clen, K, Dp, ix->mstart, ix->mtile);
+    LAUNCHCHK("minima_tiles_kernel");
+    neighbour_norm_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->nbr, nsub, ix->cnorm, ix->nbr_norm);
+    LAUNCHCHK("neighbour_norm_kernel");
+    RadixBufs rb;
+    StreamWait before_they_go(st);
+    if ((rc = rb.init(K))) return rc;
+    uint32_t *keys, *order;
+    if ((rc = launch_region_keys(ix->nbr, K, L, ix->order_inv, rb.keys_a(), st))) return rc;
+    if ((rc = rb.sort(K, SHINGLE_BITS, false, &keys, &order, st))) return rc;
+    HIPCHK(hipMemcpyAsync(ix->order, order, (size_t)K * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+    inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(ix->order, K, ix->order_inv);
+    LAUNCHCHK("inverse_kernel");
+    HIPCHK(hipStreamSynchronize(st));
+    return IVF_OK;
+}
+
 int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
 {
     const int64_t K = d->K, N = d->N, nsub = K * d->L;
@@ -595,50 +639,6 @@ int load_impl(const ivf_index_desc *d, hipStream_t st, ivf_index *ix)
     HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->csi), 2 * sizeof(float)));
     if ((rc = pack_rows(ix->centroids, K, D, reinterpret_cast<uint32_t *>(ix->csi + 1), ix->cpk, ix->cnorm, ix->csi, st)))
         return rc;
-    if (sparse_table(K, D)) {
-        const int Dp = packed_dim(D);
-        const int64_t tiles = (K + GT - 1) / GT, pad = packed_rows(K);
-        size_t total = 0;
-        auto place = [&](auto *&p, size_t count) {               // pieces of one allocation, which starts with chi
-            p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(reinterpret_cast<unsigned char *>(ix->chi) + total);
-            total += (count * sizeof(*p) + 255) / 256 * 256;
-        };
-        auto all = [&]() {
-            total = ((size_t)pad * Dp * sizeof(_Float16) + 255) / 256 * 256;
-            place(ix->clen, (size_t)pad);
-            place(ix->mstart, (size_t)tiles * GT);
-            place(ix->mtile, (size_t)tiles);
-            place(ix->nbr_norm, (size_t)nsub);
-            place(ix->order, (size_t)K);
-            place(ix->order_inv, (size_t)K);
-            return total;
-        };
-        ix->chi_bytes = all();
-        const hipError_t e = g_pool.fresh(reinterpret_cast<void **>(&ix->chi), ix->chi_bytes);
-        if (e != hipSuccess && e != hipErrorOutOfMemory) HIPCHK(e);
-        if (e != hipSuccess) ix->chi = nullptr;                  // (no room: searches go with the distance matrix)
-        else (void)all();
-    }
-    if (ix->chi) {
-        const int Dp = packed_dim(D);
-        const int64_t tiles = (K + GT - 1) / GT, pad = packed_rows(K);
-        pack_hi_rows_kernel<<<dim3((unsigned)((pad + 15) / 16)), dim3(256), 0, st>>>(ix->centroids, K, pad, D, Dp,
-                                                                                     reinterpret_cast<uint32_t *>(ix->csi + 1), ix->chi, ix->clen);
-        LAUNCHCHK("pack_hi_rows_kernel");
-        minima_tiles_kernel<<<dim3((unsigned)tiles), dim3(128), 0, st>>>(ix->clen, K, Dp, ix->mstart, ix->mtile);
-        LAUNCHCHK("minima_tiles_kernel");
-        neighbour_norm_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->nbr, nsub, ix->cnorm, ix->nbr_norm);
-        LAUNCHCHK("neighbour_norm_kernel");
-        RadixBufs rb;
-        StreamWait before_they_go(st);
-        if ((rc = rb.init(K))) return rc;
-        uint32_t *keys, *order;
-        if ((rc = launch_region_keys(ix->nbr, K, L, ix->order_inv, rb.keys_a(), st))) return rc;
-        if ((rc = rb.sort(K, SHINGLE_BITS, false, &keys, &order, st))) return rc;
-        HIPCHK(hipMemcpyAsync(ix->order, order, (size_t)K * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
-        inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(ix->order, K, ix->order_inv);
-        LAUNCHCHK("inverse_kernel");
-    }
     HIPCHK(g_pool.fresh(reinterpret_cast<void **>(&ix->cst), (size_t)nsub * sizeof(float)));
     cst_kernel<<<dim3((unsigned)((nsub + 255) / 256)), dim3(256), 0, st>>>(ix->alpha, d->cs_dist2, L, nsub, ix->cst);
     LAUNCHCHK("cst_kernel");
@@ -690,6 +690,12 @@ extern "C" int ivf_load_index(const ivf_index_desc *d, void *hip_stream, ivf_ind
     ivf_index *ix = new (std::nothrow) ivf_index;
     if (!ix) return fail(IVF_ENOMEM, "host allocation failed");
     rc = load_impl(d, static_cast<hipStream_t>(hip_stream), ix);
+    // last, and without the scratch of the rest: where there is no room for them searches go with the distance matrix
+    if (!rc && sparse_table(ix->K, ix->D) && (rc = load_sparse_tables(ix, static_cast<hipStream_t>(hip_stream))) == IVF_ENOMEM) {
+        if (ix->chi) (void)hipFree(ix->chi);
+        ix->chi = nullptr;
+        rc = IVF_OK;
+    }
     if (rc) {
         std::string keep = g_err;
         ivf_free_index(ix);

@@ -5,7 +5,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def make(K, D, L, M, seed, spread, offset):
+def make_desc(K, D, L, M, seed, spread, offset):
     import torch
     import paper_1802_02422_amd as ivf
     g = torch.Generator(device="cuda").manual_seed(seed)
@@ -21,6 +21,12 @@ def make(K, D, L, M, seed, spread, offset):
                          sub_offsets=off, codes=torch.randint(0, 256, (n, M), generator=g, device="cuda", dtype=torch.uint8),
                          const_byte=torch.randint(0, 256, (n,), generator=g, device="cuda", dtype=torch.uint8),
                          ids=torch.randperm(n, generator=g, device="cuda").int())
+    return desc, cent, g
+
+
+def make(*args):
+    import paper_1802_02422_amd as ivf
+    desc, cent, g = make_desc(*args)
     return ivf.ivf_load_index(desc), cent, g
 
 
@@ -207,4 +213,35 @@ def test_no_memory_beside_the_tables():
         del held
         torch.cuda.empty_cache()
     assert all(torch.equal(a, b) for a, b in zip(got + less, ref + small))
+    ivf.ivf_free_index(h)
+
+
+def test_no_memory_for_the_tables():
+    """An index that can be loaded, but not with the tables of the search without the matrix: it goes with the matrix."""
+    import torch
+    import paper_1802_02422_amd as ivf
+    K = 1 << 20
+    desc, cent, g = make_desc(K, 128, 8, 8, 9, 1.0, 0.0)      # (312 bytes a region; sizes and offsets on the way 64)
+    q = cent[torch.randint(0, K, (16,), generator=g, device="cuda")].contiguous()
+    small = [make_desc(1000, 32, 8, 8, 1, 1.0, 0.0)[0] for _ in range(2)]
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    h = ivf.ivf_load_index(desc)
+    ivf.ivf_free_index(ivf.ivf_load_index(small[0]))          # (gives back what the library keeps for index-time calls)
+    need = free - torch.cuda.mem_get_info()[0]
+    ref = ivf.ivf_search(h, q, 16, 0.2, 10)
+    ivf.ivf_free_index(h)
+    held = fill_memory(need - (200 << 20))
+    try:
+        h = ivf.ivf_load_index(desc)
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    ivf.ivf_free_index(ivf.ivf_load_index(small[1]))
+    before = ivf.ivf_search_stats()
+    got = ivf.ivf_search(h, q, 16, 0.2, 10)
+    torch.cuda.synchronize()
+    assert ivf.ivf_search_stats()[1] == before[1] + 1
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
     ivf.ivf_free_index(h)
