@@ -440,6 +440,7 @@ struct ivf_index {
     uint4 *sub_info = nullptr;   // per subregion: block offset, first position, length
     uint8_t *blocks = nullptr;
     size_t chi_bytes = 0;        // of that allocation
+    uint32_t hard = 0;           // of SPARSE_DIRECT centroids
     int64_t scratch_limit = 8ll << 30;
     size_t no_room = SIZE_MAX;   // scratch of the smallest pass without the distance matrix that there was no memory for
     Buf dt, bm, qn, qpk, qsi, probe_id, probe_d, desc, lut, partial, qrot;
@@ -571,6 +572,14 @@ int dev_copy(T *&dst, const T *src, size_t count, hipStream_t st)
     return IVF_OK;
 }
 
+// Of SPARSE_DIRECT centroids of the index, as queries, those whose bound leaves too many blocks: with any of them small batches go with
+// the matrix, with more than SPARSE_HARD all do.  A hard query costs exact block minima of a tile of queries over the whole table (one of
+// them alone, K = 2^20, P = 16 254 us, with the matrix 133; in a batch of 64 272 and 207), in a large batch its share of the distance GEMM:
+// 10 000, K = 2^20, P = 16, with 160 of the 256 7.57 ms, 210 11.4 - 11.8, all 14.6, with the matrix 10.7; none of them 3.1.
+// Centroids as far from the origin as four times their spread are such, up to twice it they are not.
+constexpr uint32_t SPARSE_HARD = 160;
+int count_hard(const ivf_index *ix, hipStream_t st, uint32_t *hard);
+
 // The tables of the search without the distance matrix, from the index's copies of centroids and neighbours
 int load_sparse_tables(ivf_index *ix, hipStream_t st)
 {
@@ -611,7 +620,10 @@ int load_sparse_tables(ivf_index *ix, hipStream_t st)
     HIPCHK(hipMemcpyAsync(ix->order, order, (size_t)K * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
     inverse_kernel<<<dim3(grid_for(K)), dim3(256), 0, st>>>(ix->order, K, ix->order_inv);
     LAUNCHCHK("inverse_kernel");
-    HIPCHK(hipStreamSynchronize(st));
+    if ((rc = count_hard(ix, st, &ix->hard))) return rc;
+    if (ix->hard <= SPARSE_HARD) return IVF_OK;
+    HIPCHK(hipFree(ix->chi));
+    ix->chi = nullptr;
     return IVF_OK;
 }
 
@@ -814,20 +826,16 @@ int plan_lds(const ivf_index *ix, int P, int k, const SearchPlan &pl, LdsPlan &l
     return IVF_OK;
 }
 
-// Stages 1 and 2 without the distance matrix: probes to pid and pd, the keys of the scores to ws.sparse() (SP_BIG).
-template <class Mark>
-int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchWs &ws, int32_t *pid, float *pd, Mark mark, hipStream_t st)
+// The first half of launch_sparse: the blocks that can hold one of a query's P closest, and the hard queries (a.total[0] of them).
+int launch_flags(const ivf_index *ix, const float *Q, int64_t n, int P, const SearchWs &ws, const SparsePlan &sp, SparseArgs &a, hipStream_t st)
 {
     const int64_t K = ix->K;
     const int D = ix->D, L = ix->L, Dp = packed_dim(D), nb = (int)((K + BMW - 1) / BMW);
-    const SparsePlan sp = plan_sparse(K, D, P, L, n);
     auto piece = [&](auto *&p, int i) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(ws.sparse() + sp.off[i]); };
-    int rc;
     _Float16 *qh;
     float2 *qlen;
     piece(qh, SP_QH);
     piece(qlen, SP_QLEN);
-    SparseArgs a;
     piece(a.best, SP_BEST);
     piece(a.n_flag, SP_FLAG);
     piece(a.blist, SP_LIST);
@@ -864,8 +872,8 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     a.Cp = ix->cpk;
     a.cnorm = ix->cnorm;
     a.csi = ix->csi;
-    a.probe_id = pid;
-    a.probe_d = pd;
+    a.probe_id = nullptr;
+    a.probe_d = nullptr;
     a.nbr = ix->nbr;
     a.nbr_norm = ix->nbr_norm;
     a.cst = ix->cst;
@@ -890,7 +898,6 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     else if (Dp == 96) sweep(&coarse_minima_kernel<3>);
     else sweep(&coarse_minima_kernel<4>);
     LAUNCHCHK("coarse_minima_kernel");
-    const bool wide = nb > 4096;                                // (16 blocks a thread at most)
     // pieces: at least 8 P of them (sparse_pays: the table has at least 8 P tiles), or 2048
     const dim3 gq((unsigned)n);
     static_assert(PS_NB_MAX <= 2 * 4 * 4 * 512, "four pieces of four tiles a thread, 512 threads");
@@ -899,6 +906,22 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     else if (tiles_c <= 4096) flag_blocks_kernel<512, 2, 4><<<gq, dim3(512), 0, st>>>(a);
     else flag_blocks_kernel<512, 4, 4><<<gq, dim3(512), 0, st>>>(a);
     LAUNCHCHK("flag_blocks_kernel");
+    return IVF_OK;
+}
+
+// Stages 1 and 2 without the distance matrix: probes to pid and pd, the keys of the scores to ws.sparse() (SP_BIG).
+template <class Mark>
+int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchWs &ws, int32_t *pid, float *pd, Mark mark, hipStream_t st)
+{
+    const int64_t K = ix->K;
+    const int L = ix->L, Dp = packed_dim(ix->D), nb = (int)((K + BMW - 1) / BMW);
+    const SparsePlan sp = plan_sparse(K, ix->D, P, L, n);
+    SparseArgs a;
+    int rc;
+    if ((rc = launch_flags(ix, Q, n, P, ws, sp, a, st))) return rc;
+    a.probe_id = pid;
+    a.probe_d = pd;
+    const bool wide = nb > 4096;                                // (16 blocks a thread at most)
     hard_minima_kernel<<<dim3(1024), dim3(256), 0, st>>>(a);
     LAUNCHCHK("hard_minima_kernel");
     if (wide) hard_flag_kernel<1024><<<dim3(512), dim3(1024), 0, st>>>(a);
@@ -935,6 +958,34 @@ int launch_sparse(ivf_index *ix, const float *Q, int64_t n, int P, const SearchW
     if ((rc = mark(2))) return rc;
     if (!sp.direct && (rc = grouped(a.region_count, K, a.total + 3, pid, P, nullptr, ix->order, ix->order_inv))) return rc;
     if ((rc = pairs(std::true_type(), sp.region_items, a.total + 4))) return rc;
+    return IVF_OK;
+}
+
+// Of SPARSE_DIRECT centroids of the index, as queries for 16 regions: those whose bound leaves too many blocks
+int count_hard(const ivf_index *ix, hipStream_t st, uint32_t *hard)
+{
+    const int64_t n = SPARSE_DIRECT, pad = packed_rows(n);
+    const int D = ix->D, P = 16;
+    const SparsePlan sp = plan_sparse(ix->K, D, P, ix->L, n);
+    DevTmp rows, packed, norm, scale, mem;
+    StreamWait before_they_go(st);
+    HIPCHK(rows.alloc((size_t)n * D * sizeof(float)));
+    HIPCHK(packed.alloc((size_t)pad * packed_dim(D) * 2 * sizeof(_Float16)));
+    HIPCHK(norm.alloc((size_t)pad * sizeof(float)));
+    HIPCHK(scale.alloc((size_t)pad * sizeof(float)));
+    HIPCHK(mem.alloc(sp.total));
+    SearchWs ws;
+    ws.dt = static_cast<float *>(mem.p);
+    ws.qn = static_cast<float *>(norm.p);
+    ws.qsi = static_cast<float *>(scale.p);
+    ws.qpk = static_cast<_Float16 *>(packed.p);
+    const size_t row = (size_t)D * sizeof(float);
+    HIPCHK(hipMemcpy2DAsync(rows.p, row, ix->centroids, (size_t)(ix->K / n) * row, row, (size_t)n, hipMemcpyDeviceToDevice, st));
+    SparseArgs a;
+    int rc;
+    if ((rc = launch_flags(ix, static_cast<const float *>(rows.p), n, P, ws, sp, a, st))) return rc;
+    HIPCHK(hipMemcpyAsync(hard, a.total, sizeof(*hard), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
     return IVF_OK;
 }
 
@@ -1126,12 +1177,13 @@ int64_t sparse_tile(const ivf_index *ix, int P, int S, int k, int64_t nq, int64_
         const SearchPlan pl = plan_without_matrix(ix, P, S, k, n);
         return (n <= tile ? pl.bytes[WS_DT] : pl.total()) <= (size_t)ix->scratch_limit && pl.total() < ix->no_room;
     };
+    auto pays = [&](int64_t n) { return (n > SPARSE_DIRECT || ix->hard == 0) && sparse_pays(ix->K, ix->D, P, ix->L, n); };
     int64_t n = nq < (1 << 20) ? nq : (1 << 20);
-    while (sparse_pays(ix->K, ix->D, P, ix->L, n) && !fits(n)) {
+    while (pays(n) && !fits(n)) {
         if (n <= 128) return 0;
         n = (n / 2 + 127) & ~127ll;
     }
-    return sparse_pays(ix->K, ix->D, P, ix->L, n) ? n : 0;
+    return pays(n) ? n : 0;
 }
 
 // Whether `bytes` of scratch find room once the tables of the search without the distance matrix have gone

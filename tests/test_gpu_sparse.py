@@ -30,8 +30,8 @@ def make(*args):
     return ivf.ivf_load_index(desc), cent, g
 
 
-# partial last tiles and blocks, every packed width, L below, at and above a group of 64 neighbours and of odd length; "hard": bounds
-# too wide for every query; "some": queries too large for the table's scale, without a finite length, zero, and equal to centroids
+# partial last tiles and blocks, every packed width, L below, at and above a group of 64 neighbours and of odd length; "hard": queries
+# far from the table, all without a bound; "some": queries too large for the table's scale, without a finite length, zero, and equal to centroids
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
     (16_400, 96, 64, 16, 16, 9000, "plain"), (16_385, 32, 7, 8, 13, 8500, "plain"), (20_033, 64, 65, 16, 16, 7001, "plain"), (16_500, 32, 128, 8, 12, 8200, "plain"),
     (17_000, 128, 33, 16, 8, 9000, "plain"), (70_001, 48, 64, 8, 60, 4200, "plain"), (16_400, 96, 32, 16, 16, 8300, "hard"),
@@ -39,9 +39,9 @@ def make(*args):
 def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     import torch
     import paper_1802_02422_amd as ivf
-    h, cent, g = make(K, D, L, M, K + D, 0.01 if kind == "hard" else 1.0, 50.0 if kind == "hard" else 0.0)
+    h, cent, g = make(K, D, L, M, K + D, 1.0, 0.0)
     q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")]
-    q = (q + 0.5 * (cent.std() if kind == "hard" else 1.0) * torch.randn(nq, D, generator=g, device="cuda")).contiguous()
+    q = (q + 0.5 * torch.randn(nq, D, generator=g, device="cuda") + (50.0 if kind == "hard" else 0.0)).contiguous()
     if kind == "some":
         q[::7] *= 1e5
         q[3::11] = 0.0
@@ -63,16 +63,16 @@ def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     ivf.ivf_free_index(h)
 
 
-# batches whose pairs are not grouped: one query, odd numbers, the largest; bounds too wide for every query or for some
+# batches whose pairs are not grouped: one query, odd numbers, the largest; no bound for every query or for some
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
     (300_000, 32, 8, 8, 16, 100, "plain"), (262_144, 96, 64, 16, 64, 1, "plain"), (270_001, 64, 33, 16, 20, 33, "plain"),
     (262_144, 128, 65, 8, 16, 129, "plain"), (262_144, 96, 16, 16, 16, 70, "hard"), (262_144, 96, 16, 16, 16, 256, "some")])
 def test_small_batches_same_bits(K, D, L, M, P, nq, kind):
     import torch
     import paper_1802_02422_amd as ivf
-    h, cent, g = make(K, D, L, M, K + D, 0.01 if kind == "hard" else 1.0, 50.0 if kind == "hard" else 0.0)
+    h, cent, g = make(K, D, L, M, K + D, 1.0, 0.0)
     q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")]
-    q = (q + 0.5 * (cent.std() if kind == "hard" else 1.0) * torch.randn(nq, D, generator=g, device="cuda")).contiguous()
+    q = (q + 0.5 * torch.randn(nq, D, generator=g, device="cuda") + (50.0 if kind == "hard" else 0.0)).contiguous()
     if kind == "some":
         q[::7] *= 1e5
         q[3::11] = 0.0
@@ -244,4 +244,17 @@ def test_no_memory_for_the_tables():
     torch.cuda.synchronize()
     assert ivf.ivf_search_stats()[1] == before[1] + 1
     assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    ivf.ivf_free_index(h)
+
+
+# a table far from the origin compared with its spread: bounds too wide for all its queries
+@pytest.mark.parametrize("K,P,nq,offset,way", [(65_536, 16, 4096, 0.0, 0), (65_536, 16, 4096, 50.0, 1), (262_144, 16, 64, 0.0, 0), (262_144, 16, 64, 50.0, 1)])
+def test_tables_with_wide_bounds_go_with_the_matrix(K, P, nq, offset, way):
+    import torch
+    import paper_1802_02422_amd as ivf
+    h, cent, g = make(K, 32, 8, 8, 6, 1.0, offset)
+    q = (cent[torch.randint(0, K, (nq,), generator=g, device="cuda")] + 0.5 * torch.randn(nq, 32, generator=g, device="cuda")).contiguous()
+    before = ivf.ivf_search_stats()
+    ivf.ivf_search(h, q, P, 0.3, 20)
+    assert ivf.ivf_search_stats()[way] == before[way] + 1
     ivf.ivf_free_index(h)
