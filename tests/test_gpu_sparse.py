@@ -1,17 +1,20 @@
 """Large batches go without the distance matrix: the same bits as the same queries in batches that go with it."""
-import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-def make_desc(K, D, L, M, seed, spread, offset):
+def make_desc(K, D, L, M, seed, spread, offset, kind=""):
     import torch
     import paper_1802_02422_amd as ivf
     g = torch.Generator(device="cuda").manual_seed(seed)
     cent = torch.randn(K, D, generator=g, device="cuda") * spread + offset
+    if kind == "copies":                                      # 47 blocks and a bit of equal centroids
+        cent[1000:4030] = cent[1000]
     nbr = torch.randint(0, K, (K, L), generator=g, device="cuda", dtype=torch.int32)
     cs = torch.stack([((cent - cent[nbr[:, l].long()]) ** 2).sum(1) for l in range(L)], 1).contiguous()
+    if kind == "holes":                                       # distance 0 from everywhere, as with the matrix
+        cent[5000], cent[9000, 3] = float("nan"), float("inf")
     alpha = torch.rand(K, generator=g, device="cuda") * 0.3
     cb = torch.randn(M, 256, D // M, generator=g, device="cuda") * 0.1 * spread
     n = 2 * K * L
@@ -30,17 +33,36 @@ def make(*args):
     return ivf.ivf_load_index(desc), cent, g
 
 
+def ways(call, *args):
+    """(what the call returns, passes it took without the matrix, passes with it)"""
+    import paper_1802_02422_amd as ivf
+    before = ivf.ivf_search_stats()
+    got = call(*args)
+    after = ivf.ivf_search_stats()
+    return got, after[0] - before[0], after[1] - before[1]
+
+
+def same(got, ref):
+    import torch
+    for name in ref:
+        assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), name
+
+
 # partial last tiles and blocks, every packed width, L below, at and above a group of 64 neighbours and of odd length; "hard": queries
-# far from the table, all without a bound; "some": queries too large for the table's scale, without a finite length, zero, and equal to centroids
+# far from the table, all without a bound; "some": queries too large for the table's scale, without a finite length, zero, and equal to centroids;
+# "copies": more centroids at the same distance than the selection holds in LDS; "holes": centroids that are not finite
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
     (16_400, 96, 64, 16, 16, 9000, "plain"), (16_385, 32, 7, 8, 13, 8500, "plain"), (20_033, 64, 65, 16, 16, 7001, "plain"), (16_500, 32, 128, 8, 12, 8200, "plain"),
     (17_000, 128, 33, 16, 8, 9000, "plain"), (70_001, 48, 64, 8, 60, 4200, "plain"), (16_400, 96, 32, 16, 16, 8300, "hard"),
-    (16_640, 96, 16, 16, 16, 8300, "some"), (16_400, 96, 16, 16, 16, 8300, "equal")])
+    (16_640, 96, 16, 16, 16, 8300, "some"), (16_400, 96, 16, 16, 16, 8300, "equal"), (66_000, 32, 16, 8, 64, 4200, "copies"),
+    (16_600, 96, 16, 16, 16, 8300, "holes")])
 def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     import torch
     import paper_1802_02422_amd as ivf
-    h, cent, g = make(K, D, L, M, K + D, 1.0, 0.0)
-    q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")]
+    h, cent, g = make(K, D, L, M, K + D, 1.0, 0.0, kind)
+    q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")].nan_to_num(0.0, 0.0, 0.0)
+    if kind == "copies":
+        q[::3] = cent[1000]
     q = (q + 0.5 * torch.randn(nq, D, generator=g, device="cuda") + (50.0 if kind == "hard" else 0.0)).contiguous()
     if kind == "some":
         q[::7] *= 1e5
@@ -50,23 +72,29 @@ def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     if kind == "equal":                                       # every query the same: one block and one region have all pairs
         q[:] = q[0]
     ivf.ivf_set_scratch_limit(h, 16 << 30)
-    whole = ivf.ivf_search_stages(h, q, P, 0.3, 20)
-    parts = [ivf.ivf_search_stages(h, q[a:a + 500].contiguous(), P, 0.3, 20) for a in range(0, nq, 500)]
-    for name in whole:
-        got, ref = whole[name].cpu().numpy(), torch.cat([p[name] for p in parts]).cpu().numpy()
-        assert np.array_equal(got.view(np.uint8), ref.view(np.uint8)), name
-    # a scratch limit that cuts the batch in passes
-    ivf.ivf_set_scratch_limit(h, 1 << 30)
-    again = ivf.ivf_search_stages(h, q, P, 0.3, 20)
-    for name in whole:
-        assert torch.equal(again[name].view(torch.uint8), whole[name].view(torch.uint8)), name
+    whole, without, matrix = ways(ivf.ivf_search_stages, h, q, P, 0.3, 20)
+    assert (without, matrix) == (1, 0)
+    parts, without, matrix = ways(lambda: [ivf.ivf_search_stages(h, q[a:a + 500].contiguous(), P, 0.3, 20) for a in range(0, nq, 500)])
+    assert (without, matrix) == (0, len(parts))
+    same(whole, {name: torch.cat([p[name] for p in parts]) for name in whole})
+    # a scratch limit that cuts three times the batch into passes
+    q, whole = q.repeat(3, 1), {name: torch.cat([v] * 3) for name, v in whole.items()}
+    for mb in range(700, 50, -25):
+        ivf.ivf_set_scratch_limit(h, mb << 20)
+        again, without, matrix = ways(ivf.ivf_search_stages, h, q, P, 0.3, 20)
+        if without != 1 or matrix:
+            break
+    assert without > 1 and matrix == 0
+    same(again, whole)
     ivf.ivf_free_index(h)
 
 
-# batches whose pairs are not grouped: one query, odd numbers, the largest; no bound for every query or for some
+# batches whose pairs are not grouped: one query, odd numbers, the largest; no bound for every query or for some.  Tables of more than
+# 4096 blocks, whose queries without a bound take another kernel: such a batch, and one whose pairs are grouped
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
     (300_000, 32, 8, 8, 16, 100, "plain"), (262_144, 96, 64, 16, 64, 1, "plain"), (270_001, 64, 33, 16, 20, 33, "plain"),
-    (262_144, 128, 65, 8, 16, 129, "plain"), (262_144, 96, 16, 16, 16, 70, "hard"), (262_144, 96, 16, 16, 16, 256, "some")])
+    (262_144, 128, 65, 8, 16, 129, "plain"), (262_144, 96, 16, 16, 16, 70, "hard"), (262_144, 96, 16, 16, 16, 256, "some"),
+    (300_000, 32, 8, 8, 16, 40, "hard"), (300_001, 32, 8, 8, 16, 700, "some")])
 def test_small_batches_same_bits(K, D, L, M, P, nq, kind):
     import torch
     import paper_1802_02422_amd as ivf
@@ -77,11 +105,16 @@ def test_small_batches_same_bits(K, D, L, M, P, nq, kind):
         q[::7] *= 1e5
         q[3::11] = 0.0
         q[1, 0], q[2, 3] = float("nan"), float("inf")
-    got = ivf.ivf_search_stages(h, q, P, 0.3, 20)
+    got, without, matrix = ways(ivf.ivf_search_stages, h, q, P, 0.3, 20)
+    assert (without, matrix) == (1, 0)
     ivf.ivf_set_scratch_limit(h, 4 << 20)                     # less than such a pass takes: the distance matrix, a few queries at a time
-    ref = ivf.ivf_search_stages(h, q, P, 0.3, 20)
-    for name in ref:
-        assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), name
+    ref, without, matrix = ways(ivf.ivf_search_stages, h, q, P, 0.3, 20)
+    assert without == 0 and matrix >= 1
+    same(got, ref)
+    if nq <= 33:                                              # what fits the static array, always with the matrix
+        ids, d = torch.empty_like(ref["ids"]), torch.empty_like(ref["dists"])
+        ivf.ivf_search_noalloc(h, q, P, 0.3, 20, ids, d)
+        same({"ids": ids, "dists": d}, {"ids": ref["ids"], "dists": ref["dists"]})
     ivf.ivf_free_index(h)
 
 
@@ -92,12 +125,13 @@ def test_last_pass_of_a_large_batch_is_a_small_one():
     h, cent, g = make(262_144, 32, 8, 8, 5, 1.0, 0.0)
     q = (cent[torch.randint(0, 262_144, (2100,), generator=g, device="cuda")] + 0.5 * torch.randn(2100, 32, generator=g, device="cuda")).contiguous()
     ivf.ivf_set_scratch_limit(h, 16 << 30)
-    ref = ivf.ivf_search_stages(h, q, 16, 0.3, 20)
-    for mb in (45, 60, 20):
+    ref, without, matrix = ways(ivf.ivf_search_stages, h, q, 16, 0.3, 20)
+    assert (without, matrix) == (1, 0)
+    for mb, passes in ((45, (4, 0)), (60, (2, 0)), (20, (0, 105))):   # (640 a pass and 180 left; 1152 and 948; 20 with the matrix)
         ivf.ivf_set_scratch_limit(h, mb << 20)
-        got = ivf.ivf_search_stages(h, q, 16, 0.3, 20)
-        for name in ref:
-            assert torch.equal(got[name].view(torch.uint8), ref[name].view(torch.uint8)), (mb, name)
+        got, without, matrix = ways(ivf.ivf_search_stages, h, q, 16, 0.3, 20)
+        assert (without, matrix) == passes, mb
+        same(got, ref)
     ivf.ivf_free_index(h)
 
 
@@ -257,4 +291,43 @@ def test_tables_with_wide_bounds_go_with_the_matrix(K, P, nq, offset, way):
     before = ivf.ivf_search_stats()
     ivf.ivf_search(h, q, P, 0.3, 20)
     assert ivf.ivf_search_stats()[way] == before[way] + 1
+    ivf.ivf_free_index(h)
+
+
+@pytest.mark.parametrize("nq", [64, 1024])
+def test_replays_from_a_captured_graph(nq):
+    """Every replay, on other queries and with eager searches of both kinds of batches in between, returns the bits of the eager call."""
+    import torch
+    import paper_1802_02422_amd as ivf
+    K = 262_144
+    h, cent, g = make(K, 32, 8, 8, 4, 1.0, 0.0)
+    draw = lambda: (cent[torch.randint(0, K, (nq,), generator=g, device="cuda")] + 0.5 * torch.randn(nq, 32, generator=g, device="cuda")).contiguous()
+    q = draw()
+    eager, without, matrix = ways(ivf.ivf_search, h, q, 16, 0.3, 20)     # sizes the scratch buffers
+    assert (without, matrix) == (1, 0)
+    ivf.ivf_search(h, draw()[:50].contiguous(), 300, 0.3, 20)
+    ids, d = torch.empty_like(eager[0]), torch.empty_like(eager[1])
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ivf.ivf_search(h, q, 16, 0.3, 20, ids, d)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ivf.ivf_search(h, q, 16, 0.3, 20, ids, d)
+    for rep in range(4):
+        q.copy_(draw())
+        ids.fill_(-7)
+        d.fill_(-7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = ids.clone(), d.clone()
+        ivf.ivf_search(h, draw()[:50].contiguous(), 300 if rep % 2 else 16, 0.3, 20)
+        ref = ivf.ivf_search(h, q, 16, 0.3, 20)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), rep
+    del graph
     ivf.ivf_free_index(h)
