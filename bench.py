@@ -19,6 +19,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+FP16_PEAK_TFLOPS = 2500.0   # dense
 DESC_BYTES = 16          # one kept-subregion descriptor read by the scan
 
 # HBM bytes per launch from rocprofv3 hardware counters (FETCH_SIZE and WRITE_SIZE in KiB per dispatch, each
@@ -28,7 +29,6 @@ DESC_BYTES = 16          # one kept-subregion descriptor read by the scan
 # None where no counter run has been made for the workload.
 MEASURED_TRAFFIC = {
     ("scan_kernel", "deep1b"): ((5_050_370 * 2.0 + 31_683 * 1.0) * 1024, "profiles/scan_kernel_deep1b.md"),
-    ("coarse_gemm_sweep_kernel", "deep1b"): ((3_475_044 * 2.0 + 42_069_101 * 1.0) * 1024, "profiles/coarse_gemm_deep1b.md"),
 }
 
 
@@ -156,12 +156,14 @@ def measure(args, workload, nq=0, with_oracle=True, with_cpu_baseline=True, cali
     for _ in range(args.warmup):
         ivf.ivf_search(handle, Q, spec.nprobe, spec.prune_frac, spec.k, out_ids, out_d)
     torch.cuda.synchronize()
+    passes_before = ivf.ivf_search_stats()
     # the headline time: exactly `steps` passes, nothing but the library's launches in the timed region
     t1 = time.perf_counter()
     for _ in range(args.steps):
         ivf.ivf_search(handle, Q, spec.nprobe, spec.prune_frac, spec.k, out_ids, out_d)
     torch.cuda.synchronize()
     t2 = time.perf_counter()
+    with_matrix = ivf.ivf_search_stats()[1] > passes_before[1]
     # the per-stage and per-kernel times: the same `steps` passes again with HIP events recorded on the stream
     # around every stage inside the library (the events cost a few microseconds per stage, which matters only
     # for the latency workloads)
@@ -179,16 +181,29 @@ def measure(args, workload, nq=0, with_oracle=True, with_cpu_baseline=True, cali
     scan_ms = stage_ms["scan"] / max(scan_launches, 1)
     algo_bytes = (codes_scanned * (spec.M + 1) + spec.nq * S * DESC_BYTES) * args.steps / max(scan_launches, 1)
     achieved = algo_bytes / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else 0.0
-    coarse_tflops = 2.0 * spec.nq * spec.K * spec.D * args.steps / (stage_ms["coarse_gemm"] * 1e-3) / 1e12
-    # stage 1 must write the distance matrix (reused by the scoring stage) and the block minima, and read the
-    # packed centroid table (4 bytes per component, hi + lo fp16) and the queries once
-    nb = (spec.K + 63) // 64
-    gemm_ms = stage_ms["coarse_gemm"] / max(passes, 1)
-    gemm_bytes = spec.nq * args.steps / max(passes, 1) * (spec.K + nb + spec.D) * 4 + spec.K * spec.D * 4   # per launch
-    gemm_kernel = ("coarse_gemm_skinny_kernel" if spec.nq <= 64 else
-                   "coarse_gemm_sweep_kernel" if spec.K % 128 == 0 and -(-spec.D // 32) * 2 in (6, 8)
-                   and -(-spec.nq // 128) * (spec.K // 128) >= 2048 else "coarse_gemm_kernel")
-    gemm_achieved = gemm_bytes / (gemm_ms * 1e-3) / 1e9 if gemm_ms > 0 else 0.0
+    # Stage 1.  With the distance matrix (three fp16 matrix-core products for each useful one): it must write the matrix (reused by
+    # the scoring stage) and the block minima, and read the packed centroid table (4 bytes per component, hi + lo fp16) and the queries
+    # once.  Without it: one fp16 product over the whole table; the time has the listing of blocks and their exact distances in it too.
+    stage1_ms = stage_ms["coarse_gemm"] / max(passes, 1)
+    flops = 2.0 * spec.nq * args.steps / max(passes, 1) * spec.K * spec.D        # per pass
+    stage1_tflops = flops / (stage1_ms * 1e-3) / 1e12 if stage1_ms > 0 else 0.0
+    if with_matrix:
+        nb = (spec.K + 63) // 64
+        kernel = ("coarse_gemm_skinny_kernel" if spec.nq <= 64 else
+                  "coarse_gemm_sweep_kernel" if spec.K % 128 == 0 and -(-spec.D // 32) * 2 in (6, 8)
+                  and -(-spec.nq // 128) * (spec.K // 128) >= 2048 else "coarse_gemm_kernel")
+        stage1_bytes = spec.nq * args.steps / max(passes, 1) * (spec.K + nb + spec.D) * 4 + spec.K * spec.D * 4   # per launch
+        achieved1 = stage1_bytes / (stage1_ms * 1e-3) / 1e9 if stage1_ms > 0 else 0.0
+        roofline1 = {"kernel": kernel, "bound": "hbm", "achieved": achieved1, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                     "frac": achieved1 / HBM_PEAK_GBS, "launches": passes, "avg_launch_ms": stage1_ms,
+                     "algorithmic_bytes_per_launch": stage1_bytes}
+        products = "stage-1 inner products as fp16 hi/lo split operands (22 bits) accumulated in fp32 on the matrix cores, same accuracy as fp32"
+    else:
+        roofline1 = {"kernel": "coarse_minima_kernel + flag_blocks_kernel + pair_distance_kernel (blocks): the whole stage", "bound": "mfma",
+                     "achieved": stage1_tflops, "peak": FP16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": stage1_tflops / FP16_PEAK_TFLOPS,
+                     "launches": passes, "avg_launch_ms": stage1_ms, "algorithmic_flops_per_launch": flops}
+        products = ("one fp16 product with a proven bound decides which centroids are looked at; every distance and score as fp16 hi/lo split "
+                    "operands (22 bits) accumulated in fp32 on the matrix cores, same accuracy as fp32")
 
     copy_gbs = None
     if calibrate:
@@ -217,9 +232,9 @@ def measure(args, workload, nq=0, with_oracle=True, with_cpu_baseline=True, cali
                    "index_build": mode, **{k_: v for k_, v in stats.items()}},
         "codes_scanned_per_s": codes_scanned * args.steps / (stage_ms["scan"] * 1e-3) if stage_ms["scan"] > 0 else 0.0,
         "stage_ms_per_step": {k_: v / args.steps for k_, v in stage_ms.items()},
-        "coarse_gemm_tflops": coarse_tflops,     # useful 2*nq*K*D flop; each is three fp16 matrix-core products
-        "arithmetic": "fp32 results throughout; stage-1 inner products as fp16 hi/lo split operands (22 bits) "
-                      "accumulated in fp32 on the matrix cores, same accuracy as fp32",
+        "distance_matrix": with_matrix,          # whether the batches went with it
+        "coarse_gemm_tflops": stage1_tflops,     # 2*nq*K*D flop over the time of stage 1
+        "arithmetic": "fp32 results throughout; " + products,
         "roofline": {"kernel": "scan_kernel", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic("scan_kernel", spec.name)[0],
@@ -228,13 +243,7 @@ def measure(args, workload, nq=0, with_oracle=True, with_cpu_baseline=True, cali
                      # the same with 12 instead of this library's 16 bytes counted per descriptor
                      "frac_at_12B_per_descriptor": (algo_bytes - 4 * spec.nq * S * args.steps / max(scan_launches, 1))
                                                    / (scan_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if scan_ms > 0 else 0.0},
-        # the longest stage, bound by its stores; timed by events around packing + GEMM (packing: a few us)
-        "roofline_coarse_gemm": {"kernel": gemm_kernel, "bound": "hbm", "achieved": gemm_achieved,
-                                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_achieved / HBM_PEAK_GBS,
-                                 "traffic": measured_traffic(gemm_kernel, spec.name)[0],
-                                 "traffic_source": measured_traffic(gemm_kernel, spec.name)[1],
-                                 "launches": passes, "avg_launch_ms": gemm_ms,
-                                 "algorithmic_bytes_per_launch": gemm_bytes},
+        "roofline_stage1": roofline1,            # timed by events around packing and stage 1
     }
     if copy_gbs is not None:
         result["copy_kernel_gbs_read_plus_write"] = copy_gbs
