@@ -86,7 +86,11 @@ typedef struct ivf_index_desc {
  * 3.2 "Subregions pruning" prescribes), so the caller may free its arrays once
  * the call has returned; while the call runs both copies exist (there is no
  * borrowing mode: the record blocks are a different layout from the caller's
- * arrays).  Runs on `hip_stream` and waits for it.  codes / const_byte / ids /
+ * arrays).  From 16 384 regions on, for D <= 128, it also builds tables for
+ * searches without the distance tile (2 D + 4 L + 20 bytes a region, D rounded
+ * up to 32), unless there is no room for them or the centroids lie too far
+ * from the origin, compared with their spread, for the bounds that such
+ * searches rely on.  Runs on `hip_stream` and waits for it.  codes / const_byte / ids /
  * sub_offsets may not be NULL here.
  * Dynamic range: the centroid table is packed for the matrix units with ONE
  * power-of-two scale for the whole table (queries: one per row), as a high and
@@ -152,8 +156,8 @@ int ivf_set_scratch_limit(ivf_index *index, int64_t bytes);
  * call has grown the scratch).  Where the GPU has no memory for a pass without
  * the distance tile, the call and those after it take smaller passes or the
  * tile (until ivf_set_scratch_limit is called again); where it has none for
- * the tile, the handle gives up its tables for the other way (up to 0.5 KB a
- * region) for good if that makes room for it.
+ * the tile, the handle gives up its tables for the other way for good if that
+ * makes room for it.
  */
 int ivf_search(ivf_index *index, const float *queries, int64_t nq, int nprobe, float prune_frac,
                int k, int32_t *out_ids, float *out_dists, void *hip_stream);
@@ -161,7 +165,8 @@ int ivf_search(ivf_index *index, const float *queries, int64_t nq, int nprobe, f
 /*
  * ivf_search for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, same kernels and bit-identical results, but every intermediate
+ * arguments and bit-identical results, but always with the distance tile
+ * (ivf_search is faster where it goes without), and every intermediate
  * buffer (distance tile, block minima, packed queries, probes, descriptors,
  * lookup tables, partial top-k lists) is carved out of one static device array
  * of IVF_NOALLOC_SCRATCH_BYTES that each GPU holds from the moment the library
@@ -210,8 +215,8 @@ int ivf_search_budget(ivf_index *index, const float *queries, int64_t nq, int np
 
 /*
  * Passes over batches of queries that this process has launched so far (out: two values, host memory): out[0] without
- * the matrix of distances from the queries to the centroids, out[1] with it.  The results are the same bits either way; which way a
- * batch goes depends on the sizes alone.  Host call.
+ * the matrix (tile) of distances from the queries to the centroids, out[1] with it.  The results are the same bits either way; which
+ * way a batch goes depends on the sizes, the index's tables and the scratch there is room for.  Host call.
  */
 void ivf_search_stats(int64_t *out);
 
@@ -378,7 +383,8 @@ int ivf_gather_rows(const void *src, int64_t row_bytes, const int32_t *perm, int
  * Per-stage device timing of ivf_search / ivf_search_stages on a handle.  While
  * enabled, every pass over a tile of queries records HIP events on the caller's
  * stream around its six kernel groups, in launch order:
- *   0 query packing + coarse distance GEMM   1 nprobe selection   2 Eq. (7) scoring fused with
+ *   0 query packing + coarse distance GEMM (without the distance tile: block minima, the
+ *   blocks that matter and their exact distances)   1 nprobe selection   2 Eq. (7) scoring fused with
  *   the pruning select   3 lookup tables   4 ADC scan   5 final k-select
  * ivf_profile_read waits for the device, writes the summed milliseconds per
  * group to stage_ms[IVF_N_STAGES] (host) and the number of passes to *launches

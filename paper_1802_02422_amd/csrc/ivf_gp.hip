@@ -249,7 +249,7 @@ int launch_probe_select(const float *Dt, const float *bm, int64_t nq, int64_t K,
         LAUNCHCHK("probe_select_wave_kernel");
         return IVF_OK;
     }
-    if (P <= PS_P_MAX && nb <= PS_NB_MAX) {   // keys in LDS
+    if (P <= PS_P_MAX && nb <= PS_NB_MAX) {   // a workgroup per query, keys in registers
         const size_t lds2 = ps_lds_bytes(P);
         if (lds2 > 48 * 1024)
             HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&probe_select_lds_kernel),

@@ -5,6 +5,10 @@
 // the smallest of what its neighbours took.  Two regions take the same with the probability that the sets within two steps of
 // them agree, and a group is of the size of such a set (a thousand regions for 64 neighbours); inside a group the first
 // round's value puts those with a neighbour in common together.
+// It pays where neighbourhoods are shared and costs nothing elsewhere.  10 000 queries, L = 64, D = 96, a search in us in the table's order /
+// in this one: K = 262 144, P = 128, neighbours within groups of 1024 2780 / 2260; the nearest of data of 10 intrinsic dimensions 2757 / 2428, of
+// 20 2766 / 2609, of 96 2733 / 2717; anywhere 2776 / 2797; K = 65 536, P = 64 1084 / 983, 1080 / 999, 1082 / 1044, 1090 / 1089, 1092 / 1092; the
+// nearest of 2^20 means that are all equally far apart, P = 256 9606 / 9737.
 #pragma once
 #include "util.hpp"
 
