@@ -24,9 +24,9 @@
 
 namespace ivf {
 
-// The queries' fp16 rows have the centroid table's scale, four times smaller: room for components eight times the table's
-// largest; a query with a larger one is a hard one.
-constexpr int SPARSE_HEADROOM = 2;
+// The queries' fp16 rows have the centroid table's scale, 2^10 times smaller: room for components 2000 times the table's
+// largest (a query with a larger one is a hard one), and 2^18 times smaller than it before they lose bits.
+constexpr int SPARSE_HEADROOM = 10;
 constexpr int64_t SPARSE_MIN_K = 16384;   // (sparse_pays: below, no batch of less than 8192 queries takes it)
 
 // |x| and |dx| of a row (see pack_hi_rows_kernel) with infinite lengths where a centroid of the tile is not finite: such a

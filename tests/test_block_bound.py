@@ -1,7 +1,7 @@
 """The bound by which the search without the distance matrix lists blocks of 64 centroids, checked on the CPU with numpy's fp16 and fp32.
 
 The sweep leaves x = the largest of <hq, hc> - (1/2 - k) |c|^2 over a block, from fp16 rows (the table's at its scale, the queries'
-at the same, four times smaller).  As a distance in units of the product, |q|^2 - 2 G, the block's smallest one lies between two
+at the same, 2^-10 of it).  As a distance in units of the product, |q|^2 - 2 G, the block's smallest one lies between two
 ends that are widened by the rounding of the exact distances too; the P-th smallest upper end of the pieces (of every TP
 tiles) bounds the P-th smallest distance, blocks whose lower end does not exceed it are listed, and thr is the bound as a
 distance.  Where that lists more than cap blocks, bins of equal width over the upper ends of all blocks give a closer bound.  All of
@@ -12,7 +12,7 @@ import pytest
 
 from test_shortlist_bound import F, _pack, _scale
 
-HEAD = 2                                                      # the queries' rows are 2^-2 of the table's scale
+HEAD = 10                                                     # the queries' rows are 2^-10 of the table's scale
 
 
 def _ends(Q, C, lengths=1.0, start_factor=1.0):
@@ -40,11 +40,11 @@ def _ends(Q, C, lengths=1.0, start_factor=1.0):
         wide = lambda a: np.repeat(a.astype(F), 2)[None, :]   # of a tile, for its two blocks
         c, d = wide(pad(cl, 0).max(1)), wide(pad(dc, 0).max(1)) * F(lengths)
         low = back * wide(pad(np.where(good, start, 0), 0).min(1))
-        q2 = (F(4) * ql * ql)[:, None]
+        q2 = (F(2.0 ** HEAD) * ql * ql)[:, None]
         eps_q = F(2.0 ** -18) * q2 + F(2.0 ** -20) * ql[:, None]
         eps_c = k * ql[:, None] + dq[:, None] * F(lengths)
         eps_d = (ql + dq)[:, None]
-        eps = eps_c * c + (eps_d * d + (F(2.0 ** -18 / 4) * c * c + eps_q))
+        eps = eps_c * c + (eps_d * d + (F(2.0 ** (-18 - HEAD)) * c * c + eps_q))
         known = eps < np.inf
         far = np.where(known, np.maximum(F(-2) * x + (F(2) * (eps - low) + q2), 0), np.inf).astype(F)
         gap = np.where(known, F(2) * (F(2) * eps - low), np.inf).astype(F)
@@ -97,9 +97,10 @@ def _rows(kind, rng):
     Q = C[at] + 0.3 * np.linalg.norm(C - C.mean(0), axis=1).mean() / np.sqrt(D) * rng.standard_normal((60, D))
     Q[:8] = C[at[:8]]
     Q[8] = 0
-    Q[9:12] *= 6 * np.abs(C).max() / np.abs(Q[9:12]).max()    # nearly as large as fp16 rows of that scale hold
+    Q[9:12] *= 1.5 * 2 ** HEAD * np.abs(C).max() / np.abs(Q[9:12]).max()   # nearly as large as fp16 rows of that scale hold
+    Q[12:15] *= 2.0 ** -np.arange(4, 25, 8)[:, None]
     if kind == "same":
-        Q[12:20] = C[700] + 1e-3 * rng.standard_normal((8, D))
+        Q[20:28] = C[700] + 1e-3 * rng.standard_normal((8, D))
     return Q.astype(F), C.astype(F)
 
 
@@ -154,6 +155,14 @@ def test_ends_need_the_rounding_errors_of_the_rows_and_the_norms():
         assert not ((_block_min(D + room) <= far).all() and (_block_min(D - room) >= far.astype(np.float64) - gap).all()), off
     D, room, far, gap, q2, _ = _ends(Q, C)
     assert (_block_min(D + room) <= far).all() and (_block_min(D - room) >= far.astype(np.float64) - gap).all()
+
+
+def test_far_queries_have_a_bound():
+    """A hundred times as far as the table is large: the list stays short."""
+    Q, C = _rows("unit", np.random.default_rng(9))
+    D, room, far, gap, q2, _ = _ends(Q[20:] * F(100), C)
+    assert np.isfinite(far).all()
+    assert max(_list(f, g, 5, 1, 16)[0].sum() for f, g in zip(far, gap)) <= 16
 
 
 def test_centroids_that_are_not_finite_are_always_looked_at():
