@@ -71,7 +71,7 @@ inline unsigned lut_grid(int64_t n, int per) { return (unsigned)(n + (n + per - 
 // Stage 2 (Eq. (7)): score[p][l] = (1-a) D[q][r] + a D[q][nbr[r][l]] + cst[r][l], r = probe_id[q][p],
 // cst[r][l] = -a(1-a)||c_r - s_l||^2 tabulated at load time.  The neighbour distances are gathered from
 // the stage-1 distance tile, not recomputed; every thread has PL/BLOCK independent gathers in flight.
-// The scores never leave the chip: they are kept in LDS as order-preserving keys.
+// The scores formed here never leave the chip: they are kept in LDS as order-preserving keys.
 // Stage 3: keep the S smallest of the P*L scores by (score, r*L + l).  probe_id is ascending in r, so
 // position order in the score row is subregion-id order and the descriptors come out sorted by address.
 // The selection leaves the kept score indices, in order, in LDS (over the keys, which every thread

@@ -49,11 +49,13 @@ def same(got, ref):
 
 
 # partial last tiles and blocks, every packed width, L below, at and above a group of 64 neighbours and of odd length; "hard": queries
-# too large for the table's scale, all without a bound; "far": far from the table; "some": queries too large for the table's scale, far, without a finite length, zero, and equal to centroids;
+# too large for the table's scale, all without a bound; "far": far from the table; "tiny": the queries' fp16 components are subnormal;
+# "some": queries too large for the table's scale, far, without a finite length, zero, and equal to centroids;
 # "copies": more centroids at the same distance than the selection holds in LDS; "holes": centroids that are not finite
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
     (16_400, 96, 64, 16, 16, 9000, "plain"), (16_385, 32, 7, 8, 13, 8500, "plain"), (20_033, 64, 65, 16, 16, 7001, "plain"), (16_500, 32, 128, 8, 12, 8200, "plain"),
     (17_000, 128, 33, 16, 8, 9000, "plain"), (70_001, 48, 64, 8, 60, 4200, "plain"), (16_400, 96, 32, 16, 16, 8300, "hard"), (16_400, 96, 32, 16, 16, 8300, "far"),
+    (16_400, 96, 32, 16, 16, 8300, "tiny"),
     (16_640, 96, 16, 16, 16, 8300, "some"), (16_400, 96, 16, 16, 16, 8300, "equal"), (66_000, 32, 16, 8, 64, 4200, "copies"),
     (16_600, 96, 16, 16, 16, 8300, "holes")])
 def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
@@ -64,6 +66,8 @@ def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     if kind == "copies":
         q[::3] = cent[1000]
     q = (q + 0.5 * torch.randn(nq, D, generator=g, device="cuda") + {"hard": 1e5, "far": 50.0}.get(kind, 0.0)).contiguous()
+    if kind == "tiny":
+        q *= 2.0 ** -19
     if kind == "some":
         q[::7] *= 1e5
         q[1::7] *= 300.0
@@ -90,18 +94,20 @@ def test_same_bits_as_with_the_distance_matrix(K, D, L, M, P, nq, kind):
     ivf.ivf_free_index(h)
 
 
-# batches whose pairs are not grouped: one query, odd numbers, the largest; no bound for every query or for some, far queries.  Tables of more than
+# batches whose pairs are not grouped: one query, odd numbers, the largest; no bound for every query or for some, far queries, tiny ones.  Tables of more than
 # 4096 blocks, whose queries without a bound take another kernel: such a batch, and one whose pairs are grouped
 @pytest.mark.parametrize("K,D,L,M,P,nq,kind", [
     (300_000, 32, 8, 8, 16, 100, "plain"), (262_144, 96, 64, 16, 64, 1, "plain"), (270_001, 64, 33, 16, 20, 33, "plain"),
     (262_144, 128, 65, 8, 16, 129, "plain"), (262_144, 96, 16, 16, 16, 70, "hard"), (262_144, 96, 16, 16, 16, 256, "some"),
-    (300_000, 32, 8, 8, 16, 40, "hard"), (300_000, 32, 8, 8, 16, 40, "far"), (300_001, 32, 8, 8, 16, 700, "some")])
+    (300_000, 32, 8, 8, 16, 40, "hard"), (300_000, 32, 8, 8, 16, 40, "far"), (262_144, 96, 16, 16, 16, 70, "tiny"), (300_001, 32, 8, 8, 16, 700, "some")])
 def test_small_batches_same_bits(K, D, L, M, P, nq, kind):
     import torch
     import paper_1802_02422_amd as ivf
     h, cent, g = make(K, D, L, M, K + D, 1.0, 0.0)
     q = cent[torch.randint(0, K, (nq,), generator=g, device="cuda")]
     q = (q + 0.5 * torch.randn(nq, D, generator=g, device="cuda") + {"hard": 1e5, "far": 50.0}.get(kind, 0.0)).contiguous()
+    if kind == "tiny":
+        q *= 2.0 ** -19
     if kind == "some":
         q[::7] *= 1e5
         q[1::7] *= 300.0
