@@ -3,7 +3,7 @@
 //
 // The nearest codeword is decided on the matrix units, with a proof per decision.  <x, c> - |c|^2 / 2 is formed for
 // all 256 codewords as fp16 products of operands split into a high and a low half (22 bits, accumulated in fp32); a
-// point whose best value leads the second best by more than twice the error bound has its answer, the others (about
+// point whose best value leads the others by more than twice the error bound has its answer, the others (about
 // one in a thousand) are decided by the whole wavefront with the chain of fused multiply-adds over the differences
 // that defines the result.  The codes are therefore those of that chain, the lowest index on ties.  A codeword equal to
 // one before it (a codebook that starts from rows may hold hundreds) can never be the answer and is left out, or every point
@@ -21,11 +21,18 @@ struct PqRow {
     static constexpr int CH = (DS + 7) / 8;
     static constexpr int LAST = DS - 8 * (CH - 1);        // components in the last piece
     static constexpr bool ROOM = LAST <= 6;
-    static constexpr int GROUP = DS == 4 ? 4 : DS <= 8 ? 2 : 1;   // quantisers whose components are loaded together
+    static constexpr int GROUP = DS == 4 ? 4 : DS == 6 ? 2 : 1;   // quantisers whose components are loaded together
     static constexpr int bytes = 256 * (32 * CH + (ROOM ? 0 : 4));   // of a quantiser in LDS
 };
 
 constexpr int PQ_LDS_MAX = 150 * 1024;
+
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any float's address
+typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
+
+// (two of them in a row are one instruction; of a number and what is no number, the latter)
+__device__ __forceinline__ float larger(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
 // quantisers of one workgroup (their codewords stay in LDS): all of them, or a multiple of 4
 inline int pq_per_group(int M, int quantiser_bytes)
@@ -41,10 +48,16 @@ inline int pq_per_group(int M, int quantiser_bytes)
 // A wavefront takes 64 points as two blocks of 32: v_mfma_f32_32x32x16_f16 with 32 codewords as the rows and 32 points
 // as the columns.  Lane half 0 feeds the high halves of its point's 8 components and half 1 the low halves, against
 // the codeword's high halves in both lane halves, then against its low halves: two products a piece of 8
-// components, and the points' operands are built once for all 256 codewords.  What is left on the vector units
-// is three instructions a value (value index into the low 4 bits, second largest, largest), which is what bounds the
-// kernel: 192 cycles a tile of 32 x 32 against 64 of the matrix units.  10^6 points x 96 components, 16 quantisers:
-// 0.58 ms (1.48 ms with a thread a point that walks all codewords in LDS, 15 instructions a codeword and quantiser).
+// components, and the points' operands are built once for all 256 codewords, each lane those of its own point (a swap of lane
+// halves brings them where they belong).  The vector units look for the four codewords in a row (a lane's quarter of 16) with
+// the largest value and for the second largest of such fours: five instructions a four, where the largest and the second largest
+// value with their numbers took three a value.  Which of the four it is is decided by dot products of the same halves, from
+// LDS, a point a lane, and within the same bound.  10^6 points x 96 components, 16 quantisers: 0.375 ms, 0.575 with three
+// instructions a value and every point packed by two lanes from words loaded one by one (1.48 ms with a thread a point
+// that walks all codewords in LDS).  Bound by the vector and matrix instructions, which overlap only in part here: 40 of the former
+// and 4 of the latter take 97 ns on a SIMD with four wavefronts, 72 and 62 alone; a tile takes 119.  Eights instead of fours (13
+// instructions a block and tile instead of 20, twice the dot products) 0.385 ms; the codewords of a tile read ahead 0.38; two
+// tiles at a time 0.41.
 template <int DS>
 __global__ __launch_bounds__(1024) void pq_encode_kernel(
     const float *__restrict__ E, const float *__restrict__ MU, int64_t n, int M, int Mg,
@@ -56,7 +69,8 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
     extern __shared__ __attribute__((aligned(16))) unsigned char pq_lds[];
     __shared__ float tab[256];
     __shared__ float cmax_s[64];                           // largest |c'|^2 of a quantiser (scaled), NaN: decide by the chain
-    __shared__ int kexp_s[64];                              // exponent of its largest component
+    __shared__ float scale_s[64];                           // power of two that takes its largest component to below 1
+    __shared__ float xmax_s[64];                            // |x'|^2 from which on the chain may overflow
     __shared__ uint32_t copy_s[64][8];                      // its codewords that are equal to one before them, a word a tile
     __shared__ uint32_t copies_s[64];                       // whether there are any
     __shared__ int tab_sorted;
@@ -87,7 +101,7 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
             }
 #pragma unroll
         for (int o = WAVE / 2; o > 0; o >>= 1) big = fmaxf(big, __shfl_xor(big, o, WAVE));
-        const int ec = __builtin_amdgcn_frexp_expf(big);    // components scaled to below 2^6
+        const int ec = __builtin_amdgcn_frexp_expf(big);    // components scaled to below 1
         // The first codeword of every hash value, in the place of the rows that are packed below, and whether the others
         // with that value are equal to it (one that is equal to a codeword which is not the first stays in: no harm).
         uint32_t *first = reinterpret_cast<uint32_t *>(rows + (size_t)m * CH * 512), hash[4];
@@ -129,19 +143,18 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
             _Float16 hi[CH * 8], lo[CH * 8];
 #pragma unroll
             for (int t = 0; t < CH * 8; ++t) {
-                const float v = t < DS ? __builtin_amdgcn_ldexpf(cw[k][t < DS ? t : 0], 6 - ec) : 0.f;
+                const float v = t < DS ? __builtin_amdgcn_ldexpf(cw[k][t < DS ? t : 0], -ec) : 0.f;
                 n2 = fmaf(v, v, n2);
                 hi[t] = (_Float16)v;
                 lo[t] = (_Float16)(v - (float)hi[t]);
             }
             cm = fmaxf(cm, n2);
-            const float nh = -0.5f * n2;                     // |c'|^2 / 2 <= 16 * 2^12 / 2: inside fp16's range
+            const float nh = -0.5f * n2;                     // (|c'|^2 / 2 <= 8)
             const _Float16 nhi = (_Float16)nh, nlo = (_Float16)(nh - (float)nhi);
             if (R::ROOM) {
                 hi[CH * 8 - 2] = nhi;
                 hi[CH * 8 - 1] = nlo;
             } else {
-                typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
                 const halfx2 p = {nhi, nlo};
                 norms[m * 256 + j] = __builtin_bit_cast(uint32_t, p);
             }
@@ -159,83 +172,91 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
         if (__any(odd) || ec < -40 || ec > 55) cm = NAN;     // the chain's own under- and overflows decide there
         if (lane == 0) {
             cmax_s[m] = cm;
-            kexp_s[m] = ec;
+            scale_s[m] = __builtin_amdgcn_ldexpf(1.f, ec < -40 ? 40 : ec > 55 ? -55 : -ec);
+            xmax_s[m] = __builtin_amdgcn_ldexpf(1.f, 2 * (55 - ec));
         }
     }
     __syncthreads();
+    uint32_t keep = ~31u, keep4 = ~3u;                       // (in registers, so that masking and index are one instruction)
+    asm volatile("" : "+v"(keep), "+v"(keep4));
     const bool sorted = tab_sorted != 0;
     const bool words = (M & 3) == 0 && (Mg & 3) == 0 && (reinterpret_cast<uintptr_t>(out_codes) & 3) == 0;
 
     // a wavefront's batches of 64 points, dealt so that few points spread over the workgroups
     for (int64_t b0 = ((int64_t)wave * gridDim.x + blockIdx.x) * WAVE; b0 < n; b0 += (int64_t)16 * gridDim.x * WAVE) {
-        const int64_t own = b0 + lane;                       // the point this lane writes
-        const int64_t i0 = b0 + l32 < n ? b0 + l32 : n - 1, i1 = b0 + 32 + l32 < n ? b0 + 32 + l32 : n - 1;
+        const int64_t own = b0 + lane, i0 = own < n ? own : n - 1;   // this lane's point: column l32 of block h
         float tval = 0.f;
         uint32_t word = 0;
-        for (int mg = 0; mg < mn; mg += G) {
-            float x[2][G * DS];                               // both blocks' points (the last group may reach back)
-            const int ml = mg + G <= mn ? mg : (mn - G > 0 ? mn - G : 0);
+        // a group's components are requested while the one before is worked on
+        float x[G * DS], xn[G * DS];
+        auto place = [&](int mg) { return mg + G <= mn ? mg : mn - G; };   // (the last group may reach back)
+        auto fetch = [&](int ml) {
+            const float *src = E + i0 * D + (int64_t)(m0 + ml) * DS;
+            if (m0 + ml >= 0) {                               // (uniform)
 #pragma unroll
-            for (int t = 0; t < G * DS; ++t) {
-                const int64_t at = (m0 + ml) * DS + t < D ? (m0 + ml) * DS + t : D - 1;
-                x[0][t] = E[i0 * D + at];
-                x[1][t] = E[i1 * D + at];
+                for (int t = 0; t + 4 <= G * DS; t += 4) {
+                    const float4u w = *reinterpret_cast<const float4u *>(src + t);
+                    xn[t] = w.x; xn[t + 1] = w.y; xn[t + 2] = w.z; xn[t + 3] = w.w;
+                }
+            } else {                                          // fewer than G quantisers
+#pragma unroll
+                for (int t = 0; t < G * DS; ++t) xn[t] = (m0 + ml) * DS + t >= 0 ? src[t] : 0.f;
             }
+        };
+        static_assert(G * DS % 4 == 0, "whole loads");
+        fetch(place(0));
+        for (int mg = 0; mg < mn; mg += G) {
+            const int ml = place(mg);
+#pragma unroll
+            for (int t = 0; t < G * DS; ++t) x[t] = xn[t];
+            if (mg + G < mn) fetch(place(mg + G));
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const int m = ml + g;
                 if (m < mg || m >= mn) continue;             // (uniform)
-                const float cm = cmax_s[m];
-                const int ec = kexp_s[m];
+                const float *xv = &x[g * DS];
+                const float cm = cmax_s[m], scale = scale_s[m];
                 const bool copies = __builtin_amdgcn_readfirstlane((int)copies_s[m]) != 0;
-                halfx8 B[2][CH], Bn[2];
-                float band[2];
-                bool chain[2];
+                // at the codewords' scale: a component that fp16 does not hold there, 2^16 times the largest of theirs, makes every
+                // value no number
+                float x2 = 0.f;
+                union { halfx8 all[CH]; uint32_t word[4 * CH]; } high, low, B[2];
+                union { halfx8 all; uint32_t word[4]; } last[2];
+                const halfx2 one = {(_Float16)1.f, (_Float16)1.f};
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const float *xv = &x[b][g * DS];
-                    float big = 0.f;
-#pragma unroll
-                    for (int t = 0; t < DS; ++t) big = fmaxf(big, fabsf(xv[t]));
-                    // scaled like the codewords by powers of two: components below 2^6 where the ratio of the two
-                    // scales, 2^dk, is one that fp16 holds beside the norms
-                    const int e = __builtin_amdgcn_frexp_expf(big);
-                    int dk = ec - e;
-                    chain[b] = dk < -20 || e > 55;            // (the halves would overflow, or the chain does)
-                    dk = dk < -14 ? -14 : dk > 8 ? 8 : dk;
-                    const int sh = 6 - ec + dk;
-                    float x2 = 0.f;
-                    _Float16 w[CH * 8];
-#pragma unroll
-                    for (int t = 0; t < CH * 8; ++t) {
-                        w[t] = (_Float16)0.f;
-                        if (t < DS) {
-                            const float v = __builtin_amdgcn_ldexpf(xv[t], sh);
-                            x2 = fmaf(v, v, x2);
-                            const _Float16 hi = (_Float16)v;
-                            w[t] = h ? (_Float16)(v - (float)hi) : hi;
-                        }
-                    }
-                    const _Float16 r = (_Float16)__builtin_amdgcn_ldexpf(1.f, dk);
-                    if (R::ROOM) {
-                        if (h == 0) w[CH * 8 - 2] = w[CH * 8 - 1] = r;
-                    }
-#pragma unroll
-                    for (int q = 0; q < CH; ++q)
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) B[b][q][t] = w[8 * q + t];
-                    if (!R::ROOM) {   // last product: half 0 high halves against low ones, half 1 the norm
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) Bn[b][t] = h ? (t < 2 ? r : (_Float16)0.f) : w[8 * (CH - 1) + t];
-                    }
-                    // Bound, in units of the products: halves of 22 bits on either side 2^-22 (X + C), the norm 2^-21 C,
-                    // fp32 accumulation 2^-21 (X + C), the chain's own roundings 18 * 2^-24 (X + C), the 4 bits an index
-                    // replaces 2^-19 (X + C): together below 2^-17 (X + C), X = |x|^2, C = the largest |c|^2; a leads b
-                    // truly if it leads by twice that here
-                    band[b] = 0x1p-16f * (__builtin_amdgcn_ldexpf(x2, -dk) + __builtin_amdgcn_ldexpf(cm, dk));
+                for (int i = 0; i < 4 * CH; ++i) {
+                    high.word[i] = low.word[i] = 0;
+                    if (2 * i >= DS) continue;
+                    const float u = xv[2 * i] * scale, v = xv[2 * i + 1] * scale;
+                    x2 = fmaf(v, v, fmaf(u, u, x2));
+                    const halfx2 hi = {(_Float16)u, (_Float16)v};
+                    high.word[i] = __builtin_bit_cast(uint32_t, hi);
+                    float du, dv;                             // u - hi[0], v - hi[1]
+                    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(du) : "v"(high.word[i]), "v"(u));
+                    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(dv) : "v"(high.word[i]), "v"(v));
+                    const halfx2 lo = {(_Float16)du, (_Float16)dv};
+                    low.word[i] = __builtin_bit_cast(uint32_t, lo);
                 }
+                if (R::ROOM) high.word[4 * CH - 1] = __builtin_bit_cast(uint32_t, one);
+                auto swap = [](uint32_t a, uint32_t b, uint32_t &lo, uint32_t &hi) {
+                    const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+                    lo = s[0];
+                    hi = s[1];
+                };
+#pragma unroll
+                for (int i = 0; i < 4 * CH; ++i) swap(high.word[i], low.word[i], B[0].word[i], B[1].word[i]);
+                if (!R::ROOM) {   // last product: half 0 high halves against low ones, half 1 the norm
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        swap(high.word[4 * CH - 4 + i], i == 0 ? __builtin_bit_cast(uint32_t, one) : 0u, last[0].word[i], last[1].word[i]);
+                }
+                // Bound, in units of the products: halves of 22 bits on either side 2^-22 (X + C), what fp16 leaves of their ends
+                // 1.5 * 2^-22 (X + C) (C is at least 1/4), the norm 2^-21 C, fp32 accumulation 2^-21 (X + C) on the matrix
+                // units and 2^-19 (X + C) of the dot products below, the chain's own roundings 18 * 2^-24 (X + C), the 5 bits an index
+                // replaces 2^-18 (X + C), 2 bits in a four: together below 2^-17 (X + C) either way, X = |x|^2, C = the largest
+                // |c|^2; a leads b truly if it leads by twice that here
+                const float band = 0x1p-16f * (x2 + cm);
                 float v1[2] = {-INFINITY, -INFINITY}, v2[2] = {-INFINITY, -INFINITY};
-                int at[2] = {0, 0};
                 const gu32x4 *mrow = rows + (size_t)m * CH * 512;
 #pragma unroll 1
                 for (int tile = 0; tile < 8; ++tile) {
@@ -261,7 +282,7 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
 #pragma unroll
                             for (int b = 0; b < 2; ++b)
                                 acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                                    __builtin_bit_cast(halfx8, a[q][p]), (!R::ROOM && q == CH - 1 && p == 1) ? Bn[b] : B[b][q], acc[b], 0, 0, 0);
+                                    __builtin_bit_cast(halfx8, a[q][p]), (!R::ROOM && q == CH - 1 && p == 1) ? last[b].all : B[b].all[q], acc[b], 0, 0, 0);
                     if (copies) {                            // (uniform; far below every value that a codeword can have)
                         const uint32_t out = copy_s[m][tile] >> (4 * h);
 #pragma unroll
@@ -270,62 +291,105 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
                     }
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
-                        const float before = v1[b];
+                        float s[4];                          // largest of four codewords in a row, its number in the low bits
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const float s = __uint_as_float((__float_as_uint(acc[b][v]) & ~15u) | (uint32_t)v);
-                            v2[b] = __builtin_amdgcn_fmed3f(v1[b], v2[b], s);
-                            // the larger (an instruction of its own: fmaxf first quiets both operands, two more)
-                            asm("v_max_f32 %0, %1, %2" : "=v"(v1[b]) : "v"(v1[b]), "v"(s));
+                        for (int k = 0; k < 4; ++k) {
+                            const float w = larger(larger(larger(acc[b][4 * k], acc[b][4 * k + 1]), acc[b][4 * k + 2]), acc[b][4 * k + 3]);
+                            s[k] = __uint_as_float((__float_as_uint(w) & keep) | (uint32_t)(4 * tile + k));
                         }
-                        at[b] = v1[b] != before ? tile : at[b];
+                        // largest and second largest of them all, two at a time
+                        const float t1 = __builtin_amdgcn_fmed3f(v1[b], s[0], s[1]);
+                        v1[b] = larger(larger(v1[b], s[0]), s[1]);
+                        const float t2 = __builtin_amdgcn_fmed3f(v1[b], s[2], s[3]);
+                        v1[b] = larger(larger(v1[b], s[2]), s[3]);
+                        v2[b] = larger(larger(v2[b], t1), t2);
                     }
                 }
                 // the halves of the lanes hold the even and odd groups of four codewords: lane p < 32 takes point p
                 // of block 0, lane 32 + p point p of block 1
-                auto swap = [](uint32_t a, uint32_t b, uint32_t &lo, uint32_t &hi) {
-                    const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-                    lo = s[0];
-                    hi = s[1];
-                };
-                uint32_t u1, w1, u2, w2, ut, wt;
+                uint32_t u1, w1, u2, w2;
                 swap(__float_as_uint(v1[0]), __float_as_uint(v1[1]), u1, w1);
                 swap(__float_as_uint(v2[0]), __float_as_uint(v2[1]), u2, w2);
-                swap((uint32_t)at[0], (uint32_t)at[1], ut, wt);
                 const float a1 = __uint_as_float(u1), b1 = __uint_as_float(w1);
                 const bool upper = b1 > a1;
                 const float best = upper ? b1 : a1;
-                const float next = fmaxf(fminf(a1, b1), fmaxf(__uint_as_float(u2), __uint_as_float(w2)));
-                const uint32_t v = (upper ? w1 : u1) & 15u;
-                int code = (int)((upper ? wt : ut) * 32u + 8u * (v >> 2) + (upper ? 4u : 0u) + (v & 3u));
-                const bool sure = best - next > (h ? band[1] : band[0]) && !(h ? chain[1] : chain[0]) && best < INFINITY;
-                uint64_t open = __ballot(!sure && own < n);
-                if (open) {
-                    float xo[DS];
+                const float next = larger(fminf(a1, b1), larger(__uint_as_float(u2), __uint_as_float(w2)));
+                const uint32_t four = (upper ? w1 : u1) & 31u;
+                const int j0 = (int)(8u * four + (upper ? 4u : 0u));   // first codeword of the four
+                // Which of the four: their values again, by dot products (the lanes start with another one each, or their reads would
+                // all go to a quarter of the banks)
+                float f[4];
 #pragma unroll
-                    for (int t = 0; t < DS; ++t) xo[t] = h ? x[1][g * DS + t] : x[0][g * DS + t];
-                    while (open) {
-                        const int s = __builtin_ctzll(open);
-                        open &= open - 1;
-                        float xs[DS];
+                for (int k = 0; k < 4; ++k) {
+                    f[k] = 0.f;
+                    if (!R::ROOM) f[k] = __builtin_amdgcn_fdot2(one, __builtin_bit_cast(halfx2, norms[m * 256 + j0 + ((lane + k) & 3)]), f[k], false);
+                }
 #pragma unroll
-                        for (int t = 0; t < DS; ++t) xs[t] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(xo[t]), s));
-                        float bd = INFINITY;
-                        int bj = 0x7fffffff;
-#pragma nounroll
-                        for (int j = lane; j < 256; j += WAVE) {
-                            const float *cw = codebook + ((int64_t)(m0 + m) * 256 + j) * DS;
-                            float dd = 0.f;
+                for (int q = 0; q < CH; ++q) {
+                    gu32x4 ch[4], cl[4];                      // (all on their way together)
 #pragma unroll
-                            for (int t = 0; t < DS; ++t) {
-                                const float u = xs[t] - cw[t];
-                                dd = fmaf(u, u, dd);
-                            }
-                            if (dd < bd) { bd = dd; bj = j; }
-                        }
-                        wave_argmin(bd, bj);
-                        if (lane == s) code = bj == 0x7fffffff ? 0 : bj;
+                    for (int k = 0; k < 4; ++k) {
+                        ch[k] = mrow[(q * 2 + 0) * 256 + j0 + ((lane + k) & 3)];
+                        cl[k] = mrow[(q * 2 + 1) * 256 + j0 + ((lane + k) & 3)];
                     }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const halfx2 xh = __builtin_bit_cast(halfx2, high.word[4 * q + i]), xl = __builtin_bit_cast(halfx2, low.word[4 * q + i]);
+                        const bool used = q < CH - 1 || 2 * i < R::LAST;   // (behind the components: zeros, or the norm's slots in `high`)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (used) f[k] = __builtin_amdgcn_fdot2(xh, __builtin_bit_cast(halfx2, (uint32_t)cl[k][i]), f[k], false);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (used) f[k] = __builtin_amdgcn_fdot2(xl, __builtin_bit_cast(halfx2, (uint32_t)ch[k][i]), f[k], false);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (used || (R::ROOM && i == 3)) f[k] = __builtin_amdgcn_fdot2(xh, __builtin_bit_cast(halfx2, (uint32_t)ch[k][i]), f[k], false);
+                    }
+                    if (q + 1 < CH) __builtin_amdgcn_sched_barrier(0);   // (room for one piece's words)
+                }
+                if (copies) {
+                    const uint32_t out = copy_s[m][four >> 2] >> (j0 & 31);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (out >> ((lane + k) & 3) & 1u) f[k] = -0x1p127f;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) f[k] = __uint_as_float((__float_as_uint(f[k]) & keep4) | (uint32_t)((lane + k) & 3));
+                const float f01 = larger(f[0], f[1]), first = larger(larger(f01, f[2]), f[3]);
+                const float second = larger(fminf(f[0], f[1]), __builtin_amdgcn_fmed3f(f01, f[2], f[3]));
+                int code = j0 + (int)(__float_as_uint(first) & 3u);
+                const bool sure = best - next > band && first - second > band && best < INFINITY && x2 < xmax_s[m];
+                uint64_t open = __ballot(!sure && own < n);
+                while (open) {
+                    const int s = __builtin_ctzll(open);
+                    open &= open - 1;
+                    float xs[DS];
+#pragma unroll
+                    for (int t = 0; t < DS; ++t) xs[t] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(xv[t]), s));
+                    float bd = INFINITY;
+                    uint32_t bj = 0xFFFFFFFFu;
+                    float cw[4][DS];                          // (all on their way together)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+#pragma unroll
+                        for (int t = 0; t < DS; t += 2) {
+                            const float2u w = *reinterpret_cast<const float2u *>(codebook + ((int64_t)(m0 + m) * 256 + lane + k * WAVE) * DS + t);
+                            cw[k][t] = w.x; cw[k][t + 1] = w.y;
+                        }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        float dd = 0.f;
+#pragma unroll
+                        for (int t = 0; t < DS; ++t) {
+                            const float u = xs[t] - cw[k][t];
+                            dd = fmaf(u, u, dd);
+                        }
+                        if (dd < bd) { bd = dd; bj = (uint32_t)(lane + k * WAVE); }
+                    }
+                    const float least = wave_smallest(bd);
+                    bj = wave_extreme<false>(bd == least ? bj : 0xFFFFFFFFu);
+                    if (lane == s) code = bj == 0xFFFFFFFFu ? 0 : (int)bj;
                 }
                 if (words) {                                  // four codes at a time
                     word |= (uint32_t)code << (8 * (m & 3));
@@ -338,11 +402,15 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
                 }
                 if (MU && own < n) {
                     const float *cw = codebook + ((int64_t)(m0 + m) * 256 + code) * DS, *mu = MU + own * D + (m0 + m) * DS;
+                    float r2[DS], u2[DS];
 #pragma unroll
-                    for (int t = 0; t < DS; ++t) {
-                        const float rv = cw[t];
-                        tval = fmaf(2.f * mu[t], rv, fmaf(rv, rv, tval));
+                    for (int t = 0; t + 2 <= DS; t += 2) {
+                        const float2u a = *reinterpret_cast<const float2u *>(cw + t), b = *reinterpret_cast<const float2u *>(mu + t);
+                        r2[t] = a.x; r2[t + 1] = a.y;
+                        u2[t] = b.x; u2[t + 1] = b.y;
                     }
+#pragma unroll
+                    for (int t = 0; t < DS; ++t) tval = fmaf(2.f * u2[t], r2[t], fmaf(r2[t], r2[t], tval));
                 }
             }
         }

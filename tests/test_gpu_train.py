@@ -268,6 +268,26 @@ def test_codeword_means_of_one_round(M, ds, n, small):
         assert (np.abs(got[m] - s / c) <= (2.0 ** -24 + 2.0 ** -28) * np.abs(s / c) + 2 * n * 2.0 ** -53 * a / c).all()
 
 
+@pytest.mark.parametrize("M,ds", [(1, 4), (3, 4), (5, 4), (9, 4), (1, 6), (3, 6), (2, 8), (1, 12), (3, 16)])
+def test_one_round_of_few_quantisers_with_equal_codewords(M, ds):
+    """Fewer quantisers than are loaded together, numbers that leave some over, rows at an address of four bytes, codewords that
+    start equal (the lowest index has all points, the others keep their value): whole numbers, every distance exact."""
+    print("case: few quantisers", M, ds, flush=True)
+    rng = np.random.default_rng(M * 100 + ds)
+    n, D = 3000, M * ds
+    E = rng.integers(-3, 4, (n, D)).astype(np.float32)
+    E[1:256:3] = E[0:255:3]                                   # every third codeword equal to the one before it
+    flat = dev(np.concatenate([np.zeros(1, np.float32), E.ravel()]))
+    got = ivf.ivf_pq_train(flat[1:].view(n, D), M, 1, dev(np.arange(256, dtype=np.int64))).cpu().numpy()
+    for m in range(M):
+        x = E[:, m * ds:(m + 1) * ds].astype(np.float64)
+        code = ((x[:, None] - x[None, :256]) ** 2).sum(-1).argmin(1)
+        s, c = np.zeros((256, ds)), np.bincount(code, minlength=256)[:, None]
+        np.add.at(s, code, x)
+        want = np.where(c > 0, s / np.maximum(c, 1), x[:256])
+        assert (np.abs(got[m] - want) <= 2.0 ** -24 * np.abs(want)).all()   # exact sums, one rounding
+
+
 @pytest.mark.parametrize("D,L,n,order", [(32, 64, 1000, "sorted"), (64, 5, 1601, "mixed"), (96, 63, 1000, "sorted"), (104, 64, 999, "mixed"),
                                          (128, 17, 65, "sorted"), (96, 1, 4000, "mixed"), (96, 64, 3, "mixed")])
 @pytest.mark.parametrize("kind", ["plain", "tight", "flat"])
