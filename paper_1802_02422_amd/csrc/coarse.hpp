@@ -1068,30 +1068,123 @@ struct TileTwists {
     __device__ __forceinline__ uint32_t of(int n) const { return SH == 3 ? word >> (2 * (n >> 2)) & 3u : word; }
 };
 
-// The same pass for SH = 1 .. 4 stages of 32 dimensions (packed dimension up to 128): a workgroup keeps the fragments of
-// ONE query tile in registers and sweeps `tiles_per_wg` consecutive centroid tiles through two LDS buffers of a whole
-// tile each, one workgroup barrier per tile (the copies of tile t + 1 are issued right behind the barrier of tile t
-// and waited for at the barrier of tile t + 1).  (Six wavefronts and 192 queries a workgroup save a third of the copies
-// and lose more at the barrier: 2.1 against 1.8 ms for 500 000 x 16 384 without the reports.)  The bound stays in registers over the sweep and reaches L[q] once.
+// ---- sweeps: a workgroup of four wavefronts keeps the fragments of its rows (queries, points) in registers, 64 a wavefront, and goes
+// through tiles of 128 centroids in two LDS buffers, one barrier a tile: the copies of tile t + 1 are issued right behind the
+// barrier of tile t and waited for at the barrier of tile t + 1.  The buffers are objects of their own, so that the compiler knows
+// that reads of one do not have to wait for copies into the other (only direct-to-LDS copies write them).
+// Rows a workgroup takes: 64 for each of its wavefronts where there are products enough to fill the chip that way (three workgroups
+// a compute unit), or 64 for two of them, which leaves more workgroups and shorter steps.  By rows x centroids, us
+// with two wavefronts to 64 rows / with one: 600 x 65 536 39 / 43, 2000 x 65 536 56 / 47, 5000 x 65 536 88 / 89, 20 000 x 2000 23 / 27,
+// 20 000 x 16 384 90 / 79, 100 000 x 1000 46 / 49, 100 000 x 16 384 407 / 340.
+inline bool sweep_wide(int64_t rows, int64_t K) { return rows > 2 * GT && (rows + GT - 1) / GT * ((K + GT - 1) / GT) >= 8192; }
+
+template <int SH>
+struct SweepTile {
+    float rows[SH * GT * ROWF];
+    float start[GT];                                       // start values of the products' accumulators
+};
+
+// Tile `tile` of the table into buf: 8 SH pieces of 1 KB, dealt to the wavefronts (tile_twist), and from two of them 64 of the start values each
+template <int SH>
+__device__ __forceinline__ void sweep_copy(const _Float16 *Ch, const float *start, int64_t tile, SweepTile<SH> &buf, const TileTwists<SH> &twists, int wave, int lane)
+{
+    typedef const __attribute__((address_space(1))) void *gptr_t;
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    if (wave < 2) __builtin_amdgcn_global_load_lds((gptr_t)(start + tile * GT + wave * 64 + lane), (lptr_t)(buf.start + wave * 64), 4, 0, 0);
+    const float *src = reinterpret_cast<const float *>(Ch) + tile * (GT * SH * DK);
+    // (one instruction in a rolled loop: the compiler tracks only a handful of distinct LDS copies exactly)
+#pragma nounroll
+    for (int n = wave; n < 8 * SH; n += 4)
+        __builtin_amdgcn_global_load_lds((gptr_t)(src + n * 256 + 4 * (lane ^ (int)twists.of(n))), (lptr_t)(buf.rows + n * 256), 16, 0, 0);
+}
+
+// This wavefront's copies are in, then everyone's, and everyone is through with the other buffer.
+__device__ __forceinline__ void sweep_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int SH>
+__device__ __forceinline__ void sweep_rows(gu32x4 (&afr)[SH][2][2], const _Float16 *rows, int64_t first, int l32, int h)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(rows) + (first + i * 32 + l32) * (SH * DK)) + 2 * h;
+#pragma unroll
+        for (int s = 0; s < SH; ++s) {
+            afr[s][i][0] = row[s * 4 + 0];
+            afr[s][i][1] = row[s * 4 + 1];
+        }
+    }
+}
+
+// The products of a wavefront's 64 rows with JN blocks of 32 centroids from row wc of the tile on; each(j, acc) looks at a
+// block's: acc[i][v] is that of row 32 i + lane % 32 and centroid wc + 32 j + 8 (v / 4) + 4 (lane / 32) + v % 4.  A block's first fragments
+// are on their way while the one before is looked at, the others under the first products.
+template <int SH, int JN, class Each>
+__device__ __forceinline__ void sweep_tile(const SweepTile<SH> &buf, const gu32x4 (&afr)[SH][2][2], int wc, int l32, int h, Each each)
+{
+    union Start { floatx16 all; floatx4 part[4]; };
+    gu32x4 b[SH][2];
+    Start start;
+    const uint32_t tw = tile_twist<SH>(l32);               // (the same for all blocks of 32)
+    auto load_start = [&](int j) {
+        const float *c = buf.start + wc + j * 32 + 4 * h;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) start.part[k] = *reinterpret_cast<const floatx4 *>(c + 8 * k);
+    };
+    auto load = [&](int j, int s) {
+        const float *r = buf.rows + (wc + j * 32 + l32) * (SH * DK);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const uint32_t chunk = SH & 1 ? 4u * s + ((uint32_t)(2 * h + p) ^ tw) : (uint32_t)(4 * s + 2 * h + p) ^ tw;
+            b[s][p] = *reinterpret_cast<const gu32x4 *>(r + 4 * chunk);
+        }
+    };
+    load(0, 0);
+    load_start(0);
+#pragma unroll
+    for (int j = 0; j < JN; ++j) {
+        floatx16 acc[2];
+#pragma unroll
+        for (int s = 1; s < SH; ++s) load(j, s);
+#pragma unroll
+        for (int s = 0; s < SH; ++s)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, b[s][p]), __builtin_bit_cast(halfx8, afr[s][i][p]),
+                                                                    s == 0 && p == 0 ? start.all : acc[i], 0, 0, 0);
+        if (j + 1 < JN) {
+            load(j + 1, 0);
+            load_start(j + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        each(j, acc);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The same pass for SH = 1 .. 4 stages of 32 dimensions (packed dimension up to 128) as a sweep over `tiles_per_wg` centroid tiles.
+// JN = 4: a wavefront has 64 rows of its own and takes all of a tile with them, JN = 2: two wavefronts share 64 rows and take half
+// a tile each (sweep_wide).  The bound stays in registers over the sweep and reaches L[q] once.
 // The start values arrive in the accumulators' layout as the C operand of the first product, so that nothing but the
 // largest value of a lane is left to the vector units (8 instructions a block of 32 x 32 against 2 SH products of
 // 32 cycles); three wavefronts a SIMD cover the LDS and barrier latencies.  A report is kept short, since the other three
 // wavefronts wait for it at the tile's barrier: no look at single centroids, no LDS round trip, no atomic; the entries
 // are held in LDS, 64 at a time, and those that the bounds have not overtaken meanwhile go out with one atomic.
-// 500 000 rows x 16 384 (65 536) centroids, 96 dimensions: 1.83 (6.7) ms, 860 (935) TFLOP/s, where a kernel with the bound
-// and the norms in its epilogue and a pair an entry took 3.07 (10.5); without any report 1.6 (6.4), without the copies
-// of the tiles 1.4 (5.4).
-// Only direct-to-LDS copies write `ring` and `cns`, only explicit ds_read instructions read them.
-template <int SH>
+// 500 000 rows x 16 384 (65 536) centroids, 96 dimensions: 1.38 (4.92) ms, 1.14 (1.28) PFLOP/s, where the library's product
+// reaches 1.37.  With two wavefronts to 64 rows and every fragment waited for where it is read 1.58 - 1.67 (5.86): a tile was copied for half
+// as many products and a wavefront had half as many between barriers.  All of a block's fragments ahead of the block before instead
+// of the first: spills, 1.44 (5.13).  What is left is power: the matrix units are busy 0.53 (0.7) of the time, at 1.9 (1.6) GHz of 2.4.
+template <int SH, int JN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void coarse_shortlist_sweep_kernel(
     ShortlistArgs a, int tiles_per_wg)
 {
-    typedef const __attribute__((address_space(1))) void *gptr_t;
-    typedef __attribute__((address_space(3))) void *lptr_t;
-    constexpr int Dpf = SH * DK;                           // floats per row of the hi-only tables
-    constexpr int SLOT = GT * ROWF;
-    __shared__ __attribute__((aligned(16))) float ring[2][SH * SLOT];
-    __shared__ __attribute__((aligned(16))) float cns[2][GT];
+    __shared__ __attribute__((aligned(16))) SweepTile<SH> buf0;
+    __shared__ __attribute__((aligned(16))) SweepTile<SH> buf1;
     __shared__ __attribute__((aligned(16))) uint2 held_all[4][WAVE];
     ShortEntry *list = a.list + (blockIdx.x % SHORTLIST_SEGS) * a.seg_cap;
     unsigned long long *count = a.count + (blockIdx.x % SHORTLIST_SEGS) * 16;
@@ -1099,7 +1192,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
+    const int wq = (JN == 4 ? wave : wave >> 1) * 64, wc = JN == 4 ? 0 : (wave & 1) * 64;
     const int tq_per = (a.tiles_q + N_XCD - 1) / N_XCD;
     const int xcd = (int)(blockIdx.x % N_XCD);
     const int64_t local = blockIdx.x / N_XCD;
@@ -1109,37 +1202,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     int t_end = tb < a.tiles_c ? a.tiles_c - tb : 0;
     if (t_end > tiles_per_wg) t_end = tiles_per_wg;
     if (t_end <= 0) return;
-    const int64_t q0 = (int64_t)tq * GT;
+    const int64_t q0 = (int64_t)tq * (GT / 2 * JN) + wq;      // this wavefront's first row
 
-    // The copies of a tile: 8 SH pieces, dealt to the wavefronts (tile_twist), and from two of them 64 of the tile's start values
     const TileTwists<SH> twists(wave, lane);
-    const float *cbase = reinterpret_cast<const float *>(a.Ch);
-    auto issue_tile = [&](int t) {
-        const int tc = t < t_end ? t : t_end - 1;            // past the range: the last tile again, never read
-        if (wave < 2)
-            __builtin_amdgcn_global_load_lds((gptr_t)(a.start + (int64_t)(tb + tc) * GT + wave * 64 + lane), (lptr_t)(&cns[t & 1][wave * 64]), 4, 0, 0);
-        const float *src = cbase + (int64_t)(tb + tc) * GT * Dpf;
-        float *dst = &ring[t & 1][0];
-        // (one instruction in a rolled loop: the compiler tracks only a handful of distinct LDS copies exactly)
-#pragma nounroll
-        for (int n = wave; n < 8 * SH; n += 4)
-            __builtin_amdgcn_global_load_lds((gptr_t)(src + n * 256 + 4 * (lane ^ (int)twists.of(n))), (lptr_t)(dst + n * 256), 16, 0, 0);
+    float4 tl, tl_next;                                      // bounds of the tile, requested with its rows
+    auto issue = [&](int t, SweepTile<SH> &buf) {
+        const int tc = tb + (t < t_end ? t : t_end - 1);     // (past the range: never read)
+        sweep_copy(a.Ch, a.start, tc, buf, twists, wave, lane);
+        tl_next = a.tile[tc];
     };
-    issue_tile(0);
+    issue(0, buf0);
 
     gu32x4 afr[SH][2][2];
     float2 ql[2];
     float bound[2], before[2];
     bool qok[2];
+    sweep_rows(afr, a.Qh, q0, l32, h);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int64_t q = q0 + wq + i * 32 + l32;
-        const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(a.Qh) + q * Dpf) + 2 * h;
-#pragma unroll
-        for (int s = 0; s < SH; ++s) {
-            afr[s][i][0] = row[s * 4 + 0];
-            afr[s][i][1] = row[s * 4 + 1];
-        }
+        const int64_t q = q0 + i * 32 + l32;
         ql[i] = q < a.nq ? a.qlen[q] : make_float2(INFINITY, INFINITY);
         qok[i] = ql[i].x < INFINITY;
         if (!qok[i]) ql[i] = make_float2(0.f, 0.f);
@@ -1149,7 +1230,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         before[i] = bound[i] = !qok[i] ? INFINITY : seen ? key_float(seen) : -INFINITY;
     }
 
-    // the wavefront's entries: query (6 bits), tile, half and lane half (8 bits), which of the 16; upper end
+    // the wavefront's entries: row (6 bits), lane half, block (2 bits), tile (6 bits), which of the 16; upper end
     const uint32_t held = (uint32_t)reinterpret_cast<uintptr_t>(&held_all[wave][0]);
     int n_held = 0;                                           // (uniform)
     auto flush = [&]() {
@@ -1165,49 +1246,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             if (lane == 0) at = atomicAdd(count, (unsigned long long)__popcll(m));
             at = __shfl(at, 0, WAVE) + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
             if (live && at < a.seg_cap)
-                list[at] = ShortEntry{(int)(q0 + wq) + qi, (tb + (int)(e.x >> 8 & 63u)) * GT + wc + (int)(e.x >> 7 & 1u) * 32 + (int)(e.x >> 6 & 1u) * 4, e.x >> 16, up};
+                list[at] = ShortEntry{(int)q0 + qi, (tb + (int)(e.x >> 9 & 63u)) * GT + wc + (int)(e.x >> 7 & 3u) * 32 + (int)(e.x >> 6 & 1u) * 4, e.x >> 16, up};
         }
         n_held = 0;
     };
 
-    for (int t = 0; t < t_end; ++t) {
-        const float4 tl = a.tile[tb + t];                    // (uniform)
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wavefront's copies of tile t (issued a tile ago) are in
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // ... and everyone's; tile t - 1's buffer is free
-        issue_tile(t + 1);
-        const int64_t c0 = (int64_t)(tb + t) * GT;
+    auto step = [&](int t, const SweepTile<SH> &buf) {
         float eps[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) eps[i] = shortlist_eps(ql[i], tl.x, tl.y, a.Dp);
-        // One half of the wavefront's 64 centroids at a time, both blocks of 32 queries: every centroid fragment and start
-        // value is read from LDS once
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            floatx16 acc[2];
-            union { floatx16 all; floatx4 part[4]; } start;
-            const int rb = wc + j * 32 + l32;
-            // reads and their wait in one block each: nothing the compiler does to a register can come between
-            const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
-            const uint32_t rsw = 4u * (uint32_t)(rb * Dpf), k0 = 16u * ((uint32_t)(2 * h) ^ tile_twist<SH>(rb)), k1 = 16u * ((uint32_t)(2 * h + 1) ^ tile_twist<SH>(rb));
-#pragma unroll
-            for (int s = 0; s < SH; ++s) {
-                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][0]) + rsw;
-                const uint32_t b0 = bs + (SH & 1 ? k0 + 64u * s : k0 ^ 64u * s), b1 = bs + (SH & 1 ? k1 + 64u * s : k1 ^ 64u * s);
-                gu32x4 b[2];
-                if (s == 0)
-                    asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:32\n\tds_read_b128 %2, %6 offset:64\n\tds_read_b128 %3, %6 offset:96\n\t"
-                                 "ds_read_b128 %4, %7\n\tds_read_b128 %5, %8\n\ts_waitcnt lgkmcnt(0)"
-                                 : "=&v"(start.part[0]), "=&v"(start.part[1]), "=&v"(start.part[2]), "=&v"(start.part[3]), "=&v"(b[0]), "=&v"(b[1])
-                                 : "v"(cb), "v"(b0), "v"(b1));
-                else
-                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(b0), "v"(b1));
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, b[p]), __builtin_bit_cast(halfx8, afr[s][i][p]),
-                                                                        s == 0 && p == 0 ? start.all : acc[i], 0, 0, 0);
-            }
+        sweep_tile<SH, JN>(buf, afr, wc, l32, h, [&](int j, const floatx16 (&acc)[2]) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 float top = acc[i][0];
@@ -1225,20 +1273,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                     const int n = __popcll(m);
                     if (n_held + n > WAVE) flush();
                     const uint32_t at = held + 8u * ((uint32_t)n_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)));
-                    const uint2 e = make_uint2((uint32_t)(i * 32 + l32) | (uint32_t)h << 6 | (uint32_t)j << 7 | (uint32_t)t << 8 | reaching(acc[i], bound[i] - eps[i]) << 16,
+                    const uint2 e = make_uint2((uint32_t)(i * 32 + l32) | (uint32_t)h << 6 | (uint32_t)j << 7 | (uint32_t)t << 9 | reaching(acc[i], bound[i] - eps[i]) << 16,
                                                __float_as_uint(top + eps[i]));
                     if (pass) asm volatile("ds_write_b64 %0, %1" ::"v"(at), "v"(e) : "memory");
                     n_held += n;
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);   // the next half's products start with this half's registers free
-        }
+        });
+    };
+    for (int t = 0; t < t_end;) {
+        sweep_barrier();
+        tl = tl_next;
+        issue(t + 1, buf1);
+        step(t, buf0);
+        if (++t == t_end) break;
+        sweep_barrier();
+        tl = tl_next;
+        issue(t + 1, buf0);
+        step(t, buf1);
+        ++t;
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no copy into LDS may outlive the workgroup
     flush();
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-        if (qok[i] && h == 0 && bound[i] > before[i]) atomicMax(&a.L[q0 + wq + i * 32 + l32], float_key(bound[i]));
+        if (qok[i] && h == 0 && bound[i] > before[i]) atomicMax(&a.L[q0 + i * 32 + l32], float_key(bound[i]));
 }
 
 // Entries -> pairs.  A wavefront looks at 64 entries at a time; a lane whose entry L leaves forms the products of its

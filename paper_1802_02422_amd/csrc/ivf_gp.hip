@@ -885,18 +885,19 @@ int launch_flags(const ivf_index *ix, const float *Q, int64_t n, int P, const Se
     sparse_queries_kernel<<<dim3(rows_grid + zero_grid), dim3(256), 0, st>>>(Q, n, pad, D, Dp, a.cmax, ws.qpk, ws.qn, ws.qsi, qh, qlen, rows_grid,
                                                                             reinterpret_cast<unsigned long long *>(a.count), sp.count_words);
     LAUNCHCHK("sparse_queries_kernel");
-    const int tiles_q = (int)((n + GT - 1) / GT), tiles_c = (int)((K + GT - 1) / GT);
+    const bool wide = sweep_wide(n, K);
+    const int per_q = wide ? 2 * GT : GT, tiles_q = (int)((n + per_q - 1) / per_q), tiles_c = (int)((K + GT - 1) / GT);
     int per_wg = 64;
     while (per_wg > 4 && group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg) < 1536) per_wg /= 2;
     const int64_t grid = group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg);
     if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
-    auto sweep = [&](auto kernel) {
-        kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(qh, ix->chi, ix->mstart, a.best, a.half_ld, tiles_q, tiles_c, per_wg);
+    auto sweep = [&](auto narrow_kernel, auto wide_kernel) {
+        (wide ? wide_kernel : narrow_kernel)<<<dim3((unsigned)grid), dim3(256), 0, st>>>(qh, ix->chi, ix->mstart, a.best, a.half_ld, tiles_q, tiles_c, per_wg);
     };
-    if (Dp == 32) sweep(&coarse_minima_kernel<1>);
-    else if (Dp == 64) sweep(&coarse_minima_kernel<2>);
-    else if (Dp == 96) sweep(&coarse_minima_kernel<3>);
-    else sweep(&coarse_minima_kernel<4>);
+    if (Dp == 32) sweep(&coarse_minima_kernel<1, 2>, &coarse_minima_kernel<1, 4>);
+    else if (Dp == 64) sweep(&coarse_minima_kernel<2, 2>, &coarse_minima_kernel<2, 4>);
+    else if (Dp == 96) sweep(&coarse_minima_kernel<3, 2>, &coarse_minima_kernel<3, 4>);
+    else sweep(&coarse_minima_kernel<4, 2>, &coarse_minima_kernel<4, 4>);
     LAUNCHCHK("coarse_minima_kernel");
     // pieces: at least 8 P of them (sparse_pays: the table has at least 8 P tiles), or 2048
     const dim3 gq((unsigned)n);
@@ -1504,7 +1505,6 @@ struct ArgminCtx {
     // (best[] is then incomplete)
     int run_shortlist(const float *x, int64_t q0, int64_t m, bool *overflow, hipStream_t st)
     {
-        const int tiles_q = (int)((m + GT - 1) / GT);
         const int64_t tiles_c = (K + GT - 1) / GT;
         const float *xm = x + q0 * D;
         uint32_t *xw = words + 1 + (keep_rows ? q0 / chunk : 0);
@@ -1539,17 +1539,20 @@ struct ArgminCtx {
         a.pair_count = a.count + N_COUNTS / 2;
         a.seg_cap = seg_cap;
         a.pair_cap = pair_cap;
-        a.tiles_q = tiles_q;
         a.tiles_c = (int)tiles_c;
-        const int64_t tq8 = (int64_t)((tiles_q + N_XCD - 1) / N_XCD) * N_XCD;
+        const bool wide = Dp <= 128 && sweep_wide(m, K);
+        const int per_q = wide ? 2 * GT : GT;
+        a.tiles_q = (int)((m + per_q - 1) / per_q);
+        const int64_t tq8 = (int64_t)((a.tiles_q + N_XCD - 1) / N_XCD) * N_XCD;
         if (Dp <= 128) {   // query tile in registers, centroid tiles swept: long sweeps unless the chip would stand empty
             int per_wg = 64;
             while (per_wg > 4 && tq8 * ((tiles_c + per_wg - 1) / per_wg) < 1536) per_wg /= 2;
             const dim3 grid((unsigned)(tq8 * ((tiles_c + per_wg - 1) / per_wg)));
-            if (Dp == 32) coarse_shortlist_sweep_kernel<1><<<grid, dim3(256), 0, st>>>(a, per_wg);
-            else if (Dp == 64) coarse_shortlist_sweep_kernel<2><<<grid, dim3(256), 0, st>>>(a, per_wg);
-            else if (Dp == 96) coarse_shortlist_sweep_kernel<3><<<grid, dim3(256), 0, st>>>(a, per_wg);
-            else coarse_shortlist_sweep_kernel<4><<<grid, dim3(256), 0, st>>>(a, per_wg);
+            auto sweep = [&](auto narrow_kernel, auto wide_kernel) { (wide ? wide_kernel : narrow_kernel)<<<grid, dim3(256), 0, st>>>(a, per_wg); };
+            if (Dp == 32) sweep(&coarse_shortlist_sweep_kernel<1, 2>, &coarse_shortlist_sweep_kernel<1, 4>);
+            else if (Dp == 64) sweep(&coarse_shortlist_sweep_kernel<2, 2>, &coarse_shortlist_sweep_kernel<2, 4>);
+            else if (Dp == 96) sweep(&coarse_shortlist_sweep_kernel<3, 2>, &coarse_shortlist_sweep_kernel<3, 4>);
+            else sweep(&coarse_shortlist_sweep_kernel<4, 2>, &coarse_shortlist_sweep_kernel<4, 4>);
             LAUNCHCHK("coarse_shortlist_sweep_kernel");
         } else {
             if (tq8 * tiles_c >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large");

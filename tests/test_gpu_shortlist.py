@@ -238,3 +238,32 @@ def test_wide_rows_take_the_tile_kernel(D, K, nq):
     last = ivf.ivf_assign_stats()
     assert last[1] == after[1] + 1 and last[0] == after[0]
     assert (gid == 0).all()
+
+
+@pytest.mark.parametrize("D,K,nq", [(96, 8191, 16_640), (96, 300, 350_000), (20, 40_001, 3400), (64, 16_385, 8193), (128, 8320, 16_129)])
+def test_rows_enough_for_a_wavefront_to_64(D, K, nq):
+    """The sweep whose workgroups take 256 rows (from 8192 tiles of 128 x 128 on): partial last tiles of rows and centroids, a last
+    workgroup with rows for one wavefront, sweeps of odd and even numbers of tiles."""
+    print("case: wide sweep", D, K, nq, flush=True)
+    assert -(-nq // 128) * -(-K // 128) >= 8192
+    g = torch.Generator(device="cuda").manual_seed(D + K + nq)
+    C = torch.randn(K, D, generator=g, device="cuda")
+    own = torch.randint(0, K, (nq,), generator=g, device="cuda")
+    Q = C[own] + 0.4 * torch.randn(nq, D, generator=g, device="cuda")
+    before = ivf.ivf_assign_stats()
+    gid, gd = ivf.ivf_coarse_topk(C, Q, 1)
+    assert ivf.ivf_assign_stats()[0] > before[0]
+    c64 = C.double()
+    cn = (c64 ** 2).sum(1)
+    for a in range(0, nq, 4096):
+        q = Q[a:a + 4096].double()
+        qn = (q ** 2).sum(1)
+        d = (qn[:, None] + cn[None]).addmm_(q, c64.t(), alpha=-2.0).clamp_(min=0.0)
+        best, first = d.min(1)
+        tol = 16 * U * (qn + cn.max())
+        at = gid[a:a + 4096, 0].long()
+        got = d.gather(1, at[:, None])[:, 0]
+        assert bool((got <= best + tol).all()) and bool(((gd[a:a + 4096, 0].double() - got).abs() <= tol).all())
+        d.scatter_(1, first[:, None], float("inf"))
+        clear = d.min(1)[0] - best > 2 * tol
+        assert bool((at[clear] == first[clear]).all())
