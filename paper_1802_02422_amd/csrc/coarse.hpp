@@ -1300,6 +1300,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         if (qok[i] && h == 0 && bound[i] > before[i]) atomicMax(&a.L[q0 + i * 32 + l32], float_key(bound[i]));
 }
 
+// Bounds to start with where a centroid of every row is known that is likely near it (the nearest one of the last round of
+// k-means): L[q] = the lower end of its value, with its own lengths, as in shortlist_pairs_kernel.  A sweep that starts without
+// reports a row whenever a centroid is nearer than all before it, ln K times, and with 32 rows to a block nearly half of the blocks:
+// 500 000 rows x 16 384 1.38 ms, 1.32 with the bounds, which take 0.033, and shortlist_pairs_kernel 0.086 and 0.057.  Four lanes a row.
+__global__ __launch_bounds__(256) void seed_bounds_kernel(ShortlistArgs a, const int32_t *__restrict__ near)
+{
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+    const int64_t q = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2);
+    const int part = threadIdx.x & 3;
+    if (q >= a.nq) return;
+    const int64_t c = near[q];
+    if (c < 0 || c >= a.K) return;                           // (a row that is not finite has none)
+    const gu32x4 *qr = reinterpret_cast<const gu32x4 *>(a.Qh + q * a.Dp), *cr = reinterpret_cast<const gu32x4 *>(a.Ch + c * a.Dp);
+    float g = 0.f;
+#pragma unroll 4
+    for (int d = part; d < a.Dp / 8; d += 4) {
+        const gu32x4 u = qr[d], w = cr[d];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) g = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, (uint32_t)u[t]), __builtin_bit_cast(halfx2, (uint32_t)w[t]), g, false);
+    }
+    g += __shfl_xor(g, 1, WAVE);
+    g += __shfl_xor(g, 2, WAVE);
+    const float2 ql = a.qlen[q], cl = a.clen[c];
+    const float k = (float)(a.Dp + 32) * 0x1p-24f, back = 2.f * k / (0.5f - k), st = a.start[c];
+    const float low = fmaf(back, st, g + st) - shortlist_eps(ql, cl.x, cl.y, a.Dp);
+    if (part == 0 && low > -INFINITY) a.L[q] = float_key(low);
+}
+
 // Entries -> pairs.  A wavefront looks at 64 entries at a time; a lane whose entry L leaves forms the products of its
 // centroids from the packed rows again, one after the other (one is usual).  Grid: (any, SHORTLIST_SEGS); a segment whose
 // list overflowed is left alone.

@@ -1502,8 +1502,8 @@ struct ArgminCtx {
         return IVF_OK;
     }
     // shortlist + exact decision for the rows q0 .. q0 + m of x; *overflow = the list did not hold every candidate
-    // (best[] is then incomplete)
-    int run_shortlist(const float *x, int64_t q0, int64_t m, bool *overflow, hipStream_t st)
+    // (best[] is then incomplete); near (may be NULL): a centroid of every row, likely a near one
+    int run_shortlist(const float *x, int64_t q0, int64_t m, const int32_t *near, bool *overflow, hipStream_t st)
     {
         const int64_t tiles_c = (K + GT - 1) / GT;
         const float *xm = x + q0 * D;
@@ -1540,6 +1540,10 @@ struct ArgminCtx {
         a.seg_cap = seg_cap;
         a.pair_cap = pair_cap;
         a.tiles_c = (int)tiles_c;
+        if (near) {
+            seed_bounds_kernel<<<dim3((unsigned)((m + 63) / 64)), dim3(256), 0, st>>>(a, near + q0);
+            LAUNCHCHK("seed_bounds_kernel");
+        }
         const bool wide = Dp <= 128 && sweep_wide(m, K);
         const int per_q = wide ? 2 * GT : GT;
         a.tiles_q = (int)((m + per_q - 1) / per_q);
@@ -1577,14 +1581,14 @@ struct ArgminCtx {
         ++g_assign_short;
         return IVF_OK;
     }
-    // out_id[i] = nearest centroid of x[i] by (distance, id), out_d[i] (may be NULL) its squared distance
-    int run(const float *x, int64_t n, int32_t *out_id, float *out_d, hipStream_t st, int32_t missing = -1)
+    // out_id[i] = nearest centroid of x[i] by (distance, id), out_d[i] (may be NULL) its squared distance; near: may be out_id
+    int run(const float *x, int64_t n, int32_t *out_id, float *out_d, hipStream_t st, int32_t missing = -1, const int32_t *near = nullptr)
     {
         int rc;
         for (int64_t q0 = 0; q0 < n; q0 += chunk) {
             const int64_t m = (n - q0 < chunk) ? n - q0 : chunk;
             bool overflow = true;
-            if (shortlist && (rc = run_shortlist(x, q0, m, &overflow, st))) return rc;
+            if (shortlist && (rc = run_shortlist(x, q0, m, near, &overflow, st))) return rc;
             if (overflow && (rc = run_exact(x + q0 * D, m, st))) return rc;
             argmin_unpack_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, missing, out_id + q0, out_d ? out_d + q0 : nullptr);
             LAUNCHCHK("argmin_unpack_kernel");

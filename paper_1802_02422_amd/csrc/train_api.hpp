@@ -132,7 +132,8 @@ extern "C" int ivf_kmeans(const float *x, int64_t n, int D, int64_t K, int iters
         const int bits = bits_for(K);
         for (int it = 0; it < iters; ++it) {
             if ((r2 = ctx.set_centroids(centroids, st))) return r2;
-            if ((r2 = ctx.run(x, n, static_cast<int32_t *>(lab.p), static_cast<float *>(dist.p), st))) return r2;
+            int32_t *lb = static_cast<int32_t *>(lab.p);
+            if ((r2 = ctx.run(x, n, lb, static_cast<float *>(dist.p), st, -1, it ? lb : nullptr))) return r2;
             if (objective) {
                 fixed_sum_kernel<float><<<dim3(1), dim3(1024), 0, st>>>(static_cast<float *>(dist.p), n, objective + it);
                 LAUNCHCHK("fixed_sum_kernel");
