@@ -960,6 +960,7 @@ struct ShortlistArgs {
     const float2 *clen;          // lengths of the centroids, whole tiles
     int Dp;
     uint32_t *L;                 // [nq] float_key of the largest lower end seen (starts at 0: below every key)
+    uint32_t *n_pairs;           // [nq] pairs of a row (starts at 0)
     ShortEntry *list;
     ShortPair *pairs;
     unsigned long long *count, *pair_count;
@@ -1386,6 +1387,7 @@ __global__ __launch_bounds__(256) void shortlist_pairs_kernel(ShortlistArgs a)
             }
             const uint64_t m = __ballot(pass);
             if (n_held + __popcll(m) > WAVE) flush();
+            if (pass) atomicAdd(&a.n_pairs[e.q], 1u);
             if (pass) held[n_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = ShortPair{e.q, c, up};
             n_held += __popcll(m);
         }
@@ -1396,7 +1398,9 @@ __global__ __launch_bounds__(256) void shortlist_pairs_kernel(ShortlistArgs a)
 // Exact decision among the pairs that the final bounds leave: a wavefront per pair computes |x - c|^2 from the fp32
 // rows (differences squared, summed in a tree over the lanes: a few ulps) and merges (distance, id) into best[q] with a
 // 64-bit atomic minimum.  best must be pre-filled with all ones.  A wavefront looks at up to 64 pairs at a time, fewer
-// where the list is short, so that all wavefronts have some (11 575 rows: 69 us with 64 always).
+// where the list is short, so that all wavefronts have some (11 575 rows: 69 us with 64 always).  Where the distances are not asked
+// for (DIST = false), a row's only pair needs none: 500 000 rows, nearly all of which have one, 100 us, 13 so.
+template <bool DIST>
 __global__ __launch_bounds__(256) void rerank_kernel(const float *__restrict__ X, const float *__restrict__ C, int D, ShortlistArgs a,
                                                      unsigned long long *__restrict__ best)
 {
@@ -1411,6 +1415,10 @@ __global__ __launch_bounds__(256) void rerank_kernel(const float *__restrict__ X
         if (live) {
             e = a.pairs[blockIdx.y * a.pair_cap + i0 + lane];
             live = float_key(e.up) >= a.L[e.q];
+            if (!DIST && a.n_pairs[e.q] == 1u) {
+                best[e.q] = (uint32_t)e.c;
+                live = false;
+            }
         }
         for (uint64_t todo = __ballot(live); todo; todo &= todo - 1) {
             const int s = __builtin_ctzll(todo);

@@ -1397,7 +1397,7 @@ struct ArgminCtx {
     float *start = nullptr;
     float4 *tile = nullptr;
     unsigned long long *best = nullptr, *counts = nullptr;
-    uint32_t *L = nullptr;
+    uint32_t *L = nullptr, *n_pairs = nullptr;                // side by side
     ShortEntry *list = nullptr;
     ShortPair *pairs = nullptr;
     unsigned long long seg_cap = 0, pair_cap = 0;
@@ -1452,7 +1452,7 @@ struct ArgminCtx {
             place(tile, (size_t)tiles_c);
             place(xhk, (size_t)packed_rows(rows) * Dp);
             place(xlen, (size_t)packed_rows(rows));
-            place(L, (size_t)(chunk + 2));                      // filled in 64-bit words
+            place(L, (size_t)(2 * (chunk + 2)));                // filled in 64-bit words
             place(list, (size_t)seg_cap * SHORTLIST_SEGS);
             place(pairs, (size_t)pair_cap * SHORTLIST_SEGS);
             place(counts, (size_t)N_COUNTS);
@@ -1502,8 +1502,9 @@ struct ArgminCtx {
         return IVF_OK;
     }
     // shortlist + exact decision for the rows q0 .. q0 + m of x; *overflow = the list did not hold every candidate
-    // (best[] is then incomplete); near (may be NULL): a centroid of every row, likely a near one
-    int run_shortlist(const float *x, int64_t q0, int64_t m, const int32_t *near, bool *overflow, hipStream_t st)
+    // (best[] is then incomplete); near (may be NULL): a centroid of every row, likely a near one; want_d: distances too, not
+    // only the centroids
+    int run_shortlist(const float *x, int64_t q0, int64_t m, const int32_t *near, bool want_d, bool *overflow, hipStream_t st)
     {
         const int64_t tiles_c = (K + GT - 1) / GT;
         const float *xm = x + q0 * D;
@@ -1517,8 +1518,9 @@ struct ArgminCtx {
         LAUNCHCHK("shortlist_tiles_kernel");
         fill_u64_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, ~0ull);
         LAUNCHCHK("fill_u64_kernel");
-        // L: 32-bit words, two per 64-bit fill; the counters likewise
-        fill_u64_kernel<<<dim3((unsigned)(((m + 1) / 2 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<unsigned long long *>(L), (m + 1) / 2, 0ull);
+        // L and the numbers of pairs: 32-bit words, two per 64-bit fill; the counters likewise
+        n_pairs = L + (m + 1) / 2 * 2;
+        fill_u64_kernel<<<dim3((unsigned)((m + 1 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<unsigned long long *>(L), (m + 1) / 2 * 2, 0ull);
         LAUNCHCHK("fill_u64_kernel");
         fill_u64_kernel<<<dim3((N_COUNTS + 255) / 256), dim3(256), 0, st>>>(counts, N_COUNTS, 0ull);
         LAUNCHCHK("fill_u64_kernel");
@@ -1533,6 +1535,7 @@ struct ArgminCtx {
         a.clen = clen;
         a.Dp = Dp;
         a.L = L;
+        a.n_pairs = n_pairs;
         a.list = list;
         a.pairs = pairs;
         a.count = counts;
@@ -1566,7 +1569,7 @@ struct ArgminCtx {
         // (loops over the lists: a grid that fills the chip, whatever their length)
         shortlist_pairs_kernel<<<dim3(64, SHORTLIST_SEGS), dim3(256), 0, st>>>(a);
         LAUNCHCHK("shortlist_pairs_kernel");
-        rerank_kernel<<<dim3(32, SHORTLIST_SEGS), dim3(256), 0, st>>>(xm, centroids, D, a, best);
+        (want_d ? &rerank_kernel<true> : &rerank_kernel<false>)<<<dim3(32, SHORTLIST_SEGS), dim3(256), 0, st>>>(xm, centroids, D, a, best);
         LAUNCHCHK("rerank_kernel");
         unsigned long long n[N_COUNTS];
         HIPCHK(hipMemcpyAsync(n, counts, sizeof(n), hipMemcpyDeviceToHost, st));
@@ -1588,7 +1591,7 @@ struct ArgminCtx {
         for (int64_t q0 = 0; q0 < n; q0 += chunk) {
             const int64_t m = (n - q0 < chunk) ? n - q0 : chunk;
             bool overflow = true;
-            if (shortlist && (rc = run_shortlist(x, q0, m, near, &overflow, st))) return rc;
+            if (shortlist && (rc = run_shortlist(x, q0, m, near, out_d != nullptr, &overflow, st))) return rc;
             if (overflow && (rc = run_exact(x + q0 * D, m, st))) return rc;
             argmin_unpack_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, missing, out_id + q0, out_d ? out_d + q0 : nullptr);
             LAUNCHCHK("argmin_unpack_kernel");

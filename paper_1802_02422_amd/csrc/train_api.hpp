@@ -127,13 +127,13 @@ extern "C" int ivf_kmeans(const float *x, int64_t n, int D, int64_t K, int iters
         if ((r2 = ctx.init(K, D, n, iters > 1))) return r2;
         if ((r2 = rb.init(n))) return r2;
         HIPCHK(lab.alloc((size_t)n * sizeof(int32_t)));
-        HIPCHK(dist.alloc((size_t)n * sizeof(float)));
+        if (objective) HIPCHK(dist.alloc((size_t)n * sizeof(float)));
         HIPCHK(off.alloc((size_t)(K + 1) * sizeof(uint32_t)));
         const int bits = bits_for(K);
         for (int it = 0; it < iters; ++it) {
             if ((r2 = ctx.set_centroids(centroids, st))) return r2;
             int32_t *lb = static_cast<int32_t *>(lab.p);
-            if ((r2 = ctx.run(x, n, lb, static_cast<float *>(dist.p), st, -1, it ? lb : nullptr))) return r2;
+            if ((r2 = ctx.run(x, n, lb, objective ? static_cast<float *>(dist.p) : nullptr, st, -1, it ? lb : nullptr))) return r2;
             if (objective) {
                 fixed_sum_kernel<float><<<dim3(1), dim3(1024), 0, st>>>(static_cast<float *>(dist.p), n, objective + it);
                 LAUNCHCHK("fixed_sum_kernel");
