@@ -208,37 +208,64 @@ __global__ __launch_bounds__(256) void segment_sum_kernel(const T *__restrict__ 
     }
 }
 
-// Means of segments of whole rows of X ([.][D] fp32), lane = column, in fp64, eight rows on their way at a time: one
-// wavefront per segment and 64 columns where the segment has up to SHORT_SEGMENT rows, the rows one after the other; a
+// Means of segments of whole rows of X ([.][D] fp32), lane = column (or two), in fp64, eight (16) rows on their way at a time: one
+// wavefront per segment and 64 (128) columns where the segment has up to SHORT_SEGMENT rows, the rows one after the other; a
 // workgroup of 16 wavefronts where it has more, wavefront w taking rows 8 w .. 8 w + 7 of every 128.  Either way the sum is a
 // function of the member list alone.  An empty segment's mean is left alone.
 // segment_sum_kernel has 256 threads and a tree with 8 barriers for every 8 columns, most of them idle when a segment
-// has 30 rows (500 000 rows in 16 384 clusters, 96 columns: 0.77 ms a call, 0.20 so).  The bound is what a wavefront's chain
+// has 30 rows (500 000 rows in 16 384 clusters, 96 columns: 0.77 ms a call, 0.09 so).  The bound is what a wavefront's chain
 // may take beside the rest: 64 steps of about a microsecond.  With 1 % (10, 60) of those rows in one cluster a call takes
 // 0.40 (2.1, 12) ms, with one wavefront for them 1.7 (15, 93), with segment_sum_kernel 0.77 (3.8, 22).
 constexpr uint32_t SHORT_SEGMENT = 512;
 
+// COLS: columns of a lane in a row, 2 where D is even.  A short segment's wavefront reads the numbers of its rows 64 at a time, ahead of the
+// rows, and has 16 rows on their way: 500 000 rows x 96 in 16 384 segments 157 us with the numbers read in front of every
+// eight rows and a wavefront for 64 columns, 45 so (4.3 TB/s of rows).
+typedef float float2any __attribute__((ext_vector_type(2), aligned(4)));   // 8 bytes at any float's address
+
+template <int COLS>
 __global__ __launch_bounds__(256) void short_segment_mean_kernel(const float *__restrict__ X, int D, const uint32_t *__restrict__ perm,
                                                                  const uint32_t *__restrict__ off, int64_t n_seg, float *__restrict__ mean)
 {
-    const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int c = blockIdx.y * WAVE + (threadIdx.x & 63);
+    const int64_t g = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, c = (blockIdx.y * WAVE + lane) * COLS;
     if (g >= n_seg) return;
     const uint32_t b = off[g], e = off[g + 1];
     if (e <= b || e - b > SHORT_SEGMENT) return;
-    double sum = 0.0;
-    for (uint32_t j0 = b; j0 < e; j0 += 8) {
-        float v[8];
+    constexpr int U = 16;
+    const int at = c < D ? c : 0;                              // (every lane loads)
+    double sum[COLS] = {};
+    uint32_t next = perm[b + lane < e ? b + lane : b];
+    for (uint32_t j0 = b; j0 < e; j0 += WAVE) {
+        const uint32_t rows = next;
+        const int n = e - j0 < WAVE ? (int)(e - j0) : WAVE;     // (uniform)
+        if (j0 + WAVE < e) next = perm[j0 + WAVE + lane < e ? j0 + WAVE + lane : b];
+        for (int i0 = 0; i0 < n; i0 += U) {
+            float v[U][COLS];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = j0 + u < e && c < D ? X[(int64_t)perm[j0 + u] * D + c] : 0.f;
+            for (int u = 0; u < U; ++u) {
+                const float *row = X + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)rows, i0 + u < n ? i0 + u : i0) * D + at;
+                if constexpr (COLS == 2) {
+                    const float2any w = *reinterpret_cast<const float2any *>(row);
+                    v[u][0] = w.x;
+                    v[u][1] = w.y;
+                } else {
+                    v[u][0] = *row;
+                }
+            }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (j0 + u < e) sum += (double)v[u];
+            for (int u = 0; u < U; ++u)
+                if (i0 + u < n) {
+#pragma unroll
+                    for (int k = 0; k < COLS; ++k) sum[k] += (double)v[u][k];
+                }
+        }
     }
-    if (c < D) mean[g * D + c] = (float)(sum / (double)(e - b));
+    if (c < D) {
+#pragma unroll
+        for (int k = 0; k < COLS; ++k) mean[g * D + c + k] = (float)(sum[k] / (double)(e - b));
+    }
 }
-
-// grid: (any, columns / 64); a workgroup looks through a share of the segments for the long ones, 64 at a time
 __global__ __launch_bounds__(1024) void long_segment_mean_kernel(const float *__restrict__ X, int D, const uint32_t *__restrict__ perm,
                                                                  const uint32_t *__restrict__ off, int64_t n_seg, float *__restrict__ mean)
 {

@@ -67,7 +67,8 @@ int launch_cluster_means(const float *x, int D, const uint32_t *perm, const uint
     const unsigned columns = (unsigned)((D + WAVE - 1) / WAVE);
     long_segment_mean_kernel<<<dim3((unsigned)(K < 256 ? K : 256), columns), dim3(1024), 0, st>>>(x, D, perm, off, K, centroids);
     LAUNCHCHK("long_segment_mean_kernel");
-    short_segment_mean_kernel<<<dim3(grid_for(K, 4), columns), dim3(256), 0, st>>>(x, D, perm, off, K, centroids);
+    if (D % 2 == 0) short_segment_mean_kernel<2><<<dim3(grid_for(K, 4), (columns + 1) / 2), dim3(256), 0, st>>>(x, D, perm, off, K, centroids);
+    else short_segment_mean_kernel<1><<<dim3(grid_for(K, 4), columns), dim3(256), 0, st>>>(x, D, perm, off, K, centroids);
     LAUNCHCHK("short_segment_mean_kernel");
     return IVF_OK;
 }
