@@ -157,46 +157,109 @@ __global__ __launch_bounds__(64) void encode_kernel(
     }
 }
 
+// The centroid table in 8 bits for subregion_kernel: row c is s ~ step * q, q in -127 .. 127, step the 127th part of its largest
+// component, with its step, |s|^2, |ds| and |s| (ds: what the rounding left out) behind the components where a row of 128 bytes has
+// room for them, so that one line holds it all, and in an array of their own where 128 components fill it.  A row that is not finite:
+// zeros with infinite lengths.
+template <int DP>   // packed dimension
+struct ByteRow {
+    static constexpr bool INSIDE = DP < 128;
+    static constexpr int BYTES = DP == 32 ? 64 : 128, TAIL_STRIDE = INSIDE ? BYTES : 16;
+    static constexpr int CHUNKS = BYTES / 64;                // 16-byte pieces of a row that a lane of four holds
+};
+inline size_t byte_row_bytes(int Dp) { return Dp == 32 ? 64 : Dp == 128 ? 144 : 128; }   // of a row and what belongs to it
+
+template <int DP>
+__global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__restrict__ X, int64_t n, int D, uint8_t *__restrict__ rows, uint8_t *__restrict__ tails)
+{
+    typedef ByteRow<DP> R;
+    constexpr int PER = R::BYTES / 16, LIVE = DP / 16;        // 16 bytes a lane
+    const int64_t row = (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER;
+    const int lane = threadIdx.x % PER;
+    float v[16], big = 0.f, s2 = 0.f, d2 = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (row < n && lane < LIVE && 16 * lane + 4 * u < D) w = *reinterpret_cast<const float4 *>(X + row * D + 16 * lane + 4 * u);   // (D is a multiple of 4)
+        v[4 * u] = w.x; v[4 * u + 1] = w.y; v[4 * u + 2] = w.z; v[4 * u + 3] = w.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        big = fmaxf(big, fabsf(v[i]));
+        s2 = fmaf(v[i], v[i], s2);
+    }
+#pragma unroll
+    for (int o = PER / 2; o > 0; o >>= 1) {
+        big = fmaxf(big, __shfl_xor(big, o, WAVE));
+        s2 += __shfl_xor(s2, o, WAVE);
+    }
+    const bool finite = s2 < INFINITY;
+    const float step = big * (1.f / 127.f), per = big > 0x1p-100f && finite ? 127.f / big : 0.f;
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const float q = fminf(fmaxf(rintf((finite ? v[i] : 0.f) * per), -127.f), 127.f), d = fmaf(-q, step, v[i]);
+        d2 = fmaf(d, d, d2);
+        w[i >> 2] |= ((uint32_t)(int)q & 255u) << (8 * (i & 3));
+    }
+#pragma unroll
+    for (int o = PER / 2; o > 0; o >>= 1) d2 += __shfl_xor(d2, o, WAVE);
+    if (row >= n) return;
+    if (lane < LIVE) *reinterpret_cast<uint4 *>(rows + row * R::BYTES + 16 * lane) = make_uint4(w[0], w[1], w[2], w[3]);
+    if (lane == 0)
+        *reinterpret_cast<float4 *>(tails + row * R::TAIL_STRIDE) =
+            finite ? make_float4(step, s2, sqrtf(d2) * (1.f + 0x1p-10f), sqrtf(s2) * (1.f + 0x1p-10f)) : make_float4(0.f, INFINITY, INFINITY, INFINITY);
+}
+
 // Subregion, displacement and subcentroid (Eqs. (3), (4)) for packed dimensions up to 128 and L <= 64, one wavefront for
 // SUB_RUN consecutive points.  Bound by the neighbours' rows: encode_kernel reads L fp32 rows a point.  Here the
-// wavefront holds the neighbours' rows as fp16 (pack_hi_rows_kernel) in registers, half the bytes, and keeps them while
+// wavefront holds the neighbours' rows in 8 bits (pack_byte_rows_kernel) in registers, a 128-byte line each, and keeps them while
 // the region stays the same: points in the order of their regions share the read.  Four lanes hold a row, 64 bytes of it
 // each load (a row a lane: 64 rows for 16 bytes each, 0.54 against 0.50 ms for 500 000 points on 65 536 regions);
-// neighbour 16 p + g is looked after by lane 4 g + p.  The score of Eq. (7) is then known to within
+// neighbour 16 p + g is looked after by lane 4 g + p.  The point is taken in 15 bits, as two 8-bit halves, so that products are whole numbers
+// (v_dot4).  The score of Eq. (7) is then known to within
 //   err_l = 2 |a| e_l + roundings,  e_l = |dx| |s_l| + (|x| + |dx|) |ds_l| + k |x| |s_l|
-// (see the nearest-centroid shortlist), and only neighbours whose lower end does not exceed the smallest upper end, 1.1
-// of 64 on unit vectors, are decided by the fp32 differences, with encode_kernel's arithmetic: the same subregion.
-// 2 * 10^6 points in region order (two a region), K = 2^20, L = 64, D = 96: 3.8 ms against 7.3, and 5.7 TB/s of the
-// 128-byte lines that rows, points and displacements touch.
+// (see the nearest-centroid shortlist), and only neighbours whose lower end does not exceed the smallest upper end are decided by the
+// fp32 differences, with encode_kernel's arithmetic: the same subregion.  A third of the points of unit vectors have several such; they
+// are put by and decided when the wavefront has been through its points, eight neighbours on their way at a time whatever point
+// they belong to (decided where they come up, with the loads and sums of one point behind those of another: 0.56 ms for
+// 500 000 points on 65 536 regions, 0.50 so, 0.445 with five wavefronts a SIMD).
+// 2 * 10^6 points in region order (two a region), K = 2^20, L = 64, D = 96: 2.27 ms; with fp16 rows, two lines each, whose bound leaves
+// 1.1 of 64, 3.8; encode_kernel 7.3.
 // perm (may be NULL): the order in which the points are taken.
 constexpr int SUB_RUN = 16;
 
-template <int NCH>   // 16-byte chunks of a packed row
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH <= 12 ? 4 : 3, NCH <= 12 ? 4 : 3))) void subregion_kernel(
+template <int DP>   // packed dimension
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) void subregion_kernel(
     const float *__restrict__ X, int64_t n, int D, int L, const int32_t *__restrict__ region, const int32_t *__restrict__ perm,
-    const float *__restrict__ C, const _Float16 *__restrict__ Ch, const float2 *__restrict__ clen, const uint32_t *__restrict__ cmax,
+    const float *__restrict__ C, const uint8_t *__restrict__ rows, const uint8_t *__restrict__ tails,
     const int32_t *__restrict__ nbr, const float *__restrict__ alpha, const float *__restrict__ cs_dist2,
     int32_t *__restrict__ out_sub, float *__restrict__ out_res, float *__restrict__ out_mu)
 {
-    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-    constexpr int Dp = NCH * 8;
-    __shared__ __attribute__((aligned(16))) float xs_all[4][Dp];
-    __shared__ __attribute__((aligned(16))) _Float16 xh_all[4][Dp];
+    typedef ByteRow<DP> R;
+    constexpr int CH = R::CHUNKS;
+    __shared__ __attribute__((aligned(16))) float xs_all[4][DP];
+    __shared__ __attribute__((aligned(16))) int8_t xh_all[4][2][R::BYTES];   // high and low halves; zeros behind the components
+    __shared__ uint16_t pairs_all[4][SUB_RUN * WAVE];
+    __shared__ unsigned long long best_all[4][SUB_RUN];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float *xs = xs_all[wave];
-    _Float16 *xh = xh_all[wave];
-    const int sh = hi_scale(*cmax);
-    const float inv_round = 1.f / (1.f + 0x1p-10f);            // (lengths are rounded up by it)
+    int8_t *xh = xh_all[wave][0], *xl = xh_all[wave][1];
+    uint16_t *pairs = pairs_all[wave];
+    unsigned long long *best = best_all[wave];
     const int64_t first = ((int64_t)blockIdx.x * 4 + wave) * SUB_RUN;
     if (first >= n) return;
+    for (int t = lane; t < 2 * R::BYTES / 4; t += WAVE) reinterpret_cast<uint32_t *>(xh)[t] = 0;
     const int cnt = n - first < SUB_RUN ? (int)(n - first) : SUB_RUN;
     // lane j: point and region of the run's j-th point, later its subregion.  The points, and the neighbour ids of the next
     // region, are requested a step ahead: what is left to wait for is the rows.
     const int64_t i_of = lane < cnt ? (perm ? (int64_t)perm[first + lane] : first + lane) : 0;
     const int32_t r_of = lane < cnt ? region[i_of] : 0;
     int32_t l_of = 0;
+    unsigned long long best_of = 0;                             // ~0: undecided
+    int n_pairs = 0;                                            // (uniform) point << 6 | neighbour in `pairs`
     auto point = [&](int j) { return ((int64_t)__builtin_amdgcn_readlane((int)(i_of >> 32), j) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)i_of, j); };
-    constexpr int XP = (Dp + WAVE - 1) / WAVE;
+    constexpr int XP = (DP + WAVE - 1) / WAVE;
     float xn[XP];
     auto fetch_x = [&](int j) {
         const int64_t i = point(j);
@@ -211,12 +274,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH <= 12 ?
         cs_n = my_l < L ? cs_dist2[r * L + my_l] : 0.f;
         a_n = alpha[r];
     };
+    auto tail = [&](int64_t r) { return *reinterpret_cast<const float4 *>(tails + r * R::TAIL_STRIDE); };
     fetch_x(0);
     fetch_nbr(__builtin_amdgcn_readlane(r_of, 0));
     int64_t held = -1;                                          // region whose rows the lanes hold
-    gu32x4 row[4][NCH / 4];                                      // [t]: of neighbour 16 t + lane / 4, chunks part, part + 4, ..
-    float a = 0.f, cs = 0.f, s2 = 0.f, c2 = 0.f;
-    float2 sl = make_float2(0.f, 0.f);
+    gu32x4 row[4][CH];                                           // [t]: of neighbour 16 t + lane / 4, chunks part, part + 4, ..
+    float a = 0.f, cs = 0.f, c2 = 0.f;
+    float4 sl = make_float4(0.f, 0.f, 0.f, 0.f);                 // step, |s|^2, |ds|, |s|
     int32_t my_nbr = 0;
     for (int j = 0; j < cnt; ++j) {                             // (uniform)
         const int64_t r = __builtin_amdgcn_readlane(r_of, j);
@@ -225,123 +289,137 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH <= 12 ?
             a = a_n;
             my_nbr = nbr_n;
             cs = cs_n;
-            sl = clen[my_nbr];
             const int of_t[4] = {__builtin_amdgcn_update_dpp(0, my_nbr, 0x00, 0xf, 0xf, false), __builtin_amdgcn_update_dpp(0, my_nbr, 0x55, 0xf, 0xf, false),
                                  __builtin_amdgcn_update_dpp(0, my_nbr, 0xAA, 0xf, 0xf, false), __builtin_amdgcn_update_dpp(0, my_nbr, 0xFF, 0xf, 0xf, false)};   // lane t of the quad
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int k = 0; k < NCH / 4; ++k)
-                    row[t][k] = *reinterpret_cast<const gu32x4 *>(Ch + (int64_t)of_t[t] * Dp + 8 * (4 * k + part));
-            const float cl = clen[r].x;
+                for (int k = 0; k < CH; ++k)
+                    row[t][k] = *reinterpret_cast<const gu32x4 *>(rows + (int64_t)of_t[t] * R::BYTES + 16 * (4 * k + part));
+            sl = tail(my_nbr);
+            c2 = tail(r).y;
             const uint64_t later = __ballot(lane > j && lane < cnt && r_of != (int32_t)r);
             if (later) fetch_nbr(__builtin_amdgcn_readlane(r_of, __builtin_ctzll(later)));
-            s2 = sl.x * inv_round * (sl.x * inv_round);
-            c2 = cl * cl;
         }
-        // the point: fp32 and, in the order of the packed rows, fp16
-        float x2 = 0.f, d2 = 0.f;
+        // the point: fp32 and as two bytes
+        float x2 = 0.f, d2 = 0.f, big = 0.f;
+#pragma unroll
+        for (int u = 0; u < XP; ++u) big = fmaxf(big, fabsf(xn[u]));
+        big = __uint_as_float(wave_extreme<true>(__float_as_uint(big)));   // (not negative: the bits order like it)
+        const float step = big * (1.f / 16256.f), per = big > 0x1p-100f && big < INFINITY ? 16256.f / big : 0.f;
         wave_sync();
 #pragma unroll
         for (int u = 0; u < XP; ++u) {
             const int t = lane + u * WAVE;
-            if (t >= Dp) break;
-            const float v = xn[u], f = __builtin_amdgcn_ldexpf(v, sh);
-            const _Float16 hi = (_Float16)f;
-            const float d = f - (float)hi;
-            x2 = fmaf(f, f, x2);
+            const float v = xn[u], q = fminf(fmaxf(rintf(v * per), -16256.f), 16256.f), d = fmaf(-q, step, v);
+            x2 = fmaf(v, v, x2);
             d2 = fmaf(d, d, d2);
-            xs[t] = v;
-            const int k8 = (t >> 3) & 3;                       // 8 dimensions k8 of 32 lie in chunk 0, 2, 1, 3
-            xh[(t & ~31) + 8 * ((k8 & 1) * 2 + (k8 >> 1)) + (t & 7)] = hi;
+            if (t < DP) {
+                xs[t] = v;
+                const int w = (int)q, hi = (w + 64) >> 7;
+                xh[t] = (int8_t)hi;
+                xl[t] = (int8_t)(w - 128 * hi);
+            }
         }
         if (j + 1 < cnt) fetch_x(j + 1);
         x2 = wave_total(x2);
         d2 = wave_total(d2);
         wave_sync();
-        float d4[4] = {0.f, 0.f, 0.f, 0.f};
+        int ih[4] = {0, 0, 0, 0}, il[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int k = 0; k < NCH / 4; ++k) {
-            const gu32x4 w = *reinterpret_cast<const gu32x4 *>(&xh[8 * (4 * k + part)]);
+        for (int k = 0; k < CH; ++k) {
+            const gu32x4 wh = *reinterpret_cast<const gu32x4 *>(&xh[16 * (4 * k + part)]), wl = *reinterpret_cast<const gu32x4 *>(&xl[16 * (4 * k + part)]);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    d4[t] = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2, (uint32_t)w[u]), __builtin_bit_cast(halfx2, (uint32_t)row[t][k][u]), d4[t], false);
+                for (int u = 0; u < 4; ++u) {
+                    ih[t] = __builtin_amdgcn_sdot4((int)wh[u], (int)row[t][k][u], ih[t], false);
+                    il[t] = __builtin_amdgcn_sdot4((int)wl[u], (int)row[t][k][u], il[t], false);
+                }
         }
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {                             // over the four lanes of the row
-            d4[t] += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(d4[t]), 0xB1, 0xf, 0xf, false));
-            d4[t] += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(d4[t]), 0x4E, 0xf, 0xf, false));
+        for (int t = 0; t < 4; ++t) {                             // over the four lanes of the row (below 2^28)
+            ih[t] = 128 * ih[t] + il[t];
+            ih[t] += __builtin_amdgcn_update_dpp(0, ih[t], 0xB1, 0xf, 0xf, false);
+            ih[t] += __builtin_amdgcn_update_dpp(0, ih[t], 0x4E, 0xf, 0xf, false);
         }
-        const float dot = part & 2 ? (part & 1 ? d4[3] : d4[2]) : (part & 1 ? d4[1] : d4[0]);
-        // in units of the scaled rows; what all neighbours have in common is left out
+        const float dot = (float)(part & 2 ? (part & 1 ? ih[3] : ih[2]) : (part & 1 ? ih[1] : ih[0])) * (step * sl.x);
+        // what all neighbours have in common is left out
         const float2 ql = make_float2(sqrtf(x2) * (1.f + 0x1p-10f), sqrtf(d2) * (1.f + 0x1p-10f));
-        const float css = __builtin_amdgcn_ldexpf(cs, 2 * sh);
-        const float h = fmaf(a, fmaf(-2.f, dot, s2), -a * (1.f - a) * css);
+        const float s2 = sl.y;
+        const float h = fmaf(a, fmaf(-2.f, dot, s2), -a * (1.f - a) * cs);
         // roundings: of the fp32 sum of differences, (D/16 + 12) 2^-24 of at most 2 (x2 + s2), and of the three-term score,
         // 2^-20 of the size of its terms (the scaling factor may be any number: none of them has to be small)
         const float aa = fabsf(a), ac = fabsf(1.f - a);
-        const float size = fmaf(aa, x2 + s2, fmaf(ac, x2 + c2, aa * ac * fabsf(css)));
-        const float err = fmaf(2.f * aa, shortlist_eps(ql, sl.x, sl.y, Dp), fmaf(aa * (float)(D / 16 + 12) * 0x1p-23f, x2 + s2, 0x1p-20f * size));
+        // (and 2^-120 for values whose squares leave the range of fp32)
+        const float size = fmaf(aa, x2 + s2, fmaf(ac, x2 + c2, aa * ac * fabsf(cs)));
+        const float err = fmaf(2.f * aa, shortlist_eps(ql, sl.w, sl.z, DP), fmaf(aa * (float)(D / 16 + 12) * 0x1p-23f, x2 + s2, fmaf(0x1p-20f, size, 0x1p-120f)));
         float up = my_l < L ? h + err : INFINITY;
         up = wave_smallest(up);
         uint64_t todo = __ballot(my_l < L && !(h - err > up));
         auto l_at = [](int s) { return 16 * (s & 3) + (s >> 2); };
         int best_l = todo ? l_at(__builtin_ctzll(todo)) : 0;
-        if (todo & (todo - 1)) {                               // more than one: the fp32 scores decide
-            const int D4 = D >> 2, g = lane >> 4, c16 = lane & 15;
-            float dxc = 0.f;
-            for (int cc = lane; cc < D4; cc += WAVE) {
-                const float4 xv = *reinterpret_cast<const float4 *>(xs + 4 * cc);
-                const float4 cv = *reinterpret_cast<const float4 *>(C + r * D + 4 * cc);
-                const float u0 = xv.x - cv.x, u1 = xv.y - cv.y, u2 = xv.z - cv.z, u3 = xv.w - cv.w;
-                dxc = fmaf(u0, u0, dxc);
-                dxc = fmaf(u1, u1, dxc);
-                dxc = fmaf(u2, u2, dxc);
-                dxc = fmaf(u3, u3, dxc);
-            }
-            dxc = wave_sum(dxc);
-            float best = INFINITY;
-            best_l = 0x7fffffff;
-            while (todo) {                                      // four at a time, 16 lanes each
-                int from = -1;
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (todo) {
-                        if (g == u) from = __builtin_ctzll(todo);
-                        todo &= todo - 1;
-                    }
-                const int l = from < 0 ? -1 : l_at(from);
-                const int64_t srow = __shfl(my_nbr, from < 0 ? 0 : from, WAVE);
-                const float csl = __shfl(cs, from < 0 ? 0 : from, WAVE);
-                float dxs = 0.f;
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-                    if (l >= 0 && c16 + 16 * hh < D4) {
-                        const float4 sv = *reinterpret_cast<const float4 *>(C + srow * D + 4 * (c16 + 16 * hh));
-                        const float4 xv = *reinterpret_cast<const float4 *>(xs + 4 * (c16 + 16 * hh));
-                        const float u0 = xv.x - sv.x, u1 = xv.y - sv.y, u2 = xv.z - sv.z, u3 = xv.w - sv.w;
-                        dxs = fmaf(u0, u0, dxs);
-                        dxs = fmaf(u1, u1, dxs);
-                        dxs = fmaf(u2, u2, dxs);
-                        dxs = fmaf(u3, u3, dxs);
-                    }
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1) dxs += __shfl_xor(dxs, o, WAVE);
-                if (l >= 0 && c16 == 0) {
-                    const float sc = fmaf(a, dxs, fmaf(1.f - a, dxc, -a * (1.f - a) * csl));
-                    if (sc < best || (sc == best && l < best_l)) { best = sc; best_l = l; }
-                }
-            }
-            wave_argmin(best, best_l);
-            if (best_l == 0x7fffffff) best_l = 0;               // (no score is a number)
-        }
-        if (lane == j) {
-            out_sub[i_of] = best_l;
+        if (todo & (todo - 1)) {                               // more than one: the fp32 scores decide, below
+            if (todo >> lane & 1u) pairs[n_pairs + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u))] = (uint16_t)(j << 6 | my_l);
+            n_pairs += __popcll(todo);
+            if (lane == j) best_of = ~0ull;
+        } else if (lane == j) {
             l_of = best_l;
         }
     }
+    // The fp32 scores of what is left, whatever point it belongs to: 16 lanes a neighbour, eight of them on their way at a time
+    if (n_pairs) {                                              // (uniform)
+        if (lane < SUB_RUN) best[lane] = best_of;
+        wave_sync();
+        const int D4 = D >> 2, g = lane >> 4, c16 = lane & 15;
+        for (int p0 = 0; p0 < n_pairs; p0 += 8) {
+            int who[2];
+            float4 sv[2][2], cv[2][2], xv[2][2];
+            float csl[2], aj[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int p = p0 + 4 * u + g;
+                who[u] = pairs[p < n_pairs ? p : p0];
+                const int j = who[u] >> 6, l = who[u] & 63;
+                const int64_t r = __shfl(r_of, j, WAVE), i = (int64_t)((uint64_t)(uint32_t)__shfl((int)(i_of >> 32), j, WAVE) << 32 | (uint32_t)__shfl((int)i_of, j, WAVE));
+                const int64_t sr = nbr[r * L + l];
+                csl[u] = cs_dist2[r * L + l];
+                aj[u] = alpha[r];
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    const int c4 = 4 * (c16 + 16 * hh < D4 ? c16 + 16 * hh : 0);
+                    xv[u][hh] = *reinterpret_cast<const float4 *>(X + i * D + c4);
+                    cv[u][hh] = *reinterpret_cast<const float4 *>(C + r * D + c4);
+                    sv[u][hh] = *reinterpret_cast<const float4 *>(C + sr * D + c4);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // encode_kernel's sums: a lane of four components each against the region's centroid, in pairs of lanes 16 apart first; against the
+                // neighbour a lane goes on with the components 64 behind
+                float dxc = 0.f, dxs = 0.f;
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    const float4 x = xv[u][hh], c = cv[u][hh], s = sv[u][hh];
+                    const bool live = c16 + 16 * hh < D4;
+                    const float c0 = x.x - c.x, c1 = x.y - c.y, c2 = x.z - c.z, c3 = x.w - c.w;
+                    const float part_c = fmaf(c3, c3, fmaf(c2, c2, fmaf(c1, c1, c0 * c0)));
+                    dxc += live ? part_c : 0.f;
+                    const float s0 = x.x - s.x, s1 = x.y - s.y, s2 = x.z - s.z, s3 = x.w - s.w;
+                    const float next = fmaf(s3, s3, fmaf(s2, s2, fmaf(s1, s1, fmaf(s0, s0, dxs))));
+                    dxs = live ? next : dxs;
+                }
+                dxc = sum_of_16(dxc);
+                dxs = sum_of_16(dxs);
+                const float sc = fmaf(aj[u], dxs, fmaf(1.f - aj[u], dxc, -aj[u] * (1.f - aj[u]) * csl[u])) + 0.f;   // (-0 is 0)
+                if (c16 == 0 && p0 + 4 * u + g < n_pairs && sc < INFINITY)
+                    atomicMin(&best[who[u] >> 6], (unsigned long long)float_key(sc) << 32 | (uint32_t)(who[u] & 63));
+            }
+        }
+        wave_sync();
+        if (lane < SUB_RUN && best_of == ~0ull) l_of = best[lane] == ~0ull ? 0 : (int32_t)(uint32_t)best[lane];   // (no score is a number: 0)
+    }
+    if (lane < cnt) out_sub[i_of] = l_of;
     // displacements: independent of each other, so that several points' rows are on their way together
 #pragma unroll 4
     for (int j = 0; j < cnt; ++j) {

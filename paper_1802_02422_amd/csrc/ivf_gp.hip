@@ -1738,20 +1738,31 @@ extern "C" int ivf_coarse_topk(const float *centroids, int64_t K, int D, const f
 
 namespace {
 
-// The centroid table as fp16 rows, their lengths and the word with its largest magnitude (rows NULL: not packed).
+// The centroid table as 8-bit rows (rows NULL: not packed).
 struct SubregionTable {
-    const _Float16 *rows = nullptr;
-    const float2 *len = nullptr;
-    const uint32_t *cmax = nullptr;
+    const uint8_t *rows = nullptr, *tails = nullptr;
 };
+
+template <int DP>
+int pack_subregion_table(const ivf_index_desc *t, uint8_t *mem, SubregionTable &table, hipStream_t st)
+{
+    typedef ByteRow<DP> R;
+    constexpr int per = 256 / (R::BYTES / 16);               // rows of a workgroup
+    uint8_t *tails = R::INSIDE ? mem + DP : mem + (size_t)t->K * R::BYTES;
+    pack_byte_rows_kernel<DP><<<dim3((unsigned)((t->K + per - 1) / per)), dim3(256), 0, st>>>(t->centroids, t->K, t->D, mem, tails);
+    LAUNCHCHK("pack_byte_rows_kernel");
+    table.rows = mem;
+    table.tails = tails;
+    return IVF_OK;
+}
 
 int launch_subregions(const ivf_index_desc *t, const float *x, int64_t n, const int32_t *region, const int32_t *perm,
                       const SubregionTable &table, int32_t *out_sub, float *out_res, float *out_mu, hipStream_t st)
 {
-    const int nch = packed_dim(t->D) / 8;
-    auto kernel = nch == 4 ? &subregion_kernel<4> : nch == 8 ? &subregion_kernel<8> : nch == 12 ? &subregion_kernel<12> : &subregion_kernel<16>;
+    const int dp = packed_dim(t->D);
+    auto kernel = dp == 32 ? &subregion_kernel<32> : dp == 64 ? &subregion_kernel<64> : dp == 96 ? &subregion_kernel<96> : &subregion_kernel<128>;
     kernel<<<dim3((unsigned)((n + 4 * SUB_RUN - 1) / (4 * SUB_RUN))), dim3(256), 0, st>>>(
-        x, n, t->D, t->L, region, perm, t->centroids, table.rows, table.len, table.cmax, t->nbr, t->alpha, t->cs_dist2, out_sub, out_res, out_mu);
+        x, n, t->D, t->L, region, perm, t->centroids, table.rows, table.tails, t->nbr, t->alpha, t->cs_dist2, out_sub, out_res, out_mu);
     LAUNCHCHK("subregion_kernel");
     return IVF_OK;
 }
@@ -1774,7 +1785,7 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     if (n == 0) return IVF_OK;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     ArgminCtx ctx;                               // the assignment's, with the packed centroid table
-    DevTmp hi_mem;
+    DevTmp byte_mem;
     StreamWait before_they_go(st);               // (every return below: the pool takes their blocks back when nothing uses them)
     SubregionTable table;
     if (region_in) {
@@ -1798,23 +1809,15 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     const bool fast = t->pq_codebook && cb_bytes <= 140 * 1024 && pq_width(ds);
     if (t->rotation && t->pq_codebook && !fast)
         return fail(IVF_EINVAL, "a rotation in front of the PQ needs D/M in {4, 6, 8, 12, 16} and a codebook that fits LDS");
-    // Subregions by fp16 rows with a bound where the rows fit registers; reading the table to pack it costs as much as
-    // the fp32 rows of K / 6 points with 64 neighbours do more than the fp16 ones.
+    // Subregions by 8-bit rows with a bound where the rows fit registers; reading the table to pack it costs as much as
+    // the fp32 rows of K / 6 points with 64 neighbours do more than the 8-bit ones.
     const bool packed_rows_fit = packed_dim(t->D) <= 128 && t->L <= 64;
     auto prepare_table = [&]() -> int {
-        if (!packed_rows_fit) return IVF_OK;
-        if (!region_in && ctx.shortlist) {
-            table = SubregionTable{ctx.chk, ctx.clen, ctx.words};
-        } else if (n * t->L >= 10 * t->K) {
-            const size_t rows = (size_t)packed_rows(t->K), row_bytes = (size_t)packed_dim(t->D) * sizeof(_Float16);
-            HIPCHK(hi_mem.alloc(rows * (row_bytes + sizeof(float2)) + sizeof(uint32_t)));
-            _Float16 *h = static_cast<_Float16 *>(hi_mem.p);
-            float2 *len = reinterpret_cast<float2 *>(reinterpret_cast<char *>(h) + rows * row_bytes);
-            uint32_t *word = reinterpret_cast<uint32_t *>(len + rows);
-            table = SubregionTable{h, len, word};
-            return launch_pack_hi(t->centroids, t->K, t->D, word, h, len, st);
-        }
-        return IVF_OK;
+        if (!packed_rows_fit || n * t->L < 10 * t->K) return IVF_OK;
+        const int dp = packed_dim(t->D);
+        HIPCHK(byte_mem.alloc((size_t)t->K * byte_row_bytes(dp)));
+        auto pack = dp == 32 ? &pack_subregion_table<32> : dp == 64 ? &pack_subregion_table<64> : dp == 96 ? &pack_subregion_table<96> : &pack_subregion_table<128>;
+        return pack(t, static_cast<uint8_t *>(byte_mem.p), table, st);
     };
     if (!fast && !t->pq_codebook) {
         rc = prepare_table();

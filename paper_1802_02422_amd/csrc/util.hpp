@@ -118,6 +118,17 @@ __device__ __forceinline__ uint32_t wave_extreme(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
 }
 
+// Sum over the 16 lanes of a row, with the additions and the order of wave_sum's last four steps (lane ^ 8, ^ 4, ^ 2, ^ 1) but without LDS: after
+// the first the values repeat every 8 lanes, so that a rotation by 4 brings lane ^ 4's.
+__device__ __forceinline__ float sum_of_16(float v)
+{
+    v += dpp_or_self<0x128, 0xf>(v);                       // row_ror:8
+    v += dpp_or_self<0x124, 0xf>(v);                       // row_ror:4
+    v += dpp_or_self<0x4E, 0xf>(v);                        // quad_perm: lane ^ 2
+    v += dpp_or_self<0xB1, 0xf>(v);                        // quad_perm: lane ^ 1
+    return v;
+}
+
 // argmin over the wave of (value, index) pairs, lowest index on equal values;
 // every lane receives the winner.
 __device__ __forceinline__ void wave_argmin(float &v, int &idx)
