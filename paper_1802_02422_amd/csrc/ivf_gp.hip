@@ -891,13 +891,13 @@ int launch_flags(const ivf_index *ix, const float *Q, int64_t n, int P, const Se
     while (per_wg > 4 && group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg) < 1536) per_wg /= 2;
     const int64_t grid = group_grid(tiles_q, (tiles_c + per_wg - 1) / per_wg);
     if (grid >= (1ll << 24)) return fail(IVF_EINVAL, "coarse tile grid too large (more than 2^32 threads)");
-    auto sweep = [&](auto narrow_kernel, auto wide_kernel) {
-        (wide ? wide_kernel : narrow_kernel)<<<dim3((unsigned)grid), dim3(256), 0, st>>>(qh, ix->chi, ix->mstart, a.best, a.half_ld, tiles_q, tiles_c, per_wg);
+    auto sweep = [&](auto few_kernel, auto wide_kernel) {
+        (wide ? wide_kernel : few_kernel)<<<dim3((unsigned)grid), dim3(256), 0, st>>>(qh, ix->chi, ix->mstart, a.best, a.half_ld, tiles_q, tiles_c, per_wg);
     };
-    if (Dp == 32) sweep(&coarse_minima_kernel<1, 2>, &coarse_minima_kernel<1, 4>);
-    else if (Dp == 64) sweep(&coarse_minima_kernel<2, 2>, &coarse_minima_kernel<2, 4>);
-    else if (Dp == 96) sweep(&coarse_minima_kernel<3, 2>, &coarse_minima_kernel<3, 4>);
-    else sweep(&coarse_minima_kernel<4, 2>, &coarse_minima_kernel<4, 4>);
+    if (Dp == 32) sweep(&coarse_minima_few_kernel<1>, &coarse_minima_kernel<1>);
+    else if (Dp == 64) sweep(&coarse_minima_few_kernel<2>, &coarse_minima_kernel<2>);
+    else if (Dp == 96) sweep(&coarse_minima_few_kernel<3>, &coarse_minima_kernel<3>);
+    else sweep(&coarse_minima_few_kernel<4>, &coarse_minima_kernel<4>);
     LAUNCHCHK("coarse_minima_kernel");
     // pieces: at least 8 P of them (sparse_pays: the table has at least 8 P tiles), or 2048
     const dim3 gq((unsigned)n);

@@ -111,11 +111,10 @@ __global__ __launch_bounds__(256) void sparse_queries_kernel(const float *__rest
 __host__ __device__ inline int64_t minima_half(int64_t K) { return ((K + GT - 1) / GT + 3) / 4 * 4; }
 
 // best[q][half][t] = the largest of <q, c> - (1/2 - k) |c|^2 over the 64 centroids of the half of tile t, for a sweep of
-// `tiles_per_wg` (a multiple of four) centroid tiles by a workgroup (sweep_tile).  A lane ends up with the maxima of one query, four tiles
-// in a row, and stores them as 16 bytes.  JN = 4: a wavefront has 64 queries of its own and takes all of a tile with them, JN = 2: two
-// wavefronts share 64 queries and take half a tile each.  10 000 x 2^20, 96 dimensions: 1.62 ms (1.24 PFLOP/s), 2.03 with JN = 2
-// and the fragments waited for where they are read; 10 000 x 65 536 0.115 and 0.131, 128 dimensions 0.156 and 0.191.
-template <int SH, int JN>
+// `tiles_per_wg` (a multiple of four) centroid tiles by a workgroup, 64 queries a wavefront (sweep_tile).  A lane ends up with the maxima of
+// one query, four tiles in a row, and stores them as 16 bytes.  10 000 x 2^20, 96 dimensions: 1.62 ms (1.24 PFLOP/s), 2.03 with two
+// wavefronts to 64 queries and the fragments waited for where they are read; 10 000 x 65 536 0.115 and 0.131, 128 dimensions 0.156 and 0.191.
+template <int SH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void coarse_minima_kernel(
     const _Float16 *__restrict__ Qh, const _Float16 *__restrict__ Ch, const float *__restrict__ start, float *__restrict__ best, int64_t half_ld,
     int tiles_q, int tiles_c, int tiles_per_wg)
@@ -125,27 +124,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    constexpr int HALVES = JN / 2;                         // of a tile, to this wavefront
-    const int wq = (JN == 4 ? wave : wave >> 1) * 64, wc = JN == 4 ? 0 : (wave & 1) * 64;
     int64_t tq, group;
     if (!group_of_block(blockIdx.x, tiles_q, (tiles_c + tiles_per_wg - 1) / tiles_per_wg, tq, group)) return;
     const int tb = (int)(group * tiles_per_wg);
     int t_end = tb < tiles_c ? tiles_c - tb : 0;
     if (t_end > tiles_per_wg) t_end = tiles_per_wg;
     if (t_end <= 0) return;
-    const int64_t q0 = tq * (GT / 2 * JN) + wq;
+    const int64_t q0 = tq * (2 * GT) + wave * 64;
     const TileTwists<SH> twists(wave, lane);
-    auto issue = [&](int t, SweepTile<SH> &buf) { sweep_copy(Ch, start, tb + (t < t_end ? t : t_end - 1), buf, twists, wave, lane); };   // (past the range: never read)
+    auto issue = [&](int t, SweepTile<SH> &buf) { sweep_copy(Ch, start, tb + t, buf, twists, wave, lane); };
     issue(0, buf0);
     gu32x4 afr[SH][2][2];
     sweep_rows(afr, Qh, q0, l32, h);
-    float *out = best + (q0 + lane) * (2 * half_ld) + (wc ? half_ld : 0) + tb;
-    floatx4 four[HALVES];
+    float *out = best + (q0 + lane) * (2 * half_ld) + tb;
+    floatx4 four[2];                                       // of the halves of the tiles
 #pragma unroll
-    for (int o = 0; o < HALVES; ++o) four[o] = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int o = 0; o < 2; ++o) four[o] = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     auto step = [&](int t, const SweepTile<SH> &buf) {
         float top[2];
-        sweep_tile<SH, JN>(buf, afr, wc, l32, h, [&](int j, const floatx16 (&acc)[2]) {
+        sweep_tile<SH, 4>(buf, afr, 0, l32, h, [&](int j, const floatx16 (&acc)[2]) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 float m = j & 1 ? top[i] : acc[i][15];
@@ -164,21 +161,123 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     };
     for (int t = 0; t < t_end;) {
         sweep_barrier();
-        issue(t + 1, buf1);
+        if (t + 1 < t_end) issue(t + 1, buf1);
         step(t, buf0);
         if (++t == t_end) break;
         sweep_barrier();
-        issue(t + 1, buf0);
+        if (t + 1 < t_end) issue(t + 1, buf0);
         step(t, buf1);
         ++t;
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no copy into LDS may outlive the workgroup
     if (t_end & 3) {
 #pragma unroll
-        for (int o = 0; o < HALVES; ++o) {
+        for (int o = 0; o < 2; ++o) {
             for (int t = t_end; t & 3; ++t) four[o] = floatx4{four[o][1], four[o][2], four[o][3], -INFINITY};
             *reinterpret_cast<floatx4 *>(out + o * half_ld + (t_end & ~3)) = four[o];
         }
+    }
+}
+
+// The same for few queries (sweep_wide), where the table's bytes are what it takes: 128 queries a workgroup, a wavefront with 64 of them and half a
+// tile, every fragment waited for where it is read.  One query on 2^20, 96 dimensions: 36 us (5.6 TB/s), 64 queries 46; with sweep_tile 38 and
+// 48.5, whichever number of tiles a workgroup takes.
+template <int SH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void coarse_minima_few_kernel(
+    const _Float16 *__restrict__ Qh, const _Float16 *__restrict__ Ch, const float *__restrict__ start, float *__restrict__ best, int64_t half_ld,
+    int tiles_q, int tiles_c, int tiles_per_wg)
+{
+    typedef const __attribute__((address_space(1))) void *gptr_t;
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    constexpr int Dpf = SH * DK;                           // floats per row of the hi-only tables
+    constexpr int SLOT = GT * ROWF;
+    __shared__ __attribute__((aligned(16))) float ring[2][SH * SLOT];
+    __shared__ __attribute__((aligned(16))) float cns[2][GT];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    const int wq = (wave >> 1) * 64, wc = (wave & 1) * 64;
+    int64_t tq, group;
+    if (!group_of_block(blockIdx.x, tiles_q, (tiles_c + tiles_per_wg - 1) / tiles_per_wg, tq, group)) return;
+    const int tb = (int)(group * tiles_per_wg);
+    int t_end = tb < tiles_c ? tiles_c - tb : 0;
+    if (t_end > tiles_per_wg) t_end = tiles_per_wg;
+    if (t_end <= 0) return;
+    const int64_t q0 = tq * GT;
+
+    const TileTwists<SH> twists(wave, lane);
+    const float *cbase = reinterpret_cast<const float *>(Ch);
+    auto issue_tile = [&](int t) {
+        if (wave < 2)
+            __builtin_amdgcn_global_load_lds((gptr_t)(start + (int64_t)(tb + t) * GT + wave * 64 + lane), (lptr_t)(&cns[t & 1][wave * 64]), 4, 0, 0);
+        const float *src = cbase + (int64_t)(tb + t) * GT * Dpf;
+        float *dst = &ring[t & 1][0];
+#pragma nounroll
+        for (int n = wave; n < 8 * SH; n += 4)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src + n * 256 + 4 * (lane ^ (int)twists.of(n))), (lptr_t)(dst + n * 256), 16, 0, 0);
+    };
+    issue_tile(0);
+    gu32x4 afr[SH][2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const gu32x4 *row = reinterpret_cast<const gu32x4 *>(reinterpret_cast<const float *>(Qh) + (q0 + wq + i * 32 + l32) * Dpf) + 2 * h;
+#pragma unroll
+        for (int s = 0; s < SH; ++s) {
+            afr[s][i][0] = row[s * 4 + 0];
+            afr[s][i][1] = row[s * 4 + 1];
+        }
+    }
+    float *out = best + (q0 + wq + lane) * (2 * half_ld) + (wave & 1) * half_ld + tb;
+    floatx4 four = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int t = 0; t < t_end; ++t) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wavefront's copies of tile t (issued a tile ago) are in
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // ... and everyone's; tile t - 1's buffer is free
+        if (t + 1 < t_end) issue_tile(t + 1);
+        float top[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            floatx16 acc[2];
+            union { floatx16 all; floatx4 part[4]; } init;
+            const int rb = wc + j * 32 + l32;
+            const uint32_t cb = (uint32_t)reinterpret_cast<uintptr_t>(&cns[t & 1][wc + j * 32 + 4 * h]);
+            const uint32_t rsw = 4u * (uint32_t)(rb * Dpf), k0 = 16u * ((uint32_t)(2 * h) ^ tile_twist<SH>(rb)), k1 = 16u * ((uint32_t)(2 * h + 1) ^ tile_twist<SH>(rb));
+#pragma unroll
+            for (int s = 0; s < SH; ++s) {
+                const uint32_t bs = (uint32_t)reinterpret_cast<uintptr_t>(&ring[t & 1][0]) + rsw;
+                const uint32_t b0 = bs + (SH & 1 ? k0 + 64u * s : k0 ^ 64u * s), b1 = bs + (SH & 1 ? k1 + 64u * s : k1 ^ 64u * s);
+                gu32x4 b[2];
+                if (s == 0)
+                    asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:32\n\tds_read_b128 %2, %6 offset:64\n\tds_read_b128 %3, %6 offset:96\n\t"
+                                 "ds_read_b128 %4, %7\n\tds_read_b128 %5, %8\n\ts_waitcnt lgkmcnt(0)"
+                                 : "=&v"(init.part[0]), "=&v"(init.part[1]), "=&v"(init.part[2]), "=&v"(init.part[3]), "=&v"(b[0]), "=&v"(b[1])
+                                 : "v"(cb), "v"(b0), "v"(b1));
+                else
+                    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(b[0]), "=&v"(b[1]) : "v"(b0), "v"(b1));
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, b[p]), __builtin_bit_cast(halfx8, afr[s][i][p]),
+                                                                        s == 0 && p == 0 ? init.all : acc[i], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                float m = acc[i][0];
+#pragma unroll
+                for (int v = 1; v < 16; ++v) m = __builtin_elementwise_maximum(m, acc[i][v]);
+                top[i] = j == 0 ? m : __builtin_elementwise_maximum(top[i], m);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the next half's products start with this half's registers free
+        }
+        // lane half 0 gets query block 0's maximum over both halves' centroids, lane half 1 block 1's
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(top[0]), __float_as_uint(top[1]), false, false);
+        four = floatx4{four[1], four[2], four[3], __builtin_elementwise_maximum(__uint_as_float(s[0]), __uint_as_float(s[1]))};
+        if ((t & 3) == 3) *reinterpret_cast<floatx4 *>(out + t - 3) = four;
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no copy into LDS may outlive the workgroup
+    if (t_end & 3) {
+        for (int t = t_end; t & 3; ++t) four = floatx4{four[1], four[2], four[3], -INFINITY};
+        *reinterpret_cast<floatx4 *>(out + (t_end & ~3)) = four;
     }
 }
 
