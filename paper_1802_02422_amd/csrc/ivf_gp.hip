@@ -1694,9 +1694,9 @@ int launch_pq_means_ds(const float *E, int64_t n, int M, const uint8_t *codes, u
     const int64_t G = pq_sum_slices(n), per = (n + G - 1) / G;
     const int groups = (M + PqSums<DS>::MG - 1) / PqSums<DS>::MG;
     HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&pq_sums_kernel<DS>), hipFuncAttributeMaxDynamicSharedMemorySize, PqSums<DS>::lds));
-    pq_sums_kernel<DS><<<dim3((unsigned)G, (unsigned)groups), dim3(512), PqSums<DS>::lds, st>>>(E, n, M, codes, state, per, psum, pcnt, rest, small);
+    pq_sums_kernel<DS><<<dim3(pq_sums_grid(G, groups)), dim3(PQ_SUM_BLOCK), PqSums<DS>::lds, st>>>(E, n, M, codes, state, (int)G, per, psum, pcnt, rest, small);
     LAUNCHCHK("pq_sums_kernel");
-    pq_means_kernel<DS><<<dim3((unsigned)(M * 256 * DS / 64)), dim3(256), 0, st>>>(psum, pcnt, M, (int)G, state, rest, small, state + 1, codebook);
+    pq_means_kernel<DS><<<dim3((unsigned)(M * 256 * DS / 64)), dim3(64 * PQ_MEAN_PARTS), 0, st>>>(psum, pcnt, M, (int)G, state, rest, small, state + 1, codebook);
     LAUNCHCHK("pq_means_kernel");
     return IVF_OK;
 }

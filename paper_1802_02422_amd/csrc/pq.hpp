@@ -455,22 +455,25 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
 // fp64 sum, a flag is raised and the training is done again with fp64 segment sums (data whose rows lie many
 // powers of two apart).
 // This takes the place of a sort by code, a segment sum with one workgroup a codeword and five more launches per
-// quantiser: 10^6 x 96, 16 quantisers, one round: 1.55 -> 0.17 ms.  Bound by the LDS additions and by reading E.
+// quantiser: 10^6 x 96, 16 quantisers, one round: 1.55 -> 0.12 ms.  Bound by the LDS additions and by reading E.
 template <int DS>
 struct PqSums {
     static constexpr int MG = DS <= 8 ? 4 : 2;              // quantisers of a workgroup
     static constexpr int lds = MG * 256 * (DS * 8 + 8);
 };
+inline unsigned pq_sums_grid(int64_t G, int groups) { return (unsigned)((G + N_XCD - 1) / N_XCD * N_XCD * groups); }
 constexpr int PQ_SUM_PART = 8192;                           // points between two write-outs: 2^13 * 2^49 stays below 2^63
 constexpr int PQ_SUM_MAX_G = 256;
+constexpr int PQ_SUM_BLOCK = 1024;                           // two workgroups a compute unit: all the wavefronts it holds (half of them: 152 us, 108 so)
 
-// Workgroup (g, group of quantisers): points [g * per, (g + 1) * per).  psum [G][M][256][DS] fp64 and pcnt [G][M][256]
+// Slice g's points [g * per, (g + 1) * per) and a group of quantisers a workgroup; the groups of a slice side by side on one XCD, whose L2 then has
+// the lines that their parts of a row share.  Grid: pq_sums_grid.  psum [G][M][256][DS] fp64 and pcnt [G][M][256]
 // receive its sums and counts (each slice is written by one workgroup, part by part in order); rest [M][256][DS] receives
 // the multiples of 2^-31 q, small [M][256] counts the values below their exact range.
 template <int DS>
-__global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ E, int64_t n, int M,
+__global__ __launch_bounds__(PQ_SUM_BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void pq_sums_kernel(const float *__restrict__ E, int64_t n, int M,
                                                       const uint8_t *__restrict__ codes, const uint32_t *__restrict__ gmax,
-                                                      int64_t per, double *__restrict__ psum, uint32_t *__restrict__ pcnt,
+                                                      int G, int64_t per, double *__restrict__ psum, uint32_t *__restrict__ pcnt,
                                                       unsigned long long *__restrict__ rest, unsigned long long *__restrict__ small)
 {
     constexpr int MG = PqSums<DS>::MG, W = MG * DS / 2;      // pairs of components a point has in this group
@@ -479,8 +482,10 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
     uint32_t *cnt = reinterpret_cast<uint32_t *>(acc + MG * 256 * DS);           // [MG][256]
     uint32_t *cut = cnt + MG * 256;                                              // [MG][256]
     const int tid = threadIdx.x;
-    const int m0 = blockIdx.y * MG, mn = M - m0 < MG ? M - m0 : MG;
-    const int64_t D = (int64_t)M * DS, g = blockIdx.x;
+    const int groups = (M + MG - 1) / MG, local = blockIdx.x / N_XCD;
+    const int m0 = local % groups * MG, mn = M - m0 < MG ? M - m0 : MG;
+    const int64_t D = (int64_t)M * DS, g = (int64_t)(local / groups) * N_XCD + blockIdx.x % N_XCD;
+    if (g >= G) return;
     // v + 1.5 * 2^(52 - k) holds round(v * 2^k) in the low bits of its mantissa (|v| 2^k < 2^49): the bit patterns are
     // added, and the pattern of the constant comes off again count times at the end
     const int ex = __builtin_amdgcn_frexp_expf(__uint_as_float(*gmax));
@@ -493,12 +498,12 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
     const int64_t lo = g * per, hi = lo + per < n ? lo + per : n;
     for (int64_t p0 = lo; p0 < hi || p0 == lo; p0 += PQ_SUM_PART) {
         const int64_t pn = hi - p0 < PQ_SUM_PART ? hi - p0 : PQ_SUM_PART;
-        for (int i = tid; i < MG * 256 * DS; i += 512) acc[i] = 0;
-        for (int i = tid; i < 2 * MG * 256; i += 512) cnt[i] = 0;
+        for (int i = tid; i < MG * 256 * DS; i += PQ_SUM_BLOCK) acc[i] = 0;
+        for (int i = tid; i < 2 * MG * 256; i += PQ_SUM_BLOCK) cnt[i] = 0;
         __syncthreads();
         const int work = (int)pn * W;
 #pragma unroll 4
-        for (int i = tid; i < work; i += 512) {
+        for (int i = tid; i < work; i += PQ_SUM_BLOCK) {
             const int p = i / W, c = (i - p * W) * 2;        // point of the part, component of the group
             const int m = c / DS, t = c - m * DS;
             if (m < mn) {
@@ -525,13 +530,13 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
         }
         __syncthreads();
         double *ps = psum + (g * M + m0) * 256 * DS;
-        for (int i = tid; i < mn * 256 * DS; i += 512) {
+        for (int i = tid; i < mn * 256 * DS; i += PQ_SUM_BLOCK) {
             const unsigned long long whole = acc[i] - mbits * (unsigned long long)cnt[i / DS];
             const double v = (double)(long long)whole * back;
             ps[i] = p0 == lo ? v : ps[i] + v;
         }
         uint32_t *pc = pcnt + (g * M + m0) * 256;
-        for (int i = tid; i < mn * 256; i += 512) {
+        for (int i = tid; i < mn * 256; i += PQ_SUM_BLOCK) {
             pc[i] = p0 == lo ? cnt[i] : pc[i] + cnt[i];
             if (cut[i]) atomicAdd(&small[m0 * 256 + i], (unsigned long long)cut[i]);
         }
@@ -540,19 +545,22 @@ __global__ __launch_bounds__(512) void pq_sums_kernel(const float *__restrict__ 
 }
 
 // codebook[m][j][t] = sum over the G slices and rest / count, rounded to fp32; a codeword without points keeps its value.
-// A workgroup takes 64 components; four threads a component add a quarter of the slices each, in order.  rest is left at
+// A workgroup takes 64 components; PARTS threads a component add a part of the slices each, in order (10^6 x 96, 256 slices: four parts 31 us,
+// 13 with 16).  rest is left at
 // 0 for the next round.  *inexact is set where values that were not added exactly (counted over all rounds) could show.
+constexpr int PQ_MEAN_PARTS = 16;
+
 template <int DS>
-__global__ __launch_bounds__(256) void pq_means_kernel(const double *__restrict__ psum, const uint32_t *__restrict__ pcnt,
+__global__ __launch_bounds__(64 * PQ_MEAN_PARTS) void pq_means_kernel(const double *__restrict__ psum, const uint32_t *__restrict__ pcnt,
                                                        int M, int G, const uint32_t *__restrict__ gmax,
                                                        unsigned long long *__restrict__ rest, const unsigned long long *__restrict__ small,
                                                        uint32_t *__restrict__ inexact, float *__restrict__ codebook)
 {
-    __shared__ double part[4][64];
-    __shared__ uint32_t part_n[4][64];
+    __shared__ double part[PQ_MEAN_PARTS][64];
+    __shared__ uint32_t part_n[PQ_MEAN_PARTS][64];
     const int c = threadIdx.x & 63, u = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + c, words = (int64_t)M * 256;   // (M * 256 * DS is a multiple of 64)
-    const int g0 = (int)((int64_t)G * u / 4), g1 = (int)((int64_t)G * (u + 1) / 4);
+    const int g0 = (int)((int64_t)G * u / PQ_MEAN_PARTS), g1 = (int)((int64_t)G * (u + 1) / PQ_MEAN_PARTS);
     double s = 0.0;
     uint32_t k = 0;
 #pragma unroll 8
@@ -564,8 +572,10 @@ __global__ __launch_bounds__(256) void pq_means_kernel(const double *__restrict_
     part_n[u][c] = k;
     __syncthreads();
     if (u) return;
-    s = ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
-    k = part_n[0][c] + part_n[1][c] + part_n[2][c] + part_n[3][c];
+    for (int v = 1; v < PQ_MEAN_PARTS; ++v) {
+        s += part[v][c];
+        k += part_n[v][c];
+    }
     if (!k) return;
     const int ex = __builtin_amdgcn_frexp_expf(__uint_as_float(*gmax));
     s += (double)(long long)rest[i] * __builtin_amdgcn_ldexp(1.0, ex - 80);
