@@ -1615,14 +1615,8 @@ __device__ __forceinline__ void wave_select(const uint32_t (&k)[R], uint32_t nse
         lo = k[r] < lo ? k[r] : lo;
         hi = k[r] != 0xFFFFFFFFu && k[r] > hi ? k[r] : hi;
     }
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
-        const uint32_t a = __shfl_xor(lo, o, WAVE), b = __shfl_xor(hi, o, WAVE);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
-    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
-    hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+    lo = wave_extreme<false>(lo);
+    hi = wave_extreme<true>(hi);
     const int top = lo < hi ? 31 - __builtin_clz(lo ^ hi) : -1;   // highest bit in which keys differ
     uint32_t t = top >= 0 ? hi & ~((2u << top) - 1u) : lo;
     uint32_t below = 0;                                        // keys < t
@@ -1669,7 +1663,8 @@ constexpr int PW_CAP = 512;         // survivors held in LDS; where there are mo
 // Four queries a workgroup.  Same three steps and the same result as probe_select_kernel.  KMAX > 0: the whole row, of
 // at most KMAX distances, goes into registers (and LDS, from where a short loop writes the selected ones out).  A small
 // batch waits for one wavefront's chain of steps, which grows with the registers it holds: 100 queries x 1024 19 us with
-// KMAX = 2048, 13 with 1024 (9 with all loads ahead of their use).
+// KMAX = 2048, 13 with 1024 (9.1 with all loads ahead of their use, 8.4 with the words that are written out read four at a time; 333 x 2000
+// 15.2 and 13.9).
 template <int KMAX>
 __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__restrict__ Dt, int64_t ldt, const float *__restrict__ bm,
                                                                 int64_t K, int nb, int P, int64_t nq, int32_t *__restrict__ probe_id,
@@ -1703,20 +1698,29 @@ __global__ __launch_bounds__(256) void probe_select_wave_kernel(const float *__r
         wave_select<R>(k, (uint32_t)P, pivot, need);
         wave_sync();
         uint32_t out = 0, eq_seen = 0;
+        // (four words on their way at a time; behind the row, none)
+        static_assert(!DIRECT || KMAX % (4 * WAVE) == 0, "whole steps");
 #pragma nounroll
-        for (int c0 = 0; c0 < n; c0 += WAVE) {
-            const uint32_t key = held[DIRECT ? c0 + lane : 0];
-            const uint64_t eqm = __ballot(key == pivot && need > 0);
-            const uint32_t eq_rank = eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u));
-            const bool sel = key < pivot || (key == pivot && eq_rank < need);
-            const uint64_t m = __ballot(sel);
-            if (sel) {
-                const uint32_t o = out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                oid[o] = c0 + lane;
-                od[o] = key_float(key);
+        for (int c4 = 0; c4 < n; c4 += 4 * WAVE) {
+            uint32_t word[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) word[u] = held[DIRECT ? c4 + u * WAVE + lane : 0];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t key = word[u];
+                const int c = c4 + u * WAVE + lane;
+                const uint64_t eqm = __ballot(key == pivot && need > 0 && c < n);
+                const uint32_t eq_rank = eq_seen + __builtin_amdgcn_mbcnt_hi((uint32_t)(eqm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eqm, 0u));
+                const bool sel = key < pivot || (key == pivot && eq_rank < need && c < n);
+                const uint64_t m = __ballot(sel);
+                if (sel) {
+                    const uint32_t o = out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    oid[o] = c;
+                    od[o] = key_float(key);
+                }
+                out += (uint32_t)__popcll(m);
+                eq_seen += (uint32_t)__popcll(eqm);
             }
-            out += (uint32_t)__popcll(m);
-            eq_seen += (uint32_t)__popcll(eqm);
         }
         return;
     }
