@@ -204,6 +204,14 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
             }
         };
         static_assert(G * DS % 4 == 0, "whole loads");
+        // codeword and subcentroid of the quantiser before: the constant follows a quantiser behind, where there are registers for it, so that
+        // the loads' way is covered (10^6 points with constants, 6 components: 0.497 ms, 0.468 so)
+        constexpr bool LAG = DS <= 8;
+        float rv[DS], mv[DS];
+        auto add_constant = [&]() {
+#pragma unroll
+            for (int t = 0; t < DS; ++t) tval = fmaf(2.f * mv[t], rv[t], fmaf(rv[t], rv[t], tval));
+        };
         fetch(place(0));
         for (int mg = 0; mg < mn; mg += G) {
             const int ml = place(mg);
@@ -400,20 +408,20 @@ __global__ __launch_bounds__(1024) void pq_encode_kernel(
                 } else if (own < n) {
                     out_codes[own * M + m0 + m] = (uint8_t)code;
                 }
-                if (MU && own < n) {
-                    const float *cw = codebook + ((int64_t)(m0 + m) * 256 + code) * DS, *mu = MU + own * D + (m0 + m) * DS;
-                    float r2[DS], u2[DS];
+                if (MU) {                                     // (uniform)
+                    if (LAG && m > 0) add_constant();
+                    const float *cw = codebook + ((int64_t)(m0 + m) * 256 + code) * DS, *mu = MU + i0 * D + (m0 + m) * DS;
 #pragma unroll
                     for (int t = 0; t + 2 <= DS; t += 2) {
                         const float2u a = *reinterpret_cast<const float2u *>(cw + t), b = *reinterpret_cast<const float2u *>(mu + t);
-                        r2[t] = a.x; r2[t + 1] = a.y;
-                        u2[t] = b.x; u2[t + 1] = b.y;
+                        rv[t] = a.x; rv[t + 1] = a.y;
+                        mv[t] = b.x; mv[t + 1] = b.y;
                     }
-#pragma unroll
-                    for (int t = 0; t < DS; ++t) tval = fmaf(2.f * u2[t], r2[t], fmaf(r2[t], r2[t], tval));
+                    if (!LAG) add_constant();
                 }
             }
         }
+        if (LAG && MU) add_constant();
         if (own >= n) continue;
         if (out_t) out_t[own] = tval;
         if (const_table) {
