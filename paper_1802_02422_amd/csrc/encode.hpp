@@ -157,7 +157,7 @@ __global__ __launch_bounds__(64) void encode_kernel(
     }
 }
 
-// The centroid table in 8 bits for subregion_kernel: row c is s ~ step * q, q in -127 .. 127, step the 127th part of its largest
+// The centroid table in 8 bits for subregion_kernel: row c is s - centre ~ step * q, q in -127 .. 127, step the 127th part of its largest
 // component, with its step, |s|^2, |ds| and |s| (ds: what the rounding left out) behind the components where a row of 128 bytes has
 // room for them, so that one line holds it all, and in an array of their own where 128 components fill it.  A row that is not finite:
 // zeros with infinite lengths.
@@ -169,8 +169,37 @@ struct ByteRow {
 };
 inline size_t byte_row_bytes(int Dp) { return Dp == 32 ? 64 : Dp == 128 ? 144 : 128; }   // of a row and what belongs to it
 
+// A point near the middle of the table, to which points and rows are taken: distances between them are the same, and an offset that all
+// have in common does not cost the 8 bits anything.  The mean of up to 256 rows (any point is right).
+constexpr int CENTRE_ROWS = 256;
+
+__global__ __launch_bounds__(1024) void table_centre_kernel(const float *__restrict__ X, int64_t n, int D, float *__restrict__ centre)
+{
+    __shared__ float part[8][128];
+    const int c = threadIdx.x & 127, g = threadIdx.x >> 7, rows = n < CENTRE_ROWS ? (int)n : CENTRE_ROWS;
+    const int64_t stride = n / rows;
+    float v[CENTRE_ROWS / 8], s = 0.f;
+#pragma unroll
+    for (int u = 0; u < CENTRE_ROWS / 8; ++u) {               // (every thread loads: all are on their way together)
+        const int i = g + 8 * u < rows ? g + 8 * u : 0;
+        v[u] = X[(int64_t)i * stride * D + (c < D ? c : 0)];
+    }
+#pragma unroll
+    for (int u = 0; u < CENTRE_ROWS / 8; ++u) {
+        const float w = g + 8 * u < rows ? v[u] * (1.f / CENTRE_ROWS) : 0.f;
+        s += fabsf(w) < INFINITY ? w : 0.f;
+    }
+    part[g][c] = s;
+    __syncthreads();
+    if (g) return;
+    for (int u = 1; u < 8; ++u) s += part[u][c];
+    s *= (float)CENTRE_ROWS / (float)rows;
+    centre[c] = c < D && fabsf(s) < INFINITY ? s : 0.f;
+}
+
 template <int DP>
-__global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__restrict__ X, int64_t n, int D, uint8_t *__restrict__ rows, uint8_t *__restrict__ tails)
+__global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__restrict__ X, int64_t n, int D, const float *__restrict__ centre,
+                                                             uint8_t *__restrict__ rows, uint8_t *__restrict__ tails)
 {
     typedef ByteRow<DP> R;
     constexpr int PER = R::BYTES / 16, LIVE = DP / 16;        // 16 bytes a lane
@@ -181,7 +210,9 @@ __global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__rest
     for (int u = 0; u < 4; ++u) {
         float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
         if (row < n && lane < LIVE && 16 * lane + 4 * u < D) w = *reinterpret_cast<const float4 *>(X + row * D + 16 * lane + 4 * u);   // (D is a multiple of 4)
-        v[4 * u] = w.x; v[4 * u + 1] = w.y; v[4 * u + 2] = w.z; v[4 * u + 3] = w.w;
+        const float4 m = lane < LIVE ? *reinterpret_cast<const float4 *>(centre + 16 * lane + 4 * u) : make_float4(0.f, 0.f, 0.f, 0.f);   // (0 behind D)
+        v[4 * u] = w.x - m.x; v[4 * u + 1] = w.y - m.y; v[4 * u + 2] = w.z - m.z; v[4 * u + 3] = w.w - m.w;
+        if (row >= n) v[4 * u] = v[4 * u + 1] = v[4 * u + 2] = v[4 * u + 3] = 0.f;
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -224,6 +255,8 @@ __global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__rest
 // are put by and decided when the wavefront has been through its points, eight neighbours on their way at a time whatever point
 // they belong to (decided where they come up, with the loads and sums of one point behind those of another: 0.56 ms for
 // 500 000 points on 65 536 regions, 0.50 so, 0.445 with five wavefronts a SIMD).
+// With vectors that share an offset of 1 (10) in every component a call of 500 000 points on 65 536 regions takes 0.73 (0.72) ms, without the centre
+// 2.2 (2.2), where fp16 rows took 1.65 (3.0).
 // 2 * 10^6 points in region order (two a region), K = 2^20, L = 64, D = 96: 2.27 ms; with fp16 rows, two lines each, whose bound leaves
 // 1.1 of 64, 3.8; encode_kernel 7.3.
 // perm (may be NULL): the order in which the points are taken.
@@ -232,24 +265,25 @@ constexpr int SUB_RUN = 16;
 template <int DP>   // packed dimension
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) void subregion_kernel(
     const float *__restrict__ X, int64_t n, int D, int L, const int32_t *__restrict__ region, const int32_t *__restrict__ perm,
-    const float *__restrict__ C, const uint8_t *__restrict__ rows, const uint8_t *__restrict__ tails,
+    const float *__restrict__ C, const float *__restrict__ centre, const uint8_t *__restrict__ rows, const uint8_t *__restrict__ tails,
     const int32_t *__restrict__ nbr, const float *__restrict__ alpha, const float *__restrict__ cs_dist2,
     int32_t *__restrict__ out_sub, float *__restrict__ out_res, float *__restrict__ out_mu)
 {
     typedef ByteRow<DP> R;
     constexpr int CH = R::CHUNKS;
-    __shared__ __attribute__((aligned(16))) float xs_all[4][DP];
+    __shared__ float mid_all[4][(DP + WAVE - 1) / WAVE * WAVE];   // the centre, 0 behind D
     __shared__ __attribute__((aligned(16))) int8_t xh_all[4][2][R::BYTES];   // high and low halves; zeros behind the components
     __shared__ uint16_t pairs_all[4][SUB_RUN * WAVE];
     __shared__ unsigned long long best_all[4][SUB_RUN];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float *xs = xs_all[wave];
     int8_t *xh = xh_all[wave][0], *xl = xh_all[wave][1];
     uint16_t *pairs = pairs_all[wave];
     unsigned long long *best = best_all[wave];
     const int64_t first = ((int64_t)blockIdx.x * 4 + wave) * SUB_RUN;
     if (first >= n) return;
     for (int t = lane; t < 2 * R::BYTES / 4; t += WAVE) reinterpret_cast<uint32_t *>(xh)[t] = 0;
+    float *mid = mid_all[wave];
+    for (int t = lane; t < (DP + WAVE - 1) / WAVE * WAVE; t += WAVE) mid[t] = centre[t];
     const int cnt = n - first < SUB_RUN ? (int)(n - first) : SUB_RUN;
     // lane j: point and region of the run's j-th point, later its subregion.  The points, and the neighbour ids of the next
     // region, are requested a step ahead: what is left to wait for is the rows.
@@ -301,21 +335,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
             const uint64_t later = __ballot(lane > j && lane < cnt && r_of != (int32_t)r);
             if (later) fetch_nbr(__builtin_amdgcn_readlane(r_of, __builtin_ctzll(later)));
         }
-        // the point: fp32 and as two bytes
-        float x2 = 0.f, d2 = 0.f, big = 0.f;
+        // the point as two bytes a component.  (What the subtraction of the centre rounds, 2^-24 of the difference, is a part of the bound's last
+        // term: the products are exact.)
+        float x2 = 0.f, d2 = 0.f, big = 0.f, xc[XP];
+        wave_sync();
 #pragma unroll
-        for (int u = 0; u < XP; ++u) big = fmaxf(big, fabsf(xn[u]));
+        for (int u = 0; u < XP; ++u) {
+            xc[u] = xn[u] - mid[lane + u * WAVE];
+            big = fmaxf(big, fabsf(xc[u]));
+        }
         big = __uint_as_float(wave_extreme<true>(__float_as_uint(big)));   // (not negative: the bits order like it)
         const float step = big * (1.f / 16256.f), per = big > 0x1p-100f && big < INFINITY ? 16256.f / big : 0.f;
         wave_sync();
 #pragma unroll
         for (int u = 0; u < XP; ++u) {
             const int t = lane + u * WAVE;
-            const float v = xn[u], q = fminf(fmaxf(rintf(v * per), -16256.f), 16256.f), d = fmaf(-q, step, v);
+            const float v = xc[u], q = fminf(fmaxf(rintf(v * per), -16256.f), 16256.f), d = fmaf(-q, step, v);
             x2 = fmaf(v, v, x2);
             d2 = fmaf(d, d, d2);
             if (t < DP) {
-                xs[t] = v;
                 const int w = (int)q, hi = (w + 64) >> 7;
                 xh[t] = (int8_t)hi;
                 xl[t] = (int8_t)(w - 128 * hi);

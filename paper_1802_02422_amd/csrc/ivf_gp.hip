@@ -1741,6 +1741,7 @@ namespace {
 // The centroid table as 8-bit rows (rows NULL: not packed).
 struct SubregionTable {
     const uint8_t *rows = nullptr, *tails = nullptr;
+    const float *centre = nullptr;
 };
 
 template <int DP>
@@ -1748,11 +1749,16 @@ int pack_subregion_table(const ivf_index_desc *t, uint8_t *mem, SubregionTable &
 {
     typedef ByteRow<DP> R;
     constexpr int per = 256 / (R::BYTES / 16);               // rows of a workgroup
+    float *centre = reinterpret_cast<float *>(mem);
+    mem += 128 * sizeof(float);
     uint8_t *tails = R::INSIDE ? mem + DP : mem + (size_t)t->K * R::BYTES;
-    pack_byte_rows_kernel<DP><<<dim3((unsigned)((t->K + per - 1) / per)), dim3(256), 0, st>>>(t->centroids, t->K, t->D, mem, tails);
+    table_centre_kernel<<<dim3(1), dim3(1024), 0, st>>>(t->centroids, t->K, t->D, centre);
+    LAUNCHCHK("table_centre_kernel");
+    pack_byte_rows_kernel<DP><<<dim3((unsigned)((t->K + per - 1) / per)), dim3(256), 0, st>>>(t->centroids, t->K, t->D, centre, mem, tails);
     LAUNCHCHK("pack_byte_rows_kernel");
     table.rows = mem;
     table.tails = tails;
+    table.centre = centre;
     return IVF_OK;
 }
 
@@ -1762,7 +1768,7 @@ int launch_subregions(const ivf_index_desc *t, const float *x, int64_t n, const 
     const int dp = packed_dim(t->D);
     auto kernel = dp == 32 ? &subregion_kernel<32> : dp == 64 ? &subregion_kernel<64> : dp == 96 ? &subregion_kernel<96> : &subregion_kernel<128>;
     kernel<<<dim3((unsigned)((n + 4 * SUB_RUN - 1) / (4 * SUB_RUN))), dim3(256), 0, st>>>(
-        x, n, t->D, t->L, region, perm, t->centroids, table.rows, table.tails, t->nbr, t->alpha, t->cs_dist2, out_sub, out_res, out_mu);
+        x, n, t->D, t->L, region, perm, t->centroids, table.centre, table.rows, table.tails, t->nbr, t->alpha, t->cs_dist2, out_sub, out_res, out_mu);
     LAUNCHCHK("subregion_kernel");
     return IVF_OK;
 }
@@ -1815,7 +1821,7 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     auto prepare_table = [&]() -> int {
         if (!packed_rows_fit || n * t->L < 10 * t->K) return IVF_OK;
         const int dp = packed_dim(t->D);
-        HIPCHK(byte_mem.alloc((size_t)t->K * byte_row_bytes(dp)));
+        HIPCHK(byte_mem.alloc(128 * sizeof(float) + (size_t)t->K * byte_row_bytes(dp)));
         auto pack = dp == 32 ? &pack_subregion_table<32> : dp == 64 ? &pack_subregion_table<64> : dp == 96 ? &pack_subregion_table<96> : &pack_subregion_table<128>;
         return pack(t, static_cast<uint8_t *>(byte_mem.p), table, st);
     };

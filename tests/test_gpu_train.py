@@ -335,6 +335,38 @@ def test_subregions_and_displacements(D, L, n, order, kind):
     assert np.abs(res - (x64 - mu)).max() <= 8 * u * (np.abs(x64).max() + np.abs(c64).max())
 
 
+@pytest.mark.parametrize("D,L,K,n,offset", [(96, 64, 700, 3000, 0.0), (96, 64, 700, 3000, 100.0), (128, 64, 66, 2000, 30.0), (32, 33, 600, 1000, -7.0),
+                                            (64, 64, 5000, 6000, 1000.0)])
+def test_subregions_of_points_with_an_offset(D, L, K, n, offset):
+    """Subregions by 8-bit rows, of unit vectors and of such with an offset that all have in common (the table's centre takes it
+    out), with a centroid and a point that are not finite: the lowest fp64 score of Eq. (7) within what fp32 can tell."""
+    print("case: subregions with an offset", D, L, K, n, offset, flush=True)
+    rng = np.random.default_rng(D + K)
+    C = rng.standard_normal((K, D))
+    C = (C / np.linalg.norm(C, axis=1, keepdims=True) + offset).astype(np.float32)
+    reg = np.sort(rng.integers(0, K - 1, n)).astype(np.int32)
+    x = (C[reg] + 0.065 * rng.standard_normal((n, D))).astype(np.float32)
+    nbr = np.stack([rng.permutation(np.delete(np.arange(K - 1), r) if r < K - 1 else np.arange(K - 1))[:L] for r in range(K)]).astype(np.int32)
+    cs = ((C[:, None].astype(np.float64) - C[nbr]) ** 2).sum(-1).astype(np.float32)
+    alpha = rng.uniform(0.05, 0.17, K).astype(np.float32)
+    C[K - 1] = np.inf                                          # nobody's region and nobody's neighbour
+    x[n // 2] = np.nan
+    d = ivf.IndexDesc(dev(C), dev(nbr), dev(alpha), dev(cs), None, M=8)
+    assert n * L >= 10 * K                                     # packed rows
+    _, sub, _, _, _, res = ivf.ivf_encode(d, dev(x), region_in=dev(reg), want_residual=True)
+    sub = sub.cpu().numpy()
+    x64, c64, a = x.astype(np.float64), C.astype(np.float64), alpha[reg].astype(np.float64)[:, None]
+    dxc = ((x64 - c64[reg]) ** 2).sum(-1)[:, None]
+    dxs = ((x64[:, None] - c64[nbr[reg]]) ** 2).sum(-1)
+    sc = a * dxs + (1 - a) * dxc - a * (1 - a) * cs[reg]
+    # encode_kernel's sums: (D / 16 + 12) u of a neighbour's distance, a few u of the score's terms
+    u = 2.0 ** -24
+    room = 2 * (a * (D / 16 + 12) * u * dxs.max(1, keepdims=True) + 8 * u * (dxc + a * dxs.max(1, keepdims=True) + cs[reg].max(1, keepdims=True)))
+    ok = np.arange(n) != n // 2
+    got = sc[np.arange(n), sub]
+    assert (got <= sc.min(1) + room[:, 0])[ok].all() and 0 <= sub[n // 2] < L
+
+
 @pytest.mark.parametrize("n,D,K", [(1, 1, 1), (2560, 64, 10), (2561, 64, 10), (5000, 65, 700), (999, 130, 1500), (300, 1024, 40), (4097, 96, 3)])
 def test_cluster_means_of_short_and_long_clusters(n, D, K):
     """Both kernels and the line between them (256 rows a cluster on average), clusters of none, one and many rows, columns
