@@ -169,77 +169,81 @@ struct ByteRow {
 };
 inline size_t byte_row_bytes(int Dp) { return Dp == 32 ? 64 : Dp == 128 ? 144 : 128; }   // of a row and what belongs to it
 
-// A point near the middle of the table, to which points and rows are taken: distances between them are the same, and an offset that all
-// have in common does not cost the 8 bits anything.  The mean of up to 256 rows (any point is right).
-constexpr int CENTRE_ROWS = 256;
-
-__global__ __launch_bounds__(1024) void table_centre_kernel(const float *__restrict__ X, int64_t n, int D, float *__restrict__ centre)
-{
-    __shared__ float part[8][128];
-    const int c = threadIdx.x & 127, g = threadIdx.x >> 7, rows = n < CENTRE_ROWS ? (int)n : CENTRE_ROWS;
-    const int64_t stride = n / rows;
-    float v[CENTRE_ROWS / 8], s = 0.f;
-#pragma unroll
-    for (int u = 0; u < CENTRE_ROWS / 8; ++u) {               // (every thread loads: all are on their way together)
-        const int i = g + 8 * u < rows ? g + 8 * u : 0;
-        v[u] = X[(int64_t)i * stride * D + (c < D ? c : 0)];
-    }
-#pragma unroll
-    for (int u = 0; u < CENTRE_ROWS / 8; ++u) {
-        const float w = g + 8 * u < rows ? v[u] * (1.f / CENTRE_ROWS) : 0.f;
-        s += fabsf(w) < INFINITY ? w : 0.f;
-    }
-    part[g][c] = s;
-    __syncthreads();
-    if (g) return;
-    for (int u = 1; u < 8; ++u) s += part[u][c];
-    s *= (float)CENTRE_ROWS / (float)rows;
-    centre[c] = c < D && fabsf(s) < INFINITY ? s : 0.f;
-}
+// The rows are taken as differences to a point near the middle of the table, like the points later: distances between them are the same, and
+// an offset that all have in common does not cost the 8 bits anything.  It is the mean of up to 16 rows (any point is right), which every
+// workgroup forms for itself, from the same numbers in the same order; the first writes it to `centre` (0 behind D).
+constexpr int CENTRE_ROWS = 16;
+constexpr int64_t BYTE_ROWS_GRID = 2048;
 
 template <int DP>
-__global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__restrict__ X, int64_t n, int D, const float *__restrict__ centre,
+__global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__restrict__ X, int64_t n, int D, float *__restrict__ centre,
                                                              uint8_t *__restrict__ rows, uint8_t *__restrict__ tails)
 {
     typedef ByteRow<DP> R;
     constexpr int PER = R::BYTES / 16, LIVE = DP / 16;        // 16 bytes a lane
-    const int64_t row = (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER;
+    __shared__ __attribute__((aligned(16))) float mid[2][128];
+    {
+        const int c = threadIdx.x & 127, g = threadIdx.x >> 7, many = n < CENTRE_ROWS ? (int)n : CENTRE_ROWS;
+        const int64_t stride = n / many;
+        float w[CENTRE_ROWS / 2], s = 0.f;
+#pragma unroll
+        for (int u = 0; u < CENTRE_ROWS / 2; ++u)             // (every thread loads: all are on their way together)
+            w[u] = X[(int64_t)(2 * u + g < many ? 2 * u + g : 0) * stride * D + (c < D ? c : 0)];
+#pragma unroll
+        for (int u = 0; u < CENTRE_ROWS / 2; ++u) {
+            const float t = c < D && 2 * u + g < many ? w[u] * (1.f / CENTRE_ROWS) : 0.f;
+            s += fabsf(t) < INFINITY ? t : 0.f;
+        }
+        mid[g][c] = s;
+        __syncthreads();
+        s = (mid[0][c] + mid[1][c]) * ((float)CENTRE_ROWS / (float)many);
+        s = fabsf(s) < INFINITY ? s : 0.f;
+        __syncthreads();
+        if (g == 0) {
+            mid[0][c] = s;
+            if (blockIdx.x == 0) centre[c] = s;
+        }
+        __syncthreads();
+    }
     const int lane = threadIdx.x % PER;
-    float v[16], big = 0.f, s2 = 0.f, d2 = 0.f;
+    for (int64_t row0 = (int64_t)blockIdx.x * (256 / PER); row0 < n; row0 += (int64_t)gridDim.x * (256 / PER)) {   // (uniform)
+        const int64_t row = row0 + threadIdx.x / PER;
+        float v[16], big = 0.f, s2 = 0.f, d2 = 0.f;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row < n && lane < LIVE && 16 * lane + 4 * u < D) w = *reinterpret_cast<const float4 *>(X + row * D + 16 * lane + 4 * u);   // (D is a multiple of 4)
-        const float4 m = lane < LIVE ? *reinterpret_cast<const float4 *>(centre + 16 * lane + 4 * u) : make_float4(0.f, 0.f, 0.f, 0.f);   // (0 behind D)
-        v[4 * u] = w.x - m.x; v[4 * u + 1] = w.y - m.y; v[4 * u + 2] = w.z - m.z; v[4 * u + 3] = w.w - m.w;
-        if (row >= n) v[4 * u] = v[4 * u + 1] = v[4 * u + 2] = v[4 * u + 3] = 0.f;
+        for (int u = 0; u < 4; ++u) {
+            float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (row < n && lane < LIVE && 16 * lane + 4 * u < D) w = *reinterpret_cast<const float4 *>(X + row * D + 16 * lane + 4 * u);   // (D is a multiple of 4)
+            const float4 m = lane < LIVE ? *reinterpret_cast<const float4 *>(&mid[0][16 * lane + 4 * u]) : make_float4(0.f, 0.f, 0.f, 0.f);   // (0 behind D)
+            v[4 * u] = w.x - m.x; v[4 * u + 1] = w.y - m.y; v[4 * u + 2] = w.z - m.z; v[4 * u + 3] = w.w - m.w;
+            if (row >= n) v[4 * u] = v[4 * u + 1] = v[4 * u + 2] = v[4 * u + 3] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            big = fmaxf(big, fabsf(v[i]));
+            s2 = fmaf(v[i], v[i], s2);
+        }
+#pragma unroll
+        for (int o = PER / 2; o > 0; o >>= 1) {
+            big = fmaxf(big, __shfl_xor(big, o, WAVE));
+            s2 += __shfl_xor(s2, o, WAVE);
+        }
+        const bool finite = s2 < INFINITY;
+        const float step = big * (1.f / 127.f), per = big > 0x1p-100f && finite ? 127.f / big : 0.f;
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float q = fminf(fmaxf(rintf((finite ? v[i] : 0.f) * per), -127.f), 127.f), d = fmaf(-q, step, v[i]);
+            d2 = fmaf(d, d, d2);
+            w[i >> 2] |= ((uint32_t)(int)q & 255u) << (8 * (i & 3));
+        }
+#pragma unroll
+        for (int o = PER / 2; o > 0; o >>= 1) d2 += __shfl_xor(d2, o, WAVE);
+        if (row >= n) continue;
+        if (lane < LIVE) *reinterpret_cast<uint4 *>(rows + row * R::BYTES + 16 * lane) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (lane == 0)
+            *reinterpret_cast<float4 *>(tails + row * R::TAIL_STRIDE) =
+                finite ? make_float4(step, s2, sqrtf(d2) * (1.f + 0x1p-10f), sqrtf(s2) * (1.f + 0x1p-10f)) : make_float4(0.f, INFINITY, INFINITY, INFINITY);
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        big = fmaxf(big, fabsf(v[i]));
-        s2 = fmaf(v[i], v[i], s2);
-    }
-#pragma unroll
-    for (int o = PER / 2; o > 0; o >>= 1) {
-        big = fmaxf(big, __shfl_xor(big, o, WAVE));
-        s2 += __shfl_xor(s2, o, WAVE);
-    }
-    const bool finite = s2 < INFINITY;
-    const float step = big * (1.f / 127.f), per = big > 0x1p-100f && finite ? 127.f / big : 0.f;
-    uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const float q = fminf(fmaxf(rintf((finite ? v[i] : 0.f) * per), -127.f), 127.f), d = fmaf(-q, step, v[i]);
-        d2 = fmaf(d, d, d2);
-        w[i >> 2] |= ((uint32_t)(int)q & 255u) << (8 * (i & 3));
-    }
-#pragma unroll
-    for (int o = PER / 2; o > 0; o >>= 1) d2 += __shfl_xor(d2, o, WAVE);
-    if (row >= n) return;
-    if (lane < LIVE) *reinterpret_cast<uint4 *>(rows + row * R::BYTES + 16 * lane) = make_uint4(w[0], w[1], w[2], w[3]);
-    if (lane == 0)
-        *reinterpret_cast<float4 *>(tails + row * R::TAIL_STRIDE) =
-            finite ? make_float4(step, s2, sqrtf(d2) * (1.f + 0x1p-10f), sqrtf(s2) * (1.f + 0x1p-10f)) : make_float4(0.f, INFINITY, INFINITY, INFINITY);
 }
 
 // Subregion, displacement and subcentroid (Eqs. (3), (4)) for packed dimensions up to 128 and L <= 64, one wavefront for

@@ -1752,9 +1752,8 @@ int pack_subregion_table(const ivf_index_desc *t, uint8_t *mem, SubregionTable &
     float *centre = reinterpret_cast<float *>(mem);
     mem += 128 * sizeof(float);
     uint8_t *tails = R::INSIDE ? mem + DP : mem + (size_t)t->K * R::BYTES;
-    table_centre_kernel<<<dim3(1), dim3(1024), 0, st>>>(t->centroids, t->K, t->D, centre);
-    LAUNCHCHK("table_centre_kernel");
-    pack_byte_rows_kernel<DP><<<dim3((unsigned)((t->K + per - 1) / per)), dim3(256), 0, st>>>(t->centroids, t->K, t->D, centre, mem, tails);
+    const int64_t grid = (t->K + per - 1) / per;
+    pack_byte_rows_kernel<DP><<<dim3((unsigned)(grid < BYTE_ROWS_GRID ? grid : BYTE_ROWS_GRID)), dim3(256), 0, st>>>(t->centroids, t->K, t->D, centre, mem, tails);
     LAUNCHCHK("pack_byte_rows_kernel");
     table.rows = mem;
     table.tails = tails;
