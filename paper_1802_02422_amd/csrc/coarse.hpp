@@ -1301,6 +1301,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         if (qok[i] && h == 0 && bound[i] > before[i]) atomicMax(&a.L[q0 + i * 32 + l32], float_key(bound[i]));
 }
 
+// What the passes of a chunk start from, in one launch: best[0 .. m-1] all ones, zero[0 .. n_zero-1] and count[0 .. n_count-1] zeros
+__global__ __launch_bounds__(256) void shortlist_clear_kernel(unsigned long long *__restrict__ best, int64_t m, unsigned long long *__restrict__ zero, int64_t n_zero,
+                                                              unsigned long long *__restrict__ count, int64_t n_count)
+{
+    const int64_t step = (int64_t)gridDim.x * 256, t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = t; i < m; i += step) best[i] = ~0ull;
+    for (int64_t i = t; i < n_zero; i += step) zero[i] = 0ull;
+    for (int64_t i = t; i < n_count; i += step) count[i] = 0ull;
+}
+
 // Bounds to start with where a centroid of every row is known that is likely near it (the nearest one of the last round of
 // k-means): L[q] = the lower end of its value, with its own lengths, as in shortlist_pairs_kernel.  A sweep that starts without
 // reports a row whenever a centroid is nearer than all before it, ln K times, and with 32 rows to a block nearly half of the blocks:

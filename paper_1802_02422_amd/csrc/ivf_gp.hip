@@ -1516,14 +1516,12 @@ struct ArgminCtx {
         shortlist_tiles_kernel<<<dim3((unsigned)tiles_c), dim3(128), 0, st>>>(clen, K, Dp, words, xw,
                                                                               start, tile);
         LAUNCHCHK("shortlist_tiles_kernel");
-        fill_u64_kernel<<<dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st>>>(best, m, ~0ull);
-        LAUNCHCHK("fill_u64_kernel");
-        // L and the numbers of pairs: 32-bit words, two per 64-bit fill; the counters likewise
+        // L and the numbers of pairs: 32-bit words, cleared two at a time
         n_pairs = L + (m + 1) / 2 * 2;
-        fill_u64_kernel<<<dim3((unsigned)((m + 1 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<unsigned long long *>(L), (m + 1) / 2 * 2, 0ull);
-        LAUNCHCHK("fill_u64_kernel");
-        fill_u64_kernel<<<dim3((N_COUNTS + 255) / 256), dim3(256), 0, st>>>(counts, N_COUNTS, 0ull);
-        LAUNCHCHK("fill_u64_kernel");
+        static_assert(N_COUNTS % 2 == 0, "whole words");
+        shortlist_clear_kernel<<<dim3((unsigned)((m + 1 + 255) / 256 + (N_COUNTS + 255) / 256)), dim3(256), 0, st>>>(
+            best, m, reinterpret_cast<unsigned long long *>(L), (m + 1) / 2 * 2, counts, N_COUNTS);
+        LAUNCHCHK("shortlist_clear_kernel");
         ShortlistArgs a;
         a.Qh = xh;
         a.qlen = xl;
