@@ -1813,12 +1813,15 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     if (t->rotation && t->pq_codebook && !fast)
         return fail(IVF_EINVAL, "a rotation in front of the PQ needs D/M in {4, 6, 8, 12, 16} and a codebook that fits LDS");
     // Subregions by 8-bit rows with a bound where the rows fit registers; reading the table to pack it costs as much as
-    // the fp32 rows of K / 6 points with 64 neighbours do more than the 8-bit ones.
-    const bool packed_rows_fit = packed_dim(t->D) <= 128 && t->L <= 64;
+    // the fp32 rows of K / 6 points with 64 neighbours do more than the 8-bit ones.  The table is allocated behind everything
+    // else: where there is no room for it, encode_kernel reads the fp32 rows.
+    const bool packs = packed_dim(t->D) <= 128 && t->L <= 64 && n * t->L >= 10 * t->K;
     auto prepare_table = [&]() -> int {
-        if (!packed_rows_fit || n * t->L < 10 * t->K) return IVF_OK;
+        if (!packs) return IVF_OK;
         const int dp = packed_dim(t->D);
-        HIPCHK(byte_mem.alloc(128 * sizeof(float) + (size_t)t->K * byte_row_bytes(dp)));
+        const hipError_t no_room = byte_mem.alloc(128 * sizeof(float) + (size_t)t->K * byte_row_bytes(dp));
+        if (no_room == hipErrorOutOfMemory) return IVF_OK;
+        HIPCHK(no_room);
         auto pack = dp == 32 ? &pack_subregion_table<32> : dp == 64 ? &pack_subregion_table<64> : dp == 96 ? &pack_subregion_table<96> : &pack_subregion_table<128>;
         return pack(t, static_cast<uint8_t *>(byte_mem.p), table, st);
     };
@@ -1845,11 +1848,10 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     DevTmp e, mu, erot, rt;
     RadixBufs rb;
     auto body = [&]() -> int {
-        int r3 = prepare_table();
-        if (r3) return r3;
         // regions found here come in the order of the points: sorted, the points of a region share its rows
-        const bool order = table.rows && !region_in && n >= 4 * t->K;
-        if (order && (r3 = rb.init(chunk))) return r3;
+        const bool order = packs && !region_in && n >= 4 * t->K;
+        int r3 = order ? rb.init(chunk) : IVF_OK;
+        if (r3) return r3;
         if (!out_residual) HIPCHK(e.alloc((size_t)chunk * D * sizeof(float)));
         HIPCHK(mu.alloc((size_t)chunk * D * sizeof(float)));
         if (t->rotation) {   // the PQ sees R (x - mu), the per-point constant is taken with R mu
@@ -1858,6 +1860,7 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
             transpose_square_kernel<<<dim3((unsigned)((D * D + 255) / 256)), dim3(256), 0, st>>>(t->rotation, D, static_cast<float *>(rt.p));
             LAUNCHCHK("transpose_square_kernel");
         }
+        if ((r3 = prepare_table())) return r3;
         float *muc = static_cast<float *>(mu.p);
         for (int64_t i0 = 0; i0 < n; i0 += chunk) {
             const int64_t m = n - i0 < chunk ? n - i0 : chunk;

@@ -367,6 +367,41 @@ def test_subregions_of_points_with_an_offset(D, L, K, n, offset):
     assert (got <= sc.min(1) + room[:, 0])[ok].all() and 0 <= sub[n // 2] < L
 
 
+@pytest.mark.parametrize("given,codes", [(True, False), (False, False), (False, True)])
+def test_no_memory_for_the_packed_table(given, codes):
+    """The table of 8-bit rows is given up where it finds no room beside what a call cannot do without; the results stay."""
+    from test_gpu_sparse import fill_memory, make
+    print("case: encoder, no memory for the packed table", given, codes, flush=True)
+    K, D, L, M = 1 << 18, 96, 64, 16
+    n = 10 * K // L + 9
+    table = K * 128                                           # bytes of the 8-bit rows
+    g = torch.Generator(device="cuda").manual_seed(5)
+    C = torch.randn(K, D, generator=g, device="cuda")
+    nbr = torch.randint(0, K, (K, L), generator=g, device="cuda", dtype=torch.int32)
+    cs = torch.rand(K, L, generator=g, device="cuda") * 2 * D
+    reg = torch.randint(0, K, (n,), generator=g, device="cuda", dtype=torch.int32)
+    x = C[reg.long()] + 0.3 * torch.randn(n, D, generator=g, device="cuda")
+    d = ivf.IndexDesc(C, nbr, torch.rand(K, generator=g, device="cuda"), cs, 0.3 * torch.randn(M, 256, D // M, generator=g, device="cuda") if codes else None, M=M,
+                      const_table=torch.linspace(-100, 100, 256, device="cuda") if codes else None)
+    give_back = lambda: ivf.ivf_free_index(make(1000, 32, 8, 8, 1, 1.0, 0.0)[0])   # what the library keeps for index-time calls
+    call = lambda: [v for v in ivf.ivf_encode(d, x, region_in=reg if given else None) if v is not None]
+    give_back()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    ref = call()
+    need = free - torch.cuda.mem_get_info()[0]
+    assert need >= table
+    give_back()
+    held = fill_memory(need - table // 2)
+    try:
+        got = call()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
 @pytest.mark.parametrize("n,D,K", [(1, 1, 1), (2560, 64, 10), (2561, 64, 10), (5000, 65, 700), (999, 130, 1500), (300, 1024, 40), (4097, 96, 3)])
 def test_cluster_means_of_short_and_long_clusters(n, D, K):
     """Both kernels and the line between them (256 rows a cluster on average), clusters of none, one and many rows, columns
