@@ -1079,6 +1079,17 @@ struct TileTwists {
 // 20 000 x 16 384 90 / 79, 100 000 x 1000 46 / 49, 100 000 x 16 384 407 / 340.
 inline bool sweep_wide(int64_t rows, int64_t K) { return rows > 2 * GT && (rows + GT - 1) / GT * ((K + GT - 1) / GT) >= 8192; }
 
+// ... of the nearest-centroid sweep, which deals its blocks of rows to the XCDs: an XCD gets up to ceil(rows / 2048) blocks of 256 or ceil(rows / 1024) of 128,
+// and where the latter is odd the former are half a block more.  That is more than the wide sweep gains while an XCD has few blocks and they have many
+// tiles to go through.  Whole calls of 96 dimensions, rows x centroids, us with two wavefronts to 64 rows / with one: 1000 x 2^20 527 / 634, 2000 x 2^20
+// 684 / 641, 2560 x 2^20 852 / 941, 1000 x 200 000 209 / 222, 3000 x 200 000 270 / 292, 3584 x 200 000 308 / 294, 5000 x 200 000 345 / 352, 7000 x 200 000 411 / 425,
+// 9000 x 200 000 498 / 483, 5000 x 131 072 274 / 280, 7000 x 131 072 327 / 323, 5000 x 100 000 257 / 256, 3000 x 65 536 176 / 178, 7000 x 65 536 230 / 224.
+inline bool shortlist_wide(int64_t rows, int64_t K)
+{
+    const int64_t each = (rows + N_XCD * GT - 1) / (N_XCD * GT);
+    return sweep_wide(rows, K) && !(each % 2 && each <= 7 && K >= 21000 * each);
+}
+
 template <int SH>
 struct SweepTile {
     float rows[SH * GT * ROWF];
@@ -1170,7 +1181,7 @@ __device__ __forceinline__ void sweep_tile(const SweepTile<SH> &buf, const gu32x
 
 // The same pass for SH = 1 .. 4 stages of 32 dimensions (packed dimension up to 128) as a sweep over `tiles_per_wg` centroid tiles.
 // JN = 4: a wavefront has 64 rows of its own and takes all of a tile with them, JN = 2: two wavefronts share 64 rows and take half
-// a tile each (sweep_wide).  The bound stays in registers over the sweep and reaches L[q] once.
+// a tile each (shortlist_wide).  The bound stays in registers over the sweep and reaches L[q] once.
 // The start values arrive in the accumulators' layout as the C operand of the first product, so that nothing but the
 // largest value of a lane is left to the vector units (8 instructions a block of 32 x 32 against 2 SH products of
 // 32 cycles); three wavefronts a SIMD cover the LDS and barrier latencies.  A report is kept short, since the other three

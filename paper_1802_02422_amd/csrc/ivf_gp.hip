@@ -1545,7 +1545,7 @@ struct ArgminCtx {
             seed_bounds_kernel<<<dim3((unsigned)((m + 63) / 64)), dim3(256), 0, st>>>(a, near + q0);
             LAUNCHCHK("seed_bounds_kernel");
         }
-        const bool wide = Dp <= 128 && sweep_wide(m, K);
+        const bool wide = Dp <= 128 && shortlist_wide(m, K);
         const int per_q = wide ? 2 * GT : GT;
         a.tiles_q = (int)((m + per_q - 1) / per_q);
         const int64_t tq8 = (int64_t)((a.tiles_q + N_XCD - 1) / N_XCD) * N_XCD;

@@ -240,10 +240,12 @@ def test_wide_rows_take_the_tile_kernel(D, K, nq):
     assert (gid == 0).all()
 
 
-@pytest.mark.parametrize("D,K,nq", [(96, 8191, 16_640), (96, 300, 350_000), (20, 40_001, 3400), (64, 16_385, 8193), (128, 8320, 16_129)])
+@pytest.mark.parametrize("D,K,nq", [(96, 8191, 16_640), (96, 300, 350_000), (20, 40_001, 3400), (64, 16_385, 8193), (128, 8320, 16_129),
+                                    (96, 140_001, 1000), (32, 66_000, 3000)])
 def test_rows_enough_for_a_wavefront_to_64(D, K, nq):
     """The sweep whose workgroups take 256 rows (from 8192 tiles of 128 x 128 on): partial last tiles of rows and centroids, a last
-    workgroup with rows for one wavefront, sweeps of odd and even numbers of tiles."""
+    workgroup with rows for one wavefront, sweeps of odd and even numbers of tiles.  The last two have tiles enough and stay with 128 rows
+    a workgroup, since 256 would leave some of the XCDs without."""
     print("case: wide sweep", D, K, nq, flush=True)
     assert -(-nq // 128) * -(-K // 128) >= 8192
     g = torch.Generator(device="cuda").manual_seed(D + K + nq)
