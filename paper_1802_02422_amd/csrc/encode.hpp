@@ -158,9 +158,9 @@ __global__ __launch_bounds__(64) void encode_kernel(
 }
 
 // The centroid table in 8 bits for subregion_kernel: row c is s - centre ~ step * q, q in -127 .. 127, step the 127th part of its largest
-// component, with its step, |s|^2, |ds| and |s| (ds: what the rounding left out) behind the components where a row of 128 bytes has
-// room for them, so that one line holds it all, and in an array of their own where 128 components fill it.  A row that is not finite:
-// zeros with infinite lengths.
+// component, with its step, |s|^2, |ds| and 2 <step q, ds> (ds: what the rounding left out) behind the components where a row of 128
+// bytes has room for them, so that one line holds it all, and in an array of their own where 128 components fill it.  A row that is not
+// finite: zeros with infinite lengths.
 template <int DP>   // packed dimension
 struct ByteRow {
     static constexpr bool INSIDE = DP < 128;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__rest
     const int lane = threadIdx.x % PER;
     for (int64_t row0 = (int64_t)blockIdx.x * (256 / PER); row0 < n; row0 += (int64_t)gridDim.x * (256 / PER)) {   // (uniform)
         const int64_t row = row0 + threadIdx.x / PER;
-        float v[16], big = 0.f, s2 = 0.f, d2 = 0.f;
+        float v[16], big = 0.f, s2 = 0.f, d2 = 0.f, qd = 0.f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -234,15 +234,19 @@ __global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__rest
         for (int i = 0; i < 16; ++i) {
             const float q = fminf(fmaxf(rintf((finite ? v[i] : 0.f) * per), -127.f), 127.f), d = fmaf(-q, step, v[i]);
             d2 = fmaf(d, d, d2);
+            qd = fmaf(q * step, d, qd);
             w[i >> 2] |= ((uint32_t)(int)q & 255u) << (8 * (i & 3));
         }
 #pragma unroll
-        for (int o = PER / 2; o > 0; o >>= 1) d2 += __shfl_xor(d2, o, WAVE);
+        for (int o = PER / 2; o > 0; o >>= 1) {
+            d2 += __shfl_xor(d2, o, WAVE);
+            qd += __shfl_xor(qd, o, WAVE);
+        }
         if (row >= n) continue;
         if (lane < LIVE) *reinterpret_cast<uint4 *>(rows + row * R::BYTES + 16 * lane) = make_uint4(w[0], w[1], w[2], w[3]);
         if (lane == 0)
             *reinterpret_cast<float4 *>(tails + row * R::TAIL_STRIDE) =
-                finite ? make_float4(step, s2, sqrtf(d2) * (1.f + 0x1p-10f), sqrtf(s2) * (1.f + 0x1p-10f)) : make_float4(0.f, INFINITY, INFINITY, INFINITY);
+                finite ? make_float4(step, s2, sqrtf(d2) * (1.f + 0x1p-10f), 2.f * qd) : make_float4(0.f, INFINITY, INFINITY, INFINITY);
     }
 }
 
@@ -252,15 +256,19 @@ __global__ __launch_bounds__(256) void pack_byte_rows_kernel(const float *__rest
 // the region stays the same: points in the order of their regions share the read.  Four lanes hold a row, 64 bytes of it
 // each load (a row a lane: 64 rows for 16 bytes each, 0.54 against 0.50 ms for 500 000 points on 65 536 regions);
 // neighbour 16 p + g is looked after by lane 4 g + p.  The point is taken in 15 bits, as two 8-bit halves, so that products are whole numbers
-// (v_dot4).  The score of Eq. (7) is then known to within
-//   err_l = 2 |a| e_l + roundings,  e_l = |dx| |s_l| + (|x| + |dx|) |ds_l| + k |x| |s_l|
-// (see the nearest-centroid shortlist), and only neighbours whose lower end does not exceed the smallest upper end are decided by the
+// (v_dot4).  With what all neighbours of a region share left out, the score of Eq. (7) is then known to within 2 |a| e_l and the
+// roundings of sums, |x - s_l|^2 being |s_l|^2 - 2 <x, q_l> with
+//   e_l = |dx| |x - q_l| + |x| |ds_l| + k |x| |s_l|,   or |s_l|^2 - 2 <q_l, ds_l> - 2 <x, q_l> with   e_l = (|dx| + |ds_l|) |x - q_l| + k |x| |s_l|
+// (q_l: the row as packed), whichever is smaller: the second where a point is nearer to its neighbours than to the table's middle, as in tables of
+// several groups far apart.  (500 000 points, 65 536 regions in 16 groups of width 1 with means of length 2, 4, 8, 16, us a call: 781, 913, 1452, 2123,
+// with the first alone 872, 1840, 2123, 2130, with fp16 rows 911, 982, 1199, 2704; of one group 755 either way.)
+// Only neighbours whose lower end does not exceed the smallest upper end are decided by the
 // fp32 differences, with encode_kernel's arithmetic: the same subregion.  A third of the points of unit vectors have several such; they
 // are put by and decided when the wavefront has been through its points, eight neighbours on their way at a time whatever point
 // they belong to (decided where they come up, with the loads and sums of one point behind those of another: 0.56 ms for
 // 500 000 points on 65 536 regions, 0.50 so, 0.445 with five wavefronts a SIMD).
-// With vectors that share an offset of 1 (10) in every component a call of 500 000 points on 65 536 regions takes 0.73 (0.72) ms, without the centre
-// 2.2 (2.2), where fp16 rows took 1.65 (3.0).
+// With vectors that share an offset of 1 (10) in every component such a call takes 0.73 (0.73) ms, without the centre 0.96 (2.16), with fp16
+// rows 1.46 (3.0); encode_kernel 1.63 whatever the vectors.
 // 2 * 10^6 points in region order (two a region), K = 2^20, L = 64, D = 96: 2.27 ms; with fp16 rows, two lines each, whose bound leaves
 // 1.1 of 64, 3.8; encode_kernel 7.3.
 // perm (may be NULL): the order in which the points are taken.
@@ -318,7 +326,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
     int64_t held = -1;                                          // region whose rows the lanes hold
     gu32x4 row[4][CH];                                           // [t]: of neighbour 16 t + lane / 4, chunks part, part + 4, ..
     float a = 0.f, cs = 0.f, c2 = 0.f;
-    float4 sl = make_float4(0.f, 0.f, 0.f, 0.f);                 // step, |s|^2, |ds|, |s|
+    float4 sl = make_float4(0.f, 0.f, 0.f, 0.f);                 // step, |s|^2, |ds|, 2 <q, ds>
     int32_t my_nbr = 0;
     for (int j = 0; j < cnt; ++j) {                             // (uniform)
         const int64_t r = __builtin_amdgcn_readlane(r_of, j);
@@ -388,14 +396,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
         const float dot = (float)(part & 2 ? (part & 1 ? ih[3] : ih[2]) : (part & 1 ? ih[1] : ih[0])) * (step * sl.x);
         // what all neighbours have in common is left out
         const float2 ql = make_float2(sqrtf(x2) * (1.f + 0x1p-10f), sqrtf(d2) * (1.f + 0x1p-10f));
-        const float s2 = sl.y;
-        const float h = fmaf(a, fmaf(-2.f, dot, s2), -a * (1.f - a) * cs);
+        const float s2 = sl.y, both = x2 + s2, len = __builtin_amdgcn_sqrtf(s2) * (1.f + 0x1p-10f);
+        // |x - q| or more, and which of the two forms has less left out
+        const float far2 = fmaf(-2.f, dot, both - sl.w) + fmaf(2.f * ql.y, len + sl.z, fmaf(0x1p-18f, both, 0x1p-120f));
+        const float far = __builtin_amdgcn_sqrtf(fmaxf(far2, 0.f)) * (1.f + 0x1p-10f);
+        const bool near = far < ql.x;
+        const float h = fmaf(a, fmaf(-2.f, dot, near ? s2 - sl.w : s2), -a * (1.f - a) * cs);
+        const float e = fmaf(ql.y, far, fmaf(near ? far : ql.x, sl.z, (float)(DP + 32) * 0x1p-24f * ql.x * len));
         // roundings: of the fp32 sum of differences, (D/16 + 12) 2^-24 of at most 2 (x2 + s2), and of the three-term score,
         // 2^-20 of the size of its terms (the scaling factor may be any number: none of them has to be small)
         const float aa = fabsf(a), ac = fabsf(1.f - a);
         // (and 2^-120 for values whose squares leave the range of fp32)
-        const float size = fmaf(aa, x2 + s2, fmaf(ac, x2 + c2, aa * ac * fabsf(cs)));
-        const float err = fmaf(2.f * aa, shortlist_eps(ql, sl.w, sl.z, DP), fmaf(aa * (float)(D / 16 + 12) * 0x1p-23f, x2 + s2, fmaf(0x1p-20f, size, 0x1p-120f)));
+        const float size = fmaf(aa, both, fmaf(ac, x2 + c2, aa * ac * fabsf(cs)));
+        const float err = fmaf(2.f * aa, e, fmaf(aa * (float)(D / 16 + 12) * 0x1p-23f, both, fmaf(0x1p-20f, size, 0x1p-120f)));
         float up = my_l < L ? h + err : INFINITY;
         up = wave_smallest(up);
         uint64_t todo = __ballot(my_l < L && !(h - err > up));
