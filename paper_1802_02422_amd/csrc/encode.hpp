@@ -395,7 +395,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
         }
         const float dot = (float)(part & 2 ? (part & 1 ? ih[3] : ih[2]) : (part & 1 ? ih[1] : ih[0])) * (step * sl.x);
         // what all neighbours have in common is left out
-        const float2 ql = make_float2(sqrtf(x2) * (1.f + 0x1p-10f), sqrtf(d2) * (1.f + 0x1p-10f));
+        // (the instruction alone: what it may be off, and for what is subnormal, is made room for)
+        const float2 ql = make_float2(__builtin_amdgcn_sqrtf(x2 + 0x1p-100f) * (1.f + 0x1p-10f), __builtin_amdgcn_sqrtf(d2 + 0x1p-100f) * (1.f + 0x1p-10f));
         const float s2 = sl.y, both = x2 + s2, len = __builtin_amdgcn_sqrtf(s2) * (1.f + 0x1p-10f);
         // |x - q| or more, and which of the two forms has less left out
         const float far2 = fmaf(-2.f, dot, both - sl.w) + fmaf(2.f * ql.y, len + sl.z, fmaf(0x1p-18f, both, 0x1p-120f));

@@ -67,7 +67,7 @@ def _scores(X, S, c, alpha, centre=None, near=True, ds=True, dx=True, qd=True, r
     u = big * F(1 / 16256)
     w = np.clip(np.rint(xc * (F(16256) / big)[:, None]), -16256, 16256)
     rest = _fma(-w, u[:, None], xc)
-    x2, xl, rl = (v[:, None] for v in (_sum2(xc), np.sqrt(_sum2(xc)) * F(1 + 2.0 ** -10), np.sqrt(_sum2(rest)) * F(1 + 2.0 ** -10)))
+    x2, xl, rl = (v[:, None] for v in (_sum2(xc), np.sqrt(_sum2(xc) + F(2.0 ** -100)) * F(1 + 2.0 ** -10), np.sqrt(_sum2(rest) + F(2.0 ** -100)) * F(1 + 2.0 ** -10)))
     if not ds:
         dl = dl * 0
     if not dx:
