@@ -1812,9 +1812,11 @@ extern "C" int ivf_encode(const ivf_index_desc *t, const float *x, int64_t n, co
     const bool fast = t->pq_codebook && cb_bytes <= 140 * 1024 && pq_width(ds);
     if (t->rotation && t->pq_codebook && !fast)
         return fail(IVF_EINVAL, "a rotation in front of the PQ needs D/M in {4, 6, 8, 12, 16} and a codebook that fits LDS");
-    // Subregions by 8-bit rows with a bound where the rows fit registers; reading the table to pack it costs as much as
-    // the fp32 rows of K / 6 points with 64 neighbours do more than the 8-bit ones.  The table is allocated behind everything
-    // else: where there is no room for it, encode_kernel reads the fp32 rows.
+    // Subregions by 8-bit rows with a bound where the rows fit registers and there are points enough to pay for packing the table.  Whole calls
+    // with given regions, 96 dimensions, us by fp32 / 8-bit rows: K = 2^20, L = 64, n L = 4 K 319 / 344, 6 K 444 / 419, 9 K 640 / 513; L = 16, 6 K 720 / 783,
+    // 9 K 1087 / 1053; L = 8, 6 K 1274 / 1278, 9 K 1904 / 1813.  On small tables the chain of 16 points that a wavefront takes one after the
+    // other is longer than the fp32 rows of so few: K = 65 536, L = 64, 9 K 108 / 130, L = 8, 9 K 155 / 172; K = 4096 80 / 110 at any of these.  The table is
+    // allocated behind everything else: where there is no room for it, encode_kernel reads the fp32 rows.
     const bool packs = packed_dim(t->D) <= 128 && t->L <= 64 && n * t->L >= 10 * t->K;
     auto prepare_table = [&]() -> int {
         if (!packs) return IVF_OK;
