@@ -213,9 +213,10 @@ __global__ __launch_bounds__(256) void segment_sum_kernel(const T *__restrict__ 
 // workgroup of 16 wavefronts where it has more, wavefront w taking rows 8 w .. 8 w + 7 of every 128.  Either way the sum is a
 // function of the member list alone.  An empty segment's mean is left alone.
 // segment_sum_kernel has 256 threads and a tree with 8 barriers for every 8 columns, most of them idle when a segment
-// has 30 rows (500 000 rows in 16 384 clusters, 96 columns: 0.77 ms a call, 0.09 so).  The bound is what a wavefront's chain
-// may take beside the rest: 64 steps of about a microsecond.  With 1 % (10, 60) of those rows in one cluster a call takes
-// 0.40 (2.1, 12) ms, with one wavefront for them 1.7 (15, 93), with segment_sum_kernel 0.77 (3.8, 22).
+// has 30 rows (500 000 rows in 16 384 clusters, 96 columns: 0.77 ms, 0.03 - 0.05 in both kernels here).  The bound is what a wavefront's
+// chain may take beside the rest: 32 steps of about a microsecond (1041 clusters of 480 rows 43 us, by workgroups 961 of 520 99 us; 4 us for the
+// kernel that has nothing to do).  With 1 % (10, 60) of those rows in one cluster the two take 0.21 (1.85, 10.8) ms; before the short
+// segments' 16 rows 0.29 (1.92, 11.0), with one wavefront for the long one 1.7 (15, 93), with segment_sum_kernel 0.77 (3.8, 22).
 constexpr uint32_t SHORT_SEGMENT = 512;
 
 // COLS: columns of a lane in a row, 2 where D is even.  A short segment's wavefront reads the numbers of its rows 64 at a time, ahead of the
@@ -266,6 +267,8 @@ __global__ __launch_bounds__(256) void short_segment_mean_kernel(const float *__
         for (int k = 0; k < COLS; ++k) mean[g * D + c + k] = (float)(sum[k] / (double)(e - b));
     }
 }
+
+// grid: (any, columns / 64); a workgroup looks through a share of the segments for the long ones, 64 at a time
 __global__ __launch_bounds__(1024) void long_segment_mean_kernel(const float *__restrict__ X, int D, const uint32_t *__restrict__ perm,
                                                                  const uint32_t *__restrict__ off, int64_t n_seg, float *__restrict__ mean)
 {
