@@ -339,17 +339,21 @@ def test_subregions_and_displacements(D, L, n, order, kind):
                                             (64, 64, 5000, 6000, 1000.0)])
 def test_subregions_of_points_with_an_offset(D, L, K, n, offset):
     """Subregions by 8-bit rows, of unit vectors and of such with an offset that all have in common (the table's centre takes it
-    out), with a centroid and a point that are not finite: the lowest fp64 score of Eq. (7) within what fp32 can tell."""
+    out), with a point and two centroids that are not finite: the lowest fp64 score of Eq. (7) within what fp32 can tell.  The two
+    centroids are nobody's region, but neighbours of many, and of the rows from which the centre is formed."""
     print("case: subregions with an offset", D, L, K, n, offset, flush=True)
     rng = np.random.default_rng(D + K)
     C = rng.standard_normal((K, D))
     C = (C / np.linalg.norm(C, axis=1, keepdims=True) + offset).astype(np.float32)
-    reg = np.sort(rng.integers(0, K - 1, n)).astype(np.int32)
+    bad = np.array([0, K // 16])
+    reg = np.sort(rng.choice(np.setdiff1d(np.arange(K), bad), n)).astype(np.int32)
     x = (C[reg] + 0.065 * rng.standard_normal((n, D))).astype(np.float32)
-    nbr = np.stack([rng.permutation(np.delete(np.arange(K - 1), r) if r < K - 1 else np.arange(K - 1))[:L] for r in range(K)]).astype(np.int32)
+    nbr = np.stack([rng.permutation(np.delete(np.arange(K), r))[:L] for r in range(K)]).astype(np.int32)
     cs = ((C[:, None].astype(np.float64) - C[nbr]) ** 2).sum(-1).astype(np.float32)
     alpha = rng.uniform(0.05, 0.17, K).astype(np.float32)
-    C[K - 1] = np.inf                                          # nobody's region and nobody's neighbour
+    C[0, 1], C[K // 16, D - 1] = np.nan, np.inf
+    lost = np.isin(nbr[reg], bad)
+    assert lost.any(1).sum() > n * L // K and not lost.all(1).any()   # (2 n L / K points have one of the two, within a tenth)
     x[n // 2] = np.nan
     d = ivf.IndexDesc(dev(C), dev(nbr), dev(alpha), dev(cs), None, M=8)
     assert n * L >= 10 * K                                     # packed rows
@@ -357,14 +361,58 @@ def test_subregions_of_points_with_an_offset(D, L, K, n, offset):
     sub = sub.cpu().numpy()
     x64, c64, a = x.astype(np.float64), C.astype(np.float64), alpha[reg].astype(np.float64)[:, None]
     dxc = ((x64 - c64[reg]) ** 2).sum(-1)[:, None]
-    dxs = ((x64[:, None] - c64[nbr[reg]]) ** 2).sum(-1)
-    sc = a * dxs + (1 - a) * dxc - a * (1 - a) * cs[reg]
+    dxs = np.where(lost, 0, ((x64[:, None] - c64[nbr[reg]]) ** 2).sum(-1))
+    sc = np.where(lost, np.inf, a * dxs + (1 - a) * dxc - a * (1 - a) * cs[reg])
     # encode_kernel's sums: (D / 16 + 12) u of a neighbour's distance, a few u of the score's terms
     u = 2.0 ** -24
     room = 2 * (a * (D / 16 + 12) * u * dxs.max(1, keepdims=True) + 8 * u * (dxc + a * dxs.max(1, keepdims=True) + cs[reg].max(1, keepdims=True)))
     ok = np.arange(n) != n // 2
     got = sc[np.arange(n), sub]
     assert (got <= sc.min(1) + room[:, 0])[ok].all() and 0 <= sub[n // 2] < L
+
+
+@pytest.mark.parametrize("D,L,kind", [(96, 64, "unit"), (96, 64, "groups"), (128, 64, "groups"), (32, 33, "equal"), (64, 64, "near"), (24, 8, "lost"),
+                                      (96, 64, "lost"), (104, 17, "whole")])
+@pytest.mark.parametrize("codes", [False, True])
+def test_subregions_are_those_of_the_fp32_rows(D, L, kind, codes):
+    """A call with points enough for the table of 8-bit rows against calls with fewer, which read the fp32 rows: the same
+    subregions, displacements and codes, bit for bit.  Groups of centroids far from the table's middle, neighbours that are equal or nearly
+    so, whole numbers with many equal scores, rows and points that are not finite."""
+    print("case: subregions against the fp32 rows", D, L, kind, codes, flush=True)
+    rng = np.random.default_rng(D + L)
+    K, n, M = 640, 5003, 8 if D < 64 else 16
+    if D // M not in (4, 6, 8) or D % M:
+        M, codes = 8, False
+    C = rng.standard_normal((K, D))
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    if kind == "groups":
+        m = rng.standard_normal((8, D))
+        C += 5 * (m / np.linalg.norm(m, axis=1, keepdims=True))[np.arange(K) % 8]
+    if kind == "equal":
+        C = C[np.arange(K) // 8]
+    if kind == "near":
+        C = C[:1] + 2.0 ** -7 * C
+    if kind == "whole":
+        C = rng.integers(-2, 3, (K, D))
+    nbr = np.stack([8 * rng.permutation(K // 8)[:L] + r % 8 if kind == "groups" else rng.permutation(K)[:L] for r in range(K)]).astype(np.int32)
+    cs = ((C[:, None] - C[nbr]) ** 2).sum(-1).astype(np.float32)
+    alpha = np.full(K, 0.25) if kind == "whole" else rng.uniform(-0.2, 1.2, K)
+    reg = rng.integers(0, K, n).astype(np.int32)
+    x = C[reg] + (rng.integers(-1, 2, (n, D)) if kind == "whole" else (2.0 ** -7 if kind == "near" else 1) * 0.065 * rng.standard_normal((n, D)))
+    C, x = C.astype(np.float32), x.astype(np.float32)
+    if kind == "lost":
+        C[0, 0], C[40, 1], C[99] = np.nan, np.inf, -np.inf
+        x[5], x[17, 3], x[18, D - 1] = np.nan, np.inf, -np.inf
+        C[7], x[40] = 3e19, -3e19                               # squares that leave the range of fp32
+    cb = (0.05 * rng.standard_normal((M, 256, D // M))).astype(np.float32)
+    d = ivf.IndexDesc(dev(C), dev(nbr), dev(alpha.astype(np.float32)), dev(cs), dev(cb) if codes else None, M=M)
+    few = (10 * K - 1) // L
+    assert n * L >= 10 * K > few * L
+    words = lambda a, b: [v if v.dtype != torch.float32 else v.view(torch.int32)
+                          for v in ivf.ivf_encode(d, dev(x[a:b]), region_in=dev(reg[a:b]), want_t=codes, want_residual=True) if v is not None]
+    got, parts = words(0, n), [words(a, min(n, a + few)) for a in range(0, n, few)]
+    for v, *w in zip(got, *parts):
+        assert torch.equal(v, torch.cat(w))
 
 
 @pytest.mark.parametrize("given,codes", [(True, False), (False, False), (False, True)])
@@ -400,6 +448,36 @@ def test_no_memory_for_the_packed_table(given, codes):
         del held
         torch.cuda.empty_cache()
     assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+@pytest.mark.parametrize("n,D,K,iters,kind", [(20_000, 96, 700, 5, "groups"), (20_000, 96, 700, 4, "tight"), (6000, 160, 300, 4, "lost"), (1500, 64, 1500, 3, "plain"),
+                                              ((1 << 20) + 3001, 8, 63, 3, "lost")])
+def test_rounds_that_start_from_the_round_before(n, D, K, iters, kind):
+    """Rounds of k-means, whose bounds start from the last round's nearest centroids and which leave a row's only candidate
+    undecided, against the nearest centroids with their distances and the means, called one after the other: the same centroids, bit
+    for bit.  Both sweeps (D = 160: wide rows), several chunks of rows, rows with many candidates ("tight"), rows that are not finite and have
+    no centroid, centroids that start equal."""
+    print("case: k-means from bounds", n, D, K, iters, kind, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n + D)
+    m = torch.randn(K, D, generator=g, device="cuda")
+    if kind == "tight":
+        m = m[:1] + 2.0 ** -9 * m
+    x = m[torch.randint(0, K, (n,), generator=g, device="cuda")] + (2.0 ** -10 if kind == "tight" else 0.7) * torch.randn(n, D, generator=g, device="cuda")
+    init = torch.randperm(n, generator=g, device="cuda")[:K].contiguous()
+    if kind == "lost":
+        rows = torch.tensor([0, 77, n // 2, n - 1], device="cuda")
+        rows = rows[~torch.isin(rows, init)]
+        x[rows[:2], 1], x[rows[2:], D - 1] = float("nan"), float("inf")
+    elif kind != "tight":
+        x[init[1]] = x[init[0]]
+    c = x[init].contiguous()
+    for _ in range(iters):
+        near, d = ivf.ivf_coarse_topk(c, x, 1)
+        c = ivf.ivf_cluster_means(x, near[:, 0].contiguous(), c.clone())
+    plain = ivf.ivf_kmeans(x, K, iters, init)
+    with_sums, _ = ivf.ivf_kmeans(x, K, iters, init, want_objective=True)
+    assert torch.isfinite(c).all()
+    assert torch.equal(plain, c) and torch.equal(with_sums, c)
 
 
 @pytest.mark.parametrize("n,D,K", [(1, 1, 1), (2560, 64, 10), (2561, 64, 10), (5000, 65, 700), (999, 130, 1500), (300, 1024, 40), (4097, 96, 3)])
