@@ -474,7 +474,11 @@ def test_rounds_that_start_from_the_round_before(n, D, K, iters, kind):
     for _ in range(iters):
         near, d = ivf.ivf_coarse_topk(c, x, 1)
         c = ivf.ivf_cluster_means(x, near[:, 0].contiguous(), c.clone())
+    before = ivf.ivf_assign_stats()
     plain = ivf.ivf_kmeans(x, K, iters, init)
+    after = ivf.ivf_assign_stats()
+    if kind != "tight":                                        # (whose lists may overflow)
+        assert after[0] - before[0] == iters * (2 if n > 1 << 20 else 1) and after[1] == before[1]
     with_sums, _ = ivf.ivf_kmeans(x, K, iters, init, want_objective=True)
     assert torch.isfinite(c).all()
     assert torch.equal(plain, c) and torch.equal(with_sums, c)
