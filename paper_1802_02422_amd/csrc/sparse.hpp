@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
 }
 
-// The same for few queries (sweep_wide), where the table's bytes are what it takes: 128 queries a workgroup, a wavefront with 64 of them and half a
+// The same for up to 256 queries and below 8192 tiles (sweep_wide), where the table's bytes are what it takes: 128 queries a workgroup, a wavefront with 64 of them and half a
 // tile, every fragment waited for where it is read.  One query on 2^20, 96 dimensions: 36 us (5.6 TB/s), 64 queries 46; with sweep_tile 38 and
 // 48.5, whichever number of tiles a workgroup takes.
 template <int SH>
